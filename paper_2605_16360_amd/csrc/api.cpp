@@ -78,35 +78,45 @@ int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) 
 
 struct Sizes {
   size_t neg_lse, x_ws, yhat_ws, h1, x, xb, qk, vt, ao, hid, zg, s3, range;
-  size_t mapper() const { return h1 + x + xb + qk + vt + ao + hid + zg + s3 + range; }  // one lane's activations
+  size_t mapper() const { return h1 + x + xb + qk + vt + ao + hid + zg + s3 + range; }  // one batch's activations
   size_t total() const { return neg_lse + x_ws + yhat_ws + mapper(); }
 };
 
-Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q) {
+Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q, int distinct_layers) {
   Sizes s;
-  int64_t n_win, T;
-  pkv::window_plan(N, c.win, c.stride, &n_win, &T);
+  const pkv::MapPlan p = pkv::map_plan(c, N, distinct_layers);
   // rows of GEMM outputs (and of the residuals they read) are padded to the GEMM's 256-row tile
-  const size_t Tp = ((size_t)T + 255) / 256 * 256, Np = (size_t)N, Npad = (Np + 255) / 256 * 256, dt = (size_t)c.d_time;
+  const size_t b = (size_t)p.batch, Tp = b * (size_t)p.Tp, Np = b * (size_t)p.Np, dt = (size_t)c.d_time;
   s.neg_lse = (size_t)c.L_s * c.H_q * (size_t)N_q * 4;
-  s.x_ws = (size_t)c.L_s * c.H_kv * Np * 4;
-  s.yhat_ws = (size_t)c.L_l * c.H_l * Np * 4;
-  s.h1 = (Np + 2) * (size_t)c.c_mid * 2;
+  s.x_ws = (size_t)c.L_s * c.H_kv * (size_t)N * 4;
+  s.yhat_ws = (size_t)c.L_l * c.H_l * (size_t)N * 4;
+  s.h1 = b * ((size_t)N + 2) * (size_t)c.c_mid * 2;
   s.x = Tp * dt * 4;
   s.xb = Tp * dt * 2;
   s.qk = Tp * 2 * dt * 2;
-  s.vt = (size_t)n_win * dt * (size_t)c.win * 2;
+  s.vt = b * (size_t)p.n_win * dt * (size_t)p.vt_ld * 2;
   s.ao = Tp * dt * 2;
   s.hid = Tp * (size_t)c.d_ffn * 2;
   s.zg = Np * dt * 2;
-  s.s3 = Npad * (size_t)(c.H_l + 1) * (size_t)c.H_kv * 4;
-  s.range = 256;
+  s.s3 = Np * (size_t)(c.H_l + 1) * (size_t)c.H_kv * 4;
+  s.range = pkv::kMaxBatch * 64;
   return s;
+}
+
+// number of distinct proxy layers that the target layers are paired with
+int count_distinct(const proxykv_config& c) {
+  int distinct = 0, prev = -1;
+  for (int ll = 0; ll < c.L_l; ++ll) {
+    const int ls = (int)(((int64_t)(ll + 1) * c.L_s + c.L_l - 1) / c.L_l - 1);
+    distinct += ls != prev;
+    prev = ls;
+  }
+  return distinct;
 }
 
 int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool map_part, bool prune_part,
                 hipStream_t stream) {
-  const Sizes s = workspace_sizes(ctx->cfg, N, N_q);
+  const Sizes s = workspace_sizes(ctx->cfg, N, N_q, ctx->distinct_layers);
   int rc = PROXYKV_OK;
   if (score_part && (rc = ensure(ctx, ctx->neg_lse, s.neg_lse, stream))) return rc;
   if (prune_part) {
@@ -115,19 +125,7 @@ int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool 
     if ((rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes((int64_t)ctx->cfg.L_l * ctx->cfg.H_l, N), stream))) return rc;
   }
   if (map_part) {
-    int64_t n_win, T;
-    pkv::window_plan(N, ctx->cfg.win, ctx->cfg.stride, &n_win, &T);
-    const int lanes = pkv::map_lanes(T, ctx->distinct_layers);
-    if (lanes > 1 && !ctx->lanes_created) {
-      for (int i = 1; i < pkv::kMapLanes; ++i) {
-        PKV_HIP(ctx, hipStreamCreateWithFlags(&ctx->lane_stream[i], hipStreamNonBlocking));
-        PKV_HIP(ctx, hipEventCreateWithFlags(&ctx->lane_join[i], hipEventDisableTiming));
-      }
-      PKV_HIP(ctx, hipEventCreateWithFlags(&ctx->lane_fork, hipEventDisableTiming));
-      ctx->lanes_created = true;
-    }
-   for (int lane = 0; lane < lanes; ++lane) {
-    pkv::MapperWorkspace& m = ctx->m[lane];
+    pkv::MapperWorkspace& m = ctx->m;
     if ((rc = ensure(ctx, m.h1, s.h1, stream))) return rc;
     if ((rc = ensure(ctx, m.x, s.x, stream))) return rc;
     if ((rc = ensure(ctx, m.xb, s.xb, stream))) return rc;
@@ -138,7 +136,6 @@ int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool 
     if ((rc = ensure(ctx, m.zg, s.zg, stream))) return rc;
     if ((rc = ensure(ctx, m.s3, s.s3, stream))) return rc;
     if ((rc = ensure(ctx, m.range, s.range, stream))) return rc;
-   }
   }
   return rc;
 }
@@ -290,8 +287,7 @@ int proxykv_create(proxykv_ctx** out, const proxykv_config* cfg) {
   ctx->pairing.resize(cfg->L_l);
   for (int ll = 0; ll < cfg->L_l; ++ll)
     ctx->pairing[ll] = (int32_t)(((int64_t)(ll + 1) * cfg->L_s + cfg->L_l - 1) / cfg->L_l - 1);
-  ctx->distinct_layers = 0;
-  for (int ll = 0; ll < cfg->L_l; ++ll) ctx->distinct_layers += (ll == 0 || ctx->pairing[ll] != ctx->pairing[ll - 1]);
+  ctx->distinct_layers = count_distinct(*cfg);
   *out = ctx;
   return PROXYKV_OK;
 }
@@ -300,9 +296,9 @@ int proxykv_destroy(proxykv_ctx* ctx) {
   if (!ctx) return PROXYKV_OK;
   std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
                                     &ctx->neg_lse,     &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws};
-  for (pkv::MapperWorkspace& m : ctx->m)
-    for (DeviceBuffer* b : {&m.h1, &m.x, &m.xb, &m.qk, &m.vt, &m.ao, &m.hid, &m.zg, &m.s3, &m.range}) all.push_back(b);
-  bool any = ctx->ev_created || ctx->lanes_created;
+  pkv::MapperWorkspace& m = ctx->m;
+  for (DeviceBuffer* b : {&m.h1, &m.x, &m.xb, &m.qk, &m.vt, &m.ao, &m.hid, &m.zg, &m.s3, &m.range}) all.push_back(b);
+  bool any = ctx->ev_created;
   for (DeviceBuffer* b : all) any = any || b->ptr;
   if (any) {
     (void)hipSetDevice(ctx->cfg.device);
@@ -310,13 +306,6 @@ int proxykv_destroy(proxykv_ctx* ctx) {
     for (DeviceBuffer* b : all) free_buffer(*b);
     if (ctx->ev_created)
       for (int i = 0; i < PROXYKV_N_STAGES + 1; ++i) (void)hipEventDestroy(ctx->ev[i]);
-    if (ctx->lanes_created) {
-      for (int i = 1; i < pkv::kMapLanes; ++i) {
-        if (ctx->lane_stream[i]) (void)hipStreamDestroy(ctx->lane_stream[i]);
-        if (ctx->lane_join[i]) (void)hipEventDestroy(ctx->lane_join[i]);
-      }
-      if (ctx->lane_fork) (void)hipEventDestroy(ctx->lane_fork);
-    }
   }
   delete ctx;
   return PROXYKV_OK;
@@ -465,16 +454,7 @@ int proxykv_workspace_bytes(const proxykv_config* cfg, int64_t N, int64_t N_q, s
   int rc = validate_config(cfg);
   if (rc) return rc;
   if ((rc = validate_lengths(N, N_q, 1))) return rc;
-  const Sizes s = workspace_sizes(*cfg, N, N_q);
-  int64_t n_win, T;
-  pkv::window_plan(N, cfg->win, cfg->stride, &n_win, &T);
-  int distinct = 0, prev = -1;
-  for (int ll = 0; ll < cfg->L_l; ++ll) {
-    const int ls = (int)(((int64_t)(ll + 1) * cfg->L_s + cfg->L_l - 1) / cfg->L_l - 1);
-    distinct += ls != prev;
-    prev = ls;
-  }
-  *out_bytes = s.total() + (size_t)(pkv::map_lanes(T, distinct) - 1) * s.mapper();
+  *out_bytes = workspace_sizes(*cfg, N, N_q, count_distinct(*cfg)).total();
   return PROXYKV_OK;
 }
 

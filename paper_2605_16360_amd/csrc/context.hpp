@@ -4,7 +4,6 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 #include <stdint.h>
-#include <stdlib.h>
 
 #include <vector>
 
@@ -46,38 +45,23 @@ struct MapperWeights {
   const float* pe;                       // fp32 [win, d_time] sinusoidal table
 };
 
-// Mapper activations for ONE proxy layer (the network runs once per distinct proxy layer).
 // Row length of the stage-3 K/V projection's output: 2*H_kv*d_head_x rounded up to the GEMM's column tile.
 inline int kv3_stride(const proxykv_config& c) { return (2 * c.H_kv * c.d_head_x + 255) / 256 * 256; }
 
-// Distinct proxy layers are independent, so kMapLanes of them run side by side, each on a stream ("lane") and in a
-// workspace of its own; lane 0 is the caller's stream.  Short contexts leave most of the chip idle inside one layer's
-// kernels (at N = 8192 a layer is 14 336 window rows: 112 output tiles for 256 CUs; 26.7 ms with one lane, 20.3 ms
-// with four); at long ones a layer's kernels fill the chip and the lanes only close the gaps at kernel boundaries
-// (N = 32 768: 88.6, 86.7, 85.8, 85.2 ms with one to four lanes).
-// The environment variable PROXYKV_MAP_LANES (1 .. kMapLanes) overrides the choice, for measurements.
-constexpr int kMapLanes = 4;
-inline int map_lanes(int64_t window_rows, int distinct_layers) {
-  (void)window_rows;
-  int lanes = kMapLanes;
-  if (const char* env = getenv("PROXYKV_MAP_LANES")) {
-    const int v = atoi(env);
-    if (v >= 1 && v <= kMapLanes) lanes = v;
-  }
-  return lanes < distinct_layers ? lanes : (distinct_layers > 0 ? distinct_layers : 1);
-}
-
+// Mapper activations for one batch of proxy layers (the network runs once per distinct proxy layer, and its weights are
+// shared by all of them, so a batch's layers lie one behind the other on the M axis of every launch).
 struct MapperWorkspace {
+  // per layer of the batch:
   DeviceBuffer h1;       // fp16 [(N+2), c_mid]  stem conv1 output with one zero row at each end
-  DeviceBuffer x;        // fp32 [T, d_time]     residual stream over all window rows
-  DeviceBuffer xb;       // fp16 [T, d_time]     fp16 copy feeding the GEMMs
-  DeviceBuffer qk;       // fp16 [T, 2*d_time]   q and k of the current layer
-  DeviceBuffer vt;       // fp16 [n_win, heads, 64, win]  v transposed per window and head
-  DeviceBuffer ao;       // fp16 [T, d_time]     attention output
-  DeviceBuffer hid;      // fp16 [T, d_ffn]
-  DeviceBuffer zg;       // fp16 [N, d_time]     overlap-averaged encoder output
-  DeviceBuffer s3;       // fp32 [N, (H_l + 1) * H_s]  stage 3: per token the H_l x H_s logits, then <w_o, V[s]> of every slot
-  DeviceBuffer range;    // 3 words: largest |score| of the layer (bits), 2^-s and 2^s of the stem's range exponent
+  DeviceBuffer x;        // fp32 [Tp, d_time]    residual stream over all window rows
+  DeviceBuffer xb;       // fp16 [Tp, d_time]    fp16 copy feeding the GEMMs
+  DeviceBuffer qk;       // fp16 [Tp, 2*d_time]  q and k of the current layer
+  DeviceBuffer vt;       // fp16 [n_win, heads, 64, vt_ld]  v transposed per window and head
+  DeviceBuffer ao;       // fp16 [Tp, d_time]    attention output
+  DeviceBuffer hid;      // fp16 [Tp, d_ffn]
+  DeviceBuffer zg;       // fp16 [Np, d_time]    overlap-averaged encoder output
+  DeviceBuffer s3;       // fp32 [Np, (H_l + 1) * H_s]  stage 3: per token the H_l x H_s logits, then <w_o, V[s]> of every slot
+  DeviceBuffer range;    // 3 of 16 words: largest |score| of the layer (bits), 2^-s and 2^s of the stem's range exponent
 };
 
 }  // namespace pkv
@@ -100,12 +84,7 @@ struct proxykv_ctx {
   pkv::DeviceBuffer yhat_ws;                       // fp32 [L_l, H_l, N]
   pkv::DeviceBuffer topk_ws;                       // per-row histograms and counters of the Top-K of rows split over workgroups
   bool fused_select = false;                       // proxykv_prune: selection and gather in one launch (measured slower)
-  pkv::MapperWorkspace m[pkv::kMapLanes];          // one per lane; only the lanes a length needs are allocated
-  // lanes 1 .. kMapLanes-1: streams (default priority, non-blocking) and the events that fork them from and join
-  // them into the caller's stream
-  bool lanes_created = false;
-  hipStream_t lane_stream[pkv::kMapLanes] = {};
-  hipEvent_t lane_fork = nullptr, lane_join[pkv::kMapLanes] = {};
+  pkv::MapperWorkspace m;
   int distinct_layers = 1;                         // distinct proxy layers in `pairing`
 };
 
@@ -121,6 +100,32 @@ inline void window_plan(int64_t N, int win, int stride, int64_t* n_win, int64_t*
   const int64_t k = (N - win + stride - 1) / stride + 1;
   *n_win = k;
   *total_rows = (k - 1) * (int64_t)win + (N - (k - 1) * (int64_t)stride);
+}
+
+// How the mapper runs a context of N tokens: `batch` distinct proxy layers at a time.
+// Small layers leave the chip idle one by one (512 window rows are 12 output tiles of the QKV product), so a batch takes
+// as many of them as make kMapBatchRows rows; a layer of 32 768 tokens has 63 488 rows, four of them make a batch, and
+// more would not make the kernels faster, only the workspace larger (about 14 KB per row).  Measured, 16 distinct
+// layers, layers on four streams against batches: N = 1500 6.15 -> 2.21 ms, N = 8192 20.2 -> 18.9 ms, N = 32 768 the same.
+constexpr int64_t kMapBatchRows = 262144;
+constexpr int kMaxBatch = 32;
+struct MapPlan {
+  int64_t n_win, T;   // windows and window rows of a layer
+  int64_t Tp, Np;     // window rows and tokens of a layer, padded to the GEMM's 256-row tile
+  int64_t vt_ld;      // row length of the transposed v
+  int batch;
+};
+inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers) {
+  MapPlan p;
+  window_plan(N, c.win, c.stride, &p.n_win, &p.T);
+  p.Tp = (p.T + 255) / 256 * 256;
+  p.Np = (N + 255) / 256 * 256;
+  p.vt_ld = p.n_win > 1 ? c.win : p.Tp;
+  int64_t cap = kMapBatchRows / p.Tp;
+  cap = cap < 1 ? 1 : (cap > kMaxBatch ? kMaxBatch : cap);
+  const int64_t n_batches = (distinct_layers + cap - 1) / cap;
+  p.batch = (int)((distinct_layers + n_batches - 1) / n_batches);
+  return p;
 }
 
 // Runs the mapper for every distinct proxy layer; implemented in mapper.hip.

@@ -1,11 +1,11 @@
-// HybridAxialMapper forward (paper Sec. 4.1) for one proxy layer at a time:
+// HybridAxialMapper forward (paper Sec. 4.1) for a batch of proxy layers at a time:
 //   stage 1  conv stem            stem_conv1_kernel (fp32 ALU) + conv 2 as an fp16 MFMA GEMM whose A rows
 //                                 are overlapping 3-token spans of the padded conv-1 output
-//   stage 2  time-axis encoder    gather_pe_kernel, then per layer: QKV GEMM (writes q, k row-major and v transposed
+//   stage 2  time-axis encoder    per encoder layer: QKV GEMM (writes q, k row-major and v transposed
 //                                 for the attention's second product) -> window attention -> out-proj GEMM whose
 //                                 epilogue adds the residual and normalises the row -> FFN-1 GEMM -> FFN-2 GEMM
-//                                 with the same epilogue; all sliding windows of the layer are batched along the
-//                                 GEMM M axis
+//                                 with the same epilogue; all sliding windows of all proxy layers of the batch lie
+//                                 on the GEMM M axis
 //            overlap averaging    overlap_avg_kernel
 //   stage 3  head-axis attention  K/V projection GEMM (inner products with queries / output weights in its epilogue)
 //                                  + stage3_kernel (softmax over the slots per token and head, fp32 ALU)
@@ -26,6 +26,13 @@ constexpr int kDT = 512;    // d_time
 constexpr int kWin = 2048;  // window length
 constexpr int kStride = 1024;
 constexpr int kHeads = 8;   // encoder heads, 64 wide
+constexpr int kRangeWords = 16;  // words between the range slots of two layers of a batch
+
+// The distinct proxy layers that one batch of launches handles, and the target layers lo .. hi-1 that each serves.
+struct LayerBatch {
+  int n;
+  int ls[kMaxBatch], lo[kMaxBatch], hi[kMaxBatch];
+};
 
 __device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
 
@@ -43,7 +50,10 @@ __device__ __forceinline__ int swz8(int row) { return (row & 7) ^ ((row >> 3) & 
 // the exponent moves.  s = 0 (nothing changes) whenever the bound below stays under 2^15.
 //   slot[0]: bits of max |x| (atomicMax, cleared again by stem_scale_kernel), slot[1] = 2^-s, slot[2] = 2^s (floats)
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x, int64_t n, uint32_t* __restrict__ slot) {
+__global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x, int64_t n, LayerBatch lb,
+                                                     uint32_t* __restrict__ slots) {
+  x += (size_t)lb.ls[blockIdx.y] * n;
+  uint32_t* slot = slots + blockIdx.y * kRangeWords;
   uint32_t m = 0;
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
     const uint32_t a = __float_as_uint(x[i]) & 0x7fffffffu;
@@ -58,8 +68,9 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x
 }
 
 // |h1| <= |scale_c| * sum |w_c| * max|x| + |shift_c| <= cw * max|x| + cs  (|GELU(y)| <= |y|)
-__global__ void stem_scale_kernel(uint32_t* __restrict__ slot, float cw, float cs) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+__global__ void stem_scale_kernel(uint32_t* __restrict__ slots, int n_layers, float cw, float cs) {
+  if ((int)threadIdx.x >= n_layers || blockIdx.x != 0) return;
+  uint32_t* slot = slots + threadIdx.x * kRangeWords;
   const float bound = __builtin_fmaf(cw, __uint_as_float(slot[0]), cs);
   const int e = (int)((__float_as_uint(bound) >> 23) & 255u) - 127;  // floor(log2(bound)); 128 for inf or NaN
   const int sh = e >= 15 ? e - 14 : 0;                                 // bound * 2^-sh < 2^15
@@ -71,7 +82,9 @@ __global__ void stem_scale_kernel(uint32_t* __restrict__ slot, float cw, float c
 // ------------------------------------------------------------------------------------------
 // stage 1, first convolution: h1[t+1, c] = half(2^-s * GELU(scale[c] * sum_{h,tap} w[c,h,tap] * x[h, t+tap-1] + shift[c]))
 // rows 0 and N+1 of h1 are zero (the padding of the second convolution).
-// grid ceil(N / 64), 256 threads; thread owns channels tid, tid+256, ...
+// grid (ceil(N / tok), layers), 256 threads; thread owns channels tid, tid+256, ...  tok <= 64 tokens per workgroup: a
+// workgroup's tokens are a serial chain, so short inputs take fewer of them (512 tokens of one layer: 23.6 us with 64
+// tokens per workgroup, eight workgroups on 256 CUs).
 // ------------------------------------------------------------------------------------------
 constexpr int kStemTok = 64;
 constexpr int kMaxHs = 16;
@@ -79,13 +92,15 @@ constexpr int kMaxHs = 16;
 __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                           const float* __restrict__ scale,
                                                           const float* __restrict__ shift,
-                                                          const float* __restrict__ range_slot,
-                                                          uint16_t* __restrict__ h1, int H_s, int N, int c_mid) {
+                                                          const float* __restrict__ range_slots, LayerBatch lb,
+                                                          uint16_t* __restrict__ h1, int H_s, int N, int c_mid, int tok) {
   __shared__ float xs[kMaxHs][kStemTok + 2];
-  const float down = range_slot[1];  // 2^-s
-  const int t0 = blockIdx.x * kStemTok;
-  for (int i = threadIdx.x; i < H_s * (kStemTok + 2); i += 256) {
-    const int h = i / (kStemTok + 2), tt = i % (kStemTok + 2);
+  const float down = range_slots[blockIdx.y * kRangeWords + 1];  // 2^-s
+  x += (size_t)lb.ls[blockIdx.y] * H_s * N;
+  h1 += (size_t)blockIdx.y * (N + 2) * c_mid;
+  const int t0 = blockIdx.x * tok;
+  for (int i = threadIdx.x; i < H_s * (tok + 2); i += 256) {
+    const int h = i / (tok + 2), tt = i % (tok + 2);
     const int t = t0 + tt - 1;
     xs[h][tt] = (t >= 0 && t < N) ? x[(size_t)h * N + t] : 0.0f;
   }
@@ -95,7 +110,7 @@ __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict
 #pragma unroll
     for (int i = 0; i < kMaxHs * 3; ++i) wr[i] = (i < H_s * 3) ? w[(size_t)c * H_s * 3 + i] : 0.0f;
     const float sc = scale[c], sh = shift[c];
-    for (int tt = 0; tt < kStemTok && t0 + tt < N; ++tt) {
+    for (int tt = 0; tt < tok && t0 + tt < N; ++tt) {
       float acc = 0.0f;
 #pragma unroll
       for (int h = 0; h < kMaxHs; ++h) {
@@ -141,6 +156,9 @@ __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict
 // row tiles x, x+8, ... and its workgroups take that list's (row tile, column tile) pairs round-robin:
 // the Nn / BN column tiles of one row tile run at the same time on one XCD and share its L2 copy of
 // the A rows.
+// The M axis holds the rows of all layers of a batch: layer b owns rows [b * row_stride, b * row_stride + rows), its A
+// rows start a_layer elements after those of layer b - 1, and row_stride is a multiple of 256, so a tile never spans two
+// layers; tile rows past a layer's last one re-read that row.
 // K % 64 == 0, Nn % BN == 0.
 // ------------------------------------------------------------------------------------------
 enum Epilogue {
@@ -165,8 +183,10 @@ struct EpiArgs {
   uint16_t* out_h;
   uint16_t* out_v;
   int ldc;  // elements between output rows
+  int vt_ld;       // kEpiQkvH: elements between the rows of the transposed v
+  int out_stride;  // kEpiGeluPeWin: output rows between layers
   const float* pe;  // kEpiGeluPeWin: positional table [kWin, d_time]
-  int n_win;        // kEpiGeluPeWin: number of windows
+  int n_win;        // kEpiGeluPeWin, kEpiQkvH: windows per layer
   int n_slot, n_head;  // kEpiStage3: slots H_s (keys in columns [0, 64 H_s), values in [64 H_s, 128 H_s)) and queries H_l
 };
 
@@ -211,9 +231,9 @@ __device__ __forceinline__ float reduce16_over_16_lanes(float (&v)[16], int lane
 }
 
 template <int EPI, int BM, int BN>
-__global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __restrict__ A, int lda,
-                                                            const uint16_t* __restrict__ W, int M, int Nn, int K,
-                                                            EpiArgs ep) {
+__global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __restrict__ A, int lda, int64_t a_layer,
+                                                            const uint16_t* __restrict__ W, int M, int rows, int row_stride,
+                                                            int Nn, int K, EpiArgs ep) {
   constexpr int WM = BM / 64, WN = 8 / WM;       // waves along M and N
   constexpr int NA = BM / 64, NS = (BM + BN) / 64;  // 64-row parts of a stage: A parts, then W parts
   constexpr int kStageU4 = (BM + BN) * (kGemmBK / 8);  // 16-byte units per stage
@@ -246,13 +266,20 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
   const int sslot = srow * 8 + (sch ^ swz8(srow));  // swz8(srow + 64 * i) == swz8(srow)
   u32x4 rg[NS];
   int f_m0 = 0, f_n0 = 0, f_k = 0, f_it = 0;  // position of the next step to fetch
-  tile_of(0, f_m0, f_n0);
+  const uint16_t* f_a = A;                    // first A row of the layer that tile f_it lies in; f_m0 counts from there
+  auto fetch_tile = [&](int it) {
+    tile_of(it, f_m0, f_n0);
+    const int layer = f_m0 / row_stride;
+    f_m0 -= layer * row_stride;
+    f_a = A + (size_t)layer * a_layer;
+  };
+  fetch_tile(0);
   auto fetch_one = [&](int i) {
     const int k0 = f_k * kGemmBK + sch * 8;
     if (i < NA) {
       int m = f_m0 + srow + 64 * i;
-      m = m < M ? m : M - 1;
-      rg[i] = *reinterpret_cast<const u32x4*>(A + (size_t)m * lda + k0);
+      m = m < rows ? m : rows - 1;
+      rg[i] = *reinterpret_cast<const u32x4*>(f_a + (size_t)m * lda + k0);
     } else {
       const int wl = srow + 64 * (i - NA);
       const int n = f_n0 + (wl & ~127) + 4 * (wl & 31) + ((wl & 127) >> 5);
@@ -265,7 +292,7 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
       if (f_it + 1 < my_tiles) {
         f_k = 0;
         ++f_it;
-        tile_of(f_it, f_m0, f_n0);
+        fetch_tile(f_it);
       } else {
         f_k = nk - 1;
       }
@@ -289,7 +316,7 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
     const int n = n0 + wn * 128 + 4 * l32;
     p0 = *reinterpret_cast<const f32x4*>(ep.p0 + n);
     if constexpr (EPI == kEpiGeluPeWin) {
-      p0 *= *ep.p2;
+      p0 *= ep.p2[(m0 / row_stride) * kRangeWords];
       p1 = *reinterpret_cast<const f32x4*>(ep.p1 + n);
     }
   };
@@ -351,6 +378,7 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
     int m0, n0;
     tile_of(s / nk, m0, n0);
     const int n = n0 + wn * 128 + 4 * l32;
+    const int layer = m0 / row_stride, r0 = m0 - layer * row_stride;  // r0: the tile's first row within its layer
     if constexpr (EPI == kEpiResLn) {
       // (1) pre-norm sum in place, acc += bias + residual row, and (2) row sums and sums of squares: four columns in
       // the lane, 32 lanes by exchange, 4 waves through LDS (the stage that this step has used up is free until
@@ -438,7 +466,7 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
             part[r] = (acc[i][0][r] + p0[0]) * c4[0] + (acc[i][1][r] + p0[1]) * c4[1] + (acc[i][2][r] + p0[2]) * c4[2] +
                       (acc[i][3][r] + p0[3]) * c4[3];
           const float tot = reduce16_over_16_lanes(part, l32);
-          if (row < M) {
+          if (row - m0 + r0 < rows) {
             if (is_k) orow[h * ep.n_slot + sv] = tot * 0.125f;
             else if (is_v && h == 0) orow[ep.n_head * ep.n_slot + sv] = tot;
           }
@@ -452,8 +480,9 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
             // v: element (token m, column vc) goes to vt[(window * heads + head) * 64 + dd][pos]; the lane's eight tokens
             // of a 16-token group (rows r = 8u .. 8u+7 of the tile pair qd = 2u, 2u+1) land in positions half*8 .. +7
             const int vc = n - 2 * kDT;  // columns vc .. vc+3: one head, dd .. dd+3
-            const int mg = m0 + wm * 64 + i * 32;
-            uint16_t* vb = ep.out_v + ((size_t)((mg / kWin) * kHeads + (vc >> 6)) * 64 + (vc & 63)) * kWin + (mg % kWin) + half * 8;
+            const int rg0 = r0 + wm * 64 + i * 32;
+            uint16_t* vb = ep.out_v + ((size_t)((layer * ep.n_win + rg0 / kWin) * kHeads + (vc >> 6)) * 64 + (vc & 63)) * ep.vt_ld +
+                           (rg0 % kWin) + half * 8;
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
@@ -461,7 +490,7 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
                 f32x8 t;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) t[e] = acc[i][jn][u * 8 + e] + p0[jn];
-                PKV_ST(reinterpret_cast<f16x8*>(vb + (size_t)jn * kWin + u * 16), __builtin_convertvector(t, f16x8));
+                PKV_ST(reinterpret_cast<f16x8*>(vb + (size_t)jn * ep.vt_ld + u * 16), __builtin_convertvector(t, f16x8));
               }
             continue;
           }
@@ -479,10 +508,10 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
               for (int e = 0; e < 4; ++e) v[e] = gelu_erf(__builtin_fmaf(v[e], p0[e], p1[e]));
               // token t sits at place t - 1024 k of window k = min(t / 1024, n_win - 1) and, if that window is not the
               // first and the token lies in its first half, at place + 1024 of the window before
-              const int t = m0 + wm * 64 + i * 32 + half * 4 + qd * 8 + e4;
-              if (t < M) {
+              const int t = r0 + wm * 64 + i * 32 + half * 4 + qd * 8 + e4;
+              if (t < rows) {
                 const int kq = t / kStride, k1 = kq < ep.n_win ? kq : ep.n_win - 1, p1w = t - k1 * kStride;
-                const size_t o1 = ((size_t)k1 * kWin + p1w) * kDT + n;
+                const size_t o1 = ((size_t)layer * ep.out_stride + (size_t)k1 * kWin + p1w) * kDT + n;
                 const f32x4 y1 = v + *reinterpret_cast<const f32x4*>(ep.pe + (size_t)p1w * kDT + n);
                 PKV_ST(reinterpret_cast<f32x4*>(ep.out_f32 + o1), y1);
                 PKV_ST(reinterpret_cast<f16x4*>(ep.out_h + o1), __builtin_convertvector(y1, f16x4));
@@ -523,9 +552,10 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
 // Online softmax with a lazily raised reference: a column's reference only moves when a logit exceeds it
 // by more than 2^8, so the rescaling of the output accumulators is rare; probabilities stay below 2^8,
 // which half holds with its full relative precision.
-// Block -> work mapping: blocks are dealt round-robin to the 8 XCDs, so block b takes q-block (b / 8) % 8
-// of item (b / 64) * 8 + b % 8: the 8 q-blocks of one (window, head) run on one XCD and share its L2 copy of
-// that head's K and V.
+// Layer b of the batch owns rows [b * Tp, b * Tp + T) of qk and ao; its windows start every 2048 rows.
+// Block -> work mapping: blocks are dealt round-robin to the 8 XCDs, so with n_qb blocks of 256 queries per window block
+// b takes q-block (b / 8) % n_qb of item (b / 8 / n_qb) * 8 + b % 8: the q-blocks of one (window, head) run on one XCD
+// and share its L2 copy of that head's K and V.
 // ------------------------------------------------------------------------------------------
 constexpr float kAttnLazy = 8.0f;
 
@@ -553,14 +583,16 @@ __device__ __forceinline__ float halves_sum(float v) {
 
 __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t* __restrict__ qk,
                                                                    const uint16_t* __restrict__ vt,
-                                                                   uint16_t* __restrict__ ao, int64_t T, int n_win) {
+                                                                   uint16_t* __restrict__ ao, int T, int Tp, int n_win, int n_qb,
+                                                                   int vt_ld) {
   __shared__ u32x4 lds[3 * 1024];  // stage = K tile (64 keys x 8 chunks) then V^T tile (64 d rows x 8 chunks)
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-  const int bj = blockIdx.x >> 3, item = (bj >> 3) * kXcds + (blockIdx.x & 7);
-  const int wk = item / kHeads, hd = item % kHeads;
-  const int64_t base = (int64_t)wk * kWin;
-  const int len = (wk < n_win - 1) ? kWin : (int)(T - base);
-  const int i0 = (bj & 7) * 256;
+  const int bj = blockIdx.x >> 3, item = (bj / n_qb) * kXcds + (blockIdx.x & 7);
+  const int wg = item / kHeads, hd = item % kHeads;  // wg: window of the batch
+  const int layer = wg / n_win, wk = wg % n_win;
+  const int64_t base = (int64_t)layer * Tp + (int64_t)wk * kWin;
+  const int len = (wk < n_win - 1) ? kWin : T - wk * kWin;
+  const int i0 = (bj % n_qb) * 256;
   if (i0 >= len) return;
   constexpr float c = 1.4426950408889634f * 0.125f;  // log2(e) / sqrt(64)
 
@@ -582,7 +614,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t
   float m_run[2] = {-1.0e30f, -1.0e30f}, l_run[2] = {0.0f, 0.0f};
 
   const uint16_t* kbase = qk + (size_t)base * (2 * kDT) + kDT + hd * 64;
-  const uint16_t* vbase = vt + (size_t)(wk * kHeads + hd) * 64 * kWin;
+  const uint16_t* vbase = vt + (size_t)(wg * kHeads + hd) * 64 * vt_ld;
   const int n_tiles = (len + 63) / 64;
   // staging: thread moves chunk tid % 8 of rows tid / 8 and tid / 8 + 32 of both tiles
   const int srow = tid >> 3, sch = tid & 7;
@@ -596,7 +628,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t
       int j = j0 + row;
       j = j < len ? j : len - 1;
       rk[i] = *reinterpret_cast<const u32x4*>(kbase + (size_t)j * (2 * kDT) + sch * 8);
-      rv[i] = *reinterpret_cast<const u32x4*>(vbase + (size_t)row * kWin + j0 + sch * 8);
+      rv[i] = *reinterpret_cast<const u32x4*>(vbase + (size_t)row * vt_ld + j0 + sch * 8);
     }
   };
   auto store = [&](int t) {
@@ -764,9 +796,12 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t
 
 // ------------------------------------------------------------------------------------------
 // overlap averaging: zg[t] = half(mean over the windows covering token t of x[row of t in that window])
+// grid (ceil(N * 128 / 256), layers)
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void overlap_avg_kernel(const float* __restrict__ x, uint16_t* __restrict__ zg,
-                                                           int64_t N, int n_win) {
+                                                           int64_t N, int n_win, int Tp, int Np) {
+  x += (size_t)blockIdx.y * Tp * kDT;
+  zg += (size_t)blockIdx.y * Np * kDT;
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (gid >= N * (kDT / 4)) return;
   const int64_t t = gid / (kDT / 4);
@@ -791,10 +826,12 @@ __global__ __launch_bounds__(256) void overlap_avg_kernel(const float* __restric
 // stage 3 per token (Eq. 3), after the K/V projection GEMM whose epilogue has already taken the inner products:
 // s3[t] = [ <Q_l[h], K[s]> / 8 for h < H_l, s < H_s | <w_o, V[s]> for s < H_s ];
 // yhat[ll, h, t] = sum_s softmax_s(logit[h][s]) * u[s] + b_o for every paired target layer ll.
-// Block = 256 threads = (256 / H_l) tokens x H_l target heads, token index fastest.
+// Block = 256 threads = (256 / H_l) tokens x H_l target heads, token index fastest; grid.y = layers.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void stage3_kernel(const float* __restrict__ s3, float b_o, float* __restrict__ yhat,
-                                                      int64_t N, int H_s, int H_l, int ll_lo, int ll_hi) {
+                                                      int64_t N, int Np, int H_s, int H_l, LayerBatch lb) {
+  const int ll_lo = lb.lo[blockIdx.y], ll_hi = lb.hi[blockIdx.y];
+  s3 += (size_t)blockIdx.y * Np * ((H_l + 1) * H_s);
   const int tok_per_block = 256 / H_l;
   const int tt = threadIdx.x % tok_per_block, h = threadIdx.x / tok_per_block;
   const int64_t t = (int64_t)blockIdx.x * tok_per_block + tt;
@@ -814,8 +851,14 @@ __global__ __launch_bounds__(256) void stage3_kernel(const float* __restrict__ s
   for (int ll = ll_lo; ll < ll_hi; ++ll) yhat[((size_t)ll * H_l + h) * N + t] = y;
 }
 
+// rows of every layer of a batch on a GEMM's M axis: `valid` of them, `stride` apart (a multiple of 256)
+struct RowSpace {
+  int layers, valid, stride;
+  int64_t a_layer;  // elements between the A rows of two layers
+};
+
 template <int EPI, int BM, int BN>
-hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, int64_t M, int Nn, int K, const EpiArgs& ep,
+hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowSpace& rs, int Nn, int K, const EpiArgs& ep,
                        int n_cu, hipStream_t stream) {
   constexpr int kLdsBytes = 2 * (BM + BN) * (kGemmBK / 8) * 16;
   static bool attr_set = false;  // per instantiation; setting it again is harmless
@@ -825,14 +868,17 @@ hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, int64_t M,
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  if (Nn % BN != 0 || K % kGemmBK != 0 || M <= 0) return hipErrorInvalidValue;
-  const int m_tiles = (int)((M + BM - 1) / BM), n_tiles = Nn / BN;
+  const int64_t M = (int64_t)rs.layers * rs.stride;
+  if (Nn % BN != 0 || K % kGemmBK != 0 || rs.valid <= 0 || rs.valid > rs.stride || rs.stride % 256 != 0 || M > INT32_MAX)
+    return hipErrorInvalidValue;
+  const int m_tiles = (int)(M / BM), n_tiles = Nn / BN;
   // one workgroup per CU, a multiple of the XCD count, no more than there are tiles per XCD list
   const int per_xcd_tiles = ((m_tiles + kXcds - 1) / kXcds) * n_tiles;
   int wg_per_xcd = n_cu / kXcds;
   if (wg_per_xcd < 1) wg_per_xcd = 1;
   if (wg_per_xcd > per_xcd_tiles) wg_per_xcd = per_xcd_tiles;
-  gemm_f16_kernel<EPI, BM, BN><<<kXcds * wg_per_xcd, 512, kLdsBytes, stream>>>(A, lda, W, (int)M, Nn, K, ep);
+  gemm_f16_kernel<EPI, BM, BN><<<kXcds * wg_per_xcd, 512, kLdsBytes, stream>>>(A, lda, rs.a_layer, W, (int)M, rs.valid,
+                                                                             rs.stride, Nn, K, ep);
   return hipGetLastError();
 }
 
@@ -842,17 +888,14 @@ hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, int64_t M,
     if (e_ != hipSuccess) return e_;   \
   } while (0)
 
-}  // namespace
-
-namespace {
-
-// The network for one proxy layer (input rows xl [H_kv, N]); writes yhat rows of the target layers ll .. ll_hi - 1.
-hipError_t mapper_layer(proxykv_ctx* ctx, MapperWorkspace& m, const float* xl, int64_t N, float* yhat, int ll, int ll_hi,
+// The network for the layers of one batch (x_in: all proxy layers' scores [L_s, H_kv, N]); writes the rows of every target
+// layer that is paired with one of them.
+hipError_t mapper_batch(proxykv_ctx* ctx, const MapPlan& p, const LayerBatch& lb, const float* x_in, int64_t N, float* yhat,
                         int n_cu, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
-  int64_t n_win, T;
-  window_plan(N, c.win, c.stride, &n_win, &T);
+  const MapperWorkspace& m = ctx->m;
+  const int T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
   uint16_t* h1 = (uint16_t*)m.h1.ptr;
   float* x = (float*)m.x.ptr;
   uint16_t* xb = (uint16_t*)m.xb.ptr;
@@ -863,19 +906,21 @@ hipError_t mapper_layer(proxykv_ctx* ctx, MapperWorkspace& m, const float* xl, i
   uint16_t* zg = (uint16_t*)m.zg.ptr;
   float* s3 = (float*)m.s3.ptr;
   uint32_t* range = (uint32_t*)m.range.ptr;
-  const unsigned ew_blocks_N = (unsigned)((N * (kDT / 4) + 255) / 256);
+  const unsigned nl = (unsigned)lb.n;
+  auto rows_T = [&](int lda) { return RowSpace{lb.n, T, Tp, (int64_t)Tp * lda}; };
 
   // stage 1
   {
     const int64_t n_x = (int64_t)c.H_kv * N;
     const unsigned blocks = (unsigned)((n_x + 256 * 16 - 1) / (256 * 16) < 1024 ? (n_x + 256 * 16 - 1) / (256 * 16) : 1024);
-    absmax_kernel<<<blocks, 256, 0, stream>>>(xl, n_x, range);
+    absmax_kernel<<<dim3(blocks, nl), 256, 0, stream>>>(x_in, n_x, lb, range);
     PKV_TRY(hipGetLastError());
-    stem_scale_kernel<<<1, 64, 0, stream>>>(range, w.stem_cw, w.stem_cs);
+    stem_scale_kernel<<<1, 64, 0, stream>>>(range, lb.n, w.stem_cw, w.stem_cs);
     PKV_TRY(hipGetLastError());
   }
-  stem_conv1_kernel<<<(unsigned)((N + kStemTok - 1) / kStemTok), 256, 0, stream>>>(
-      xl, w.conv1_w, w.bn1_scale, w.bn1_shift, reinterpret_cast<const float*>(range), h1, c.H_kv, (int)N, c.c_mid);
+  const int tok = (int64_t)nl * N >= 64 * 512 ? kStemTok : 16;
+  stem_conv1_kernel<<<dim3((unsigned)((N + tok - 1) / tok), nl), 256, 0, stream>>>(
+      x_in, w.conv1_w, w.bn1_scale, w.bn1_shift, reinterpret_cast<const float*>(range), lb, h1, c.H_kv, (int)N, c.c_mid, tok);
   PKV_TRY(hipGetLastError());
   EpiArgs e2 = {};
   e2.p0 = w.bn2_scale;
@@ -885,10 +930,13 @@ hipError_t mapper_layer(proxykv_ctx* ctx, MapperWorkspace& m, const float* xl, i
   e2.out_h = xb;
   e2.ldc = kDT;
   e2.pe = w.pe;
-  e2.n_win = (int)n_win;
-  PKV_TRY((launch_gemm<kEpiGeluPeWin, 256, 256>(h1, c.c_mid, w.conv2_w, N, kDT, 3 * c.c_mid, e2, n_cu, stream)));
+  e2.n_win = n_win;
+  e2.out_stride = Tp;
+  const RowSpace rows_conv = {lb.n, (int)N, Np, (int64_t)(N + 2) * c.c_mid};
+  PKV_TRY((launch_gemm<kEpiGeluPeWin, 256, 256>(h1, c.c_mid, w.conv2_w, rows_conv, kDT, 3 * c.c_mid, e2, n_cu, stream)));
 
   // stage 2 (the stem's epilogue has written its input rows)
+  const int n_qb = ((T < kWin ? T : kWin) + 255) / 256;
   for (int li = 0; li < c.n_enc_layers; ++li) {
     const EncoderLayerWeights& e = w.enc[li];
     EpiArgs eq = {};
@@ -896,8 +944,10 @@ hipError_t mapper_layer(proxykv_ctx* ctx, MapperWorkspace& m, const float* xl, i
     eq.out_h = qk;
     eq.out_v = vt;
     eq.ldc = 2 * kDT;
-    PKV_TRY((launch_gemm<kEpiQkvH, 256, 256>(xb, kDT, e.in_w, T, 3 * kDT, kDT, eq, n_cu, stream)));
-    window_attention_kernel<<<(unsigned)(n_win * kHeads * (kWin / 256)), 256, 0, stream>>>(qk, vt, ao, T, (int)n_win);
+    eq.n_win = n_win;
+    eq.vt_ld = vt_ld;
+    PKV_TRY((launch_gemm<kEpiQkvH, 256, 256>(xb, kDT, e.in_w, rows_T(kDT), 3 * kDT, kDT, eq, n_cu, stream)));
+    window_attention_kernel<<<nl * (unsigned)(n_win * kHeads * n_qb), 256, 0, stream>>>(qk, vt, ao, T, Tp, n_win, n_qb, vt_ld);
     PKV_TRY(hipGetLastError());
     EpiArgs eo = {};
     eo.p0 = e.out_b;
@@ -907,19 +957,19 @@ hipError_t mapper_layer(proxykv_ctx* ctx, MapperWorkspace& m, const float* xl, i
     eo.out_f32 = x;
     eo.out_h = xb;
     eo.ldc = kDT;
-    PKV_TRY((launch_gemm<kEpiResLn, 128, 512>(ao, kDT, e.out_w, T, kDT, kDT, eo, n_cu, stream)));
+    PKV_TRY((launch_gemm<kEpiResLn, 128, 512>(ao, kDT, e.out_w, rows_T(kDT), kDT, kDT, eo, n_cu, stream)));
     EpiArgs e1 = {};
     e1.p0 = e.ffn1_b;
     e1.out_h = hid;
     e1.ldc = c.d_ffn;
-    PKV_TRY((launch_gemm<kEpiBiasReluH, 256, 256>(xb, kDT, e.ffn1_w, T, c.d_ffn, kDT, e1, n_cu, stream)));
+    PKV_TRY((launch_gemm<kEpiBiasReluH, 256, 256>(xb, kDT, e.ffn1_w, rows_T(kDT), c.d_ffn, kDT, e1, n_cu, stream)));
     EpiArgs ef = eo;
     ef.p0 = e.ffn2_b;
     ef.g = e.ln2_g;
     ef.b = e.ln2_b;
-    PKV_TRY((launch_gemm<kEpiResLn, 128, 512>(hid, c.d_ffn, e.ffn2_w, T, kDT, c.d_ffn, ef, n_cu, stream)));
+    PKV_TRY((launch_gemm<kEpiResLn, 128, 512>(hid, c.d_ffn, e.ffn2_w, rows_T(c.d_ffn), kDT, c.d_ffn, ef, n_cu, stream)));
   }
-  overlap_avg_kernel<<<ew_blocks_N, 256, 0, stream>>>(x, zg, N, (int)n_win);
+  overlap_avg_kernel<<<dim3((unsigned)((N * (kDT / 4) + 255) / 256), nl), 256, 0, stream>>>(x, zg, N, n_win, Tp, Np);
   PKV_TRY(hipGetLastError());
 
   // stage 3
@@ -932,10 +982,11 @@ hipError_t mapper_layer(proxykv_ctx* ctx, MapperWorkspace& m, const float* xl, i
   e3.ldc = (c.H_l + 1) * c.H_kv;
   e3.n_slot = c.H_kv;
   e3.n_head = c.H_l;
-  PKV_TRY((launch_gemm<kEpiStage3, 256, 256>(zg, kDT, w.kv_w, N, nkv, kDT, e3, n_cu, stream)));
+  const RowSpace rows_N = {lb.n, (int)N, Np, (int64_t)Np * kDT};
+  PKV_TRY((launch_gemm<kEpiStage3, 256, 256>(zg, kDT, w.kv_w, rows_N, nkv, kDT, e3, n_cu, stream)));
   const int tok_per_block = 256 / c.H_l;
-  stage3_kernel<<<(unsigned)((N + tok_per_block - 1) / tok_per_block), 256, 0, stream>>>(s3, w.out_b, yhat, N, c.H_kv, c.H_l, ll,
-                                                                                        ll_hi);
+  stage3_kernel<<<dim3((unsigned)((N + tok_per_block - 1) / tok_per_block), nl), 256, 0, stream>>>(s3, w.out_b, yhat, N, Np,
+                                                                                                c.H_kv, c.H_l, lb);
   return hipGetLastError();
 }
 
@@ -946,29 +997,20 @@ hipError_t mapper_forward(proxykv_ctx* ctx, const float* x_in, int64_t N, float*
   int n_cu = 0, dev = 0;
   PKV_TRY(hipGetDevice(&dev));
   PKV_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  int64_t n_win, T;
-  window_plan(N, c.win, c.stride, &n_win, &T);
-  // distinct proxy layers are dealt round-robin to the lanes; lane 0 is the caller's stream, the others start behind
-  // the work already queued there and are joined into it at the end
-  const int lanes = map_lanes(T, ctx->distinct_layers);
-  if (lanes > 1) {
-    PKV_TRY(hipEventRecord(ctx->lane_fork, stream));
-    for (int lane = 1; lane < lanes; ++lane) PKV_TRY(hipStreamWaitEvent(ctx->lane_stream[lane], ctx->lane_fork, 0));
-  }
-  int ll = 0, item = 0;
-  while (ll < c.L_l) {
-    const int ls = ctx->pairing[ll];
+  const MapPlan p = map_plan(c, N, ctx->distinct_layers);
+  LayerBatch lb = {};
+  for (int ll = 0; ll < c.L_l;) {
     int ll_hi = ll + 1;
-    while (ll_hi < c.L_l && ctx->pairing[ll_hi] == ls) ++ll_hi;
-    const int lane = item % lanes;
-    PKV_TRY(mapper_layer(ctx, ctx->m[lane], x_in + (size_t)ls * c.H_kv * N, N, yhat, ll, ll_hi, n_cu,
-                         lane == 0 ? stream : ctx->lane_stream[lane]));
+    while (ll_hi < c.L_l && ctx->pairing[ll_hi] == ctx->pairing[ll]) ++ll_hi;
+    lb.ls[lb.n] = ctx->pairing[ll];
+    lb.lo[lb.n] = ll;
+    lb.hi[lb.n] = ll_hi;
+    ++lb.n;
     ll = ll_hi;
-    ++item;
-  }
-  for (int lane = 1; lane < lanes; ++lane) {
-    PKV_TRY(hipEventRecord(ctx->lane_join[lane], ctx->lane_stream[lane]));
-    PKV_TRY(hipStreamWaitEvent(stream, ctx->lane_join[lane], 0));
+    if (lb.n == p.batch || ll == c.L_l) {
+      PKV_TRY(mapper_batch(ctx, p, lb, x_in, N, yhat, n_cu, stream));
+      lb.n = 0;
+    }
   }
   return hipSuccess;
 }

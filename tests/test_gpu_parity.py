@@ -351,6 +351,23 @@ def test_mapper_degenerate_lengths(N):
     pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("L_s,L_l,N", [(33, 33, 5), (5, 3, 257), (3, 3, 2305), (4, 9, 255)])
+def test_mapper_batches_of_layers(L_s, L_l, N):
+    """Distinct proxy layers share their launches: more layers than one batch takes, layers that no target layer reads,
+    several target layers per proxy layer, lengths just past and just short of the 256-row stride between two layers, and
+    a second window.  Scores differ by a factor between layers, so a row that leaked into a neighbour would show."""
+    case = synth.scaled_case(synth.CASES["llama_8k"], name="batch", L_s=L_s, H_kv=2, H_q=2, L_l=L_l, H_l=4, N=N, N_q=1, chunk=1,
+                             n_planted=0)
+    w = synth.make_mapper_weights(case.H_kv, case.H_l)
+    g = torch.Generator().manual_seed(300 + N)
+    X = (torch.rand(L_s, case.H_kv, N, generator=g) ** 8) * (1.0 + torch.arange(L_s).view(-1, 1, 1) % 7)
+    ctx = _ctx(case, w)
+    y = pk.proxykv_map(ctx, X.float().cuda())
+    torch.cuda.synchronize()
+    assert_close(y, oracle.mapper(X.float(), w, L_l), f"map {L_s} -> {L_l} layers, N={N}")
+    pk.proxykv_destroy(ctx)
+
+
 def test_mapper_with_scores_beyond_the_half_range():
     """Sum-form scores with an attention sink (Sec. 3 prints the feature as a sum over the query axis, so one key can
     collect a share of every row): the first conv block's output reaches 1.4e5, beyond what IEEE half holds.  The
