@@ -77,8 +77,8 @@ int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) 
 }
 
 struct Sizes {
-  size_t neg_lse, x_ws, yhat_ws, h1, x, xb, qk, vt, ao, hid, zg, s3, range;
-  size_t mapper() const { return h1 + x + xb + qk + vt + ao + hid + zg + s3 + range; }  // one batch's activations
+  size_t neg_lse, x_ws, yhat_ws, h1, x, xb, qk, vt, ao, hid, zg, s3, pre, range;
+  size_t mapper() const { return h1 + x + xb + qk + vt + ao + hid + zg + s3 + pre + range; }  // one batch's activations
   size_t total() const { return neg_lse + x_ws + yhat_ws + mapper(); }
 };
 
@@ -99,6 +99,7 @@ Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q, int disti
   s.hid = Tp * (size_t)c.d_ffn * 2;
   s.zg = Np * dt * 2;
   s.s3 = Np * (size_t)(c.H_l + 1) * (size_t)c.H_kv * 4;
+  s.pre = p.small ? Tp * dt * 4 : 0;
   s.range = pkv::kMaxBatch * 64;
   return s;
 }
@@ -135,6 +136,7 @@ int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool 
     if ((rc = ensure(ctx, m.hid, s.hid, stream))) return rc;
     if ((rc = ensure(ctx, m.zg, s.zg, stream))) return rc;
     if ((rc = ensure(ctx, m.s3, s.s3, stream))) return rc;
+    if ((rc = ensure(ctx, m.pre, s.pre, stream))) return rc;
     if ((rc = ensure(ctx, m.range, s.range, stream))) return rc;
   }
   return rc;
@@ -297,7 +299,7 @@ int proxykv_destroy(proxykv_ctx* ctx) {
   std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
                                     &ctx->neg_lse,     &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws};
   pkv::MapperWorkspace& m = ctx->m;
-  for (DeviceBuffer* b : {&m.h1, &m.x, &m.xb, &m.qk, &m.vt, &m.ao, &m.hid, &m.zg, &m.s3, &m.range}) all.push_back(b);
+  for (DeviceBuffer* b : {&m.h1, &m.x, &m.xb, &m.qk, &m.vt, &m.ao, &m.hid, &m.zg, &m.s3, &m.pre, &m.range}) all.push_back(b);
   bool any = ctx->ev_created;
   for (DeviceBuffer* b : all) any = any || b->ptr;
   if (any) {

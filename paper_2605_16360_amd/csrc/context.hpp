@@ -61,7 +61,8 @@ struct MapperWorkspace {
   DeviceBuffer hid;      // fp16 [Tp, d_ffn]
   DeviceBuffer zg;       // fp16 [Np, d_time]    overlap-averaged encoder output
   DeviceBuffer s3;       // fp32 [Np, (H_l + 1) * H_s]  stage 3: per token the H_l x H_s logits, then <w_o, V[s]> of every slot
-  DeviceBuffer range;    // 3 of 16 words: largest |score| of the layer (bits), 2^-s and 2^s of the stem's range exponent
+  DeviceBuffer pre;      // fp32 [Tp, d_time]    small inputs only: sums that the next kernel normalises as it reads them
+  DeviceBuffer range;    // 16 words: partial maxima of |score| (bits)
 };
 
 }  // namespace pkv
@@ -109,11 +110,15 @@ inline void window_plan(int64_t N, int win, int stride, int64_t* n_win, int64_t*
 // layers, layers on four streams against batches: N = 1500 6.15 -> 2.21 ms, N = 8192 20.2 -> 18.9 ms, N = 32 768 the same.
 constexpr int64_t kMapBatchRows = 262144;
 constexpr int kMaxBatch = 32;
+// Up to this many rows in a batch the small tiles are faster (large tiles on the left: one layer of 512 rows 867 / 231 us, of 2000
+// rows 1060 / 566 us; 16 layers of 256 rows 970 / 882 us).
+constexpr int64_t kMapSmallRows = 4096;
 struct MapPlan {
   int64_t n_win, T;   // windows and window rows of a layer
   int64_t Tp, Np;     // window rows and tokens of a layer, padded to the GEMM's 256-row tile
   int64_t vt_ld;      // row length of the transposed v
   int batch;
+  bool small;         // few rows: the small-tile kernels
 };
 inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers) {
   MapPlan p;
@@ -125,6 +130,7 @@ inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers)
   cap = cap < 1 ? 1 : (cap > kMaxBatch ? kMaxBatch : cap);
   const int64_t n_batches = (distinct_layers + cap - 1) / cap;
   p.batch = (int)((distinct_layers + n_batches - 1) / n_batches);
+  p.small = p.batch * p.T <= kMapSmallRows && c.n_enc_layers > 0;
   return p;
 }
 

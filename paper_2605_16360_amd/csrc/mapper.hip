@@ -14,48 +14,18 @@
 #include "common.hpp"
 #include "context.hpp"
 #include "kernels.hpp"
+#include "mapper.hpp"
 
 namespace pkv {
 namespace {
 
-typedef float f32x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-
-constexpr float kNegInf = -__builtin_huge_valf();
-constexpr int kDT = 512;    // d_time
-constexpr int kWin = 2048;  // window length
-constexpr int kStride = 1024;
-constexpr int kHeads = 8;   // encoder heads, 64 wide
-constexpr int kRangeWords = 16;  // words between the range slots of two layers of a batch
-
-// The distinct proxy layers that one batch of launches handles, and the target layers lo .. hi-1 that each serves.
-struct LayerBatch {
-  int n;
-  int ls[kMaxBatch], lo[kMaxBatch], hi[kMaxBatch];
-};
-
-__device__ __forceinline__ float gelu_erf(float x) { return 0.5f * x * (1.0f + erff(x * 0.70710678118654752f)); }
-
-__device__ __forceinline__ uint16_t to_h(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
-
-// 8 chunks of 16 bytes per 128-byte LDS row, XOR-swizzled so that 16-byte tile stores and MFMA fragment reads
-// (32 consecutive rows, same chunk) both spread over all LDS banks
-__device__ __forceinline__ int swz8(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-
-// ------------------------------------------------------------------------------------------
-// Range of the first convolution's output.  The scores of Sec. 3 in their sum form are not bounded by one (an
-// attention sink collects up to G * N_q), so GELU(BN(conv1(x))) can exceed what IEEE half holds.  The operand of the
-// second convolution is therefore stored as half(h1 * 2^-s) with one exponent s per proxy layer, taken from the
-// largest score of the layer, and the second convolution's per-channel scale is multiplied by 2^s: exact, since only
-// the exponent moves.  s = 0 (nothing changes) whenever the bound below stays under 2^15.
-//   slot[0]: bits of max |x| (atomicMax, cleared again by stem_scale_kernel), slot[1] = 2^-s, slot[2] = 2^s (floats)
-// ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x, int64_t n, LayerBatch lb,
-                                                     uint32_t* __restrict__ slots) {
+// partial maxima of |x| of every layer's scores (n per layer), as bits; grid (kRangeWords, layers)
+__global__ __launch_bounds__(1024) void absmax_kernel(const float* __restrict__ x, int64_t n, LayerBatch lb,
+                                                      uint32_t* __restrict__ words) {
+  __shared__ uint32_t part[16];
   x += (size_t)lb.ls[blockIdx.y] * n;
-  uint32_t* slot = slots + blockIdx.y * kRangeWords;
   uint32_t m = 0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
+  for (int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x; i < n; i += (int64_t)kRangeWords * 1024) {
     const uint32_t a = __float_as_uint(x[i]) & 0x7fffffffu;
     m = a > m ? a : m;
   }
@@ -64,19 +34,13 @@ __global__ __launch_bounds__(256) void absmax_kernel(const float* __restrict__ x
     const uint32_t o = __shfl_xor(m, off, 64);
     m = o > m ? o : m;
   }
-  if ((threadIdx.x & 63) == 0) atomicMax(slot, m);
-}
-
-// |h1| <= |scale_c| * sum |w_c| * max|x| + |shift_c| <= cw * max|x| + cs  (|GELU(y)| <= |y|)
-__global__ void stem_scale_kernel(uint32_t* __restrict__ slots, int n_layers, float cw, float cs) {
-  if ((int)threadIdx.x >= n_layers || blockIdx.x != 0) return;
-  uint32_t* slot = slots + threadIdx.x * kRangeWords;
-  const float bound = __builtin_fmaf(cw, __uint_as_float(slot[0]), cs);
-  const int e = (int)((__float_as_uint(bound) >> 23) & 255u) - 127;  // floor(log2(bound)); 128 for inf or NaN
-  const int sh = e >= 15 ? e - 14 : 0;                                 // bound * 2^-sh < 2^15
-  slot[1] = (uint32_t)(127 - sh) << 23;
-  slot[2] = (uint32_t)(127 + sh) << 23;
-  slot[0] = 0u;
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+#pragma unroll
+    for (int w = 1; w < 16; ++w) m = part[w] > m ? part[w] : m;
+    words[blockIdx.y * kRangeWords + blockIdx.x] = m;
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -92,10 +56,10 @@ constexpr int kMaxHs = 16;
 __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict__ x, const float* __restrict__ w,
                                                           const float* __restrict__ scale,
                                                           const float* __restrict__ shift,
-                                                          const float* __restrict__ range_slots, LayerBatch lb,
+                                                          const uint32_t* __restrict__ range, float cw, float cs, LayerBatch lb,
                                                           uint16_t* __restrict__ h1, int H_s, int N, int c_mid, int tok) {
   __shared__ float xs[kMaxHs][kStemTok + 2];
-  const float down = range_slots[blockIdx.y * kRangeWords + 1];  // 2^-s
+  const float down = exp2_int(-stem_exponent(range + blockIdx.y * kRangeWords, cw, cs));
   x += (size_t)lb.ls[blockIdx.y] * H_s * N;
   h1 += (size_t)blockIdx.y * (N + 2) * c_mid;
   const int t0 = blockIdx.x * tok;
@@ -162,7 +126,7 @@ __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict
 // K % 64 == 0, Nn % BN == 0.
 // ------------------------------------------------------------------------------------------
 enum Epilogue {
-  kEpiGeluPeWin,      // z = GELU(acc * (p0[n] * *p2) + p1[n]) of token m goes, plus the positional row of its place, into the
+  kEpiGeluPeWin,      // z = GELU(acc * (p0[n] * 2^s) + p1[n]), s from `range`, of token m goes, plus the positional row of its place, into the
                       // row of every window that holds the token: out_f32 and out_h (second stem convolution -> stage-2 input)
   kEpiQkvH,           // columns below 2 * d_time: out_h[m, n] = half(acc + p0[n]), rows ldc apart (q and k);
                       // the others (v): out_v in the transposed, key-permuted layout of the attention kernel
@@ -175,7 +139,8 @@ enum Epilogue {
 struct EpiArgs {
   const float* p0;
   const float* p1;
-  const float* p2;
+  const uint32_t* range;  // kEpiGeluPeWin: partial maxima per layer, cw and cs as in stem_exponent
+  float cw, cs;
   const float* g;
   const float* b;
   const float* res;
@@ -194,7 +159,6 @@ struct EpiArgs {
 #define PKV_ST(ptr, val) __builtin_nontemporal_store((val), (ptr))
 
 constexpr int kGemmBK = 64;
-constexpr int kXcds = 8;
 
 // Sum of v[0..15] over the 32 lanes that share bit 5 of the lane number, sixteen sums at once: in every step a lane
 // keeps the half of its values that its own lane bit selects, hands the other half to the partner and adds what it
@@ -316,7 +280,7 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
     const int n = n0 + wn * 128 + 4 * l32;
     p0 = *reinterpret_cast<const f32x4*>(ep.p0 + n);
     if constexpr (EPI == kEpiGeluPeWin) {
-      p0 *= ep.p2[(m0 / row_stride) * kRangeWords];
+      p0 *= exp2_int(stem_exponent(ep.range + (m0 / row_stride) * kRangeWords, ep.cw, ep.cs));
       p1 = *reinterpret_cast<const f32x4*>(ep.p1 + n);
     }
   };
@@ -557,30 +521,6 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
 // b takes q-block (b / 8) % n_qb of item (b / 8 / n_qb) * 8 + b % 8: the q-blocks of one (window, head) run on one XCD
 // and share its L2 copy of that head's K and V.
 // ------------------------------------------------------------------------------------------
-constexpr float kAttnLazy = 8.0f;
-
-// max over the 32 elements of two accumulator tiles (v_max3 tree)
-__device__ __forceinline__ float max16_8(const f32x16& a, const f32x16& b) {
-  float m = max3f(a[0], a[1], a[2]);
-#pragma unroll
-  for (int r = 3; r < 15; r += 2) m = max3f(m, a[r], a[r + 1]);
-  m = max3f(m, a[15], b[0]);
-#pragma unroll
-  for (int r = 1; r < 15; r += 2) m = max3f(m, b[r], b[r + 1]);
-  return __builtin_fmaxf(m, b[15]);
-}
-
-// max / sum over the two half-waves without an LDS round trip: the swap leaves the lower half's value in both
-// halves of the first register and the upper half's in both halves of the second
-__device__ __forceinline__ float halves_max(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __builtin_fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float halves_sum(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
 __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t* __restrict__ qk,
                                                                    const uint16_t* __restrict__ vt,
                                                                    uint16_t* __restrict__ ao, int T, int Tp, int n_win, int n_qb,
@@ -851,12 +791,6 @@ __global__ __launch_bounds__(256) void stage3_kernel(const float* __restrict__ s
   for (int ll = ll_lo; ll < ll_hi; ++ll) yhat[((size_t)ll * H_l + h) * N + t] = y;
 }
 
-// rows of every layer of a batch on a GEMM's M axis: `valid` of them, `stride` apart (a multiple of 256)
-struct RowSpace {
-  int layers, valid, stride;
-  int64_t a_layer;  // elements between the A rows of two layers
-};
-
 template <int EPI, int BM, int BN>
 hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowSpace& rs, int Nn, int K, const EpiArgs& ep,
                        int n_cu, hipStream_t stream) {
@@ -882,21 +816,13 @@ hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowS
   return hipGetLastError();
 }
 
-#define PKV_TRY(call)                  \
-  do {                                 \
-    hipError_t e_ = (call);            \
-    if (e_ != hipSuccess) return e_;   \
-  } while (0)
-
-// The network for the layers of one batch (x_in: all proxy layers' scores [L_s, H_kv, N]); writes the rows of every target
-// layer that is paired with one of them.
-hipError_t mapper_batch(proxykv_ctx* ctx, const MapPlan& p, const LayerBatch& lb, const float* x_in, int64_t N, float* yhat,
-                        int n_cu, hipStream_t stream) {
+// Second stem convolution, encoder and stage-3 inner products of one batch with the large tiles: from m.h1 to m.s3.
+hipError_t mapper_large_body(proxykv_ctx* ctx, const MapPlan& p, int n_layers, int64_t N, int n_cu, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
   const MapperWorkspace& m = ctx->m;
   const int T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
-  uint16_t* h1 = (uint16_t*)m.h1.ptr;
+  const uint16_t* h1 = (const uint16_t*)m.h1.ptr;
   float* x = (float*)m.x.ptr;
   uint16_t* xb = (uint16_t*)m.xb.ptr;
   uint16_t* qk = (uint16_t*)m.qk.ptr;
@@ -904,35 +830,22 @@ hipError_t mapper_batch(proxykv_ctx* ctx, const MapPlan& p, const LayerBatch& lb
   uint16_t* ao = (uint16_t*)m.ao.ptr;
   uint16_t* hid = (uint16_t*)m.hid.ptr;
   uint16_t* zg = (uint16_t*)m.zg.ptr;
-  float* s3 = (float*)m.s3.ptr;
-  uint32_t* range = (uint32_t*)m.range.ptr;
-  const unsigned nl = (unsigned)lb.n;
-  auto rows_T = [&](int lda) { return RowSpace{lb.n, T, Tp, (int64_t)Tp * lda}; };
+  const unsigned nl = (unsigned)n_layers;
+  auto rows_T = [&](int lda) { return RowSpace{n_layers, T, Tp, (int64_t)Tp * lda}; };
 
-  // stage 1
-  {
-    const int64_t n_x = (int64_t)c.H_kv * N;
-    const unsigned blocks = (unsigned)((n_x + 256 * 16 - 1) / (256 * 16) < 1024 ? (n_x + 256 * 16 - 1) / (256 * 16) : 1024);
-    absmax_kernel<<<dim3(blocks, nl), 256, 0, stream>>>(x_in, n_x, lb, range);
-    PKV_TRY(hipGetLastError());
-    stem_scale_kernel<<<1, 64, 0, stream>>>(range, lb.n, w.stem_cw, w.stem_cs);
-    PKV_TRY(hipGetLastError());
-  }
-  const int tok = (int64_t)nl * N >= 64 * 512 ? kStemTok : 16;
-  stem_conv1_kernel<<<dim3((unsigned)((N + tok - 1) / tok), nl), 256, 0, stream>>>(
-      x_in, w.conv1_w, w.bn1_scale, w.bn1_shift, reinterpret_cast<const float*>(range), lb, h1, c.H_kv, (int)N, c.c_mid, tok);
-  PKV_TRY(hipGetLastError());
   EpiArgs e2 = {};
   e2.p0 = w.bn2_scale;
   e2.p1 = w.bn2_shift;
-  e2.p2 = reinterpret_cast<const float*>(range) + 2;
+  e2.range = (const uint32_t*)m.range.ptr;
+  e2.cw = w.stem_cw;
+  e2.cs = w.stem_cs;
   e2.out_f32 = x;
   e2.out_h = xb;
   e2.ldc = kDT;
   e2.pe = w.pe;
   e2.n_win = n_win;
   e2.out_stride = Tp;
-  const RowSpace rows_conv = {lb.n, (int)N, Np, (int64_t)(N + 2) * c.c_mid};
+  const RowSpace rows_conv = {n_layers, (int)N, Np, (int64_t)(N + 2) * c.c_mid};
   PKV_TRY((launch_gemm<kEpiGeluPeWin, 256, 256>(h1, c.c_mid, w.conv2_w, rows_conv, kDT, 3 * c.c_mid, e2, n_cu, stream)));
 
   // stage 2 (the stem's epilogue has written its input rows)
@@ -978,14 +891,33 @@ hipError_t mapper_batch(proxykv_ctx* ctx, const MapPlan& p, const LayerBatch& lb
   e3.p0 = w.kv_b;
   e3.p1 = w.queries;
   e3.g = w.out_w;
-  e3.out_f32 = s3;
+  e3.out_f32 = (float*)m.s3.ptr;
   e3.ldc = (c.H_l + 1) * c.H_kv;
   e3.n_slot = c.H_kv;
   e3.n_head = c.H_l;
-  const RowSpace rows_N = {lb.n, (int)N, Np, (int64_t)Np * kDT};
-  PKV_TRY((launch_gemm<kEpiStage3, 256, 256>(zg, kDT, w.kv_w, rows_N, nkv, kDT, e3, n_cu, stream)));
+  const RowSpace rows_N = {n_layers, (int)N, Np, (int64_t)Np * kDT};
+  return launch_gemm<kEpiStage3, 256, 256>(zg, kDT, w.kv_w, rows_N, nkv, kDT, e3, n_cu, stream);
+}
+
+// The network for the layers of one batch (x_in: all proxy layers' scores [L_s, H_kv, N]); writes the rows of every target
+// layer that is paired with one of them.
+hipError_t mapper_batch(proxykv_ctx* ctx, const MapPlan& p, const LayerBatch& lb, const float* x_in, int64_t N, float* yhat,
+                        int n_cu, hipStream_t stream) {
+  const proxykv_config& c = ctx->cfg;
+  const MapperWeights& w = ctx->w;
+  const MapperWorkspace& m = ctx->m;
+  uint32_t* range = (uint32_t*)m.range.ptr;
+  const unsigned nl = (unsigned)lb.n;
+  absmax_kernel<<<dim3(kRangeWords, nl), 1024, 0, stream>>>(x_in, (int64_t)c.H_kv * N, lb, range);
+  PKV_TRY(hipGetLastError());
+  const int tok = (int64_t)nl * N >= 64 * 512 ? kStemTok : 16;
+  stem_conv1_kernel<<<dim3((unsigned)((N + tok - 1) / tok), nl), 256, 0, stream>>>(
+      x_in, w.conv1_w, w.bn1_scale, w.bn1_shift, range, w.stem_cw, w.stem_cs, lb, (uint16_t*)m.h1.ptr, c.H_kv, (int)N, c.c_mid, tok);
+  PKV_TRY(hipGetLastError());
+  if (p.small) PKV_TRY(mapper_small_body(ctx, p, lb.n, N, stream));
+  else PKV_TRY(mapper_large_body(ctx, p, lb.n, N, n_cu, stream));
   const int tok_per_block = 256 / c.H_l;
-  stage3_kernel<<<dim3((unsigned)((N + tok_per_block - 1) / tok_per_block), nl), 256, 0, stream>>>(s3, w.out_b, yhat, N, Np,
+  stage3_kernel<<<dim3((unsigned)((N + tok_per_block - 1) / tok_per_block), nl), 256, 0, stream>>>((const float*)m.s3.ptr, w.out_b, yhat, N, (int)p.Np,
                                                                                                 c.H_kv, c.H_l, lb);
   return hipGetLastError();
 }
