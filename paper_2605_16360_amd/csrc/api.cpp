@@ -525,7 +525,7 @@ int proxykv_topk(proxykv_ctx* ctx, const float* scores, int64_t rows, int64_t N,
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
   const int rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes(rows, N), (hipStream_t)stream);
   if (rc) return rc;
-  PKV_HIP(ctx, pkv::launch_topk(scores, rows, N, K, idx_out, ctx->topk_ws.ptr, (hipStream_t)stream));
+  PKV_HIP(ctx, pkv::launch_topk(scores, rows, N, K, idx_out, ctx->topk_ws.ptr, ctx->topk_ws.bytes, (hipStream_t)stream));
   return PROXYKV_OK;
 }
 
@@ -558,7 +558,7 @@ int proxykv_topk_pooled(proxykv_ctx* ctx, const float* scores, int64_t layers, i
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
   const int rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes(layers, heads * N), (hipStream_t)stream);
   if (rc) return rc;
-  PKV_HIP(ctx, pkv::launch_topk(scores, layers, heads * N, heads * K, flat_out, ctx->topk_ws.ptr, (hipStream_t)stream));
+  PKV_HIP(ctx, pkv::launch_topk(scores, layers, heads * N, heads * K, flat_out, ctx->topk_ws.ptr, ctx->topk_ws.bytes, (hipStream_t)stream));
   PKV_HIP(ctx, pkv::launch_head_counts(flat_out, layers, heads, N, K, counts_out, (hipStream_t)stream));
   return PROXYKV_OK;
 }
@@ -608,9 +608,9 @@ int proxykv_prune(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const 
     // selection and gather in one launch: the workgroup that has written a stretch of a row's kept indices moves those
     // tokens' K and V rows; the whole launch is booked as the compaction stage
     if ((rc = mark(ctx, 4, s))) return rc;
-    PKV_HIP(ctx, pkv::launch_topk_gather(y, rows, N, K, idx_out, ctx->topk_ws.ptr, k_in, v_in, (int64_t)c.D * 2, k_out, v_out, s));
+    PKV_HIP(ctx, pkv::launch_topk_gather(y, rows, N, K, idx_out, ctx->topk_ws.ptr, ctx->topk_ws.bytes, k_in, v_in, (int64_t)c.D * 2, k_out, v_out, s));
   } else {
-    PKV_HIP(ctx, pkv::launch_topk(y, rows, N, K, idx_out, ctx->topk_ws.ptr, s));
+    PKV_HIP(ctx, pkv::launch_topk(y, rows, N, K, idx_out, ctx->topk_ws.ptr, ctx->topk_ws.bytes, s));
     if ((rc = mark(ctx, 4, s))) return rc;
     PKV_HIP(ctx, pkv::launch_compact(k_in, v_in, idx_out, rows, N, K, (int64_t)c.D * 2, k_out, v_out, s));
   }

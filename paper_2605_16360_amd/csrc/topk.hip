@@ -1,12 +1,18 @@
 // Per-row Top-K selection (paper Sec. 3: the mask keeps the Top-K of the mapped scores per target
 // layer and head; Sec. 4.3 names a Top-K kernel that materialises it).  Integer work only: scores
-// are turned into order-preserving 32-bit keys, the K-th largest key is found by an 8-bit radix select
-// (at most four passes) on the keys relative to the row's smallest key, and one more ordered pass emits the kept indices in ascending order, taking
-// equal keys by lower index.  A row of up to 36 864 scores is read from global memory once and its keys stay in
-// registers for all passes.  A longer row is split into parts of at most 36 864 scores, one workgroup each, so that
-// few long rows still fill the chip: four launches of an 8-bit radix pass on the raw keys whose per-part histograms
-// meet in a per-row histogram in device scratch memory (the last workgroup of a row to arrive picks the digit), then
-// one launch that writes every part's kept indices behind those of the parts before it.
+// are turned into order-preserving 32-bit keys, the K-th largest key is found by a radix select, and one more ordered
+// pass emits the kept indices in ascending order, taking equal keys by lower index.
+//
+// Every kernel reads a row in chunks of 4096 scores, four consecutive ones per thread: a wave's load is 1 KB in one piece
+// (36 consecutive scores per thread, which makes the ordered output a plain prefix sum over the threads, reads 64 lines
+// per load instead of 8 and took 44 us for 256 rows of 32 768 against 26 us).  The order of the output is kept
+// by counting per (chunk, wave) and ranking inside a wave with ballots, so that stores too lie side by side.
+//
+// A row of up to 36 864 scores is one workgroup's, its keys stay in registers for all passes.  A longer row is split into
+// parts, one workgroup each, so that few long rows still fill the chip: three launches of an 11-bit radix pass on the raw
+// keys whose per-part histograms meet in a per-row histogram in device scratch memory (the last workgroup of a row to
+// arrive picks the digit), then one launch that writes every part's kept indices behind those of the parts before it.
+// Where the scratch memory is too small for 2048-bin histograms the same kernels run four passes of 8 bits.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -16,47 +22,160 @@ namespace {
 constexpr int kTopkThreads = 1024;
 constexpr int kTopkWaves = kTopkThreads / 64;
 
-// Larger key <=> earlier in the selection order.  NaN maps to 0 (below -inf), -0.0 onto +0.0.
+// Larger key <=> earlier in the selection order.  NaN maps to 0 (below -inf), -0.0 onto +0.0 (-0.0 + 0.0 = +0.0).
 __device__ __forceinline__ uint32_t order_key(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return 0u;
-  if (u == 0x80000000u) u = 0u;
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t u = __float_as_uint(f + 0.0f);
+  const uint32_t k = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);
+  return f == f ? k : 0u;
+}
+// The score of a key other than 0: score > that float <=> key above it, and NaN is neither above nor equal.
+__device__ __forceinline__ float key_score(uint32_t k) {
+  return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k);
 }
 
-// ---------------------------------------------------------------------------------------------
-// Rows of up to kTopkRegMax scores: thread t keeps the keys of the kTopkItems consecutive scores
-// [t * kTopkItems, (t + 1) * kTopkItems) in registers, so the row is read from memory once, every radix
-// pass runs on registers, and the ordered output needs one prefix sum over the threads' kept counts
-// instead of one per tile.  The K-th largest key is found on the keys relative to the row's smallest key, top-aligned
-// to the width of the range: digits of the raw key are badly skewed (scores share sign and exponent) and lanes that
-// add to the same LDS counter are serialised; digits of the range-relative key are spread over all 256 bins.
-// ---------------------------------------------------------------------------------------------
-constexpr int kTopkItems = 36;
-constexpr int kTopkRegMax = kTopkItems * kTopkThreads;
-static_assert(kTopkRegMax == kTopkSingleMax, "kernels.hpp states the longest single-workgroup row");
+// Four scores at row[i], ..., row[i + 3], those at or past `hi` read as NaN (never out of bounds).  `vec`: the row starts on a
+// 16-byte boundary (i is a multiple of four).
+__device__ __forceinline__ f32x4 load_quad(const float* row, int i, int hi, bool vec) {
+  if (vec && i + 4 <= hi) return *reinterpret_cast<const f32x4*>(row + i);
+  f32x4 v;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = i + j < hi ? row[i + j] : __builtin_nanf("");
+  return v;
+}
+constexpr int kChunk = 4 * kTopkThreads;
 
-// exclusive prefix sum of one value per thread over the workgroup (16 waves); also returns the total
-__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* wave_tot, int wave, int lane, uint32_t& total) {
+__device__ __forceinline__ uint32_t lanes_below(uint64_t mask, uint32_t add) {
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, add));
+}
+// inclusive prefix sum over the wave within the vector ALU: four steps inside rows of 16 lanes, then the row totals
+__device__ __forceinline__ uint32_t wave_inclusive_scan(uint32_t v) {
+  auto add = [&](auto ctrl, auto rows) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xf, true);
+  };
+  add(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xf>{});  // row_shr 1
+  add(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xf>{});  // row_shr 2
+  add(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xf>{});  // row_shr 4
+  add(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xf>{});  // row_shr 8
+  add(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xa>{});  // row_bcast 15 into rows 1 and 3
+  add(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xc>{});  // row_bcast 31 into rows 2 and 3
+  return v;
+}
+__device__ __forceinline__ uint32_t wave_total(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(v), 63);
+}
+// Ordered output of a wave's scores: quad q of lane l holds the scores 256 q + 4 l .. +3 of the wave's stretch, whose first has
+// index i0.  Kept: scores above the threshold (bit 4 q + j of m_gt), and those equal to it (m_eq) of which fewer than
+// eq_take equal ones lie in front; gt and eq count the scores above and equal in front of the stretch.  A kept one goes to
+// out[kept ones in front of it].  Loops are left rolled: this code runs once per wave, and straight-line code of 25 KB
+// spends its time on instruction fetch (112 rows of 170 000 scores: 31 us without any load or store).
+__device__ __forceinline__ void wave_write(uint64_t m_gt, uint64_t m_eq, int quads, uint32_t gt, uint32_t eq, uint32_t eq_take,
+                                           int i0, int lane, int32_t* out) {
+  const bool any_eq = __builtin_amdgcn_ballot_w64(m_eq != 0) != 0;
+  int i = i0 + 4 * lane;
+#pragma unroll 1
+  for (int q = 0; q < quads; ++q, i += 256) {
+    const uint32_t bg = (uint32_t)m_gt & 15u;
+    m_gt >>= 4;
+    const uint32_t n = (uint32_t)__popc(bg), inc = wave_inclusive_scan(n);
+    uint32_t pos = gt + inc - n + (eq < eq_take ? eq : eq_take);
+    gt += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+    if (!any_eq) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t b = (bg >> j) & 1u;
+        if (b) out[pos] = i + j;
+        pos += b;
+      }
+    } else {
+      const uint32_t be = (uint32_t)m_eq & 15u;
+      m_eq >>= 4;
+      const uint32_t ne = (uint32_t)__popc(be), ince = wave_inclusive_scan(ne);
+      uint32_t g = pos - (eq < eq_take ? eq : eq_take), e = eq + ince - ne;  // scores above, and equal ones, in front
+      eq += (uint32_t)__builtin_amdgcn_readlane((int)ince, 63);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const bool is_g = (bg >> j) & 1u, is_e = (be >> j) & 1u;
+        if (is_g || (is_e && e < eq_take)) out[g + (e < eq_take ? e : eq_take)] = i + j;
+        g += is_g;
+        e += is_e;
+      }
+    }
+  }
+}
+// bits of a quad's scores above and equal to the threshold: t = key_score(T), or any number with nan_t where T is the key
+// of NaN (then every number lies above it and NaNs are equal to it).  `valid`: scores of the quad that exist.
+__device__ __forceinline__ void quad_bits(const f32x4& v, int valid, float t, bool nan_t, uint32_t& bg, uint32_t& be) {
+  bg = 0;
+  be = 0;
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    bg |= (uint32_t)(nan_t ? v[j] == v[j] : v[j] > t) << j;
+    be |= (uint32_t)(nan_t ? v[j] != v[j] : v[j] == t) << j;
+  }
+  const uint32_t m = valid >= 4 ? 15u : (valid > 0 ? (1u << valid) - 1u : 0u);
+  bg &= m;
+  be &= m;
+}
+
+// sum over the workgroup of one value per thread; `part`: kTopkWaves words of LDS, free again after the call
+__device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* part, int tid) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  if ((tid & 63) == 0) part[tid >> 6] = v;
+  __syncthreads();
+  uint32_t t = 0;
+#pragma unroll
+  for (int w = 0; w < kTopkWaves; ++w) t += part[w];
+  __syncthreads();
+  return t;
+}
+
+// exclusive prefix sum of one value per thread over the workgroup; `part` as in block_sum
+__device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* part, int wave, int lane) {
   uint32_t inc = v;
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
     const uint32_t t = __shfl_up(inc, off, 64);
     if (lane >= off) inc += t;
   }
-  if (lane == 63) wave_tot[wave] = inc;
+  if (lane == 63) part[wave] = inc;
   __syncthreads();
-  uint32_t before = 0, tot = 0;
+  uint32_t before = inc - v;
 #pragma unroll
-  for (int w = 0; w < kTopkWaves; ++w) {
-    const uint32_t t = wave_tot[w];
-    if (w < wave) before += t;
-    tot += t;
-  }
+  for (int w = 0; w < kTopkWaves; ++w) before += w < wave ? part[w] : 0u;
   __syncthreads();
-  total = tot;
-  return before + inc - v;
+  return before;
 }
+
+// The digit that holds the krem-th largest key, from the counts of kDigits bins, thread t holding the kPer bins
+// kDigits - 1 - t * kPer, ... in descending order (cnt zero for threads without bins): calls found(digit, krem left) in
+// one thread.
+template <int kDigits, int kPer, class F>
+__device__ __forceinline__ void pick_digit(const uint32_t (&cnt)[kPer], uint32_t krem, uint32_t* part, int tid, F&& found) {
+  uint32_t own = 0;
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) own += cnt[i];
+  uint32_t above = block_exclusive_scan(own, part, tid >> 6, tid & 63);
+#pragma unroll
+  for (int i = 0; i < kPer; ++i) {
+    if (above < krem && krem <= above + cnt[i]) found((uint32_t)(kDigits - 1 - (tid * kPer + i)), krem - above);
+    above += cnt[i];
+  }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Rows of up to kTopkRegMax scores: the workgroup keeps the row's keys in registers, so the row is read from memory once
+// and every radix pass runs on registers: 11, 11 and 10 bits of the raw key.  The first digit holds the sign, the exponent
+// and two bits of mantissa, so scores of a row hit a few dozen of its 2048 bins; eight copies of every bin side by side,
+// one per lane modulo eight, keep the lanes of a wave off each other's words.  (8-bit digits of the key's distance from
+// the row's smallest, a histogram per wave: 28 us of the kernel's 44 in the passes where scores change sign, since the
+// positive ones then share two or three bins.)  Wave w owns the scores [w * kRegSeg, (w + 1) * kRegSeg).
+// ---------------------------------------------------------------------------------------------
+constexpr int kTopkChunks = 9;                     // quads per thread
+constexpr int kRegSeg = kTopkChunks * 256;
+constexpr int kTopkRegMax = kTopkWaves * kRegSeg;
+static_assert(kTopkRegMax == kTopkSingleMax, "kernels.hpp states the longest single-workgroup row");
+constexpr int kRegCopies = 8;
 
 // Ordered gather of the token rows a workgroup has just selected (the mask applied to the target's cache, Sec. 4.3):
 // dst[j, :] = src[list[j], :] for j in [j_lo, j_hi), K and V together.  `list` was written by this workgroup before
@@ -102,140 +221,85 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
                                                                 int32_t* __restrict__ idx_out, GatherArgs ga) {
   const float* row = scores + (size_t)blockIdx.x * N;
   int32_t* out = idx_out + (size_t)blockIdx.x * K;
-  __shared__ uint32_t hist[kTopkWaves][256];
-  __shared__ uint32_t tot[2][256];
+  __shared__ __attribute__((aligned(16))) uint32_t hist[2048 * kRegCopies];
+  __shared__ uint32_t wave_part[kTopkWaves], wave_eq[kTopkWaves];
   __shared__ uint32_t s_prefix, s_krem;
-  __shared__ uint32_t wave_a[kTopkWaves], wave_b[kTopkWaves];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int i0 = tid * kTopkItems;
+  const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
+  const int i0 = wave * kRegSeg + 4 * lane;  // index of the thread's first quad; the next ones follow 256 apart
 
-  // keys of this thread's scores; positions at and past N hold the key 0 and are never counted
-  uint32_t key[kTopkItems];
-  if ((reinterpret_cast<uintptr_t>(row) & 15) == 0 && i0 + kTopkItems <= N) {
+  // keys of this thread's scores; those at and past N hold a key that no score has (the largest, +inf's, is 0xff800000)
+  constexpr uint32_t kNoKey = 0xffffffffu;
+  uint32_t key[kTopkChunks][4];
 #pragma unroll
-    for (int j = 0; j < kTopkItems; j += 4) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(row + i0 + j);
-      key[j] = order_key(v[0]);
-      key[j + 1] = order_key(v[1]);
-      key[j + 2] = order_key(v[2]);
-      key[j + 3] = order_key(v[3]);
-    }
-  } else {
+  for (int c = 0; c < kTopkChunks; ++c) {
+    const f32x4 v = load_quad(row, i0 + c * 256, N, vec);
 #pragma unroll
-    for (int j = 0; j < kTopkItems; ++j) key[j] = i0 + j < N ? order_key(row[i0 + j]) : 0u;
+    for (int j = 0; j < 4; ++j) key[c][j] = i0 + c * 256 + j < N ? order_key(v[j]) : kNoKey;
   }
-  const int mine = N - i0 < 0 ? 0 : (N - i0 < kTopkItems ? N - i0 : kTopkItems);  // valid items of this thread
 
-  // the first pass's histograms (one per wave) are cleared under the barrier of the range reduction
-  for (int i = tid; i < kTopkWaves * 256; i += kTopkThreads) (&hist[0][0])[i] = 0;
-  uint32_t kmin = 0xffffffffu, kmax = 0u;
-#pragma unroll
-  for (int j = 0; j < kTopkItems; ++j) {
-    if (j < mine) {
-      kmin = key[j] < kmin ? key[j] : kmin;
-      kmax = key[j] > kmax ? key[j] : kmax;
-    }
-  }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const uint32_t a = __shfl_xor(kmin, off, 64), c = __shfl_xor(kmax, off, 64);
-    kmin = a < kmin ? a : kmin;
-    kmax = c > kmax ? c : kmax;
-  }
-  if (lane == 0) {
-    wave_a[wave] = kmin;
-    wave_b[wave] = kmax;
-  }
-  __syncthreads();
-#pragma unroll
-  for (int w = 0; w < kTopkWaves; ++w) {
-    kmin = wave_a[w] < kmin ? wave_a[w] : kmin;
-    kmax = wave_b[w] > kmax ? wave_b[w] : kmax;
-  }
-  const uint32_t span = kmax - kmin;
-  int prev_sh = span == 0 ? 0 : 32 - __builtin_clz(span);
-
-  // Pass p counts into tot[p & 1].  First pass: every key counts, one histogram per wave keeps lanes of different waves
-  // off the same counter, and their sum goes to tot[0].  Later passes: only the keys under the prefix (a 256th of the
-  // row per pass) count, straight into tot[p & 1], which was cleared while the pass before picked its digit.
+  uint32_t* mine = hist + (lane & (kRegCopies - 1));
   uint32_t prefix = 0, krem = (uint32_t)K;
-  int pass = 0;
-  while (prev_sh > 0) {
-    const int shift = prev_sh > 8 ? prev_sh - 8 : 0;
-    const uint32_t dmask = (1u << (prev_sh - shift)) - 1u;
-    uint32_t* cur = tot[pass & 1];
-    if (pass == 0) {
+#pragma unroll 1
+  for (int hi_bit = 32; hi_bit > 0; hi_bit -= 11) {  // 11, 11 and 10 bits; rolled, like everything that runs once per wave
+    const int shift = hi_bit > 11 ? hi_bit - 11 : 0;
+    const uint32_t dmask = (1u << (hi_bit - shift)) - 1u;
+    const uint32_t high = hi_bit == 32 ? 0u : ~0u << hi_bit, want = hi_bit == 32 ? 0u : prefix << hi_bit;
 #pragma unroll
-      for (int j = 0; j < kTopkItems; ++j)
-        if (j < mine) atomicAdd(&hist[wave][((key[j] - kmin) >> shift) & dmask], 1u);
-      __syncthreads();
-      if (tid < 256) {
-        uint32_t sum = 0;
-#pragma unroll
-        for (int w = 0; w < kTopkWaves; ++w) sum += hist[w][tid];
-        cur[tid] = sum;
-      }
-    } else {
-#pragma unroll
-      for (int j = 0; j < kTopkItems; ++j) {
-        const uint32_t rel = key[j] - kmin;
-        if (j < mine && (rel >> prev_sh) == prefix) atomicAdd(&cur[(rel >> shift) & dmask], 1u);
-      }
-    }
+    for (int i = 0; i < 2048 * kRegCopies / 4 / kTopkThreads; ++i) reinterpret_cast<u32x4*>(hist)[tid + i * kTopkThreads] = u32x4{0, 0, 0, 0};
     __syncthreads();
-    if (tid < 256) tot[(pass + 1) & 1][tid] = 0;
-    if (wave == 0) {
-      const uint32_t c0 = cur[4 * lane], c1 = cur[4 * lane + 1], c2 = cur[4 * lane + 2], c3 = cur[4 * lane + 3];
-      const uint32_t own = c0 + c1 + c2 + c3;
-      uint32_t v = own;
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t t = __shfl_down(v, off, 64);
-        if (lane + off < 64) v += t;
-      }
-      const uint32_t a3 = v - own, a2 = a3 + c3, a1 = a2 + c2, a0 = a1 + c1;
-      const uint32_t above[4] = {a0, a1, a2, a3};
-      const uint32_t cnt[4] = {c0, c1, c2, c3};
+    for (int c = 0; c < kTopkChunks; ++c)
 #pragma unroll
-      for (int bsel = 0; bsel < 4; ++bsel) {
-        if (above[bsel] < krem && krem <= above[bsel] + cnt[bsel]) {
-          s_prefix = (prefix << (prev_sh - shift)) | (uint32_t)(4 * lane + bsel);
-          s_krem = krem - above[bsel];
-        }
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t k = key[c][j];
+        if ((k & high) == want) atomicAdd(&mine[((k >> shift) & dmask) * kRegCopies], 1u);
       }
+    __syncthreads();
+    uint32_t cnt[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const u32x4* h = reinterpret_cast<const u32x4*>(hist + (2047 - (tid * 2 + i)) * kRegCopies);
+      const u32x4 a = h[0], b = h[1];
+      cnt[i] = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
     }
+    if (hi_bit == 32 && tid == 0) cnt[0] = 0;  // kNoKey's bin
+    pick_digit<2048, 2>(cnt, krem, wave_part, tid, [&](uint32_t d, uint32_t left) {
+      s_prefix = prefix << (hi_bit - shift) | d;
+      s_krem = left;
+    });
     __syncthreads();
     prefix = s_prefix;
     krem = s_krem;
-    prev_sh = shift;
-    ++pass;
   }
-  const uint32_t T = prefix + kmin, eq_take = krem;
+  const uint32_t T = prefix, eq_take = krem;
 
-  // kept: keys above T, and the eq_take lowest-index keys equal to T.  One prefix sum over the threads carries both
-  // counts (each at most 36 864, so 16 bits apiece): the kept equal keys before a thread are min(equal before, eq_take).
-  uint32_t n_gt = 0, n_eq = 0;
+  // kept: keys above T, and the eq_take lowest-index keys equal to T
+  uint64_t m_gt = 0, m_eq = 0;
 #pragma unroll
-  for (int j = 0; j < kTopkItems; ++j) {
-    if (j < mine) {
-      n_gt += key[j] > T;
-      n_eq += key[j] == T;
-    }
-  }
-  static_assert(kTopkRegMax < 65536, "two 16-bit counts share one prefix sum");
-  uint32_t both_total;
-  const uint32_t both = block_exclusive_scan((n_gt << 16) | n_eq, wave_a, wave, lane, both_total);
-  const uint32_t eq_before = both & 0xffffu, gt_before = both >> 16;
-  uint32_t pos = gt_before + (eq_before < eq_take ? eq_before : eq_take);
-  uint32_t eq_left = eq_before >= eq_take ? 0u : (eq_take - eq_before < n_eq ? eq_take - eq_before : n_eq);
+  for (int c = 0; c < kTopkChunks; ++c) {
+    uint32_t bg = 0, be = 0;
 #pragma unroll
-  for (int j = 0; j < kTopkItems; ++j) {
-    if (j < mine) {
-      const bool take = key[j] > T || (key[j] == T && eq_left > 0);
-      if (key[j] == T && eq_left > 0) --eq_left;
-      if (take) out[pos++] = i0 + j;
+    for (int j = 0; j < 4; ++j) {
+      bg |= (uint32_t)(key[c][j] > T && key[c][j] != kNoKey) << j;
+      be |= (uint32_t)(key[c][j] == T) << j;
     }
+    m_gt |= (uint64_t)bg << (4 * c);
+    m_eq |= (uint64_t)be << (4 * c);
   }
+  const uint32_t n_gt = wave_total((uint32_t)__popcll(m_gt)), n_eq = wave_total((uint32_t)__popcll(m_eq));
+  if (lane == 0) {
+    wave_part[wave] = n_gt;
+    wave_eq[wave] = n_eq;
+  }
+  __syncthreads();
+  uint32_t gt = 0, eq = 0;  // in front of the wave's scores
+#pragma unroll
+  for (int w = 0; w < kTopkWaves; ++w) {
+    gt += w < wave ? wave_part[w] : 0u;
+    eq += w < wave ? wave_eq[w] : 0u;
+  }
+  wave_write(m_gt, m_eq, kTopkChunks, gt, eq, eq_take, wave * kRegSeg, lane, out);
   if constexpr (GATHER) {
     __syncthreads();  // the row's list is complete and visible to the whole workgroup
     gather_rows(ga, (size_t)blockIdx.x * N * ga.cpr, (size_t)blockIdx.x * K * ga.cpr, out, 0, K, tid);
@@ -243,248 +307,276 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rows longer than kTopkRegMax are cut into parts of at most kMwPartMax = 45 056 scores (170 000 scores: four parts,
-// so that 112 rows are 448 workgroups, one round on 256 CUs); part p of a row (thread t keeps the keys of the
-// consecutive scores [p * part_len + t * kMwItems, + kMwItems) in registers) is one workgroup.  Scratch memory per row (32-bit words):
-//   [0, 16)                      state: prefix, krem, then one arrival counter per pass at [4 + pass]
-//   [16, 16 + 4 * 256)           the row's histogram of every pass
-//   [1040, 1040 + parts * 257)   per part: its histogram of the last pass (256), then its number of keys above the
-//                                24-bit prefix that the last pass starts from
-// mw_init_kernel clears the first 1040 words of every row; the per-part words are all written by pass 3.
-// Pass `pass` takes the digit (key >> (24 - 8 * pass)) & 255 of the keys whose higher bits equal the prefix found so
-// far; the workgroup that arrives last at the row's counter has every part's contribution in the row's histogram
-// (each part adds its bins, fences, then takes its ticket) and picks the bin that holds the krem-th largest key.
+// Rows longer than kTopkRegMax are cut into parts of at most kMwPartMax = 45 056 scores, one workgroup each.
+// Scratch memory per row (32-bit words), B = 2^BITS bins, P passes:
+//   [0, 16)                          state: prefix, krem, then one arrival counter per pass at [4 + pass]
+//   [16, 16 + P * B)                 the row's histogram of every pass
+//   [16 + P * B, ... )               per part, for every digit of the last pass and one past them: its number of keys under
+//                                    the prefix with at least that digit plus its keys above the prefix
+// mw_init_kernel clears the first 16 + P * B words of every row; the per-part words are all written by the last pass.
+// A pass takes the next BITS bits of the keys whose higher bits equal the prefix found so far; the workgroup that arrives
+// last at the row's counter has every part's contribution in the row's histogram and picks the bin that holds the krem-th
+// largest key.
+// Eleven bits: three passes instead of four, and the first digit (sign, exponent, two bits of mantissa) spreads scores
+// that share an exponent over four bins.  112 rows of 170 000 scores: 87 us in all, with 8 bits and scores read by thread 222 us.
 // ---------------------------------------------------------------------------------------------
-constexpr int kMwItems = 44, kMwPartMax = kMwItems * kTopkThreads;  // scores per thread and per part
-constexpr int kMwStateWords = 16, kMwRowFixedWords = kMwStateWords + 4 * 256, kMwPartWords = 257;
+constexpr int kMwQuads = 11, kMwPartMax = kMwQuads * 256 * kTopkWaves;  // quads per lane and scores per part
+constexpr int kMwStateWords = 16;
 
+template <int BITS>
+struct Mw {
+  static constexpr int kBins = 1 << BITS;
+  static constexpr int kPasses = (32 + BITS - 1) / BITS;
+  static constexpr int kLastBits = 32 - (kPasses - 1) * BITS;
+  static constexpr int kFixedWords = kMwStateWords + kPasses * kBins;
+  static constexpr int kPartWords = (1 << kLastBits) + 1;
+  // Copies of the LDS histogram, one per lane modulo kCopies and side by side, so that lanes that hit one bin (scores of
+  // a row share sign and exponent) hit different words and banks.
+  static constexpr int kCopies = BITS == 8 ? 16 : 8;
+};
+
+template <int BITS>
 __global__ void mw_init_kernel(uint32_t* __restrict__ scratch, int rows, int row_words, int K) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (gid >= (int64_t)rows * kMwRowFixedWords) return;
-  const int r = (int)(gid / kMwRowFixedWords), w = (int)(gid % kMwRowFixedWords);
+  if (gid >= (int64_t)rows * Mw<BITS>::kFixedWords) return;
+  const int r = (int)(gid / Mw<BITS>::kFixedWords), w = (int)(gid % Mw<BITS>::kFixedWords);
   scratch[(size_t)r * row_words + w] = (w == 1) ? (uint32_t)K : 0u;  // word 0: prefix, word 1: krem
 }
 
-// keys of part `part` of the row in registers; positions at and past the part's end hold key 0 and are never counted
-__device__ __forceinline__ int mw_load_keys(const float* row, int N, int part_len, int part, int tid, uint32_t (&key)[kMwItems],
-                                            int& i0) {
-  const int lo = part * part_len, hi = lo + part_len < N ? lo + part_len : N;
-  i0 = lo + tid * kMwItems;
-  if ((reinterpret_cast<uintptr_t>(row + i0) & 15) == 0 && i0 + kMwItems <= hi) {
-#pragma unroll
-    for (int j = 0; j < kMwItems; j += 4) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(row + i0 + j);
-      key[j] = order_key(v[0]);
-      key[j + 1] = order_key(v[1]);
-      key[j + 2] = order_key(v[2]);
-      key[j + 3] = order_key(v[3]);
-    }
-  } else {
-#pragma unroll
-    for (int j = 0; j < kMwItems; ++j) key[j] = i0 + j < hi ? order_key(row[i0 + j]) : 0u;
-  }
-  return hi - i0 < 0 ? 0 : (hi - i0 < kMwItems ? hi - i0 : kMwItems);
-}
-
 // grid (parts, rows)
+template <int BITS, int PASS>
 __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __restrict__ scores, int N, int part_len,
-                                                               int pass, uint32_t* __restrict__ scratch, int row_words) {
+                                                               uint32_t* __restrict__ scratch, int row_words) {
+  using C = Mw<BITS>;
+  constexpr int kHi = 32 - BITS * PASS, kShift = kHi > BITS ? kHi - BITS : 0, kDigitBins = 1 << (kHi - kShift);
+  constexpr bool kLast = PASS == C::kPasses - 1;
   const int part = blockIdx.x, parts = gridDim.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const float* row = scores + (size_t)blockIdx.y * N;
   uint32_t* rs = scratch + (size_t)blockIdx.y * row_words;
-  __shared__ uint32_t hist[kTopkWaves][256];
-  __shared__ uint32_t tot[256];
-  __shared__ uint32_t s_last, wave_hi[kTopkWaves];
-  uint32_t key[kMwItems];
-  int i0;
-  const int mine = mw_load_keys(row, N, part_len, part, tid, key, i0);
-  const uint32_t prefix = rs[0];  // the bits above `shift + 8` of the K-th largest key (written by the previous launch)
-  const int shift = 24 - 8 * pass;
-  for (int i = tid; i < kTopkWaves * 256; i += kTopkThreads) (&hist[0][0])[i] = 0;
+  uint32_t* row_hist = rs + kMwStateWords + PASS * C::kBins;
+  __shared__ __attribute__((aligned(16))) uint32_t hist[C::kBins * C::kCopies];
+  __shared__ uint32_t wave_part[kTopkWaves];
+  __shared__ uint32_t s_last;
+  const int lo = part * part_len, len = N - lo < part_len ? N - lo : part_len;
+  row += lo;
+  const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
+  const uint32_t prefix = rs[0];  // the bits above kHi of the K-th largest key (written by the previous launch)
+  for (int i = tid; i < C::kBins * C::kCopies / 4; i += kTopkThreads) reinterpret_cast<u32x4*>(hist)[i] = u32x4{0, 0, 0, 0};
   __syncthreads();
   uint32_t n_hi = 0;  // last pass: keys above the prefix
+  uint32_t* mine = hist + (lane & (C::kCopies - 1));
+  for (int c0 = 0; c0 < len; c0 += 4 * kChunk) {  // four chunks in flight
+    f32x4 v[4];
 #pragma unroll
-  for (int j = 0; j < kMwItems; ++j) {
-    const bool valid = j < mine;
-    const bool match = valid && (pass == 0 || (key[j] >> (shift + 8)) == prefix);
-    const uint32_t digit = (key[j] >> shift) & 255u;
-    // scores of one row share sign and exponent, so in the first passes most lanes of a wave hit one counter: a wave
-    // whose matching lanes all carry the same digit adds their number once
-    const uint64_t bm = __builtin_amdgcn_ballot_w64(match);
-    if (bm != 0) {
-      const uint32_t d0 = __builtin_amdgcn_readlane(digit, __builtin_ctzll(bm));
-      const uint64_t same = __builtin_amdgcn_ballot_w64(match && digit == d0);
-      if (same == bm) {
-        if (lane == (int)__builtin_ctzll(bm)) atomicAdd(&hist[wave][d0], (uint32_t)__popcll(bm));
-      } else if (match) {
-        atomicAdd(&hist[wave][digit], 1u);
+    for (int u = 0; u < 4; ++u) v[u] = load_quad(row, c0 + u * kChunk + 4 * tid, len, vec);
+    auto count = [&](bool valid, float f) {
+      const uint32_t key = order_key(f);
+      if constexpr (PASS == 0) {
+        if (valid) atomicAdd(&mine[(key >> kShift) * C::kCopies], 1u);
+      } else {
+        const uint32_t top = key >> (kHi & 31);
+        if (valid && top == prefix) atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
+        if (kLast) n_hi += valid && top > prefix;
       }
+    };
+    if (c0 + 4 * kChunk <= len) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) count(true, v[u][j]);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) count(c0 + u * kChunk + 4 * tid + j < len, v[u][j]);
     }
-    if (pass == 3) n_hi += valid && (key[j] >> 8) > prefix;
   }
   __syncthreads();
-  if (tid < 256) {
+  // thread t holds bins kDigitBins - 1 - t, ... (descending)
+  uint32_t n_hi_all = 0;
+  if (kLast) n_hi_all = block_sum(n_hi, wave_part, tid);
+  uint32_t last_sum = 0;
+  for (int t = tid; t < kDigitBins; t += kTopkThreads) {
+    const int b = kDigitBins - 1 - t;
     uint32_t sum = 0;
 #pragma unroll
-    for (int w = 0; w < kTopkWaves; ++w) sum += hist[w][tid];
-    if (sum) atomicAdd(&rs[kMwStateWords + pass * 256 + tid], sum);
-    if (pass == 3) rs[kMwRowFixedWords + part * kMwPartWords + tid] = sum;
-  }
-  if (pass == 3) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) n_hi += __shfl_xor(n_hi, off, 64);
-    if (lane == 0) wave_hi[wave] = n_hi;
-    __syncthreads();
-    if (tid == 0) {
-      uint32_t t = 0;
-#pragma unroll
-      for (int w = 0; w < kTopkWaves; ++w) t += wave_hi[w];
-      rs[kMwRowFixedWords + part * kMwPartWords + 256] = t;
+    for (int i = 0; i < C::kCopies; i += 4) {
+      const u32x4 h = *reinterpret_cast<const u32x4*>(hist + b * C::kCopies + i);
+      sum += (h[0] + h[1]) + (h[2] + h[3]);
     }
+    if (sum) atomicAdd(&row_hist[b], sum);
+    last_sum = sum;  // the last pass has at most one bin per thread
+  }
+  if constexpr (kLast) {
+    static_assert(kDigitBins <= kTopkThreads, "one bin per thread");
+    const uint32_t at_or_above = n_hi_all + last_sum + block_exclusive_scan(last_sum, wave_part, wave, lane);
+    uint32_t* part_words = rs + C::kFixedWords + (size_t)part * C::kPartWords;
+    if (tid < kDigitBins) part_words[kDigitBins - 1 - tid] = at_or_above;
+    if (tid == 0) part_words[kDigitBins] = n_hi_all;
   }
   // This part's bins are in the row's histogram before its ticket is taken: the adds are device-scope atomics, carried
   // out where all workgroups meet, and the barrier lets no wave pass before its own adds have been acknowledged.  (A
   // device-wide fence here instead costs a write-back of the whole L2 per workgroup: 200 us per launch at 560 groups.)
   __syncthreads();
-  if (tid == 0) s_last = (atomicAdd(&rs[4 + pass], 1u) == (uint32_t)(parts - 1));
+  if (tid == 0) s_last = (atomicAdd(&rs[4 + PASS], 1u) == (uint32_t)(parts - 1));
   __syncthreads();
   if (!s_last) return;
-  if (tid < 256) tot[tid] = atomicAdd(&rs[kMwStateWords + pass * 256 + tid], 0u);  // read where the adds met
-  __syncthreads();
-  if (wave == 0) {
-    const uint32_t krem = rs[1];
-    const uint32_t c0 = tot[4 * lane], c1 = tot[4 * lane + 1], c2 = tot[4 * lane + 2], c3 = tot[4 * lane + 3];
-    const uint32_t own = c0 + c1 + c2 + c3;
-    uint32_t v = own;
+  // the bins in descending order, kPer per thread, read where the adds met
+  constexpr int kPer = kDigitBins > kTopkThreads ? kDigitBins / kTopkThreads : 1;
+  uint32_t cnt[kPer];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const uint32_t t = __shfl_down(v, off, 64);
-      if (lane + off < 64) v += t;
-    }
-    const uint32_t a3 = v - own, a2 = a3 + c3, a1 = a2 + c2, a0 = a1 + c1;
-    const uint32_t above[4] = {a0, a1, a2, a3};
-    const uint32_t cnt[4] = {c0, c1, c2, c3};
-#pragma unroll
-    for (int bsel = 0; bsel < 4; ++bsel) {
-      if (above[bsel] < krem && krem <= above[bsel] + cnt[bsel]) {
-        rs[0] = (prefix << 8) | (uint32_t)(4 * lane + bsel);
-        rs[1] = krem - above[bsel];
-      }
-    }
-  }
+  for (int i = 0; i < kPer; ++i)
+    cnt[i] = tid * kPer < kDigitBins ? atomicAdd(&row_hist[kDigitBins - 1 - (tid * kPer + i)], 0u) : 0u;
+  const uint32_t krem = rs[1];
+  // (pick_digit's barriers lie between this read and the write)
+  pick_digit<kDigitBins, kPer>(cnt, krem, wave_part, tid, [&](uint32_t d, uint32_t left) {
+    rs[0] = (PASS == 0 ? 0u : prefix << (kHi - kShift)) | d;
+    rs[1] = left;
+  });
 }
 
 // grid (parts, rows): rs[0] is the K-th largest key T, rs[1] the number of keys equal to T that are kept (lowest
-// index first).  A part's first output slot follows from the last-pass histograms of the parts before it.
-template <bool GATHER>
-__global__ __launch_bounds__(kTopkThreads) void mw_write_kernel(const float* __restrict__ scores, int N, int K, int part_len,
+// index first).  A part's first output slot follows from two words of every part before it.
+template <int BITS, bool GATHER>
+__global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* __restrict__ scores, int N, int K, int part_len,
                                                                 const uint32_t* __restrict__ scratch, int row_words,
                                                                 int32_t* __restrict__ idx_out, GatherArgs ga) {
-  const int part = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  using C = Mw<BITS>;
+  constexpr int kDigitBins = 1 << C::kLastBits;
+  const int part = blockIdx.x, tid = threadIdx.x;
   const float* row = scores + (size_t)blockIdx.y * N;
   const uint32_t* rs = scratch + (size_t)blockIdx.y * row_words;
   int32_t* out = idx_out + (size_t)blockIdx.y * K;
-  __shared__ uint32_t wave_a[kTopkWaves], wave_b[kTopkWaves];
-  uint32_t key[kMwItems];
-  int i0;
-  const int mine = mw_load_keys(row, N, part_len, part, tid, key, i0);
-  const uint32_t T = rs[0], eq_take = rs[1], t8 = T & 255u;
+  __shared__ uint32_t wave_part[kTopkWaves], wave_eq[kTopkWaves];
+  const int lo = part * part_len, len = N - lo < part_len ? N - lo : part_len;
+  row += lo;
+  const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
+  const int wave = tid >> 6, lane = tid & 63;
+  // wave w owns the scores [w * seg, (w + 1) * seg) of the part, at most kMwQuads quads per lane
+  const int seg = ((len + kTopkWaves - 1) / kTopkWaves + 255) & ~255;
+  const int s0 = wave * seg < len ? wave * seg : len, s1 = s0 + seg < len ? s0 + seg : len;
+  const uint32_t T = rs[0], eq_take = rs[1], t_last = T & (kDigitBins - 1);
   // keys above T and keys equal to T in the parts before this one
   uint32_t g = 0, e = 0;
-  if (tid < 256) {
-    for (int q = 0; q < part; ++q) {
-      const uint32_t* ph = rs + kMwRowFixedWords + q * kMwPartWords;
-      const uint32_t h = ph[tid];
-      g += (uint32_t)tid > t8 ? h : 0u;
-      e += (uint32_t)tid == t8 ? h : 0u;
-      if (tid == 0) g += ph[256];
-    }
+  for (int q = tid; q < part; q += kTopkThreads) {
+    const uint32_t* pw = rs + C::kFixedWords + (size_t)q * C::kPartWords + t_last;
+    g += pw[1];
+    e += pw[0] - pw[1];
   }
-  uint32_t gt_before, eq_before_parts;
-  (void)block_exclusive_scan(g, wave_a, wave, lane, gt_before);
-  (void)block_exclusive_scan(e, wave_b, wave, lane, eq_before_parts);
-
-  uint32_t n_gt = 0, n_eq = 0;
+  const uint32_t gt_before = block_sum(g, wave_part, tid), eq_before = block_sum(e, wave_part, tid);
+  const float t = key_score(T);
+  const bool nan_t = T == 0;
+  uint64_t m_gt = 0, m_eq = 0;
+  const int quads = (s1 - s0 + 255) / 256;
+#pragma unroll 1
+  for (int q0 = 0; q0 < quads; q0 += 4) {
+    f32x4 v[4];
 #pragma unroll
-  for (int j = 0; j < kMwItems; ++j) {
-    if (j < mine) {
-      n_gt += key[j] > T;
-      n_eq += key[j] == T;
-    }
-  }
-  uint32_t tot_eq, tot_kept;
-  const uint32_t eq_before = eq_before_parts + block_exclusive_scan(n_eq, wave_a, wave, lane, tot_eq);
-  const uint32_t eq_mine = eq_before >= eq_take ? 0u : (eq_take - eq_before < n_eq ? eq_take - eq_before : n_eq);
-  const uint32_t part_pos = gt_before + (eq_before_parts < eq_take ? eq_before_parts : eq_take);
-  uint32_t pos = part_pos + block_exclusive_scan(n_gt + eq_mine, wave_b, wave, lane, tot_kept);
-  uint32_t eq_left = eq_mine;
+    for (int u = 0; u < 4; ++u) v[u] = load_quad(row, s0 + (q0 + u) * 256 + 4 * lane, s1, vec);
 #pragma unroll
-  for (int j = 0; j < kMwItems; ++j) {
-    if (j < mine) {
-      const bool take = key[j] > T || (key[j] == T && eq_left > 0);
-      if (key[j] == T && eq_left > 0) --eq_left;
-      if (take) out[pos++] = i0 + j;
+    for (int u = 0; u < 4; ++u) {
+      uint32_t bg, be;
+      quad_bits(v[u], s1 - (s0 + (q0 + u) * 256 + 4 * lane), t, nan_t, bg, be);
+      m_gt |= (uint64_t)bg << (4 * (q0 + u));
+      m_eq |= (uint64_t)be << (4 * (q0 + u));
     }
   }
+  const uint32_t n_gt = wave_total((uint32_t)__popcll(m_gt)), n_eq = wave_total((uint32_t)__popcll(m_eq));
+  if (lane == 0) {
+    wave_part[wave] = n_gt;
+    wave_eq[wave] = n_eq;
+  }
+  __syncthreads();
+  uint32_t gt = gt_before, eq = eq_before, gt_end = gt_before, eq_end = eq_before;
+#pragma unroll
+  for (int w = 0; w < kTopkWaves; ++w) {
+    const uint32_t a = wave_part[w], b = wave_eq[w];
+    gt += w < wave ? a : 0u;
+    eq += w < wave ? b : 0u;
+    gt_end += a;
+    eq_end += b;
+  }
+  wave_write(m_gt, m_eq, quads, gt, eq, eq_take, lo + s0, lane, out);
   if constexpr (GATHER) {
     __syncthreads();  // this part's stretch of the list is complete and visible to the whole workgroup
-    gather_rows(ga, (size_t)blockIdx.y * N * ga.cpr, (size_t)blockIdx.y * K * ga.cpr, out, (int)part_pos,
-                (int)(part_pos + tot_kept), tid);
+    gather_rows(ga, (size_t)blockIdx.y * N * ga.cpr, (size_t)blockIdx.y * K * ga.cpr, out,
+                (int)(gt_before + (eq_before < eq_take ? eq_before : eq_take)),
+                (int)(gt_end + (eq_end < eq_take ? eq_end : eq_take)), tid);
   }
 }
 
 }  // namespace
 
-// parts of a row that is too long for one register-resident workgroup (may be one)
-static int topk_parts(int64_t N) { return (int)((N + kMwPartMax - 1) / kMwPartMax); }
-
-size_t topk_scratch_bytes(int64_t rows, int64_t N) {
+// Parts of a row that is too long for one register-resident workgroup.  With 8 bits as few as there can be (the caller's
+// scratch memory is short); with 11 as many as give 512 workgroups, two per CU, of at least 8192 scores.
+template <int BITS>
+static int topk_parts(int64_t rows, int64_t N) {
+  const int64_t least = (N + kMwPartMax - 1) / kMwPartMax;
+  if (BITS == 8) return (int)least;
+  const int64_t most = (N + 8191) / 8192, want = 512 / rows < most ? 512 / rows : most;
+  return (int)(want > least ? want : least);
+}
+template <int BITS>
+static size_t topk_scratch(int64_t rows, int64_t N) {
   if (N <= kTopkRegMax || rows <= 0) return 0;
-  const int parts = topk_parts(N);
-  return (size_t)rows * (size_t)(kMwRowFixedWords + parts * kMwPartWords) * 4;
+  return (size_t)rows * (size_t)(Mw<BITS>::kFixedWords + (size_t)topk_parts<BITS>(rows, N) * Mw<BITS>::kPartWords) * 4;
+}
+size_t topk_scratch_bytes(int64_t rows, int64_t N) { return topk_scratch<11>(rows, N); }
+size_t topk_scratch_bytes_least(int64_t rows, int64_t N) { return topk_scratch<8>(rows, N); }
+
+template <int BITS>
+static hipError_t launch_topk_split(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
+                                    const GatherArgs* gather, hipStream_t stream) {
+  using C = Mw<BITS>;
+  const GatherArgs none = {nullptr, nullptr, nullptr, nullptr, 0};
+  // parts of equal length, a multiple of four scores (16-byte loads when the row itself is aligned), none of them empty
+  const int most_parts = topk_parts<BITS>(rows, N);
+  const int part_len = (int)((((N + most_parts - 1) / most_parts) + 3) & ~(int64_t)3);
+  const int parts = (int)((N + part_len - 1) / part_len);
+  const int row_words = C::kFixedWords + parts * C::kPartWords;
+  uint32_t* sc = (uint32_t*)scratch;
+  const int64_t init_words = rows * C::kFixedWords;
+  mw_init_kernel<BITS><<<(unsigned)((init_words + 255) / 256), 256, 0, stream>>>(sc, (int)rows, row_words, (int)K);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const dim3 grid((unsigned)parts, (unsigned)rows);
+  mw_pass_kernel<BITS, 0><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words);
+  mw_pass_kernel<BITS, 1><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words);
+  mw_pass_kernel<BITS, 2><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words);
+  if constexpr (C::kPasses > 3) mw_pass_kernel<BITS, 3><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (gather) mw_write_kernel<BITS, true><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, part_len, sc, row_words, idx_out, *gather);
+  else mw_write_kernel<BITS, false><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, part_len, sc, row_words, idx_out, none);
+  return hipGetLastError();
 }
 
 // gather != nullptr: every workgroup also gathers the token rows it selected (k/v in [rows, N, row_bytes], out [rows, K, row_bytes])
 static hipError_t launch_topk_impl(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
-                                   const GatherArgs* gather, hipStream_t stream) {
+                                   size_t scratch_bytes, const GatherArgs* gather, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
-  const GatherArgs none = {nullptr, nullptr, nullptr, nullptr, 0};
-  const int parts = topk_parts(N);
   if (N <= kTopkRegMax) {
+    const GatherArgs none = {nullptr, nullptr, nullptr, nullptr, 0};
     if (gather) topk_reg_kernel<true><<<dim3((unsigned)rows), kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, idx_out, *gather);
     else topk_reg_kernel<false><<<dim3((unsigned)rows), kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, idx_out, none);
     return hipGetLastError();
   }
   if (scratch == nullptr || rows > 65535) return hipErrorInvalidValue;
-  // parts of equal length, a multiple of four scores (16-byte loads when the row itself is aligned)
-  const int part_len = (int)((((N + parts - 1) / parts) + 3) & ~(int64_t)3);
-  const int row_words = kMwRowFixedWords + parts * kMwPartWords;
-  uint32_t* sc = (uint32_t*)scratch;
-  const int64_t init_words = rows * kMwRowFixedWords;
-  mw_init_kernel<<<(unsigned)((init_words + 255) / 256), 256, 0, stream>>>(sc, (int)rows, row_words, (int)K);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  const dim3 grid((unsigned)parts, (unsigned)rows);
-  for (int pass = 0; pass < 4; ++pass) {
-    mw_pass_kernel<<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, pass, sc, row_words);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  }
-  if (gather) mw_write_kernel<true><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, part_len, sc, row_words, idx_out, *gather);
-  else mw_write_kernel<false><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, part_len, sc, row_words, idx_out, none);
-  return hipGetLastError();
+  if (scratch_bytes >= topk_scratch<11>(rows, N)) return launch_topk_split<11>(scores, rows, N, K, idx_out, scratch, gather, stream);
+  if (scratch_bytes >= topk_scratch<8>(rows, N)) return launch_topk_split<8>(scores, rows, N, K, idx_out, scratch, gather, stream);
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_topk(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
-                       hipStream_t stream) {
-  return launch_topk_impl(scores, rows, N, K, idx_out, scratch, nullptr, stream);
+                       size_t scratch_bytes, hipStream_t stream) {
+  return launch_topk_impl(scores, rows, N, K, idx_out, scratch, scratch_bytes, nullptr, stream);
 }
 
 hipError_t launch_topk_gather(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
-                              const void* k_in, const void* v_in, int64_t row_bytes, void* k_out, void* v_out,
+                              size_t scratch_bytes, const void* k_in, const void* v_in, int64_t row_bytes, void* k_out, void* v_out,
                               hipStream_t stream) {
   const GatherArgs ga = {(const u32x4*)k_in, (const u32x4*)v_in, (u32x4*)k_out, (u32x4*)v_out, (int)(row_bytes / 16)};
   if (ga.cpr < 1 || ga.cpr > kTopkThreads || kTopkThreads % ga.cpr != 0) return hipErrorInvalidValue;
-  return launch_topk_impl(scores, rows, N, K, idx_out, scratch, &ga, stream);
+  return launch_topk_impl(scores, rows, N, K, idx_out, scratch, scratch_bytes, &ga, stream);
 }
 
 }  // namespace pkv

@@ -20,7 +20,7 @@ extern "C" int proxykv_topk_static(proxykv_ctx* ctx, const float* scores, int64_
   if (!ctx || !scores || !idx_out) return PROXYKV_EINVAL;
   if (rows <= 0 || rows >= (1ll << 31) || N <= 0 || N >= (1ll << 31) - 4096 || K < 1 || K > N) return PROXYKV_EINVAL;
   if (N > pkv::kTopkSingleMax && rows > 65535) return PROXYKV_EUNSUPPORTED;
-  const size_t need = pkv::topk_scratch_bytes(rows, N);
+  const size_t need = pkv::topk_scratch_bytes_least(rows, N);
   if (need > kScratchBytes) return PROXYKV_ELIMIT;
   const int dev = ctx->cfg.device;
   if (dev < 0 || dev >= kMaxDevices) return PROXYKV_EUNSUPPORTED;
@@ -31,7 +31,7 @@ extern "C" int proxykv_topk_static(proxykv_ctx* ctx, const float* scores, int64_
     e = hipGetSymbolAddress(&p, HIP_SYMBOL(scratch));
     if (e == hipSuccess) g_scratch_ptr[dev] = p;
   }
-  if (e == hipSuccess) e = pkv::launch_topk(scores, rows, N, K, idx_out, g_scratch_ptr[dev], (hipStream_t)stream);
+  if (e == hipSuccess) e = pkv::launch_topk(scores, rows, N, K, idx_out, g_scratch_ptr[dev], kScratchBytes, (hipStream_t)stream);
   if (e != hipSuccess) {
     ctx->last_hip_error = (int)e;
     (void)hipGetLastError();

@@ -74,6 +74,36 @@ def test_topk_bit_exact_around_the_kernel_switch(N):
         assert torch.equal(got.cpu(), oracle.topk(s, K)), (N, K)
 
 
+@pytest.mark.parametrize("rows,N", [(3, 255), (3, 2305), (3, 36861), (3, 36865), (600, 36868), (3, 45057), (2, 524293)])
+def test_topk_ties_nan_thresholds_and_odd_lengths(rows, N):
+    """Rows of a few distinct values (ties across the stretches of waves and parts), rows that are mostly NaN (the K-th
+    largest is NaN), rows with both zeros and infinities, a constant row; lengths that leave a row off a 16-byte boundary,
+    at the edge of the one-workgroup kernel, and few enough rows that one is cut into many parts.  proxykv_topk_static's
+    histograms are narrower than proxykv_topk's for the long rows."""
+    g = torch.Generator().manual_seed(N)
+    distinct = 3 if rows > 2 else rows
+    base = torch.randn(distinct, N, generator=g)
+    base[0] = torch.randint(-2, 3, (N,), generator=g).float() * 0.0 + torch.randint(0, 4, (N,), generator=g).float()
+    base[0, ::7] = -0.0
+    base[1, torch.rand(N, generator=g) < 0.7] = float("nan")
+    base[1, ::11] = float("inf")
+    base[1, 1::13] = float("-inf")
+    if distinct > 2:
+        base[2] = 0.25
+    s = base.repeat((rows + distinct - 1) // distinct, 1)[:rows].contiguous()
+    ctx = _ctx(synth.CASES["tiny"])
+    d = s.cuda()
+    for K in sorted({1, max(1, N // 5), max(1, N // 2), N - 1 if N > 1 else 1, N}):
+        ref = oracle.topk(base, K).repeat((rows + distinct - 1) // distinct, 1)[:rows]
+        idx = pk.proxykv_topk(ctx, d, K)
+        out = torch.empty_like(idx)
+        pk.proxykv_topk_static(ctx, d, K, out)
+        torch.cuda.synchronize()
+        assert torch.equal(idx.cpu().long(), ref.long()), (N, K)
+        assert torch.equal(out.cpu().long(), ref.long()), (N, K)
+    pk.proxykv_destroy(ctx)
+
+
 def test_compact_bit_exact():
     ctx = _ctx(synth.CASES["tiny"])
     g = torch.Generator().manual_seed(3)
