@@ -3,6 +3,7 @@
 #include <math.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -87,7 +88,9 @@ Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q, int disti
   const pkv::MapPlan p = pkv::map_plan(c, N, distinct_layers);
   // rows of GEMM outputs (and of the residuals they read) are padded to the GEMM's 256-row tile
   const size_t b = (size_t)p.batch, Tp = b * (size_t)p.Tp, Np = b * (size_t)p.Np, dt = (size_t)c.d_time;
-  s.neg_lse = (size_t)c.L_s * c.H_q * (size_t)N_q * 4;
+  // the causal form runs pass 1 without context keys, over N_q == N of its own
+  const int splits = std::max(pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q), pkv::score_splits(c.L_s, c.H_q, c.d, N_q, N_q));
+  s.neg_lse = (size_t)c.L_s * c.H_q * (size_t)N_q * (splits > 1 ? 8 * (size_t)splits : 4);
   s.x_ws = (size_t)c.L_s * c.H_kv * (size_t)N * 4;
   s.yhat_ws = (size_t)c.L_l * c.H_l * (size_t)N * 4;
   s.h1 = b * ((size_t)N + 2) * (size_t)c.c_mid * 2;
@@ -205,9 +208,10 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
     if ((rc = ensure(ctx, ctx->q_bf16, nq * 2, stream))) return rc;
     if ((rc = ensure(ctx, ctx->kctx_bf16, nkc * 2, stream))) return rc;
     if ((rc = ensure(ctx, ctx->krec_bf16, nkr * 2, stream))) return rc;
-    PKV_HIP(ctx, pkv::launch_f32_to_bf16((const float*)q_rec, (uint16_t*)ctx->q_bf16.ptr, (int64_t)nq, stream));
-    PKV_HIP(ctx, pkv::launch_f32_to_bf16((const float*)k_ctx, (uint16_t*)ctx->kctx_bf16.ptr, (int64_t)nkc, stream));
-    PKV_HIP(ctx, pkv::launch_f32_to_bf16((const float*)k_rec, (uint16_t*)ctx->krec_bf16.ptr, (int64_t)nkr, stream));
+    const float* const in[3] = {(const float*)q_rec, (const float*)k_ctx, (const float*)k_rec};
+    uint16_t* const out[3] = {(uint16_t*)ctx->q_bf16.ptr, (uint16_t*)ctx->kctx_bf16.ptr, (uint16_t*)ctx->krec_bf16.ptr};
+    const int64_t n[3] = {(int64_t)nq, (int64_t)nkc, (int64_t)nkr};
+    PKV_HIP(ctx, pkv::launch_f32_to_bf16(in, out, n, stream));
     q = (const uint16_t*)ctx->q_bf16.ptr;
     kc = (const uint16_t*)ctx->kctx_bf16.ptr;
     kr = (const uint16_t*)ctx->krec_bf16.ptr;
@@ -216,12 +220,14 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
   float* nl = (float*)ctx->neg_lse.ptr;
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
-  PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
+  const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q);
+  const int64_t n_x = (int64_t)c.L_s * c.H_kv * N;
+  PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, splits, x_out, n_x, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
   if (c.reduce == PROXYKV_REDUCE_SUM)
-    PKV_HIP(ctx, pkv::launch_score_colsum(q, kc, nl, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, false, stream));
+    PKV_HIP(ctx, pkv::launch_score_colsum(q, kc, nl, splits, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, false, stream));
   else
-    PKV_HIP(ctx, pkv::launch_score_colmax(q, kc, nl, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, stream));
+    PKV_HIP(ctx, pkv::launch_score_colmax(q, kc, nl, splits, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, stream));
   if ((rcm = mark(ctx, 2, stream))) return rcm;
   return PROXYKV_OK;
 }
@@ -237,8 +243,10 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
     const size_t nq = (size_t)c.L_s * c.H_q * (size_t)N * c.d, nk = (size_t)c.L_s * c.H_kv * (size_t)N * c.d;
     if ((rc = ensure(ctx, ctx->q_bf16, nq * 2, stream))) return rc;
     if ((rc = ensure(ctx, ctx->krec_bf16, nk * 2, stream))) return rc;
-    PKV_HIP(ctx, pkv::launch_f32_to_bf16((const float*)q_in, (uint16_t*)ctx->q_bf16.ptr, (int64_t)nq, stream));
-    PKV_HIP(ctx, pkv::launch_f32_to_bf16((const float*)k_in, (uint16_t*)ctx->krec_bf16.ptr, (int64_t)nk, stream));
+    const float* const in[3] = {(const float*)q_in, (const float*)k_in, nullptr};
+    uint16_t* const out[3] = {(uint16_t*)ctx->q_bf16.ptr, (uint16_t*)ctx->krec_bf16.ptr, nullptr};
+    const int64_t n[3] = {(int64_t)nq, (int64_t)nk, 0};
+    PKV_HIP(ctx, pkv::launch_f32_to_bf16(in, out, n, stream));
     q = (const uint16_t*)ctx->q_bf16.ptr;
     k = (const uint16_t*)ctx->krec_bf16.ptr;
   }
@@ -246,9 +254,10 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
   float* nl = (float*)ctx->neg_lse.ptr;
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
-  PKV_HIP(ctx, pkv::launch_score_lse(q, k, k, nl, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
+  const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N);
+  PKV_HIP(ctx, pkv::launch_score_lse(q, k, k, nl, splits, x_out, (int64_t)c.L_s * c.H_kv * N, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
-  PKV_HIP(ctx, pkv::launch_score_colsum(q, k, nl, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N, true, stream));
+  PKV_HIP(ctx, pkv::launch_score_colsum(q, k, nl, splits, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N, true, stream));
   if ((rcm = mark(ctx, 2, stream))) return rcm;
   return PROXYKV_OK;
 }

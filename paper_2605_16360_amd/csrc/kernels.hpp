@@ -6,22 +6,26 @@
 
 namespace pkv {
 
-// fp32 -> bf16 (round to nearest even), n elements.
-hipError_t launch_f32_to_bf16(const float* in, uint16_t* out, int64_t n, hipStream_t stream);
+// fp32 -> bf16 (round to nearest even) of three arrays (n[i] elements, a multiple of eight; 0 = none).
+hipError_t launch_f32_to_bf16(const float* const in[3], uint16_t* const out[3], const int64_t n[3], hipStream_t stream);
 
 // Scoring, pass 1: neg_lse[l, h, i] = -log2(sum_k 2^(c * <q_i, k>)) / c with c = log2(e) / sqrt(d),
 // the sum running over the N context keys and the visible reconstruction keys of query i.
-hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* k_rec, float* neg_lse,
-                            int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
+// With splits = score_splits(...) > 1 several workgroups share a query's keys: neg_lse then takes 8 * splits bytes per query
+// instead of four, and x [n_x] is cleared for pass 2.
+int score_splits(int L_s, int H_q, int d, int64_t N, int64_t N_q);
+hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* k_rec, float* neg_lse, int splits,
+                            float* x, int64_t n_x, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
                             hipStream_t stream);
 // Scoring, pass 2: x[l, g, n] = 2^(c * max over (head of group g, query i) of (<q_i, k_n> + neg_lse[l, h, i])).
-hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, float* x,
+// neg_lse and splits as pass 1 left them.
+hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x,
                                int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q,
                                hipStream_t stream);
 
 // Scoring, pass 2 in the sum form: x[l, g, n] = sum over (head of group g, query i) of 2^(c * (<q_i, k_n> + neg_lse[l, h, i])).
 // causal: the keys are the queries' own sequence (N == N_q) and query i adds to keys n <= i only.
-hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, float* x,
+hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x,
                                int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, bool causal,
                                hipStream_t stream);
 // Per-row Top-K.  Rows longer than 36 864 scores are split over several workgroups and need `scratch` (device memory, any

@@ -33,12 +33,14 @@ namespace {
 // Chains are handled in pairs (two column sub-tiles): the MFMAs of pair i are issued while the
 // VALU reduces the accumulators of pair i-1 (also across tile boundaries).
 // ---------------------------------------------------------------------------------------------
-template <int D, int NCOL>
+// SPLIT (see score_lse.hip): neg_lse holds shares; the query tiles of a key block are dealt to q_splits workgroups as well, and
+// each raises x (cleared by pass 1; probabilities are not negative, so their bits compare like integers).
+template <int D, int NCOL, bool SPLIT>
 __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_ctx,
                                                                const float* __restrict__ neg_lse,
                                                                float* __restrict__ x, int L_s, int H_q, int G, int N, int N_q,
-                                                               float c) {
+                                                               float c, float inv_c, int splits, int q_splits) {
   using C = ScoreCfg<D>;
   static_assert(NCOL % 2 == 0, "column sub-tiles are processed in pairs");
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
@@ -46,10 +48,11 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   constexpr int KB = 128 * NCOL;
   const int H_kv = H_q / G;
-  const GroupBlock gb = group_block((N + KB - 1) / KB);  // a group's blocks: its key blocks (they stream the same queries)
+  // a group's blocks: its key blocks (they stream the same queries), each in q_splits parts
+  const GroupBlock gb = group_block((N + KB - 1) / KB * (SPLIT ? q_splits : 1));
   if (gb.group >= L_s * H_kv) return;
   const int l = gb.group / H_kv, hs = gb.group % H_kv;
-  const int n0 = gb.item * KB;
+  const int n0 = (SPLIT ? gb.item / q_splits : gb.item) * KB;
   const uint16_t* kc = k_ctx + (size_t)(l * H_kv + hs) * N * D;
 
   bf16x8 b[NCOL][C::KK];
@@ -68,16 +71,20 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
 
   // tiles are fetched in order: head g = 0..G-1 of the group, query tile qt = 0..nqt-1
   const int nqt = (N_q + C::ROWS - 1) / C::ROWS;
-  const int total = G * nqt;
+  const int part = SPLIT ? gb.item % q_splits : 0;
+  const int first = SPLIT ? (int)((int64_t)G * nqt * part / q_splits) : 0;
+  const int total = SPLIT ? (int)((int64_t)G * nqt * (part + 1) / q_splits) - first : G * nqt;
   TileRegs<D> regs;
-  float nl_reg = kNegInf;
-  int fg = 0, fqt = 0;
+  LseRegs<SPLIT> nl_reg;
+  nl_reg.none();
+  int fg = SPLIT ? first / nqt : 0, fqt = SPLIT ? first % nqt : 0;
   auto fetch_next = [&]() {
     const size_t head = (size_t)(l * H_q + hs * G + fg);
     tile_fetch<D>(regs, q + head * N_q * D, fqt * C::ROWS, N_q, tid);
     if (tid < C::ROWS) {
       const int i = fqt * C::ROWS + tid;
-      nl_reg = i < N_q ? neg_lse[head * N_q + i] : kNegInf;
+      if (i < N_q) nl_reg.read(neg_lse, head * N_q + i, (size_t)L_s * H_q * N_q, splits);
+      else nl_reg.none();
     }
     if (++fqt == nqt) {
       fqt = 0;
@@ -86,7 +93,7 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
   };
   auto store = [&](int t) {
     tile_store<D>(regs, lds + (t % kNBuf) * C::TILE_U4, tid);
-    if (tid < C::ROWS) lds_nl[(t % kNBuf) * C::ROWS + tid] = nl_reg;
+    if (tid < C::ROWS) lds_nl[(t % kNBuf) * C::ROWS + tid] = nl_reg.neg_lse(inv_c);
   };
   fetch_next();
   store(0);
@@ -170,7 +177,12 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
 #pragma unroll
   for (int cs = 0; cs < NCOL; ++cs) {
     const float m = __builtin_fmaxf(runmax[cs], swap_halves(runmax[cs]));
-    if (half == 0 && kn[cs] < N) x[(size_t)(l * H_kv + hs) * N + kn[cs]] = __builtin_fminf(__builtin_amdgcn_exp2f(c * m), 1.0f);
+    const float p = __builtin_fminf(__builtin_amdgcn_exp2f(c * m), 1.0f);
+    if (half == 0 && kn[cs] < N) {
+      float* dst = x + (size_t)(l * H_kv + hs) * N + kn[cs];
+      if constexpr (SPLIT) atomicMax(reinterpret_cast<unsigned int*>(dst), __float_as_uint(p));
+      else *dst = p;
+    }
   }
 }
 
@@ -185,12 +197,12 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
 //
 // CAUSAL: the proxy's own prefill attention (N_q == N, the keys are the sequence's own): query i sees keys n <= i, so a
 // workgroup starts at the query tile that holds its first key and masks the tiles that the diagonal cuts.
-template <int D, int NCOL, bool CAUSAL>
+template <int D, int NCOL, bool CAUSAL, bool SPLIT>
 __global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_ctx,
                                                                const float* __restrict__ neg_lse,
                                                                float* __restrict__ x, int L_s, int H_q, int G, int N, int N_q,
-                                                               float c) {
+                                                               float c, float inv_c, int splits) {
   using C = ScoreCfg<D>;
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
   __shared__ __attribute__((aligned(16))) float lds_nl[kNBuf * C::ROWS];
@@ -221,14 +233,16 @@ __global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __
   const int qt_first = CAUSAL ? n0 / C::ROWS : 0;  // KB is a multiple of ROWS
   const int total = G * (nqt - qt_first);
   TileRegs<D> regs;
-  float nl_reg = kNegInf;
+  LseRegs<SPLIT> nl_reg;
+  nl_reg.none();
   int fg = 0, fqt = qt_first;
   auto fetch_next = [&]() {
     const size_t head = (size_t)(l * H_q + hs * G + fg);
     tile_fetch<D>(regs, q + head * N_q * D, fqt * C::ROWS, N_q, tid);
     if (tid < C::ROWS) {
       const int i = fqt * C::ROWS + tid;
-      nl_reg = i < N_q ? neg_lse[head * N_q + i] : kNegInf;
+      if (i < N_q) nl_reg.read(neg_lse, head * N_q + i, (size_t)L_s * H_q * N_q, splits);
+      else nl_reg.none();
     }
     if (++fqt == nqt) {
       fqt = qt_first;
@@ -237,7 +251,7 @@ __global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __
   };
   auto store = [&](int t) {
     tile_store<D>(regs, lds + (t % kNBuf) * C::TILE_U4, tid);
-    if (tid < C::ROWS) lds_nl[(t % kNBuf) * C::ROWS + tid] = nl_reg;
+    if (tid < C::ROWS) lds_nl[(t % kNBuf) * C::ROWS + tid] = nl_reg.neg_lse(inv_c);
   };
   fetch_next();
   store(0);
@@ -314,56 +328,90 @@ __global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __
   }
 }
 
-__global__ void f32_to_bf16_kernel(const float* __restrict__ in, uint16_t* __restrict__ out, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) out[i] = f32_to_bf16_bits(in[i]);
+// fp32 -> bf16 of up to three arrays in one launch, eight elements per thread (n counts eights; every array of queries or
+// keys is a multiple of eight long)
+struct ConvertArgs {
+  const float* in[3];
+  uint16_t* out[3];
+  int64_t n[3];
+};
+__global__ __launch_bounds__(256) void f32_to_bf16_kernel(ConvertArgs a) {
+  const int64_t stride = (int64_t)gridDim.x * 256, total = a.n[0] + a.n[1] + a.n[2];
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += stride) {
+    const int64_t i1 = i - a.n[0], i2 = i1 - a.n[1];
+    const float* in = i1 < 0 ? a.in[0] + i * 8 : (i2 < 0 ? a.in[1] + i1 * 8 : a.in[2] + i2 * 8);
+    uint16_t* out = i1 < 0 ? a.out[0] + i * 8 : (i2 < 0 ? a.out[1] + i1 * 8 : a.out[2] + i2 * 8);
+    const f32x4 v = *reinterpret_cast<const f32x4*>(in), w = *reinterpret_cast<const f32x4*>(in + 4);
+    *reinterpret_cast<u32x4*>(out) = u32x4{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]), pack_bf16x2(w[0], w[1]), pack_bf16x2(w[2], w[3])};
+  }
 }
 
 }  // namespace
 
-hipError_t launch_f32_to_bf16(const float* in, uint16_t* out, int64_t n, hipStream_t stream) {
-  if (n <= 0) return hipSuccess;
-  const int blocks = (int)((n + 255) / 256 < 65536 ? (n + 255) / 256 : 65536);
-  f32_to_bf16_kernel<<<blocks, 256, 0, stream>>>(in, out, n);
+hipError_t launch_f32_to_bf16(const float* const in[3], uint16_t* const out[3], const int64_t n[3], hipStream_t stream) {
+  ConvertArgs a;
+  int64_t total = 0;
+  for (int i = 0; i < 3; ++i) {
+    if (n[i] % 8 != 0) return hipErrorInvalidValue;
+    a.in[i] = in[i];
+    a.out[i] = out[i];
+    a.n[i] = n[i] / 8;
+    total += a.n[i];
+  }
+  if (total <= 0) return hipSuccess;
+  const int64_t blocks = (total + 255) / 256;
+  f32_to_bf16_kernel<<<(unsigned)(blocks < 16384 ? blocks : 16384), 256, 0, stream>>>(a);
   return hipGetLastError();
 }
 
-hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, float* x, int L_s,
+hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x, int L_s,
                                int H_q, int H_kv, int d, int64_t N, int64_t N_q, bool causal, hipStream_t stream) {
   const int G = H_q / H_kv;
-  const float c = 1.4426950408889634f / sqrtf((float)d);
+  const float c = 1.4426950408889634f / sqrtf((float)d), inv_c = 1.0f / c;
   constexpr int NCOL = 2;
   if (causal && N != N_q) return hipErrorInvalidValue;
   const unsigned grid = group_grid((int64_t)L_s * H_kv, (N + 128 * NCOL - 1) / (128 * NCOL));
   if (grid == 0) return hipErrorInvalidValue;
-  const int n = (int)N, nq = (int)N_q;
-  if (d == 64) {
-    if (causal) score_colsum_kernel<64, NCOL, true><<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, n, nq, c);
-    else score_colsum_kernel<64, NCOL, false><<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, n, nq, c);
-  } else {
-    if (causal) score_colsum_kernel<128, NCOL, true><<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, n, nq, c);
-    else score_colsum_kernel<128, NCOL, false><<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, n, nq, c);
-  }
+  auto go = [&](auto dc, auto cc, auto sc) {
+    score_colsum_kernel<decltype(dc)::value, NCOL, decltype(cc)::value, decltype(sc)::value>
+        <<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, (int)N, (int)N_q, c, inv_c, splits);
+  };
+  auto pick = [&](auto dc) {
+    if (causal && splits > 1) go(dc, std::true_type{}, std::true_type{});
+    else if (causal) go(dc, std::true_type{}, std::false_type{});
+    else if (splits > 1) go(dc, std::false_type{}, std::true_type{});
+    else go(dc, std::false_type{}, std::false_type{});
+  };
+  if (d == 64) pick(std::integral_constant<int, 64>{});
+  else pick(std::integral_constant<int, 128>{});
   return hipGetLastError();
 }
 
-hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, float* x, int L_s,
+hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x, int L_s,
                                int H_q, int H_kv, int d, int64_t N, int64_t N_q, hipStream_t stream) {
   const int G = H_q / H_kv;
-  const float c = 1.4426950408889634f / sqrtf((float)d);
-  if (d == 64) {
-    constexpr int NCOL = 4;
-    const unsigned grid = group_grid((int64_t)L_s * H_kv, (N + 128 * NCOL - 1) / (128 * NCOL));
-    if (grid == 0) return hipErrorInvalidValue;
-    score_colmax_kernel<64, NCOL><<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, (int)N, (int)N_q, c);
-  } else {
-    // one workgroup per CU (the resident keys of 4 column sub-tiles alone take 128 registers): a wave has the SIMD's
-    // whole register file, and the pinned issue order keeps the matrix pipe fed without a second wave
-    constexpr int NCOL = 4;
-    const unsigned grid = group_grid((int64_t)L_s * H_kv, (N + 128 * NCOL - 1) / (128 * NCOL));
-    if (grid == 0) return hipErrorInvalidValue;
-    score_colmax_kernel<128, NCOL><<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, (int)N, (int)N_q, c);
+  const float c = 1.4426950408889634f / sqrtf((float)d), inv_c = 1.0f / c;
+  // d = 64: two workgroups per CU.  d = 128: one (the resident keys of 4 column sub-tiles alone take 128 registers): a wave
+  // has the SIMD's whole register file, and the pinned issue order keeps the matrix pipe fed without a second wave
+  constexpr int NCOL = 4;
+  const int64_t key_blocks = (N + 128 * NCOL - 1) / (128 * NCOL), q_tiles = G * ((N_q + 8192 / d - 1) / (8192 / d));
+  int64_t q_splits = 1;
+  if (splits > 1) {
+    // as many parts of the query tiles as fill the chip, two tiles or more each (the first tile of a part waits for memory)
+    q_splits = (d == 64 ? 512 : 256) / (key_blocks * L_s * H_kv);
+    q_splits = q_splits < q_tiles / 2 ? q_splits : q_tiles / 2;
+    q_splits = q_splits < 1 ? 1 : q_splits;
   }
+  const unsigned grid = group_grid((int64_t)L_s * H_kv, key_blocks * q_splits);
+  if (grid == 0) return hipErrorInvalidValue;
+  auto go = [&](auto dc, auto sc) {
+    score_colmax_kernel<decltype(dc)::value, NCOL, decltype(sc)::value>
+        <<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, (int)N, (int)N_q, c, inv_c, splits, (int)q_splits);
+  };
+  if (d == 64 && splits > 1) go(std::integral_constant<int, 64>{}, std::true_type{});
+  else if (d == 64) go(std::integral_constant<int, 64>{}, std::false_type{});
+  else if (splits > 1) go(std::integral_constant<int, 128>{}, std::true_type{});
+  else go(std::integral_constant<int, 128>{}, std::false_type{});
   return hipGetLastError();
 }
 

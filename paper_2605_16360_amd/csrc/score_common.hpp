@@ -113,6 +113,42 @@ constexpr float kNegInf = -__builtin_huge_valf();
 // A lane re-bases its partial sum when a logit exceeds its reference by more than 2^kRescaleGap.
 constexpr float kRescaleGap = 60.0f;
 
+// One workgroup's share of a query's softmax denominator: sum 2^(c * logit - m) over its keys.
+struct LsePart {
+  float m, l;
+};
+constexpr int kMaxLseSplits = 8;
+// What pass 1 left of query `row` of [rows], from one word or from `splits` shares; neg_lse() = -log2(sum over all keys of
+// 2^(c * logit)) / c.  Read when the query's tile is asked for, put together when the tile goes to LDS.
+template <bool SPLIT>
+struct LseRegs {
+  float v;
+  __device__ __forceinline__ void none() { v = kNegInf; }
+  __device__ __forceinline__ void read(const float* p, size_t row, size_t, int) { v = p[row]; }
+  __device__ __forceinline__ float neg_lse(float) const { return v; }
+};
+template <>
+struct LseRegs<true> {
+  LsePart p[kMaxLseSplits];
+  __device__ __forceinline__ void none() {  // a sum that is too large for any logit: -inf
+#pragma unroll
+    for (int s = 0; s < kMaxLseSplits; ++s) p[s] = LsePart{0.0f, s == 0 ? -kNegInf : 0.0f};
+  }
+  __device__ __forceinline__ void read(const float* parts, size_t row, size_t rows, int splits) {
+#pragma unroll
+    for (int s = 0; s < kMaxLseSplits; ++s)
+      p[s] = s < splits ? reinterpret_cast<const LsePart*>(parts)[(size_t)s * rows + row] : LsePart{-1.0e30f, 0.0f};
+  }
+  __device__ __forceinline__ float neg_lse(float inv_c) const {
+    float m = p[0].m, l = 0.0f;
+#pragma unroll
+    for (int s = 1; s < kMaxLseSplits; ++s) m = __builtin_fmaxf(m, p[s].m);
+#pragma unroll
+    for (int s = 0; s < kMaxLseSplits; ++s) l = __builtin_fmaf(p[s].l, __builtin_amdgcn_exp2f(p[s].m - m), l);
+    return -(m + __builtin_amdgcn_logf(l)) * inv_c;
+  }
+};
+
 __device__ __forceinline__ f32x16 splat16(float v) {
   f32x16 r;
 #pragma unroll

@@ -20,6 +20,10 @@
 //
 // Streaming: three LDS buffers and one barrier per tile.  While tile t is computed, tile t+2 goes
 // from registers to LDS and tile t+3 is fetched from global memory into registers.
+//
+// Few queries (one layer, a short sequence) leave most of the chip without a workgroup.  The key tiles of a query block are
+// then shared by several workgroups, each of which leaves its reference and sum of every query; pass 2 puts them together
+// where it reads a query's log-sum-exp.
 #include "kernels.hpp"
 #include "score_common.hpp"
 
@@ -32,18 +36,27 @@ constexpr float kRebase = 1.8446744e19f;  // 2^64
 // undoes the tile and sums it again chain by chain with the check.
 constexpr float kTileRedo = 1.2676506e30f;  // 2^100
 
-template <int D, int NCOL, int MINB>
+// SPLIT: `splits` workgroups per query block, neg_lse holds (reference, sum) pairs [splits][L_s * H_q * N_q]; they also clear
+// x [n_x], which pass 2's workgroups then raise.
+template <int D, int NCOL, int MINB, bool SPLIT>
 __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_ctx,
                                                                const uint16_t* __restrict__ k_rec,
                                                                float* __restrict__ neg_lse, int H_q, int G, int N,
-                                                               int N_q, int chunk, float c, float inv_c) {
+                                                               int N_q, int chunk, float c, float inv_c, int splits,
+                                                               float* __restrict__ x, int64_t n_x) {
   using C = ScoreCfg<D>;
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int h = blockIdx.y, l = blockIdx.z, H_kv = H_q / G, hs = h / G;
   constexpr int QB = 128 * NCOL;
-  const int i0 = blockIdx.x * QB;
+  const int split = SPLIT ? blockIdx.x % splits : 0;
+  const int i0 = (SPLIT ? blockIdx.x / splits : blockIdx.x) * QB;
+  if constexpr (SPLIT) {
+    const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * gridDim.y * gridDim.z * 256;
+    for (int64_t i = wg * 256 + tid; i < n_x; i += stride) x[i] = 0.0f;
+  }
   const uint16_t* qh = q + (size_t)(l * H_q + h) * N_q * D;
   const uint16_t* kc = k_ctx + (size_t)(l * H_kv + hs) * N * D;
   const uint16_t* kr = k_rec + (size_t)(l * H_kv + hs) * N_q * D;
@@ -73,13 +86,18 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
   const int i_end = (i0 + QB < N_q ? i0 + QB : N_q);  // one past the block's last query
   const int rec_lo = (i0 / chunk) * chunk;            // first reconstruction key any query of the block sees
   const int n_rec = (i_end - rec_lo + C::ROWS - 1) / C::ROWS;
-  const int total = n_ctx + n_rec;
+  const int total_all = n_ctx + n_rec;
+  // this workgroup's tiles: t0, ..., t0 + total - 1 of the list
+  const int t0 = SPLIT ? (int)((int64_t)total_all * split / splits) : 0;
+  const int total = SPLIT ? (int)((int64_t)total_all * (split + 1) / splits) - t0 : total_all;
   const int wave_i_lo = i0 + wave * NCOL * 32;  // first query of this wave
   TileRegs<D> regs;
-  auto fetch = [&](int t) {
-    if (t < n_ctx) tile_fetch<D>(regs, kc, t * C::ROWS, N, tid);
-    else tile_fetch<D>(regs, kr, rec_lo + (t - n_ctx) * C::ROWS, i_end, tid);
+  auto fetch_to = [&](TileRegs<D>& r, int t) {
+    t += t0;
+    if (t < n_ctx) tile_fetch<D>(r, kc, t * C::ROWS, N, tid);
+    else tile_fetch<D>(r, kr, rec_lo + (t - n_ctx) * C::ROWS, i_end, tid);
   };
+  auto fetch = [&](int t) { fetch_to(regs, t); };
 
   // sum of one chain: 16 x (fma, exp2, add); re-based when it leaves [0, 2^64)
   auto accumulate = [&](const f32x16& acc, int cs) {
@@ -142,13 +160,14 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     }
   };
 
-  fetch(0);
-  tile_store<D>(regs, lds, tid);
-  if (total > 1) {
-    fetch(1);
-    tile_store<D>(regs, lds + C::TILE_U4, tid);
+  if (total > 0) {
+    TileRegs<D> second;  // the first two tiles are asked for together
+    fetch(0);
+    if (total > 1) fetch_to(second, 1);
+    tile_store<D>(regs, lds, tid);
+    if (total > 1) tile_store<D>(second, lds + C::TILE_U4, tid);
+    if (total > 2) fetch(2);
   }
-  if (total > 2) fetch(2);
 
   for (int t = 0; t < total; ++t) {
     // every wave has finished tile t-1: its buffer takes tile t+2, the registers take tile t+3
@@ -156,13 +175,15 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     if (t + 2 < total) tile_store<D>(regs, lds + ((t + 2) % kNBuf) * C::TILE_U4, tid);
     if (t + 3 < total) fetch(t + 3);
     const u32x4* buf = lds + (t % kNBuf) * C::TILE_U4;
-    const bool is_rec = t >= n_ctx;
-    const int row0 = is_rec ? rec_lo + (t - n_ctx) * C::ROWS : t * C::ROWS;
+    const int tg = t0 + t;
+    const bool is_rec = tg >= n_ctx;
+    const int row0 = is_rec ? rec_lo + (tg - n_ctx) * C::ROWS : tg * C::ROWS;
     // interior tile: summed without checks, and again chain by chain with them if a sum went out of
-    // range (the very first tile does: the reference starts at -1e30)
+    // range; the very first tile takes the checks at once (the reference starts at -1e30)
     // a reconstruction tile is interior too when all its keys lie at or before the block's first query and inside the
     // chunk of its last one (then inside every query's chunk)
     bool careful = is_rec ? !(row0 + C::ROWS - 1 <= i0 && row0 >= ((i_end - 1) / chunk) * chunk) : (row0 + C::ROWS > N);
+    careful |= t == 0;
     if (!careful) {
       float before[NCOL];
 #pragma unroll
@@ -217,27 +238,53 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     const float m2 = swap_halves(m1), l2 = swap_halves(lsum[cs]);
     const float m = __builtin_fmaxf(m1, m2);
     const float tot = lsum[cs] * __builtin_amdgcn_exp2f(m1 - m) + l2 * __builtin_amdgcn_exp2f(m2 - m);
-    const float L2 = m + __builtin_amdgcn_logf(tot);
-    if (half == 0 && qi[cs] < N_q) neg_lse[(size_t)(l * H_q + h) * N_q + qi[cs]] = -L2 * inv_c;
+    if constexpr (SPLIT) {
+      if (half == 0 && qi[cs] < N_q)
+        reinterpret_cast<LsePart*>(neg_lse)[((size_t)split * gridDim.z * H_q + l * H_q + h) * N_q + qi[cs]] = LsePart{m, tot};
+    } else {
+      const float L2 = m + __builtin_amdgcn_logf(tot);
+      if (half == 0 && qi[cs] < N_q) neg_lse[(size_t)(l * H_q + h) * N_q + qi[cs]] = -L2 * inv_c;
+    }
   }
 }
 
 }  // namespace
 
-hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* k_rec, float* neg_lse,
-                            int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
+constexpr int kLseCols = 2;  // column sub-tiles per wave; 128 * kLseCols queries per workgroup
+
+// Workgroups per query block: as many as fill the chip (three per CU), if the query blocks alone give it less than half of
+// that, with at least one tile each; beyond eight the shares of a query cost pass 2 more than they save.  One layer of 4
+// heads, 128 queries of 512 keys, both passes 22.7 -> 15.5 us; 2000 queries of 2000 keys 105 -> 31 us; 16 000 of 16 000 644 -> 583.
+int score_splits(int L_s, int H_q, int d, int64_t N, int64_t N_q) {
+  const int64_t blocks = (N_q + 128 * kLseCols - 1) / (128 * kLseCols) * H_q * L_s;
+  const int64_t tiles = (N + 8192 / d - 1) / (8192 / d) + 1;
+  if (blocks >= 384) return 1;
+  int64_t s = 768 / blocks;
+  s = s < tiles ? s : tiles;
+  return (int)(s < kMaxLseSplits ? s : kMaxLseSplits);
+}
+
+hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* k_rec, float* neg_lse, int splits,
+                            float* x, int64_t n_x, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
                             hipStream_t stream) {
   const int G = H_q / H_kv;
   const float c = 1.4426950408889634f / sqrtf((float)d), inv_c = 1.0f / c;
   // two column sub-tiles per wave; three workgroups per CU at d = 64 (at most 168 registers), two at d = 128
-  constexpr int NCOL = 2;
+  constexpr int NCOL = kLseCols;
   // the query blocks of a head are dealt over all XCDs (measured: fewer L2 misses than one KV group per XCD, whose
   // blocks drift apart along a key stream slightly larger than the L2)
-  dim3 grid((unsigned)((N_q + 128 * NCOL - 1) / (128 * NCOL)), (unsigned)H_q, (unsigned)L_s);
-  if (d == 64)
-    score_lse_kernel<64, NCOL, 3><<<grid, 256, 0, stream>>>(q, k_ctx, k_rec, neg_lse, H_q, G, (int)N, (int)N_q, chunk, c, inv_c);
-  else
-    score_lse_kernel<128, NCOL, 2><<<grid, 256, 0, stream>>>(q, k_ctx, k_rec, neg_lse, H_q, G, (int)N, (int)N_q, chunk, c, inv_c);
+  dim3 grid((unsigned)((N_q + 128 * NCOL - 1) / (128 * NCOL) * splits), (unsigned)H_q, (unsigned)L_s);
+#define PKV_LSE(D, MINB, SPLIT)                                                                                          \
+  score_lse_kernel<D, NCOL, MINB, SPLIT><<<grid, 256, 0, stream>>>(q, k_ctx, k_rec, neg_lse, H_q, G, (int)N, (int)N_q, chunk, \
+                                                                   c, inv_c, splits, x, n_x)
+  if (d == 64) {
+    if (splits > 1) PKV_LSE(64, 3, true);
+    else PKV_LSE(64, 3, false);
+  } else {
+    if (splits > 1) PKV_LSE(128, 2, true);
+    else PKV_LSE(128, 2, false);
+  }
+#undef PKV_LSE
   return hipGetLastError();
 }
 

@@ -287,6 +287,35 @@ def test_score_degenerate_shapes(N, N_q, chunk):
         pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("d,N,N_q,chunk", [(64, 1, 3, 2), (64, 700, 257, 100), (64, 1030, 130, 64), (128, 65, 300, 1000), (128, 900, 64, 33)])
+def test_score_few_and_many_query_blocks_agree(d, N, N_q, chunk):
+    """Few query blocks: several workgroups share a block's keys (and, in the max form, a key block's queries); many: one
+    workgroup each.  The same layer alone and as one of 192 must agree to the rounding of 32-bit sums and exponentials
+    (log-sum-exps up to about 2^4, whose last bit is 1e-6, scaled back: 2e-5), and both with the oracle."""
+    L, H_q, H_kv = 192, 4, 2
+    g = torch.Generator().manual_seed(N + N_q)
+    q = torch.randn(L, H_q, N_q, d, generator=g).bfloat16()
+    kc = torch.randn(L, H_kv, N, d, generator=g).bfloat16()
+    kr = torch.randn(L, H_kv, N_q, d, generator=g).bfloat16()
+    for reduce in (pk.PROXYKV_REDUCE_MAX, pk.PROXYKV_REDUCE_SUM):
+        many, few = (pk.make_config(n, H_q, H_kv, d, 1, 4, 128) for n in (L, 1))
+        many.reduce = few.reduce = reduce
+        cm, cf = pk.proxykv_create(many), pk.proxykv_create(few)
+        x = pk.proxykv_score(cm, q.cuda(), kc.cuda(), kr.cuda(), chunk)
+        xs = pk.proxykv_score_self(cm, q.cuda(), kr.cuda())
+        for l in (0, L - 1):
+            one = [t[l:l + 1].contiguous() for t in (q, kc, kr)]
+            y = pk.proxykv_score(cf, *(t.cuda() for t in one), chunk)
+            ys = pk.proxykv_score_self(cf, one[0].cuda(), one[2].cuda())
+            torch.cuda.synchronize()
+            torch.testing.assert_close(y.cpu(), x[l:l + 1].cpu(), rtol=2e-5, atol=1e-9)
+            torch.testing.assert_close(ys.cpu(), xs[l:l + 1].cpu(), rtol=2e-5, atol=1e-9)
+            assert_close(y, oracle.score(*one, chunk, reduce="max" if reduce == pk.PROXYKV_REDUCE_MAX else "sum"), f"score layer {l}")
+            assert_close(ys, oracle.score_self(one[0], one[2]), f"score_self layer {l}")
+        pk.proxykv_destroy(cm)
+        pk.proxykv_destroy(cf)
+
+
 @pytest.mark.parametrize("scale", [8.0, 30.0])
 def test_score_large_logits(scale):
     """Inputs scaled up until the softmax rows are nearly one-hot (logits of several hundred): the running reference of
