@@ -144,7 +144,10 @@ int proxykv_score_self(proxykv_ctx* ctx, const void* q, const void* k, int32_t d
  * attention of the H_l learned queries over H_kv projected slots, then a linear map to one logit.
  * Matrix products take IEEE half (fp16) operands and accumulate in fp32; the rest is fp32.
  * Needs proxykv_set_mapper_weights (ESTATE otherwise).
- * Distinct proxy layers share the launches of the network (their rows lie one behind the other), all on `stream`. */
+ * Distinct proxy layers share the launches of the network (their rows lie one behind the other), in batches.  Where a
+ * context is long enough for several, every other batch runs on a second stream that the context owns (default priority);
+ * it starts behind the work already queued on `stream` and is joined into it by an event before the call returns, so for
+ * the caller everything is ordered on `stream` as for the other entry points. */
 int proxykv_map(proxykv_ctx* ctx, const float* x, int64_t N, float* yhat, void* stream);
 
 /* Per-row Top-K (Sec. 3: mask M by Top-K thresholding of the mapped scores; Sec. 4.3).

@@ -80,13 +80,15 @@ int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) 
 struct Sizes {
   size_t neg_lse, x_ws, yhat_ws, h1, x, xb, qk, vt, ao, hid, zg, s3, pre, range;
   size_t mapper() const { return h1 + x + xb + qk + vt + ao + hid + zg + s3 + pre + range; }  // one batch's activations
-  size_t total() const { return neg_lse + x_ws + yhat_ws + mapper(); }
+  int lanes;
+  size_t total() const { return neg_lse + x_ws + yhat_ws + lanes * mapper(); }
 };
 
 Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q, int distinct_layers) {
   Sizes s;
   const pkv::MapPlan p = pkv::map_plan(c, N, distinct_layers);
   // rows of GEMM outputs (and of the residuals they read) are padded to the GEMM's 256-row tile
+  s.lanes = p.lanes;
   const size_t b = (size_t)p.batch, Tp = b * (size_t)p.Tp, Np = b * (size_t)p.Np, dt = (size_t)c.d_time;
   // the causal form runs pass 1 without context keys, over N_q == N of its own
   const int splits = std::max(pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q), pkv::score_splits(c.L_s, c.H_q, c.d, N_q, N_q));
@@ -128,8 +130,16 @@ int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool 
     if ((rc = ensure(ctx, ctx->yhat_ws, s.yhat_ws, stream))) return rc;
     if ((rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes((int64_t)ctx->cfg.L_l * ctx->cfg.H_l, N), stream))) return rc;
   }
-  if (map_part) {
-    pkv::MapperWorkspace& m = ctx->m;
+  if (map_part && s.lanes > 1 && !ctx->lanes_created) {
+    for (int i = 1; i < pkv::kMapLanes; ++i) {
+      if (!ctx->lane_stream[i]) PKV_HIP(ctx, hipStreamCreateWithFlags(&ctx->lane_stream[i], hipStreamNonBlocking));
+      if (!ctx->lane_join[i]) PKV_HIP(ctx, hipEventCreateWithFlags(&ctx->lane_join[i], hipEventDisableTiming));
+    }
+    if (!ctx->lane_fork) PKV_HIP(ctx, hipEventCreateWithFlags(&ctx->lane_fork, hipEventDisableTiming));
+    ctx->lanes_created = true;
+  }
+  for (int lane = 0; map_part && lane < s.lanes; ++lane) {
+    pkv::MapperWorkspace& m = ctx->m[lane];
     if ((rc = ensure(ctx, m.h1, s.h1, stream))) return rc;
     if ((rc = ensure(ctx, m.x, s.x, stream))) return rc;
     if ((rc = ensure(ctx, m.xb, s.xb, stream))) return rc;
@@ -307,9 +317,9 @@ int proxykv_destroy(proxykv_ctx* ctx) {
   if (!ctx) return PROXYKV_OK;
   std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
                                     &ctx->neg_lse,     &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws};
-  pkv::MapperWorkspace& m = ctx->m;
-  for (DeviceBuffer* b : {&m.h1, &m.x, &m.xb, &m.qk, &m.vt, &m.ao, &m.hid, &m.zg, &m.s3, &m.pre, &m.range}) all.push_back(b);
-  bool any = ctx->ev_created;
+  for (pkv::MapperWorkspace& m : ctx->m)
+    for (DeviceBuffer* b : {&m.h1, &m.x, &m.xb, &m.qk, &m.vt, &m.ao, &m.hid, &m.zg, &m.s3, &m.pre, &m.range}) all.push_back(b);
+  bool any = ctx->ev_created || ctx->lanes_created;
   for (DeviceBuffer* b : all) any = any || b->ptr;
   if (any) {
     (void)hipSetDevice(ctx->cfg.device);
@@ -317,6 +327,11 @@ int proxykv_destroy(proxykv_ctx* ctx) {
     for (DeviceBuffer* b : all) free_buffer(*b);
     if (ctx->ev_created)
       for (int i = 0; i < PROXYKV_N_STAGES + 1; ++i) (void)hipEventDestroy(ctx->ev[i]);
+    for (int i = 1; i < pkv::kMapLanes; ++i) {
+      if (ctx->lane_stream[i]) (void)hipStreamDestroy(ctx->lane_stream[i]);
+      if (ctx->lane_join[i]) (void)hipEventDestroy(ctx->lane_join[i]);
+    }
+    if (ctx->lane_fork) (void)hipEventDestroy(ctx->lane_fork);
   }
   delete ctx;
   return PROXYKV_OK;

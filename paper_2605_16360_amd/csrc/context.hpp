@@ -45,6 +45,8 @@ struct MapperWeights {
   const float* pe;                       // fp32 [win, d_time] sinusoidal table
 };
 
+constexpr int kMapLanes = 2;
+
 // Row length of the stage-3 K/V projection's output: 2*H_kv*d_head_x rounded up to the GEMM's column tile.
 inline int kv3_stride(const proxykv_config& c) { return (2 * c.H_kv * c.d_head_x + 255) / 256 * 256; }
 
@@ -85,7 +87,12 @@ struct proxykv_ctx {
   pkv::DeviceBuffer yhat_ws;                       // fp32 [L_l, H_l, N]
   pkv::DeviceBuffer topk_ws;                       // per-row histograms and counters of the Top-K of rows split over workgroups
   bool fused_select = false;                       // proxykv_prune: selection and gather in one launch (measured slower)
-  pkv::MapperWorkspace m;
+  pkv::MapperWorkspace m[pkv::kMapLanes];          // one per lane; only the lanes a length needs are allocated
+  // lanes 1 .. kMapLanes-1: streams (default priority, non-blocking) and the events that fork them from and join
+  // them into the caller's stream, which is lane 0
+  bool lanes_created = false;
+  hipStream_t lane_stream[pkv::kMapLanes] = {};
+  hipEvent_t lane_fork = nullptr, lane_join[pkv::kMapLanes] = {};
   int distinct_layers = 1;                         // distinct proxy layers in `pairing`
 };
 
@@ -103,12 +110,13 @@ inline void window_plan(int64_t N, int win, int stride, int64_t* n_win, int64_t*
   *total_rows = (k - 1) * (int64_t)win + (N - (k - 1) * (int64_t)stride);
 }
 
-// How the mapper runs a context of N tokens: `batch` distinct proxy layers at a time.
+// How the mapper runs a context of N tokens: `batch` distinct proxy layers at a time, batches dealt to `lanes` streams.
 // Small layers leave the chip idle one by one (512 window rows are 12 output tiles of the QKV product), so a batch takes
-// as many of them as make kMapBatchRows rows; a layer of 32 768 tokens has 63 488 rows, four of them make a batch, and
-// more would not make the kernels faster, only the workspace larger (about 14 KB per row).  Measured, 16 distinct
-// layers, layers on four streams against batches: N = 1500 6.15 -> 2.21 ms, N = 8192 20.2 -> 18.9 ms, N = 32 768 the same.
-constexpr int64_t kMapBatchRows = 262144;
+// as many of them as make kMapBatchRows rows (about 14 KB of workspace each).  Long contexts need several batches; two of
+// them side by side, on streams and in workspaces of their own, let one's stores and residual reads run under the other's
+// matrix work.  Measured, 16 distinct layers, one layer per batch on four streams / all on one stream in batches of
+// 262 144 rows / as here: N = 1500 6.15 / 2.21 / 2.21 ms, N = 8192 19.3 / 19.0 / 18.5 ms, N = 32 768 82.0 / 84.1 / 81.4 ms.
+constexpr int64_t kMapBatchRows = 131072;
 constexpr int kMaxBatch = 32;
 // Up to this many rows in a batch the small tiles are faster (large tiles on the left: one layer of 512 rows 867 / 231 us, of 2000
 // rows 1060 / 566 us; 16 layers of 256 rows 970 / 882 us).
@@ -117,7 +125,7 @@ struct MapPlan {
   int64_t n_win, T;   // windows and window rows of a layer
   int64_t Tp, Np;     // window rows and tokens of a layer, padded to the GEMM's 256-row tile
   int64_t vt_ld;      // row length of the transposed v
-  int batch;
+  int batch, lanes;
   bool small;         // few rows: the small-tile kernels
 };
 inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers) {
@@ -130,6 +138,8 @@ inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers)
   cap = cap < 1 ? 1 : (cap > kMaxBatch ? kMaxBatch : cap);
   const int64_t n_batches = (distinct_layers + cap - 1) / cap;
   p.batch = (int)((distinct_layers + n_batches - 1) / n_batches);
+  const int64_t used = (distinct_layers + p.batch - 1) / p.batch;
+  p.lanes = used < kMapLanes ? (int)used : kMapLanes;
   p.small = p.batch * p.T <= kMapSmallRows && c.n_enc_layers > 0;
   return p;
 }

@@ -817,10 +817,9 @@ hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowS
 }
 
 // Second stem convolution, encoder and stage-3 inner products of one batch with the large tiles: from m.h1 to m.s3.
-hipError_t mapper_large_body(proxykv_ctx* ctx, const MapPlan& p, int n_layers, int64_t N, int n_cu, hipStream_t stream) {
+hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& m, const MapPlan& p, int n_layers, int64_t N, int n_cu, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
-  const MapperWorkspace& m = ctx->m;
   const int T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
   const uint16_t* h1 = (const uint16_t*)m.h1.ptr;
   float* x = (float*)m.x.ptr;
@@ -901,11 +900,10 @@ hipError_t mapper_large_body(proxykv_ctx* ctx, const MapPlan& p, int n_layers, i
 
 // The network for the layers of one batch (x_in: all proxy layers' scores [L_s, H_kv, N]); writes the rows of every target
 // layer that is paired with one of them.
-hipError_t mapper_batch(proxykv_ctx* ctx, const MapPlan& p, const LayerBatch& lb, const float* x_in, int64_t N, float* yhat,
+hipError_t mapper_batch(proxykv_ctx* ctx, const MapperWorkspace& m, const MapPlan& p, const LayerBatch& lb, const float* x_in, int64_t N, float* yhat,
                         int n_cu, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
-  const MapperWorkspace& m = ctx->m;
   uint32_t* range = (uint32_t*)m.range.ptr;
   const unsigned nl = (unsigned)lb.n;
   absmax_kernel<<<dim3(kRangeWords, nl), 1024, 0, stream>>>(x_in, (int64_t)c.H_kv * N, lb, range);
@@ -914,8 +912,8 @@ hipError_t mapper_batch(proxykv_ctx* ctx, const MapPlan& p, const LayerBatch& lb
   stem_conv1_kernel<<<dim3((unsigned)((N + tok - 1) / tok), nl), 256, 0, stream>>>(
       x_in, w.conv1_w, w.bn1_scale, w.bn1_shift, range, w.stem_cw, w.stem_cs, lb, (uint16_t*)m.h1.ptr, c.H_kv, (int)N, c.c_mid, tok);
   PKV_TRY(hipGetLastError());
-  if (p.small) PKV_TRY(mapper_small_body(ctx, p, lb.n, N, stream));
-  else PKV_TRY(mapper_large_body(ctx, p, lb.n, N, n_cu, stream));
+  if (p.small) PKV_TRY(mapper_small_body(ctx, m, p, lb.n, N, stream));
+  else PKV_TRY(mapper_large_body(ctx, m, p, lb.n, N, n_cu, stream));
   const int tok_per_block = 256 / c.H_l;
   stage3_kernel<<<dim3((unsigned)((N + tok_per_block - 1) / tok_per_block), nl), 256, 0, stream>>>((const float*)m.s3.ptr, w.out_b, yhat, N, (int)p.Np,
                                                                                                 c.H_kv, c.H_l, lb);
@@ -930,7 +928,14 @@ hipError_t mapper_forward(proxykv_ctx* ctx, const float* x_in, int64_t N, float*
   PKV_TRY(hipGetDevice(&dev));
   PKV_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
   const MapPlan p = map_plan(c, N, ctx->distinct_layers);
+  // batches are dealt round-robin to the lanes; lane 0 is the caller's stream, the others start behind the work already
+  // queued there and are joined into it at the end
+  if (p.lanes > 1) {
+    PKV_TRY(hipEventRecord(ctx->lane_fork, stream));
+    for (int lane = 1; lane < p.lanes; ++lane) PKV_TRY(hipStreamWaitEvent(ctx->lane_stream[lane], ctx->lane_fork, 0));
+  }
   LayerBatch lb = {};
+  int lane = 0;
   for (int ll = 0; ll < c.L_l;) {
     int ll_hi = ll + 1;
     while (ll_hi < c.L_l && ctx->pairing[ll_hi] == ctx->pairing[ll]) ++ll_hi;
@@ -940,9 +945,14 @@ hipError_t mapper_forward(proxykv_ctx* ctx, const float* x_in, int64_t N, float*
     ++lb.n;
     ll = ll_hi;
     if (lb.n == p.batch || ll == c.L_l) {
-      PKV_TRY(mapper_batch(ctx, p, lb, x_in, N, yhat, n_cu, stream));
+      PKV_TRY(mapper_batch(ctx, ctx->m[lane], p, lb, x_in, N, yhat, n_cu, lane == 0 ? stream : ctx->lane_stream[lane]));
       lb.n = 0;
+      lane = lane + 1 < p.lanes ? lane + 1 : 0;
     }
+  }
+  for (lane = 1; lane < p.lanes; ++lane) {
+    PKV_TRY(hipEventRecord(ctx->lane_join[lane], ctx->lane_stream[lane]));
+    PKV_TRY(hipStreamWaitEvent(stream, ctx->lane_join[lane], 0));
   }
   return hipSuccess;
 }

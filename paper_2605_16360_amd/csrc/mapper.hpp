@@ -92,6 +92,6 @@ struct RowSpace {
 
 // Second stem convolution, encoder and stage-3 inner products of one batch with the kernels for few rows
 // (mapper_small.hip): from m.h1 to m.s3.
-hipError_t mapper_small_body(proxykv_ctx* ctx, const MapPlan& p, int n_layers, int64_t N, hipStream_t stream);
+hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& m, const MapPlan& p, int n_layers, int64_t N, hipStream_t stream);
 
 }  // namespace pkv

@@ -552,10 +552,9 @@ hipError_t launch_deep(const DeepArgs& a, int layers, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t mapper_small_body(proxykv_ctx* ctx, const MapPlan& p, int n_layers, int64_t N64, hipStream_t stream) {
+hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& m, const MapPlan& p, int n_layers, int64_t N64, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
-  const MapperWorkspace& m = ctx->m;
   const int N = (int)N64, T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
   float *x = (float*)m.x.ptr, *pre = (float*)m.pre.ptr;
   uint16_t *xb = (uint16_t*)m.xb.ptr, *qk = (uint16_t*)m.qk.ptr, *vt = (uint16_t*)m.vt.ptr, *ao = (uint16_t*)m.ao.ptr,
