@@ -18,6 +18,10 @@
 // attained one, so neither overflow nor underflow loses anything.  The kernel writes -L2 / c per
 // row, L2 = m_ref + log2(lsum), which pass 2 uses as the accumulator's initial value.
 //
+// Tiles that causality, a chunk boundary or the end of the context cuts are masked and summed the same way; the checked
+// path, whose chains wait for each other (three times as long per tile), is left for columns without a reference and for
+// sums out of range.  The first reference comes from the first 32 keys.  16 layers of 4097 tokens, causal: 1343 -> 980 us.
+//
 // Streaming: three LDS buffers and one barrier per tile.  While tile t is computed, tile t+2 goes
 // from registers to LDS and tile t+3 is fetched from global memory into registers.
 //
@@ -160,6 +164,57 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     }
   };
 
+  // Where a chain of the tile at row0 (32 keys from jbase on, the wave's column sub-tile cs) stands: nothing of it is visible,
+  // some of it, or all.  All of it is where every key lies at or before the first query, and inside its last one's chunk.
+  auto hidden = [&](bool is_rec, int jbase, int limit, int cs) {
+    return jbase >= limit || (is_rec && jbase > wave_i_lo + cs * 32 + 31);
+  };
+  auto cut = [&](bool is_rec, int jbase, int limit, int cs) {
+    const int cs_i_lo = wave_i_lo + cs * 32;
+    return is_rec ? !(jbase + 31 <= cs_i_lo && jbase >= ((cs_i_lo + 31) / chunk) * chunk) : jbase + 32 > limit;
+  };
+  auto mask_chain = [&](f32x16& acc, bool is_rec, int jbase, int cs) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int j = jbase + (r >> 2) * 8 + half * 4 + (r & 3);
+      const bool vis = is_rec ? (j <= qi[cs] && j >= qlo[cs]) : (j < N);
+      acc[r] = vis ? acc[r] : kNegInf;
+    }
+  };
+  // a tile that causality, a chunk boundary or the end of the context cuts: its visible chains, summed without checks
+  auto cut_tile = [&](const u32x4* buf, bool is_rec, int row0, int limit) {
+    for (int s = 0; s < C::SUB; ++s) {
+      const int jbase = row0 + s * 32;
+      if (hidden(is_rec, jbase, limit, NCOL - 1)) break;
+      bf16x8 a[C::KK];
+#pragma unroll
+      for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, s * 32 + l32, kk * 2 + half);
+#pragma unroll
+      for (int cs = 0; cs < NCOL; ++cs) {
+        if (hidden(is_rec, jbase, limit, cs)) continue;
+        f32x16 acc = splat16(0.0f);
+#pragma unroll
+        for (int kk = 0; kk < C::KK; ++kk) acc = mfma_32x32x16(a[kk], b[cs][kk], acc);
+        if (cut(is_rec, jbase, limit, cs)) mask_chain(acc, is_rec, jbase, cs);
+        lsum[cs] += fast_sum(acc, cs);
+      }
+    }
+  };
+  // the first reference of every column: the largest logit of the first 32 keys of an interior tile
+  auto first_reference = [&](const u32x4* buf) {
+    bf16x8 a[C::KK];
+#pragma unroll
+    for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, l32, kk * 2 + half);
+#pragma unroll
+    for (int cs = 0; cs < NCOL; ++cs) {
+      f32x16 acc = splat16(0.0f);
+#pragma unroll
+      for (int kk = 0; kk < C::KK; ++kk) acc = mfma_32x32x16(a[kk], b[cs][kk], acc);
+      const float tm = max16_tree(acc, kNegInf) * c;
+      if (tm > -1.0e30f) nref[cs] = -tm;
+    }
+  };
+
   if (total > 0) {
     TileRegs<D> second;  // the first two tiles are asked for together
     fetch(0);
@@ -178,55 +233,44 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     const int tg = t0 + t;
     const bool is_rec = tg >= n_ctx;
     const int row0 = is_rec ? rec_lo + (tg - n_ctx) * C::ROWS : tg * C::ROWS;
-    // interior tile: summed without checks, and again chain by chain with them if a sum went out of
-    // range; the very first tile takes the checks at once (the reference starts at -1e30)
-    // a reconstruction tile is interior too when all its keys lie at or before the block's first query and inside the
-    // chunk of its last one (then inside every query's chunk)
-    bool careful = is_rec ? !(row0 + C::ROWS - 1 <= i0 && row0 >= ((i_end - 1) / chunk) * chunk) : (row0 + C::ROWS > N);
-    careful |= t == 0;
-    if (!careful) {
+    // Summed without checks, and again chain by chain with them if a sum went out of range (as it does where a column has
+    // no reference yet).  A reconstruction tile is interior too when all its keys lie at or before the block's first query
+    // and inside the chunk of its last one (then inside every query's chunk).
+    const int limit = is_rec ? i_end : N;
+    const bool interior = is_rec ? row0 + C::ROWS - 1 <= i0 && row0 >= ((i_end - 1) / chunk) * chunk : row0 + C::ROWS <= N;
+    // A share of a few tiles starts with the checks at once: there the way to a first reference costs more than it saves.
+    bool redo = SPLIT && t == 0 && total < 4;
+    if (!redo) {
+      if (t == 0 && interior) first_reference(buf);
       float before[NCOL];
 #pragma unroll
       for (int cs = 0; cs < NCOL; ++cs) before[cs] = lsum[cs];
-      interior_tile(buf);
+      if (interior) interior_tile(buf);
+      else cut_tile(buf, is_rec, row0, limit);
       bool bad = false;
 #pragma unroll
       for (int cs = 0; cs < NCOL; ++cs) bad |= !(lsum[cs] < kTileRedo);
-      if (__builtin_amdgcn_ballot_w64(bad)) {
+      redo = __builtin_amdgcn_ballot_w64(bad) != 0;
+      if (redo) {
 #pragma unroll
         for (int cs = 0; cs < NCOL; ++cs) lsum[cs] = before[cs];
-        careful = true;
       }
     }
-    if (careful) {
-      // ragged context tail, a reconstruction tile where causality and chunk boundaries cut, or a redo
-      const int limit = is_rec ? i_end : N;
-#pragma unroll
+    if (redo) {
+#pragma unroll 1
       for (int s = 0; s < C::SUB; ++s) {
         const int jbase = row0 + s * 32;
-        if (jbase >= limit) break;
-        if (is_rec && jbase > wave_i_lo + NCOL * 32 - 1) break;  // keys after the wave's last query
+        if (hidden(is_rec, jbase, limit, NCOL - 1)) break;
         bf16x8 a[C::KK];
 #pragma unroll
         for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, s * 32 + l32, kk * 2 + half);
 #pragma unroll
         for (int cs = 0; cs < NCOL; ++cs) {
-          const int cs_i_lo = wave_i_lo + cs * 32;
-          if (is_rec && jbase > cs_i_lo + 31) continue;  // wave-uniform: keys after the sub-tile's last query
+          if (hidden(is_rec, jbase, limit, cs)) continue;
           f32x16 acc = splat16(0.0f);
 #pragma unroll
           for (int kk = 0; kk < C::KK; ++kk) acc = mfma_32x32x16(a[kk], b[cs][kk], acc);
-          // no mask needed when every key of the sub-tile is <= the first query and >= every query's chunk start
-          const bool cut = is_rec ? !(jbase + 31 <= cs_i_lo && jbase >= ((cs_i_lo + 31) / chunk) * chunk)
-                                  : (jbase + 32 > limit);
-          if (cut) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int j = jbase + (r >> 2) * 8 + half * 4 + (r & 3);
-              const bool vis = is_rec ? (j <= qi[cs] && j >= qlo[cs]) : (j < N);
-              acc[r] = vis ? acc[r] : kNegInf;
-            }
-          }
+          if (cut(is_rec, jbase, limit, cs)) mask_chain(acc, is_rec, jbase, cs);
           accumulate(acc, cs);
         }
       }
