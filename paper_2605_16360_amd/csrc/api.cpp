@@ -78,10 +78,10 @@ int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) 
 }
 
 struct Sizes {
-  size_t neg_lse, x_ws, yhat_ws, h1, x, xb, qk, vt, ao, hid, zg, s3, pre, range;
+  size_t neg_lse, x_parts, x_ws, yhat_ws, h1, x, xb, qk, vt, ao, hid, zg, s3, pre, range;
   size_t mapper() const { return h1 + x + xb + qk + vt + ao + hid + zg + s3 + pre + range; }  // one batch's activations
   int lanes;
-  size_t total() const { return neg_lse + x_ws + yhat_ws + lanes * mapper(); }
+  size_t total() const { return neg_lse + x_parts + x_ws + yhat_ws + lanes * mapper(); }
 };
 
 Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q, int distinct_layers) {
@@ -93,6 +93,10 @@ Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q, int disti
   // the causal form runs pass 1 without context keys, over N_q == N of its own
   const int splits = std::max(pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q), pkv::score_splits(c.L_s, c.H_q, c.d, N_q, N_q));
   s.neg_lse = (size_t)c.L_s * c.H_q * (size_t)N_q * (splits > 1 ? 8 * (size_t)splits : 4);
+  const size_t n_x = (size_t)c.L_s * c.H_kv * (size_t)N;
+  int parts = pkv::score_query_splits(true, c.L_s, c.H_q, c.H_kv, c.d, N, N);  // the causal form
+  if (c.reduce == PROXYKV_REDUCE_SUM) parts = std::max(parts, pkv::score_query_splits(true, c.L_s, c.H_q, c.H_kv, c.d, N, N_q));
+  s.x_parts = parts > 1 ? n_x * 4 * (size_t)parts : 0;
   s.x_ws = (size_t)c.L_s * c.H_kv * (size_t)N * 4;
   s.yhat_ws = (size_t)c.L_l * c.H_l * (size_t)N * 4;
   s.h1 = b * ((size_t)N + 2) * (size_t)c.c_mid * 2;
@@ -125,6 +129,7 @@ int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool 
   const Sizes s = workspace_sizes(ctx->cfg, N, N_q, ctx->distinct_layers);
   int rc = PROXYKV_OK;
   if (score_part && (rc = ensure(ctx, ctx->neg_lse, s.neg_lse, stream))) return rc;
+  if (score_part && (rc = ensure(ctx, ctx->x_parts, s.x_parts, stream))) return rc;
   if (prune_part) {
     if ((rc = ensure(ctx, ctx->x_ws, s.x_ws, stream))) return rc;
     if ((rc = ensure(ctx, ctx->yhat_ws, s.yhat_ws, stream))) return rc;
@@ -231,13 +236,15 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q);
-  const int64_t n_x = (int64_t)c.L_s * c.H_kv * N;
-  PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, splits, x_out, n_x, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
+  const bool sum = c.reduce == PROXYKV_REDUCE_SUM;
+  const int q_splits = pkv::score_query_splits(sum, c.L_s, c.H_q, c.H_kv, c.d, N, N_q);
+  const int64_t n_clear = !sum && (splits > 1 || q_splits > 1) ? (int64_t)c.L_s * c.H_kv * N : 0;
+  PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, splits, x_out, n_clear, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
-  if (c.reduce == PROXYKV_REDUCE_SUM)
-    PKV_HIP(ctx, pkv::launch_score_colsum(q, kc, nl, splits, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, false, stream));
+  if (sum)
+    PKV_HIP(ctx, pkv::launch_score_colsum(q, kc, nl, splits, x_out, (float*)ctx->x_parts.ptr, q_splits, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, false, stream));
   else
-    PKV_HIP(ctx, pkv::launch_score_colmax(q, kc, nl, splits, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, stream));
+    PKV_HIP(ctx, pkv::launch_score_colmax(q, kc, nl, splits, x_out, q_splits, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, stream));
   if ((rcm = mark(ctx, 2, stream))) return rcm;
   return PROXYKV_OK;
 }
@@ -265,9 +272,10 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N);
-  PKV_HIP(ctx, pkv::launch_score_lse(q, k, k, nl, splits, x_out, (int64_t)c.L_s * c.H_kv * N, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
+  const int q_splits = pkv::score_query_splits(true, c.L_s, c.H_q, c.H_kv, c.d, N, N);
+  PKV_HIP(ctx, pkv::launch_score_lse(q, k, k, nl, splits, x_out, 0, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
-  PKV_HIP(ctx, pkv::launch_score_colsum(q, k, nl, splits, x_out, c.L_s, c.H_q, c.H_kv, c.d, N, N, true, stream));
+  PKV_HIP(ctx, pkv::launch_score_colsum(q, k, nl, splits, x_out, (float*)ctx->x_parts.ptr, q_splits, c.L_s, c.H_q, c.H_kv, c.d, N, N, true, stream));
   if ((rcm = mark(ctx, 2, stream))) return rcm;
   return PROXYKV_OK;
 }
@@ -316,7 +324,7 @@ int proxykv_create(proxykv_ctx** out, const proxykv_config* cfg) {
 int proxykv_destroy(proxykv_ctx* ctx) {
   if (!ctx) return PROXYKV_OK;
   std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
-                                    &ctx->neg_lse,     &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws};
+                                    &ctx->neg_lse, &ctx->x_parts, &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws};
   for (pkv::MapperWorkspace& m : ctx->m)
     for (DeviceBuffer* b : {&m.h1, &m.x, &m.xb, &m.qk, &m.vt, &m.ao, &m.hid, &m.zg, &m.s3, &m.pre, &m.range}) all.push_back(b);
   bool any = ctx->ev_created || ctx->lanes_created;

@@ -82,7 +82,8 @@ struct proxykv_ctx {
   std::vector<int32_t> pairing;  // [L_l] 0-based proxy layer per target layer
   // workspace
   pkv::DeviceBuffer q_bf16, kctx_bf16, krec_bf16;  // bf16 copies of fp32 inputs
-  pkv::DeviceBuffer neg_lse;                       // fp32 [L_s, H_q, N_q]
+  pkv::DeviceBuffer neg_lse;                       // fp32 [L_s, H_q, N_q], or (reference, sum) pairs of several workgroups
+  pkv::DeviceBuffer x_parts;                       // sum form: the column sums of several workgroups per key block
   pkv::DeviceBuffer x_ws;                          // fp32 [L_s, H_kv, N]
   pkv::DeviceBuffer yhat_ws;                       // fp32 [L_l, H_l, N]
   pkv::DeviceBuffer topk_ws;                       // per-row histograms and counters of the Top-K of rows split over workgroups

@@ -12,21 +12,24 @@ hipError_t launch_f32_to_bf16(const float* const in[3], uint16_t* const out[3], 
 // Scoring, pass 1: neg_lse[l, h, i] = -log2(sum_k 2^(c * <q_i, k>)) / c with c = log2(e) / sqrt(d),
 // the sum running over the N context keys and the visible reconstruction keys of query i.
 // With splits = score_splits(...) > 1 several workgroups share a query's keys: neg_lse then takes 8 * splits bytes per query
-// instead of four, and x [n_x] is cleared for pass 2.
+// instead of four.  x [n_x] is cleared for pass 2 (n_x = 0: left alone).
 int score_splits(int L_s, int H_q, int d, int64_t N, int64_t N_q);
 hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* k_rec, float* neg_lse, int splits,
                             float* x, int64_t n_x, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
                             hipStream_t stream);
 // Scoring, pass 2: x[l, g, n] = 2^(c * max over (head of group g, query i) of (<q_i, k_n> + neg_lse[l, h, i])).
-// neg_lse and splits as pass 1 left them.
+// neg_lse and splits as pass 1 left them.  q_splits = score_query_splits(...) workgroups share a key block's queries; with
+// splits > 1 or q_splits > 1 they raise x, which pass 1 has to clear.
+int score_query_splits(bool sum, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q);
 hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x,
-                               int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q,
+                               int q_splits, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q,
                                hipStream_t stream);
 
 // Scoring, pass 2 in the sum form: x[l, g, n] = sum over (head of group g, query i) of 2^(c * (<q_i, k_n> + neg_lse[l, h, i])).
 // causal: the keys are the queries' own sequence (N == N_q) and query i adds to keys n <= i only.
+// With q_splits > 1 `parts` takes q_splits * L_s * H_kv * N floats on the way.
 hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x,
-                               int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, bool causal,
+                               float* parts, int q_splits, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, bool causal,
                                hipStream_t stream);
 // Per-row Top-K.  Rows longer than 36 864 scores are split over several workgroups and need `scratch` (device memory, any
 // contents, 256-byte aligned; rows <= 65535 then) of topk_scratch_bytes(rows, N) bytes, or, for one more pass over the

@@ -33,9 +33,9 @@ namespace {
 // Chains are handled in pairs (two column sub-tiles): the MFMAs of pair i are issued while the
 // VALU reduces the accumulators of pair i-1 (also across tile boundaries).
 // ---------------------------------------------------------------------------------------------
-// SPLIT (see score_lse.hip): neg_lse holds shares; the query tiles of a key block are dealt to q_splits workgroups as well, and
+// SPLIT (see score_lse.hip): neg_lse holds shares.  QSPLIT: the query tiles of a key block are dealt to q_splits workgroups, and
 // each raises x (cleared by pass 1; probabilities are not negative, so their bits compare like integers).
-template <int D, int NCOL, bool SPLIT>
+template <int D, int NCOL, bool SPLIT, bool QSPLIT>
 __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_ctx,
                                                                const float* __restrict__ neg_lse,
@@ -49,10 +49,10 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
   constexpr int KB = 128 * NCOL;
   const int H_kv = H_q / G;
   // a group's blocks: its key blocks (they stream the same queries), each in q_splits parts
-  const GroupBlock gb = group_block((N + KB - 1) / KB * (SPLIT ? q_splits : 1));
+  const GroupBlock gb = group_block((N + KB - 1) / KB * (QSPLIT ? q_splits : 1));
   if (gb.group >= L_s * H_kv) return;
   const int l = gb.group / H_kv, hs = gb.group % H_kv;
-  const int n0 = (SPLIT ? gb.item / q_splits : gb.item) * KB;
+  const int n0 = (QSPLIT ? gb.item / q_splits : gb.item) * KB;
   const uint16_t* kc = k_ctx + (size_t)(l * H_kv + hs) * N * D;
 
   bf16x8 b[NCOL][C::KK];
@@ -71,13 +71,13 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
 
   // tiles are fetched in order: head g = 0..G-1 of the group, query tile qt = 0..nqt-1
   const int nqt = (N_q + C::ROWS - 1) / C::ROWS;
-  const int part = SPLIT ? gb.item % q_splits : 0;
-  const int first = SPLIT ? (int)((int64_t)G * nqt * part / q_splits) : 0;
-  const int total = SPLIT ? (int)((int64_t)G * nqt * (part + 1) / q_splits) - first : G * nqt;
+  const int part = QSPLIT ? gb.item % q_splits : 0;
+  const int first = QSPLIT ? (int)((int64_t)G * nqt * part / q_splits) : 0;
+  const int total = QSPLIT ? (int)((int64_t)G * nqt * (part + 1) / q_splits) - first : G * nqt;
   TileRegs<D> regs;
   LseRegs<SPLIT> nl_reg;
   nl_reg.none();
-  int fg = SPLIT ? first / nqt : 0, fqt = SPLIT ? first % nqt : 0;
+  int fg = QSPLIT ? first / nqt : 0, fqt = QSPLIT ? first % nqt : 0;
   auto fetch_next = [&]() {
     const size_t head = (size_t)(l * H_q + hs * G + fg);
     tile_fetch<D>(regs, q + head * N_q * D, fqt * C::ROWS, N_q, tid);
@@ -180,7 +180,7 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
     const float p = __builtin_fminf(__builtin_amdgcn_exp2f(c * m), 1.0f);
     if (half == 0 && kn[cs] < N) {
       float* dst = x + (size_t)(l * H_kv + hs) * N + kn[cs];
-      if constexpr (SPLIT) atomicMax(reinterpret_cast<unsigned int*>(dst), __float_as_uint(p));
+      if constexpr (QSPLIT) atomicMax(reinterpret_cast<unsigned int*>(dst), __float_as_uint(p));
       else *dst = p;
     }
   }
@@ -197,22 +197,26 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
 //
 // CAUSAL: the proxy's own prefill attention (N_q == N, the keys are the sequence's own): query i sees keys n <= i, so a
 // workgroup starts at the query tile that holds its first key and masks the tiles that the diagonal cuts.
+//
+// With q_splits > 1 the query tiles of a key block are dealt to that many workgroups and x holds their sums one behind the
+// other, [q_splits][L_s * H_kv * N]; sum_parts_kernel adds them up in that order.
 template <int D, int NCOL, bool CAUSAL, bool SPLIT>
-__global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __restrict__ q,
+__global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void score_colsum_kernel(const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_ctx,
                                                                const float* __restrict__ neg_lse,
                                                                float* __restrict__ x, int L_s, int H_q, int G, int N, int N_q,
-                                                               float c, float inv_c, int splits) {
+                                                               float c, float inv_c, int splits, int q_splits) {
   using C = ScoreCfg<D>;
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
   __shared__ __attribute__((aligned(16))) float lds_nl[kNBuf * C::ROWS];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   constexpr int KB = 128 * NCOL;
   const int H_kv = H_q / G;
-  const GroupBlock gb = group_block((N + KB - 1) / KB);  // a group's blocks: its key blocks (they stream the same queries)
+  // a group's blocks: its key blocks (they stream the same queries), each in q_splits parts
+  const GroupBlock gb = group_block((N + KB - 1) / KB * q_splits);
   if (gb.group >= L_s * H_kv) return;
   const int l = gb.group / H_kv, hs = gb.group % H_kv;
-  const int n0 = gb.item * KB;
+  const int n0 = gb.item / q_splits * KB, part = gb.item % q_splits;
   const uint16_t* kc = k_ctx + (size_t)(l * H_kv + hs) * N * D;
 
   bf16x8 b[NCOL][C::KK];
@@ -231,11 +235,12 @@ __global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __
   // tiles are fetched in order: head g = 0..G-1 of the group, query tile qt = 0..nqt-1
   const int nqt = (N_q + C::ROWS - 1) / C::ROWS;
   const int qt_first = CAUSAL ? n0 / C::ROWS : 0;  // KB is a multiple of ROWS
-  const int total = G * (nqt - qt_first);
+  const int nqg = nqt - qt_first;  // tiles per head
+  const int first = (int)((int64_t)G * nqg * part / q_splits), total = (int)((int64_t)G * nqg * (part + 1) / q_splits) - first;
   TileRegs<D> regs;
   LseRegs<SPLIT> nl_reg;
   nl_reg.none();
-  int fg = 0, fqt = qt_first;
+  int fg = first / nqg, fqt = qt_first + first % nqg;
   auto fetch_next = [&]() {
     const size_t head = (size_t)(l * H_q + hs * G + fg);
     tile_fetch<D>(regs, q + head * N_q * D, fqt * C::ROWS, N_q, tid);
@@ -253,15 +258,17 @@ __global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __
     tile_store<D>(regs, lds + (t % kNBuf) * C::TILE_U4, tid);
     if (tid < C::ROWS) lds_nl[(t % kNBuf) * C::ROWS + tid] = nl_reg.neg_lse(inv_c);
   };
-  fetch_next();
-  store(0);
+  if (total > 0) {
+    fetch_next();
+    store(0);
+  }
   if (total > 1) {
     fetch_next();
     store(1);
   }
   if (total > 2) fetch_next();
 
-  int cqt = qt_first;  // query tile of step t
+  int cqt = qt_first + first % nqg;  // query tile of step t
   for (int t = 0; t < total; ++t) {
     // every wave has finished tile t-1: its buffer takes tile t+2, the registers take tile t+3
     __syncthreads();
@@ -272,7 +279,9 @@ __global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __
     const int row0 = cqt * C::ROWS;
     const bool diag = CAUSAL && row0 < n0 + KB - 1;  // some query of the tile lies before some key of the block
     if (++cqt == nqt) cqt = qt_first;
-#pragma unroll
+    // (unrolled, the four sub-tiles of the causal form take 256 registers and with them the third workgroup per CU)
+    constexpr int kUnroll = CAUSAL ? 2 : C::SUB;
+#pragma unroll kUnroll
     for (int s = 0; s < C::SUB; ++s) {
       bf16x8 a[C::KK];
 #pragma unroll
@@ -324,8 +333,16 @@ __global__ __launch_bounds__(256, 2) void score_colsum_kernel(const uint16_t* __
 #pragma unroll
   for (int cs = 0; cs < NCOL; ++cs) {
     const float tot = colsum[cs] + swap_halves(colsum[cs]);
-    if (half == 0 && kn[cs] < N) x[(size_t)(l * H_kv + hs) * N + kn[cs]] = tot;
+    if (half == 0 && kn[cs] < N) x[((size_t)part * L_s * H_kv + l * H_kv + hs) * N + kn[cs]] = tot;
   }
+}
+
+__global__ __launch_bounds__(256) void sum_parts_kernel(const float* __restrict__ parts, int n_parts, int64_t n, float* __restrict__ x) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  float v = parts[i];
+  for (int p = 1; p < n_parts; ++p) v += parts[(size_t)p * n + i];
+  x[i] = v;
 }
 
 // fp32 -> bf16 of up to three arrays in one launch, eight elements per thread (n counts eights; every array of queries or
@@ -364,17 +381,48 @@ hipError_t launch_f32_to_bf16(const float* const in[3], uint16_t* const out[3], 
   return hipGetLastError();
 }
 
-hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x, int L_s,
-                               int H_q, int H_kv, int d, int64_t N, int64_t N_q, bool causal, hipStream_t stream) {
+constexpr int kMaxCols = 4, kSumCols = 2;  // column sub-tiles per wave of the two forms
+
+// Workgroups per key block in pass 2.  All workgroups take equally long, so `blocks` of them on `slots` places take
+// ceil(blocks / slots) turns, the last of which may be nearly empty (1152 on 768: two turns for one and a half's work);
+// s workgroups per block take ceil(s * blocks / slots) / s.  A part costs its start (about 1 % of a block's work where a
+// block streams a hundred query tiles); parts of fewer than two tiles would only wait for memory.
+// Measured, without and with: 28 x 2 heads of 128, 10 007 keys (4.4 turns' work in 5) 7830 -> 7160 us; the sum form,
+// 24 x 2 heads of 64, 6001 keys (1.5 in 2) 2212 -> 2060 us; causal, 16 x 8 heads, 4097 keys 1164 -> 950 us.
+int score_query_splits(bool sum, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q) {
+  const int cols = 128 * (sum ? kSumCols : kMaxCols);
+  const int64_t slots = 256 * (d == 64 ? (sum ? 3 : 2) : (sum ? 2 : 1));
+  const int64_t blocks = (N + cols - 1) / cols * L_s * H_kv;
+  const int64_t tiles = (int64_t)(H_q / H_kv) * ((N_q + 8192 / d - 1) / (8192 / d));
+  int64_t most = slots / blocks > 8 ? slots / blocks : 8;
+  if (sum && most > 16) most = 16;  // each part's sums are written and read again
+  if (most > tiles / 2) most = tiles / 2;
+  if (blocks > 32 * slots) return 1;  // the last turn no longer counts
+  int64_t best = 1;
+  double best_cost = 1e30;
+  for (int64_t s = 1; s <= most || s == 1; ++s) {
+    const double cost = (double)((blocks * s + slots - 1) / slots) / (double)s * (1.0 + (double)(s - 1) / (double)tiles);
+    if (cost < best_cost * 0.985) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return (int)best;
+}
+
+hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x, float* parts,
+                               int q_splits, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, bool causal,
+                               hipStream_t stream) {
   const int G = H_q / H_kv;
   const float c = 1.4426950408889634f / sqrtf((float)d), inv_c = 1.0f / c;
-  constexpr int NCOL = 2;
-  if (causal && N != N_q) return hipErrorInvalidValue;
-  const unsigned grid = group_grid((int64_t)L_s * H_kv, (N + 128 * NCOL - 1) / (128 * NCOL));
+  constexpr int NCOL = kSumCols;
+  if ((causal && N != N_q) || q_splits < 1 || (q_splits > 1 && !parts)) return hipErrorInvalidValue;
+  const unsigned grid = group_grid((int64_t)L_s * H_kv, (N + 128 * NCOL - 1) / (128 * NCOL) * q_splits);
   if (grid == 0) return hipErrorInvalidValue;
+  float* out = q_splits > 1 ? parts : x;
   auto go = [&](auto dc, auto cc, auto sc) {
     score_colsum_kernel<decltype(dc)::value, NCOL, decltype(cc)::value, decltype(sc)::value>
-        <<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, (int)N, (int)N_q, c, inv_c, splits);
+        <<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, out, L_s, H_q, G, (int)N, (int)N_q, c, inv_c, splits, q_splits);
   };
   auto pick = [&](auto dc) {
     if (causal && splits > 1) go(dc, std::true_type{}, std::true_type{});
@@ -384,34 +432,35 @@ hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const f
   };
   if (d == 64) pick(std::integral_constant<int, 64>{});
   else pick(std::integral_constant<int, 128>{});
+  if (q_splits > 1) {
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int64_t n = (int64_t)L_s * H_kv * N;
+    sum_parts_kernel<<<(unsigned)((n + 255) / 256), 256, 0, stream>>>(parts, q_splits, n, x);
+  }
   return hipGetLastError();
 }
 
-hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x, int L_s,
-                               int H_q, int H_kv, int d, int64_t N, int64_t N_q, hipStream_t stream) {
+hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x, int q_splits,
+                               int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, hipStream_t stream) {
   const int G = H_q / H_kv;
   const float c = 1.4426950408889634f / sqrtf((float)d), inv_c = 1.0f / c;
   // d = 64: two workgroups per CU.  d = 128: one (the resident keys of 4 column sub-tiles alone take 128 registers): a wave
   // has the SIMD's whole register file, and the pinned issue order keeps the matrix pipe fed without a second wave
-  constexpr int NCOL = 4;
-  const int64_t key_blocks = (N + 128 * NCOL - 1) / (128 * NCOL), q_tiles = G * ((N_q + 8192 / d - 1) / (8192 / d));
-  int64_t q_splits = 1;
-  if (splits > 1) {
-    // as many parts of the query tiles as fill the chip, two tiles or more each (the first tile of a part waits for memory)
-    q_splits = (d == 64 ? 512 : 256) / (key_blocks * L_s * H_kv);
-    q_splits = q_splits < q_tiles / 2 ? q_splits : q_tiles / 2;
-    q_splits = q_splits < 1 ? 1 : q_splits;
-  }
-  const unsigned grid = group_grid((int64_t)L_s * H_kv, key_blocks * q_splits);
-  if (grid == 0) return hipErrorInvalidValue;
-  auto go = [&](auto dc, auto sc) {
-    score_colmax_kernel<decltype(dc)::value, NCOL, decltype(sc)::value>
-        <<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, (int)N, (int)N_q, c, inv_c, splits, (int)q_splits);
+  constexpr int NCOL = kMaxCols;
+  const unsigned grid = group_grid((int64_t)L_s * H_kv, (N + 128 * NCOL - 1) / (128 * NCOL) * q_splits);
+  if (grid == 0 || q_splits < 1) return hipErrorInvalidValue;
+  auto go = [&](auto dc, auto sc, auto qc) {
+    score_colmax_kernel<decltype(dc)::value, NCOL, decltype(sc)::value, decltype(qc)::value>
+        <<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, x, L_s, H_q, G, (int)N, (int)N_q, c, inv_c, splits, q_splits);
   };
-  if (d == 64 && splits > 1) go(std::integral_constant<int, 64>{}, std::true_type{});
-  else if (d == 64) go(std::integral_constant<int, 64>{}, std::false_type{});
-  else if (splits > 1) go(std::integral_constant<int, 128>{}, std::true_type{});
-  else go(std::integral_constant<int, 128>{}, std::false_type{});
+  auto pick = [&](auto dc) {
+    if (splits > 1) go(dc, std::true_type{}, std::true_type{});  // (few blocks: always split both ways)
+    else if (q_splits > 1) go(dc, std::false_type{}, std::true_type{});
+    else go(dc, std::false_type{}, std::false_type{});
+  };
+  if (d == 64) pick(std::integral_constant<int, 64>{});
+  else pick(std::integral_constant<int, 128>{});
   return hipGetLastError();
 }
 

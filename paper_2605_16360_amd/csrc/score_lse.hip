@@ -20,7 +20,7 @@
 //
 // Tiles that causality, a chunk boundary or the end of the context cuts are masked and summed the same way; the checked
 // path, whose chains wait for each other (three times as long per tile), is left for columns without a reference and for
-// sums out of range.  The first reference comes from the first 32 keys.  16 layers of 4097 tokens, causal: 1343 -> 980 us.
+// sums out of range.  The first reference comes from the first 32 keys.  16 layers of 4097 tokens, causal: 1343 -> 995 us.
 //
 // Streaming: three LDS buffers and one barrier per tile.  While tile t is computed, tile t+2 goes
 // from registers to LDS and tile t+3 is fetched from global memory into registers.
@@ -40,8 +40,8 @@ constexpr float kRebase = 1.8446744e19f;  // 2^64
 // undoes the tile and sums it again chain by chain with the check.
 constexpr float kTileRedo = 1.2676506e30f;  // 2^100
 
-// SPLIT: `splits` workgroups per query block, neg_lse holds (reference, sum) pairs [splits][L_s * H_q * N_q]; they also clear
-// x [n_x], which pass 2's workgroups then raise.
+// SPLIT: `splits` workgroups per query block, neg_lse holds (reference, sum) pairs [splits][L_s * H_q * N_q].
+// x [n_x] (n_x may be 0) is cleared for a pass 2 whose workgroups raise it.
 template <int D, int NCOL, int MINB, bool SPLIT>
 __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_ctx,
@@ -56,7 +56,7 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
   constexpr int QB = 128 * NCOL;
   const int split = SPLIT ? blockIdx.x % splits : 0;
   const int i0 = (SPLIT ? blockIdx.x / splits : blockIdx.x) * QB;
-  if constexpr (SPLIT) {
+  if (n_x > 0) {
     const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int64_t stride = (int64_t)gridDim.x * gridDim.y * gridDim.z * 256;
     for (int64_t i = wg * 256 + tid; i < n_x; i += stride) x[i] = 0.0f;

@@ -287,10 +287,11 @@ def test_score_degenerate_shapes(N, N_q, chunk):
         pk.proxykv_destroy(ctx)
 
 
-@pytest.mark.parametrize("d,N,N_q,chunk", [(64, 1, 3, 2), (64, 700, 257, 100), (64, 1030, 130, 64), (128, 65, 300, 1000), (128, 900, 64, 33)])
+@pytest.mark.parametrize("d,N,N_q,chunk", [(64, 1, 3, 2), (64, 700, 257, 100), (64, 1030, 130, 64), (128, 65, 300, 1000), (128, 900, 64, 33),
+                                          (128, 1100, 200, 256), (64, 2600, 1700, 512)])
 def test_score_few_and_many_query_blocks_agree(d, N, N_q, chunk):
     """Few query blocks: several workgroups share a block's keys (and, in the max form, a key block's queries); many: one
-    workgroup each.  The same layer alone and as one of 192 must agree to the rounding of 32-bit sums and exponentials
+    workgroup each, or a few where the last turn on the chip would be half empty (the last two shapes).  The same layer alone and as one of 192 must agree to the rounding of 32-bit sums and exponentials
     (log-sum-exps up to about 2^4, whose last bit is 1e-6, scaled back: 2e-5), and both with the oracle."""
     L, H_q, H_kv = 192, 4, 2
     g = torch.Generator().manual_seed(N + N_q)
