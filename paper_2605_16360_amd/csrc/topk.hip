@@ -33,13 +33,20 @@ __device__ __forceinline__ float key_score(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? k ^ 0x80000000u : ~k);
 }
 
-// Four scores at row[i], ..., row[i + 3], those at or past `hi` read as NaN (never out of bounds).  `vec`: the row starts on a
-// 16-byte boundary (i is a multiple of four).
-__device__ __forceinline__ f32x4 load_quad(const float* row, int i, int hi, bool vec) {
-  if (vec && i + 4 <= hi) return *reinterpret_cast<const f32x4*>(row + i);
-  f32x4 v;
-#pragma unroll
-  for (int j = 0; j < 4; ++j) v[j] = i + j < hi ? row[i + j] : __builtin_nanf("");
+// Four scores row[i], ..., row[i + 3] of a row that starts on any 4-byte boundary.  Nothing at or past hi is read: a quad that
+// would is the last four below it, so that row[i] is its element quad_shift(i, hi) (the row has at least four scores below
+// hi).  There is no branch: with one per quad the compiler waits for a quad before it asks for the next (nine trips to
+// memory, one after the other, in a row of 36 864 scores).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ int quad_shift(int i, int hi) { return i > hi - 4 ? i - (hi - 4) : 0; }
+__device__ __forceinline__ f32x4 load_quad(const float* row, int i, int hi) {
+  const f32x4_any v = *reinterpret_cast<const f32x4_any*>(row + (i - quad_shift(i, hi)));
+  return f32x4{v[0], v[1], v[2], v[3]};
+}
+// the quad with row[i] in element 0 again; the last `shift` elements mean nothing
+__device__ __forceinline__ f32x4 shift_quad(f32x4 v, int shift) {
+  if (shift & 2) v = f32x4{v[2], v[3], v[3], v[3]};
+  if (shift & 1) v = f32x4{v[1], v[2], v[3], v[3]};
   return v;
 }
 constexpr int kChunk = 4 * kTopkThreads;
@@ -119,8 +126,7 @@ __device__ __forceinline__ void quad_bits(const f32x4& v, int valid, float t, bo
 
 // sum over the workgroup of one value per thread; `part`: kTopkWaves words of LDS, free again after the call
 __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* part, int tid) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
+  v = wave_total(v);
   if ((tid & 63) == 0) part[tid >> 6] = v;
   __syncthreads();
   uint32_t t = 0;
@@ -130,20 +136,15 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t v, uint32_t* part, int ti
   return t;
 }
 
-// exclusive prefix sum of one value per thread over the workgroup; `part` as in block_sum
+// exclusive prefix sum of one value per thread over the workgroup; `part` as in block_sum, but in use until the caller's
+// next barrier
 __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* part, int wave, int lane) {
-  uint32_t inc = v;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t t = __shfl_up(inc, off, 64);
-    if (lane >= off) inc += t;
-  }
+  const uint32_t inc = wave_inclusive_scan(v);
   if (lane == 63) part[wave] = inc;
   __syncthreads();
   uint32_t before = inc - v;
 #pragma unroll
   for (int w = 0; w < kTopkWaves; ++w) before += w < wave ? part[w] : 0u;
-  __syncthreads();
   return before;
 }
 
@@ -169,11 +170,11 @@ __device__ __forceinline__ void pick_digit(const uint32_t (&cnt)[kPer], uint32_t
 // and two bits of mantissa, so scores of a row hit a few dozen of its 2048 bins; eight copies of every bin side by side,
 // one per lane modulo eight, keep the lanes of a wave off each other's words.  (8-bit digits of the key's distance from
 // the row's smallest, a histogram per wave: 28 us of the kernel's 44 in the passes where scores change sign, since the
-// positive ones then share two or three bins.)  Wave w owns the scores [w * kRegSeg, (w + 1) * kRegSeg).
+// positive ones then share two or three bins.)  Wave w owns the scores [w * seg, (w + 1) * seg), seg = 256 * ceil(N / 4096):
+// a short row is one quad per thread in all waves, not 36 scores per thread in a few.
 // ---------------------------------------------------------------------------------------------
 constexpr int kTopkChunks = 9;                     // quads per thread
-constexpr int kRegSeg = kTopkChunks * 256;
-constexpr int kTopkRegMax = kTopkWaves * kRegSeg;
+constexpr int kTopkRegMax = kTopkChunks * kChunk;
 static_assert(kTopkRegMax == kTopkSingleMax, "kernels.hpp states the longest single-workgroup row");
 constexpr int kRegCopies = 8;
 
@@ -224,19 +225,34 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
   __shared__ __attribute__((aligned(16))) uint32_t hist[2048 * kRegCopies];
   __shared__ uint32_t wave_part[kTopkWaves], wave_eq[kTopkWaves];
   __shared__ uint32_t s_prefix, s_krem;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
-  const int i0 = wave * kRegSeg + 4 * lane;  // index of the thread's first quad; the next ones follow 256 apart
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int seg = (N + kChunk - 1) / kChunk * 256, s0 = wave * seg;
+  const int left = N - s0 < seg ? N - s0 : seg, quads = left > 0 ? (left + 255) / 256 : 0;  // the wave's scores, and quads per lane
+  const int i0 = s0 + 4 * lane;  // index of the thread's first quad; the next ones follow 256 apart
+
+#pragma unroll
+  for (int i = 0; i < 2048 * kRegCopies / 4 / kTopkThreads; ++i) reinterpret_cast<u32x4*>(hist)[tid + i * kTopkThreads] = u32x4{0, 0, 0, 0};
 
   // keys of this thread's scores; those at and past N hold a key that no score has (the largest, +inf's, is 0xff800000)
   constexpr uint32_t kNoKey = 0xffffffffu;
   uint32_t key[kTopkChunks][4];
+  f32x4 v[kTopkChunks];
+  if (N < 4) {
 #pragma unroll
-  for (int c = 0; c < kTopkChunks; ++c) {
-    const f32x4 v = load_quad(row, i0 + c * 256, N, vec);
+    for (int j = 0; j < 4; ++j) v[0][j] = row[j < N ? j : 0];
+  } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) key[c][j] = i0 + c * 256 + j < N ? order_key(v[j]) : kNoKey;
+    for (int c = 0; c < kTopkChunks; ++c)
+      if (c < quads) v[c] = load_quad(row, i0 + c * 256, N);
   }
+#pragma unroll
+  for (int c = 0; c < kTopkChunks; ++c)
+    if (c < quads) {
+      if (left < (c + 1) * 256 && N >= 4) v[c] = shift_quad(v[c], quad_shift(i0 + c * 256, N));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) key[c][j] = i0 + c * 256 + j < N ? order_key(v[c][j]) : kNoKey;
+    }
+  __syncthreads();
 
   uint32_t* mine = hist + (lane & (kRegCopies - 1));
   uint32_t prefix = 0, krem = (uint32_t)K;
@@ -246,21 +262,22 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
     const uint32_t dmask = (1u << (hi_bit - shift)) - 1u;
     const uint32_t high = hi_bit == 32 ? 0u : ~0u << hi_bit, want = hi_bit == 32 ? 0u : prefix << hi_bit;
 #pragma unroll
-    for (int i = 0; i < 2048 * kRegCopies / 4 / kTopkThreads; ++i) reinterpret_cast<u32x4*>(hist)[tid + i * kTopkThreads] = u32x4{0, 0, 0, 0};
-    __syncthreads();
-#pragma unroll
     for (int c = 0; c < kTopkChunks; ++c)
+      if (c < quads) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t k = key[c][j];
-        if ((k & high) == want) atomicAdd(&mine[((k >> shift) & dmask) * kRegCopies], 1u);
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t k = key[c][j];
+          if ((k & high) == want) atomicAdd(&mine[((k >> shift) & dmask) * kRegCopies], 1u);
+        }
       }
     __syncthreads();
     uint32_t cnt[2];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const u32x4* h = reinterpret_cast<const u32x4*>(hist + (2047 - (tid * 2 + i)) * kRegCopies);
+    for (int i = 0; i < 2; ++i) {  // the thread's bins, which it clears for the next pass (whose adds lie two barriers ahead)
+      u32x4* h = reinterpret_cast<u32x4*>(hist + (2047 - (tid * 2 + i)) * kRegCopies);
       const u32x4 a = h[0], b = h[1];
+      h[0] = u32x4{0, 0, 0, 0};
+      h[1] = u32x4{0, 0, 0, 0};
       cnt[i] = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
     }
     if (hi_bit == 32 && tid == 0) cnt[0] = 0;  // kNoKey's bin
@@ -277,16 +294,17 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
   // kept: keys above T, and the eq_take lowest-index keys equal to T
   uint64_t m_gt = 0, m_eq = 0;
 #pragma unroll
-  for (int c = 0; c < kTopkChunks; ++c) {
-    uint32_t bg = 0, be = 0;
+  for (int c = 0; c < kTopkChunks; ++c)
+    if (c < quads) {
+      uint32_t bg = 0, be = 0;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      bg |= (uint32_t)(key[c][j] > T && key[c][j] != kNoKey) << j;
-      be |= (uint32_t)(key[c][j] == T) << j;
+      for (int j = 0; j < 4; ++j) {
+        bg |= (uint32_t)(key[c][j] > T && key[c][j] != kNoKey) << j;
+        be |= (uint32_t)(key[c][j] == T) << j;
+      }
+      m_gt |= (uint64_t)bg << (4 * c);
+      m_eq |= (uint64_t)be << (4 * c);
     }
-    m_gt |= (uint64_t)bg << (4 * c);
-    m_eq |= (uint64_t)be << (4 * c);
-  }
   const uint32_t n_gt = wave_total((uint32_t)__popcll(m_gt)), n_eq = wave_total((uint32_t)__popcll(m_eq));
   if (lane == 0) {
     wave_part[wave] = n_gt;
@@ -299,7 +317,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
     gt += w < wave ? wave_part[w] : 0u;
     eq += w < wave ? wave_eq[w] : 0u;
   }
-  wave_write(m_gt, m_eq, kTopkChunks, gt, eq, eq_take, wave * kRegSeg, lane, out);
+  wave_write(m_gt, m_eq, quads, gt, eq, eq_take, s0, lane, out);
   if constexpr (GATHER) {
     __syncthreads();  // the row's list is complete and visible to the whole workgroup
     gather_rows(ga, (size_t)blockIdx.x * N * ga.cpr, (size_t)blockIdx.x * K * ga.cpr, out, 0, K, tid);
@@ -359,7 +377,6 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
   __shared__ uint32_t s_last;
   const int lo = part * part_len, len = N - lo < part_len ? N - lo : part_len;
   row += lo;
-  const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
   const uint32_t prefix = rs[0];  // the bits above kHi of the K-th largest key (written by the previous launch)
   for (int i = tid; i < C::kBins * C::kCopies / 4; i += kTopkThreads) reinterpret_cast<u32x4*>(hist)[i] = u32x4{0, 0, 0, 0};
   __syncthreads();
@@ -368,7 +385,7 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
   for (int c0 = 0; c0 < len; c0 += 4 * kChunk) {  // four chunks in flight
     f32x4 v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = load_quad(row, c0 + u * kChunk + 4 * tid, len, vec);
+    for (int u = 0; u < 4; ++u) v[u] = load_quad(row, c0 + u * kChunk + 4 * tid, len);
     auto count = [&](bool valid, float f) {
       const uint32_t key = order_key(f);
       if constexpr (PASS == 0) {
@@ -388,7 +405,7 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
 #pragma unroll
       for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int j = 0; j < 4; ++j) count(c0 + u * kChunk + 4 * tid + j < len, v[u][j]);
+        for (int j = 0; j < 4; ++j) count(j >= quad_shift(c0 + u * kChunk + 4 * tid, len), v[u][j]);
     }
   }
   __syncthreads();
@@ -450,8 +467,7 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
   __shared__ uint32_t wave_part[kTopkWaves], wave_eq[kTopkWaves];
   const int lo = part * part_len, len = N - lo < part_len ? N - lo : part_len;
   row += lo;
-  const bool vec = (reinterpret_cast<uintptr_t>(row) & 15) == 0;
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   // wave w owns the scores [w * seg, (w + 1) * seg) of the part, at most kMwQuads quads per lane
   const int seg = ((len + kTopkWaves - 1) / kTopkWaves + 255) & ~255;
   const int s0 = wave * seg < len ? wave * seg : len, s1 = s0 + seg < len ? s0 + seg : len;
@@ -472,9 +488,11 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
   for (int q0 = 0; q0 < quads; q0 += 4) {
     f32x4 v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = load_quad(row, s0 + (q0 + u) * 256 + 4 * lane, s1, vec);
+    for (int u = 0; u < 4; ++u) v[u] = load_quad(row, s0 + (q0 + u) * 256 + 4 * lane, s1);
+    const bool cut = s0 + (q0 + 4) * 256 > s1;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
+      if (cut) v[u] = shift_quad(v[u], quad_shift(s0 + (q0 + u) * 256 + 4 * lane, s1));
       uint32_t bg, be;
       quad_bits(v[u], s1 - (s0 + (q0 + u) * 256 + 4 * lane), t, nan_t, bg, be);
       m_gt |= (uint64_t)bg << (4 * (q0 + u));
