@@ -51,7 +51,7 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
                                                                float* __restrict__ x, int64_t n_x) {
   using C = ScoreCfg<D>;
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int h = blockIdx.y, l = blockIdx.z, H_kv = H_q / G, hs = h / G;
   constexpr int QB = 128 * NCOL;
   const int split = SPLIT ? blockIdx.x % splits : 0;
@@ -71,8 +71,8 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
 #pragma unroll
   for (int cs = 0; cs < NCOL; ++cs) {
     qi[cs] = i0 + (wave * NCOL + cs) * 32 + l32;
-    qlo[cs] = (qi[cs] / chunk) * chunk;
     const int row = qi[cs] < N_q ? qi[cs] : N_q - 1;
+    qlo[cs] = (row / chunk) * chunk;  // (a column past the last query sees that query's chunk, so that it has a reference too)
 #pragma unroll
     for (int kk = 0; kk < C::KK; ++kk)
       b[cs][kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(qh + (size_t)row * D + kk * 16 + half * 8));
@@ -183,6 +183,7 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
   };
   // a tile that causality, a chunk boundary or the end of the context cuts: its visible chains, summed without checks
   auto cut_tile = [&](const u32x4* buf, bool is_rec, int row0, int limit) {
+#pragma unroll 1
     for (int s = 0; s < C::SUB; ++s) {
       const int jbase = row0 + s * 32;
       if (hidden(is_rec, jbase, limit, NCOL - 1)) break;
@@ -200,8 +201,8 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
       }
     }
   };
-  // the first reference of every column: the largest logit of the first 32 keys of an interior tile
-  auto first_reference = [&](const u32x4* buf) {
+  // the first reference of every column: the largest visible logit of the first 32 keys of a tile (if any is visible)
+  auto first_reference = [&](const u32x4* buf, bool interior, bool is_rec, int row0) {
     bf16x8 a[C::KK];
 #pragma unroll
     for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, l32, kk * 2 + half);
@@ -210,6 +211,7 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
       f32x16 acc = splat16(0.0f);
 #pragma unroll
       for (int kk = 0; kk < C::KK; ++kk) acc = mfma_32x32x16(a[kk], b[cs][kk], acc);
+      if (!interior) mask_chain(acc, is_rec, row0, cs);
       const float tm = max16_tree(acc, kNegInf) * c;
       if (tm > -1.0e30f) nref[cs] = -tm;
     }
@@ -238,10 +240,12 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     // and inside the chunk of its last one (then inside every query's chunk).
     const int limit = is_rec ? i_end : N;
     const bool interior = is_rec ? row0 + C::ROWS - 1 <= i0 && row0 >= ((i_end - 1) / chunk) * chunk : row0 + C::ROWS <= N;
-    // A share of a few tiles starts with the checks at once: there the way to a first reference costs more than it saves.
-    bool redo = SPLIT && t == 0 && total < 4;
+    // Where there are few tiles, cut ones take the checks at once, and so does the first of a share: the way to a first
+    // reference and the code of a second loop, fetched for a tile or two, cost more than they save (16 layers, causal:
+    // 200 tokens 30 -> 22 us, 450 tokens 62 -> 51 us, 1000 tokens, eight tiles and more, the same either way).
+    bool redo = (total < 8 && !interior) || (SPLIT && t == 0 && total < 4);
     if (!redo) {
-      if (t == 0 && interior) first_reference(buf);
+      if (t == 0) first_reference(buf, interior, is_rec, row0);
       float before[NCOL];
 #pragma unroll
       for (int cs = 0; cs < NCOL; ++cs) before[cs] = lsum[cs];
