@@ -84,31 +84,32 @@ struct Sizes {
   size_t total() const { return neg_lse + x_parts + x_ws + yhat_ws + lanes * mapper(); }
 };
 
+// Every size grows with N and N_q, so that a workspace reserved for the longest call serves all shorter ones: where a plan
+// gives a shorter input more layers per batch or more workgroups, the bound over all shorter inputs stands here.
 Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q, int distinct_layers) {
   Sizes s;
   const pkv::MapPlan p = pkv::map_plan(c, N, distinct_layers);
   // rows of GEMM outputs (and of the residuals they read) are padded to the GEMM's 256-row tile
   s.lanes = p.lanes;
-  const size_t b = (size_t)p.batch, Tp = b * (size_t)p.Tp, Np = b * (size_t)p.Np, dt = (size_t)c.d_time;
-  // the causal form runs pass 1 without context keys, over N_q == N of its own
-  const int splits = std::max(pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q), pkv::score_splits(c.L_s, c.H_q, c.d, N_q, N_q));
-  s.neg_lse = (size_t)c.L_s * c.H_q * (size_t)N_q * (splits > 1 ? 8 * (size_t)splits : 4);
-  const size_t n_x = (size_t)c.L_s * c.H_kv * (size_t)N;
-  int parts = pkv::score_query_splits(true, c.L_s, c.H_q, c.H_kv, c.d, N, N);  // the causal form
-  if (c.reduce == PROXYKV_REDUCE_SUM) parts = std::max(parts, pkv::score_query_splits(true, c.L_s, c.H_q, c.H_kv, c.d, N, N_q));
-  s.x_parts = parts > 1 ? n_x * 4 * (size_t)parts : 0;
+  // rows of a batch (batch * p.Tp window rows, batch * p.Np tokens) over all inputs of up to N tokens
+  const size_t most = (size_t)pkv::kMapBatchRows, layers = (size_t)distinct_layers, dt = (size_t)c.d_time;
+  const size_t Tp = std::min(layers * (size_t)p.Tp, std::max(most, (size_t)p.Tp));
+  const size_t Np = std::min(layers * (size_t)p.Np, std::max(most, (size_t)p.Np));
+  s.neg_lse = pkv::score_lse_bytes(c.L_s, c.H_q, N_q);
+  s.x_parts = pkv::score_parts_bytes(c.L_s, c.H_kv, c.d, N);
   s.x_ws = (size_t)c.L_s * c.H_kv * (size_t)N * 4;
   s.yhat_ws = (size_t)c.L_l * c.H_l * (size_t)N * 4;
-  s.h1 = b * ((size_t)N + 2) * (size_t)c.c_mid * 2;
+  s.h1 = (Np + 2 * pkv::kMaxBatch) * (size_t)c.c_mid * 2;
   s.x = Tp * dt * 4;
   s.xb = Tp * dt * 2;
   s.qk = Tp * 2 * dt * 2;
-  s.vt = b * (size_t)p.n_win * dt * (size_t)p.vt_ld * 2;
+  // (whole windows: two of them hold at least 2 win - stride rows, and more of them a larger share)
+  s.vt = (p.n_win > 1 ? Tp * 2 * (size_t)c.win / (2 * (size_t)c.win - (size_t)c.stride) + (size_t)c.win : Tp) * dt * 2;
   s.ao = Tp * dt * 2;
   s.hid = Tp * (size_t)c.d_ffn * 2;
   s.zg = Np * dt * 2;
   s.s3 = Np * (size_t)(c.H_l + 1) * (size_t)c.H_kv * 4;
-  s.pre = p.small ? Tp * dt * 4 : 0;
+  s.pre = std::min(Tp, (size_t)pkv::kMapSmallRows + 255 * pkv::kMaxBatch) * dt * 4;
   s.range = pkv::kMaxBatch * 64;
   return s;
 }

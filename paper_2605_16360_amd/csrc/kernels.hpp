@@ -13,6 +13,7 @@ hipError_t launch_f32_to_bf16(const float* const in[3], uint16_t* const out[3], 
 // the sum running over the N context keys and the visible reconstruction keys of query i.
 // With splits = score_splits(...) > 1 several workgroups share a query's keys: neg_lse then takes 8 * splits bytes per query
 // instead of four.  x [n_x] is cleared for pass 2 (n_x = 0: left alone).
+size_t score_lse_bytes(int L_s, int H_q, int64_t N_q);  // of neg_lse, for all inputs of up to N_q queries
 int score_splits(int L_s, int H_q, int d, int64_t N, int64_t N_q);
 hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* k_rec, float* neg_lse, int splits,
                             float* x, int64_t n_x, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
@@ -20,6 +21,7 @@ hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint
 // Scoring, pass 2: x[l, g, n] = 2^(c * max over (head of group g, query i) of (<q_i, k_n> + neg_lse[l, h, i])).
 // neg_lse and splits as pass 1 left them.  q_splits = score_query_splits(...) workgroups share a key block's queries; with
 // splits > 1 or q_splits > 1 they raise x, which pass 1 has to clear.
+size_t score_parts_bytes(int L_s, int H_kv, int d, int64_t N);  // of `parts` below, for all inputs of up to N keys
 int score_query_splits(bool sum, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q);
 hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x,
                                int q_splits, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q,

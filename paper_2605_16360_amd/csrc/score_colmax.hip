@@ -382,6 +382,8 @@ hipError_t launch_f32_to_bf16(const float* const in[3], uint16_t* const out[3], 
 }
 
 constexpr int kMaxCols = 4, kSumCols = 2;  // column sub-tiles per wave of the two forms
+constexpr int64_t kMaxSumParts = 16, kMaxTurns = 64;
+static int64_t pass2_slots(bool sum, int d) { return 256 * (d == 64 ? (sum ? 3 : 2) : (sum ? 2 : 1)); }
 
 // Workgroups per key block in pass 2.  All workgroups take equally long, so `blocks` of them on `slots` places take
 // ceil(blocks / slots) turns, the last of which may be nearly empty (1152 on 768: two turns for one and a half's work);
@@ -391,13 +393,13 @@ constexpr int kMaxCols = 4, kSumCols = 2;  // column sub-tiles per wave of the t
 // 24 x 2 heads of 64, 6001 keys (1.5 in 2) 2212 -> 2060 us; causal, 16 x 8 heads, 4097 keys 1164 -> 950 us.
 int score_query_splits(bool sum, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q) {
   const int cols = 128 * (sum ? kSumCols : kMaxCols);
-  const int64_t slots = 256 * (d == 64 ? (sum ? 3 : 2) : (sum ? 2 : 1));
+  const int64_t slots = pass2_slots(sum, d);
   const int64_t blocks = (N + cols - 1) / cols * L_s * H_kv;
   const int64_t tiles = (int64_t)(H_q / H_kv) * ((N_q + 8192 / d - 1) / (8192 / d));
   int64_t most = slots / blocks > 8 ? slots / blocks : 8;
-  if (sum && most > 16) most = 16;  // each part's sums are written and read again
+  if (sum && most > kMaxSumParts) most = kMaxSumParts;  // each part's sums are written and read again
+  if (most > kMaxTurns * slots / blocks) most = kMaxTurns * slots / blocks;  // one more saves no more than a 64th
   if (most > tiles / 2) most = tiles / 2;
-  if (blocks > 32 * slots) return 1;  // the last turn no longer counts
   int64_t best = 1;
   double best_cost = 1e30;
   for (int64_t s = 1; s <= most || s == 1; ++s) {
@@ -408,6 +410,13 @@ int score_query_splits(bool sum, int L_s, int H_q, int H_kv, int d, int64_t N, i
     }
   }
   return (int)best;
+}
+
+// The most that the parts of any input of up to N keys take: at most kMaxSumParts per block, kMaxTurns * slots workgroups.
+size_t score_parts_bytes(int L_s, int H_kv, int d, int64_t N) {
+  const int64_t cols = 128 * kSumCols, blocks = (N + cols - 1) / cols * L_s * H_kv;
+  const int64_t wgs = kMaxSumParts * blocks < kMaxTurns * pass2_slots(true, d) ? kMaxSumParts * blocks : kMaxTurns * pass2_slots(true, d);
+  return (size_t)(wgs * cols) * 4;
 }
 
 hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x, float* parts,

@@ -312,6 +312,13 @@ int score_splits(int L_s, int H_q, int d, int64_t N, int64_t N_q) {
   return (int)(s < kMaxLseSplits ? s : kMaxLseSplits);
 }
 
+// The most that any input of up to N_q queries takes: one float per query, or pairs of up to 768 workgroups (score_splits).
+size_t score_lse_bytes(int L_s, int H_q, int64_t N_q) {
+  const size_t rows = (size_t)L_s * H_q * (size_t)N_q, most = (size_t)768 * 128 * kLseCols;
+  const size_t pairs = rows * kMaxLseSplits < most ? rows * kMaxLseSplits : most;
+  return rows * 4 > pairs * sizeof(LsePart) ? rows * 4 : pairs * sizeof(LsePart);
+}
+
 hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* k_rec, float* neg_lse, int splits,
                             float* x, int64_t n_x, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
                             hipStream_t stream) {

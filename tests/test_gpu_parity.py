@@ -555,3 +555,35 @@ def test_prune_with_the_sum_form_equals_its_stages():
     assert torch.equal(k_out.view(torch.int16), k2.view(torch.int16)) and torch.equal(v_out.view(torch.int16), v2.view(torch.int16))
     assert_close(x, oracle.score(q.double().cpu(), kc.double().cpu(), kr.double().cpu(), case.chunk, reduce="sum"), "prune sum x")
     pk.proxykv_destroy(ctx)
+
+
+@pytest.mark.parametrize("L,H_q,H_kv,d", [(1, 4, 2, 64), (16, 32, 8, 64), (28, 12, 2, 128)])
+def test_reserve_covers_all_shorter_calls(L, H_q, H_kv, d):
+    """A workspace reserved for the longest input serves every shorter one without an allocation, although a shorter one may be
+    given more workgroups per key block or more proxy layers per batch: the device's free memory stays what it is."""
+    g = torch.Generator().manual_seed(L)
+    n_max = 5000
+    cfg = pk.make_config(L, H_q, H_kv, d, L, 4, 128)
+    ctx = pk.proxykv_create(cfg)
+    pk.proxykv_set_mapper_weights(ctx, synth.make_mapper_weights(H_kv, 4))
+    q = torch.randn(L, H_q, n_max, d, generator=g).bfloat16().cuda()
+    k = torch.randn(L, H_kv, n_max, d, generator=g).bfloat16().cuda()
+    x = torch.rand(L, H_kv, n_max, generator=g).cuda()
+    calls = []
+    for n in (200, 700, 1500, 2049, 4097):
+        cut = [t[:, :, :n].contiguous() for t in (q, k, x)]
+        calls.append((cut, torch.empty(L, H_kv, n, device="cuda"), torch.empty(L, 4, n, device="cuda")))
+    pk.proxykv_reserve(ctx, n_max, n_max)
+    pk.proxykv_map(ctx, x)  # code objects and streams are loaded
+    pk.proxykv_score(ctx, q, k, k, 512)
+    pk.proxykv_score_self(ctx, q, k)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    free = torch.cuda.mem_get_info()[0]
+    for (qn, kn, xn), out, yhat in calls:
+        pk.proxykv_score(ctx, qn, kn, kn, 512, x_out=out)
+        pk.proxykv_score_self(ctx, qn, kn, x_out=out)
+        pk.proxykv_map(ctx, xn, yhat=yhat)
+        torch.cuda.synchronize()
+        assert torch.cuda.mem_get_info()[0] == free, f"{out.shape[2]} tokens"
+    pk.proxykv_destroy(ctx)
