@@ -5,7 +5,7 @@
 //
 // Every kernel reads a row in chunks of 4096 scores, four consecutive ones per thread: a wave's load is 1 KB in one piece
 // (36 consecutive scores per thread, which makes the ordered output a plain prefix sum over the threads, reads 64 lines
-// per load instead of 8 and took 44 us for 256 rows of 32 768 against 26 us).  The order of the output is kept
+// per load instead of 8 and took 44 us for 256 rows of 32 768 against 27 us).  The order of the output is kept
 // by counting per (chunk, wave) and ranking inside a wave with ballots, so that stores too lie side by side.
 //
 // A row of up to 36 864 scores is one workgroup's, its keys stay in registers for all passes.  A longer row is split into
@@ -336,7 +336,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
 // last at the row's counter has every part's contribution in the row's histogram and picks the bin that holds the krem-th
 // largest key.
 // Eleven bits: three passes instead of four, and the first digit (sign, exponent, two bits of mantissa) spreads scores
-// that share an exponent over four bins.  112 rows of 170 000 scores: 87 us in all, with 8 bits and scores read by thread 222 us.
+// that share an exponent over four bins.  112 rows of 170 000 scores: 79 us in all, with 8 bits and scores read by thread 222 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMwQuads = 11, kMwPartMax = kMwQuads * 256 * kTopkWaves;  // quads per lane and scores per part
 constexpr int kMwStateWords = 16;
