@@ -431,9 +431,11 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
     if (tid < kDigitBins) part_words[kDigitBins - 1 - tid] = at_or_above;
     if (tid == 0) part_words[kDigitBins] = n_hi_all;
   }
-  // This part's bins are in the row's histogram before its ticket is taken: the adds are device-scope atomics, carried
-  // out where all workgroups meet, and the barrier lets no wave pass before its own adds have been acknowledged.  (A
-  // device-wide fence here instead costs a write-back of the whole L2 per workgroup: 200 us per launch at 560 groups.)
+  // This part's bins must be in the row's histogram before its ticket is taken.  The adds are device-scope atomics, carried out
+  // where all workgroups meet, but nothing orders them before the ticket, which is an add to another address: a barrier does
+  // not wait for memory operations under way.  So every wave waits until its own adds have been acknowledged, then the
+  // workgroup meets.  (A device-wide fence instead writes back the whole L2 per workgroup: 200 us per launch at 560 groups.)
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) s_last = (atomicAdd(&rs[4 + PASS], 1u) == (uint32_t)(parts - 1));
   __syncthreads();
