@@ -428,6 +428,23 @@ def test_mapper_batches_of_layers(L_s, L_l, N):
     pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("L,N", [(1, 2049), (1, 2500), (1, 3072), (1, 3073), (2, 2048), (2, 2049), (3, 1365), (3, 1366)])
+def test_mapper_on_both_sides_of_the_small_tiles(L, N):
+    """Batches of up to 4096 window rows run in the small-tile kernels.  One layer of 2049 .. 3072 tokens has two windows there
+    (overlap averaging, a token's row stored into both windows, v split at the window), 3073 tokens are the first of the
+    large tiles; two and three layers of one window on either side of the line."""
+    case = synth.scaled_case(synth.CASES["llama_8k"], name="small", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=N, N_q=1, chunk=1,
+                             n_planted=0)
+    w = synth.make_mapper_weights(case.H_kv, case.H_l)
+    g = torch.Generator().manual_seed(400 + N)
+    X = (torch.rand(L, case.H_kv, N, generator=g) ** 8) * (1.0 + torch.arange(L).view(-1, 1, 1))
+    ctx = _ctx(case, w)
+    y = pk.proxykv_map(ctx, X.float().cuda())
+    torch.cuda.synchronize()
+    assert_close(y, oracle.mapper(X.float(), w, L), f"map {L} layers, N={N}")
+    pk.proxykv_destroy(ctx)
+
+
 def test_mapper_with_scores_beyond_the_half_range():
     """Sum-form scores with an attention sink (Sec. 3 prints the feature as a sum over the query axis, so one key can
     collect a share of every row): the first conv block's output reaches 1.4e5, beyond what IEEE half holds.  The
