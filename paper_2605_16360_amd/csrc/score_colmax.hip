@@ -266,6 +266,7 @@ __global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void sc
     fetch_next();
     store(1);
   }
+  __builtin_amdgcn_s_waitcnt(kVmcnt0);  // the resident keys have landed: no tile waits for them (see score_lse.hip)
   if (total > 2) fetch_next();
 
   int cqt = qt_first + first % nqg;  // query tile of step t

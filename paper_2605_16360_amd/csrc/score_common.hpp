@@ -16,6 +16,7 @@ struct ScoreCfg {
   static constexpr int TILE_U4 = ROWS * CPR;    // 16-byte units per tile
 };
 constexpr int kNBuf = 3;
+constexpr int kVmcnt0 = 0x0F70;  // s_waitcnt vmcnt(0)
 
 // Block -> (group, item) on a one-dimensional grid.  The hardware deals blocks round-robin to the 8 XCDs, so XCD x
 // = block % 8 takes the (layer, KV head) groups x, x + 8, ... one after the other: the `per_group` blocks of a group run

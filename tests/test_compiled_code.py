@@ -1,0 +1,51 @@
+"""Properties of the compiled kernels that a run does not show, or shows only as time: read from the assembly that the
+package's own compiler flags give."""
+import functools
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2605_16360_amd import build
+
+
+@functools.lru_cache(maxsize=None)
+def kernels(source):
+    """(name, assembly) of every kernel of a source file"""
+    r = subprocess.run([build._hipcc(), *build.FLAGS, "-x", "hip", "--cuda-device-only", "-S", os.path.join(build.CSRC, source),
+                        "-o", "-"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    return re.findall(r"^(_ZN\w*):(.*?)^\.Lfunc_end", r.stdout, re.M | re.S)
+
+
+def test_every_topk_pass_waits_for_its_adds_before_the_ticket():
+    """The split Top-K's workgroups meet in a per-row histogram: each adds its bins, then takes a ticket, and the last to arrive
+    reads the histogram.  Nothing but a wait for outstanding memory operations orders a wave's adds before the ticket, so
+    `s_waitcnt vmcnt(0)` has to stand between the last add without a result and the barrier in front of the ticket."""
+    passes = [(name, body) for name, body in kernels("topk.hip") if "mw_pass_kernel" in name]
+    assert len(passes) == 7  # three of 11 bits, four of 8
+    for name, body in passes:
+        ops = re.findall(r"^\s+(global_atomic_add\b.*|s_barrier\b|s_waitcnt\b.*)$", body, re.M)
+        adds = [i for i, op in enumerate(ops) if op.startswith("global_atomic_add")]
+        bins = [i for i in adds if "sc0" not in ops[i]]  # sc0: the old value is returned
+        ticket = next(i for i in adds if i > bins[-1])
+        barriers = [i for i in range(bins[-1], ticket) if ops[i].startswith("s_barrier")]
+        assert barriers, name
+        assert any("vmcnt(0)" in op for op in ops[bins[-1]:barriers[-1]]), name
+
+
+@pytest.mark.parametrize("source", ["score_lse.hip", "score_colmax.hip"])
+def test_no_scoring_tile_waits_for_its_own_prefetch(source):
+    """The resident operand is loaded once, in front of the loop.  Where the compiler cannot tell that it has landed, it puts a
+    wait for global loads in front of the loop's MFMAs, and every tile then waits for the prefetch it has just issued."""
+    seen = 0
+    for name, body in kernels(source):
+        ops = re.findall(r"^\s+(s_waitcnt\b.*|v_mfma\w*|s_barrier|v_\w+|ds_\w+|global_\w+)", body, re.M)
+        if not any(op.startswith("v_mfma") for op in ops):
+            continue
+        seen += 1
+        first = next(i for i, op in enumerate(ops) if op.startswith("s_barrier"))
+        waiting = [i for i in range(first, len(ops)) if ops[i].startswith("v_mfma") and "vmcnt" in ops[i - 1]]
+        assert not waiting, f"{name}: {len(waiting)} MFMAs behind a wait for global loads"
+    assert seen >= 4
