@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
   const int i_end = (i0 + QB < N_q ? i0 + QB : N_q);  // one past the block's last query
   const int rec_lo = (i0 / chunk) * chunk;            // first reconstruction key any query of the block sees
   const int n_rec = (i_end - rec_lo + C::ROWS - 1) / C::ROWS;
-  const int total_all = n_ctx + n_rec;
+  const int total_all = n_ctx + n_rec, n_whole = N / C::ROWS;  // n_whole: context tiles that the end does not cut
   // this workgroup's tiles: t0, ..., t0 + total - 1 of the list
   const int t0 = SPLIT ? (int)((int64_t)total_all * split / splits) : 0;
   const int total = SPLIT ? (int)((int64_t)total_all * (split + 1) / splits) - t0 : total_all;
@@ -173,13 +173,15 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     const int cs_i_lo = wave_i_lo + cs * 32;
     return is_rec ? !(jbase + 31 <= cs_i_lo && jbase >= ((cs_i_lo + 31) / chunk) * chunk) : jbase + 32 > limit;
   };
+  // a column sees the context keys below N, the reconstruction keys from its chunk's first to its own: one range either way, so
+  // that the mask is three instructions per element (as a choice per element it compiled to two branches for each, fetched for a
+  // few tiles: 28 layers of 12 heads of 128, 200 queries of 2000 keys, both passes: 123 -> 109 us)
   auto mask_chain = [&](f32x16& acc, bool is_rec, int jbase, int cs) {
+    const int first = is_rec ? qlo[cs] : 0, last = is_rec ? qi[cs] : N - 1;
+    const int from = first - (jbase + half * 4);
+    const uint32_t span = (uint32_t)(last - first);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int j = jbase + (r >> 2) * 8 + half * 4 + (r & 3);
-      const bool vis = is_rec ? (j <= qi[cs] && j >= qlo[cs]) : (j < N);
-      acc[r] = vis ? acc[r] : kNegInf;
-    }
+    for (int r = 0; r < 16; ++r) acc[r] = (uint32_t)((r >> 2) * 8 + (r & 3) - from) <= span ? acc[r] : kNegInf;
   };
   // a tile that causality, a chunk boundary or the end of the context cuts: its visible chains, summed without checks
   auto cut_tile = [&](const u32x4* buf, bool is_rec, int row0, int limit) {
@@ -217,6 +219,21 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     }
   };
 
+  // sums a tile without checks; false, and the sums as they were, if one of them went out of range
+  auto sum_unchecked = [&](auto&& sum_tile) {
+    float before[NCOL];
+#pragma unroll
+    for (int cs = 0; cs < NCOL; ++cs) before[cs] = lsum[cs];
+    sum_tile();
+    bool bad = false;
+#pragma unroll
+    for (int cs = 0; cs < NCOL; ++cs) bad |= !(lsum[cs] < kTileRedo);
+    if (__builtin_amdgcn_ballot_w64(bad) == 0) return true;
+#pragma unroll
+    for (int cs = 0; cs < NCOL; ++cs) lsum[cs] = before[cs];
+    return false;
+  };
+
   if (total > 0) {
     TileRegs<D> second;  // the first two tiles are asked for together
     fetch(0);
@@ -237,6 +254,10 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     if (t + 3 < total) fetch(t + 3);
     const u32x4* buf = lds + (t % kNBuf) * C::TILE_U4;
     const int tg = t0 + t;
+    // Whole context tiles, nearly all there are, go round a loop of their own: with the choices below in it a tile of heads of
+    // 128 took 1 to 3 % longer (28 layers of 12 heads, 300 queries of 16 000 keys, both passes: 1123 -> 1108 us).
+    const bool whole = t > 0 && tg < n_whole;
+    if (whole && sum_unchecked([&]() { interior_tile(buf); })) continue;
     const bool is_rec = tg >= n_ctx;
     const int row0 = is_rec ? rec_lo + (tg - n_ctx) * C::ROWS : tg * C::ROWS;
     // Summed without checks, and again chain by chain with them if a sum went out of range (as it does where a column has
@@ -247,22 +268,13 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     // Where there are few tiles, cut ones take the checks at once, and so does the first of a share: the way to a first
     // reference and the code of a second loop, fetched for a tile or two, cost more than they save (16 layers, causal:
     // 200 tokens 30 -> 22 us, 450 tokens 62 -> 51 us, 1000 tokens, eight tiles and more, the same either way).
-    bool redo = (total < 8 && !interior) || (SPLIT && t == 0 && total < 4);
+    bool redo = whole || (total < 8 && !interior) || (SPLIT && t == 0 && total < 4);
     if (!redo) {
       if (t == 0) first_reference(buf, interior, is_rec, row0);
-      float before[NCOL];
-#pragma unroll
-      for (int cs = 0; cs < NCOL; ++cs) before[cs] = lsum[cs];
-      if (interior) interior_tile(buf);
-      else cut_tile(buf, is_rec, row0, limit);
-      bool bad = false;
-#pragma unroll
-      for (int cs = 0; cs < NCOL; ++cs) bad |= !(lsum[cs] < kTileRedo);
-      redo = __builtin_amdgcn_ballot_w64(bad) != 0;
-      if (redo) {
-#pragma unroll
-        for (int cs = 0; cs < NCOL; ++cs) lsum[cs] = before[cs];
-      }
+      redo = !sum_unchecked([&]() {
+        if (interior) interior_tile(buf);
+        else cut_tile(buf, is_rec, row0, limit);
+      });
     }
     if (redo) {
 #pragma unroll 1

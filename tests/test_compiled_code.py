@@ -49,3 +49,12 @@ def test_no_scoring_tile_waits_for_its_own_prefetch(source):
         waiting = [i for i in range(first, len(ops)) if ops[i].startswith("v_mfma") and "vmcnt" in ops[i - 1]]
         assert not waiting, f"{name}: {len(waiting)} MFMAs behind a wait for global loads"
     assert seen >= 4
+
+
+def test_scoring_masks_do_not_branch_per_element():
+    """A column sees one range of keys, so the mask of a cut tile is a comparison per element.  Written as a choice per element
+    it compiles to hundreds of branches, fetched for the few cut tiles of a short input."""
+    passes = [(name, body) for name, body in kernels("score_lse.hip") if "score_lse_kernel" in name]
+    assert len(passes) == 4
+    for name, body in passes:
+        assert len(re.findall(r"^\s+s_cbranch", body, re.M)) < 128, name
