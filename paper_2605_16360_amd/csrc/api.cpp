@@ -238,7 +238,7 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
   if ((rcm = mark(ctx, 0, stream))) return rcm;
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q);
   const bool sum = c.reduce == PROXYKV_REDUCE_SUM;
-  const int q_splits = pkv::score_query_splits(sum, c.L_s, c.H_q, c.H_kv, c.d, N, N_q);
+  const int q_splits = pkv::score_query_splits(sum, false, c.L_s, c.H_q, c.H_kv, c.d, N, N_q);
   const int64_t n_clear = !sum && (splits > 1 || q_splits > 1) ? (int64_t)c.L_s * c.H_kv * N : 0;
   PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, splits, x_out, n_clear, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
@@ -273,7 +273,7 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N);
-  const int q_splits = pkv::score_query_splits(true, c.L_s, c.H_q, c.H_kv, c.d, N, N);
+  const int q_splits = pkv::score_query_splits(true, true, c.L_s, c.H_q, c.H_kv, c.d, N, N);
   PKV_HIP(ctx, pkv::launch_score_lse(q, k, k, nl, splits, x_out, 0, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
   PKV_HIP(ctx, pkv::launch_score_colsum(q, k, nl, splits, x_out, (float*)ctx->x_parts.ptr, q_splits, c.L_s, c.H_q, c.H_kv, c.d, N, N, true, stream));

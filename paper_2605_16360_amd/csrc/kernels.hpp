@@ -22,7 +22,7 @@ hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint
 // neg_lse and splits as pass 1 left them.  q_splits = score_query_splits(...) workgroups share a key block's queries; with
 // splits > 1 or q_splits > 1 they raise x, which pass 1 has to clear.
 size_t score_parts_bytes(int L_s, int H_kv, int d, int64_t N);  // of `parts` below, for all inputs of up to N keys
-int score_query_splits(bool sum, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q);
+int score_query_splits(bool sum, bool causal, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q);
 hipError_t launch_score_colmax(const uint16_t* q, const uint16_t* k_ctx, const float* neg_lse, int splits, float* x,
                                int q_splits, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q,
                                hipStream_t stream);

@@ -388,11 +388,16 @@ static int64_t pass2_slots(bool sum, int d) { return 256 * (d == 64 ? (sum ? 3 :
 
 // Workgroups per key block in pass 2.  All workgroups take equally long, so `blocks` of them on `slots` places take
 // ceil(blocks / slots) turns, the last of which may be nearly empty (1152 on 768: two turns for one and a half's work);
-// s workgroups per block take ceil(s * blocks / slots) / s.  A part costs its start (about 1 % of a block's work where a
-// block streams a hundred query tiles); parts of fewer than two tiles would only wait for memory.
+// s workgroups per block take ceil(s * blocks / slots) turns of a part each.  A part takes its share of the block's query tiles
+// and a start: the resident keys and the first tiles have to arrive, as long as four tiles take in the max form, whose part loads
+// twice the keys of the sum form's two (one in the causal form, whose parts are not equally long: the late ones are short).
+// Parts of fewer than two tiles would only wait for memory.
 // Measured, without and with: 28 x 2 heads of 128, 10 007 keys (4.4 turns' work in 5) 7830 -> 7160 us; the sum form,
-// 24 x 2 heads of 64, 6001 keys (1.5 in 2) 2212 -> 2060 us; causal, 16 x 8 heads, 4097 keys 1164 -> 950 us.
-int score_query_splits(bool sum, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q) {
+// 24 x 2 heads of 64, 6001 keys (1.5 in 2) 2212 -> 2060 us; causal, 16 x 8 heads, 4097 keys 1164 -> 950 us.  Short streams,
+// with a start of one tile and as here, both passes: 28 x 2 heads of 128, 4096 keys, 200 queries 237 -> 224 us (217 before
+// any were split), 2000 keys, 800 queries 436 -> 400 us (397); the sum form, 16 x 8 heads of 64, 2000 keys, 64 queries
+// 84.5 -> 82 us; the causal form with a start of two tiles instead of one, 4097 keys, 1660 -> 1810 us.
+int score_query_splits(bool sum, bool causal, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q) {
   const int cols = 128 * (sum ? kSumCols : kMaxCols);
   const int64_t slots = pass2_slots(sum, d);
   const int64_t blocks = (N + cols - 1) / cols * L_s * H_kv;
@@ -401,10 +406,11 @@ int score_query_splits(bool sum, int L_s, int H_q, int H_kv, int d, int64_t N, i
   if (sum && most > kMaxSumParts) most = kMaxSumParts;  // each part's sums are written and read again
   if (most > kMaxTurns * slots / blocks) most = kMaxTurns * slots / blocks;  // one more saves no more than a 64th
   if (most > tiles / 2) most = tiles / 2;
+  const double start = causal ? 1.0 : (sum ? 2.0 : 4.0);
   int64_t best = 1;
   double best_cost = 1e30;
   for (int64_t s = 1; s <= most || s == 1; ++s) {
-    const double cost = (double)((blocks * s + slots - 1) / slots) / (double)s * (1.0 + (double)(s - 1) / (double)tiles);
+    const double cost = (double)((blocks * s + slots - 1) / slots) * ((double)tiles / (double)s + start);
     if (cost < best_cost * 0.985) {
       best = s;
       best_cost = cost;

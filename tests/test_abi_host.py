@@ -122,3 +122,17 @@ def test_compute_calls_fail_loudly_without_a_gpu():
         pk.proxykv_reserve(ctx, 64, 64)
     assert e.value.status == pk.PROXYKV_EHIP
     pk.proxykv_destroy(ctx)
+
+
+def test_scoring_splits_a_key_block_only_where_it_pays():
+    """Workgroups per key block in pass 2: a short query axis (a part's start costs several of its few tiles) is not split to
+    fill a last turn that is three quarters full; long ones with a half-empty last turn are, and few blocks fill the chip."""
+    f = pk.load()._ZN3pkv18score_query_splitsEbbiiiill  # (sum, causal, L_s, H_q, H_kv, d, N, N_q)
+    f.argtypes = [ctypes.c_bool] * 2 + [ctypes.c_int] * 4 + [ctypes.c_int64] * 2
+    for N, N_q in [(4096, 200), (4096, 256), (4096, 300), (2000, 800)]:
+        assert f(False, False, 28, 12, 2, 128, N, N_q) == 1, (N, N_q)
+    assert f(True, False, 16, 32, 8, 64, 2000, 64) == 1
+    assert f(False, False, 28, 12, 2, 128, 10007, 10007) > 1
+    assert f(True, False, 24, 14, 2, 64, 6001, 6001) > 1
+    assert f(True, True, 16, 32, 8, 64, 4097, 4097) > 1
+    assert f(False, False, 1, 4, 2, 64, 4000, 600) > 1
