@@ -125,12 +125,13 @@ int count_distinct(const proxykv_config& c) {
   return distinct;
 }
 
-int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool map_part, bool prune_part,
+// `parts`: the column sums of several workgroups per key block too (the sum and the causal form; the max form has none)
+int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool parts, bool map_part, bool prune_part,
                 hipStream_t stream) {
   const Sizes s = workspace_sizes(ctx->cfg, N, N_q, ctx->distinct_layers);
   int rc = PROXYKV_OK;
   if (score_part && (rc = ensure(ctx, ctx->neg_lse, s.neg_lse, stream))) return rc;
-  if (score_part && (rc = ensure(ctx, ctx->x_parts, s.x_parts, stream))) return rc;
+  if (parts && (rc = ensure(ctx, ctx->x_parts, s.x_parts, stream))) return rc;
   if (prune_part) {
     if ((rc = ensure(ctx, ctx->x_ws, s.x_ws, stream))) return rc;
     if ((rc = ensure(ctx, ctx->yhat_ws, s.yhat_ws, stream))) return rc;
@@ -232,12 +233,12 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
     kc = (const uint16_t*)ctx->kctx_bf16.ptr;
     kr = (const uint16_t*)ctx->krec_bf16.ptr;
   }
-  if ((rc = reserve_all(ctx, N, N_q, true, false, false, stream))) return rc;
+  const bool sum = c.reduce == PROXYKV_REDUCE_SUM;
+  if ((rc = reserve_all(ctx, N, N_q, true, sum, false, false, stream))) return rc;
   float* nl = (float*)ctx->neg_lse.ptr;
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q);
-  const bool sum = c.reduce == PROXYKV_REDUCE_SUM;
   const int q_splits = pkv::score_query_splits(sum, false, c.L_s, c.H_q, c.H_kv, c.d, N, N_q);
   const int64_t n_clear = !sum && (splits > 1 || q_splits > 1) ? (int64_t)c.L_s * c.H_kv * N : 0;
   PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, splits, x_out, n_clear, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
@@ -268,7 +269,7 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
     q = (const uint16_t*)ctx->q_bf16.ptr;
     k = (const uint16_t*)ctx->krec_bf16.ptr;
   }
-  if ((rc = reserve_all(ctx, N, N, true, false, false, stream))) return rc;
+  if ((rc = reserve_all(ctx, N, N, true, true, false, false, stream))) return rc;
   float* nl = (float*)ctx->neg_lse.ptr;
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
@@ -283,7 +284,7 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
 
 int map_impl(proxykv_ctx* ctx, const float* x, int64_t N, float* yhat, hipStream_t stream) {
   int rc;
-  if ((rc = reserve_all(ctx, N, 1, false, true, false, stream))) return rc;
+  if ((rc = reserve_all(ctx, N, 1, false, false, true, false, stream))) return rc;
   PKV_HIP(ctx, pkv::mapper_forward(ctx, x, N, yhat, stream));
   return PROXYKV_OK;
 }
@@ -498,7 +499,7 @@ int proxykv_reserve(proxykv_ctx* ctx, int64_t N, int64_t N_q) {
   const int rc = validate_lengths(N, N_q, 1);
   if (rc) return rc;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  return reserve_all(ctx, N, N_q, true, true, true, nullptr);
+  return reserve_all(ctx, N, N_q, true, true, true, true, nullptr);  // parts: proxykv_score_self needs them in any context
 }
 
 int proxykv_keep_count(int64_t N, double keep_ratio, int64_t* K_out) {
@@ -630,7 +631,7 @@ int proxykv_prune(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const 
   if (rows > 65535 || 256 % ((c.D * 2) / 16) != 0) return PROXYKV_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
   PKV_HIP(ctx, hipSetDevice(c.device));
-  if ((rc = reserve_all(ctx, N, N_q, true, true, true, s))) return rc;
+  if ((rc = reserve_all(ctx, N, N_q, true, c.reduce == PROXYKV_REDUCE_SUM, true, true, s))) return rc;
   float* x = x_out ? x_out : (float*)ctx->x_ws.ptr;
   float* y = yhat_out ? yhat_out : (float*)ctx->yhat_ws.ptr;
   if ((rc = score_impl(ctx, q_rec, k_ctx, k_rec, dtype, N, N_q, chunk, x, s))) return rc;
