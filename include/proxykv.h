@@ -21,7 +21,11 @@
  *     call returns without synchronising.  Outputs are valid once the stream has been synchronised.
  *   - A context owns device workspace (row log-sum-exps, mapper activations, histograms) and a
  *     device copy of the mapper weights.  Workspace grows on demand inside a call; call
- *     proxykv_reserve beforehand to keep allocation out of a timed or captured region.
+ *     proxykv_reserve beforehand to keep allocation out of a timed or captured region.  A call
+ *     no longer than one that the context has served, or has reserved for, allocates nothing.
+ *     The mapper takes about 7 KB per window row of as many proxy layers as run at a time (up to
+ *     0.9 GB below 16 384 tokens, 1.9 GB at 32 768); where the device has less free, it runs
+ *     fewer at a time, and only if one layer does not fit is PROXYKV_ENOMEM returned.
  *     One context serves one stream at a time; concurrent calls on one context race.
  *   - Return value: PROXYKV_OK (0) or a negative proxykv_status.  All argument checks run before
  *     the first HIP call, so PROXYKV_EINVAL / PROXYKV_EUNSUPPORTED are returned on any machine.

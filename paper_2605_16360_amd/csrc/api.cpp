@@ -49,6 +49,27 @@ int validate_lengths(int64_t N, int64_t N_q, int64_t chunk) {
   return PROXYKV_OK;
 }
 
+void free_buffer(DeviceBuffer& b) {
+  if (b.ptr) (void)hipFree(b.ptr);
+  b.ptr = nullptr;
+  b.bytes = 0;
+}
+
+// The mapper's workspace, lane by lane.  The last buffer is used by the small tiles only.
+constexpr int kLaneBuffers = 6;
+void lane_buffers(pkv::MapperWorkspace& m, DeviceBuffer* (&b)[kLaneBuffers]) {
+  DeviceBuffer* all[kLaneBuffers] = {&m.x, &m.xb, &m.work, &m.s3, &m.range, &m.pre};
+  std::copy(all, all + kLaneBuffers, b);
+}
+void free_lanes(proxykv_ctx* ctx) {
+  for (pkv::MapperWorkspace& m : ctx->m) {
+    DeviceBuffer* b[kLaneBuffers];
+    lane_buffers(m, b);
+    for (DeviceBuffer* x : b) free_buffer(*x);
+  }
+  ctx->map_len = 0;
+}
+
 int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) {
   if (bytes <= b.bytes) return PROXYKV_OK;
   if (b.ptr) {
@@ -60,6 +81,13 @@ int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) 
   }
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, bytes);
+  if (e == hipErrorOutOfMemory && ctx->map_len > 0) {
+    // the mapper makes do with less: it takes what is left when it runs next
+    (void)hipGetLastError();
+    PKV_HIP(ctx, hipStreamSynchronize(stream));
+    free_lanes(ctx);
+    e = hipMalloc(&p, bytes);
+  }
   if (e != hipSuccess) {
     hip_ok(ctx, e);
     return e == hipErrorOutOfMemory ? PROXYKV_ENOMEM : PROXYKV_EHIP;
@@ -77,42 +105,7 @@ int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) 
   return PROXYKV_OK;
 }
 
-struct Sizes {
-  size_t neg_lse, x_parts, x_ws, yhat_ws, h1, x, xb, qk, vt, ao, hid, zg, s3, pre, range;
-  size_t mapper() const { return h1 + x + xb + qk + vt + ao + hid + zg + s3 + pre + range; }  // one batch's activations
-  int lanes;
-  size_t total() const { return neg_lse + x_parts + x_ws + yhat_ws + lanes * mapper(); }
-};
-
-// Every size grows with N and N_q, so that a workspace reserved for the longest call serves all shorter ones: where a plan
-// gives a shorter input more layers per batch or more workgroups, the bound over all shorter inputs stands here.
-Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q, int distinct_layers) {
-  Sizes s;
-  const pkv::MapPlan p = pkv::map_plan(c, N, distinct_layers);
-  // rows of GEMM outputs (and of the residuals they read) are padded to the GEMM's 256-row tile
-  s.lanes = p.lanes;
-  // rows of a batch (batch * p.Tp window rows, batch * p.Np tokens) over all inputs of up to N tokens
-  const size_t most = (size_t)pkv::kMapBatchRows, layers = (size_t)distinct_layers, dt = (size_t)c.d_time;
-  const size_t Tp = std::min(layers * (size_t)p.Tp, std::max(most, (size_t)p.Tp));
-  const size_t Np = std::min(layers * (size_t)p.Np, std::max(most, (size_t)p.Np));
-  s.neg_lse = pkv::score_lse_bytes(c.L_s, c.H_q, N_q);
-  s.x_parts = pkv::score_parts_bytes(c.L_s, c.H_kv, c.d, N);
-  s.x_ws = (size_t)c.L_s * c.H_kv * (size_t)N * 4;
-  s.yhat_ws = (size_t)c.L_l * c.H_l * (size_t)N * 4;
-  s.h1 = (Np + 2 * pkv::kMaxBatch) * (size_t)c.c_mid * 2;
-  s.x = Tp * dt * 4;
-  s.xb = Tp * dt * 2;
-  s.qk = Tp * 2 * dt * 2;
-  // (whole windows: two of them hold at least 2 win - stride rows, and more of them a larger share)
-  s.vt = (p.n_win > 1 ? Tp * 2 * (size_t)c.win / (2 * (size_t)c.win - (size_t)c.stride) + (size_t)c.win : Tp) * dt * 2;
-  s.ao = Tp * dt * 2;
-  s.hid = Tp * (size_t)c.d_ffn * 2;
-  s.zg = Np * dt * 2;
-  s.s3 = Np * (size_t)(c.H_l + 1) * (size_t)c.H_kv * 4;
-  s.pre = std::min(Tp, (size_t)pkv::kMapSmallRows + 255 * pkv::kMaxBatch) * dt * 4;
-  s.range = pkv::kMaxBatch * 64;
-  return s;
-}
+// ---- workspace
 
 // number of distinct proxy layers that the target layers are paired with
 int count_distinct(const proxykv_config& c) {
@@ -125,19 +118,69 @@ int count_distinct(const proxykv_config& c) {
   return distinct;
 }
 
-// `parts`: the column sums of several workgroups per key block too (the sum and the causal form; the max form has none)
-int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool parts, bool map_part, bool prune_part,
-                hipStream_t stream) {
-  const Sizes s = workspace_sizes(ctx->cfg, N, N_q, ctx->distinct_layers);
-  int rc = PROXYKV_OK;
-  if (score_part && (rc = ensure(ctx, ctx->neg_lse, s.neg_lse, stream))) return rc;
-  if (parts && (rc = ensure(ctx, ctx->x_parts, s.x_parts, stream))) return rc;
-  if (prune_part) {
-    if ((rc = ensure(ctx, ctx->x_ws, s.x_ws, stream))) return rc;
-    if ((rc = ensure(ctx, ctx->yhat_ws, s.yhat_ws, stream))) return rc;
-    if ((rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes((int64_t)ctx->cfg.L_l * ctx->cfg.H_l, N), stream))) return rc;
+// A lane's buffers, in bytes for one layer of the plan's length (row counts of GEMM outputs, and of the residuals they read, are
+// padded to the GEMM's 256-row tile).
+struct LaneBytes {
+  size_t per_layer[kLaneBuffers];
+};
+LaneBytes lane_bytes(const proxykv_config& c, const pkv::MapPlan& p) {
+  const size_t row = (size_t)p.Tp * c.d_time;
+  return {{row * 4, row * 2, pkv::map_work_bytes(c, p), (size_t)p.Np * (size_t)(c.H_l + 1) * (size_t)c.H_kv * 4, 64, row * 4}};
+}
+// bytes of buffer i of a lane: the plan's largest batch.  Shorter calls are served from the same workspace, so `pre` covers the
+// small-tile batches of all shorter lengths (they have one lane, unless there are more layers than a batch takes).
+size_t lane_need(const proxykv_config& c, const pkv::MapPlan& p, const LaneBytes& lb, int lane, int distinct, int i) {
+  if (i < kLaneBuffers - 1) return (size_t)p.batch * lb.per_layer[i];
+  if (c.n_enc_layers == 0 || (lane > 0 && distinct <= pkv::kMaxBatch)) return 0;
+  return (size_t)pkv::small_rows(p, distinct) * (size_t)c.d_time * 4;
+}
+// layers of the plan's length that lane m has room for
+int lane_room(pkv::MapperWorkspace& m, const pkv::MapPlan& p, const LaneBytes& lb) {
+  DeviceBuffer* b[kLaneBuffers];
+  lane_buffers(m, b);
+  size_t room = (size_t)pkv::kMaxBatch;
+  for (int i = 0; i < kLaneBuffers - (p.small ? 0 : 1); ++i) room = std::min(room, b[i]->bytes / lb.per_layer[i]);
+  return (int)room;
+}
+
+// The mapper's plan for N tokens, with the workspace for it.  A context that has served a longer one has room for every shorter
+// one, if not always for as many layers at a time as would be asked for: then the batches are smaller, and nothing is allocated
+// (the call may be under capture).  Where the device has too little memory, the batches are halved until they fit.
+int reserve_map(proxykv_ctx* ctx, int64_t N, hipStream_t stream, pkv::MapPlan* out) {
+  const proxykv_config& c = ctx->cfg;
+  const int distinct = ctx->distinct_layers;
+  pkv::MapPlan p = pkv::map_plan(c, N, distinct);
+  const LaneBytes lb = lane_bytes(c, p);
+  if (N <= ctx->map_len) {
+    int room = lane_room(ctx->m[0], p, lb), lanes = 1;
+    for (; lanes < p.lanes; ++lanes) {
+      const int r = lane_room(ctx->m[lanes], p, lb);
+      if (r < 1) break;
+      room = std::min(room, r);
+    }
+    if (room >= 1) {
+      *out = pkv::map_plan(c, N, distinct, room, lanes);
+      return PROXYKV_OK;
+    }
   }
-  if (map_part && s.lanes > 1 && !ctx->lanes_created) {
+  ctx->map_len = 0;
+  for (;;) {
+    int rc = PROXYKV_OK;
+    for (int lane = 0; lane < p.lanes && rc == PROXYKV_OK; ++lane) {
+      DeviceBuffer* b[kLaneBuffers];
+      lane_buffers(ctx->m[lane], b);
+      for (int i = 0; i < kLaneBuffers && rc == PROXYKV_OK; ++i) rc = ensure(ctx, *b[i], lane_need(c, p, lb, lane, distinct, i), stream);
+    }
+    if (rc == PROXYKV_ENOMEM && (p.batch > 1 || p.lanes > 1)) {
+      PKV_HIP(ctx, hipStreamSynchronize(stream));
+      free_lanes(ctx);
+      p = p.batch > 1 ? pkv::map_plan(c, N, distinct, (p.batch + 1) / 2) : pkv::map_plan(c, N, distinct, 1, 1);
+      continue;
+    }
+    if (rc != PROXYKV_OK) return rc;
+    break;
+  }
+  if (p.lanes > 1 && !ctx->lanes_created) {
     for (int i = 1; i < pkv::kMapLanes; ++i) {
       if (!ctx->lane_stream[i]) PKV_HIP(ctx, hipStreamCreateWithFlags(&ctx->lane_stream[i], hipStreamNonBlocking));
       if (!ctx->lane_join[i]) PKV_HIP(ctx, hipEventCreateWithFlags(&ctx->lane_join[i], hipEventDisableTiming));
@@ -145,20 +188,32 @@ int reserve_all(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool score_part, bool 
     if (!ctx->lane_fork) PKV_HIP(ctx, hipEventCreateWithFlags(&ctx->lane_fork, hipEventDisableTiming));
     ctx->lanes_created = true;
   }
-  for (int lane = 0; map_part && lane < s.lanes; ++lane) {
-    pkv::MapperWorkspace& m = ctx->m[lane];
-    if ((rc = ensure(ctx, m.h1, s.h1, stream))) return rc;
-    if ((rc = ensure(ctx, m.x, s.x, stream))) return rc;
-    if ((rc = ensure(ctx, m.xb, s.xb, stream))) return rc;
-    if ((rc = ensure(ctx, m.qk, s.qk, stream))) return rc;
-    if ((rc = ensure(ctx, m.vt, s.vt, stream))) return rc;
-    if ((rc = ensure(ctx, m.ao, s.ao, stream))) return rc;
-    if ((rc = ensure(ctx, m.hid, s.hid, stream))) return rc;
-    if ((rc = ensure(ctx, m.zg, s.zg, stream))) return rc;
-    if ((rc = ensure(ctx, m.s3, s.s3, stream))) return rc;
-    if ((rc = ensure(ctx, m.pre, s.pre, stream))) return rc;
-    if ((rc = ensure(ctx, m.range, s.range, stream))) return rc;
-  }
+  ctx->map_len = N;
+  *out = p;
+  return PROXYKV_OK;
+}
+
+// What scoring and pruning need beside the mapper.  Every size grows with N and N_q, so that a workspace that has served the longest
+// call serves all shorter ones.  `parts`: the column sums of several workgroups per key block too (the sum and the causal
+// form; the max form has none).
+struct Sizes {
+  size_t neg_lse, x_parts, x_ws, yhat_ws;
+};
+Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q) {
+  return {pkv::score_lse_bytes(c.L_s, c.H_q, N_q), pkv::score_parts_bytes(c.L_s, c.H_kv, c.d, N), (size_t)c.L_s * c.H_kv * (size_t)N * 4,
+          (size_t)c.L_l * c.H_l * (size_t)N * 4};
+}
+int reserve_score(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool parts, hipStream_t stream) {
+  const Sizes s = workspace_sizes(ctx->cfg, N, N_q);
+  int rc = ensure(ctx, ctx->neg_lse, s.neg_lse, stream);
+  if (rc == PROXYKV_OK && parts) rc = ensure(ctx, ctx->x_parts, s.x_parts, stream);
+  return rc;
+}
+int reserve_prune(proxykv_ctx* ctx, int64_t N, hipStream_t stream) {
+  const Sizes s = workspace_sizes(ctx->cfg, N, 1);
+  int rc = ensure(ctx, ctx->x_ws, s.x_ws, stream);
+  if (rc == PROXYKV_OK) rc = ensure(ctx, ctx->yhat_ws, s.yhat_ws, stream);
+  if (rc == PROXYKV_OK) rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes((int64_t)ctx->cfg.L_l * ctx->cfg.H_l, N), stream);
   return rc;
 }
 
@@ -200,12 +255,6 @@ struct Stager {
   }
 };
 
-void free_buffer(DeviceBuffer& b) {
-  if (b.ptr) (void)hipFree(b.ptr);
-  b.ptr = nullptr;
-  b.bytes = 0;
-}
-
 // Records stage boundary `i` on the stream when stage timing is switched on.
 int mark(proxykv_ctx* ctx, int i, hipStream_t stream) {
   if (!ctx->profile) return PROXYKV_OK;
@@ -234,7 +283,7 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
     kr = (const uint16_t*)ctx->krec_bf16.ptr;
   }
   const bool sum = c.reduce == PROXYKV_REDUCE_SUM;
-  if ((rc = reserve_all(ctx, N, N_q, true, sum, false, false, stream))) return rc;
+  if ((rc = reserve_score(ctx, N, N_q, sum, stream))) return rc;
   float* nl = (float*)ctx->neg_lse.ptr;
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
@@ -269,7 +318,7 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
     q = (const uint16_t*)ctx->q_bf16.ptr;
     k = (const uint16_t*)ctx->krec_bf16.ptr;
   }
-  if ((rc = reserve_all(ctx, N, N, true, true, false, false, stream))) return rc;
+  if ((rc = reserve_score(ctx, N, N, true, stream))) return rc;
   float* nl = (float*)ctx->neg_lse.ptr;
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
@@ -284,8 +333,9 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
 
 int map_impl(proxykv_ctx* ctx, const float* x, int64_t N, float* yhat, hipStream_t stream) {
   int rc;
-  if ((rc = reserve_all(ctx, N, 1, false, false, true, false, stream))) return rc;
-  PKV_HIP(ctx, pkv::mapper_forward(ctx, x, N, yhat, stream));
+  pkv::MapPlan p;
+  if ((rc = reserve_map(ctx, N, stream, &p))) return rc;
+  PKV_HIP(ctx, pkv::mapper_forward(ctx, p, x, yhat, stream));
   return PROXYKV_OK;
 }
 
@@ -327,8 +377,11 @@ int proxykv_destroy(proxykv_ctx* ctx) {
   if (!ctx) return PROXYKV_OK;
   std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
                                     &ctx->neg_lse, &ctx->x_parts, &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws};
-  for (pkv::MapperWorkspace& m : ctx->m)
-    for (DeviceBuffer* b : {&m.h1, &m.x, &m.xb, &m.qk, &m.vt, &m.ao, &m.hid, &m.zg, &m.s3, &m.pre, &m.range}) all.push_back(b);
+  for (pkv::MapperWorkspace& m : ctx->m) {
+    DeviceBuffer* b[kLaneBuffers];
+    lane_buffers(m, b);
+    all.insert(all.end(), b, b + kLaneBuffers);
+  }
   bool any = ctx->ev_created || ctx->lanes_created;
   for (DeviceBuffer* b : all) any = any || b->ptr;
   if (any) {
@@ -490,16 +543,26 @@ int proxykv_workspace_bytes(const proxykv_config* cfg, int64_t N, int64_t N_q, s
   int rc = validate_config(cfg);
   if (rc) return rc;
   if ((rc = validate_lengths(N, N_q, 1))) return rc;
-  *out_bytes = workspace_sizes(*cfg, N, N_q, count_distinct(*cfg)).total();
+  const int distinct = count_distinct(*cfg);
+  const Sizes s = workspace_sizes(*cfg, N, N_q);
+  const pkv::MapPlan p = pkv::map_plan(*cfg, N, distinct);
+  const LaneBytes lb = lane_bytes(*cfg, p);
+  size_t total = s.neg_lse + s.x_parts + s.x_ws + s.yhat_ws + pkv::topk_scratch_bytes((int64_t)cfg->L_l * cfg->H_l, N);
+  for (int lane = 0; lane < p.lanes; ++lane)
+    for (int i = 0; i < kLaneBuffers; ++i) total += lane_need(*cfg, p, lb, lane, distinct, i);
+  *out_bytes = total;
   return PROXYKV_OK;
 }
 
 int proxykv_reserve(proxykv_ctx* ctx, int64_t N, int64_t N_q) {
   if (!ctx) return PROXYKV_EINVAL;
-  const int rc = validate_lengths(N, N_q, 1);
+  int rc = validate_lengths(N, N_q, 1);
   if (rc) return rc;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  return reserve_all(ctx, N, N_q, true, true, true, true, nullptr);  // parts: proxykv_score_self needs them in any context
+  if ((rc = reserve_score(ctx, N, N_q, true, nullptr))) return rc;  // (proxykv_score_self has parts in any context)
+  if ((rc = reserve_prune(ctx, N, nullptr))) return rc;
+  pkv::MapPlan p;
+  return reserve_map(ctx, N, nullptr, &p);  // last: it makes do with what is left
 }
 
 int proxykv_keep_count(int64_t N, double keep_ratio, int64_t* K_out) {
@@ -631,7 +694,9 @@ int proxykv_prune(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const 
   if (rows > 65535 || 256 % ((c.D * 2) / 16) != 0) return PROXYKV_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
   PKV_HIP(ctx, hipSetDevice(c.device));
-  if ((rc = reserve_all(ctx, N, N_q, true, c.reduce == PROXYKV_REDUCE_SUM, true, true, s))) return rc;
+  pkv::MapPlan plan;  // everything is there before the first launch
+  if ((rc = reserve_score(ctx, N, N_q, c.reduce == PROXYKV_REDUCE_SUM, s)) || (rc = reserve_prune(ctx, N, s)) || (rc = reserve_map(ctx, N, s, &plan)))
+    return rc;
   float* x = x_out ? x_out : (float*)ctx->x_ws.ptr;
   float* y = yhat_out ? yhat_out : (float*)ctx->yhat_ws.ptr;
   if ((rc = score_impl(ctx, q_rec, k_ctx, k_rec, dtype, N, N_q, chunk, x, s))) return rc;

@@ -53,18 +53,12 @@ inline int kv3_stride(const proxykv_config& c) { return (2 * c.H_kv * c.d_head_x
 // Mapper activations for one batch of proxy layers (the network runs once per distinct proxy layer, and its weights are
 // shared by all of them, so a batch's layers lie one behind the other on the M axis of every launch).
 struct MapperWorkspace {
-  // per layer of the batch:
-  DeviceBuffer h1;       // fp16 [(N+2), c_mid]  stem conv1 output with one zero row at each end
-  DeviceBuffer x;        // fp32 [Tp, d_time]    residual stream over all window rows
-  DeviceBuffer xb;       // fp16 [Tp, d_time]    fp16 copy feeding the GEMMs
-  DeviceBuffer qk;       // fp16 [Tp, 2*d_time]  q and k of the current layer
-  DeviceBuffer vt;       // fp16 [n_win, heads, 64, vt_ld]  v transposed per window and head
-  DeviceBuffer ao;       // fp16 [Tp, d_time]    attention output
-  DeviceBuffer hid;      // fp16 [Tp, d_ffn]
-  DeviceBuffer zg;       // fp16 [Np, d_time]    overlap-averaged encoder output
-  DeviceBuffer s3;       // fp32 [Np, (H_l + 1) * H_s]  stage 3: per token the H_l x H_s logits, then <w_o, V[s]> of every slot
-  DeviceBuffer pre;      // fp32 [Tp, d_time]    small inputs only: sums that the next kernel normalises as it reads them
-  DeviceBuffer range;    // 16 words: partial maxima of |score| (bits)
+  DeviceBuffer x;      // fp32 [Tp, d_time] per layer: residual stream over all window rows
+  DeviceBuffer xb;     // fp16 [Tp, d_time]: fp16 copy feeding the GEMMs
+  DeviceBuffer work;   // what one kernel leaves for the next (LanePointers in mapper.hpp)
+  DeviceBuffer s3;     // fp32 [Np, (H_l + 1) * H_s]  stage 3: per token the H_l x H_s logits, then <w_o, V[s]> of every slot
+  DeviceBuffer range;  // 16 words: partial maxima of |score| (bits)
+  DeviceBuffer pre;    // fp32 [Tp, d_time]: small inputs only: sums that the next kernel normalises as it reads them
 };
 
 }  // namespace pkv
@@ -89,6 +83,7 @@ struct proxykv_ctx {
   pkv::DeviceBuffer topk_ws;                       // per-row histograms and counters of the Top-K of rows split over workgroups
   bool fused_select = false;                       // proxykv_prune: selection and gather in one launch (measured slower)
   pkv::MapperWorkspace m[pkv::kMapLanes];          // one per lane; only the lanes a length needs are allocated
+  int64_t map_len = 0;                             // longest context that m has been sized for
   // lanes 1 .. kMapLanes-1: streams (default priority, non-blocking) and the events that fork them from and join
   // them into the caller's stream, which is lane 0
   bool lanes_created = false;
@@ -111,42 +106,68 @@ inline void window_plan(int64_t N, int win, int stride, int64_t* n_win, int64_t*
   *total_rows = (k - 1) * (int64_t)win + (N - (k - 1) * (int64_t)stride);
 }
 
-// How the mapper runs a context of N tokens: `batch` distinct proxy layers at a time, batches dealt to `lanes` streams.
+// How the mapper runs a context of N tokens: the distinct proxy layers in `n_batches` batches, dealt to `lanes` streams.
 // Small layers leave the chip idle one by one (512 window rows are 12 output tiles of the QKV product), so a batch takes
-// as many of them as make kMapBatchRows rows (about 14 KB of workspace each).  Long contexts need several batches; two of
-// them side by side, on streams and in workspaces of their own, let one's stores and residual reads run under the other's
-// matrix work.  Measured, 16 distinct layers, one layer per batch on four streams / all on one stream in batches of
-// 262 144 rows / as here: N = 1500 6.15 / 2.21 / 2.21 ms, N = 8192 19.3 / 19.0 / 18.5 ms, N = 32 768 82.0 / 84.1 / 81.4 ms.
-constexpr int64_t kMapBatchRows = 131072;
+// several, up to kMapBatchRows rows.  Two batches side by side, on streams and in workspaces of their own, let one's stores and
+// residual reads run under the other's matrix work; and because two lanes of one long layer each are slower than four layers in
+// flight (N = 32 768: 83.3 and 82.7 ms), a batch takes two layers if they are no more than kMapPairRows rows.
+// Every row holds about 7 KB of workspace for as long as the context lives, so the limits are where more costs more than it gives.
+// 16 distinct layers, ms and MB: one layer per batch on four streams / batches of up to 131 072 rows, 12 KB per row / as here:
+//   N = 1500   4.56, 94  / 2.24, 334  / 2.12, 186      N = 8192    19.5, 690  / 18.7, 3410 / 18.9, 812
+//   N = 4096   9.06, 306 / 8.41, 1228 / 8.18, 700      N = 32 768  82.9, 2998 / 82.9, 3442 / 82.7, 1810
+constexpr int64_t kMapBatchRows = 65536, kMapPairRows = 131072;
 constexpr int kMaxBatch = 32;
+static_assert(kMapBatchRows >= 256 * kMaxBatch, "a small-tile batch is not cut");
 // Up to this many rows in a batch the small tiles are faster (large tiles on the left: one layer of 512 rows 867 / 231 us, of 2000
 // rows 1060 / 566 us; 16 layers of 256 rows 970 / 882 us).
 constexpr int64_t kMapSmallRows = 4096;
 struct MapPlan {
-  int64_t n_win, T;   // windows and window rows of a layer
-  int64_t Tp, Np;     // window rows and tokens of a layer, padded to the GEMM's 256-row tile
-  int64_t vt_ld;      // row length of the transposed v
-  int batch, lanes;
-  bool small;         // few rows: the small-tile kernels
+  int64_t N, n_win, T;  // tokens, windows and window rows of a layer
+  int64_t Tp, Np;       // window rows and tokens of a layer, padded to the GEMM's 256-row tile
+  int64_t vt_ld;        // row length of the transposed v
+  int n_batches, batch, lanes;  // batch: layers of the largest batch
+  bool small;           // few rows: the small-tile kernels
 };
-inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers) {
+// `most` layers per batch and `most_lanes` lanes: what a workspace has room for.  Neither changes a result: the kernels' arithmetic
+// does not depend on the other layers of a batch, and `small` is decided by the layers alone.
+inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers, int most = kMaxBatch, int most_lanes = kMapLanes) {
   MapPlan p;
+  p.N = N;
   window_plan(N, c.win, c.stride, &p.n_win, &p.T);
   p.Tp = (p.T + 255) / 256 * 256;
   p.Np = (N + 255) / 256 * 256;
   p.vt_ld = p.n_win > 1 ? c.win : p.Tp;
+  const int64_t few = (distinct_layers + kMaxBatch - 1) / kMaxBatch;  // batches, if only their number of layers were limited
+  p.small = (distinct_layers + few - 1) / few * p.T <= kMapSmallRows && c.n_enc_layers > 0;
   int64_t cap = kMapBatchRows / p.Tp;
-  cap = cap < 1 ? 1 : (cap > kMaxBatch ? kMaxBatch : cap);
-  const int64_t n_batches = (distinct_layers + cap - 1) / cap;
-  p.batch = (int)((distinct_layers + n_batches - 1) / n_batches);
-  const int64_t used = (distinct_layers + p.batch - 1) / p.batch;
-  p.lanes = used < kMapLanes ? (int)used : kMapLanes;
-  p.small = p.batch * p.T <= kMapSmallRows && c.n_enc_layers > 0;
+  if (cap < 2) cap = 2 * p.Tp <= kMapPairRows ? 2 : 1;
+  if (cap > most) cap = most;
+  int64_t n = (distinct_layers + cap - 1) / cap;
+  if (n > distinct_layers) n = distinct_layers;
+  p.n_batches = (int)n;
+  p.batch = (int)((distinct_layers + n - 1) / n);
+  p.lanes = (int)(n < most_lanes ? n : most_lanes);
   return p;
+}
+// Bytes of `work` per layer, the largest of what is there at a time: the stem's first output, read before the encoder starts;
+// q and k, v transposed and the attention's output, all read before the FFN's hidden rows are written; those, read before the
+// next layer's q, k and v are; the overlap-averaged encoder output.  (12 KB of buffers per row, 7 KB with this one in their place.)
+inline size_t map_work_bytes(const proxykv_config& c, const MapPlan& p) {
+  const size_t row = (size_t)c.d_time * 2, Tp = (size_t)p.Tp;
+  const size_t attn = 3 * Tp * row + (size_t)p.n_win * (size_t)p.vt_ld * row, hid = Tp * (size_t)c.d_ffn * 2;
+  const size_t h1 = ((size_t)(p.N + 2) * c.c_mid * 2 + 255) / 256 * 256, zg = (size_t)p.Np * row;
+  const size_t a = attn > hid ? attn : hid, b = h1 > zg ? h1 : zg;
+  return a > b ? a : b;
+}
+// Layers of a small-tile batch times their padded rows, over all lengths of up to p.N tokens.
+inline int64_t small_rows(const MapPlan& p, int distinct_layers) {
+  const int64_t few = (distinct_layers + kMaxBatch - 1) / kMaxBatch, b = (distinct_layers + few - 1) / few;
+  const int64_t tp = (kMapSmallRows / b + 255) / 256 * 256;
+  return b * (p.Tp < tp ? p.Tp : tp);
 }
 
 // Runs the mapper for every distinct proxy layer; implemented in mapper.hip.
-// Returns a hipError_t; the workspace must already be large enough.
-hipError_t mapper_forward(proxykv_ctx* ctx, const float* x, int64_t N, float* yhat, hipStream_t stream);
+// Returns a hipError_t; the workspace must already be large enough for the plan.
+hipError_t mapper_forward(proxykv_ctx* ctx, const MapPlan& p, const float* x, float* yhat, hipStream_t stream);
 
 }  // namespace pkv

@@ -816,26 +816,22 @@ hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowS
   return hipGetLastError();
 }
 
-// Second stem convolution, encoder and stage-3 inner products of one batch with the large tiles: from m.h1 to m.s3.
-hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& m, const MapPlan& p, int n_layers, int64_t N, int n_cu, hipStream_t stream) {
+// Second stem convolution, encoder and stage-3 inner products of one batch with the large tiles: from h1 to s3.
+hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const MapPlan& p, int n_layers, int64_t N, int n_cu, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
   const int T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
-  const uint16_t* h1 = (const uint16_t*)m.h1.ptr;
-  float* x = (float*)m.x.ptr;
-  uint16_t* xb = (uint16_t*)m.xb.ptr;
-  uint16_t* qk = (uint16_t*)m.qk.ptr;
-  uint16_t* vt = (uint16_t*)m.vt.ptr;
-  uint16_t* ao = (uint16_t*)m.ao.ptr;
-  uint16_t* hid = (uint16_t*)m.hid.ptr;
-  uint16_t* zg = (uint16_t*)m.zg.ptr;
+  const LanePointers m = lane_pointers(c, p, ws);
+  const uint16_t* h1 = m.h1;
+  float* x = m.x;
+  uint16_t *xb = m.xb, *qk = m.qk, *vt = m.vt, *ao = m.ao, *hid = m.hid, *zg = m.zg;
   const unsigned nl = (unsigned)n_layers;
   auto rows_T = [&](int lda) { return RowSpace{n_layers, T, Tp, (int64_t)Tp * lda}; };
 
   EpiArgs e2 = {};
   e2.p0 = w.bn2_scale;
   e2.p1 = w.bn2_shift;
-  e2.range = (const uint32_t*)m.range.ptr;
+  e2.range = m.range;
   e2.cw = w.stem_cw;
   e2.cs = w.stem_cs;
   e2.out_f32 = x;
@@ -890,7 +886,7 @@ hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& m, const M
   e3.p0 = w.kv_b;
   e3.p1 = w.queries;
   e3.g = w.out_w;
-  e3.out_f32 = (float*)m.s3.ptr;
+  e3.out_f32 = m.s3;
   e3.ldc = (c.H_l + 1) * c.H_kv;
   e3.n_slot = c.H_kv;
   e3.n_head = c.H_l;
@@ -900,34 +896,33 @@ hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& m, const M
 
 // The network for the layers of one batch (x_in: all proxy layers' scores [L_s, H_kv, N]); writes the rows of every target
 // layer that is paired with one of them.
-hipError_t mapper_batch(proxykv_ctx* ctx, const MapperWorkspace& m, const MapPlan& p, const LayerBatch& lb, const float* x_in, int64_t N, float* yhat,
+hipError_t mapper_batch(proxykv_ctx* ctx, const MapperWorkspace& ws, const MapPlan& p, const LayerBatch& lb, const float* x_in, int64_t N, float* yhat,
                         int n_cu, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
-  uint32_t* range = (uint32_t*)m.range.ptr;
+  const LanePointers m = lane_pointers(c, p, ws);
   const unsigned nl = (unsigned)lb.n;
-  absmax_kernel<<<dim3(kRangeWords, nl), 1024, 0, stream>>>(x_in, (int64_t)c.H_kv * N, lb, range);
+  absmax_kernel<<<dim3(kRangeWords, nl), 1024, 0, stream>>>(x_in, (int64_t)c.H_kv * N, lb, m.range);
   PKV_TRY(hipGetLastError());
   const int tok = (int64_t)nl * N >= 64 * 512 ? kStemTok : 16;
   stem_conv1_kernel<<<dim3((unsigned)((N + tok - 1) / tok), nl), 256, 0, stream>>>(
-      x_in, w.conv1_w, w.bn1_scale, w.bn1_shift, range, w.stem_cw, w.stem_cs, lb, (uint16_t*)m.h1.ptr, c.H_kv, (int)N, c.c_mid, tok);
+      x_in, w.conv1_w, w.bn1_scale, w.bn1_shift, m.range, w.stem_cw, w.stem_cs, lb, m.h1, c.H_kv, (int)N, c.c_mid, tok);
   PKV_TRY(hipGetLastError());
-  if (p.small) PKV_TRY(mapper_small_body(ctx, m, p, lb.n, N, stream));
-  else PKV_TRY(mapper_large_body(ctx, m, p, lb.n, N, n_cu, stream));
+  if (p.small) PKV_TRY(mapper_small_body(ctx, ws, p, lb.n, N, stream));
+  else PKV_TRY(mapper_large_body(ctx, ws, p, lb.n, N, n_cu, stream));
   const int tok_per_block = 256 / c.H_l;
-  stage3_kernel<<<dim3((unsigned)((N + tok_per_block - 1) / tok_per_block), nl), 256, 0, stream>>>((const float*)m.s3.ptr, w.out_b, yhat, N, (int)p.Np,
+  stage3_kernel<<<dim3((unsigned)((N + tok_per_block - 1) / tok_per_block), nl), 256, 0, stream>>>(m.s3, w.out_b, yhat, N, (int)p.Np,
                                                                                                 c.H_kv, c.H_l, lb);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t mapper_forward(proxykv_ctx* ctx, const float* x_in, int64_t N, float* yhat, hipStream_t stream) {
+hipError_t mapper_forward(proxykv_ctx* ctx, const MapPlan& p, const float* x_in, float* yhat, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   int n_cu = 0, dev = 0;
   PKV_TRY(hipGetDevice(&dev));
   PKV_TRY(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev));
-  const MapPlan p = map_plan(c, N, ctx->distinct_layers);
   // batches are dealt round-robin to the lanes; lane 0 is the caller's stream, the others start behind the work already
   // queued there and are joined into it at the end
   if (p.lanes > 1) {
@@ -935,7 +930,7 @@ hipError_t mapper_forward(proxykv_ctx* ctx, const float* x_in, int64_t N, float*
     for (int lane = 1; lane < p.lanes; ++lane) PKV_TRY(hipStreamWaitEvent(ctx->lane_stream[lane], ctx->lane_fork, 0));
   }
   LayerBatch lb = {};
-  int lane = 0;
+  int lane = 0, done = 0, batches = 0;  // layers and batches so far
   for (int ll = 0; ll < c.L_l;) {
     int ll_hi = ll + 1;
     while (ll_hi < c.L_l && ctx->pairing[ll_hi] == ctx->pairing[ll]) ++ll_hi;
@@ -944,8 +939,9 @@ hipError_t mapper_forward(proxykv_ctx* ctx, const float* x_in, int64_t N, float*
     lb.hi[lb.n] = ll_hi;
     ++lb.n;
     ll = ll_hi;
-    if (lb.n == p.batch || ll == c.L_l) {
-      PKV_TRY(mapper_batch(ctx, ctx->m[lane], p, lb, x_in, N, yhat, n_cu, lane == 0 ? stream : ctx->lane_stream[lane]));
+    if (++done == (int)((int64_t)ctx->distinct_layers * (batches + 1) / p.n_batches)) {
+      PKV_TRY(mapper_batch(ctx, ctx->m[lane], p, lb, x_in, p.N, yhat, n_cu, lane == 0 ? stream : ctx->lane_stream[lane]));
+      ++batches;
       lb.n = 0;
       lane = lane + 1 < p.lanes ? lane + 1 : 0;
     }

@@ -82,6 +82,27 @@ struct RowSpace {
   int64_t a_layer;  // elements between the A rows of two layers
 };
 
+// Where a lane's buffers lie for a plan: all layers of a batch one behind the other in each.  h1, qk and the two behind it, hid and zg
+// share `work`: each is read for the last time before the next one of them is written.
+struct LanePointers {
+  uint16_t* h1;     // fp16 [(N+2), c_mid]  stem conv1 output with one zero row at each end
+  float* x;
+  uint16_t *xb, *qk;  // qk: fp16 [Tp, 2*d_time]  q and k of the current layer
+  uint16_t* vt;     // fp16 [n_win, heads, 64, vt_ld]  v transposed per window and head
+  uint16_t* ao;     // fp16 [Tp, d_time]    attention output
+  uint16_t* hid;    // fp16 [Tp, d_ffn]
+  uint16_t* zg;     // fp16 [Np, d_time]    overlap-averaged encoder output
+  float *s3, *pre;
+  uint32_t* range;
+};
+inline LanePointers lane_pointers(const proxykv_config& c, const MapPlan& p, const MapperWorkspace& m) {
+  uint16_t* work = (uint16_t*)m.work.ptr;
+  const size_t n = (size_t)p.batch, d = (size_t)c.d_time;
+  uint16_t* vt = work + n * p.Tp * 2 * d;
+  uint16_t* ao = vt + n * p.n_win * p.vt_ld * d;
+  return {work, (float*)m.x.ptr, (uint16_t*)m.xb.ptr, work, vt, ao, work, work, (float*)m.s3.ptr, (float*)m.pre.ptr, (uint32_t*)m.range.ptr};
+}
+
 #define PKV_TRY(call)                  \
   do {                                 \
     hipError_t e_ = (call);            \
@@ -91,7 +112,7 @@ struct RowSpace {
 }  // namespace
 
 // Second stem convolution, encoder and stage-3 inner products of one batch with the kernels for few rows
-// (mapper_small.hip): from m.h1 to m.s3.
-hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& m, const MapPlan& p, int n_layers, int64_t N, hipStream_t stream);
+// (mapper_small.hip): from h1 to s3.
+hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const MapPlan& p, int n_layers, int64_t N, hipStream_t stream);
 
 }  // namespace pkv

@@ -552,16 +552,16 @@ hipError_t launch_deep(const DeepArgs& a, int layers, hipStream_t stream) {
 
 }  // namespace
 
-hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& m, const MapPlan& p, int n_layers, int64_t N64, hipStream_t stream) {
+hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const MapPlan& p, int n_layers, int64_t N64, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
   const int N = (int)N64, T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
-  float *x = (float*)m.x.ptr, *pre = (float*)m.pre.ptr;
-  uint16_t *xb = (uint16_t*)m.xb.ptr, *qk = (uint16_t*)m.qk.ptr, *vt = (uint16_t*)m.vt.ptr, *ao = (uint16_t*)m.ao.ptr,
-           *hid = (uint16_t*)m.hid.ptr;
+  const LanePointers m = lane_pointers(c, p, ws);
+  float *x = m.x, *pre = m.pre;
+  uint16_t *xb = m.xb, *qk = m.qk, *vt = m.vt, *ao = m.ao, *hid = m.hid;
 
   DeepArgs d = {};
-  d.a = (const uint16_t*)m.h1.ptr;
+  d.a = m.h1;
   d.lda = c.c_mid;
   d.a_layer = (int64_t)(N + 2) * c.c_mid;
   d.w = w.conv2_w;
@@ -575,7 +575,7 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& m, const M
   d.out_h = xb;
   d.pe = w.pe;
   d.n_win = n_win;
-  d.range = (const uint32_t*)m.range.ptr;
+  d.range = m.range;
   d.cw = w.stem_cw;
   d.cs = w.stem_cs;
   PKV_TRY(launch_deep<kDeepGeluPeWin>(d, n_layers, stream));
@@ -649,7 +649,7 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& m, const M
   h.pre_stride = Tp;
   h.g = w.enc[c.n_enc_layers - 1].ln2_g;
   h.b = w.enc[c.n_enc_layers - 1].ln2_b;
-  h.out_f32 = (float*)m.s3.ptr;
+  h.out_f32 = m.s3;
   h.ldc = (c.H_l + 1) * c.H_kv;
   h.queries = w.queries;
   h.out_w = w.out_w;

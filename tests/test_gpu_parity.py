@@ -494,6 +494,24 @@ def test_mapper_context_reuse_across_lengths():
     pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("L,longest,N", [(16, 11500, 4608), (5, 9000, 2049), (33, 700, 100)])
+def test_mapper_in_the_workspace_of_a_longer_call(L, longest, N):
+    """A shorter call runs in what a longer one has allocated, with as many layers at a time as that holds (16 layers of 4608
+    tokens behind one of 11 500: two or three, a fresh context takes eight): same bits as in a fresh context."""
+    case = synth.scaled_case(synth.CASES["llama_8k"], name="longer", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=N, N_q=1, chunk=1, n_planted=0)
+    w = synth.make_mapper_weights(case.H_kv, case.H_l)
+    g = torch.Generator().manual_seed(500 + N)
+    long = (torch.rand(L, case.H_kv, longest, generator=g) ** 8).cuda()
+    X = long[:, :, 3:N + 3].contiguous()
+    used, fresh = _ctx(case, w), _ctx(case, w)
+    pk.proxykv_map(used, long)
+    y, y_fresh = pk.proxykv_map(used, X), pk.proxykv_map(fresh, X)
+    torch.cuda.synchronize()
+    assert torch.equal(y, y_fresh)
+    pk.proxykv_destroy(used)
+    pk.proxykv_destroy(fresh)
+
+
 # ----------------------------------------------------------------------------------------------
 # whole path
 # ----------------------------------------------------------------------------------------------

@@ -76,3 +76,94 @@ def test_the_max_form_allocates_row_sums_and_nothing_else():
         lse = max(4 * rows, 8 * min(8 * rows, 768 * 256))  # a float per query, or a pair per query and sharing workgroup
         assert out[f"max {n}"] == lse
         assert out[f"sum {n}"] == out[f"self {n}"] > lse
+
+
+def test_mapper_memory_is_bounded():
+    """Batches of layers hold about 7 KB per window row and no more rows than all layers have, or 2 x 65 536, or, where layers are
+    longer than half of that, four of them: below 1 GB up to 16 384 tokens, and from there on less than four layers at the 12 KB
+    per row that one layer at a time on four streams took.  proxykv_workspace_bytes counts what proxykv_reserve allocates."""
+    out = run("""
+        out = []
+        for shape in (LLAMA, QWEN, QWEN32B):
+            for n in (512, 1500, 2500, 4096, 8192, 16384, 32768, 65536, 170000):
+                used = fake.fake_used()
+                h = context(shape, weights=True)
+                weights = fake.fake_used()
+                assert lib.proxykv_map(h, P, n, P, None) == 0
+                size = ctypes.c_size_t()
+                assert lib.proxykv_workspace_bytes(ctypes.byref(pk.make_config(*shape)), n, n, ctypes.byref(size)) == 0
+                total = ctypes.c_size_t(fake.fake_used() - weights)
+                before = fake.fake_used()
+                assert lib.proxykv_reserve(h, n, n) == 0
+                out.append((shape[0], n, total.value, size.value, total.value + fake.fake_used() - before))
+    """)
+    for layers, n, mapper, said, reserved in out:
+        windows = 1 if n <= 2048 else -(-(n - 2048) // 1024) + 1
+        rows = -(-(n + (windows - 1) * 1024) // 256) * 256
+        assert mapper <= max(min(layers * rows, 2 * 65536), (4 if rows <= 65536 else 2) * rows) * 7.5 * 1024 + 20e6, (layers, n, mapper)
+        assert n > 16384 or mapper < 1e9, (layers, n, mapper)
+        assert n < 16384 or mapper < 4 * rows * 12 * 1024, (layers, n, mapper)
+        assert said == reserved, (layers, n, said, reserved)
+
+
+def test_mapper_makes_do_with_less_memory():
+    """A device with room for one layer's activations runs all layers one at a time; with less the call is refused; and a workspace
+    that the mapper has taken is given up when another buffer does not fit beside it."""
+    out = run("""
+        out = {}
+        n = 8192
+        one = ctypes.c_size_t()
+        h = context((1,) + LLAMA[1:4] + (1,) + LLAMA[5:], weights=True)
+        base = fake.fake_used()
+        assert lib.proxykv_map(h, P, n, P, None) == 0
+        layer = fake.fake_used() - base
+        for room in (0.9, 1.1, 2.3, 5.0):
+            h = context(LLAMA, weights=True)
+            fake.fake_budget(fake.fake_used() + int(room * layer))
+            launches()
+            for again in range(2):
+                rc = lib.proxykv_map(h, P, n, P, None)
+                out[f"{room} {again}"] = [rc, [l[2] for l in launches("stage3_kernel")]]
+            fake.fake_budget((1 << 63) - 1)
+        # score in fp32 after the mapper: its bf16 copies fit only if the mapper gives way
+        h = context(LLAMA, weights=True)
+        assert lib.proxykv_map(h, P, n, P, None) == 0
+        fake.fake_budget(fake.fake_used() + layer)
+        out["score"] = lib.proxykv_score(h, P, P, P, 1, n, n, 2048, P, None)
+        launches()
+        out["map"] = lib.proxykv_map(h, P, n, P, None)
+        out["layers"] = [l[2] for l in launches("stage3_kernel")]
+    """)
+    assert out["0.9 0"][0] == out["0.9 1"][0] == -3  # PROXYKV_ENOMEM
+    for room, most in (("1.1", 1), ("2.3", 1), ("5.0", 2)):
+        for again in "01":
+            rc, layers = out[f"{room} {again}"]
+            assert rc == 0 and sum(layers) == 16 and max(layers) == most, (room, again, layers)
+    assert out["score"] == out["map"] == 0 and sum(out["layers"]) == 16
+
+
+def test_no_call_allocates_after_a_longer_one():
+    """A context that has served a call (or proxykv_reserve) serves every shorter one from the same memory, so that it can be captured:
+    whatever the plan of the shorter one would rather have, all layers are covered and nothing is allocated."""
+    out = run("""
+        out = []
+        lengths = [5, 200, 700, 1024, 1500, 2048, 2049, 3000, 4097, 4608, 5000, 8192, 11500, 16384, 30000]
+        for shape in (LLAMA, QWEN, QWEN32B, (33, 4, 2, 64, 33, 4, 128), (3, 4, 2, 64, 3, 4, 128)):
+            for longest in lengths[5::3]:
+                for reserved in (False, True):
+                    h = context(shape, weights=True)
+                    if reserved:
+                        assert lib.proxykv_reserve(h, longest, longest) == 0
+                    calls = 0
+                    for n in [longest] + [n for n in lengths if n < longest]:
+                        launches()
+                        before = fake.fake_mallocs()
+                        rc = [lib.proxykv_map(h, P, n, P, None), lib.proxykv_score(h, P, P, P, 0, n, n, 512, P, None),
+                              lib.proxykv_score_self(h, P, P, 0, n, P, None)]
+                        layers = sum(l[2] for l in launches("stage3_kernel"))
+                        if n < longest or reserved:
+                            out.append((rc, layers == shape[0], fake.fake_mallocs() - before, shape, longest, n))
+    """)
+    assert len(out) > 200
+    for rc, covered, mallocs, shape, longest, n in out:
+        assert rc == [0, 0, 0] and covered and mallocs == 0, (shape, longest, n, mallocs)
