@@ -167,3 +167,17 @@ def test_no_call_allocates_after_a_longer_one():
     assert len(out) > 200
     for rc, covered, mallocs, shape, longest, n in out:
         assert rc == [0, 0, 0] and covered and mallocs == 0, (shape, longest, n, mallocs)
+
+
+def test_mapper_deals_few_layers_to_both_lanes():
+    """More rows than fill the chip in one turn go to two streams also where one batch could hold all layers: three layers of 3000
+    tokens one behind the other took longer than side by side.  Short ones stay in one batch."""
+    out = run("""
+        out = {}
+        for layers, n in ((3, 3000), (4, 4500), (16, 1500), (5, 9000), (2, 1500), (16, 250), (1, 30000)):
+            h = context((layers, 4, 2, 64, layers, 4, 128), weights=True)
+            assert lib.proxykv_map(h, P, n, P, None) == 0
+            out[f"{layers} {n}"] = [l[2] for l in launches("stage3_kernel")]
+    """)
+    assert out == {"3 3000": [1, 2], "4 4500": [2, 2], "16 1500": [8, 8], "5 9000": [2, 3], "2 1500": [2], "16 250": [16],
+                   "1 30000": [1]}
