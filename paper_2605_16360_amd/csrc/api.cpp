@@ -206,14 +206,35 @@ Sizes workspace_sizes(const proxykv_config& c, int64_t N, int64_t N_q) {
 int reserve_score(proxykv_ctx* ctx, int64_t N, int64_t N_q, bool parts, hipStream_t stream) {
   const Sizes s = workspace_sizes(ctx->cfg, N, N_q);
   int rc = ensure(ctx, ctx->neg_lse, s.neg_lse, stream);
-  if (rc == PROXYKV_OK && parts) rc = ensure(ctx, ctx->x_parts, s.x_parts, stream);
+  if (rc == PROXYKV_OK && parts && (ctx->parts_short == 0 || s.x_parts < ctx->parts_short)) {
+    rc = ensure(ctx, ctx->x_parts, s.x_parts, stream);
+    if (rc == PROXYKV_ENOMEM) {  // then one workgroup per key block
+      ctx->parts_short = s.x_parts;
+      rc = PROXYKV_OK;
+    }
+  }
+  return rc;
+}
+// workgroups per key block that pass 2 may use
+int query_splits(const proxykv_ctx* ctx, bool sum, bool causal, int64_t N, int64_t N_q) {
+  const proxykv_config& c = ctx->cfg;
+  const int s = pkv::score_query_splits(sum, causal, c.L_s, c.H_q, c.H_kv, c.d, N, N_q);
+  return sum && ctx->x_parts.bytes < (size_t)s * c.L_s * c.H_kv * (size_t)N * 4 ? 1 : s;
+}
+// where the wide histograms do not fit, the narrow ones
+int reserve_topk(proxykv_ctx* ctx, int64_t rows, int64_t N, hipStream_t stream) {
+  const size_t least = pkv::topk_scratch_bytes_least(rows, N);
+  if (ctx->topk_short && ctx->topk_ws.bytes >= least) return PROXYKV_OK;
+  int rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes(rows, N), stream);
+  ctx->topk_short = rc == PROXYKV_ENOMEM;
+  if (ctx->topk_short) rc = ensure(ctx, ctx->topk_ws, least, stream);
   return rc;
 }
 int reserve_prune(proxykv_ctx* ctx, int64_t N, hipStream_t stream) {
   const Sizes s = workspace_sizes(ctx->cfg, N, 1);
   int rc = ensure(ctx, ctx->x_ws, s.x_ws, stream);
   if (rc == PROXYKV_OK) rc = ensure(ctx, ctx->yhat_ws, s.yhat_ws, stream);
-  if (rc == PROXYKV_OK) rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes((int64_t)ctx->cfg.L_l * ctx->cfg.H_l, N), stream);
+  if (rc == PROXYKV_OK) rc = reserve_topk(ctx, (int64_t)ctx->cfg.L_l * ctx->cfg.H_l, N, stream);
   return rc;
 }
 
@@ -288,7 +309,7 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q);
-  const int q_splits = pkv::score_query_splits(sum, false, c.L_s, c.H_q, c.H_kv, c.d, N, N_q);
+  const int q_splits = query_splits(ctx, sum, false, N, N_q);
   const int64_t n_clear = !sum && (splits > 1 || q_splits > 1) ? (int64_t)c.L_s * c.H_kv * N : 0;
   PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, splits, x_out, n_clear, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
@@ -323,7 +344,7 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
   int rcm;
   if ((rcm = mark(ctx, 0, stream))) return rcm;
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N);
-  const int q_splits = pkv::score_query_splits(true, true, c.L_s, c.H_q, c.H_kv, c.d, N, N);
+  const int q_splits = query_splits(ctx, true, true, N, N);
   PKV_HIP(ctx, pkv::launch_score_lse(q, k, k, nl, splits, x_out, 0, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
   PKV_HIP(ctx, pkv::launch_score_colsum(q, k, nl, splits, x_out, (float*)ctx->x_parts.ptr, q_splits, c.L_s, c.H_q, c.H_kv, c.d, N, N, true, stream));
@@ -620,7 +641,7 @@ int proxykv_topk(proxykv_ctx* ctx, const float* scores, int64_t rows, int64_t N,
   if (rows <= 0 || rows >= (1ll << 31) || N <= 0 || N >= (1ll << 31) - 4096 || K < 1 || K > N) return PROXYKV_EINVAL;
   if (N > pkv::kTopkSingleMax && rows > 65535) return PROXYKV_EUNSUPPORTED;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  const int rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes(rows, N), (hipStream_t)stream);
+  const int rc = reserve_topk(ctx, rows, N, (hipStream_t)stream);
   if (rc) return rc;
   PKV_HIP(ctx, pkv::launch_topk(scores, rows, N, K, idx_out, ctx->topk_ws.ptr, ctx->topk_ws.bytes, (hipStream_t)stream));
   return PROXYKV_OK;
@@ -653,7 +674,7 @@ int proxykv_topk_pooled(proxykv_ctx* ctx, const float* scores, int64_t layers, i
   if (layers * heads >= (1ll << 31) || heads * N >= (1ll << 31) - 4096) return PROXYKV_EINVAL;
   if (heads * N > pkv::kTopkSingleMax && layers > 65535) return PROXYKV_EUNSUPPORTED;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  const int rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes(layers, heads * N), (hipStream_t)stream);
+  const int rc = reserve_topk(ctx, layers, heads * N, (hipStream_t)stream);
   if (rc) return rc;
   PKV_HIP(ctx, pkv::launch_topk(scores, layers, heads * N, heads * K, flat_out, ctx->topk_ws.ptr, ctx->topk_ws.bytes, (hipStream_t)stream));
   PKV_HIP(ctx, pkv::launch_head_counts(flat_out, layers, heads, N, K, counts_out, (hipStream_t)stream));

@@ -78,9 +78,11 @@ struct proxykv_ctx {
   pkv::DeviceBuffer q_bf16, kctx_bf16, krec_bf16;  // bf16 copies of fp32 inputs
   pkv::DeviceBuffer neg_lse;                       // fp32 [L_s, H_q, N_q], or (reference, sum) pairs of several workgroups
   pkv::DeviceBuffer x_parts;                       // sum form: the column sums of several workgroups per key block
+  size_t parts_short = 0;                          // bytes of x_parts that the device did not have
   pkv::DeviceBuffer x_ws;                          // fp32 [L_s, H_kv, N]
   pkv::DeviceBuffer yhat_ws;                       // fp32 [L_l, H_l, N]
   pkv::DeviceBuffer topk_ws;                       // per-row histograms and counters of the Top-K of rows split over workgroups
+  bool topk_short = false;                         // memory was short: topk_ws holds the narrower histograms
   bool fused_select = false;                       // proxykv_prune: selection and gather in one launch (measured slower)
   pkv::MapperWorkspace m[pkv::kMapLanes];          // one per lane; only the lanes a length needs are allocated
   int64_t map_len = 0;                             // longest context that m has been sized for

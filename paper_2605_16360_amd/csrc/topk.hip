@@ -541,7 +541,12 @@ static size_t topk_scratch(int64_t rows, int64_t N) {
   if (N <= kTopkRegMax || rows <= 0) return 0;
   return (size_t)rows * (size_t)(Mw<BITS>::kFixedWords + (size_t)topk_parts<BITS>(rows, N) * Mw<BITS>::kPartWords) * 4;
 }
-size_t topk_scratch_bytes(int64_t rows, int64_t N) { return topk_scratch<11>(rows, N); }
+// (the parts of up to `rows` rows of up to N scores: 512, or as few as each row can have)
+size_t topk_scratch_bytes(int64_t rows, int64_t N) {
+  if (N <= kTopkRegMax || rows <= 0) return 0;
+  const size_t least = (size_t)rows * (size_t)((N + kMwPartMax - 1) / kMwPartMax), parts = least > 512 ? least : 512;
+  return ((size_t)rows * Mw<11>::kFixedWords + parts * Mw<11>::kPartWords) * 4;
+}
 size_t topk_scratch_bytes_least(int64_t rows, int64_t N) { return topk_scratch<8>(rows, N); }
 
 template <int BITS>

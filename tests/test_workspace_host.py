@@ -181,3 +181,40 @@ def test_mapper_deals_few_layers_to_both_lanes():
     """)
     assert out == {"3 3000": [1, 2], "4 4500": [2, 2], "16 1500": [8, 8], "5 9000": [2, 3], "2 1500": [2], "16 250": [16],
                    "1 30000": [1]}
+
+
+def test_topk_and_column_sums_make_do_with_less_memory():
+    """The wide histograms of long rows take five times the memory of the narrow ones, the column sums of several workgroups per key block
+    take some where there were none: both are done without where they do not fit, on the next call too, and no call of
+    fewer or shorter rows than one before it allocates."""
+    out = run("""
+        out = {}
+        h = context(LLAMA)
+        rows, n = 1000, 170000
+        fake.fake_budget(fake.fake_used() + 10 * 1000 * 1000)  # narrow 8.3 MB, wide 41 MB
+        out["topk"] = [[lib.proxykv_topk(h, P, rows, n, 1000, P, None), sorted({l[0] for l in launches("mw_pass_kernel")})] for _ in range(2)]
+        h = context(QWEN, reduce=1)
+        fake.fake_budget(fake.fake_used() + 20 * 1000 * 1000)  # row sums 8 MB, column sums 19 MB
+        out["sum"] = []
+        for _ in range(2):
+            launches()
+            before = fake.fake_mallocs()
+            rc = lib.proxykv_score(h, P, P, P, 0, 6001, 6001, 2048, P, None)
+            out["sum"].append([rc, len(launches("sum_parts_kernel")), fake.fake_mallocs() - before])
+        fake.fake_budget((1 << 63) - 1)
+        h = context(QWEN, reduce=1)
+        assert lib.proxykv_score(h, P, P, P, 0, 6001, 6001, 2048, P, None) == 0
+        out["parts"] = len(launches("sum_parts_kernel"))
+        out["mallocs"] = []
+        for big, small in (((257, 45000), (256, 45000)), ((600, 60000), (100, 50000)), ((5, 300000), (1, 299999)), ((112, 170000), (40, 80000))):
+            h = context(LLAMA)
+            assert lib.proxykv_topk(h, P, big[0], big[1], 9, P, None) == 0
+            before = fake.fake_mallocs()
+            assert lib.proxykv_topk(h, P, small[0], small[1], 9, P, None) == 0
+            assert lib.proxykv_topk_pooled(h, P, small[0], 1, small[1], 9, P, P, None) == 0
+            out["mallocs"].append(fake.fake_mallocs() - before)
+    """)
+    for rc, kernels in out["topk"]:
+        assert rc == 0 and len(kernels) == 4 and all("ILi8E" in k for k in kernels)
+    assert out["sum"][0][:2] == [0, 0] and out["sum"][1] == [0, 0, 0]
+    assert out["parts"] == 1 and out["mallocs"] == [0, 0, 0, 0]
