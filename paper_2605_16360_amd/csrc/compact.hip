@@ -10,6 +10,7 @@ namespace pkv {
 namespace {
 
 constexpr int kUnroll = 2;
+constexpr int64_t kMaxThreads = 0xffffffff;  // per dimension of a launch
 
 // grid (ceil(K / rows_per_block), rows); cpr = 16-byte chunks per token row.
 __global__ __launch_bounds__(256) void compact_kernel(const u32x4* __restrict__ k_in, const u32x4* __restrict__ v_in,
@@ -127,33 +128,35 @@ __global__ __launch_bounds__(1024) void mask_kernel(const int32_t* __restrict__ 
 // counts[layer, h] = number of a layer's kept flat indices (ascending, heads * K of them) that fall into
 // [h * N, (h + 1) * N): the difference of two lower bounds.  One wave per (layer, head); every step of a search probes 64
 // places at once, so that the two searches are three or four trips to memory instead of 34 (9.9 us with one thread each).
-__global__ __launch_bounds__(64) void head_counts_kernel(const int32_t* __restrict__ flat, int heads, int64_t N, int K,
+__global__ __launch_bounds__(64) void head_counts_kernel(const int32_t* __restrict__ flat, int64_t pairs, int heads, int64_t N, int K,
                                                          int32_t* __restrict__ counts) {
-  const int t = blockIdx.x, layer = t / heads, h = t % heads, n = heads * K, lane = threadIdx.x;
-  const int32_t* row = flat + (size_t)layer * n;
-  int lo[2] = {0, 0}, hi[2] = {n, n};  // the first position whose index is >= (h + e) * N lies in [lo[e], hi[e]]
-  while (lo[0] < hi[0] || lo[1] < hi[1]) {
-    bool less[2];
-    int step[2];
+  for (int64_t t = blockIdx.x; t < pairs; t += gridDim.x) {
+    const int h = (int)(t % heads), n = heads * K, lane = threadIdx.x;
+    const int32_t* row = flat + (size_t)(t / heads) * n;
+    int lo[2] = {0, 0}, hi[2] = {n, n};  // the first position whose index is >= (h + e) * N lies in [lo[e], hi[e]]
+    while (lo[0] < hi[0] || lo[1] < hi[1]) {
+      bool less[2];
+      int step[2];
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      step[e] = (hi[e] - lo[e] + 63) / 64;
-      const int64_t at = lo[e] + (int64_t)lane * step[e];
-      less[e] = at < hi[e] && (int64_t)row[at] < (int64_t)(h + e) * N;
-    }
+      for (int e = 0; e < 2; ++e) {
+        step[e] = (hi[e] - lo[e] + 63) / 64;
+        const int64_t at = lo[e] + (int64_t)lane * step[e];
+        less[e] = at < hi[e] && (int64_t)row[at] < (int64_t)(h + e) * N;
+      }
 #pragma unroll
-    for (int e = 0; e < 2; ++e) {
-      const int below = __popcll(__builtin_amdgcn_ballot_w64(less[e]));  // the probes are in order: the first `below` are less
-      if (below == 0) {
-        hi[e] = lo[e];
-      } else {
-        const int64_t top = lo[e] + (int64_t)below * step[e];
-        hi[e] = top < hi[e] ? (int)top : hi[e];
-        lo[e] += (below - 1) * step[e] + 1;
+      for (int e = 0; e < 2; ++e) {
+        const int below = __popcll(__builtin_amdgcn_ballot_w64(less[e]));  // the probes are in order: the first `below` are less
+        if (below == 0) {
+          hi[e] = lo[e];
+        } else {
+          const int64_t top = lo[e] + (int64_t)below * step[e];
+          hi[e] = top < hi[e] ? (int)top : hi[e];
+          lo[e] += (below - 1) * step[e] + 1;
+        }
       }
     }
+    if (lane == 0) counts[t] = lo[1] - lo[0];
   }
-  if (lane == 0) counts[t] = lo[1] - lo[0];
 }
 
 }  // namespace
@@ -187,13 +190,14 @@ hipError_t launch_head_counts(const int32_t* flat, int64_t layers, int64_t heads
                               hipStream_t stream) {
   const int64_t n = layers * heads;
   if (n <= 0) return hipSuccess;
-  head_counts_kernel<<<(unsigned)n, 64, 0, stream>>>(flat, (int)heads, N, (int)K, counts);
+  const int64_t most = kMaxThreads / 64;
+  head_counts_kernel<<<(unsigned)(n < most ? n : most), 64, 0, stream>>>(flat, n, (int)heads, N, (int)K, counts);
   return hipGetLastError();
 }
 
 hipError_t launch_mask(const int32_t* idx, int64_t rows, int64_t N, int64_t K, uint8_t* mask, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
-  mask_kernel<<<(unsigned)rows, N >= 8192 ? 1024 : 256, 0, stream>>>(idx, N, (int)K, mask);
+  mask_kernel<<<(unsigned)rows, N >= 8192 && rows <= kMaxThreads / 1024 ? 1024 : 256, 0, stream>>>(idx, N, (int)K, mask);
   return hipGetLastError();
 }
 

@@ -73,7 +73,6 @@ int hipDeviceGetAttribute(int* v, int, int) {
   return kSuccess;
 }
 int hipDeviceSynchronize() { return kSuccess; }
-int hipGetLastError() { return kSuccess; }
 int hipStreamSynchronize(void*) { return kSuccess; }
 int hipStreamCreateWithFlags(void** s, unsigned) {
   static uintptr_t next = 16;
@@ -116,13 +115,18 @@ int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** strea
   return kSuccess;
 }
 static int g_launch_error = 0;
+int hipGetLastError() {
+  const int e = g_launch_error;
+  g_launch_error = kSuccess;
+  return e;
+}
 int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t, void*) {
   char line[512];
   const bool bad = grid.x == 0 || grid.y == 0 || grid.z == 0 || grid.y > 65535 || grid.z > 65535 || block.x > 1024 ||
                    (uint64_t)grid.x * block.x > 0xffffffffu;  // the runtime counts work-items per dimension in 32 bits
   snprintf(line, sizeof line, "%s%s %u %u %u %u\n", bad ? "REFUSED " : "", names()[f].c_str(), grid.x, grid.y, grid.z, block.x);
   g_log += line;
-  g_launch_error = bad ? kInvalidConfiguration : kSuccess;
-  return g_launch_error;
+  if (bad) g_launch_error = kInvalidConfiguration;
+  return bad ? kInvalidConfiguration : kSuccess;
 }
 }

@@ -139,6 +139,17 @@ def test_compact_inplace_and_mask_bit_exact():
         assert torch.equal(m.cpu(), oracle.mask(idx, N)), (N, K)
 
 
+def test_pooled_counts_of_more_heads_than_a_launch_has_waves():
+    """72 million (layer, head) pairs of one token each: every pair keeps its token, and the waves that count take several pairs."""
+    layers, heads = 2000, 36000
+    ctx = _ctx(synth.CASES["tiny"])
+    flat, counts = pk.proxykv_topk_pooled(ctx, torch.zeros(layers, heads, 1, device="cuda"), 1)
+    torch.cuda.synchronize()
+    assert bool((counts == 1).all())
+    assert bool((flat == torch.arange(heads, device="cuda", dtype=torch.int32)).all())
+    pk.proxykv_destroy(ctx)
+
+
 def test_pooled_budget_bit_exact():
     """One budget per layer shared by its heads: kept flat indices, per-head counts, and the ragged in-place
     compaction, against the oracle.  Covers short rows (register-resident selection) and long ones, heads that

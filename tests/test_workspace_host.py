@@ -218,3 +218,18 @@ def test_topk_and_column_sums_make_do_with_less_memory():
         assert rc == 0 and len(kernels) == 4 and all("ILi8E" in k for k in kernels)
     assert out["sum"][0][:2] == [0, 0] and out["sum"][1] == [0, 0, 0]
     assert out["parts"] == 1 and out["mallocs"] == [0, 0, 0, 0]
+
+
+def test_launches_of_many_rows_stay_within_the_runtime():
+    """A launch counts its threads per dimension in 32 bits: more rows than 1024 threads each allow are marked with fewer, and more
+    (layer, head) pairs than a wave each allows are counted by waves that take several."""
+    out = run("""
+        out = {}
+        h = context(LLAMA)
+        out["mask"] = [lib.proxykv_mask(h, P, 5 * 1000 * 1000, 8192, 1, P, None), launches("mask_kernel")]
+        out["pooled"] = [lib.proxykv_topk_pooled(h, P, 2000, 36000, 1, 1, P, P, None), launches("head_counts_kernel")]
+        out["few"] = [lib.proxykv_topk_pooled(h, P, 3, 5, 100, 10, P, P, None), launches("head_counts_kernel")[0][1]]
+    """)
+    assert out["mask"][0] == 0 and out["mask"][1][0][1:] == [5000000, 1, 1, 256]
+    assert out["pooled"][0] == 0 and out["pooled"][1][0][1] * 64 <= 0xffffffff
+    assert out["few"] == [0, 15]
