@@ -52,11 +52,11 @@ __global__ __launch_bounds__(256) void compact_kernel(const u32x4* __restrict__ 
 // of 128 in order: the loads of chunk c+1 are issued, a barrier makes sure every thread holds chunk
 // c, then chunk c is stored.  Chunk c+1 reads tokens at or behind (c+1)*128, which chunk c's stores
 // (tokens below (c+1)*128) cannot touch, so the two overlap safely.  K and V, and the 128-byte parts of a token, are
-// independent of each other, so each gets a workgroup of its own: what bounds this kernel is the bytes in flight (512 rows
-// of 12 345 tokens of 256 bytes, half kept, 3.2 GB moved: 953 us with one workgroup per row, 790 us with four).
+// independent of each other, so each gets a workgroup of its own: what bounds this kernel is the bytes in flight (tokens of
+// 256 bytes, half kept: 32 rows of 12 000 with one workgroup per row 264 us, so 56; 600 rows 814 and 778).
 // grid (rows, 2 * slices), 256 threads; cpr = 16-byte chunks per token, cps = those of a slice (<= 32).
 // ---------------------------------------------------------------------------------------------
-constexpr int kInplaceTokens = 128;
+constexpr int kInplaceTokens = 128, kNoToken = 1 << 30;
 
 // With counts != nullptr the rows are ragged (a budget shared by the `heads` rows of a layer): idx holds,
 // per layer, heads * K flat indices h * N + n in ascending order, row r = (layer, h) keeps counts[r] of
@@ -74,6 +74,7 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(u32x4* __restrict_
     for (int hh = 0; hh < h; ++hh) start += counts[layer * heads + hh];
     ridx = idx + (size_t)layer * heads * K + start;
     K = counts[r];
+    if (K <= 0) return;
     sub = (int32_t)(h * N);
   }
   u32x4* base = ((blockIdx.y & 1) ? v : k) + (size_t)r * N * cpr + (blockIdx.y >> 1) * cps;
@@ -82,47 +83,63 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(u32x4* __restrict_
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
     const int piece = tid + 256 * u;
-    tok[u] = piece < kInplaceTokens * cps ? piece / cps : 1 << 30;
+    tok[u] = piece < kInplaceTokens * cps ? piece / cps : kNoToken;
     ch[u] = piece % cps;
   }
-  u32x4 now[PER], next[PER];
-  auto load = [&](int c, u32x4 (&x)[PER]) {
-#pragma unroll
-    for (int u = 0; u < PER; ++u)
-      if (tok[u] < K - c * kInplaceTokens)
-        x[u] = __builtin_nontemporal_load(base + (size_t)(ridx[c * kInplaceTokens + tok[u]] - sub) * cpr + ch[u]);
-  };
-  load(0, now);
-  for (int c = 0; c < n_chunks; ++c) {
-    if (c + 1 < n_chunks) load(c + 1, next);
-    // every thread holds its part of chunk c (and of every chunk before it) before any of chunk c is stored
-    __syncthreads();
+  // A piece without a token reads the last kept one and stores nothing.  There is no branch around a load, and indices are asked
+  // for a chunk ahead of the pieces they lead to: with a branch and its index in front of every piece, a thread has one
+  // piece in flight instead of two chunks of them (600 rows of 12 000 tokens of 256 bytes, half kept: 889 us, so 778).
+  auto load_idx = [&](int c, int32_t (&at)[PER]) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      if (tok[u] < K - c * kInplaceTokens) base[(size_t)(c * kInplaceTokens + tok[u]) * cpr + ch[u]] = now[u];
-      now[u] = next[u];
+      const int left = K - 1 - c * kInplaceTokens;
+      at[u] = ridx[c * kInplaceTokens + (tok[u] < left ? tok[u] : left)];
     }
+  };
+  auto load = [&](const int32_t (&at)[PER], u32x4 (&x)[PER]) {
+#pragma unroll
+    for (int u = 0; u < PER; ++u) x[u] = __builtin_nontemporal_load(base + (size_t)(at[u] - sub) * cpr + ch[u]);
+  };
+  // x holds chunk c and a the indices of chunk c + 1; y takes that chunk and b the indices of the one behind it
+  auto step = [&](int c, u32x4 (&x)[PER], u32x4 (&y)[PER], int32_t (&a)[PER], int32_t (&b)[PER]) {
+    load_idx(c + 2, b);
+    if (c + 1 < n_chunks) load(a, y);
+    // every thread has asked for its part of chunk c (and of every chunk before it) before any of chunk c is stored
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+      if (tok[u] < K - c * kInplaceTokens) base[(size_t)(c * kInplaceTokens + tok[u]) * cpr + ch[u]] = x[u];
+  };
+  int32_t a0[PER], a1[PER];
+  u32x4 x0[PER], x1[PER];
+  load_idx(0, a0);
+  load_idx(1, a1);
+  load(a0, x0);
+  for (int c = 0; c < n_chunks; c += 2) {  // (two steps by name: moving x1 to x0 would wait for it)
+    step(c, x0, x1, a1, a0);
+    if (c + 1 < n_chunks) step(c + 1, x1, x0, a0, a1);
   }
 }
 
 // mask[r, n] = 1 for the kept tokens of row r, 0 elsewhere (uint8).  One workgroup per row clears the row,
 // then sets the kept positions: 1024 threads for rows that keep them busy (256 rows of 32 768: 9.2 us with 256, 5.4 us with
 // 1024; 512 rows of 3000: 1.9 and 3.1 us).
-__global__ __launch_bounds__(1024) void mask_kernel(const int32_t* __restrict__ idx, int64_t N, int K,
-                                                    uint8_t* __restrict__ mask) {
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void mask_kernel(const int32_t* __restrict__ idx, int64_t N, int K,
+                                                       uint8_t* __restrict__ mask) {
   const int r = blockIdx.x, tid = threadIdx.x;
   uint8_t* row = mask + (size_t)r * N;
   // 16-byte stores over the aligned middle, bytes at the ragged ends
   const uintptr_t addr = reinterpret_cast<uintptr_t>(row);
   const int64_t head = (int64_t)((16 - (addr & 15)) & 15) < N ? (int64_t)((16 - (addr & 15)) & 15) : N;
   const int64_t n16 = (N - head) / 16;
-  for (int64_t i = tid; i < head; i += blockDim.x) row[i] = 0;
+  for (int64_t i = tid; i < head; i += THREADS) row[i] = 0;
   u32x4* mid = reinterpret_cast<u32x4*>(row + head);
-  for (int64_t i = tid; i < n16; i += blockDim.x) mid[i] = u32x4{0, 0, 0, 0};
-  for (int64_t i = head + n16 * 16 + tid; i < N; i += blockDim.x) row[i] = 0;
+  for (int64_t i = tid; i < n16; i += THREADS) mid[i] = u32x4{0, 0, 0, 0};
+  for (int64_t i = head + n16 * 16 + tid; i < N; i += THREADS) row[i] = 0;
   __syncthreads();  // workgroup-scope release/acquire: the zeros are in place before the ones
   const int32_t* ridx = idx + (size_t)r * K;
-  for (int j = tid; j < K; j += blockDim.x) row[ridx[j]] = 1;
+  for (int j = tid; j < K; j += THREADS) row[ridx[j]] = 1;
 }
 
 // counts[layer, h] = number of a layer's kept flat indices (ascending, heads * K of them) that fall into
@@ -180,8 +197,12 @@ hipError_t launch_compact_inplace(void* k, void* v, const int32_t* idx, int64_t 
   const int per = (kInplaceTokens * cps + 255) / 256;                 // 16-byte pieces per thread and chunk
   u32x4 *kp = (u32x4*)k, *vp = (u32x4*)v;
   const dim3 grid((unsigned)rows, (unsigned)(2 * slices));
-  if (per <= 4) compact_inplace_kernel<4><<<grid, 256, 0, stream>>>(kp, vp, idx, N, (int)K, cpr, cps, counts, heads);
-  else if (per <= 16) compact_inplace_kernel<16><<<grid, 256, 0, stream>>>(kp, vp, idx, N, (int)K, cpr, cps, counts, heads);
+  auto go = [&](auto p) { compact_inplace_kernel<decltype(p)::value><<<grid, 256, 0, stream>>>(kp, vp, idx, N, (int)K, cpr, cps, counts, heads); };
+  if (per <= 1) go(std::integral_constant<int, 1>{});
+  else if (per <= 2) go(std::integral_constant<int, 2>{});
+  else if (per <= 4) go(std::integral_constant<int, 4>{});
+  else if (per <= 8) go(std::integral_constant<int, 8>{});
+  else if (per <= 16) go(std::integral_constant<int, 16>{});
   else return hipErrorInvalidValue;
   return hipGetLastError();
 }
@@ -197,7 +218,8 @@ hipError_t launch_head_counts(const int32_t* flat, int64_t layers, int64_t heads
 
 hipError_t launch_mask(const int32_t* idx, int64_t rows, int64_t N, int64_t K, uint8_t* mask, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
-  mask_kernel<<<(unsigned)rows, N >= 8192 && rows <= kMaxThreads / 1024 ? 1024 : 256, 0, stream>>>(idx, N, (int)K, mask);
+  if (N >= 8192 && rows <= kMaxThreads / 1024) mask_kernel<1024><<<(unsigned)rows, 1024, 0, stream>>>(idx, N, (int)K, mask);
+  else mask_kernel<256><<<(unsigned)rows, 256, 0, stream>>>(idx, N, (int)K, mask);
   return hipGetLastError();
 }
 

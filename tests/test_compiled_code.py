@@ -58,3 +58,15 @@ def test_scoring_masks_do_not_branch_per_element():
     assert len(passes) == 4
     for name, body in passes:
         assert len(re.findall(r"^\s+s_cbranch", body, re.M)) < 128, name
+
+
+def test_in_place_compaction_keeps_its_loads_in_flight():
+    """A thread asks for all pieces of a chunk back to back, behind indices that it asked for a chunk earlier.  With an index and a
+    branch in front of every piece the compiler waits for all loads before each of them."""
+    moves = [(name, body) for name, body in kernels("compact.hip") if "compact_inplace_kernel" in name]
+    assert len(moves) == 5
+    for name, body in moves:
+        ops = re.findall(r"^\s+(s_barrier|s_waitcnt\b.*|global_load_dwordx4)", body, re.M)
+        loop = ops[next(i for i, op in enumerate(ops) if op.startswith("s_barrier")):]
+        loads = [i for i, op in enumerate(loop) if op.startswith("global_load_dwordx4")]
+        assert loads and not any("vmcnt(0)" in loop[i - 1] for i in loads), name
