@@ -104,7 +104,10 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(u32x4* __restrict_
   auto step = [&](int c, u32x4 (&x)[PER], u32x4 (&y)[PER], int32_t (&a)[PER], int32_t (&b)[PER]) {
     load_idx(c + 2, b);
     if (c + 1 < n_chunks) load(a, y);
-    // every thread has asked for its part of chunk c (and of every chunk before it) before any of chunk c is stored
+    // Every thread holds its part of chunk c (and of every chunk before it) before any of chunk c is stored: the barrier alone does
+    // not wait for loads under way, so each thread's must have arrived in front of it (no slower: they are stored next).
+#pragma unroll
+    for (int u = 0; u < PER; ++u) asm volatile("" : "+v"(x[u]));
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < PER; ++u)

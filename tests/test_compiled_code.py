@@ -70,3 +70,24 @@ def test_in_place_compaction_keeps_its_loads_in_flight():
         loop = ops[next(i for i, op in enumerate(ops) if op.startswith("s_barrier")):]
         loads = [i for i, op in enumerate(loop) if op.startswith("global_load_dwordx4")]
         assert loads and not any("vmcnt(0)" in loop[i - 1] for i in loads), name
+
+
+def test_in_place_compaction_holds_a_chunk_before_it_stores_one():
+    """A token's new place may be another's old one, so a thread's loads of a chunk have to be over before any thread of the workgroup
+    stores that chunk.  The barrier between does not wait for loads: a wait that leaves at most the next chunk's loads and
+    the indices behind them stands in front of it, and none of the stored registers is waited for behind it."""
+    for name, body in kernels("compact.hip"):
+        if "compact_inplace_kernel" not in name:
+            continue
+        per = int(re.search(r"compact_inplace_kernelILi(\d+)E", name)[1])
+        ops = re.findall(r"^\s+(s_barrier|s_waitcnt\b.*|global_\w+)", body, re.M)
+        for i in [i for i, op in enumerate(ops) if op.startswith("s_barrier")]:
+            waits = []
+            for op in ops[i - 1::-1]:
+                if op.startswith("global_load") or op.startswith("s_barrier"):
+                    break
+                waits += [int(n) for n in re.findall(r"vmcnt\((\d+)\)", op)]
+            assert waits and min(waits) <= 2 * per, (name, ops[max(0, i - 8):i + 1])
+            behind = ops[i + 1:i + 2 + 2 * per]
+            stores = [j for j, op in enumerate(behind) if op.startswith("global_store")]
+            assert not stores or not any("vmcnt" in op for op in behind[:stores[0]]), (name, behind)
