@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(u32x4* __restrict_
     sub = (int32_t)(h * N);
   }
   u32x4* base = ((blockIdx.y & 1) ? v : k) + (size_t)r * N * cpr + (blockIdx.y >> 1) * cps;
-  const int n_chunks = (K + kInplaceTokens - 1) / kInplaceTokens;
+  const int whole = K / kInplaceTokens, tail0 = whole * kInplaceTokens;  // whole chunks; the first token of the cut one behind them
   int tok[PER], ch[PER];  // token within a chunk of tokens, and 16-byte chunk of it, of this thread's pieces
 #pragma unroll
   for (int u = 0; u < PER; ++u) {
@@ -86,41 +86,62 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(u32x4* __restrict_
     tok[u] = piece < kInplaceTokens * cps ? piece / cps : kNoToken;
     ch[u] = piece % cps;
   }
-  // A piece without a token reads the last kept one and stores nothing.  There is no branch around a load, and indices are asked
-  // for a chunk ahead of the pieces they lead to: with a branch and its index in front of every piece, a thread has one
-  // piece in flight instead of two chunks of them (600 rows of 12 000 tokens of 256 bytes, half kept: 889 us, so 778).
-  auto load_idx = [&](int c, int32_t (&at)[PER]) {
+  auto load_idx = [&](int c, int last, int32_t (&at)[PER]) {  // (positions behind `last` read that one)
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
-      const int left = K - 1 - c * kInplaceTokens;
+      const int left = last - c * kInplaceTokens;
       at[u] = ridx[c * kInplaceTokens + (tok[u] < left ? tok[u] : left)];
     }
   };
-  auto load = [&](const int32_t (&at)[PER], u32x4 (&x)[PER]) {
+  auto store = [&](int c, int n, const u32x4 (&x)[PER]) {
 #pragma unroll
-    for (int u = 0; u < PER; ++u) x[u] = __builtin_nontemporal_load(base + (size_t)(at[u] - sub) * cpr + ch[u]);
+    for (int u = 0; u < PER; ++u)
+      if (tok[u] < n) base[(size_t)(c * kInplaceTokens + tok[u]) * cpr + ch[u]] = x[u];
   };
-  // x holds chunk c and a the indices of chunk c + 1; y takes that chunk and b the indices of the one behind it
-  auto step = [&](int c, u32x4 (&x)[PER], u32x4 (&y)[PER], int32_t (&a)[PER], int32_t (&b)[PER]) {
-    load_idx(c + 2, b);
-    if (c + 1 < n_chunks) load(a, y);
-    // Every thread holds its part of chunk c (and of every chunk before it) before any of chunk c is stored: the barrier alone does
-    // not wait for loads under way, so each thread's must have arrived in front of it (no slower: they are stored next).
+  // Every thread holds its part of a chunk (and of every chunk before it) before any of that chunk is stored: a barrier alone does
+  // not wait for loads under way, so each thread's must have arrived in front of it (no slower: they are stored next).
+  auto meet = [&](u32x4 (&x)[PER]) {
 #pragma unroll
     for (int u = 0; u < PER; ++u) asm volatile("" : "+v"(x[u]));
     __syncthreads();
+  };
+  // the cut chunk: nothing that is stored before it lies in its way, so it is asked for first and stored last
+  u32x4 xt[PER];
+  if (tail0 < K) {
+    int32_t at[PER];
+    load_idx(whole, K - 1, at);
 #pragma unroll
     for (int u = 0; u < PER; ++u)
-      if (tok[u] < K - c * kInplaceTokens) base[(size_t)(c * kInplaceTokens + tok[u]) * cpr + ch[u]] = x[u];
-  };
-  int32_t a0[PER], a1[PER];
-  u32x4 x0[PER], x1[PER];
-  load_idx(0, a0);
-  load_idx(1, a1);
-  load(a0, x0);
-  for (int c = 0; c < n_chunks; c += 2) {  // (two steps by name: moving x1 to x0 would wait for it)
-    step(c, x0, x1, a1, a0);
-    if (c + 1 < n_chunks) step(c + 1, x1, x0, a0, a1);
+      if (tok[u] < K - tail0) xt[u] = __builtin_nontemporal_load(base + (size_t)(at[u] - sub) * cpr + ch[u]);
+  }
+  if (whole > 0) {
+    // A piece without a token reads the last one of its chunks and stores nothing.  There is no branch around a load, and indices are
+    // asked for a chunk ahead of the pieces they lead to: with a branch and its index in front of every piece, a thread has one
+    // piece in flight instead of two chunks of them (600 rows of 12 000 tokens of 256 bytes, half kept: 889 us, so 775).
+    auto load = [&](const int32_t (&at)[PER], u32x4 (&x)[PER]) {
+#pragma unroll
+      for (int u = 0; u < PER; ++u) x[u] = __builtin_nontemporal_load(base + (size_t)(at[u] - sub) * cpr + ch[u]);
+    };
+    // x holds chunk c and a the indices of chunk c + 1; y takes that chunk and b the indices of the one behind it
+    auto step = [&](int c, u32x4 (&x)[PER], u32x4 (&y)[PER], int32_t (&a)[PER], int32_t (&b)[PER]) {
+      load_idx(c + 2, tail0 - 1, b);
+      if (c + 1 < whole) load(a, y);
+      meet(x);
+      store(c, kInplaceTokens, x);
+    };
+    int32_t a0[PER], a1[PER];
+    u32x4 x0[PER], x1[PER];
+    load_idx(0, tail0 - 1, a0);
+    load_idx(1, tail0 - 1, a1);
+    load(a0, x0);
+    for (int c = 0; c < whole; c += 2) {  // (two steps by name: moving x1 to x0 would wait for it)
+      step(c, x0, x1, a1, a0);
+      if (c + 1 < whole) step(c + 1, x1, x0, a0, a1);
+    }
+  }
+  if (tail0 < K) {
+    meet(xt);
+    store(whole, K - tail0, xt);
   }
 }
 
