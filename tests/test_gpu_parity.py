@@ -139,6 +139,26 @@ def test_compact_inplace_and_mask_bit_exact():
         assert torch.equal(m.cpu(), oracle.mask(idx, N)), (N, K)
 
 
+@pytest.mark.parametrize("D", [8, 24, 40, 64, 72, 136, 256])
+def test_compact_inplace_at_the_edges_of_chunks(D):
+    """Kept counts around whole chunks of 128 tokens, every number of 16-byte pieces per thread, tokens with and without 128-byte
+    parts, and kept tokens that each move by a few places only, so that a token's new place is another's old one."""
+    ctx = _ctx(synth.CASES["tiny"])
+    g = torch.Generator().manual_seed(D)
+    for K in (1, 127, 128, 129, 255, 256, 257, 1000):
+        N, rows = K + 5, 3
+        idx = torch.stack([torch.randperm(N, generator=g)[:K].sort().values for _ in range(rows)]).to(torch.int32)
+        kv = torch.randn(2, rows, N, D, generator=g).to(torch.bfloat16)
+        k, v = kv[0].cuda(), kv[1].cuda()
+        pk.proxykv_compact_inplace(ctx, k.view(1, rows, N, D), v.view(1, rows, N, D), idx.view(1, rows, K).cuda())
+        torch.cuda.synchronize()
+        for got, src in ((k, kv[0]), (v, kv[1])):
+            want = src.clone()
+            want[:, :K] = torch.gather(src, 1, idx.long().unsqueeze(2).expand(-1, -1, D))
+            assert torch.equal(got.cpu().view(torch.int16), want.view(torch.int16)), K
+    pk.proxykv_destroy(ctx)
+
+
 def test_pooled_counts_of_more_heads_than_a_launch_has_waves():
     """72 million (layer, head) pairs of one token each: every pair keeps its token, and the waves that count take several pairs."""
     layers, heads = 2000, 36000
