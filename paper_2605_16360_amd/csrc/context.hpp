@@ -121,8 +121,9 @@ inline void window_plan(int64_t N, int win, int stride, int64_t* n_win, int64_t*
 constexpr int64_t kMapBatchRows = 65536, kMapPairRows = 131072, kMapSplitRows = 8192;
 constexpr int kMaxBatch = 32;
 static_assert(kMapBatchRows >= 256 * kMaxBatch && kMapSplitRows >= 256 * kMaxBatch, "a small-tile batch is neither cut nor split");
-// Up to this many rows in a batch the small tiles are faster (large tiles on the left: one layer of 512 rows 867 / 231 us, of 2000
-// rows 1060 / 566 us; 16 layers of 256 rows 970 / 882 us).
+// Up to this many rows in a batch the small tiles are faster (large tiles on the left, us: one layer of 200 rows 824 / 200, of 2000
+// 1061 / 565, of 4024 1084 / 997; two layers of 2000 1078 / 1003; 16 layers of 250 886 / 887), beyond it the large ones (one layer
+// of 6048 rows 1110 / 1435, of 8000 1208 / 1877; 16 layers of 400 1004 / 1467).
 constexpr int64_t kMapSmallRows = 4096;
 struct MapPlan {
   int64_t N, n_win, T;  // tokens, windows and window rows of a layer

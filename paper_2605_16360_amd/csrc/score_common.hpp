@@ -111,8 +111,6 @@ __device__ __forceinline__ float max16_tree(const f32x16& a, float seed) {
 }
 
 constexpr float kNegInf = -__builtin_huge_valf();
-// A lane re-bases its partial sum when a logit exceeds its reference by more than 2^kRescaleGap.
-constexpr float kRescaleGap = 60.0f;
 
 // One workgroup's share of a query's softmax denominator: sum 2^(c * logit - m) over its keys.
 struct LsePart {

@@ -316,9 +316,12 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
 
 constexpr int kLseCols = 2;  // column sub-tiles per wave; 128 * kLseCols queries per workgroup
 
-// Workgroups per query block: as many as fill the chip (three per CU), if the query blocks alone give it less than half of
-// that, with at least one tile each; beyond eight the shares of a query cost pass 2 more than they save.  One layer of 4
+// Workgroups per query block: as many as fill the chip (three per CU at d = 64), if the query blocks alone give it less than half
+// of that, with at least one tile each; beyond eight the shares of a query cost pass 2 more than they save.  One layer of 4
 // heads, 128 queries of 512 keys, both passes 22.7 -> 15.5 us; 2000 queries of 2000 keys 105 -> 31 us; 16 000 of 16 000 644 -> 583.
+// At d = 128 two workgroups per CU are resident; 256 to 383 blocks are shared all the same, since one whole block per place leaves
+// half of the CUs with one and half with two (336 blocks, both passes, whole / shared: 1000 keys 81 / 88 us, 4096 226 / 221,
+// 8192 426 / 409, 16 000 770 / 730).
 int score_splits(int L_s, int H_q, int d, int64_t N, int64_t N_q) {
   const int64_t blocks = (N_q + 128 * kLseCols - 1) / (128 * kLseCols) * H_q * L_s;
   const int64_t tiles = (N + 8192 / d - 1) / (8192 / d) + 1;

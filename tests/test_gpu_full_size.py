@@ -383,7 +383,7 @@ def test_qwen32b_shape_score_two_sided_mid_size():
 
 def test_prune_is_bit_identical_next_to_a_busy_second_stream():
     """The paper's single-GPU regime (Sec. 4.3, App. A): the proxy side shares the device with the target's prefill
-    through streams.  One proxykv_prune (which itself spreads the mapper over up to four streams the context owns) runs
+    through streams.  One proxykv_prune (whose mapper itself runs on the work stream and one more that the context owns) runs
     while a second stream loops large bf16 matrix products; scores, mapped scores, kept indices and the compacted
     cache must equal those of a run on a quiet device bit for bit."""
     case = synth.CASES["llama_8k"]
