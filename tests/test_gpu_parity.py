@@ -547,6 +547,30 @@ def test_mapper_in_the_workspace_of_a_longer_call(L, longest, N):
 # whole path
 # ----------------------------------------------------------------------------------------------
 
+@pytest.mark.parametrize("L,N", [(2, 700), (16, 300), (1, 3100), (3, 2500)])
+def test_mapper_after_scores_that_are_not_finite(L, N):
+    """What a longer call with NaN scores leaves in the workspace, behind a shorter call's last rows, does not reach that call's
+    results, nor do the NaN scores of one proxy layer reach another layer: small tiles, large tiles, one window and several, the
+    last of them cut inside a 64-key tile."""
+    g = torch.Generator().manual_seed(N)
+    cfg = pk.make_config(L, 4, 2, 64, L, 2, 64)
+    w = synth.make_mapper_weights(2, 2)
+    x = torch.rand(L, 2, N, generator=g).cuda()
+    ctx = pk.proxykv_create(cfg)
+    pk.proxykv_set_mapper_weights(ctx, w)
+    want = pk.proxykv_map(ctx, x)
+    assert bool(torch.isfinite(want).all())
+    pk.proxykv_destroy(ctx)
+    ctx = pk.proxykv_create(cfg)
+    pk.proxykv_set_mapper_weights(ctx, w)
+    pk.proxykv_map(ctx, torch.full((L, 2, N + 1200), float("nan"), device="cuda"))
+    assert torch.equal(pk.proxykv_map(ctx, x), want)
+    if L > 1:
+        x[0] = float("nan")
+        assert torch.equal(pk.proxykv_map(ctx, x)[1:], want[1:])
+    pk.proxykv_destroy(ctx)
+
+
 def _band_check(y_ref: torch.Tensor, idx_gpu: torch.Tensor, K: int):
     """Every token whose oracle score clears the K-th score by more than the tolerance is kept, every
     token that misses it by more than the tolerance is dropped; exact equality when the K-th and
