@@ -396,7 +396,7 @@ int proxykv_create(proxykv_ctx** out, const proxykv_config* cfg) {
 
 int proxykv_destroy(proxykv_ctx* ctx) {
   if (!ctx) return PROXYKV_OK;
-  std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
+  std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->block_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
                                     &ctx->neg_lse, &ctx->x_parts, &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws};
   for (pkv::MapperWorkspace& m : ctx->m) {
     DeviceBuffer* b[kLaneBuffers];
@@ -555,6 +555,21 @@ int proxykv_set_mapper_weights(proxykv_ctx* ctx, const float* blob, size_t n_flo
   w.out_w = F32(o_ow);
   w.out_b = out_b;
   w.pe = F32(o_pe);
+  if (c.n_enc_layers > 0) {
+    size_t frags = 0, bias_frags = 0;
+    for (int li = 0; li <= c.n_enc_layers; ++li) {
+      frags += 4 * pkv::block_frags(c, li);
+      bias_frags += 4 * pkv::block_bias_frags(c, li);
+    }
+    const size_t w_bytes = (frags + pkv::kBlkRing) * pkv::kBlkFragBytes;  // the last wave asks for as much beyond its last
+    rc = ensure(ctx, ctx->block_blob, w_bytes + (bias_frags + 2) * pkv::kBlkFragBytes, nullptr);
+    if (rc) return rc;
+    void* bias = (uint8_t*)ctx->block_blob.ptr + w_bytes;
+    PKV_HIP(ctx, pkv::pack_encoder_blocks(c, w, ctx->block_blob.ptr, bias, nullptr));
+    PKV_HIP(ctx, hipStreamSynchronize(nullptr));
+    w.blk_w = ctx->block_blob.ptr;
+    w.blk_b = bias;
+  }
   ctx->weights_set = true;
   return PROXYKV_OK;
 }

@@ -43,7 +43,19 @@ struct MapperWeights {
   const float* out_w;                    // [d_head_x]
   float out_b;
   const float* pe;                       // fp32 [win, d_time] sinusoidal table
+  const void *blk_w = nullptr, *blk_b = nullptr;  // the encoder's weights and biases once more, in the order in which mapper_block.hip reads them
 };
+
+// What launch li (0 .. n_enc_layers) of mapper_block.hip reads per wave, in fragments of 1 KB: weights and biases.
+inline size_t block_frags(const proxykv_config& c, int li) {
+  return (li > 0 ? 128 + (size_t)c.d_ffn / 2 : 0) + (li < c.n_enc_layers ? 384 : 0);
+}
+inline size_t block_bias_frags(const proxykv_config& c, int li) {
+  return (li > 0 ? 8 + (size_t)c.d_ffn / 128 : 0) + (li < c.n_enc_layers ? 12 : 0);
+}
+constexpr size_t kBlkFragBytes = 1024, kBlkRing = 8;  // a wave asks for weights eight fragments ahead
+// Puts w.enc's matrices and biases in that order (w.blk_w, w.blk_b); implemented in mapper_block.hip.
+hipError_t pack_encoder_blocks(const proxykv_config& c, const MapperWeights& w, void* blk_w, void* blk_b, hipStream_t stream);
 
 constexpr int kMapLanes = 2;
 
@@ -54,7 +66,7 @@ inline int kv3_stride(const proxykv_config& c) { return (2 * c.H_kv * c.d_head_x
 // shared by all of them, so a batch's layers lie one behind the other on the M axis of every launch).
 struct MapperWorkspace {
   DeviceBuffer x;      // fp32 [Tp, d_time] per layer: residual stream over all window rows
-  DeviceBuffer xb;     // fp16 [Tp, d_time]: fp16 copy feeding the GEMMs
+  DeviceBuffer xb;     // fp16 [Tp, d_time]: attention output (large tiles); the stem's output, feeding the first projection (small tiles)
   DeviceBuffer work;   // what one kernel leaves for the next (LanePointers in mapper.hpp)
   DeviceBuffer s3;     // fp32 [Np, (H_l + 1) * H_s]  stage 3: per token the H_l x H_s logits, then <w_o, V[s]> of every slot
   DeviceBuffer range;  // 16 words: partial maxima of |score| (bits)
@@ -71,7 +83,7 @@ struct proxykv_ctx {
   bool profile = false, ev_created = false;
   hipEvent_t ev[PROXYKV_N_STAGES + 1] = {};
   bool ev_recorded[PROXYKV_N_STAGES + 1] = {};
-  pkv::DeviceBuffer weight_blob;
+  pkv::DeviceBuffer weight_blob, block_blob;       // block_blob: the encoder's weights in the large tiles' order
   pkv::MapperWeights w;
   std::vector<int32_t> pairing;  // [L_l] 0-based proxy layer per target layer
   // workspace
@@ -155,8 +167,9 @@ inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers,
   return p;
 }
 // Bytes of `work` per layer, the largest of what is there at a time: the stem's first output, read before the encoder starts;
-// q and k, v transposed and the attention's output, all read before the FFN's hidden rows are written; those, read before the
-// next layer's q, k and v are; the overlap-averaged encoder output.  (12 KB of buffers per row, 7 KB with this one in their place.)
+// q, k and v and, with the small tiles, the attention's output, all read before the FFN's hidden rows are written; those, which the
+// small tiles alone write, read before the next layer's q, k and v are; the overlap-averaged encoder output.  A longer call's buffer
+// serves the small tiles of a shorter one, so their hidden rows count in every plan.  (12 KB of buffers per row, 7 KB with this one in their place.)
 inline size_t map_work_bytes(const proxykv_config& c, const MapPlan& p) {
   const size_t row = (size_t)c.d_time * 2, Tp = (size_t)p.Tp;
   const size_t attn = 3 * Tp * row + (size_t)p.n_win * (size_t)p.vt_ld * row, hid = Tp * (size_t)c.d_ffn * 2;

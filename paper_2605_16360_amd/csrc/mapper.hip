@@ -127,13 +127,10 @@ __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict
 // ------------------------------------------------------------------------------------------
 enum Epilogue {
   kEpiGeluPeWin,      // z = GELU(acc * (p0[n] * 2^s) + p1[n]), s from `range`, of token m goes, plus the positional row of its place, into the
-                      // row of every window that holds the token: out_f32 and out_h (second stem convolution -> stage-2 input)
-  kEpiQkvH,           // columns below 2 * d_time: out_h[m, n] = half(acc + p0[n]), rows ldc apart (q and k);
-                      // the others (v): out_v in the transposed, key-permuted layout of the attention kernel
-  kEpiBiasReluH,      // out_h = relu(acc + p0[n])
-  kEpiStage3,         // columns = stage-3 key and value slots of 64: per token and slot the inner products of
+                      // row of every window that holds the token: out_f32, in blocks as block_x4 lays them (second stem convolution ->
+                      // stage-2 input)
+  kEpiStage3          // columns = stage-3 key and value slots of 64: per token and slot the inner products of
                       // acc + p0 with the learned queries (p1, n_head of them, times 1/8) or with the output weights (g)
-  kEpiResLn           // BN = 512: y = LayerNorm(res[m, :] + acc + p0) * g + b -> out_f32 (may be res) and out_h
 };
 
 struct EpiArgs {
@@ -142,44 +139,19 @@ struct EpiArgs {
   const uint32_t* range;  // kEpiGeluPeWin: partial maxima per layer, cw and cs as in stem_exponent
   float cw, cs;
   const float* g;
-  const float* b;
-  const float* res;
   float* out_f32;
-  uint16_t* out_h;
-  uint16_t* out_v;
-  int ldc;  // elements between output rows
-  int vt_ld;       // kEpiQkvH: elements between the rows of the transposed v
+  int ldc;  // kEpiStage3: elements between output rows
   int out_stride;  // kEpiGeluPeWin: output rows between layers
   const float* pe;  // kEpiGeluPeWin: positional table [kWin, d_time]
-  int n_win;        // kEpiGeluPeWin, kEpiQkvH: windows per layer
+  int n_win;        // kEpiGeluPeWin: windows per layer
   int n_slot, n_head;  // kEpiStage3: slots H_s (keys in columns [0, 64 H_s), values in [64 H_s, 128 H_s)) and queries H_l
 };
 
-// epilogue stores bypass L2 allocation: the output is not read again by this kernel and would evict W and A rows
-#define PKV_ST(ptr, val) __builtin_nontemporal_store((val), (ptr))
+constexpr int kGemmTile = 256, kGemmBK = 64;
 
-constexpr int kGemmBK = 64;
-
-// Sum of v[0..15] over the 32 lanes that share bit 5 of the lane number, sixteen sums at once: in every step a lane
+// Sum of v[0..15] over the 16 lanes that share the upper bits of the lane number, sixteen sums at once: in every step a lane
 // keeps the half of its values that its own lane bit selects, hands the other half to the partner and adds what it
-// receives; after four steps it holds one value, the row (lane & 31) >> 1 of the sixteen, summed over sixteen lanes,
-// and the last step adds the neighbour's.  31 exchanges instead of 80.
-__device__ __forceinline__ float reduce16_over_lanes(float (&v)[16], int l32) {
-  static_for<4>([&](auto sc) {
-    constexpr int step = decltype(sc)::value, n = 8 >> step, mask = 16 >> step;
-    const bool up = (l32 & mask) != 0;
-#pragma unroll
-    for (int j = 0; j < n; ++j) {
-      const float send = up ? v[j] : v[j + n];
-      const float keep = up ? v[j + n] : v[j];
-      v[j] = keep + __shfl_xor(send, mask, 64);
-    }
-  });
-  return v[0] + __shfl_xor(v[0], 1, 64);
-}
-
-// Sum of v[0..15] over the 16 lanes that share the upper bits of the lane number, sixteen sums at once, by the same
-// halving exchange: afterwards lane j (lane & 15) holds the sum of v[j].  15 exchanges.
+// receives; afterwards lane j (lane & 15) holds the sum of v[j].  15 exchanges.
 __device__ __forceinline__ float reduce16_over_16_lanes(float (&v)[16], int lane) {
   static_for<4>([&](auto sc) {
     constexpr int step = decltype(sc)::value, n = 8 >> step, mask = 8 >> step;
@@ -194,15 +166,14 @@ __device__ __forceinline__ float reduce16_over_16_lanes(float (&v)[16], int lane
   return v[0];
 }
 
-template <int EPI, int BM, int BN>
+template <int EPI>
 __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __restrict__ A, int lda, int64_t a_layer,
                                                             const uint16_t* __restrict__ W, int M, int rows, int row_stride,
                                                             int Nn, int K, EpiArgs ep) {
-  constexpr int WM = BM / 64, WN = 8 / WM;       // waves along M and N
+  constexpr int BM = kGemmTile, BN = kGemmTile, WM = BM / 64, WN = 8 / WM;  // waves along M and N
   constexpr int NA = BM / 64, NS = (BM + BN) / 64;  // 64-row parts of a stage: A parts, then W parts
   constexpr int kStageU4 = (BM + BN) * (kGemmBK / 8);  // 16-byte units per stage
   static_assert(WM * WN == 8 && BN / WN == 128, "a wave computes 64 x 128");
-  static_assert(EPI != kEpiResLn || BN == kDT, "the normalising epilogue needs the whole row in one tile");
   extern __shared__ u32x4 lds[];  // 2 stages
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int wm = wave / WN, wn = wave % WN;
@@ -343,71 +314,7 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
     tile_of(s / nk, m0, n0);
     const int n = n0 + wn * 128 + 4 * l32;
     const int layer = m0 / row_stride, r0 = m0 - layer * row_stride;  // r0: the tile's first row within its layer
-    if constexpr (EPI == kEpiResLn) {
-      // (1) pre-norm sum in place, acc += bias + residual row, and (2) row sums and sums of squares: four columns in
-      // the lane, 32 lanes by exchange, 4 waves through LDS (the stage that this step has used up is free until
-      // phase 2 of the next step)
-      struct Pair {
-        float s1, s2;
-      };
-      Pair* red = reinterpret_cast<Pair*>(st);  // [128 rows][4 waves along N]
-      int own_row[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const float* rb = ep.res + (size_t)(m0 + wm * 64 + i * 32 + half * 4) * kDT + n;
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-          f32x4 rv[4];
-#pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) rv[e4] = *reinterpret_cast<const f32x4*>(rb + (size_t)(qd * 8 + e4) * kDT);
-#pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4)
-#pragma unroll
-            for (int jn = 0; jn < 4; ++jn) acc[i][jn][qd * 4 + e4] += rv[e4][jn] + p0[jn];
-        }
-        float t[2];
-#pragma unroll
-        for (int which = 0; which < 2; ++which) {
-          float sv[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float a0 = acc[i][0][r], a1 = acc[i][1][r], a2 = acc[i][2][r], a3 = acc[i][3][r];
-            sv[r] = which == 0 ? (a0 + a1) + (a2 + a3) : (a0 * a0 + a1 * a1) + (a2 * a2 + a3 * a3);
-          }
-          t[which] = reduce16_over_lanes(sv, l32);
-        }
-        own_row[i] = ((wm * 2 + i) * 2 + half) * 16 + (l32 >> 1);
-        if ((l32 & 1) == 0) red[own_row[i] * 4 + wn] = Pair{t[0], t[1]};
-      }
-      __syncthreads();
-      float mean_o[2], rstd_o[2];  // of the row this lane reduced
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const f32x4 lo = *reinterpret_cast<const f32x4*>(&red[own_row[i] * 4]);
-        const f32x4 hi = *reinterpret_cast<const f32x4*>(&red[own_row[i] * 4 + 2]);
-        const float sum = (lo[0] + lo[2]) + (hi[0] + hi[2]), sq = (lo[1] + lo[3]) + (hi[1] + hi[3]);
-        const float mu = sum * (1.0f / kDT);
-        const float var = __builtin_fmaxf(__builtin_fmaf(-mu, mu, sq * (1.0f / kDT)), 0.0f);
-        mean_o[i] = mu;
-        rstd_o[i] = 1.0f / sqrtf(var + 1e-5f);
-      }
-      // (3) normalise and store: the statistics of row r sit in lanes 2r and 2r+1 of the lane's own half
-      const f32x4 g4 = *reinterpret_cast<const f32x4*>(ep.g + n), b4 = *reinterpret_cast<const f32x4*>(ep.b + n);
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const size_t ob = (size_t)(m0 + wm * 64 + i * 32 + half * 4) * kDT + n;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const float mu = __shfl(mean_o[i], (half << 5) | (2 * r), 64), rs = __shfl(rstd_o[i], (half << 5) | (2 * r), 64);
-          f32x4 v = {acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
-          v = (v - mu) * rs * g4 + b4;
-          const size_t o = ob + (size_t)((r >> 2) * 8 + (r & 3)) * kDT;
-          PKV_ST(reinterpret_cast<f32x4*>(ep.out_f32 + o), v);
-          PKV_ST(reinterpret_cast<f16x4*>(ep.out_h + o), __builtin_convertvector(v, f16x4));
-        }
-      }
-      __syncthreads();  // the stage may be overwritten again
-    } else if constexpr (EPI == kEpiStage3) {
+    if constexpr (EPI == kEpiStage3) {
       // The 64 columns of a slot sit in 16 lanes (four columns each).  Per 32-row block: the lane's share of every row's
       // inner product with one coefficient vector, sixteen rows reduced over the 16 lanes at once, lane j keeps row j of
       // the sixteen that its half-wave holds.  Key slots take the n_head queries in turn, value slots the output weights.
@@ -439,61 +346,22 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
     } else {
 #pragma unroll
       for (int i = 0; i < 2; ++i) {
-        if constexpr (EPI == kEpiQkvH) {
-          if (n0 >= 2 * kDT) {
-            // v: element (token m, column vc) goes to vt[(window * heads + head) * 64 + dd][pos]; the lane's eight tokens
-            // of a 16-token group (rows r = 8u .. 8u+7 of the tile pair qd = 2u, 2u+1) land in positions half*8 .. +7
-            const int vc = n - 2 * kDT;  // columns vc .. vc+3: one head, dd .. dd+3
-            const int rg0 = r0 + wm * 64 + i * 32;
-            uint16_t* vb = ep.out_v + ((size_t)((layer * ep.n_win + rg0 / kWin) * kHeads + (vc >> 6)) * 64 + (vc & 63)) * ep.vt_ld +
-                           (rg0 % kWin) + half * 8;
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
+        for (int r = 0; r < 16; ++r) {
+          f32x4 v = {acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
 #pragma unroll
-              for (int jn = 0; jn < 4; ++jn) {
-                f32x8 t;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) t[e] = acc[i][jn][u * 8 + e] + p0[jn];
-                PKV_ST(reinterpret_cast<f16x8*>(vb + (size_t)jn * ep.vt_ld + u * 16), __builtin_convertvector(t, f16x8));
-              }
-            continue;
-          }
-        }
-        const size_t ob = (size_t)(m0 + wm * 64 + i * 32 + half * 4) * ep.ldc + n;
-#pragma unroll
-        for (int qd = 0; qd < 4; ++qd) {
-#pragma unroll
-          for (int e4 = 0; e4 < 4; ++e4) {
-            const int r = qd * 4 + e4;
-            f32x4 v = {acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
-            const size_t o = ob + (size_t)(qd * 8 + e4) * ep.ldc;
-            if constexpr (EPI == kEpiGeluPeWin) {
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = gelu_erf(__builtin_fmaf(v[e], p0[e], p1[e]));
-              // token t sits at place t - 1024 k of window k = min(t / 1024, n_win - 1) and, if that window is not the
-              // first and the token lies in its first half, at place + 1024 of the window before
-              const int t = r0 + wm * 64 + i * 32 + half * 4 + qd * 8 + e4;
-              if (t < rows) {
-                const int kq = t / kStride, k1 = kq < ep.n_win ? kq : ep.n_win - 1, p1w = t - k1 * kStride;
-                const size_t o1 = ((size_t)layer * ep.out_stride + (size_t)k1 * kWin + p1w) * kDT + n;
-                const f32x4 y1 = v + *reinterpret_cast<const f32x4*>(ep.pe + (size_t)p1w * kDT + n);
-                PKV_ST(reinterpret_cast<f32x4*>(ep.out_f32 + o1), y1);
-                PKV_ST(reinterpret_cast<f16x4*>(ep.out_h + o1), __builtin_convertvector(y1, f16x4));
-                if (k1 >= 1 && kq == k1) {
-                  const size_t o0 = o1 - (size_t)(kWin - kStride) * kDT;  // window k1 - 1, place p1w + 1024
-                  const f32x4 y0 = v + *reinterpret_cast<const f32x4*>(ep.pe + (size_t)(p1w + kStride) * kDT + n);
-                  PKV_ST(reinterpret_cast<f32x4*>(ep.out_f32 + o0), y0);
-                  PKV_ST(reinterpret_cast<f16x4*>(ep.out_h + o0), __builtin_convertvector(y0, f16x4));
-                }
-              }
-            } else if constexpr (EPI == kEpiQkvH) {
-              PKV_ST(reinterpret_cast<f16x4*>(ep.out_h + o), __builtin_convertvector(v + p0, f16x4));
-            } else if constexpr (EPI == kEpiBiasReluH) {
-              v += p0;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaxf(v[e], 0.0f);
-              PKV_ST(reinterpret_cast<f16x4*>(ep.out_h + o), __builtin_convertvector(v, f16x4));
-            }
+          for (int e = 0; e < 4; ++e) v[e] = gelu_erf(__builtin_fmaf(v[e], p0[e], p1[e]));
+          // token t sits at place t - 1024 k of window k = min(t / 1024, n_win - 1) and, if that window is not the
+          // first and the token lies in its first half, at place + 1024 of the window before
+          const int t = r0 + wm * 64 + i * 32 + half * 4 + (r >> 2) * 8 + (r & 3);
+          if (t < rows) {
+            const int kq = t / kStride, k1 = kq < ep.n_win ? kq : ep.n_win - 1, p1w = t - k1 * kStride;
+            const int64_t row = (int64_t)layer * ep.out_stride + (int64_t)k1 * kWin + p1w;
+            f32x4* xo = reinterpret_cast<f32x4*>(ep.out_f32);
+            xo[block_x4(row, n)] = v + *reinterpret_cast<const f32x4*>(ep.pe + (size_t)p1w * kDT + n);
+            // window k1 - 1, place p1w + 1024
+            if (k1 >= 1 && kq == k1)
+              xo[block_x4(row - (kWin - kStride), n)] = v + *reinterpret_cast<const f32x4*>(ep.pe + (size_t)(p1w + kStride) * kDT + n);
           }
         }
       }
@@ -521,31 +389,29 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
 // b takes q-block (b / 8) % n_qb of item (b / 8 / n_qb) * 8 + b % 8: the q-blocks of one (window, head) run on one XCD
 // and share its L2 copy of that head's K and V.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t* __restrict__ qk,
-                                                                   const uint16_t* __restrict__ vt,
-                                                                   uint16_t* __restrict__ ao, int T, int Tp, int n_win, int n_qb,
-                                                                   int vt_ld) {
-  __shared__ u32x4 lds[3 * 1024];  // stage = K tile (64 keys x 8 chunks) then V^T tile (64 d rows x 8 chunks)
+__global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* __restrict__ qkv,
+                                                                   u32x4* __restrict__ ao, int T, int Tp, int n_win, int n_qb) {
+  __shared__ u32x4 lds[3 * 1024];  // stage = K tile (64 keys), then V tile, as they lie in memory
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int bj = blockIdx.x >> 3, item = (bj / n_qb) * kXcds + (blockIdx.x & 7);
   const int wg = item / kHeads, hd = item % kHeads;  // wg: window of the batch
   const int layer = wg / n_win, wk = wg % n_win;
-  const int64_t base = (int64_t)layer * Tp + (int64_t)wk * kWin;
+  const size_t blk0 = ((size_t)layer * Tp + (size_t)wk * kWin) / kBlk;  // the window's first block of rows
   const int len = (wk < n_win - 1) ? kWin : T - wk * kWin;
   const int i0 = (bj % n_qb) * 256;
   if (i0 >= len) return;
   constexpr float c = 1.4426950408889634f * 0.125f;  // log2(e) / sqrt(64)
 
+  // units of 16 bytes: a block's q, k and v of one head are 1024 each
+  const u32x4* hbase = qkv + (blk0 * kHeads + hd) * 3 * 1024;
+  constexpr size_t kBlkStride = kHeads * 3 * 1024;
+  const int qt = (i0 >> 5) + wave * 2;  // the wave's first tile of 32 queries
   f16x8 bq[2][4];
-  int qi[2];
 #pragma unroll
-  for (int cs = 0; cs < 2; ++cs) {
-    qi[cs] = i0 + wave * 64 + cs * 32 + l32;
-    const int row = qi[cs] < len ? qi[cs] : len - 1;
+  for (int cs = 0; cs < 2; ++cs)
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
-      bq[cs][kk] = as_f16x8(*reinterpret_cast<const u32x4*>(qk + (size_t)(base + row) * (2 * kDT) + hd * 64 + kk * 16 + half * 8));
-  }
+      bq[cs][kk] = as_f16x8(hbase[(size_t)((qt + cs) >> 2) * kBlkStride + (((qt + cs) & 3) * 4 + kk) * 64 + lane]);
   f32x16 o[2][2];  // [d half][query sub-tile]
 #pragma unroll
   for (int ds = 0; ds < 2; ++ds)
@@ -553,30 +419,22 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t
     for (int cs = 0; cs < 2; ++cs) o[ds][cs] = f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   float m_run[2] = {-1.0e30f, -1.0e30f}, l_run[2] = {0.0f, 0.0f};
 
-  const uint16_t* kbase = qk + (size_t)base * (2 * kDT) + kDT + hd * 64;
-  const uint16_t* vbase = vt + (size_t)(wg * kHeads + hd) * 64 * vt_ld;
   const int n_tiles = (len + 63) / 64;
-  // staging: thread moves chunk tid % 8 of rows tid / 8 and tid / 8 + 32 of both tiles
-  const int srow = tid >> 3, sch = tid & 7;
-  const int sslot = srow * 8 + (sch ^ swz8(srow));  // swz8(srow + 32) == swz8(srow)
   u32x4 rk[2], rv[2];
   auto fetch = [&](int t) {
-    const int j0 = t * 64;
+    const u32x4* kb = hbase + (size_t)(t >> 1) * kBlkStride + 1024 + (t & 1) * 512 + tid;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      const int row = srow + 32 * i;
-      int j = j0 + row;
-      j = j < len ? j : len - 1;
-      rk[i] = *reinterpret_cast<const u32x4*>(kbase + (size_t)j * (2 * kDT) + sch * 8);
-      rv[i] = *reinterpret_cast<const u32x4*>(vbase + (size_t)row * vt_ld + j0 + sch * 8);
+      rk[i] = kb[i * 256];
+      rv[i] = kb[1024 + i * 256];
     }
   };
   auto store = [&](int t) {
-    u32x4* st = lds + (t % 3) * 1024;
+    u32x4* st = lds + (t % 3) * 1024 + tid;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      st[sslot + 32 * 8 * i] = rk[i];
-      st[512 + sslot + 32 * 8 * i] = rv[i];
+      st[i * 256] = rk[i];
+      st[512 + i * 256] = rv[i];
     }
   };
   fetch(0);
@@ -586,7 +444,6 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t
     store(1);
   }
   if (n_tiles > 2) fetch(2);
-  const int fsw = swz8(l32);
   // Every load so far (the wave's query fragments among them) has landed before the loop starts.  Without this the
   // compiler, which cannot tell at the loop head that the query fragments arrived long ago, waits for ALL outstanding
   // loads in front of the first MFMAs of every tile (the counter is in order), i.e. for the prefetch it has just issued.
@@ -599,11 +456,11 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t
   // 16-key step are read one step ahead and serve both query sub-tiles.
   auto read_k = [&](const u32x4* st, int ks, f16x8 (&fk)[4]) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) fk[kk] = as_f16x8(st[(ks * 32 + l32) * 8 + ((kk * 2 + half) ^ fsw)]);
+    for (int kk = 0; kk < 4; ++kk) fk[kk] = as_f16x8(st[(ks * 4 + kk) * 64 + lane]);
   };
   auto read_v = [&](const u32x4* st, int u, f16x8 (&fv)[2]) {
 #pragma unroll
-    for (int ds = 0; ds < 2; ++ds) fv[ds] = as_f16x8(st[512 + (ds * 32 + l32) * 8 + ((u * 2 + half) ^ fsw)]);  // d row, step u
+    for (int ds = 0; ds < 2; ++ds) fv[ds] = as_f16x8(st[512 + (u * 2 + ds) * 64 + lane]);  // 32 of d, step u
   };
   f16x8 fk0[4];
   for (int t = 0; t < n_tiles; ++t) {
@@ -707,59 +564,55 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const uint16_t
     for (int cs = 0; cs < 2; ++cs) l_run[cs] += lsum[cs];
   }
 
-  // output: O^T / row sum, through LDS so that every query row is written as 128 contiguous bytes
-  __syncthreads();
-  uint16_t* ot = reinterpret_cast<uint16_t*>(lds) + wave * (64 * 72);  // [64 queries][64 d + 8 pad] per wave
+  // output: O^T / row sum; a lane's eight accumulators are the unit that the next product's operand wants from it
 #pragma unroll
   for (int cs = 0; cs < 2; ++cs) {
     const float inv = 1.0f / halves_sum(l_run[cs]);
+    const int tile = qt + cs;
+    if (tile * 32 >= (len + kBlk - 1) / kBlk * kBlk) continue;
+    u32x4* ob = ao + (blk0 + (tile >> 2)) * (kBlk * kDT / 8) + ((tile & 3) * 32 + hd * 4) * 64 + lane;
 #pragma unroll
     for (int ds = 0; ds < 2; ++ds)
 #pragma unroll
-      for (int rg = 0; rg < 4; ++rg) {
-        f16x4 pk;
+      for (int s = 0; s < 2; ++s) {
+        f32x8 v;
 #pragma unroll
-        for (int e = 0; e < 4; ++e) pk[e] = (_Float16)(o[ds][cs][rg * 4 + e] * inv);
-        *reinterpret_cast<f16x4*>(ot + (cs * 32 + l32) * 72 + ds * 32 + rg * 8 + half * 4) = pk;
+        for (int e = 0; e < 8; ++e) v[e] = o[ds][cs][s * 8 + e] * inv;
+        ob[(ds * 2 + s) * 64] = __builtin_bit_cast(u32x4, __builtin_convertvector(v, f16x8));
       }
-  }
-  // the wave reads back its own rows only: no barrier needed beyond the wave's own LDS ordering
-#pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int id = lane + 64 * i, row = id >> 3, ch = id & 7;  // 64 rows x 8 chunks of 16 bytes
-    const int q = i0 + wave * 64 + row;
-    if (q < len)
-      *reinterpret_cast<u32x4*>(ao + (size_t)(base + q) * kDT + hd * 64 + ch * 8) =
-          *reinterpret_cast<const u32x4*>(ot + row * 72 + ch * 8);
   }
 }
 
 // ------------------------------------------------------------------------------------------
 // overlap averaging: zg[t] = half(mean over the windows covering token t of x[row of t in that window])
-// grid (ceil(N * 128 / 256), layers)
+// grid (ceil(N / 32), layers).  x lies in blocks (block_x4): half a wave reads the same four columns of 32 tokens, 512 bytes in one
+// piece; the rows of zg are put together in LDS.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void overlap_avg_kernel(const float* __restrict__ x, uint16_t* __restrict__ zg,
-                                                           int64_t N, int n_win, int Tp, int Np) {
-  x += (size_t)blockIdx.y * Tp * kDT;
+__global__ __launch_bounds__(256) void overlap_avg_kernel(const f32x4* __restrict__ x, uint16_t* __restrict__ zg,
+                                                           int N, int n_win, int Tp, int Np) {
+  __shared__ f16x4 rows[32][kDT / 4 + 2];
   zg += (size_t)blockIdx.y * Np * kDT;
-  const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (gid >= N * (kDT / 4)) return;
-  const int64_t t = gid / (kDT / 4);
-  const int c4 = (int)(gid % (kDT / 4));
-  f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
-  float cnt = 0.0f;
-  const int64_t khi = t / kStride;
-#pragma unroll
-  for (int dk = 0; dk < 2; ++dk) {
-    const int64_t k = khi - dk;
-    if (k < 0 || k >= n_win) continue;
-    const int64_t p = t - k * kStride;
-    if (p >= kWin) continue;
-    sum += *reinterpret_cast<const f32x4*>(x + (size_t)(k * kWin + p) * kDT + c4 * 4);
-    cnt += 1.0f;
+  const int t0 = blockIdx.x * 32, l32 = threadIdx.x & 31, g = threadIdx.x >> 5;
+  const int khi = t0 / kStride;  // the same for all 32 tokens
+  const bool second = khi < n_win, first = khi >= 1 && khi - 1 < n_win;
+  const int64_t row1 = (int64_t)blockIdx.y * Tp + (int64_t)khi * kWin + (t0 - khi * kStride) + l32;  // in window khi
+  const int64_t row0 = row1 - (kWin - kStride);                                                       // in window khi - 1
+  if (t0 + l32 < N) {
+#pragma unroll 4
+    for (int it = 0; it < 16; ++it) {
+      const int c4 = it * 8 + g;
+      f32x4 sum = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (second) sum += x[block_x4(row1, c4 * 4)];
+      if (first) sum += x[block_x4(row0, c4 * 4)];
+      const f32x4 mean = sum / (first && second ? 2.0f : 1.0f);
+      rows[l32][c4] = __builtin_convertvector(mean, f16x4);
+    }
   }
-  const f32x4 mean = sum / cnt;
-  *reinterpret_cast<f16x4*>(zg + (size_t)t * kDT + c4 * 4) = __builtin_convertvector(mean, f16x4);
+  __syncthreads();
+  for (int i = threadIdx.x; i < 32 * (kDT / 4); i += 256) {
+    const int r = i / (kDT / 4), c4 = i % (kDT / 4);
+    if (t0 + r < N) *reinterpret_cast<f16x4*>(zg + (size_t)(t0 + r) * kDT + c4 * 4) = rows[r][c4];
+  }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -791,13 +644,13 @@ __global__ __launch_bounds__(256) void stage3_kernel(const float* __restrict__ s
   for (int ll = ll_lo; ll < ll_hi; ++ll) yhat[((size_t)ll * H_l + h) * N + t] = y;
 }
 
-template <int EPI, int BM, int BN>
+template <int EPI>
 hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowSpace& rs, int Nn, int K, const EpiArgs& ep,
                        int n_cu, hipStream_t stream) {
-  constexpr int kLdsBytes = 2 * (BM + BN) * (kGemmBK / 8) * 16;
+  constexpr int BM = kGemmTile, BN = kGemmTile, kLdsBytes = 2 * (BM + BN) * (kGemmBK / 8) * 16;
   static bool attr_set = false;  // per instantiation; setting it again is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f16_kernel<EPI, BM, BN>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f16_kernel<EPI>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
     if (e != hipSuccess) return e;
     attr_set = true;
@@ -811,7 +664,7 @@ hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowS
   int wg_per_xcd = n_cu / kXcds;
   if (wg_per_xcd < 1) wg_per_xcd = 1;
   if (wg_per_xcd > per_xcd_tiles) wg_per_xcd = per_xcd_tiles;
-  gemm_f16_kernel<EPI, BM, BN><<<kXcds * wg_per_xcd, 512, kLdsBytes, stream>>>(A, lda, rs.a_layer, W, (int)M, rs.valid,
+  gemm_f16_kernel<EPI><<<kXcds * wg_per_xcd, 512, kLdsBytes, stream>>>(A, lda, rs.a_layer, W, (int)M, rs.valid,
                                                                              rs.stride, Nn, K, ep);
   return hipGetLastError();
 }
@@ -820,13 +673,10 @@ hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowS
 hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const MapPlan& p, int n_layers, int64_t N, int n_cu, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
-  const int T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
+  const int T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win;
   const LanePointers m = lane_pointers(c, p, ws);
-  const uint16_t* h1 = m.h1;
-  float* x = m.x;
-  uint16_t *xb = m.xb, *qk = m.qk, *vt = m.vt, *ao = m.ao, *hid = m.hid, *zg = m.zg;
+  uint16_t* zg = m.zg;
   const unsigned nl = (unsigned)n_layers;
-  auto rows_T = [&](int lda) { return RowSpace{n_layers, T, Tp, (int64_t)Tp * lda}; };
 
   EpiArgs e2 = {};
   e2.p0 = w.bn2_scale;
@@ -834,50 +684,23 @@ hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   e2.range = m.range;
   e2.cw = w.stem_cw;
   e2.cs = w.stem_cs;
-  e2.out_f32 = x;
-  e2.out_h = xb;
-  e2.ldc = kDT;
+  e2.out_f32 = m.x;
   e2.pe = w.pe;
   e2.n_win = n_win;
   e2.out_stride = Tp;
   const RowSpace rows_conv = {n_layers, (int)N, Np, (int64_t)(N + 2) * c.c_mid};
-  PKV_TRY((launch_gemm<kEpiGeluPeWin, 256, 256>(h1, c.c_mid, w.conv2_w, rows_conv, kDT, 3 * c.c_mid, e2, n_cu, stream)));
+  PKV_TRY(launch_gemm<kEpiGeluPeWin>(m.h1, c.c_mid, w.conv2_w, rows_conv, kDT, 3 * c.c_mid, e2, n_cu, stream));
 
   // stage 2 (the stem's epilogue has written its input rows)
   const int n_qb = ((T < kWin ? T : kWin) + 255) / 256;
   for (int li = 0; li < c.n_enc_layers; ++li) {
-    const EncoderLayerWeights& e = w.enc[li];
-    EpiArgs eq = {};
-    eq.p0 = e.in_b;
-    eq.out_h = qk;
-    eq.out_v = vt;
-    eq.ldc = 2 * kDT;
-    eq.n_win = n_win;
-    eq.vt_ld = vt_ld;
-    PKV_TRY((launch_gemm<kEpiQkvH, 256, 256>(xb, kDT, e.in_w, rows_T(kDT), 3 * kDT, kDT, eq, n_cu, stream)));
-    window_attention_kernel<<<nl * (unsigned)(n_win * kHeads * n_qb), 256, 0, stream>>>(qk, vt, ao, T, Tp, n_win, n_qb, vt_ld);
+    PKV_TRY(launch_encoder_block(ctx, p, n_layers, li, m.x, m.xb, m.qk, stream));
+    window_attention_kernel<<<nl * (unsigned)(n_win * kHeads * n_qb), 256, 0, stream>>>(
+        reinterpret_cast<const u32x4*>(m.qk), reinterpret_cast<u32x4*>(m.xb), T, Tp, n_win, n_qb);
     PKV_TRY(hipGetLastError());
-    EpiArgs eo = {};
-    eo.p0 = e.out_b;
-    eo.g = e.ln1_g;
-    eo.b = e.ln1_b;
-    eo.res = x;
-    eo.out_f32 = x;
-    eo.out_h = xb;
-    eo.ldc = kDT;
-    PKV_TRY((launch_gemm<kEpiResLn, 128, 512>(ao, kDT, e.out_w, rows_T(kDT), kDT, kDT, eo, n_cu, stream)));
-    EpiArgs e1 = {};
-    e1.p0 = e.ffn1_b;
-    e1.out_h = hid;
-    e1.ldc = c.d_ffn;
-    PKV_TRY((launch_gemm<kEpiBiasReluH, 256, 256>(xb, kDT, e.ffn1_w, rows_T(kDT), c.d_ffn, kDT, e1, n_cu, stream)));
-    EpiArgs ef = eo;
-    ef.p0 = e.ffn2_b;
-    ef.g = e.ln2_g;
-    ef.b = e.ln2_b;
-    PKV_TRY((launch_gemm<kEpiResLn, 128, 512>(hid, c.d_ffn, e.ffn2_w, rows_T(c.d_ffn), kDT, c.d_ffn, ef, n_cu, stream)));
   }
-  overlap_avg_kernel<<<dim3((unsigned)((N * (kDT / 4) + 255) / 256), nl), 256, 0, stream>>>(x, zg, N, n_win, Tp, Np);
+  if (c.n_enc_layers > 0) PKV_TRY(launch_encoder_block(ctx, p, n_layers, c.n_enc_layers, m.x, m.xb, m.qk, stream));
+  overlap_avg_kernel<<<dim3((unsigned)((N + 31) / 32), nl), 256, 0, stream>>>(reinterpret_cast<const f32x4*>(m.x), zg, (int)N, n_win, Tp, Np);
   PKV_TRY(hipGetLastError());
 
   // stage 3
@@ -891,7 +714,7 @@ hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   e3.n_slot = c.H_kv;
   e3.n_head = c.H_l;
   const RowSpace rows_N = {n_layers, (int)N, Np, (int64_t)Np * kDT};
-  return launch_gemm<kEpiStage3, 256, 256>(zg, kDT, w.kv_w, rows_N, nkv, kDT, e3, n_cu, stream);
+  return launch_gemm<kEpiStage3>(zg, kDT, w.kv_w, rows_N, nkv, kDT, e3, n_cu, stream);
 }
 
 // The network for the layers of one batch (x_in: all proxy layers' scores [L_s, H_kv, N]); writes the rows of every target

@@ -12,6 +12,7 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kNegInf = -__builtin_huge_valf();
 constexpr int kDT = 512;    // d_time
+constexpr int kBlk = 128;   // rows of a block of the large-tile encoder kernels
 constexpr int kWin = 2048;  // window length
 constexpr int kStride = 1024;
 constexpr int kHeads = 8;   // encoder heads, 64 wide
@@ -32,6 +33,14 @@ __device__ __forceinline__ uint16_t to_h(float f) { return __builtin_bit_cast(ui
 __device__ __forceinline__ int swz8(int row) { return (row & 7) ^ ((row >> 3) & 1); }
 
 constexpr int kXcds = 8;
+
+// Where four columns n .. n+3 (n % 4 == 0) of row `row` of the residual stream lie, in units of 16 bytes.  A block of 128 rows is
+// kept as the accumulators of encoder_block_kernel hold it, so that its loads and stores are whole kilobytes: by the wave that owns
+// 128 columns, by 32 rows, by 32 columns, by 8 of these; then a unit per lane.
+__device__ __forceinline__ size_t block_x4(int64_t row, int n) {
+  const int r = (int)(row & (kBlk - 1));
+  return ((((size_t)(row / kBlk) * 4 + (n >> 7)) * 4 + (r >> 5)) * 4 + ((n >> 5) & 3)) * 256 + ((n >> 3) & 3) * 64 + ((n >> 2) & 1) * 32 + (r & 31);
+}
 
 // ------------------------------------------------------------------------------------------
 // Range of the first convolution's output.  The scores of Sec. 3 in their sum form are not bounded by one (an
@@ -89,7 +98,7 @@ struct LanePointers {
   float* x;
   uint16_t *xb, *qk;  // qk: fp16 [Tp, 2*d_time]  q and k of the current layer
   uint16_t* vt;     // fp16 [n_win, heads, 64, vt_ld]  v transposed per window and head
-  uint16_t* ao;     // fp16 [Tp, d_time]    attention output
+  uint16_t* ao;     // fp16 [Tp, d_time]    attention output of the small tiles; of the large ones, whose q, k and v lie in blocks at qk, in xb
   uint16_t* hid;    // fp16 [Tp, d_ffn]
   uint16_t* zg;     // fp16 [Np, d_time]    overlap-averaged encoder output
   float *s3, *pre;
@@ -110,6 +119,11 @@ inline LanePointers lane_pointers(const proxykv_config& c, const MapPlan& p, con
   } while (0)
 
 }  // namespace
+
+// Launch `li` of the large-tile encoder (mapper_block.hip): all of layer li - 1 behind its attention, then q, k and v of layer li; the
+// first has only the latter, the last (li = n_enc_layers) only the former.
+hipError_t launch_encoder_block(const proxykv_ctx* ctx, const MapPlan& p, int n_layers, int li, float* x, const uint16_t* ao, uint16_t* qkv,
+                                hipStream_t stream);
 
 // Second stem convolution, encoder and stage-3 inner products of one batch with the kernels for few rows
 // (mapper_small.hip): from h1 to s3.
