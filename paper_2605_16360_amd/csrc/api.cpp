@@ -562,7 +562,7 @@ int proxykv_set_mapper_weights(proxykv_ctx* ctx, const float* blob, size_t n_flo
       bias_frags += 4 * pkv::block_bias_frags(c, li);
     }
     const size_t w_bytes = (frags + pkv::kBlkRing) * pkv::kBlkFragBytes;  // the last wave asks for as much beyond its last
-    rc = ensure(ctx, ctx->block_blob, w_bytes + (bias_frags + 2) * pkv::kBlkFragBytes, nullptr);
+    rc = ensure(ctx, ctx->block_blob, w_bytes + (bias_frags + 4) * pkv::kBlkFragBytes, nullptr);
     if (rc) return rc;
     void* bias = (uint8_t*)ctx->block_blob.ptr + w_bytes;
     PKV_HIP(ctx, pkv::pack_encoder_blocks(c, w, ctx->block_blob.ptr, bias, nullptr));

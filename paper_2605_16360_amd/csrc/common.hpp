@@ -50,6 +50,12 @@ __device__ __forceinline__ f32x16 mfma_f16_32x32x16(f16x8 a, f16x8 b, f32x16 c) 
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
 }
 
+// 16 x 16 tiles with K = 32: at the power limit the chip does 1.91 PFLOP/s with them and 1.62 with 32 x 32 x 16 (256 CUs, operands of
+// random normal values in registers), whose instructions take as many cycles per flop but draw more.
+__device__ __forceinline__ f32x4 mfma_f16_16x16x32(f16x8 a, f16x8 b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
+}
+
 __device__ __forceinline__ float max3f(float a, float b, float c) { return __builtin_fmaxf(__builtin_fmaxf(a, b), c); }
 
 // value held by lane (lane ^ 32)

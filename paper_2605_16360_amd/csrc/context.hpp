@@ -51,7 +51,7 @@ inline size_t block_frags(const proxykv_config& c, int li) {
   return (li > 0 ? 128 + (size_t)c.d_ffn / 2 : 0) + (li < c.n_enc_layers ? 384 : 0);
 }
 inline size_t block_bias_frags(const proxykv_config& c, int li) {
-  return (li > 0 ? 8 + (size_t)c.d_ffn / 128 : 0) + (li < c.n_enc_layers ? 12 : 0);
+  return (li > 0 ? 16 + (size_t)c.d_ffn / 64 : 0) + (li < c.n_enc_layers ? 24 : 0);
 }
 constexpr size_t kBlkFragBytes = 1024, kBlkRing = 8;  // a wave asks for weights eight fragments ahead
 // Puts w.enc's matrices and biases in that order (w.blk_w, w.blk_b); implemented in mapper_block.hip.

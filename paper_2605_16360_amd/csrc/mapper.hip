@@ -373,26 +373,26 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
 
 // ------------------------------------------------------------------------------------------
 // Window attention (8 heads x 64, full bidirectional attention inside each window).
-// qk [T, 2 * d_time] holds q then k of every window row; vt [window][head][64][win] holds v transposed, the keys of
-// every 16-group in the order the second product consumes them (both written by the QKV GEMM's epilogue).
+// qkv [block of 128 rows][head][q, k, v][16 KB] as encoder_block_kernel leaves it: MFMA fragments of 1 KB, a lane's 16 bytes each.  q and k:
+// [16 rows][32 of d]; v: [32 keys][16 of d].  ao: [block][16 rows][32 columns], the next product's fragments.
 // Computes S^T = K Q^T so that a lane owns one query column; P^T then feeds the second MFMA as its
-// B operand straight from the accumulator registers, with V^T tiles as the A operand.
-// 256 threads; a workgroup owns 256 queries of one (window, head), a wave 64 of them (two 32-column
-// sub-tiles); keys stream in tiles of 64 through three LDS stages (K tile + V^T tile, 16 KB each) with one
-// barrier per tile: while tile t is computed, tile t+2 goes from registers to LDS and tile t+3 is
-// fetched from global memory.
+// B operand straight from the accumulator registers, with V^T fragments as the A operand.
+// 256 threads; a workgroup owns 256 queries of one (window, head), a wave 64 of them (four 16-column
+// sub-tiles); keys stream in tiles of 64, copied as they lie, by loads that write LDS, into four LDS stages (K, then V, 8 KB
+// each) with one barrier per tile: while tile t is computed, tile t+1 lies there and t+2 and t+3 are on their way.
 // Online softmax with a lazily raised reference: a column's reference only moves when a logit exceeds it
 // by more than 2^8, so the rescaling of the output accumulators is rare; probabilities stay below 2^8,
 // which half holds with its full relative precision.
-// Layer b of the batch owns rows [b * Tp, b * Tp + T) of qk and ao; its windows start every 2048 rows.
+// Layer b of the batch owns rows [b * Tp, b * Tp + T); its windows start every 2048 rows.  What the block of a layer's last row holds beyond
+// it is finite, and keys there are masked; blocks beyond are not read as keys, and queries there are computed and dropped.
 // Block -> work mapping: blocks are dealt round-robin to the 8 XCDs, so with n_qb blocks of 256 queries per window block
 // b takes q-block (b / 8) % n_qb of item (b / 8 / n_qb) * 8 + b % 8: the q-blocks of one (window, head) run on one XCD
 // and share its L2 copy of that head's K and V.
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* __restrict__ qkv,
                                                                    u32x4* __restrict__ ao, int T, int Tp, int n_win, int n_qb) {
-  __shared__ u32x4 lds[3 * 1024];  // stage = K tile (64 keys), then V tile, as they lie in memory
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  __shared__ u32x4 lds[4 * 1024];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, quad = lane >> 4;
   const int bj = blockIdx.x >> 3, item = (bj / n_qb) * kXcds + (blockIdx.x & 7);
   const int wg = item / kHeads, hd = item % kHeads;  // wg: window of the batch
   const int layer = wg / n_win, wk = wg % n_win;
@@ -402,184 +402,182 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
   if (i0 >= len) return;
   constexpr float c = 1.4426950408889634f * 0.125f;  // log2(e) / sqrt(64)
 
-  // units of 16 bytes: a block's q, k and v of one head are 1024 each
   const u32x4* hbase = qkv + (blk0 * kHeads + hd) * 3 * 1024;
   constexpr size_t kBlkStride = kHeads * 3 * 1024;
-  const int qt = (i0 >> 5) + wave * 2;  // the wave's first tile of 32 queries
-  f16x8 bq[2][4];
+  const int q0 = (i0 >> 4) + wave * 4;  // the wave's first tile of 16 queries; its four lie in one block
+  const u32x4* qb = hbase + (size_t)(q0 >> 3) * kBlkStride + (q0 & 7) * 2 * 64 + lane;
+  f16x8 bq[4][2];
 #pragma unroll
-  for (int cs = 0; cs < 2; ++cs)
+  for (int qt = 0; qt < 4; ++qt)
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-      bq[cs][kk] = as_f16x8(hbase[(size_t)((qt + cs) >> 2) * kBlkStride + (((qt + cs) & 3) * 4 + kk) * 64 + lane]);
-  f32x16 o[2][2];  // [d half][query sub-tile]
+    for (int kk = 0; kk < 2; ++kk) bq[qt][kk] = as_f16x8(qb[(qt * 2 + kk) * 64]);
+  f32x4 o[4][4];  // [16 of d][query sub-tile]
 #pragma unroll
-  for (int ds = 0; ds < 2; ++ds)
+  for (int d = 0; d < 4; ++d)
 #pragma unroll
-    for (int cs = 0; cs < 2; ++cs) o[ds][cs] = f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-  float m_run[2] = {-1.0e30f, -1.0e30f}, l_run[2] = {0.0f, 0.0f};
+    for (int qt = 0; qt < 4; ++qt) o[d][qt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  float m_run[4], l_run[4];
+#pragma unroll
+  for (int qt = 0; qt < 4; ++qt) {
+    m_run[qt] = -1.0e30f;
+    l_run[qt] = 0.0f;
+  }
 
   const int n_tiles = (len + 63) / 64;
-  u32x4 rk[2], rv[2];
-  auto fetch = [&](int t) {
-    const u32x4* kb = hbase + (size_t)(t >> 1) * kBlkStride + 1024 + (t & 1) * 512 + tid;
+  typedef const __attribute__((address_space(1))) void* gptr_t;
+  typedef __attribute__((address_space(3))) void* lptr_t;
+  // past the last tile the last one is copied again, so that every tile has the same number of loads behind it
+  auto fetch = [&](int t, int stage) {
+    const int tc = t < n_tiles ? t : n_tiles - 1;
+    const u32x4* kb = hbase + (size_t)(tc >> 1) * kBlkStride + 1024 + (tc & 1) * 512 + wave * 64 + lane;
+    u32x4* st = lds + stage * 1024 + wave * 64;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      rk[i] = kb[i * 256];
-      rv[i] = kb[1024 + i * 256];
+      __builtin_amdgcn_global_load_lds((gptr_t)(kb + i * 256), (lptr_t)(st + i * 256), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr_t)(kb + 1024 + i * 256), (lptr_t)(st + 512 + i * 256), 16, 0, 0);
     }
   };
-  auto store = [&](int t) {
-    u32x4* st = lds + (t % 3) * 1024 + tid;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      st[i * 256] = rk[i];
-      st[512 + i * 256] = rv[i];
-    }
-  };
-  fetch(0);
-  store(0);
-  if (n_tiles > 1) {
-    fetch(1);
-    store(1);
-  }
-  if (n_tiles > 2) fetch(2);
-  // Every load so far (the wave's query fragments among them) has landed before the loop starts.  Without this the
-  // compiler, which cannot tell at the loop head that the query fragments arrived long ago, waits for ALL outstanding
-  // loads in front of the first MFMAs of every tile (the counter is in order), i.e. for the prefetch it has just issued.
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  fetch(0, 0);
+  fetch(1, 1);
+  fetch(2, 2);
 
   typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
   const f16x2 ones = {(_Float16)1.0f, (_Float16)1.0f};
-  // LDS reads run ahead of their use: the first four K fragments of tile t+1 are read in the tail of tile t (its stage
-  // has been complete since the barrier of tile t), the other four behind the first MFMAs; the V^T fragments of a
-  // 16-key step are read one step ahead and serve both query sub-tiles.
-  auto read_k = [&](const u32x4* st, int ks, f16x8 (&fk)[4]) {
+  // LDS reads run ahead of their use: the first half of tile t+1's K fragments is read in the tail of tile t, the other half and
+  // the first V fragments while the first products run.
+  f16x8 fa[2][2], fb[2][2], fv[4];
+  auto read_k = [&](const u32x4* st, int kt, f16x8 (&fk)[2][2]) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk) fk[kk] = as_f16x8(st[(ks * 4 + kk) * 64 + lane]);
+    for (int i = 0; i < 4; ++i) fk[i >> 1][i & 1] = as_f16x8(st[(kt * 2 + i) * 64]);
   };
-  auto read_v = [&](const u32x4* st, int u, f16x8 (&fv)[2]) {
-#pragma unroll
-    for (int ds = 0; ds < 2; ++ds) fv[ds] = as_f16x8(st[512 + (u * 2 + ds) * 64 + lane]);  // 32 of d, step u
-  };
-  f16x8 fk0[4];
+  __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8): tile 0
+  __syncthreads();
+  read_k(lds + lane, 0, fa);
   for (int t = 0; t < n_tiles; ++t) {
-    // every wave has finished tile t-1: its stage takes tile t+2, the registers take tile t+3
+    // this wave's part of tile t+1 has landed (the four loads of tile t+2 may be outstanding); behind the barrier everyone's has, and
+    // every wave has finished tile t-1, whose stage takes tile t+3
+    __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4)
     __syncthreads();
-    if (t + 2 < n_tiles) store(t + 2);
-    if (t + 3 < n_tiles) fetch(t + 3);
-    const u32x4* st = lds + (t % 3) * 1024;
+    fetch(t + 3, (t + 3) & 3);
+    const u32x4* st = lds + (t & 3) * 1024 + lane;
     const int j0 = t * 64;
-    const bool ragged = j0 + 64 > len;
-    if (t == 0) read_k(st, 0, fk0);
 
-    // S^T tiles of both query sub-tiles: s[cs][ks] = K[ks] Q[cs]^T
-    f32x16 s[2][2];
-    f16x8 fk1[4], fv[2][2];
-    read_k(st, 1, fk1);
-    read_v(st, 0, fv[0]);
+    // S^T tiles: s[kt][qt] = K[kt] Q[qt]^T, 16 keys each
+    f32x4 s[4][4];
+    read_k(st, 2, fb);
 #pragma unroll
-    for (int cs = 0; cs < 2; ++cs) {
-      f32x16 acc = f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+    for (int d = 0; d < 4; ++d) fv[d] = as_f16x8(st[512 + d * 64]);
+    auto logits = [&](int kt, const f16x8 (&fk)[2]) {
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) acc = mfma_f16_32x32x16(fk0[kk], bq[cs][kk], acc);
-      s[cs][0] = acc;
+      for (int q = 0; q < 4; ++q) s[kt][q] = mfma_f16_16x16x32(fk[0], bq[q][0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+#pragma unroll
+      for (int q = 3; q >= 0; --q) s[kt][q] = mfma_f16_16x16x32(fk[1], bq[q][1], s[kt][q]);
+    };
+    logits(0, fa[0]);
+    logits(1, fa[1]);
+    __builtin_amdgcn_sched_barrier(0);
+    logits(2, fb[0]);
+    logits(3, fb[1]);
+    if (j0 + 64 > len) {
+      const int lim = len - j0 - quad * 4;  // element i of tile kt is key j0 + kt*16 + quad*4 + i
+#pragma unroll
+      for (int kt = 0; kt < 4; ++kt)
+#pragma unroll
+        for (int qt = 0; qt < 4; ++qt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) s[kt][qt][i] = kt * 16 + i < lim ? s[kt][qt][i] : kNegInf;
     }
+    float tmax[4];
+    bool raise = false;
 #pragma unroll
-    for (int cs = 0; cs < 2; ++cs) {
-      f32x16 acc = f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) acc = mfma_f16_32x32x16(fk1[kk], bq[cs][kk], acc);
-      s[cs][1] = acc;
+    for (int qt = 0; qt < 4; ++qt) {
+      float m = max3f(s[0][qt][0], s[0][qt][1], s[0][qt][2]);
+      m = max3f(m, s[0][qt][3], s[1][qt][0]);
+      m = max3f(m, s[1][qt][1], s[1][qt][2]);
+      m = max3f(m, s[1][qt][3], s[2][qt][0]);
+      m = max3f(m, s[2][qt][1], s[2][qt][2]);
+      m = max3f(m, s[2][qt][3], s[3][qt][0]);
+      m = max3f(m, s[3][qt][1], s[3][qt][2]);
+      tmax[qt] = __builtin_fmaxf(m, s[3][qt][3]) * c;
+      raise |= tmax[qt] > m_run[qt] + kAttnLazy;
     }
-    if (ragged) {
-      const int lim = len - j0 - half * 4;  // element r of tile ks is key j0 + ks*32 + (r>>2)*8 + half*4 + (r&3)
+    // a column's logits lie in four lanes; only where one of them is beyond the reference do they have to agree on a new one
+    if (__builtin_amdgcn_ballot_w64(raise)) {
 #pragma unroll
-      for (int cs = 0; cs < 2; ++cs)
+      for (int qt = 0; qt < 4; ++qt) {
+        const float tm = quads_max(tmax[qt]);
+        const float nm = tm > m_run[qt] + kAttnLazy ? tm : m_run[qt];
+        const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - nm);
+        l_run[qt] *= alpha;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
+        for (int d = 0; d < 4; ++d)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) s[cs][ks][r] = (ks * 32 + (r >> 2) * 8 + (r & 3)) < lim ? s[cs][ks][r] : kNegInf;
-    }
-    float tmax[2];
-#pragma unroll
-    for (int cs = 0; cs < 2; ++cs) tmax[cs] = halves_max(max16_8(s[cs][0], s[cs][1])) * c;
-    if (__builtin_amdgcn_ballot_w64(tmax[0] > m_run[0] + kAttnLazy || tmax[1] > m_run[1] + kAttnLazy)) {
-#pragma unroll
-      for (int cs = 0; cs < 2; ++cs) {
-        const float nm = tmax[cs] > m_run[cs] + kAttnLazy ? tmax[cs] : m_run[cs];
-        const float alpha = __builtin_amdgcn_exp2f(m_run[cs] - nm);
-        l_run[cs] *= alpha;
-#pragma unroll
-        for (int ds = 0; ds < 2; ++ds)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) o[ds][cs][r] *= alpha;
-        m_run[cs] = nm;
+          for (int i = 0; i < 4; ++i) o[d][qt][i] *= alpha;
+        m_run[qt] = nm;
       }
     }
-    // Four steps of 16 keys.  A wave issues in order, so an MFMA that finds the matrix pipe busy holds back the vector
-    // instructions behind it: the four MFMAs of step u-1 are therefore spread between the vector instructions of
-    // step u (one MFMA, then a quarter of the step's exponentials, conversions and sums), each finding the pipe free.
-    float lsum[2] = {0.0f, 0.0f};
-    f16x8 pb[2][2];  // [step parity][query sub-tile]
+    // Four steps of 32 keys and 32 queries.  A wave issues in order, so an MFMA that finds the matrix pipe busy holds back the vector
+    // instructions behind it: the eight MFMAs of step u-1 are therefore spread between the vector instructions of
+    // step u (one MFMA, then an eighth of the step's exponentials, conversions and sums), each finding the pipe free.
+    f16x8 pb[2][2];  // [step parity][query sub-tile of the step]
     static_for<5>([&](auto uc) {
       constexpr int u = decltype(uc)::value;
       if constexpr (u > 0) {
+        constexpr int qh = (u - 1) & 1;
 #pragma unroll
-        for (int ds = 0; ds < 2; ++ds)
+        for (int d = 0; d < 4; ++d) {
 #pragma unroll
-          for (int cs = 0; cs < 2; ++cs) o[ds][cs] = mfma_f16_32x32x16(fv[(u - 1) & 1][ds], pb[(u - 1) & 1][cs], o[ds][cs]);
+          for (int i = 0; i < 2; ++i) o[d][qh * 2 + i] = mfma_f16_16x16x32(fv[d], pb[(u - 1) & 1][i], o[d][qh * 2 + i]);
+          if constexpr (u == 2) fv[d] = as_f16x8(st[512 + (4 + d) * 64]);
+        }
       }
       if constexpr (u < 4) {
-        constexpr int ks = u >> 1, u2 = u & 1;
+        constexpr int p = u >> 1, qh = u & 1;
 #pragma unroll
-        for (int cs = 0; cs < 2; ++cs) {
-          const float nref = -m_run[cs];
-          f32x8 p;
+        for (int i = 0; i < 2; ++i) {
+          constexpr int q2 = qh * 2;
+          const float nref = -m_run[q2 + i];
+          f32x8 e;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) p[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[cs][ks][u2 * 8 + e], c, nref));
-          pb[u & 1][cs] = __builtin_convertvector(p, f16x8);
+          for (int j = 0; j < 8; ++j) e[j] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[p * 2 + (j >> 2)][q2 + i][j & 3], c, nref));
+          pb[u & 1][i] = __builtin_convertvector(e, f16x8);
           // the row sum takes the probabilities as the second product sees them (rounded to half), two per instruction
 #pragma unroll
-          for (int e = 0; e < 8; e += 2)
-            lsum[cs] = __builtin_amdgcn_fdot2(f16x2{pb[u & 1][cs][e], pb[u & 1][cs][e + 1]}, ones, lsum[cs], false);
+          for (int j = 0; j < 8; j += 2)
+            l_run[q2 + i] = __builtin_amdgcn_fdot2(f16x2{pb[u & 1][i][j], pb[u & 1][i][j + 1]}, ones, l_run[q2 + i], false);
         }
         // pins the row sums to this step: left alone, the compiler moves all of them behind the last step
-        asm volatile("" : "+v"(lsum[0]), "+v"(lsum[1]));
+        asm volatile("" : "+v"(l_run[qh * 2]), "+v"(l_run[qh * 2 + 1]));
         if constexpr (u > 0) {
 #pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // one MFMA
-            __builtin_amdgcn_sched_group_barrier(0x002, 12, 0);  // twelve vector instructions
+          for (int i = 0; i < 8; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);  // six vector instructions
           }
         }
-        // V^T fragments of step u+1 into the buffer that the MFMAs of step u-1 have just released
-        if constexpr (u < 3) read_v(st, u + 1, fv[(u + 1) & 1]);
       } else {
-        if (t + 1 < n_tiles) read_k(lds + ((t + 1) % 3) * 1024, 0, fk0);
+        read_k(lds + ((t + 1) & 3) * 1024 + lane, 0, fa);  // behind the last tile: of a copy that nobody uses
       }
       __builtin_amdgcn_sched_barrier(0);
     });
-#pragma unroll
-    for (int cs = 0; cs < 2; ++cs) l_run[cs] += lsum[cs];
   }
+
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing of this workgroup writes LDS that another may have by then
 
   // output: O^T / row sum; a lane's eight accumulators are the unit that the next product's operand wants from it
 #pragma unroll
-  for (int cs = 0; cs < 2; ++cs) {
-    const float inv = 1.0f / halves_sum(l_run[cs]);
-    const int tile = qt + cs;
-    if (tile * 32 >= (len + kBlk - 1) / kBlk * kBlk) continue;
-    u32x4* ob = ao + (blk0 + (tile >> 2)) * (kBlk * kDT / 8) + ((tile & 3) * 32 + hd * 4) * 64 + lane;
+  for (int qt = 0; qt < 4; ++qt) {
+    const float inv = 1.0f / quads_sum(l_run[qt]);
+    const int tile = q0 + qt;
+    if (tile * 16 >= (len + kBlk - 1) / kBlk * kBlk) continue;
+    u32x4* ob = ao + (blk0 + (tile >> 3)) * (kBlk * kDT / 8) + ((tile & 7) * 16 + hd * 2) * 64 + lane;
 #pragma unroll
-    for (int ds = 0; ds < 2; ++ds)
+    for (int s = 0; s < 2; ++s) {
+      f32x8 v;
 #pragma unroll
-      for (int s = 0; s < 2; ++s) {
-        f32x8 v;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = o[ds][cs][s * 8 + e] * inv;
-        ob[(ds * 2 + s) * 64] = __builtin_bit_cast(u32x4, __builtin_convertvector(v, f16x8));
-      }
+      for (int e = 0; e < 8; ++e) v[e] = o[s * 2 + (e >> 2)][qt][e & 3] * inv;
+      ob[s * 64] = __builtin_bit_cast(u32x4, __builtin_convertvector(v, f16x8));
+    }
   }
 }
 

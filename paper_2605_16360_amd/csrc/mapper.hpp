@@ -36,10 +36,10 @@ constexpr int kXcds = 8;
 
 // Where four columns n .. n+3 (n % 4 == 0) of row `row` of the residual stream lie, in units of 16 bytes.  A block of 128 rows is
 // kept as the accumulators of encoder_block_kernel hold it, so that its loads and stores are whole kilobytes: by the wave that owns
-// 128 columns, by 32 rows, by 32 columns, by 8 of these; then a unit per lane.
+// 128 columns, by 16 rows, by 16 columns; then a unit per lane.
 __device__ __forceinline__ size_t block_x4(int64_t row, int n) {
   const int r = (int)(row & (kBlk - 1));
-  return ((((size_t)(row / kBlk) * 4 + (n >> 7)) * 4 + (r >> 5)) * 4 + ((n >> 5) & 3)) * 256 + ((n >> 3) & 3) * 64 + ((n >> 2) & 1) * 32 + (r & 31);
+  return ((((size_t)(row / kBlk) * 4 + (n >> 7)) * 8 + (r >> 4)) * 8 + ((n >> 4) & 7)) * 64 + ((n >> 2) & 3) * 16 + (r & 15);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -83,6 +83,16 @@ __device__ __forceinline__ float halves_max(float v) {
 __device__ __forceinline__ float halves_sum(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// the same over the four quarters of 16 lanes
+__device__ __forceinline__ float quads_sum(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return halves_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+__device__ __forceinline__ float quads_max(float v) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return halves_max(__builtin_fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
 }
 
 // rows of every layer of a batch on a GEMM's M axis: `valid` of them, `stride` apart (a multiple of 256)

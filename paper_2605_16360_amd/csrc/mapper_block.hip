@@ -8,11 +8,11 @@
 // Four waves, one per SIMD, each with all 512 registers of a lane.  The block's operand (attention output, then normalised rows) lies
 // in LDS, 128 KB, in the order in which MFMA fragments are read.  Every wave owns a quarter of each product's features, so it needs
 // weights that no other wave of the workgroup reads: they come from L2 straight into registers, in the order of their use, eight
-// fragments ahead, and never through LDS (16 columns of arithmetic per byte read from either: 128 rows x 128 features per wave).
+// fragments ahead, and never through LDS.
 // The weights are the products' left operand, so a lane holds a token's column and what it has accumulated are, eight
 // at a time, exactly what it has to supply of the next product's right operand: the hidden rows go to the other waves through
 // LDS as they are, 64 features at a time, the product with them starting from the residual row in the accumulators.
-// K is taken in that order everywhere: element j of half-wave h's eight is feature 4 h + j % 4 + 8 (j / 4) of the sixteen.
+// K is taken in that order everywhere: element j of lane quarter g's eight is feature 4 g + j % 4 + 16 (j / 4) of the thirty-two.
 // Biases are products as well: three bf16 terms, which add up to the fp32 bias exactly, times ones.
 #include "common.hpp"
 #include "context.hpp"
@@ -21,8 +21,6 @@
 
 namespace pkv {
 namespace {
-
-constexpr int kBlkWaves = 4;
 
 // LDS in 16-byte units: the token tile, then two stages of 64 hidden features
 constexpr int kXtU4 = kBlk * kDT / 8, kHidU4 = kBlk * 64 / 8;
@@ -43,65 +41,103 @@ struct BlockArgs {
 // The hidden features' accumulators lie in vector registers (the other 256 of a lane's accumulators fill the accumulation registers), which
 // the compiler does not choose by itself.  It does not know these instructions' hazards either: no operand of theirs is
 // written by a vector instruction less than two issues before, and s_nop 24 stands between the last of them and the first reader.
-__device__ __forceinline__ void mfma_v(f32x16& d, f16x8 a, f16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+__device__ __forceinline__ void mfma_v(f32x4& d, u32x4 a, u32x4 b) {
+  asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void bias_v(f32x16& d, bf16x8 a, bf16x8 b) {
-  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
+// d = bias: the first product of a sum, which needs no cleared accumulators
+__device__ __forceinline__ void bias_v(f32x4& d, u32x4 a, u32x4 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
 }
-__device__ __forceinline__ void bias_a(f32x16& d, bf16x8 a, bf16x8 b) {
-  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&a"(d) : "v"(a), "v"(b));
+__device__ __forceinline__ void bias_a(f32x4& d, u32x4 a, u32x4 b) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&a"(d) : "v"(a), "v"(b));
+}
+
+// Memory through buffer resources: a uniform base and offset in scalar registers, the lane's 16 bytes the same vector register everywhere.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t resource(const void* base, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ u32x4 load16(__amdgpu_buffer_rsrc_t r, unsigned lane_bytes, int at) {
+  return __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_bytes, at, 0);
+}
+__device__ __forceinline__ void store16(__amdgpu_buffer_rsrc_t r, unsigned lane_bytes, int at, u32x4 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)lane_bytes, at, 0);
+}
+
+__device__ __forceinline__ u32x4 pack8(const f32x4& lo, const f32x4& hi) {
+  const f32x8 t = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+  return __builtin_bit_cast(u32x4, __builtin_convertvector(t, f16x8));
 }
 
 template <bool FIRST, bool LAST>
 __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void encoder_block_kernel(BlockArgs a) {
+  // the token tile, [8 tiles of 16 tokens][16 K steps of 32], then two stages of hidden rows, [2][8][2]
   extern __shared__ u32x4 lds[];
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = (unsigned)lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const unsigned ul = (unsigned)lane;
   const int layer = blockIdx.x / a.blocks, b = blockIdx.x % a.blocks;
   const size_t blk = (size_t)layer * (a.Tp / kBlk) + b;
-  u32x4* xt = lds + lane;
-  u32x4* hid = lds + kXtU4 + lane;
-  f32x4* xu = a.x + (blk * 4 + wave) * (4 * 4 * 4 * 64);  // the wave's part of the residual stream
-  const unsigned ul = (unsigned)lane;
-
-  const u32x4* wp = a.w + (size_t)wave * a.w_wave * 64;
-  const u32x4* bp = a.bias + (size_t)wave * a.bias_wave * 64;
-  u32x4 rg[8];
+  const unsigned l16b = ul * 16;
+  const __amdgpu_buffer_rsrc_t xr = resource(a.x + (blk * 4 + wave) * (8 * 8 * 64), 8 * 8 * 1024);  // the wave's part of the residual stream
+  const __amdgpu_buffer_rsrc_t wr = resource(a.w + (size_t)wave * a.w_wave * 64, (a.w_wave + kBlkRing) * kBlkFragBytes);
+  const __amdgpu_buffer_rsrc_t br = resource(a.bias + (size_t)wave * a.bias_wave * 64, (a.bias_wave + 4) * kBlkFragBytes);
+  int wp = 0, bp = 0;  // positions in the weights and the biases, bytes
+  u32x4 rg[kBlkRing];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) rg[i] = (wp + i * 64)[ul];
+  for (int i = 0; i < (int)kBlkRing; ++i) rg[i] = load16(wr, l16b, i * 1024);
 
-  const bf16x8 ones = as_bf16x8(u32x4{0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u});
-  f32x16 acc[4][4];  // [32 tokens][32 features]
+  u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};  // bf16
+  asm volatile("" : "+v"(ones));  // made once, and not in front of an instruction that reads it
+  f32x4 acc[8][8];  // [16 tokens][16 features]
+  u32x4 f[2][8];    // token fragments of this K step and the next
 
-  auto store_half = [&](const f32x16& v, int which) {
-    f32x8 t;
+  // The lane, as a value that the compiler does not know: addresses made from it are made anew and not kept (and spilled) between
+  // phases.  A reload behind the stores of the residual rows would wait for all of them.
+  auto fresh = [&]() __attribute__((always_inline)) {
+    unsigned v = ul;
+    asm volatile("" : "+v"(v));
+    return v;
+  };
+  auto read_x = [&]() __attribute__((always_inline)) {
+    const u32x4* src = lds + fresh();
 #pragma unroll
-    for (int e = 0; e < 8; ++e) t[e] = v[which * 8 + e];
-    return __builtin_bit_cast(u32x4, __builtin_convertvector(t, f16x8));
+    for (int tt = 0; tt < 8; ++tt) f[0][tt] = src[tt * 16 * 64];
+  };
+  // acc (+)= product with the token tile, K = 512.  Of two MFMAs in a row one operand is the same, also where the feature tile changes:
+  // what the matrix cores draw, and with it the clock, depends on how much of their input changes.
+  auto gemm_x = [&](auto swap) __attribute__((always_inline)) {
+    const u32x4* xp = lds + fresh();
+    for (int g = 0; g < 8; ++g) {
+      static_for<2>([&](auto kc) {
+        constexpr int kk = decltype(kc)::value;
+        static_for<64>([&](auto jc) {
+          constexpr int j = decltype(jc)::value, mt = j >> 3, tt = (mt & 1) ? 7 - (j & 7) : (j & 7);
+          const f16x8 fw = as_f16x8(rg[mt]), fx = as_f16x8(f[kk][tt]);
+          acc[tt][mt] = decltype(swap)::value ? mfma_f16_16x16x32(fx, fw, acc[tt][mt]) : mfma_f16_16x16x32(fw, fx, acc[tt][mt]);
+          if constexpr (j % 4 == 0 && j < 32) f[kk ^ 1][j / 4] = xp[(j / 4 * 16 + kk + 1) * 64];
+          if constexpr ((j & 7) == 7) rg[mt] = load16(wr, l16b, wp + (mt + (int)kBlkRing) * 1024);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        wp += (int)kBlkRing * 1024;
+      });
+      xp += 2 * 64;
+    }
+  };
+  auto put_x = [&]() __attribute__((always_inline)) {
+    u32x4* dst = lds + wave * 4 * 64 + fresh();
+#pragma unroll
+    for (int tt = 0; tt < 8; ++tt)
+#pragma unroll
+      for (int s = 0; s < 4; ++s) dst[(tt * 16 + s) * 64] = pack8(acc[tt][2 * s], acc[tt][2 * s + 1]);
   };
 
-  if constexpr (FIRST) {
-    const int rows = a.T - b * kBlk;  // valid rows of the block
+  u32x4 bf[8];      // bias fragments
+  auto load_bf = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt) {
-      const bool in = tt * 32 + l32 < rows;
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-        f32x16 v;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          f32x4 t = (xu + ((tt * 4 + mt) * 4 + q) * 64)[ul];
-          if (!in) t = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-          if (rows < kBlk) (xu + ((tt * 4 + mt) * 4 + q) * 64)[ul] = t;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[q * 4 + e] = t[e];
-        }
-#pragma unroll
-        for (int s = 0; s < 2; ++s) xt[(tt * 32 + wave * 8 + mt * 2 + s) * 64] = store_half(v, s);
-      }
-    }
-    __syncthreads();
-  } else {
+    for (int mt = 0; mt < 8; ++mt) bf[mt] = load16(br, l16b, bp + mt * 1024);
+    bp += 8 * 1024;
+  };
+
+  if constexpr (!FIRST) {
     // the block's attention output, as it lies
     const u32x4* ag = a.ao + blk * kXtU4 + wave * 64;
     typedef const __attribute__((address_space(1))) void* gptr_t;
@@ -109,245 +145,223 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 #pragma unroll
     for (int i = 0; i < kXtU4 / 256; ++i)
       __builtin_amdgcn_global_load_lds((gptr_t)((ag + i * 256) + ul), (lptr_t)(lds + i * 256 + wave * 64), 16, 0, 0);
+  }
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+  for (int tt = 0; tt < 8; ++tt)
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < 8; ++mt) acc[tt][mt] = __builtin_bit_cast(f32x4, load16(xr, l16b, (tt * 8 + mt) * 1024));
+
+  if constexpr (FIRST) {
+    // rows past the layer's last one become zeros, so that everything computed from them is finite
+    const int rows = a.T - b * kBlk;
+    if (rows < kBlk) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 t = (xu + ((tt * 4 + mt) * 4 + q) * 64)[ul];
+      for (int tt = 0; tt < 8; ++tt)
+        if (tt * 16 + (lane & 15) >= rows) {
 #pragma unroll
-          for (int e = 0; e < 4; ++e) acc[tt][mt][q * 4 + e] = t[e];
+          for (int mt = 0; mt < 8; ++mt) {
+            acc[tt][mt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            store16(xr, l16b, (tt * 8 + mt) * 1024, u32x4{0u, 0u, 0u, 0u});
+          }
         }
-    bf16x8 bf[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) bf[mt] = as_bf16x8((bp + mt * 64)[ul]);
-    __builtin_amdgcn_s_waitcnt(0x0F70);
+    }
+    load_bf();
+    put_x();
     __syncthreads();
+    read_x();
+  } else {
+    // acc = residual + bias + out-projection
+    load_bf();
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the tile has landed
+    __syncthreads();
+    read_x();
+    auto add_bias = [&]() __attribute__((always_inline)) {
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+      for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) acc[tt][mt] = mfma_32x32x16(bf[mt], ones, acc[tt][mt]);
-    bp += 4 * 64;
-
-    // K = 512 over the token tile, four feature tiles
-    auto gemm_x4 = [&](auto swap) {
-      f16x8 xf[2][4];
-#pragma unroll
-      for (int tt = 0; tt < 4; ++tt) xf[0][tt] = as_f16x8(xt[tt * 32 * 64]);
-      const u32x4* xp = xt;
-      for (int g = 0; g < 16; ++g) {
-        static_for<2>([&](auto kc) {
-          constexpr int kk = decltype(kc)::value, cur = kk, nxt = cur ^ 1;
-          static_for<16>([&](auto jc) {
-            constexpr int j = decltype(jc)::value, mt = j >> 2, tt = j & 3;
-            if constexpr (decltype(swap)::value) acc[tt][mt] = mfma_f16_32x32x16(xf[cur][tt], as_f16x8(rg[kk * 4 + mt]), acc[tt][mt]);
-            else acc[tt][mt] = mfma_f16_32x32x16(as_f16x8(rg[kk * 4 + mt]), xf[cur][tt], acc[tt][mt]);
-            if constexpr (j < 4) xf[nxt][j] = as_f16x8(xp[(j * 32 + kk + 1) * 64]);
-            if constexpr (tt == 3) rg[kk * 4 + mt] = (wp + (kk * 4 + mt + 8) * 64)[ul];
-            __builtin_amdgcn_sched_barrier(0);
-          });
-        });
-        xp += 2 * 64;
-        wp += 8 * 64;
-      }
+        for (int tt = 0; tt < 8; ++tt)
+          acc[tt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bf[mt]), as_bf16x8(ones), acc[tt][mt], 0, 0, 0);
     };
-    gemm_x4(std::false_type{});
+    add_bias();
+    gemm_x(std::false_type{});
 
+    // LayerNorm of the rows: a token's features lie in four lanes of each of four waves
     struct Pair {
       float s1, s2;
     };
-    Pair* red = reinterpret_cast<Pair*>(lds + kXtU4);  // [4 waves][128 tokens]
-    auto layer_norm = [&](const float* g, const float* be) {
+    Pair* red = reinterpret_cast<Pair*>(lds + kXtU4);  // [4 waves][128 tokens], in place of the hidden rows
+    auto layer_norm = [&](const float* g, const float* be) __attribute__((always_inline)) {
+      const __amdgpu_buffer_rsrc_t gr = resource(g + wave * 128, 512), er = resource(be + wave * 128, 512);
+      const unsigned l = fresh(), q = l >> 4, col = l & 15;
+      f32x4 g4[8], b4[8];
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
+      for (int mt = 0; mt < 8; ++mt) {
+        g4[mt] = __builtin_bit_cast(f32x4, load16(gr, q * 16, mt * 64));
+        b4[mt] = __builtin_bit_cast(f32x4, load16(er, q * 16, mt * 64));
+      }
+#pragma unroll
+      for (int tt = 0; tt < 8; ++tt) {
         float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
+        for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) {
+          for (int i = 0; i < 4; ++i) {
             s1 += acc[tt][mt][i];
             s2 = __builtin_fmaf(acc[tt][mt][i], acc[tt][mt][i], s2);
           }
-        s1 = halves_sum(s1);
-        s2 = halves_sum(s2);
-        if (half == 0) red[wave * kBlk + tt * 32 + l32] = Pair{s1, s2};
+        s1 = quads_sum(s1);
+        s2 = quads_sum(s2);
+        if (q == 0) red[wave * kBlk + tt * 16 + col] = Pair{s1, s2};
+        __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
-      const f32x4 *gw = reinterpret_cast<const f32x4*>(g + wave * 128), *bw = reinterpret_cast<const f32x4*>(be + wave * 128);
-      float mu[4], rs[4];
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) {
+      for (int tt = 0; tt < 8; ++tt) {
         float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          const Pair p = red[w * kBlk + tt * 32 + l32];
+          const Pair p = red[w * kBlk + tt * 16 + col];
           s1 += p.s1;
           s2 += p.s2;
         }
-        mu[tt] = s1 * (1.0f / kDT);
-        const float var = __builtin_fmaxf(__builtin_fmaf(-mu[tt], mu[tt], s2 * (1.0f / kDT)), 0.0f);
-        rs[tt] = 1.0f / sqrtf(var + 1e-5f);
+        const float mu = s1 * (1.0f / kDT);
+        const float var = __builtin_fmaxf(__builtin_fmaf(-mu, mu, s2 * (1.0f / kDT)), 0.0f);
+        const float rs = 1.0f / sqrtf(var + 1e-5f), shift = -mu * rs;
+#pragma unroll
+        for (int mt = 0; mt < 8; ++mt)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[tt][mt][e] = __builtin_fmaf(__builtin_fmaf(acc[tt][mt][e], rs, shift), g4[mt][e], b4[mt][e]);
+        __builtin_amdgcn_sched_barrier(0);
       }
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 g4 = (gw + mt * 8 + q * 2)[half], b4 = (bw + mt * 8 + q * 2)[half];
-#pragma unroll
-          for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) acc[tt][mt][q * 4 + e] = (acc[tt][mt][q * 4 + e] - mu[tt]) * rs[tt] * g4[e] + b4[e];
-        }
-      }
-    };
-    auto put_x = [&]() {
-#pragma unroll
-      for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-          for (int s = 0; s < 2; ++s) xt[(tt * 32 + wave * 8 + mt * 2 + s) * 64] = store_half(acc[tt][mt], s);
     };
     layer_norm(a.ln1_g, a.ln1_b);
     put_x();
-    // second FFN product's bias
+    load_bf();
+    u32x4 b1[4];
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt) bf[mt] = as_bf16x8((bp + mt * 64)[ul]);
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-      for (int tt = 0; tt < 4; ++tt) acc[tt][mt] = mfma_32x32x16(bf[mt], ones, acc[tt][mt]);
-    bp += 4 * 64;
-    bf16x8 b1[2] = {as_bf16x8(bp[ul]), as_bf16x8((bp + 64)[ul])};
+    for (int mt = 0; mt < 4; ++mt) b1[mt] = load16(br, l16b, bp + mt * 1024);
+    add_bias();  // the second FFN product's
     __syncthreads();
+    read_x();
 
     for (int c = 0; c < a.chunks; ++c) {
-      u32x4 ph[4][4];  // [token tile][quarter]
-      {
-        f32x16 h[4][2];
+      // 64 hidden features per wave
+      f32x4 h[8][4];
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
+      for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-          for (int tt = 0; tt < 4; ++tt) bias_v(h[tt][mt], b1[mt], ones);
-        f16x8 xf[2][4];
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) xf[0][tt] = as_f16x8(xt[tt * 32 * 64]);
-        const u32x4* xp = xt;
-        for (int g = 0; g < 8; ++g) {
-          static_for<4>([&](auto kc) {
-            constexpr int kk = decltype(kc)::value, cur = kk & 1, nxt = cur ^ 1;
-            static_for<8>([&](auto jc) {
-              constexpr int j = decltype(jc)::value, mt = j >> 2, tt = j & 3;
-              mfma_v(h[tt][mt], as_f16x8(rg[kk * 2 + mt]), xf[cur][tt]);
-              if constexpr (j < 4) xf[nxt][j] = as_f16x8(xp[(j * 32 + kk + 1) * 64]);
-              if constexpr (tt == 3) rg[kk * 2 + mt] = (wp + (kk * 2 + mt + 8) * 64)[ul];
-              __builtin_amdgcn_sched_barrier(0);
-            });
-          });
-          xp += 4 * 64;
-          wp += 8 * 64;
-        }
-        asm volatile("s_nop 15\n\ts_nop 7" : "+v"(h[0][0]), "+v"(h[0][1]), "+v"(h[1][0]), "+v"(h[1][1]), "+v"(h[2][0]), "+v"(h[2][1]), "+v"(h[3][0]), "+v"(h[3][1]));
-        bp += 2 * 64;
-        b1[0] = as_bf16x8(bp[ul]);
-        b1[1] = as_bf16x8((bp + 64)[ul]);
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            f32x8 t;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) t[e] = __builtin_fmaxf(h[tt][q >> 1][(q & 1) * 8 + e], 0.0f);
-            ph[tt][q] = __builtin_bit_cast(u32x4, __builtin_convertvector(t, f16x8));
-          }
+        for (int tt = 0; tt < 8; ++tt) bias_v(h[tt][mt], b1[mt], ones);
+      const u32x4* xp = lds + fresh();
+      u32x2 ph[8][4];
+      // ReLU and rounding of a finished tile; half of them are at once what another wave reads
+      auto finish = [&](auto tc, auto mc) __attribute__((always_inline)) {
+        constexpr int tt = decltype(tc)::value, mt = decltype(mc)::value;
+        const f16x4 z = {0, 0, 0, 0};
+        ph[tt][mt] = __builtin_bit_cast(u32x2, __builtin_elementwise_max(__builtin_convertvector(h[tt][mt], f16x4), z));
+      };
+      auto step = [&](auto kc, auto last) __attribute__((always_inline)) {
+        constexpr int kk = decltype(kc)::value;
+        static_for<32>([&](auto jc) {
+          constexpr int j = decltype(jc)::value, mt = j >> 3, tt = (mt & 1) ? 7 - (j & 7) : (j & 7);
+          mfma_v(h[tt][mt], rg[kk * 4 + mt], f[kk][tt]);
+          if constexpr (!decltype(last)::value && j % 3 == 0 && j < 24) f[kk ^ 1][j / 3] = xp[(j / 3 * 16 + kk + 1) * 64];
+          if constexpr ((j & 7) == 7) rg[kk * 4 + mt] = load16(wr, l16b, wp + (kk * 4 + mt + (int)kBlkRing) * 1024);
+          // the tile whose last MFMA was eight MFMAs ago
+          if constexpr (decltype(last)::value && mt > 0) finish(std::integral_constant<int, 7 - tt>{}, std::integral_constant<int, mt - 1>{});
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      };
+      for (int g = 0; g < 7; ++g) {
+        step(std::integral_constant<int, 0>{}, std::false_type{});
+        step(std::integral_constant<int, 1>{}, std::false_type{});
+        xp += 2 * 64;
+        wp += (int)kBlkRing * 1024;
       }
+      step(std::integral_constant<int, 0>{}, std::false_type{});
+      step(std::integral_constant<int, 1>{}, std::true_type{});
+      wp += (int)kBlkRing * 1024;
+      asm volatile("s_nop 15\n\ts_nop 7" : "+v"(h[0][3]), "+v"(h[1][3]), "+v"(h[2][3]), "+v"(h[3][3]), "+v"(h[4][3]), "+v"(h[5][3]), "+v"(h[6][3]), "+v"(h[7][3]));
+      static_for<8>([&](auto tc) { finish(tc, std::integral_constant<int, 3>{}); });
+      bp += 4 * 1024;
 #pragma unroll
-      for (int tt = 0; tt < 4; ++tt) hid[(tt * 4 + wave) * 64] = ph[tt][0];
+      for (int mt = 0; mt < 4; ++mt) b1[mt] = load16(br, l16b, bp + mt * 1024);
+      // Stage q holds feature tile q of every wave: two K steps, each half of one wave's and half of the next's.
+      auto put_h = [&](int q) __attribute__((always_inline)) {
+        u32x2* dst = reinterpret_cast<u32x2*>(lds + kXtU4 + (q & 1) * kHidU4 + (wave >> 1) * 64 + fresh()) + (wave & 1);
+#pragma unroll
+        for (int tt = 0; tt < 8; ++tt) dst[tt * 2 * 64 * 2] = ph[tt][q];
+      };
+      put_h(0);
+      put_h(1);
+      __syncthreads();
+#pragma unroll
+      for (int tt = 0; tt < 8; ++tt) f[0][tt] = lds[kXtU4 + tt * 2 * 64 + ul];
       static_for<4>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
-        __syncthreads();
-        if constexpr (q < 3) {
-#pragma unroll
-          for (int tt = 0; tt < 4; ++tt) hid[((q + 1) & 1) * kHidU4 + (tt * 4 + wave) * 64] = ph[tt][q + 1];
-        }
-        const u32x4* hp = hid + (q & 1) * kHidU4;
-        f16x8 hf[2][4];
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) hf[0][tt] = as_f16x8(hp[tt * 4 * 64]);
-        static_for<4>([&](auto kc) {
-          constexpr int kk = decltype(kc)::value, cur = kk & 1, nxt = cur ^ 1;
-          static_for<16>([&](auto jc) {
-            constexpr int j = decltype(jc)::value, mt = j >> 2, tt = j & 3;
-            acc[tt][mt] = mfma_f16_32x32x16(as_f16x8(rg[cur * 4 + mt]), hf[cur][tt], acc[tt][mt]);
-            if constexpr (j < 4 && kk < 3) hf[nxt][j] = as_f16x8(hp[(j * 4 + kk + 1) * 64]);
-            if constexpr (tt == 3) rg[cur * 4 + mt] = (wp + (cur * 4 + mt + 8) * 64)[ul];
+        const u32x4* hp = lds + kXtU4 + (q & 1) * kHidU4 + ul;
+        const u32x4* hn = lds + kXtU4 + ((q + 1) & 1) * kHidU4 + ul;
+        static_for<2>([&](auto kc) {
+          constexpr int kk = decltype(kc)::value;
+          if constexpr (kk == 1) {
+            // Every wave has read all of stage q: stage q + 2 takes its place, and stage q + 1, written a step ago, is complete.
+            __syncthreads();
+            if constexpr (q < 2) put_h(q + 2);
+          }
+          static_for<64>([&](auto jc) {
+            constexpr int j = decltype(jc)::value, mt = j >> 3, tt = (mt & 1) ? 7 - (j & 7) : (j & 7);
+            acc[tt][mt] = mfma_f16_16x16x32(as_f16x8(rg[mt]), as_f16x8(f[kk][tt]), acc[tt][mt]);
+            if constexpr (j % 4 == 0 && j < 32) {
+              if constexpr (kk == 0) f[1][j / 4] = hp[(j / 4 * 2 + 1) * 64];
+              else if constexpr (q < 3) f[0][j / 4] = hn[j / 4 * 2 * 64];
+              else f[0][j / 4] = lds[j / 4 * 16 * 64 + ul];
+            }
+            if constexpr ((j & 7) == 7) rg[mt] = load16(wr, l16b, wp + (mt + (int)kBlkRing) * 1024);
             __builtin_amdgcn_sched_barrier(0);
           });
-          if constexpr (cur == 1) wp += 8 * 64;
+          wp += (int)kBlkRing * 1024;
         });
       });
     }
     layer_norm(a.ln2_g, a.ln2_b);
-    asm volatile("" : "+s"(xu));
+    if constexpr (!LAST) load_bf();  // in front of the stores: loads are counted in order with them
 #pragma unroll
-    for (int tt = 0; tt < 4; ++tt)
+    for (int tt = 0; tt < 8; ++tt)
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          (xu + ((tt * 4 + mt) * 4 + q) * 64)[ul] = f32x4{acc[tt][mt][q * 4], acc[tt][mt][q * 4 + 1], acc[tt][mt][q * 4 + 2], acc[tt][mt][q * 4 + 3]};
+      for (int mt = 0; mt < 8; ++mt) store16(xr, l16b, (tt * 8 + mt) * 1024, __builtin_bit_cast(u32x4, acc[tt][mt]));
     if constexpr (!LAST) {
       put_x();
       __syncthreads();
+      read_x();
     }
   }
   if constexpr (!LAST) {
+    // q, k (a lane holds a token's column) and v (a lane holds a feature's column of tokens, as the attention's second product wants it)
+    const __amdgpu_buffer_rsrc_t qr = resource(a.qkv + (blk * 4 + wave) * (kBlk * 3 * kDT / 8 / 4), kBlk * 3 * kDT * 2 / 4);
     static_for<3>([&](auto rc) {
       constexpr int r = decltype(rc)::value;
-      bf16x8 bf[4];
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt) bf[mt] = as_bf16x8((bp + (r * 4 + mt) * 64)[ul]);
+      for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-      for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-        for (int tt = 0; tt < 4; ++tt) {
+        for (int tt = 0; tt < 8; ++tt) {
           if constexpr (r < 2) bias_a(acc[tt][mt], bf[mt], ones);
           else bias_a(acc[tt][mt], ones, bf[mt]);
         }
-      f16x8 xf[2][4];
-#pragma unroll
-      for (int tt = 0; tt < 4; ++tt) xf[0][tt] = as_f16x8(xt[tt * 32 * 64]);
-      const u32x4* xp = xt;
-      for (int g = 0; g < 16; ++g) {
-        static_for<2>([&](auto kc) {
-          constexpr int kk = decltype(kc)::value, cur = kk, nxt = cur ^ 1;
-          static_for<16>([&](auto jc) {
-            constexpr int j = decltype(jc)::value, mt = j >> 2, tt = j & 3;
-            if constexpr (r == 2) acc[tt][mt] = mfma_f16_32x32x16(xf[cur][tt], as_f16x8(rg[kk * 4 + mt]), acc[tt][mt]);
-            else acc[tt][mt] = mfma_f16_32x32x16(as_f16x8(rg[kk * 4 + mt]), xf[cur][tt], acc[tt][mt]);
-            if constexpr (j < 4) xf[nxt][j] = as_f16x8(xp[(j * 32 + kk + 1) * 64]);
-            if constexpr (tt == 3) rg[kk * 4 + mt] = (wp + (kk * 4 + mt + 8) * 64)[ul];
-            __builtin_amdgcn_sched_barrier(0);
-          });
+      if constexpr (r > 0) read_x();
+      gemm_x(std::integral_constant<bool, r == 2>{});
+      if constexpr (r < 2) load_bf();
+      static_for<16>([&](auto uc) {
+        constexpr int u = decltype(uc)::value;
+        static_for<2>([&](auto hc) {
+          constexpr int head = decltype(hc)::value;
+          const int at = ((head * 3 + r) * 16 + u) * 1024;
+          if constexpr (r < 2) store16(qr, l16b, at, pack8(acc[u >> 1][head * 4 + 2 * (u & 1)], acc[u >> 1][head * 4 + 2 * (u & 1) + 1]));
+          else store16(qr, l16b, at, pack8(acc[2 * (u >> 2)][head * 4 + (u & 3)], acc[2 * (u >> 2) + 1][head * 4 + (u & 3)]));
         });
-        xp += 2 * 64;
-        wp += 8 * 64;
-      }
-      u32x4* og = a.qkv + blk * (kBlk * 3 * kDT / 8) + (size_t)wave * (2 * 3 * 1024);
-#pragma unroll
-      for (int tt = 0; tt < 4; ++tt)
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt)
-#pragma unroll
-          for (int s = 0; s < 2; ++s) {
-            const int head = mt >> 1;
-            const int at = r < 2 ? tt * 4 + (mt & 1) * 2 + s : (tt * 2 + s) * 2 + (mt & 1);
-            (og + (head * 3 + r) * 1024 + at * 64)[ul] = store_half(acc[tt][mt], s);
-          }
+      });
     });
   }
 }
+
 // ------------------------------------------------------------------------------------------
 // Packing: fragment f of wave w of launch li.  grid (fragments of a wave), 256 threads, a wave each.
 // ------------------------------------------------------------------------------------------
@@ -359,48 +373,49 @@ struct PackArgs {
 };
 
 __global__ __launch_bounds__(256) void pack_weights_kernel(PackArgs a) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, half = lane >> 5, l32 = lane & 31;
-  int f = blockIdx.x;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, quad = lane >> 4, l16 = lane & 15;
+  int f = blockIdx.x, second = 16;  // second: elements from the first four of a lane's eight to the others
   const uint16_t* src;
   const int layer_frags = 128 + a.d_ffn / 2;
   if (a.out_w && f < layer_frags) {
     if (f < 128) {
-      src = a.out_w + (size_t)(wave * 128 + (f & 3) * 32 + l32) * kDT + (f >> 2) * 16;
+      src = a.out_w + (size_t)(wave * 128 + (f & 7) * 16 + l16) * kDT + (f >> 3) * 32;
     } else {
       const int c = (f - 128) >> 7, g = (f - 128) & 127;
       if (g < 64) {
-        src = a.ffn1_w + (size_t)(c * 256 + wave * 64 + (g & 1) * 32 + l32) * kDT + (g >> 1) * 16;
+        src = a.ffn1_w + (size_t)(c * 256 + wave * 64 + (g & 3) * 16 + l16) * kDT + (g >> 2) * 32;
       } else {
-        const int q = (g - 64) >> 4, k = ((g - 64) >> 2) & 3;
-        src = a.ffn2_w + (size_t)(wave * 128 + (g & 3) * 32 + l32) * a.d_ffn + c * 256 + k * 64 + q * 16;
+        const int q = (g - 64) >> 4, k = ((g - 64) >> 3) & 1;
+        src = a.ffn2_w + (size_t)(wave * 128 + (g & 7) * 16 + l16) * a.d_ffn + c * 256 + k * 128 + q * 16;
+        second = 64;
       }
     }
   } else {
     if (a.out_w) f -= layer_frags;
-    src = a.in_w + (size_t)((f >> 7) * kDT + wave * 128 + (f & 3) * 32 + l32) * kDT + ((f & 127) >> 2) * 16;
+    src = a.in_w + (size_t)((f >> 7) * kDT + wave * 128 + (f & 7) * 16 + l16) * kDT + ((f & 127) >> 3) * 32;
   }
-  const u32x2 lo = *reinterpret_cast<const u32x2*>(src + half * 4), hi = *reinterpret_cast<const u32x2*>(src + half * 4 + 8);
+  const u32x2 lo = *reinterpret_cast<const u32x2*>(src + quad * 4), hi = *reinterpret_cast<const u32x2*>(src + quad * 4 + second);
   a.w[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = u32x4{lo[0], lo[1], hi[0], hi[1]};
 }
 
 __global__ __launch_bounds__(256) void pack_bias_kernel(PackArgs a) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31;
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15;
   int f = blockIdx.x;
   float b;
-  const int layer_frags = 8 + a.d_ffn / 128;
+  const int layer_frags = 16 + a.d_ffn / 64;
   if (a.out_b && f < layer_frags) {
-    if (f < 4) b = a.out_b[wave * 128 + f * 32 + l32];
-    else if (f < 8) b = a.ffn2_b[wave * 128 + (f - 4) * 32 + l32];
-    else b = a.ffn1_b[((f - 8) >> 1) * 256 + wave * 64 + (f & 1) * 32 + l32];
+    if (f < 8) b = a.out_b[wave * 128 + f * 16 + l16];
+    else if (f < 16) b = a.ffn2_b[wave * 128 + (f - 8) * 16 + l16];
+    else b = a.ffn1_b[((f - 16) >> 2) * 256 + wave * 64 + (f & 3) * 16 + l16];
   } else {
     if (a.out_b) f -= layer_frags;
-    b = a.in_b[(f >> 2) * kDT + wave * 128 + (f & 3) * 32 + l32];
+    b = a.in_b[(f >> 3) * kDT + wave * 128 + (f & 7) * 16 + l16];
   }
   const float hi = bf16_bits_to_f32(f32_to_bf16_bits(b));
   float mid = bf16_bits_to_f32(f32_to_bf16_bits(b - hi)), lo = (b - hi) - mid;
   if (!(__builtin_fabsf(hi) < __builtin_huge_valf())) mid = lo = 0.0f;
   u32x4 v = {pack_bf16x2(hi, mid), pack_bf16x2(lo, 0.0f), 0u, 0u};
-  if (lane >= 32) v = u32x4{0u, 0u, 0u, 0u};
+  if (lane >= 16) v = u32x4{0u, 0u, 0u, 0u};
   a.bias[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = v;
 }
 

@@ -91,3 +91,53 @@ def test_in_place_compaction_holds_a_chunk_before_it_stores_one():
             behind = ops[i + 1:i + 2 + 2 * per]
             stores = [j for j, op in enumerate(behind) if op.startswith("global_store")]
             assert not stores or not any("vmcnt" in op for op in behind[:stores[0]]), (name, behind)
+
+
+def _registers(text):
+    """{("v", 3), ("v", 4), ...} named in an operand list"""
+    out = set()
+    for kind, one, lo, hi in re.findall(r"\b([av])(?:(\d+)\b|\[(\d+):(\d+)\])", text):
+        out |= {(kind, int(one))} if one else {(kind, i) for i in range(int(lo), int(hi) + 1)}
+    return out
+
+
+def test_written_out_matrix_instructions_keep_their_distances():
+    """The compiler does not look into inline assembly for hazards: no operand of such a matrix instruction may come from a vector
+    instruction less than two wait states before it, and nothing but a matrix instruction may touch its result less than 19 behind."""
+    seen = 0
+    for name, body in kernels("mapper_block.hip"):
+        if "encoder_block_kernel" not in name:
+            continue
+        lines = [l.strip() for l in body.splitlines()]
+        ops, inside = [], False
+        for l in lines:
+            inside = l.startswith(";;#ASMSTART") or (inside and not l.startswith(";;#ASMEND"))
+            if re.match(r"[vsdgb][a-z]*_", l):
+                ops.append((l, inside))
+        for i, (op, written_out) in enumerate(ops):
+            if not (written_out and op.startswith("v_mfma")):
+                continue
+            seen += 1
+            dst, src = op.split(None, 1)[1].split(",", 1)
+            dst, src, states = _registers(dst), _registers(src), 0
+            for before, _ in reversed(ops[max(0, i - 2):i]):
+                states += 1 + (int(before.split()[1]) if before.startswith("s_nop") else 0)
+                if before.startswith("v_") and not before.startswith("v_mfma") and states <= 2:
+                    assert not _registers(before.split(None, 1)[1].split(",", 1)[0]) & src, (name, before, op)
+            states = 0
+            for behind, _ in ops[i + 1:i + 20]:
+                if states >= 19 or behind.startswith("s_cbranch"):
+                    break
+                assert behind.startswith("v_mfma") or not _registers(behind) & dst, (name, op, behind)
+                # a matrix instruction behind it holds the next one back for four passes
+                states += 1 + (int(behind.split()[1]) if behind.startswith("s_nop") else 3 if behind.startswith("v_mfma") else 0)
+    assert seen >= 500
+
+
+def test_encoder_block_keeps_its_registers():
+    """256 accumulators and 128 more for the hidden features leave little: nothing may be spilled inside the loops over K."""
+    blocks = [(name, body) for name, body in kernels("mapper_block.hip") if "encoder_block_kernel" in name]
+    assert len(blocks) == 3
+    for name, body in blocks:
+        for loop in re.findall(r"^(\.LBB\w+):(.*?)s_cbranch_scc\d \1$", body, re.M | re.S):
+            assert "v_mfma" not in loop[1] or "scratch_" not in loop[1], name

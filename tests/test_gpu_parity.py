@@ -476,6 +476,22 @@ def test_mapper_on_both_sides_of_the_small_tiles(L, N):
     pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("L,N", [(32, 129), (26, 191), (2, 2175), (2, 2176), (2, 2177), (1, 4096)])
+def test_mapper_at_the_edges_of_a_block(L, N):
+    """The large tiles take blocks of 128 rows: one row in a layer's last block, all but one, a whole one, keys that end inside and at the
+    end of an attention tile of 64, layers of several blocks side by side, a last window of whole blocks."""
+    case = synth.scaled_case(synth.CASES["llama_8k"], name="block", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=N, N_q=1, chunk=1,
+                             n_planted=0)
+    w = synth.make_mapper_weights(case.H_kv, case.H_l)
+    g = torch.Generator().manual_seed(600 + N)
+    X = (torch.rand(L, case.H_kv, N, generator=g) ** 8) * (1.0 + torch.arange(L).view(-1, 1, 1) % 7)
+    ctx = _ctx(case, w)
+    y = pk.proxykv_map(ctx, X.float().cuda())
+    torch.cuda.synchronize()
+    assert_close(y, oracle.mapper(X.float(), w, L), f"map {L} layers, N={N}")
+    pk.proxykv_destroy(ctx)
+
+
 def test_mapper_with_scores_beyond_the_half_range():
     """Sum-form scores with an attention sink (Sec. 3 prints the feature as a sum over the query axis, so one key can
     collect a share of every row): the first conv block's output reaches 1.4e5, beyond what IEEE half holds.  The
