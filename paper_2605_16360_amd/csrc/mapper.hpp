@@ -74,27 +74,6 @@ __device__ __forceinline__ float max16_8(const f32x16& a, const f32x16& b) {
   return __builtin_fmaxf(m, b[15]);
 }
 
-// max / sum over the two half-waves without an LDS round trip: the swap leaves the lower half's value in both
-// halves of the first register and the upper half's in both halves of the second
-__device__ __forceinline__ float halves_max(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __builtin_fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float halves_sum(float v) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// the same over the four quarters of 16 lanes
-__device__ __forceinline__ float quads_sum(float v) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return halves_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
-}
-__device__ __forceinline__ float quads_max(float v) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-  return halves_max(__builtin_fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
-}
-
 // rows of every layer of a batch on a GEMM's M axis: `valid` of them, `stride` apart (a multiple of 256)
 struct RowSpace {
   int layers, valid, stride;

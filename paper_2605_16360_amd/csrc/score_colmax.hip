@@ -2,11 +2,15 @@
 // reduced over the query axis to one score per context key): per context key, the maximum over all
 // reconstruction queries and over the query heads of the GQA group of exp(logit - lse).
 //
-// The logit matrix is never stored: Q K^T tiles are recomputed with v_mfma_f32_32x32x16_bf16.  The
+// The logit matrix is never stored: Q K^T tiles are recomputed.  The
 // context keys of a workgroup (the "columns", 32*NCOL per wave) stay in registers as the MFMA B
 // operand for the whole kernel; the queries (the "rows") stream through 16 KB LDS tiles.  With
-// rows on the MFMA M axis a lane owns ONE key column and 16 query rows of every tile, so the
-// maximum over queries runs inside a lane and needs one cross-lane step (lane ^ 32) at the end.
+// rows on the MFMA M axis a lane owns a key column and some query rows of every tile, so the
+// maximum over queries runs inside a lane and needs one or two cross-lane steps at the end.
+//
+// The max form keeps the matrix pipe busy 83 % of the cycles, so the chip's power sets its clock: it uses v_mfma_f32_16x16x32_bf16,
+// which draw less per flop than 32 x 32 x 16.  Both passes, in steady repetition: 16 x 32 heads of 64, 8192 keys 9390 -> 9030 us;
+// 28 x 12 heads of 128 (pass 1 with the same), 10 007 keys 18 440 -> 17 000.
 //
 // With c = log2(e) / sqrt(d) the probability is p = 2^(c*s - L2), L2 the row's log2-sum-exp2.
 // Pass 1 stores -L2 / c per query row; it is fed to the MFMA as the accumulator's initial value,
@@ -42,10 +46,11 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
                                                                float* __restrict__ x, int L_s, int H_q, int G, int N, int N_q,
                                                                float c, float inv_c, int splits, int q_splits) {
   using C = ScoreCfg<D>;
+  using R = Rows32<D, 16>;
   static_assert(NCOL % 2 == 0, "column sub-tiles are processed in pairs");
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
   __shared__ __attribute__((aligned(16))) float lds_nl[kNBuf * C::ROWS];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, quad = lane >> 4;
   constexpr int KB = 128 * NCOL;
   const int H_kv = H_q / G;
   // a group's blocks: its key blocks (they stream the same queries), each in q_splits parts
@@ -55,19 +60,16 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
   const int n0 = (QSPLIT ? gb.item / q_splits : gb.item) * KB;
   const uint16_t* kc = k_ctx + (size_t)(l * H_kv + hs) * N * D;
 
-  bf16x8 b[NCOL][C::KK];
-  int kn[NCOL];
+  constexpr int NT = 2 * NCOL;  // column tiles of 16
+  bf16x8 b[NT][R::KK];
+  int kn[NT];
+  float runmax[NT];
 #pragma unroll
-  for (int cs = 0; cs < NCOL; ++cs) {
-    kn[cs] = n0 + (wave * NCOL + cs) * 32 + l32;
-    const int row = kn[cs] < N ? kn[cs] : N - 1;
-#pragma unroll
-    for (int kk = 0; kk < C::KK; ++kk)
-      b[cs][kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(kc + (size_t)row * D + kk * 16 + half * 8));
+  for (int ct = 0; ct < NT; ++ct) {
+    kn[ct] = n0 + (wave * NT + ct) * 16 + (lane & 15);
+    R::columns(b[ct], kc, kn[ct] < N ? kn[ct] : N - 1, lane);
+    runmax[ct] = kNegInf;
   }
-  float runmax[NCOL];
-#pragma unroll
-  for (int cs = 0; cs < NCOL; ++cs) runmax[cs] = kNegInf;
 
   // tiles are fetched in order: head g = 0..G-1 of the group, query tile qt = 0..nqt-1
   const int nqt = (N_q + C::ROWS - 1) / C::ROWS;
@@ -104,82 +106,72 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
   if (total > 2) fetch_next();
   __syncthreads();
 
-  // Fragments and initial values of the current 32-row sub-tile, refilled in place: a[kk] right behind
-  // the last MFMA that consumes it, init behind the pair's second MFMA (the last one that reads it).
-  bf16x8 a[C::KK];
-  f32x16 init;
-  auto load_a = [&](int t, int s, int kk) {
-    a[kk] = frag_read<D>(lds + (t % kNBuf) * C::TILE_U4, s * 32 + l32, kk * 2 + half);
+  // Fragments and initial values of the current 32-row sub-tile, refilled in place: a[rt][kk] right behind
+  // the last MFMA that consumes it, init[rt] behind the last one that starts from it.
+  bf16x8 a[2][R::KK];
+  f32x4 init[2];
+  auto load_a = [&](int t, int s, int rt, int kk) {
+    a[rt][kk] = frag_read<D>(lds + (t % kNBuf) * C::TILE_U4, s * 32 + rt * 16 + (lane & 15), kk * 4 + quad);
   };
-  auto load_init = [&](int t, int s) {
-    const float* nl = lds_nl + (t % kNBuf) * C::ROWS;
-    // accumulator rows of this lane: (r/4)*8 + half*4 + r%4
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const f32x4 v = *reinterpret_cast<const f32x4*>(&nl[s * 32 + j * 8 + half * 4]);
-      init[4 * j + 0] = v[0];
-      init[4 * j + 1] = v[1];
-      init[4 * j + 2] = v[2];
-      init[4 * j + 3] = v[3];
-    }
+  auto load_init = [&](int t, int s, int rt) {
+    init[rt] = *reinterpret_cast<const f32x4*>(&lds_nl[(t % kNBuf) * C::ROWS + s * 32 + rt * 16 + quad * 4]);
   };
 #pragma unroll
-  for (int kk = 0; kk < C::KK; ++kk) load_a(0, 0, kk);
-  load_init(0, 0);
-  f32x16 pend0 = splat16(kNegInf), pend1 = splat16(kNegInf);
+  for (int rt = 0; rt < 2; ++rt) {
+#pragma unroll
+    for (int kk = 0; kk < R::KK; ++kk) load_a(0, 0, rt, kk);
+    load_init(0, 0, rt);
+  }
+  // accumulators of the four column tiles of the pair before
+  f32x4 pend[2][4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) pend[i >> 2][i & 3] = f32x4{kNegInf, kNegInf, kNegInf, kNegInf};
+  // step v of 16: first all of the first sixteen rows, whose MFMAs were done first
+  auto max_step = [&](auto vc, int pp) {
+    constexpr int v = decltype(vc)::value, rt = v >> 3, ct = (v >> 1) & 3, e = (v & 1) * 2;
+    runmax[pp * 4 + ct] = max3f(runmax[pp * 4 + ct], pend[rt][ct][e], pend[rt][ct][e + 1]);
+  };
   constexpr int NP = NCOL / 2;  // pairs per sub-tile
   for (int t = 0; t < total; ++t) {
     static_for<C::SUB * NP>([&](auto ic) {
       constexpr int i = decltype(ic)::value, s = i / NP, pr = i % NP;
       constexpr int pp = (pr + NP - 1) % NP;  // pair whose accumulators are pending
-      constexpr int NM = 2 * C::KK;
-      f32x16 c0, c1;
-      MaxTree w0, w1;
+      constexpr int NM = 8 * R::KK;
+      f32x4 acc[2][4];
       static_for<NM>([&](auto jc) {
-        constexpr int j = decltype(jc)::value, kk = j / 2;
-        if constexpr (j == 0) c0 = mfma_32x32x16(a[0], b[2 * pr][0], init);
-        else if constexpr (j == 1) c1 = mfma_32x32x16(a[0], b[2 * pr + 1][0], init);
-        else if constexpr (j % 2 == 0) c0 = mfma_32x32x16(a[kk], b[2 * pr][kk], c0);
-        else c1 = mfma_32x32x16(a[kk], b[2 * pr + 1][kk], c1);
+        // of two MFMAs in a row one operand is the same: the less of their input changes, the less they draw
+        constexpr int j = decltype(jc)::value, kk = j / 8, rt = (j >> 2) & 1, ct = rt ? 3 - (j & 3) : (j & 3);
+        acc[rt][ct] = mfma_bf16_16x16x32(a[rt][kk], b[4 * pr + ct][kk], kk == 0 ? init[rt] : acc[rt][ct]);
         if constexpr (i == 0 && j == 1) {
           // every wave has finished tile t-1: its buffer takes tile t+2, the registers take tile t+3
           __syncthreads();
           if (t + 2 < total) store(t + 2);
           if (t + 3 < total) fetch_next();
         }
-        if constexpr (pr == NP - 1 && (j & 1)) {
-          // last pair of the sub-tile: refill from the next sub-tile (sub-tile 0 of the next tile after the last)
-          if constexpr (s + 1 < C::SUB) {
-            load_a(t, s + 1, kk);
-            if constexpr (j == 1) load_init(t, s + 1);
-          } else {  // past the last tile this reads a stale buffer, harmlessly
-            load_a(t + 1, 0, kk);
-            if constexpr (j == 1) load_init(t + 1, 0);
-          }
+        if constexpr (pr == NP - 1 && (j & 3) == 3) {
+          // last pair of the sub-tile: refill from the next sub-tile (sub-tile 0 of the next tile after the last;
+          // past the last tile this reads a stale buffer, harmlessly)
+          constexpr int next = s + 1 < C::SUB ? 0 : 1, sn = s + 1 < C::SUB ? s + 1 : 0;
+          load_a(t + next, sn, rt, kk);
+          if constexpr (kk == 0) load_init(t + next, sn, rt);
         }
-        // the 16 v_max3 of the pending pair behind MFMAs 2, 3, ... (its last MFMA has retired by then)
+        // the 16 v_max3 of the pending pair behind MFMAs 2, 3, ... (its last MFMAs have retired by then)
         if constexpr (j >= 2) {
           constexpr int g = j - 2, lo = (16 * g) / (NM - 2), hi = (16 * (g + 1)) / (NM - 2);
-          static_for<hi - lo>([&](auto vc) {
-            constexpr int v = lo + decltype(vc)::value;
-            if constexpr (v < 8) max_step<v>(pend0, w0, runmax[2 * pp]);
-            else max_step<v - 8>(pend1, w1, runmax[2 * pp + 1]);
-          });
+          static_for<hi - lo>([&](auto vc) { max_step(std::integral_constant<int, lo + decltype(vc)::value>{}, pp); });
         }
         __builtin_amdgcn_sched_barrier(0);
       });
-      pend0 = c0;
-      pend1 = c1;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) pend[e >> 2][e & 3] = acc[e >> 2][e & 3];
     });
   }
-  runmax[NCOL - 2] = max16_tree(pend0, runmax[NCOL - 2]);
-  runmax[NCOL - 1] = max16_tree(pend1, runmax[NCOL - 1]);
+  static_for<16>([&](auto vc) { max_step(vc, NP - 1); });
 #pragma unroll
-  for (int cs = 0; cs < NCOL; ++cs) {
-    const float m = __builtin_fmaxf(runmax[cs], swap_halves(runmax[cs]));
-    const float p = __builtin_fminf(__builtin_amdgcn_exp2f(c * m), 1.0f);
-    if (half == 0 && kn[cs] < N) {
-      float* dst = x + (size_t)(l * H_kv + hs) * N + kn[cs];
+  for (int ct = 0; ct < NT; ++ct) {
+    const float p = __builtin_fminf(__builtin_amdgcn_exp2f(c * quads_max(runmax[ct])), 1.0f);
+    if (quad == 0 && kn[ct] < N) {
+      float* dst = x + (size_t)(l * H_kv + hs) * N + kn[ct];
       if constexpr (QSPLIT) atomicMax(reinterpret_cast<unsigned int*>(dst), __float_as_uint(p));
       else *dst = p;
     }
@@ -200,36 +192,45 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
 //
 // With q_splits > 1 the query tiles of a key block are dealt to that many workgroups and x holds their sums one behind the
 // other, [q_splits][L_s * H_kv * N]; sum_parts_kernel adds them up in that order.
-template <int D, int NCOL, bool CAUSAL, bool SPLIT>
+template <int D, int NCOL, int W, bool CAUSAL, bool SPLIT>
 __global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void score_colsum_kernel(const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_ctx,
                                                                const float* __restrict__ neg_lse,
                                                                float* __restrict__ x, int L_s, int H_q, int G, int N, int N_q,
                                                                float c, float inv_c, int splits, int q_splits) {
   using C = ScoreCfg<D>;
+  using R = Rows32<D, W>;
+  using Acc = typename R::Acc;
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
   __shared__ __attribute__((aligned(16))) float lds_nl[kNBuf * C::ROWS];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rows4 = lane / W * 4;
   constexpr int KB = 128 * NCOL;
   const int H_kv = H_q / G;
   // a group's blocks: its key blocks (they stream the same queries), each in q_splits parts
-  const GroupBlock gb = group_block((N + KB - 1) / KB * q_splits);
+  const int per_group = (N + KB - 1) / KB * q_splits;
+  GroupBlock gb = group_block(per_group);
+  if constexpr (CAUSAL) {
+    // the first key block has the most queries; an XCD takes four groups (or as many as fill its 96 places) at a time
+    // (16 x 32 heads of 64, both passes: 4097 tokens 1590 -> 1582 us, 1000 tokens 156 -> 137; all 16 groups at once, whose queries
+    // do not fit the L2, 4097 tokens 1602)
+    const SetItem it = longest_first(blockIdx.x / kScoreXcds, gridDim.x / kScoreXcds / per_group, per_group,
+                                     per_group < 32 ? 128 / per_group : 4);
+    gb = {it.set * kScoreXcds + (int)blockIdx.x % kScoreXcds, it.item};
+  }
   if (gb.group >= L_s * H_kv) return;
   const int l = gb.group / H_kv, hs = gb.group % H_kv;
   const int n0 = gb.item / q_splits * KB, part = gb.item % q_splits;
   const uint16_t* kc = k_ctx + (size_t)(l * H_kv + hs) * N * D;
 
-  bf16x8 b[NCOL][C::KK];
-  int kn[NCOL];
-  float colsum[NCOL];
+  constexpr int NT = 32 * NCOL / W;  // column tiles
+  bf16x8 b[NT][R::KK];
+  int kn[NT];
+  float colsum[NT];
 #pragma unroll
-  for (int cs = 0; cs < NCOL; ++cs) {
-    kn[cs] = n0 + (wave * NCOL + cs) * 32 + l32;
-    const int row = kn[cs] < N ? kn[cs] : N - 1;
-#pragma unroll
-    for (int kk = 0; kk < C::KK; ++kk)
-      b[cs][kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(kc + (size_t)row * D + kk * 16 + half * 8));
-    colsum[cs] = 0.0f;
+  for (int ct = 0; ct < NT; ++ct) {
+    kn[ct] = n0 + (wave * NT + ct) * W + lane % W;
+    R::columns(b[ct], kc, kn[ct] < N ? kn[ct] : N - 1, lane);
+    colsum[ct] = 0.0f;
   }
 
   // tiles are fetched in order: head g = 0..G-1 of the group, query tile qt = 0..nqt-1
@@ -284,57 +285,42 @@ __global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void sc
     constexpr int kUnroll = CAUSAL ? 2 : C::SUB;
 #pragma unroll kUnroll
     for (int s = 0; s < C::SUB; ++s) {
-      bf16x8 a[C::KK];
+      R a;
+      a.read(buf, s * 32, lane);
+      Acc init;
 #pragma unroll
-      for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, s * 32 + l32, kk * 2 + half);
-      // accumulator rows of this lane: (r/4)*8 + half*4 + r%4
-      f32x16 init;
+      for (int r = 0; r < R::E; r += 4) {
+        const f32x4 v = *reinterpret_cast<const f32x4*>(&nl[s * 32 + R::acc_row(r) + rows4]);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(&nl[s * 32 + j * 8 + half * 4]);
-        init[4 * j + 0] = v[0];
-        init[4 * j + 1] = v[1];
-        init[4 * j + 2] = v[2];
-        init[4 * j + 3] = v[3];
+        for (int e = 0; e < 4; ++e) init.set(r + e, v[e]);
+      }
+      Acc acc[NT];
+#pragma unroll
+      for (int ct = 0; ct < NT; ++ct) acc[ct] = a.product(b[ct], init);
+      if (diag) {
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct)
+#pragma unroll
+          for (int r = 0; r < R::E; ++r)
+            acc[ct].set(r, row0 + s * 32 + rows4 + R::acc_row(r) >= kn[ct] ? acc[ct].get(r) : kNegInf);
       }
 #pragma unroll
-      for (int cp = 0; cp < NCOL; cp += 2) {
-        f32x16 acc[2];
+      for (int ct = 0; ct < NT; ++ct) {
+        float v[4];
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          acc[e] = init;
+        for (int r = 0; r < 4; ++r) v[r] = __builtin_amdgcn_exp2f(acc[ct].get(r) * c);
 #pragma unroll
-          for (int kk = 0; kk < C::KK; ++kk) acc[e] = mfma_32x32x16(a[kk], b[cp + e][kk], acc[e]);
-        }
-        if (diag) {
-#pragma unroll
-          for (int e = 0; e < 2; ++e)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const int i = row0 + s * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-              acc[e][r] = i >= kn[cp + e] ? acc[e][r] : kNegInf;
-            }
-        }
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          float s0 = __builtin_amdgcn_exp2f(acc[e][0] * c), s1 = __builtin_amdgcn_exp2f(acc[e][1] * c);
-          float s2 = __builtin_amdgcn_exp2f(acc[e][2] * c), s3 = __builtin_amdgcn_exp2f(acc[e][3] * c);
-#pragma unroll
-          for (int r = 4; r < 16; r += 4) {
-            s0 += __builtin_amdgcn_exp2f(acc[e][r + 0] * c);
-            s1 += __builtin_amdgcn_exp2f(acc[e][r + 1] * c);
-            s2 += __builtin_amdgcn_exp2f(acc[e][r + 2] * c);
-            s3 += __builtin_amdgcn_exp2f(acc[e][r + 3] * c);
-          }
-          colsum[cp + e] += (s0 + s1) + (s2 + s3);
-        }
+        for (int r = 4; r < R::E; ++r) v[r & 3] += __builtin_amdgcn_exp2f(acc[ct].get(r) * c);
+        colsum[ct] += (v[0] + v[1]) + (v[2] + v[3]);
       }
     }
   }
 #pragma unroll
-  for (int cs = 0; cs < NCOL; ++cs) {
-    const float tot = colsum[cs] + swap_halves(colsum[cs]);
-    if (half == 0 && kn[cs] < N) x[((size_t)part * L_s * H_kv + l * H_kv + hs) * N + kn[cs]] = tot;
+  for (int ct = 0; ct < NT; ++ct) {
+    float tot = colsum[ct];
+#pragma unroll
+    for (int o = W; o < 64; o *= 2) tot += __shfl_xor(tot, o, 64);
+    if (lane < W && kn[ct] < N) x[((size_t)part * L_s * H_kv + l * H_kv + hs) * N + kn[ct]] = tot;
   }
 }
 
@@ -382,6 +368,10 @@ hipError_t launch_f32_to_bf16(const float* const in[3], uint16_t* const out[3], 
   return hipGetLastError();
 }
 
+// Columns of an MFMA tile in the sum form.  Where mul, exp2 and add take much longer than the products (d = 64) the wide tile's fewer
+// instructions are level or ahead (24 x 14 heads, 6001 keys, both passes 4303 us, 4317 with 16; one layer of 3000 keys, 300 queries 24.8
+// and 25.2); the causal form spills 20 registers with it (16 x 32 heads, 4097 tokens 1664, 1543 with 16).
+constexpr int kSumW(int d, bool causal) { return d == 64 && !causal ? 32 : 16; }
 constexpr int kMaxCols = 4, kSumCols = 2;  // column sub-tiles per wave of the two forms
 constexpr int64_t kMaxSumParts = 16, kMaxTurns = 64;
 static int64_t pass2_slots(bool sum, int d) { return 256 * (d == 64 ? (sum ? 3 : 2) : (sum ? 2 : 1)); }
@@ -437,7 +427,7 @@ hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const f
   if (grid == 0) return hipErrorInvalidValue;
   float* out = q_splits > 1 ? parts : x;
   auto go = [&](auto dc, auto cc, auto sc) {
-    score_colsum_kernel<decltype(dc)::value, NCOL, decltype(cc)::value, decltype(sc)::value>
+    score_colsum_kernel<decltype(dc)::value, NCOL, kSumW(decltype(dc)::value, decltype(cc)::value), decltype(cc)::value, decltype(sc)::value>
         <<<grid, 256, 0, stream>>>(q, k_ctx, neg_lse, out, L_s, H_q, G, (int)N, (int)N_q, c, inv_c, splits, q_splits);
   };
   auto pick = [&](auto dc) {

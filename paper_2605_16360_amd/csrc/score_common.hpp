@@ -1,5 +1,5 @@
 // Helpers shared by the two scoring passes: tile geometry, the XOR-swizzled LDS tile layout, the
-// global -> register -> LDS staging of a tile, MFMA fragment reads and the v_max3 reduction tree.
+// global -> register -> LDS staging of a tile, MFMA fragment reads and products of 32 rows.
 #pragma once
 #include "common.hpp"
 
@@ -11,7 +11,6 @@ struct ScoreCfg {
   static constexpr int CPR = D / 8;             // 16-byte chunks per row
   static constexpr int ROWS = 8192 / D;         // rows of one streamed tile (16 KB)
   static constexpr int SUB = ROWS / 32;         // 32-row sub-tiles per tile
-  static constexpr int KK = D / 16;             // MFMA k-steps per 32x32 tile
   static constexpr int LOADS = ROWS * CPR / 256;  // 16-byte chunks staged per thread and tile
   static constexpr int TILE_U4 = ROWS * CPR;    // 16-byte units per tile
 };
@@ -36,8 +35,19 @@ inline unsigned group_grid(int64_t n_groups, int64_t per_group) {
   return blocks < (1ll << 31) ? (unsigned)blocks : 0u;
 }
 
+// Item j of n_sets sets of `per` items each, whose items get shorter with their number: `batch` sets at a time, first the longest items
+// of all of them, so that what is left at the end is short.  Not all sets at once: those that run together share an L2.
+struct SetItem {
+  int set, item;
+};
+__device__ __forceinline__ SetItem longest_first(int j, int n_sets, int per, int batch) {
+  const int b = j / (batch * per), r = j - b * (batch * per);
+  const int n = n_sets - b * batch < batch ? n_sets - b * batch : batch;
+  return {b * batch + r % n, r / n};
+}
+
 // XOR swizzle of the 16-byte chunk index inside a row; keeps both the 16-byte tile stores and the
-// MFMA fragment reads (32 consecutive rows, same chunk) spread over all LDS banks.
+// MFMA fragment reads (16 consecutive rows, four neighbouring chunks) spread over all LDS banks.
 template <int D>
 __device__ __forceinline__ int swz(int row) {
   if constexpr (D == 64) return (row & 7) ^ ((row >> 3) & 1);
@@ -88,26 +98,74 @@ __device__ __forceinline__ bf16x8 frag_read(const u32x4* lds, int row, int ch) {
   return as_bf16x8(lds[row * ScoreCfg<D>::CPR + (ch ^ swz<D>(row))]);
 }
 
-// max(seed, a[0..15]) as a tree of v_max3 (depth three); the steps can be placed one by one.
-struct MaxTree {
-  float m0, m1, m2, m3, m4, t0, t1;
+// Products of 32 rows (of an LDS tile) with a tile of W columns (resident), W = 32 with v_mfma_f32_32x32x16_bf16, W = 16 with two
+// v_mfma_f32_16x16x32_bf16 per k-step.  A lane owns column lane % W and E of the 32 rows, acc_row(r) + 4 (lane / W).
+template <int D, int W>
+struct Rows32 {
+  static constexpr int RT = 32 / W, KS = W == 32 ? 16 : 32, KK = D / KS, E = W / 2;
+  struct Acc {
+    std::conditional_t<W == 32, f32x16, f32x4> v[RT];
+    __device__ __forceinline__ float get(int r) const { return W == 32 ? v[0][r] : v[r >> 2][r & 3]; }
+    __device__ __forceinline__ void set(int r, float x) {
+      if constexpr (W == 32) v[0][r] = x;
+      else v[r >> 2][r & 3] = x;
+    }
+  };
+  static __device__ __forceinline__ constexpr int acc_row(int r) { return (r >> 2) * (W == 32 ? 8 : 16) + (r & 3); }
+
+  bf16x8 a[RT][KK];
+  __device__ __forceinline__ void read(const u32x4* lds, int row0, int lane) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) a[rt][kk] = frag_read<D>(lds, row0 + rt * W + lane % W, kk * (KS / 8) + lane / W);
+  }
+  // a column tile's resident fragments: this lane's column is row `row` of a [*, D] matrix
+  static __device__ __forceinline__ void columns(bf16x8 (&b)[KK], const uint16_t* base, int row, int lane) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) b[kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(base + (size_t)row * D + kk * KS + lane / W * 8));
+  }
+  static __device__ __forceinline__ Acc zero() {
+    Acc c;
+#pragma unroll
+    for (int r = 0; r < E; ++r) c.set(r, 0.0f);
+    return c;
+  }
+  __device__ __forceinline__ void step(Acc& c, const bf16x8 (&b)[KK], int rt, int kk) const {
+    if constexpr (W == 32) c.v[rt] = mfma_bf16_32x32x16(a[rt][kk], b[kk], c.v[rt]);
+    else c.v[rt] = mfma_bf16_16x16x32(a[rt][kk], b[kk], c.v[rt]);
+  }
+  // init + rows x one column tile
+  __device__ __forceinline__ Acc product(const bf16x8 (&b)[KK], const Acc& init) const {
+    Acc c = init;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int rt = 0; rt < RT; ++rt) step(c, b, rt, kk);
+    return c;
+  }
+  // the same with NT column tiles, a tile's products of two k-steps NT instructions or more apart
+  template <int NT>
+  __device__ __forceinline__ void products(Acc (&c)[NT], const bf16x8 (&b)[NT][KK], const Acc& init) const {
+#pragma unroll
+    for (int ct = 0; ct < NT; ++ct) c[ct] = init;
+    static_for<KK * RT * NT>([&](auto jc) {
+      constexpr int j = decltype(jc)::value, kk = j / (RT * NT), rt = (j / NT) % RT, ct = rt ? NT - 1 - j % NT : j % NT;
+      step(c[ct], b[ct], rt, kk);
+    });
+  }
 };
-template <int I>
-__device__ __forceinline__ void max_step(const f32x16& a, MaxTree& w, float& run) {
-  if constexpr (I == 0) w.m0 = max3f(a[0], a[1], a[2]);
-  else if constexpr (I == 1) w.m1 = max3f(a[3], a[4], a[5]);
-  else if constexpr (I == 2) w.m2 = max3f(a[6], a[7], a[8]);
-  else if constexpr (I == 3) w.m3 = max3f(a[9], a[10], a[11]);
-  else if constexpr (I == 4) w.m4 = max3f(a[12], a[13], a[14]);
-  else if constexpr (I == 5) w.t0 = max3f(w.m0, w.m1, w.m2);
-  else if constexpr (I == 6) w.t1 = max3f(w.m3, w.m4, a[15]);
-  else run = max3f(run, w.t0, w.t1);
-}
-__device__ __forceinline__ float max16_tree(const f32x16& a, float seed) {
-  MaxTree w;
-  float run = seed;
-  static_for<8>([&](auto ic) { max_step<decltype(ic)::value>(a, w, run); });
-  return run;
+
+// max(seed, the accumulators)
+template <class R>
+__device__ __forceinline__ float max_of(const typename R::Acc& a, float seed) {
+  float m = max3f(a.get(0), a.get(1), a.get(2)), n = max3f(a.get(3), a.get(4), a.get(5));
+#pragma unroll
+  for (int r = 6; r < R::E; r += 4) {
+    m = max3f(m, a.get(r), a.get(r + 1));
+    if (r + 3 < R::E) n = max3f(n, a.get(r + 2), a.get(r + 3));
+  }
+  return max3f(seed, m, n);
 }
 
 constexpr float kNegInf = -__builtin_huge_valf();
@@ -147,13 +205,6 @@ struct LseRegs<true> {
     return -(m + __builtin_amdgcn_logf(l)) * inv_c;
   }
 };
-
-__device__ __forceinline__ f32x16 splat16(float v) {
-  f32x16 r;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) r[i] = v;
-  return r;
-}
 
 }  // namespace
 }  // namespace pkv

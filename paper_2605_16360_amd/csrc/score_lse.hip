@@ -2,17 +2,17 @@
 // row log-sum-exp of every reconstruction query over the N context keys plus the reconstruction
 // keys of its own chunk up to and including itself.
 //
-// The logit matrix is never stored: K Q^T tiles are computed with v_mfma_f32_32x32x16_bf16.  The
+// The logit matrix is never stored: K Q^T tiles are computed with v_mfma_f32_32x32x16_bf16 or v_mfma_f32_16x16x32_bf16.  The
 // queries of a workgroup (the "columns", 32*NCOL per wave) stay in registers as the MFMA B operand
 // for the whole kernel; the keys (the "rows") stream through 16 KB LDS tiles.  With rows on the
-// MFMA M axis a lane owns ONE query column and 16 key rows of every tile, so the sum over keys runs
-// inside a lane and needs one cross-lane step (lane ^ 32) at the end.
+// MFMA M axis a lane owns a query column and some key rows of every tile, so the sum over keys runs
+// inside a lane and needs one or two cross-lane steps at the end.
 //
 // With c = log2(e) / sqrt(d) the kernel accumulates lsum = sum 2^(c*s - m_ref) per lane and column.
 // The vector ALU, not the matrix pipe, bounds this pass (one v_exp_f32 costs two ALU slots), so the
 // work per element is cut to the three instructions that cannot be avoided (fma, exp2, add): no
 // running maximum is tracked.  The reference m_ref is an attained logit of the column; it is only
-// replaced when the sum of one 16-element chain leaves [0, 2^64), which the first chain of every
+// replaced when the sum of one chain of 8 or 16 elements leaves [0, 2^64), which the first chain of every
 // column does by construction (m_ref starts at -1e30) and later chains practically never do.  A term
 // can exceed the reference by up to 2^64 and every term far below it is negligible against the
 // attained one, so neither overflow nor underflow loses anything.  The kernel writes -L2 / c per
@@ -42,7 +42,7 @@ constexpr float kTileRedo = 1.2676506e30f;  // 2^100
 
 // SPLIT: `splits` workgroups per query block, neg_lse holds (reference, sum) pairs [splits][L_s * H_q * N_q].
 // x [n_x] (n_x may be 0) is cleared for a pass 2 whose workgroups raise it.
-template <int D, int NCOL, int MINB, bool SPLIT>
+template <int D, int NCOL, int W, int MINB, bool SPLIT>
 __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_ctx,
                                                                const uint16_t* __restrict__ k_rec,
@@ -50,12 +50,23 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
                                                                int N_q, int chunk, float c, float inv_c, int splits,
                                                                float* __restrict__ x, int64_t n_x) {
   using C = ScoreCfg<D>;
+  using R = Rows32<D, W>;
+  using Acc = typename R::Acc;
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-  const int h = blockIdx.y, l = blockIdx.z, H_kv = H_q / G, hs = h / G;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rows4 = lane / W * 4;
   constexpr int QB = 128 * NCOL;
   const int split = SPLIT ? blockIdx.x % splits : 0;
-  const int i0 = (SPLIT ? blockIdx.x / splits : blockIdx.x) * QB;
+  int h = blockIdx.y, l = blockIdx.z, qb = SPLIT ? blockIdx.x / splits : blockIdx.x;
+  if (!SPLIT && N == 0) {
+    // causal over the whole sequence: the last query block has the most keys; 64 heads (or as many as fill the chip) at a time
+    // (16 x 32 heads of 64, 4097 tokens, both passes: 1625 -> 1590 us; 1000 tokens: 173 -> 156)
+    const int nb = gridDim.x, id = ((int)blockIdx.z * gridDim.y + blockIdx.y) * nb + blockIdx.x;
+    const SetItem it = longest_first(id, gridDim.y * gridDim.z, nb, nb < 16 ? 1024 / nb : 64);
+    qb = nb - 1 - it.item;
+    h = it.set % H_q;
+    l = it.set / H_q;
+  }
+  const int H_kv = H_q / G, hs = h / G, i0 = qb * QB;
   if (n_x > 0) {
     const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int64_t stride = (int64_t)gridDim.x * gridDim.y * gridDim.z * 256;
@@ -65,23 +76,22 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
   const uint16_t* kc = k_ctx + (size_t)(l * H_kv + hs) * N * D;
   const uint16_t* kr = k_rec + (size_t)(l * H_kv + hs) * N_q * D;
 
-  // resident B operand: the wave's queries
-  bf16x8 b[NCOL][C::KK];
-  int qi[NCOL], qlo[NCOL];
+  // resident B operand: the wave's queries, NT tiles of W, NS to 32 columns
+  constexpr int NT = 32 * NCOL / W, NS = 32 / W;
+  bf16x8 b[NT][R::KK];
+  int qi[NT], qlo[NT];
 #pragma unroll
-  for (int cs = 0; cs < NCOL; ++cs) {
-    qi[cs] = i0 + (wave * NCOL + cs) * 32 + l32;
-    const int row = qi[cs] < N_q ? qi[cs] : N_q - 1;
-    qlo[cs] = (row / chunk) * chunk;  // (a column past the last query sees that query's chunk, so that it has a reference too)
-#pragma unroll
-    for (int kk = 0; kk < C::KK; ++kk)
-      b[cs][kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(qh + (size_t)row * D + kk * 16 + half * 8));
+  for (int ct = 0; ct < NT; ++ct) {
+    qi[ct] = i0 + (wave * NT + ct) * W + lane % W;
+    const int row = qi[ct] < N_q ? qi[ct] : N_q - 1;
+    qlo[ct] = (row / chunk) * chunk;  // (a column past the last query sees that query's chunk, so that it has a reference too)
+    R::columns(b[ct], qh, row, lane);
   }
-  float nref[NCOL], lsum[NCOL];  // nref = -m_ref
+  float nref[NT], lsum[NT];  // nref = -m_ref
 #pragma unroll
-  for (int cs = 0; cs < NCOL; ++cs) {
-    nref[cs] = 1.0e30f;
-    lsum[cs] = 0.0f;
+  for (int ct = 0; ct < NT; ++ct) {
+    nref[ct] = 1.0e30f;
+    lsum[ct] = 0.0f;
   }
 
   // tile list: the context tiles, then the reconstruction tiles from the start of the block's chunk to
@@ -103,68 +113,73 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
   };
   auto fetch = [&](int t) { fetch_to(regs, t); };
 
-  // sum of one chain: 16 x (fma, exp2, add); re-based when it leaves [0, 2^64)
-  auto accumulate = [&](const f32x16& acc, int cs) {
-    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f, s3 = 0.0f;
+  // sum of one chain (32 keys, of which a lane has R::E, and one column tile), no check: fma, exp2, add per element
+  auto fast_sum = [&](const Acc& acc, int ct) {
+    float s[4];
 #pragma unroll
-    for (int r = 0; r < 16; r += 4) {
-      s0 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r + 0], c, nref[cs]));
-      s1 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r + 1], c, nref[cs]));
-      s2 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r + 2], c, nref[cs]));
-      s3 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r + 3], c, nref[cs]));
-    }
-    float sum = (s0 + s1) + (s2 + s3);
+    for (int r = 0; r < 4; ++r) s[r] = __builtin_amdgcn_exp2f(__builtin_fmaf(acc.get(r), c, nref[ct]));
+#pragma unroll
+    for (int r = 4; r < R::E; ++r) s[r & 3] += __builtin_amdgcn_exp2f(__builtin_fmaf(acc.get(r), c, nref[ct]));
+    return (s[0] + s[1]) + (s[2] + s[3]);
+  };
+  // the same, re-based when it leaves [0, 2^64)
+  auto accumulate = [&](const Acc& acc, int ct) {
+    float sum = fast_sum(acc, ct);
     const bool bad = !(sum < kRebase);  // too large, infinite or NaN
     if (__builtin_amdgcn_ballot_w64(bad)) {
       if (bad) {
-        const float tm = max16_tree(acc, kNegInf) * c;
-        // all 16 rows masked: keep the reference (their terms are zero under any finite reference)
-        const float nm = tm > -1.0e30f ? tm : -nref[cs];
-        lsum[cs] *= __builtin_amdgcn_exp2f(-nref[cs] - nm);
-        nref[cs] = -nm;
-        sum = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r], c, nref[cs]));
+        const float tm = max_of<R>(acc, kNegInf) * c;
+        // all rows masked: keep the reference (their terms are zero under any finite reference)
+        const float nm = tm > -1.0e30f ? tm : -nref[ct];
+        lsum[ct] *= __builtin_amdgcn_exp2f(-nref[ct] - nm);
+        nref[ct] = -nm;
+        sum = fast_sum(acc, ct);
       }
     }
-    lsum[cs] += sum;
+    lsum[ct] += sum;
   };
-
-  // sum of one chain, no check: 16 x (fma, exp2, add)
-  auto fast_sum = [&](const f32x16& acc, int cs) {
-    float s0 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[0], c, nref[cs]));
-    float s1 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[1], c, nref[cs]));
-    float s2 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[2], c, nref[cs]));
-    float s3 = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[3], c, nref[cs]));
-#pragma unroll
-    for (int r = 4; r < 16; r += 4) {
-      s0 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r + 0], c, nref[cs]));
-      s1 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r + 1], c, nref[cs]));
-      s2 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r + 2], c, nref[cs]));
-      s3 += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[r + 3], c, nref[cs]));
-    }
-    return (s0 + s1) + (s2 + s3);
-  };
-  // the keys of an interior tile, visible to every query of the block, summed without checks
+  // The keys of an interior tile, visible to every query of the block, summed without checks.  At d = 128, where matrix and vector
+  // work take nearly as long, the products of one sub-tile are issued between the exponentials of the one before (28 x 12 heads,
+  // 10 007 keys, both passes: 17 190 -> 16 890 us); at d = 64 the compiler's own order is the faster one (8192 keys, 16 x 32 heads:
+  // 9030 and 9100 us).
   auto interior_tile = [&](const u32x4* buf) {
+    if constexpr (D == 128) {
+      Acc acc[2][NT];
+      R a[2];
+      a[0].read(buf, 0, lane);
+      a[0].products(acc[0], b, R::zero());
+      a[1].read(buf, 32, lane);
+      static_for<C::SUB>([&](auto sc) {
+        constexpr int s = decltype(sc)::value, cur = s & 1, nxt = cur ^ 1;
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (s + 1 < C::SUB) a[nxt].products(acc[nxt], b, R::zero());
+        if constexpr (s + 2 < C::SUB) a[cur].read(buf, (s + 2) * 32, lane);
 #pragma unroll
-    for (int s = 0; s < C::SUB; ++s) {
-      bf16x8 a[C::KK];
+        for (int ct = 0; ct < NT; ++ct) lsum[ct] += fast_sum(acc[cur][ct], ct);
+        if constexpr (s + 1 < C::SUB) {
 #pragma unroll
-      for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, s * 32 + l32, kk * 2 + half);
-      f32x16 acc[NCOL];
+          for (int i = 0; i < R::RT * NT * R::KK; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+            __builtin_amdgcn_sched_group_barrier(0x402, 3, 0);  // three vector instructions, exponentials among them
+          }
+        }
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    } else {
 #pragma unroll
-      for (int cs = 0; cs < NCOL; ++cs) {
-        acc[cs] = splat16(0.0f);
+      for (int s = 0; s < C::SUB; ++s) {
+        R a;
+        a.read(buf, s * 32, lane);
+        Acc acc[NT];
 #pragma unroll
-        for (int kk = 0; kk < C::KK; ++kk) acc[cs] = mfma_32x32x16(a[kk], b[cs][kk], acc[cs]);
+        for (int ct = 0; ct < NT; ++ct) acc[ct] = a.product(b[ct], R::zero());
+#pragma unroll
+        for (int ct = 0; ct < NT; ++ct) lsum[ct] += fast_sum(acc[ct], ct);
       }
-#pragma unroll
-      for (int cs = 0; cs < NCOL; ++cs) lsum[cs] += fast_sum(acc[cs], cs);
     }
   };
 
-  // Where a chain of the tile at row0 (32 keys from jbase on, the wave's column sub-tile cs) stands: nothing of it is visible,
+  // Where a chain of the tile at row0 (32 keys from jbase on, the wave's 32 columns cs) stands: nothing of it is visible,
   // some of it, or all.  All of it is where every key lies at or before the first query, and inside its last one's chunk.
   auto hidden = [&](bool is_rec, int jbase, int limit, int cs) {
     return jbase >= limit || (is_rec && jbase > wave_i_lo + cs * 32 + 31);
@@ -176,61 +191,65 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
   // a column sees the context keys below N, the reconstruction keys from its chunk's first to its own: one range either way, so
   // that the mask is three instructions per element (as a choice per element it compiled to two branches for each, fetched for a
   // few tiles: 28 layers of 12 heads of 128, 200 queries of 2000 keys, both passes: 123 -> 109 us)
-  auto mask_chain = [&](f32x16& acc, bool is_rec, int jbase, int cs) {
-    const int first = is_rec ? qlo[cs] : 0, last = is_rec ? qi[cs] : N - 1;
-    const int from = first - (jbase + half * 4);
+  auto mask_chain = [&](Acc& acc, bool is_rec, int jbase, int ct) {
+    const int first = is_rec ? qlo[ct] : 0, last = is_rec ? qi[ct] : N - 1;
+    const int from = first - (jbase + rows4);
     const uint32_t span = (uint32_t)(last - first);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = (uint32_t)((r >> 2) * 8 + (r & 3) - from) <= span ? acc[r] : kNegInf;
+    for (int r = 0; r < R::E; ++r) acc.set(r, (uint32_t)(R::acc_row(r) - from) <= span ? acc.get(r) : kNegInf);
+  };
+  // one sub-tile of 32 keys: its visible chains, masked where they are cut, go to `sum`; false: nothing of it or behind it is visible
+  auto cut_rows = [&](const u32x4* buf, bool is_rec, int s, int row0, int limit, auto&& sum) {
+    const int jbase = row0 + s * 32;
+    if (hidden(is_rec, jbase, limit, NCOL - 1)) return false;
+    R a;
+    a.read(buf, s * 32, lane);
+#pragma unroll
+    for (int cs = 0; cs < NCOL; ++cs) {
+      if (hidden(is_rec, jbase, limit, cs)) continue;
+      Acc acc[NS];
+#pragma unroll
+      for (int e = 0; e < NS; ++e) acc[e] = a.product(b[NS * cs + e], R::zero());
+      if (cut(is_rec, jbase, limit, cs)) {
+#pragma unroll
+        for (int e = 0; e < NS; ++e) mask_chain(acc[e], is_rec, jbase, NS * cs + e);
+      }
+#pragma unroll
+      for (int e = 0; e < NS; ++e) sum(acc[e], NS * cs + e);
+    }
+    return true;
   };
   // a tile that causality, a chunk boundary or the end of the context cuts: its visible chains, summed without checks
   auto cut_tile = [&](const u32x4* buf, bool is_rec, int row0, int limit) {
 #pragma unroll 1
-    for (int s = 0; s < C::SUB; ++s) {
-      const int jbase = row0 + s * 32;
-      if (hidden(is_rec, jbase, limit, NCOL - 1)) break;
-      bf16x8 a[C::KK];
-#pragma unroll
-      for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, s * 32 + l32, kk * 2 + half);
-#pragma unroll
-      for (int cs = 0; cs < NCOL; ++cs) {
-        if (hidden(is_rec, jbase, limit, cs)) continue;
-        f32x16 acc = splat16(0.0f);
-#pragma unroll
-        for (int kk = 0; kk < C::KK; ++kk) acc = mfma_32x32x16(a[kk], b[cs][kk], acc);
-        if (cut(is_rec, jbase, limit, cs)) mask_chain(acc, is_rec, jbase, cs);
-        lsum[cs] += fast_sum(acc, cs);
-      }
-    }
+    for (int s = 0; s < C::SUB; ++s)
+      if (!cut_rows(buf, is_rec, s, row0, limit, [&](const Acc& acc, int ct) { lsum[ct] += fast_sum(acc, ct); })) break;
   };
-  // the first reference of every column: the largest visible logit of the first 32 keys of a tile (if any is visible)
+  // the first reference of every column: the largest visible logit that the lane has of the first 32 keys of a tile (if any is visible)
   auto first_reference = [&](const u32x4* buf, bool interior, bool is_rec, int row0) {
-    bf16x8 a[C::KK];
+    R a;
+    a.read(buf, 0, lane);
 #pragma unroll
-    for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, l32, kk * 2 + half);
-#pragma unroll
-    for (int cs = 0; cs < NCOL; ++cs) {
-      f32x16 acc = splat16(0.0f);
-#pragma unroll
-      for (int kk = 0; kk < C::KK; ++kk) acc = mfma_32x32x16(a[kk], b[cs][kk], acc);
-      if (!interior) mask_chain(acc, is_rec, row0, cs);
-      const float tm = max16_tree(acc, kNegInf) * c;
-      if (tm > -1.0e30f) nref[cs] = -tm;
+    for (int ct = 0; ct < NT; ++ct) {
+      Acc acc = a.product(b[ct], R::zero());
+      if (!interior) mask_chain(acc, is_rec, row0, ct);
+      const float tm = max_of<R>(acc, kNegInf) * c;
+      if (tm > -1.0e30f) nref[ct] = -tm;
     }
   };
 
   // sums a tile without checks; false, and the sums as they were, if one of them went out of range
   auto sum_unchecked = [&](auto&& sum_tile) {
-    float before[NCOL];
+    float before[NT];
 #pragma unroll
-    for (int cs = 0; cs < NCOL; ++cs) before[cs] = lsum[cs];
+    for (int ct = 0; ct < NT; ++ct) before[ct] = lsum[ct];
     sum_tile();
     bool bad = false;
 #pragma unroll
-    for (int cs = 0; cs < NCOL; ++cs) bad |= !(lsum[cs] < kTileRedo);
+    for (int ct = 0; ct < NT; ++ct) bad |= !(lsum[ct] < kTileRedo);
     if (__builtin_amdgcn_ballot_w64(bad) == 0) return true;
 #pragma unroll
-    for (int cs = 0; cs < NCOL; ++cs) lsum[cs] = before[cs];
+    for (int ct = 0; ct < NT; ++ct) lsum[ct] = before[ct];
     return false;
   };
 
@@ -278,42 +297,36 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     }
     if (redo) {
 #pragma unroll 1
-      for (int s = 0; s < C::SUB; ++s) {
-        const int jbase = row0 + s * 32;
-        if (hidden(is_rec, jbase, limit, NCOL - 1)) break;
-        bf16x8 a[C::KK];
-#pragma unroll
-        for (int kk = 0; kk < C::KK; ++kk) a[kk] = frag_read<D>(buf, s * 32 + l32, kk * 2 + half);
-#pragma unroll
-        for (int cs = 0; cs < NCOL; ++cs) {
-          if (hidden(is_rec, jbase, limit, cs)) continue;
-          f32x16 acc = splat16(0.0f);
-#pragma unroll
-          for (int kk = 0; kk < C::KK; ++kk) acc = mfma_32x32x16(a[kk], b[cs][kk], acc);
-          if (cut(is_rec, jbase, limit, cs)) mask_chain(acc, is_rec, jbase, cs);
-          accumulate(acc, cs);
-        }
-      }
+      for (int s = 0; s < C::SUB; ++s)
+        if (!cut_rows(buf, is_rec, s, row0, limit, accumulate)) break;
     }
   }
+  // a column's sums lie in 64 / W lanes, each with a reference of its own
 #pragma unroll
-  for (int cs = 0; cs < NCOL; ++cs) {
-    const float m1 = -nref[cs];
-    const float m2 = swap_halves(m1), l2 = swap_halves(lsum[cs]);
-    const float m = __builtin_fmaxf(m1, m2);
-    const float tot = lsum[cs] * __builtin_amdgcn_exp2f(m1 - m) + l2 * __builtin_amdgcn_exp2f(m2 - m);
+  for (int ct = 0; ct < NT; ++ct) {
+    float m = -nref[ct], tot = lsum[ct];
+#pragma unroll
+    for (int x = W; x < 64; x *= 2) {
+      const float m2 = __shfl_xor(m, x, 64), l2 = __shfl_xor(tot, x, 64), mm = __builtin_fmaxf(m, m2);
+      tot = tot * __builtin_amdgcn_exp2f(m - mm) + l2 * __builtin_amdgcn_exp2f(m2 - mm);
+      m = mm;
+    }
     if constexpr (SPLIT) {
-      if (half == 0 && qi[cs] < N_q)
-        reinterpret_cast<LsePart*>(neg_lse)[((size_t)split * gridDim.z * H_q + l * H_q + h) * N_q + qi[cs]] = LsePart{m, tot};
+      if (lane < W && qi[ct] < N_q)
+        reinterpret_cast<LsePart*>(neg_lse)[((size_t)split * gridDim.z * H_q + l * H_q + h) * N_q + qi[ct]] = LsePart{m, tot};
     } else {
       const float L2 = m + __builtin_amdgcn_logf(tot);
-      if (half == 0 && qi[cs] < N_q) neg_lse[(size_t)(l * H_q + h) * N_q + qi[cs]] = -L2 * inv_c;
+      if (lane < W && qi[ct] < N_q) neg_lse[(size_t)(l * H_q + h) * N_q + qi[ct]] = -L2 * inv_c;
     }
   }
 }
 
 }  // namespace
 
+// Columns of an MFMA tile.  16 x 16 x 32 instructions draw less than 32 x 32 x 16, but there are twice as many to issue: at d = 128, where
+// the products take as long as the exponentials, they gain (28 x 12 heads, 10 007 keys, both passes 18 170 -> 17 000 us), at d = 64,
+// where the vector ALU sets the time, they do not (16 x 32 heads, 8192 keys 9030 and 9050; causal, 4097 tokens, pass 1 alone 885 and 920).
+constexpr int kLseW(int d) { return d == 64 ? 32 : 16; }
 constexpr int kLseCols = 2;  // column sub-tiles per wave; 128 * kLseCols queries per workgroup
 
 // Workgroups per query block: as many as fill the chip (three per CU at d = 64), if the query blocks alone give it less than half
@@ -349,7 +362,7 @@ hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint
   // blocks drift apart along a key stream slightly larger than the L2)
   dim3 grid((unsigned)((N_q + 128 * NCOL - 1) / (128 * NCOL) * splits), (unsigned)H_q, (unsigned)L_s);
 #define PKV_LSE(D, MINB, SPLIT)                                                                                          \
-  score_lse_kernel<D, NCOL, MINB, SPLIT><<<grid, 256, 0, stream>>>(q, k_ctx, k_rec, neg_lse, H_q, G, (int)N, (int)N_q, chunk, \
+  score_lse_kernel<D, NCOL, kLseW(D), MINB, SPLIT><<<grid, 256, 0, stream>>>(q, k_ctx, k_rec, neg_lse, H_q, G, (int)N, (int)N_q, chunk, \
                                                                    c, inv_c, splits, x, n_x)
   if (d == 64) {
     if (splits > 1) PKV_LSE(64, 3, true);
