@@ -331,12 +331,13 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
 //   [16, 16 + P * B)                 the row's histogram of every pass
 //   [16 + P * B, ... )               per part, for every digit of the last pass and one past them: its number of keys under
 //                                    the prefix with at least that digit plus its keys above the prefix
+// and behind all rows, where there is room, two 64-bit masks per thread of every part: its scores above the prefix and under it.
 // mw_init_kernel clears the first 16 + P * B words of every row; the per-part words are all written by the last pass.
 // A pass takes the next BITS bits of the keys whose higher bits equal the prefix found so far; the workgroup that arrives
 // last at the row's counter has every part's contribution in the row's histogram and picks the bin that holds the krem-th
 // largest key.
 // Eleven bits: three passes instead of four, and the first digit (sign, exponent, two bits of mantissa) spreads scores
-// that share an exponent over four bins.  112 rows of 170 000 scores: 79 us in all, with 8 bits and scores read by thread 222 us.
+// that share an exponent over four bins.  112 rows of 170 000 scores: 70 us in all, with 8 bits and scores read by thread 222 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMwQuads = 11, kMwPartMax = kMwQuads * 256 * kTopkWaves;  // quads per lane and scores per part
 constexpr int kMwStateWords = 16;
@@ -353,6 +354,24 @@ struct Mw {
   static constexpr int kCopies = BITS == 8 ? 16 : 8;
 };
 
+// bits = 2 bits + (f > t), and with f >= t: false for NaN
+__device__ __forceinline__ void shift_in_gt(uint32_t& bits, float f, float t) {
+  asm("v_cmp_gt_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(f), "v"(t) : "vcc");
+}
+__device__ __forceinline__ void shift_in_ge(uint32_t& bits, float f, float t) {
+  asm("v_cmp_ge_f32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(f), "v"(t) : "vcc");
+}
+
+// Wave w owns the scores [s0, s1) of its part of `len`, at most kMwQuads quads per lane.
+struct WaveSpan {
+  int s0, s1, quads;
+};
+__device__ __forceinline__ WaveSpan wave_span(int len, int wave) {
+  const int seg = ((len + kTopkWaves - 1) / kTopkWaves + 255) & ~255;
+  const int s0 = wave * seg < len ? wave * seg : len, s1 = s0 + seg < len ? s0 + seg : len;
+  return {s0, s1, (s1 - s0 + 255) / 256};
+}
+
 template <int BITS>
 __global__ void mw_init_kernel(uint32_t* __restrict__ scratch, int rows, int row_words, int K) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -364,11 +383,11 @@ __global__ void mw_init_kernel(uint32_t* __restrict__ scratch, int rows, int row
 // grid (parts, rows)
 template <int BITS, int PASS>
 __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __restrict__ scores, int N, int part_len,
-                                                               uint32_t* __restrict__ scratch, int row_words) {
+                                                               uint32_t* __restrict__ scratch, int row_words, u32x4* __restrict__ masks) {
   using C = Mw<BITS>;
   constexpr int kHi = 32 - BITS * PASS, kShift = kHi > BITS ? kHi - BITS : 0, kDigitBins = 1 << (kHi - kShift);
   constexpr bool kLast = PASS == C::kPasses - 1;
-  const int part = blockIdx.x, parts = gridDim.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int part = blockIdx.x, parts = gridDim.x, tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const float* row = scores + (size_t)blockIdx.y * N;
   uint32_t* rs = scratch + (size_t)blockIdx.y * row_words;
   uint32_t* row_hist = rs + kMwStateWords + PASS * C::kBins;
@@ -382,30 +401,108 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
   __syncthreads();
   uint32_t n_hi = 0;  // last pass: keys above the prefix
   uint32_t* mine = hist + (lane & (C::kCopies - 1));
-  for (int c0 = 0; c0 < len; c0 += 4 * kChunk) {  // four chunks in flight
-    f32x4 v[4];
+  if constexpr (kLast) {
+    // in the order of mw_write_kernel, which takes what is found here about every score from `masks`
+    const WaveSpan w = wave_span(len, wave);
+    uint64_t m_hi = 0, m_in = 0;  // keys above the prefix, and under it
+    // Two comparisons per score and a bit each: as integer keys, with the histogram's adds in the loop, this pass is bound by the vector
+    // ALU (112 rows of 170 000 scores: 24 us, so 20.5).  The bins that hold infinities, NaN or the last number below zero, whose key no zero
+    // may share, take the way over the keys, and so do rows with many scores (nearly) the same.
+    const uint32_t k_lo = prefix << kHi, k_hi = k_lo | ((1u << kHi) - 1u);
+    bool by_key = !(k_lo >= 0x00800000u && k_hi < 0xff800000u && k_hi != 0x7fffffffu);
+    if (!by_key) {
+      const float f_lo = key_score(k_lo), f_hi = key_score(k_hi);
+      constexpr int kFly = 6;  // quads in flight
+#pragma unroll 1
+      for (int q0 = 0; q0 < w.quads; q0 += kFly) {
+        f32x4 v[kFly];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = load_quad(row, c0 + u * kChunk + 4 * tid, len);
-    auto count = [&](bool valid, float f) {
-      const uint32_t key = order_key(f);
-      if constexpr (PASS == 0) {
-        if (valid) atomicAdd(&mine[(key >> kShift) * C::kCopies], 1u);
-      } else {
-        const uint32_t top = key >> (kHi & 31);
-        if (valid && top == prefix) atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
-        if (kLast) n_hi += valid && top > prefix;
+        for (int u = 0; u < kFly; ++u) v[u] = load_quad(row, w.s0 + (q0 + u) * 256 + 4 * lane, w.s1);
+        uint32_t above = 0, from = 0, valid = ~0u;  // four bits a quad, the first score's the highest
+        if (w.s0 + (q0 + kFly) * 256 > w.s1) {
+          valid = 0;
+#pragma unroll
+          for (int u = 0; u < kFly; ++u) {
+            const int i = w.s0 + (q0 + u) * 256 + 4 * lane, n = w.s1 - i;
+            v[u] = shift_quad(v[u], quad_shift(i, w.s1));
+            valid |= (n >= 4 ? 15u : (n > 0 ? (1u << n) - 1u : 0u)) << (4 * u);
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < kFly; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            shift_in_gt(above, v[u][j], f_hi);
+            shift_in_ge(from, v[u][j], f_lo);
+          }
+        above = __brev(above) >> (32 - 4 * kFly);
+        from = __brev(from) >> (32 - 4 * kFly);
+        m_hi |= (uint64_t)(above & valid) << (4 * q0);
+        m_in |= (uint64_t)(from & ~above & valid) << (4 * q0);
       }
-    };
-    if (c0 + 4 * kChunk <= len) {
+      by_key = __builtin_amdgcn_ballot_w64(__popcll(m_in) > 3) != 0;
+      for (uint64_t left = by_key ? 0 : m_in; __builtin_amdgcn_ballot_w64(left != 0);)
+        if (left != 0) {
+          const int bit = __ffsll((unsigned long long)left) - 1;
+          left &= left - 1;
+          const uint32_t key = order_key(row[w.s0 + (bit >> 2) * 256 + 4 * lane + (bit & 3)]);
+          atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
+        }
+    }
+    if (by_key) {
+      m_hi = m_in = 0;
+#pragma unroll 1
+      for (int q0 = 0; q0 < w.quads; q0 += 4) {
+        f32x4 v[4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u) v[u] = load_quad(row, w.s0 + (q0 + u) * 256 + 4 * lane, w.s1);
+        const bool cut = w.s0 + (q0 + 4) * 256 > w.s1;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) count(true, v[u][j]);
-    } else {
+        for (int u = 0; u < 4; ++u) {
+          const int i = w.s0 + (q0 + u) * 256 + 4 * lane;
+          if (cut) v[u] = shift_quad(v[u], quad_shift(i, w.s1));
+          uint32_t bh = 0, bi = 0;
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t key = order_key(v[u][j]), top = key >> kHi;
+            const bool valid = !cut || i + j < w.s1;
+            bh |= (uint32_t)(valid && top > prefix) << j;
+            bi |= (uint32_t)(valid && top == prefix) << j;
+            if (valid && top == prefix) atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
+          }
+          m_hi |= (uint64_t)bh << (4 * (q0 + u));
+          m_in |= (uint64_t)bi << (4 * (q0 + u));
+        }
+      }
+    }
+    n_hi = (uint32_t)__popcll(m_hi);
+    if (masks != nullptr)
+      masks[((size_t)blockIdx.y * parts + part) * kTopkThreads + tid] =
+          u32x4{(uint32_t)m_hi, (uint32_t)(m_hi >> 32), (uint32_t)m_in, (uint32_t)(m_in >> 32)};
+  } else {
+    for (int c0 = 0; c0 < len; c0 += 4 * kChunk) {  // four chunks in flight
+      f32x4 v[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) count(j >= quad_shift(c0 + u * kChunk + 4 * tid, len), v[u][j]);
+      for (int u = 0; u < 4; ++u) v[u] = load_quad(row, c0 + u * kChunk + 4 * tid, len);
+      auto count = [&](bool valid, float f) {
+        const uint32_t key = order_key(f);
+        if constexpr (PASS == 0) {
+          if (valid) atomicAdd(&mine[(key >> kShift) * C::kCopies], 1u);
+        } else {
+          if (valid && key >> (kHi & 31) == prefix) atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
+        }
+      };
+      if (c0 + 4 * kChunk <= len) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) count(true, v[u][j]);
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) count(j >= quad_shift(c0 + u * kChunk + 4 * tid, len), v[u][j]);
+      }
     }
   }
   __syncthreads();
@@ -459,7 +556,8 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
 template <int BITS, bool GATHER>
 __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* __restrict__ scores, int N, int K, int part_len,
                                                                 const uint32_t* __restrict__ scratch, int row_words,
-                                                                int32_t* __restrict__ idx_out, GatherArgs ga) {
+                                                                const u32x4* __restrict__ masks, int32_t* __restrict__ idx_out,
+                                                                GatherArgs ga) {
   using C = Mw<BITS>;
   constexpr int kDigitBins = 1 << C::kLastBits;
   const int part = blockIdx.x, tid = threadIdx.x;
@@ -470,9 +568,10 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
   const int lo = part * part_len, len = N - lo < part_len ? N - lo : part_len;
   row += lo;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  // wave w owns the scores [w * seg, (w + 1) * seg) of the part, at most kMwQuads quads per lane
-  const int seg = ((len + kTopkWaves - 1) / kTopkWaves + 255) & ~255;
-  const int s0 = wave * seg < len ? wave * seg : len, s1 = s0 + seg < len ? s0 + seg : len;
+  const WaveSpan w = wave_span(len, wave);
+  const int s0 = w.s0, s1 = w.s1, quads = w.quads;
+  u32x4 m = {0, 0, 0, 0};
+  if (masks != nullptr) m = masks[((size_t)blockIdx.y * gridDim.x + part) * kTopkThreads + tid];
   const uint32_t T = rs[0], eq_take = rs[1], t_last = T & (kDigitBins - 1);
   // keys above T and keys equal to T in the parts before this one
   uint32_t g = 0, e = 0;
@@ -484,21 +583,40 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
   const uint32_t gt_before = block_sum(g, wave_part, tid), eq_before = block_sum(e, wave_part, tid);
   const float t = key_score(T);
   const bool nan_t = T == 0;
-  uint64_t m_gt = 0, m_eq = 0;
-  const int quads = (s1 - s0 + 255) / 256;
+  uint64_t m_gt = 0, m_eq = 0, m_in = 0;
+  bool again = masks == nullptr;
+  if (!again) {
+    m_gt = (uint64_t)m[1] << 32 | m[0];
+    m_in = (uint64_t)m[3] << 32 | m[2];
+    // keys that agree with T in all but the last digit: a few per row, looked up one by one, unless many scores are (nearly) the same
+    again = __builtin_amdgcn_ballot_w64(__popcll(m_in) > 3) != 0;
+  }
+  if (!again) {
+    while (__builtin_amdgcn_ballot_w64(m_in != 0)) {
+      if (m_in != 0) {
+        const int bit = __ffsll((unsigned long long)m_in) - 1;
+        const float f = row[s0 + (bit >> 2) * 256 + 4 * lane + (bit & 3)];
+        m_in &= m_in - 1;
+        m_gt |= (uint64_t)(nan_t ? f == f : f > t) << bit;
+        m_eq |= (uint64_t)(nan_t ? f != f : f == t) << bit;
+      }
+    }
+  } else {
+    m_gt = 0;
 #pragma unroll 1
-  for (int q0 = 0; q0 < quads; q0 += 4) {
-    f32x4 v[4];
+    for (int q0 = 0; q0 < quads; q0 += 4) {
+      f32x4 v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = load_quad(row, s0 + (q0 + u) * 256 + 4 * lane, s1);
-    const bool cut = s0 + (q0 + 4) * 256 > s1;
+      for (int u = 0; u < 4; ++u) v[u] = load_quad(row, s0 + (q0 + u) * 256 + 4 * lane, s1);
+      const bool cut = s0 + (q0 + 4) * 256 > s1;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      if (cut) v[u] = shift_quad(v[u], quad_shift(s0 + (q0 + u) * 256 + 4 * lane, s1));
-      uint32_t bg, be;
-      quad_bits(v[u], s1 - (s0 + (q0 + u) * 256 + 4 * lane), t, nan_t, bg, be);
-      m_gt |= (uint64_t)bg << (4 * (q0 + u));
-      m_eq |= (uint64_t)be << (4 * (q0 + u));
+      for (int u = 0; u < 4; ++u) {
+        if (cut) v[u] = shift_quad(v[u], quad_shift(s0 + (q0 + u) * 256 + 4 * lane, s1));
+        uint32_t bg, be;
+        quad_bits(v[u], s1 - (s0 + (q0 + u) * 256 + 4 * lane), t, nan_t, bg, be);
+        m_gt |= (uint64_t)bg << (4 * (q0 + u));
+        m_eq |= (uint64_t)be << (4 * (q0 + u));
+      }
     }
   }
   const uint32_t n_gt = wave_total((uint32_t)__popcll(m_gt)), n_eq = wave_total((uint32_t)__popcll(m_eq));
@@ -541,17 +659,18 @@ static size_t topk_scratch(int64_t rows, int64_t N) {
   if (N <= kTopkRegMax || rows <= 0) return 0;
   return (size_t)rows * (size_t)(Mw<BITS>::kFixedWords + (size_t)topk_parts<BITS>(rows, N) * Mw<BITS>::kPartWords) * 4;
 }
-// (the parts of up to `rows` rows of up to N scores: 512, or as few as each row can have)
+constexpr size_t kMaskBytes = kTopkThreads * 16;  // of a part: four words per thread
+// (the parts of up to `rows` rows of up to N scores: 512, or as few as each row can have; the masks start on a 16-byte boundary)
 size_t topk_scratch_bytes(int64_t rows, int64_t N) {
   if (N <= kTopkRegMax || rows <= 0) return 0;
   const size_t least = (size_t)rows * (size_t)((N + kMwPartMax - 1) / kMwPartMax), parts = least > 512 ? least : 512;
-  return ((size_t)rows * Mw<11>::kFixedWords + parts * Mw<11>::kPartWords) * 4;
+  return ((size_t)rows * Mw<11>::kFixedWords + parts * Mw<11>::kPartWords) * 4 + 16 + parts * kMaskBytes;
 }
 size_t topk_scratch_bytes_least(int64_t rows, int64_t N) { return topk_scratch<8>(rows, N); }
 
 template <int BITS>
 static hipError_t launch_topk_split(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
-                                    const GatherArgs* gather, hipStream_t stream) {
+                                    size_t scratch_bytes, const GatherArgs* gather, hipStream_t stream) {
   using C = Mw<BITS>;
   const GatherArgs none = {nullptr, nullptr, nullptr, nullptr, 0};
   // parts of equal length, a multiple of four scores (16-byte loads when the row itself is aligned), none of them empty
@@ -560,18 +679,22 @@ static hipError_t launch_topk_split(const float* scores, int64_t rows, int64_t N
   const int parts = (int)((N + part_len - 1) / part_len);
   const int row_words = C::kFixedWords + parts * C::kPartWords;
   uint32_t* sc = (uint32_t*)scratch;
+  // What the last pass finds about every score, two bits each, saves the kernel behind it from reading the scores (112 rows of
+  // 170 000: that one 28 -> 16 us, the last pass 17 -> 20.5); where the scratch memory does not hold that, the scores are read a fourth time.
+  const size_t mask_at = ((size_t)rows * row_words * 4 + 15) & ~(size_t)15;
+  u32x4* masks = BITS == 11 && mask_at + (size_t)(rows * parts) * kMaskBytes <= scratch_bytes ? (u32x4*)((uint8_t*)scratch + mask_at) : nullptr;
   const int64_t init_words = rows * C::kFixedWords;
   mw_init_kernel<BITS><<<(unsigned)((init_words + 255) / 256), 256, 0, stream>>>(sc, (int)rows, row_words, (int)K);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const dim3 grid((unsigned)parts, (unsigned)rows);
-  mw_pass_kernel<BITS, 0><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words);
-  mw_pass_kernel<BITS, 1><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words);
-  mw_pass_kernel<BITS, 2><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words);
-  if constexpr (C::kPasses > 3) mw_pass_kernel<BITS, 3><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words);
+  mw_pass_kernel<BITS, 0><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words, masks);
+  mw_pass_kernel<BITS, 1><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words, masks);
+  mw_pass_kernel<BITS, 2><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words, masks);
+  if constexpr (C::kPasses > 3) mw_pass_kernel<BITS, 3><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, part_len, sc, row_words, masks);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (gather) mw_write_kernel<BITS, true><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, part_len, sc, row_words, idx_out, *gather);
-  else mw_write_kernel<BITS, false><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, part_len, sc, row_words, idx_out, none);
+  if (gather) mw_write_kernel<BITS, true><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, part_len, sc, row_words, masks, idx_out, *gather);
+  else mw_write_kernel<BITS, false><<<grid, kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, part_len, sc, row_words, masks, idx_out, none);
   return hipGetLastError();
 }
 
@@ -586,8 +709,8 @@ static hipError_t launch_topk_impl(const float* scores, int64_t rows, int64_t N,
     return hipGetLastError();
   }
   if (scratch == nullptr || rows > 65535) return hipErrorInvalidValue;
-  if (scratch_bytes >= topk_scratch<11>(rows, N)) return launch_topk_split<11>(scores, rows, N, K, idx_out, scratch, gather, stream);
-  if (scratch_bytes >= topk_scratch<8>(rows, N)) return launch_topk_split<8>(scores, rows, N, K, idx_out, scratch, gather, stream);
+  if (scratch_bytes >= topk_scratch<11>(rows, N)) return launch_topk_split<11>(scores, rows, N, K, idx_out, scratch, scratch_bytes, gather, stream);
+  if (scratch_bytes >= topk_scratch<8>(rows, N)) return launch_topk_split<8>(scores, rows, N, K, idx_out, scratch, scratch_bytes, gather, stream);
   return hipErrorInvalidValue;
 }
 

@@ -139,6 +139,36 @@ def test_compact_inplace_and_mask_bit_exact():
         assert torch.equal(m.cpu(), oracle.mask(idx, N)), (N, K)
 
 
+@pytest.mark.parametrize("rows", [10, 200])
+def test_topk_of_long_rows_by_bits_and_by_keys(rows):
+    """The last pass over a long row compares scores with the ends of the threshold's bin and leaves two bits each for the kernel that
+    writes.  Rows whose bin holds infinities, NaN, both zeros or the numbers next to them, and rows with many scores in it, go
+    another way; and with 200 rows proxykv_topk_static's scratch memory has no room for the bits."""
+    N, K = 50001, 20000
+    g = torch.Generator().manual_seed(71)
+    x = torch.randn(10, N, generator=g)
+    half = torch.rand(10, N, generator=g) < 0.55
+    x[1][half[1]] = float("-inf")
+    x[2][half[2]] = float("nan")
+    x[3][half[3]] = float("inf")
+    x[4] = torch.where(half[4], torch.tensor(-0.0), torch.tensor(0.0)) * 1.0
+    x[4][::3] = -1e-45 * torch.randint(1, 500, (N,), generator=g)[::3]      # the largest numbers below zero
+    x[5] = torch.randint(-300, 300, (N,), generator=g) * 1e-45              # around zero, all in two bins
+    x[6] = 1.0 + torch.randint(0, 900, (N,), generator=g) * 2.0 ** -23       # all in one bin of the last digit
+    x[7][half[7]] = float(x[7].kthvalue(N - K + 1)[0])                       # more scores at the threshold than are kept
+    x[8] = -x[8].abs() * 3e38
+    x[9] = x[9] * 1e-41
+    d = x.repeat(rows // 10, 1).cuda()
+    ref = oracle.topk(x, K).repeat(rows // 10, 1)
+    ctx = pk.proxykv_create(pk.config_for_case(synth.CASES["tiny"]))
+    assert torch.equal(pk.proxykv_topk(ctx, d, K).cpu(), ref)
+    out = torch.empty(rows, K, dtype=torch.int32, device="cuda")
+    pk.proxykv_topk_static(ctx, d, K, out)
+    torch.cuda.synchronize()
+    assert torch.equal(out.cpu(), ref)
+    pk.proxykv_destroy(ctx)
+
+
 @pytest.mark.parametrize("D", [8, 24, 40, 64, 72, 136, 256])
 def test_compact_inplace_at_the_edges_of_chunks(D):
     """Kept counts around whole chunks of 128 tokens, every number of 16-byte pieces per thread, tokens with and without 128-byte
