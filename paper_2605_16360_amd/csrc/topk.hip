@@ -149,8 +149,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t v, uint32_t* p
 }
 
 // The digit that holds the krem-th largest key, from the counts of kDigits bins, thread t holding the kPer bins
-// kDigits - 1 - t * kPer, ... in descending order (cnt zero for threads without bins): calls found(digit, krem left) in
-// one thread.
+// kDigits - 1 - t * kPer, ... in descending order (cnt zero for threads without bins): calls found(digit, krem left, the digit's
+// count) in one thread.
 template <int kDigits, int kPer, class F>
 __device__ __forceinline__ void pick_digit(const uint32_t (&cnt)[kPer], uint32_t krem, uint32_t* part, int tid, F&& found) {
   uint32_t own = 0;
@@ -159,7 +159,7 @@ __device__ __forceinline__ void pick_digit(const uint32_t (&cnt)[kPer], uint32_t
   uint32_t above = block_exclusive_scan(own, part, tid >> 6, tid & 63);
 #pragma unroll
   for (int i = 0; i < kPer; ++i) {
-    if (above < krem && krem <= above + cnt[i]) found((uint32_t)(kDigits - 1 - (tid * kPer + i)), krem - above);
+    if (above < krem && krem <= above + cnt[i]) found((uint32_t)(kDigits - 1 - (tid * kPer + i)), krem - above, cnt[i]);
     above += cnt[i];
   }
 }
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
       cnt[i] = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
     }
     if (hi_bit == 32 && tid == 0) cnt[0] = 0;  // kNoKey's bin
-    pick_digit<2048, 2>(cnt, krem, wave_part, tid, [&](uint32_t d, uint32_t left) {
+    pick_digit<2048, 2>(cnt, krem, wave_part, tid, [&](uint32_t d, uint32_t left, uint32_t) {
       s_prefix = prefix << (hi_bit - shift) | d;
       s_krem = left;
     });
@@ -327,7 +327,8 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
 // ---------------------------------------------------------------------------------------------
 // Rows longer than kTopkRegMax are cut into parts of at most kMwPartMax = 45 056 scores, one workgroup each.
 // Scratch memory per row (32-bit words), B = 2^BITS bins, P passes:
-//   [0, 16)                          state: prefix, krem, then one arrival counter per pass at [4 + pass]
+//   [0, 16)                          state: prefix, krem, the keys under the last pass's prefix, then one arrival counter per pass at
+//                                    [4 + pass]
 //   [16, 16 + P * B)                 the row's histogram of every pass
 //   [16 + P * B, ... )               per part, for every digit of the last pass and one past them: its number of keys under
 //                                    the prefix with at least that digit plus its keys above the prefix
@@ -337,7 +338,7 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
 // last at the row's counter has every part's contribution in the row's histogram and picks the bin that holds the krem-th
 // largest key.
 // Eleven bits: three passes instead of four, and the first digit (sign, exponent, two bits of mantissa) spreads scores
-// that share an exponent over four bins.  112 rows of 170 000 scores: 70 us in all, with 8 bits and scores read by thread 222 us.
+// that share an exponent over four bins.  112 rows of 170 000 scores: 67 us in all, with 8 bits and scores read by thread 222 us.
 // ---------------------------------------------------------------------------------------------
 constexpr int kMwQuads = 11, kMwPartMax = kMwQuads * 256 * kTopkWaves;  // quads per lane and scores per part
 constexpr int kMwStateWords = 16;
@@ -372,6 +373,16 @@ __device__ __forceinline__ WaveSpan wave_span(int len, int wave) {
   return {s0, s1, (s1 - s0 + 255) / 256};
 }
 
+// Whether the last pass leaves two bits per score for mw_write_kernel: where there is room for them, where few keys of the row lie
+// under its prefix (each is looked up on its own, and rows with many scores nearly the same have many), and where that bin is an
+// interval of numbers: not with infinities or NaN in it, or the key of -0.0 at its end, which no score has.
+constexpr uint32_t kFewKeys = 1024;
+template <int BITS>
+__device__ __forceinline__ bool by_bits(const u32x4* masks, uint32_t n_keys, uint32_t prefix) {
+  const uint32_t k_lo = prefix << Mw<BITS>::kLastBits, k_hi = k_lo | ((1u << Mw<BITS>::kLastBits) - 1u);
+  return masks != nullptr && n_keys <= kFewKeys && k_lo >= 0x00800000u && k_hi < 0xff800000u && k_hi != 0x7fffffffu;
+}
+
 template <int BITS>
 __global__ void mw_init_kernel(uint32_t* __restrict__ scratch, int rows, int row_words, int K) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -401,84 +412,50 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
   __syncthreads();
   uint32_t n_hi = 0;  // last pass: keys above the prefix
   uint32_t* mine = hist + (lane & (C::kCopies - 1));
-  if constexpr (kLast) {
-    // in the order of mw_write_kernel, which takes what is found here about every score from `masks`
+  if (kLast && by_bits<BITS>(masks, rs[2], prefix)) {
+    // Two comparisons per score and a bit each, in the order of mw_write_kernel, which takes them from `masks`; the few keys under the
+    // prefix are counted afterwards.  (With keys and the histogram's adds in the loop this pass is bound by the vector ALU: 112 rows
+    // of 170 000 scores 24 us, so 20.5.)
     const WaveSpan w = wave_span(len, wave);
     uint64_t m_hi = 0, m_in = 0;  // keys above the prefix, and under it
-    // Two comparisons per score and a bit each: as integer keys, with the histogram's adds in the loop, this pass is bound by the vector
-    // ALU (112 rows of 170 000 scores: 24 us, so 20.5).  The bins that hold infinities, NaN or the last number below zero, whose key no zero
-    // may share, take the way over the keys, and so do rows with many scores (nearly) the same.
-    const uint32_t k_lo = prefix << kHi, k_hi = k_lo | ((1u << kHi) - 1u);
-    bool by_key = !(k_lo >= 0x00800000u && k_hi < 0xff800000u && k_hi != 0x7fffffffu);
-    if (!by_key) {
-      const float f_lo = key_score(k_lo), f_hi = key_score(k_hi);
-      constexpr int kFly = 6;  // quads in flight
+    const float f_lo = key_score(prefix << kHi), f_hi = key_score(prefix << kHi | ((1u << kHi) - 1u));
+    constexpr int kFly = 6;  // quads in flight
 #pragma unroll 1
-      for (int q0 = 0; q0 < w.quads; q0 += kFly) {
-        f32x4 v[kFly];
+    for (int q0 = 0; q0 < w.quads; q0 += kFly) {
+      f32x4 v[kFly];
 #pragma unroll
-        for (int u = 0; u < kFly; ++u) v[u] = load_quad(row, w.s0 + (q0 + u) * 256 + 4 * lane, w.s1);
-        uint32_t above = 0, from = 0, valid = ~0u;  // four bits a quad, the first score's the highest
-        if (w.s0 + (q0 + kFly) * 256 > w.s1) {
-          valid = 0;
+      for (int u = 0; u < kFly; ++u) v[u] = load_quad(row, w.s0 + (q0 + u) * 256 + 4 * lane, w.s1);
+      uint32_t above = 0, from = 0, valid = ~0u;  // four bits a quad, the first score's the highest
+      if (w.s0 + (q0 + kFly) * 256 > w.s1) {
+        valid = 0;
 #pragma unroll
-          for (int u = 0; u < kFly; ++u) {
-            const int i = w.s0 + (q0 + u) * 256 + 4 * lane, n = w.s1 - i;
-            v[u] = shift_quad(v[u], quad_shift(i, w.s1));
-            valid |= (n >= 4 ? 15u : (n > 0 ? (1u << n) - 1u : 0u)) << (4 * u);
-          }
-        }
-#pragma unroll
-        for (int u = 0; u < kFly; ++u)
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            shift_in_gt(above, v[u][j], f_hi);
-            shift_in_ge(from, v[u][j], f_lo);
-          }
-        above = __brev(above) >> (32 - 4 * kFly);
-        from = __brev(from) >> (32 - 4 * kFly);
-        m_hi |= (uint64_t)(above & valid) << (4 * q0);
-        m_in |= (uint64_t)(from & ~above & valid) << (4 * q0);
-      }
-      by_key = __builtin_amdgcn_ballot_w64(__popcll(m_in) > 3) != 0;
-      for (uint64_t left = by_key ? 0 : m_in; __builtin_amdgcn_ballot_w64(left != 0);)
-        if (left != 0) {
-          const int bit = __ffsll((unsigned long long)left) - 1;
-          left &= left - 1;
-          const uint32_t key = order_key(row[w.s0 + (bit >> 2) * 256 + 4 * lane + (bit & 3)]);
-          atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
-        }
-    }
-    if (by_key) {
-      m_hi = m_in = 0;
-#pragma unroll 1
-      for (int q0 = 0; q0 < w.quads; q0 += 4) {
-        f32x4 v[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) v[u] = load_quad(row, w.s0 + (q0 + u) * 256 + 4 * lane, w.s1);
-        const bool cut = w.s0 + (q0 + 4) * 256 > w.s1;
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int i = w.s0 + (q0 + u) * 256 + 4 * lane;
-          if (cut) v[u] = shift_quad(v[u], quad_shift(i, w.s1));
-          uint32_t bh = 0, bi = 0;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const uint32_t key = order_key(v[u][j]), top = key >> kHi;
-            const bool valid = !cut || i + j < w.s1;
-            bh |= (uint32_t)(valid && top > prefix) << j;
-            bi |= (uint32_t)(valid && top == prefix) << j;
-            if (valid && top == prefix) atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
-          }
-          m_hi |= (uint64_t)bh << (4 * (q0 + u));
-          m_in |= (uint64_t)bi << (4 * (q0 + u));
+        for (int u = 0; u < kFly; ++u) {
+          const int i = w.s0 + (q0 + u) * 256 + 4 * lane, n = w.s1 - i;
+          v[u] = shift_quad(v[u], quad_shift(i, w.s1));
+          valid |= (n >= 4 ? 15u : (n > 0 ? (1u << n) - 1u : 0u)) << (4 * u);
         }
       }
+#pragma unroll
+      for (int u = 0; u < kFly; ++u)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          shift_in_gt(above, v[u][j], f_hi);
+          shift_in_ge(from, v[u][j], f_lo);
+        }
+      above = __brev(above) >> (32 - 4 * kFly);
+      from = __brev(from) >> (32 - 4 * kFly);
+      m_hi |= (uint64_t)(above & valid) << (4 * q0);
+      m_in |= (uint64_t)(from & ~above & valid) << (4 * q0);
     }
     n_hi = (uint32_t)__popcll(m_hi);
-    if (masks != nullptr)
-      masks[((size_t)blockIdx.y * parts + part) * kTopkThreads + tid] =
-          u32x4{(uint32_t)m_hi, (uint32_t)(m_hi >> 32), (uint32_t)m_in, (uint32_t)(m_in >> 32)};
+    masks[((size_t)blockIdx.y * parts + part) * kTopkThreads + tid] =
+        u32x4{(uint32_t)m_hi, (uint32_t)(m_hi >> 32), (uint32_t)m_in, (uint32_t)(m_in >> 32)};
+    for (; __builtin_amdgcn_ballot_w64(m_in != 0); m_in &= m_in - 1)
+      if (m_in != 0) {
+        const int bit = __ffsll((unsigned long long)m_in) - 1;
+        const uint32_t key = order_key(row[w.s0 + (bit >> 2) * 256 + 4 * lane + (bit & 3)]);
+        atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
+      }
   } else {
     for (int c0 = 0; c0 < len; c0 += 4 * kChunk) {  // four chunks in flight
       f32x4 v[4];
@@ -489,7 +466,9 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
         if constexpr (PASS == 0) {
           if (valid) atomicAdd(&mine[(key >> kShift) * C::kCopies], 1u);
         } else {
-          if (valid && key >> (kHi & 31) == prefix) atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
+          const uint32_t top = key >> (kHi & 31);
+          if (valid && top == prefix) atomicAdd(&mine[((key >> kShift) & (kDigitBins - 1)) * C::kCopies], 1u);
+          if (kLast) n_hi += valid && top > prefix;
         }
       };
       if (c0 + 4 * kChunk <= len) {
@@ -545,9 +524,10 @@ __global__ __launch_bounds__(kTopkThreads) void mw_pass_kernel(const float* __re
     cnt[i] = tid * kPer < kDigitBins ? atomicAdd(&row_hist[kDigitBins - 1 - (tid * kPer + i)], 0u) : 0u;
   const uint32_t krem = rs[1];
   // (pick_digit's barriers lie between this read and the write)
-  pick_digit<kDigitBins, kPer>(cnt, krem, wave_part, tid, [&](uint32_t d, uint32_t left) {
+  pick_digit<kDigitBins, kPer>(cnt, krem, wave_part, tid, [&](uint32_t d, uint32_t left, uint32_t n) {
     rs[0] = (PASS == 0 ? 0u : prefix << (kHi - kShift)) | d;
     rs[1] = left;
+    if (PASS == C::kPasses - 2) rs[2] = n;
   });
 }
 
@@ -570,8 +550,6 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const WaveSpan w = wave_span(len, wave);
   const int s0 = w.s0, s1 = w.s1, quads = w.quads;
-  u32x4 m = {0, 0, 0, 0};
-  if (masks != nullptr) m = masks[((size_t)blockIdx.y * gridDim.x + part) * kTopkThreads + tid];
   const uint32_t T = rs[0], eq_take = rs[1], t_last = T & (kDigitBins - 1);
   // keys above T and keys equal to T in the parts before this one
   uint32_t g = 0, e = 0;
@@ -583,26 +561,19 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
   const uint32_t gt_before = block_sum(g, wave_part, tid), eq_before = block_sum(e, wave_part, tid);
   const float t = key_score(T);
   const bool nan_t = T == 0;
-  uint64_t m_gt = 0, m_eq = 0, m_in = 0;
-  bool again = masks == nullptr;
-  if (!again) {
+  uint64_t m_gt = 0, m_eq = 0;
+  if (by_bits<BITS>(masks, rs[2], T >> C::kLastBits)) {
+    const u32x4 m = masks[((size_t)blockIdx.y * gridDim.x + part) * kTopkThreads + tid];
     m_gt = (uint64_t)m[1] << 32 | m[0];
-    m_in = (uint64_t)m[3] << 32 | m[2];
-    // keys that agree with T in all but the last digit: a few per row, looked up one by one, unless many scores are (nearly) the same
-    again = __builtin_amdgcn_ballot_w64(__popcll(m_in) > 3) != 0;
-  }
-  if (!again) {
-    while (__builtin_amdgcn_ballot_w64(m_in != 0)) {
+    // keys that agree with T in all but the last digit
+    for (uint64_t m_in = (uint64_t)m[3] << 32 | m[2]; __builtin_amdgcn_ballot_w64(m_in != 0); m_in &= m_in - 1)
       if (m_in != 0) {
         const int bit = __ffsll((unsigned long long)m_in) - 1;
         const float f = row[s0 + (bit >> 2) * 256 + 4 * lane + (bit & 3)];
-        m_in &= m_in - 1;
-        m_gt |= (uint64_t)(nan_t ? f == f : f > t) << bit;
-        m_eq |= (uint64_t)(nan_t ? f != f : f == t) << bit;
+        m_gt |= (uint64_t)(f > t) << bit;
+        m_eq |= (uint64_t)(f == t) << bit;
       }
-    }
   } else {
-    m_gt = 0;
 #pragma unroll 1
     for (int q0 = 0; q0 < quads; q0 += 4) {
       f32x4 v[4];
@@ -680,7 +651,8 @@ static hipError_t launch_topk_split(const float* scores, int64_t rows, int64_t N
   const int row_words = C::kFixedWords + parts * C::kPartWords;
   uint32_t* sc = (uint32_t*)scratch;
   // What the last pass finds about every score, two bits each, saves the kernel behind it from reading the scores (112 rows of
-  // 170 000: that one 28 -> 16 us, the last pass 17 -> 20.5); where the scratch memory does not hold that, the scores are read a fourth time.
+  // 170 000: that one 28 -> 16 us, the last pass 17 -> 20.5, all 78 -> 67; 4 rows of 262 144, in 64 parts each, 26.4 -> 25.3); where the
+  // scratch memory does not hold it, the scores are read a fourth time.
   const size_t mask_at = ((size_t)rows * row_words * 4 + 15) & ~(size_t)15;
   u32x4* masks = BITS == 11 && mask_at + (size_t)(rows * parts) * kMaskBytes <= scratch_bytes ? (u32x4*)((uint8_t*)scratch + mask_at) : nullptr;
   const int64_t init_words = rows * C::kFixedWords;
