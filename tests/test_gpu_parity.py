@@ -550,6 +550,27 @@ def test_mapper_with_scores_beyond_the_half_range():
     pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("sink", [30.0, 300.0, 3.0e3])
+def test_mapper_with_logits_far_above_those_of_the_first_keys(sink):
+    """The window attention of the large tiles takes a query's reference from its first 64 keys and looks at no later logit; where one is
+    more than 2^16 times as likely, half overflows, and the workgroup starts over with the reference raised on the way.  Sinks behind
+    the first keys of both windows give logits in the thousands; a cut last tile, two layers of which one is ordinary.  Three seeds and
+    two ways of summing stay within 0.29 of the bound up to 3e3; at 3e4 logits reach the millions, where one rounding of an operand
+    to half decides between two keys, and both ways are the same 4.9e-3 off."""
+    case = synth.scaled_case(synth.CASES["llama_8k"], name="late", L_s=2, H_kv=2, H_q=2, L_l=2, H_l=4, N=2200, N_q=1, chunk=1, n_planted=0)
+    w = synth.make_mapper_weights(case.H_kv, case.H_l)
+    g = torch.Generator().manual_seed(8)
+    X = (torch.rand(case.L_s, case.H_kv, case.N, generator=g) ** 8).to(torch.float32)
+    X[0, :, 700] = sink
+    X[0, :, 1900] = 0.3 * sink
+    X[0, :, 2199] = 0.1 * sink
+    ctx = _ctx(case, w)
+    y = pk.proxykv_map(ctx, X.cuda())
+    torch.cuda.synchronize()
+    assert_close(y, oracle.mapper(X, w, case.L_l), f"map with late sinks of {sink:g}")
+    pk.proxykv_destroy(ctx)
+
+
 def test_mapper_context_reuse_across_lengths():
     """One context called with a short, a longer and again a shorter sequence (the workspace of every lane grows in
     between; three distinct proxy layers run side by side): same bits as a fresh context each time, and the oracle's
