@@ -742,7 +742,7 @@ hipError_t mapper_batch(proxykv_ctx* ctx, const MapperWorkspace& ws, const MapPl
   const unsigned nl = (unsigned)lb.n;
   absmax_kernel<<<dim3(kRangeWords, nl), 1024, 0, stream>>>(x_in, (int64_t)c.H_kv * N, lb, m.range);
   PKV_TRY(hipGetLastError());
-  const int tok = (int64_t)nl * N >= 64 * 512 ? kStemTok : 16;
+  const int tok = (int64_t)nl * N >= 64 * 512 ? kStemTok : ((int64_t)nl * N >= 16 * 512 ? 16 : 4);
   stem_conv1_kernel<<<dim3((unsigned)((N + tok - 1) / tok), nl), 256, 0, stream>>>(
       x_in, w.conv1_w, w.bn1_scale, w.bn1_shift, m.range, w.stem_cw, w.stem_cs, lb, m.h1, c.H_kv, (int)N, c.c_mid, tok);
   PKV_TRY(hipGetLastError());

@@ -39,16 +39,22 @@ __device__ __forceinline__ void small_tile(int n_tiles, int& nt, int& mt) {
 // Where the A rows of small_wide_kernel come from.
 enum Prologue {
   kProHalf,    // fp16 rows as they are
-  kProLn,      // LayerNorm of fp32 rows; the normalised rows also go to x_out (fp32, the residual of the next sum)
+  kProLn,      // LayerNorm of fp32 rows; their means and scales also go to `stats`, for the residual of the next sum
   kProLnAvg    // token t: the mean, over the one or two windows that hold it, of the LayerNorm of its rows
 };
 enum WideEpilogue { kWideQkv, kWideRelu, kWideStage3 };
+
+// mean and 1 / standard deviation of a row: the next sum takes its residual as the row normalised once more (the rows themselves,
+// 1 MB per 512, took 0.8 us per launch to store)
+struct RowStats {
+  float mu, rstd;
+};
 
 struct WideArgs {
   const uint16_t* a_half;
   const float* pre;           // kProLn, kProLnAvg: rows to normalise
   const float *g, *b;         // LayerNorm scale and shift
-  float* x_out;
+  RowStats* stats;
   const uint16_t* w;          // [n_tiles * 64, 512]
   const float* bias;
   int n_tiles, tiles_per_layer;  // column tiles; row tiles of a layer
@@ -82,7 +88,7 @@ __device__ __forceinline__ float sum16(float v) {
   add(std::integral_constant<int, 0x140>{});  // row_mirror
   return v;
 }
-__device__ __forceinline__ void layernorm_row16(f32x8 (&v)[4], const f32x8 (&g)[4], const f32x8 (&b)[4]) {
+__device__ __forceinline__ RowStats layernorm_row16(f32x8 (&v)[4], const f32x8 (&g)[4], const f32x8 (&b)[4]) {
   float s = 0.0f;
 #pragma unroll
   for (int c = 0; c < 4; ++c)
@@ -99,6 +105,7 @@ __device__ __forceinline__ void layernorm_row16(f32x8 (&v)[4], const f32x8 (&g)[
   const float rstd = 1.0f / sqrtf(sum16(q) * (1.0f / kDT) + 1e-5f);
 #pragma unroll
   for (int c = 0; c < 4; ++c) v[c] = v[c] * rstd * g[c] + b[c];
+  return {mu, rstd};
 }
 
 // grid n_tiles * layers * tiles_per_layer, 128 KB of LDS: 64 A rows, then 64 W rows, 64 chunks of 16 bytes each, chunk c
@@ -165,22 +172,13 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void small_wide_kernel(WideArgs
 #pragma unroll
       for (int it = 0; it < kBatch; ++it) {
         const int row = wave * kWideRows + (it0 + it) * 4 + (lane >> 4);
-        layernorm_row16(v[it], g, b);
+        const RowStats st = layernorm_row16(v[it], g, b);
         if constexpr (PRO == kProLnAvg) {
           layernorm_row16(v2[it], g, b);
 #pragma unroll
           for (int c = 0; c < 4; ++c) v[it][c] = two[it] ? (v2[it][c] + v[it][c]) * 0.5f : v[it][c];
-        }
-        if constexpr (PRO == kProLn) {
-          // the column tiles of a row tile share the store of the normalised rows (all by one of them: 2 us longer)
-          if (row % a.n_tiles == nt && r0 + row < a.rows) {
-            float* dst = a.x_out + ((size_t)layer * a.stride + r0 + row) * kDT;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-              *reinterpret_cast<f32x4*>(dst + (c * 16 + j) * 8) = f32x4{v[it][c][0], v[it][c][1], v[it][c][2], v[it][c][3]};
-              *reinterpret_cast<f32x4*>(dst + (c * 16 + j) * 8 + 4) = f32x4{v[it][c][4], v[it][c][5], v[it][c][6], v[it][c][7]};
-            }
-          }
+        } else {
+          if (nt == 0 && j == 0 && r0 + row < a.rows) a.stats[(size_t)layer * a.stride + r0 + row] = st;
         }
 #pragma unroll
         for (int c = 0; c < 4; ++c)
@@ -308,7 +306,9 @@ struct DeepArgs {
   int K, rows, tiles_per_layer;
   int out_stride;     // output rows between layers
   const float *p0, *p1;  // bias, or scale and shift
-  const float* res;
+  const float* res;      // kDeepRes: the residual rows, as they are or, with `stats`, to be normalised; may be out_f32
+  const RowStats* stats;
+  const float *g, *b;    // LayerNorm scale and shift
   float* out_f32;
   uint16_t* out_h;
   const float* pe;
@@ -382,7 +382,12 @@ __global__ __launch_bounds__(256, 2) void small_deep_kernel(DeepArgs a) {
   const f32x4 p0 = *reinterpret_cast<const f32x4*>(a.p0 + n);
   if constexpr (EPI == kDeepRes) {
     const size_t o = ((size_t)layer * a.out_stride + t) * kDT + n;
-    *reinterpret_cast<f32x4*>(a.out_f32 + o) = v + (*reinterpret_cast<const f32x4*>(a.res + o) + p0);
+    f32x4 r = *reinterpret_cast<const f32x4*>(a.res + o);
+    if (a.stats != nullptr) {
+      const RowStats st = a.stats[(size_t)layer * a.out_stride + t];
+      r = (r - st.mu) * st.rstd * *reinterpret_cast<const f32x4*>(a.g + n) + *reinterpret_cast<const f32x4*>(a.b + n);
+    }
+    *reinterpret_cast<f32x4*>(a.out_f32 + o) = v + (r + p0);
   } else {
     const f32x4 p1 = *reinterpret_cast<const f32x4*>(a.p1 + n);
     const float up = exp2_int(stem_exponent(a.range + layer * kRangeWords, a.cw, a.cs));
@@ -558,6 +563,7 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   const int N = (int)N64, T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
   const LanePointers m = lane_pointers(c, p, ws);
   float *x = m.x, *pre = m.pre;
+  RowStats* stats = reinterpret_cast<RowStats*>(x);  // x is read for the last time before the first of them is written
   uint16_t *xb = m.xb, *qk = m.qk, *vt = m.vt, *ao = m.ao, *hid = m.hid;
 
   DeepArgs d = {};
@@ -580,7 +586,8 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   d.cs = w.stem_cs;
   PKV_TRY(launch_deep<kDeepGeluPeWin>(d, n_layers, stream));
 
-  // x: the normalised residual stream; pre: the sum that the next kernel normalises
+  // x: the encoder's first rows, the residual of the first sum; pre: the sum that the next kernel normalises, and the one behind it once
+  // more for its residual
   const int n_qb = ((T < kWin ? T : kWin) + 31) / 32;
   WideArgs a = {};
   a.tiles_per_layer = (T + 63) / 64;
@@ -588,7 +595,7 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   a.stride = Tp;
   a.n_win = n_win;
   a.pre = pre;
-  a.x_out = x;
+  a.stats = stats;
   d = DeepArgs{};
   d.rows = T;
   d.tiles_per_layer = (T + 31) / 32;
@@ -615,6 +622,11 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
     }
     small_attention_kernel<<<(unsigned)(n_layers * n_win * kHeads * n_qb), 256, 0, stream>>>(qk, vt, ao, T, Tp, n_win, n_qb, vt_ld);
     PKV_TRY(hipGetLastError());
+    if (li > 0) {
+      d.stats = stats;
+      d.g = w.enc[li - 1].ln2_g;
+      d.b = w.enc[li - 1].ln2_b;
+    }
     d.a = ao;
     d.lda = kDT;
     d.a_layer = (int64_t)Tp * kDT;
@@ -631,6 +643,10 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
     f.out_h = hid;
     f.ldc = c.d_ffn;
     PKV_TRY((launch_wide<kProLn, kWideRelu>(f, n_layers, stream)));
+    d.res = pre;
+    d.stats = stats;
+    d.g = e.ln1_g;
+    d.b = e.ln1_b;
     d.a = hid;
     d.lda = c.d_ffn;
     d.a_layer = (int64_t)Tp * c.d_ffn;
