@@ -53,7 +53,7 @@ inline size_t block_frags(const proxykv_config& c, int li) {
 inline size_t block_bias_frags(const proxykv_config& c, int li) {
   return (li > 0 ? 16 + (size_t)c.d_ffn / 64 : 0) + (li < c.n_enc_layers ? 24 : 0);
 }
-constexpr size_t kBlkFragBytes = 1024, kBlkRing = 8;  // a wave asks for weights eight fragments ahead
+constexpr size_t kBlkFragBytes = 1024, kBlkRing = 16;  // a wave asks for weights up to sixteen fragments ahead
 // Puts w.enc's matrices and biases in that order (w.blk_w, w.blk_b); implemented in mapper_block.hip.
 hipError_t pack_encoder_blocks(const proxykv_config& c, const MapperWeights& w, void* blk_w, void* blk_b, hipStream_t stream);
 
@@ -133,10 +133,11 @@ inline void window_plan(int64_t N, int win, int stride, int64_t* n_win, int64_t*
 constexpr int64_t kMapBatchRows = 65536, kMapPairRows = 131072, kMapSplitRows = 8192;
 constexpr int kMaxBatch = 32;
 static_assert(kMapBatchRows >= 256 * kMaxBatch && kMapSplitRows >= 256 * kMaxBatch, "a small-tile batch is neither cut nor split");
-// Up to this many rows in a batch the small tiles are faster (large tiles on the left, us: one layer of 200 rows 824 / 200, of 2000
-// 1061 / 565, of 4024 1084 / 997; two layers of 2000 1078 / 1003; 16 layers of 250 886 / 887), beyond it the large ones (one layer
-// of 6048 rows 1110 / 1435, of 8000 1208 / 1877; 16 layers of 400 1004 / 1467).
-constexpr int64_t kMapSmallRows = 4096;
+// Up to this many rows, each layer's counted in whole tiles of 64, the small tiles are faster (large tiles on the left, us: one layer of
+// 2048 rows 790 / 570, two of 1250 708 / 672, eight of 256 594 / 491, 20 of 110 586 / 591), beyond it the large ones, whose half blocks
+// take the same time until the chip is full (two layers of 1300 rows 717 / 730, eight of 380 614 / 709, 16 of 140 588 / 646, 28 of
+// 80 587 / 720; with whole blocks alone the line lay at 4096 rows: one layer of 5548 rows 1139, with half blocks 821).
+constexpr int64_t kMapSmallRows = 2560;
 struct MapPlan {
   int64_t N, n_win, T;  // tokens, windows and window rows of a layer
   int64_t Tp, Np;       // window rows and tokens of a layer, padded to the GEMM's 256-row tile
@@ -154,7 +155,7 @@ inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers,
   p.Np = (N + 255) / 256 * 256;
   p.vt_ld = p.n_win > 1 ? c.win : p.Tp;
   const int64_t few = (distinct_layers + kMaxBatch - 1) / kMaxBatch;  // batches, if only their number of layers were limited
-  p.small = (distinct_layers + few - 1) / few * p.T <= kMapSmallRows && c.n_enc_layers > 0;
+  p.small = (distinct_layers + few - 1) / few * ((p.T + 63) / 64 * 64) <= kMapSmallRows && c.n_enc_layers > 0;
   int64_t cap = kMapBatchRows / p.Tp;
   if (cap < 2) cap = 2 * p.Tp <= kMapPairRows ? 2 : 1;
   if (cap > most) cap = most;

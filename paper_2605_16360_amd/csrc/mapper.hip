@@ -384,8 +384,8 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
 // held with half's full relative precision up to 2^16, and those far below the reference are nothing beside the attained one.  Where
 // one goes beyond, a row sum is infinite, and the workgroup does its keys again with the reference raised wherever a logit
 // exceeds it by more than 2^8.  (With that check in every tile the maxima are a sixth of the vector instructions.)
-// Layer b of the batch owns rows [b * Tp, b * Tp + T); its windows start every 2048 rows.  What the block of a layer's last row holds beyond
-// it is finite, and keys there are masked; blocks beyond are not read as keys, and queries there are computed and dropped.
+// Layer b of the batch owns rows [b * Tp, b * Tp + T); its windows start every 2048 rows.  What the 64 rows of a layer's last row hold beyond
+// it is finite, and keys there are masked; rows behind are not read as keys, and queries there are computed and dropped.
 // Block -> work mapping: blocks are dealt round-robin to the 8 XCDs, so with n_qb blocks of 256 queries per window block
 // b takes q-block (b / 8) % n_qb of item (b / 8 / n_qb) * 8 + b % 8: the q-blocks of one (window, head) run on one XCD
 // and share its L2 copy of that head's K and V.
@@ -578,7 +578,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
   attend(std::false_type{});
   bool bad = false;
 #pragma unroll
-  for (int qt = 0; qt < 4; ++qt) bad |= (q0 + qt) * 16 < (len + kBlk - 1) / kBlk * kBlk && !(ls[qt][0] < 1.0e30f);
+  for (int qt = 0; qt < 4; ++qt) bad |= (q0 + qt) * 16 < n_tiles * 64 && !(ls[qt][0] < 1.0e30f);
   if (__syncthreads_or(bad)) attend(std::true_type{});
 
   // output: O^T / row sum; a lane's eight accumulators are the unit that the next product's operand wants from it
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
   for (int qt = 0; qt < 4; ++qt) {
     const float inv = 1.0f / ls[qt][0];
     const int tile = q0 + qt;
-    if (tile * 16 >= (len + kBlk - 1) / kBlk * kBlk) continue;
+    if (tile * 16 >= n_tiles * 64) continue;
     u32x4* ob = ao + (blk0 + (tile >> 3)) * (kBlk * kDT / 8) + ((tile & 7) * 16 + hd * 2) * 64 + lane;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {

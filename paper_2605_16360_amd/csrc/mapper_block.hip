@@ -1,14 +1,14 @@
 // The encoder of the large-tile mapper, everything but the attention: out-projection, residual, LayerNorm, both FFN products, residual,
 // LayerNorm and the next layer's q, k and v in one launch per layer.  (The first launch has only q, k and v, the last no q, k and v.)
 //
-// A workgroup takes a block of 128 rows through all of it.  As separate products (256 x 256 and 128 x 512 tiles, normalised rows
+// A workgroup takes a block of 128 rows, or half of one, through all of it.  As separate products (256 x 256 and 128 x 512 tiles, normalised rows
 // and hidden rows through memory) a layer moved 28 times the 1 KB of an fp16 row, as here with the attention 12 times; and those kernels
 // stood in waits of one workgroup per CU 28 to 42 % of the time: 126 976 rows took 1117 us per layer beside the attention.
 //
 // Four waves, one per SIMD, each with all 512 registers of a lane.  The block's operand (attention output, then normalised rows) lies
 // in LDS, 128 KB, in the order in which MFMA fragments are read.  Every wave owns a quarter of each product's features, so it needs
 // weights that no other wave of the workgroup reads: they come from L2 straight into registers, in the order of their use, eight
-// fragments ahead, and never through LDS.
+// fragments ahead (sixteen for half a block), and never through LDS.
 // The weights are the products' left operand, so a lane holds a token's column and what it has accumulated are, eight
 // at a time, exactly what it has to supply of the next product's right operand: the hidden rows go to the other waves through
 // LDS as they are, 64 features at a time, the product with them starting from the residual row in the accumulators.
@@ -23,8 +23,10 @@ namespace pkv {
 namespace {
 
 // LDS in 16-byte units: the token tile, then two stages of 64 hidden features
-constexpr int kXtU4 = kBlk * kDT / 8, kHidU4 = kBlk * 64 / 8;
-constexpr int kBlkLds = (kXtU4 + 2 * kHidU4) * 16;
+template <int NT>
+struct BlockLds {
+  static constexpr int kX = NT * 16 * 64, kHid = NT * 2 * 64, kBytes = (kX + 2 * kHid) * 16;
+};
 
 struct BlockArgs {
   const u32x4* w;      // packed weights, this launch's stream of wave 0; wave w's starts w_wave fragments later
@@ -34,7 +36,7 @@ struct BlockArgs {
   const u32x4* ao;     // attention output
   f32x4* x;            // residual stream
   u32x4* qkv;
-  int T, Tp, blocks;   // valid rows of a layer, rows between layers, blocks of a layer
+  int T, Tp, parts;    // valid rows of a layer, rows between layers, workgroups of a layer
   int chunks;          // d_ffn / 256
 };
 
@@ -68,27 +70,29 @@ __device__ __forceinline__ u32x4 pack8(const f32x4& lo, const f32x4& hi) {
   return __builtin_bit_cast(u32x4, __builtin_convertvector(t, f16x8));
 }
 
-template <bool FIRST, bool LAST>
+// NT token tiles of 16: a whole block of 128 rows, or half of one (kHalfBlocks).  The sums are the same, in the same order.
+template <int NT, bool FIRST, bool LAST>
 __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) void encoder_block_kernel(BlockArgs a) {
-  // the token tile, [8 tiles of 16 tokens][16 K steps of 32], then two stages of hidden rows, [2][8][2]
+  // the token tile, [NT tiles of 16 tokens][16 K steps of 32], then two stages of hidden rows, [2][NT][2]
   extern __shared__ u32x4 lds[];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const unsigned ul = (unsigned)lane;
-  const int layer = blockIdx.x / a.blocks, b = blockIdx.x % a.blocks;
+  constexpr int kXtU4 = BlockLds<NT>::kX, kHidU4 = BlockLds<NT>::kHid, P = 8 / NT, R = NT == 8 ? 8 : 16;  // R: fragments asked for ahead
+  const int layer = blockIdx.x / a.parts, part = blockIdx.x % a.parts, b = part / P, t0 = part % P * NT;
   const size_t blk = (size_t)layer * (a.Tp / kBlk) + b;
   const unsigned l16b = ul * 16;
-  const __amdgpu_buffer_rsrc_t xr = resource(a.x + (blk * 4 + wave) * (8 * 8 * 64), 8 * 8 * 1024);  // the wave's part of the residual stream
-  const __amdgpu_buffer_rsrc_t wr = resource(a.w + (size_t)wave * a.w_wave * 64, (a.w_wave + kBlkRing) * kBlkFragBytes);
+  const __amdgpu_buffer_rsrc_t xr = resource(a.x + ((blk * 4 + wave) * 8 + t0) * (8 * 64), NT * 8 * 1024);  // the wave's part of the residual stream
+  const __amdgpu_buffer_rsrc_t wr = resource(a.w + (size_t)wave * a.w_wave * 64, (a.w_wave + R) * kBlkFragBytes);
   const __amdgpu_buffer_rsrc_t br = resource(a.bias + (size_t)wave * a.bias_wave * 64, (a.bias_wave + 4) * kBlkFragBytes);
   int wp = 0, bp = 0;  // positions in the weights and the biases, bytes
-  u32x4 rg[kBlkRing];
+  u32x4 rg[R];
 #pragma unroll
-  for (int i = 0; i < (int)kBlkRing; ++i) rg[i] = load16(wr, l16b, i * 1024);
+  for (int i = 0; i < R; ++i) rg[i] = load16(wr, l16b, i * 1024);
 
   u32x4 ones = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};  // bf16
   asm volatile("" : "+v"(ones));  // made once, and not in front of an instruction that reads it
-  f32x4 acc[8][8];  // [16 tokens][16 features]
-  u32x4 f[2][8];    // token fragments of this K step and the next
+  f32x4 acc[NT][8];  // [16 tokens][16 features]
+  u32x4 f[2][NT];    // token fragments of this K step and the next
 
   // The lane, as a value that the compiler does not know: addresses made from it are made anew and not kept (and spilled) between
   // phases.  A reload behind the stores of the residual rows would wait for all of them.
@@ -100,7 +104,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
   auto read_x = [&]() __attribute__((always_inline)) {
     const u32x4* src = lds + fresh();
 #pragma unroll
-    for (int tt = 0; tt < 8; ++tt) f[0][tt] = src[tt * 16 * 64];
+    for (int tt = 0; tt < NT; ++tt) f[0][tt] = src[tt * 16 * 64];
   };
   // acc (+)= product with the token tile, K = 512.  Of two MFMAs in a row one operand is the same, also where the feature tile changes:
   // what the matrix cores draw, and with it the clock, depends on how much of their input changes.
@@ -109,23 +113,23 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     for (int g = 0; g < 8; ++g) {
       static_for<2>([&](auto kc) {
         constexpr int kk = decltype(kc)::value;
-        static_for<64>([&](auto jc) {
-          constexpr int j = decltype(jc)::value, mt = j >> 3, tt = (mt & 1) ? 7 - (j & 7) : (j & 7);
-          const f16x8 fw = as_f16x8(rg[mt]), fx = as_f16x8(f[kk][tt]);
+        static_for<8 * NT>([&](auto jc) {
+          constexpr int j = decltype(jc)::value, mt = j / NT, tt = (mt & 1) ? NT - 1 - j % NT : j % NT, slot = (kk * 8 + mt) % R;
+          const f16x8 fw = as_f16x8(rg[slot]), fx = as_f16x8(f[kk][tt]);
           acc[tt][mt] = decltype(swap)::value ? mfma_f16_16x16x32(fx, fw, acc[tt][mt]) : mfma_f16_16x16x32(fw, fx, acc[tt][mt]);
-          if constexpr (j % 4 == 0 && j < 32) f[kk ^ 1][j / 4] = xp[(j / 4 * 16 + kk + 1) * 64];
-          if constexpr ((j & 7) == 7) rg[mt] = load16(wr, l16b, wp + (mt + (int)kBlkRing) * 1024);
+          if constexpr (j % 4 == 0 && j < 4 * NT) f[kk ^ 1][j / 4] = xp[(j / 4 * 16 + kk + 1) * 64];
+          if constexpr (j % NT == NT - 1) rg[slot] = load16(wr, l16b, wp + (kk * 8 + mt + R) * 1024);
           __builtin_amdgcn_sched_barrier(0);
         });
-        wp += (int)kBlkRing * 1024;
       });
+      wp += 16 * 1024;
       xp += 2 * 64;
     }
   };
   auto put_x = [&]() __attribute__((always_inline)) {
     u32x4* dst = lds + wave * 4 * 64 + fresh();
 #pragma unroll
-    for (int tt = 0; tt < 8; ++tt)
+    for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
       for (int s = 0; s < 4; ++s) dst[(tt * 16 + s) * 64] = pack8(acc[tt][2 * s], acc[tt][2 * s + 1]);
   };
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 
   if constexpr (!FIRST) {
     // the block's attention output, as it lies
-    const u32x4* ag = a.ao + blk * kXtU4 + wave * 64;
+    const u32x4* ag = a.ao + (blk * 8 + t0) * (16 * 64) + wave * 64;
     typedef const __attribute__((address_space(1))) void* gptr_t;
     typedef __attribute__((address_space(3))) void* lptr_t;
 #pragma unroll
@@ -147,16 +151,16 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
       __builtin_amdgcn_global_load_lds((gptr_t)((ag + i * 256) + ul), (lptr_t)(lds + i * 256 + wave * 64), 16, 0, 0);
   }
 #pragma unroll
-  for (int tt = 0; tt < 8; ++tt)
+  for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
     for (int mt = 0; mt < 8; ++mt) acc[tt][mt] = __builtin_bit_cast(f32x4, load16(xr, l16b, (tt * 8 + mt) * 1024));
 
   if constexpr (FIRST) {
     // rows past the layer's last one become zeros, so that everything computed from them is finite
-    const int rows = a.T - b * kBlk;
-    if (rows < kBlk) {
+    const int rows = a.T - b * kBlk - t0 * 16;
+    if (rows < NT * 16) {
 #pragma unroll
-      for (int tt = 0; tt < 8; ++tt)
+      for (int tt = 0; tt < NT; ++tt)
         if (tt * 16 + (lane & 15) >= rows) {
 #pragma unroll
           for (int mt = 0; mt < 8; ++mt) {
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 #pragma unroll
       for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-        for (int tt = 0; tt < 8; ++tt)
+        for (int tt = 0; tt < NT; ++tt)
           acc[tt][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(bf[mt]), as_bf16x8(ones), acc[tt][mt], 0, 0, 0);
     };
     add_bias();
@@ -189,7 +193,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
     struct Pair {
       float s1, s2;
     };
-    Pair* red = reinterpret_cast<Pair*>(lds + kXtU4);  // [4 waves][128 tokens], in place of the hidden rows
+    Pair* red = reinterpret_cast<Pair*>(lds + kXtU4);  // [4 waves][16 NT tokens], in place of the hidden rows
     auto layer_norm = [&](const float* g, const float* be) __attribute__((always_inline)) {
       const __amdgpu_buffer_rsrc_t gr = resource(g + wave * 128, 512), er = resource(be + wave * 128, 512);
       const unsigned l = fresh(), q = l >> 4, col = l & 15;
@@ -200,7 +204,7 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
         b4[mt] = __builtin_bit_cast(f32x4, load16(er, q * 16, mt * 64));
       }
 #pragma unroll
-      for (int tt = 0; tt < 8; ++tt) {
+      for (int tt = 0; tt < NT; ++tt) {
         float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
         for (int mt = 0; mt < 8; ++mt)
@@ -211,16 +215,16 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
           }
         s1 = quads_sum(s1);
         s2 = quads_sum(s2);
-        if (q == 0) red[wave * kBlk + tt * 16 + col] = Pair{s1, s2};
+        if (q == 0) red[wave * NT * 16 + tt * 16 + col] = Pair{s1, s2};
         __builtin_amdgcn_sched_barrier(0);
       }
       __syncthreads();
 #pragma unroll
-      for (int tt = 0; tt < 8; ++tt) {
+      for (int tt = 0; tt < NT; ++tt) {
         float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          const Pair p = red[w * kBlk + tt * 16 + col];
+          const Pair p = red[w * NT * 16 + tt * 16 + col];
           s1 += p.s1;
           s2 += p.s2;
         }
@@ -246,42 +250,49 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 
     for (int c = 0; c < a.chunks; ++c) {
       // 64 hidden features per wave
-      f32x4 h[8][4];
+      f32x4 h[NT][4];
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-        for (int tt = 0; tt < 8; ++tt) bias_v(h[tt][mt], b1[mt], ones);
+        for (int tt = 0; tt < NT; ++tt) bias_v(h[tt][mt], b1[mt], ones);
       const u32x4* xp = lds + fresh();
-      u32x2 ph[8][4];
+      u32x2 ph[NT][4];
       // ReLU and rounding of a finished tile; half of them are at once what another wave reads
       auto finish = [&](auto tc, auto mc) __attribute__((always_inline)) {
         constexpr int tt = decltype(tc)::value, mt = decltype(mc)::value;
         const f16x4 z = {0, 0, 0, 0};
         ph[tt][mt] = __builtin_bit_cast(u32x2, __builtin_elementwise_max(__builtin_convertvector(h[tt][mt], f16x4), z));
       };
+      constexpr int kLag = 8 / NT;  // rows of tiles between a tile's last MFMA and its rounding: eight MFMAs
       auto step = [&](auto kc, auto last) __attribute__((always_inline)) {
-        constexpr int kk = decltype(kc)::value;
-        static_for<32>([&](auto jc) {
-          constexpr int j = decltype(jc)::value, mt = j >> 3, tt = (mt & 1) ? 7 - (j & 7) : (j & 7);
-          mfma_v(h[tt][mt], rg[kk * 4 + mt], f[kk][tt]);
-          if constexpr (!decltype(last)::value && j % 3 == 0 && j < 24) f[kk ^ 1][j / 3] = xp[(j / 3 * 16 + kk + 1) * 64];
-          if constexpr ((j & 7) == 7) rg[kk * 4 + mt] = load16(wr, l16b, wp + (kk * 4 + mt + (int)kBlkRing) * 1024);
-          // the tile whose last MFMA was eight MFMAs ago
-          if constexpr (decltype(last)::value && mt > 0) finish(std::integral_constant<int, 7 - tt>{}, std::integral_constant<int, mt - 1>{});
+        constexpr int kk = decltype(kc)::value, cur = kk & 1;
+        static_for<4 * NT>([&](auto jc) {
+          constexpr int j = decltype(jc)::value, mt = j / NT, tt = (mt & 1) ? NT - 1 - j % NT : j % NT, slot = (kk * 4 + mt) % R;
+          mfma_v(h[tt][mt], rg[slot], f[cur][tt]);
+          if constexpr (!decltype(last)::value && j % 3 == 0 && j < 3 * NT) f[cur ^ 1][j / 3] = xp[(j / 3 * 16 + kk + 1) * 64];
+          if constexpr (j % NT == NT - 1) rg[slot] = load16(wr, l16b, wp + (kk * 4 + mt + R) * 1024);
+          if constexpr (decltype(last)::value && mt >= kLag)
+            finish(std::integral_constant<int, kLag % 2 ? NT - 1 - tt : tt>{}, std::integral_constant<int, mt - kLag>{});
           __builtin_amdgcn_sched_barrier(0);
         });
       };
-      for (int g = 0; g < 7; ++g) {
-        step(std::integral_constant<int, 0>{}, std::false_type{});
-        step(std::integral_constant<int, 1>{}, std::false_type{});
-        xp += 2 * 64;
-        wp += (int)kBlkRing * 1024;
+      constexpr int kSteps = R / 4;
+#pragma unroll 1
+      for (int g = 0; g < 16 / kSteps - 1; ++g) {
+        static_for<kSteps>([&](auto kc) { step(kc, std::false_type{}); });
+        xp += kSteps * 64;
+        wp += R * 1024;
       }
-      step(std::integral_constant<int, 0>{}, std::false_type{});
-      step(std::integral_constant<int, 1>{}, std::true_type{});
-      wp += (int)kBlkRing * 1024;
-      asm volatile("s_nop 15\n\ts_nop 7" : "+v"(h[0][3]), "+v"(h[1][3]), "+v"(h[2][3]), "+v"(h[3][3]), "+v"(h[4][3]), "+v"(h[5][3]), "+v"(h[6][3]), "+v"(h[7][3]));
-      static_for<8>([&](auto tc) { finish(tc, std::integral_constant<int, 3>{}); });
+      static_for<kSteps>([&](auto kc) { step(kc, std::integral_constant<bool, decltype(kc)::value == kSteps - 1>{}); });
+      wp += R * 1024;
+      if constexpr (NT == 8)
+        asm volatile("s_nop 15\n\ts_nop 7" : "+v"(h[0][3]), "+v"(h[1][3]), "+v"(h[2][3]), "+v"(h[3][3]), "+v"(h[4][3]), "+v"(h[5][3]), "+v"(h[6][3]), "+v"(h[7][3]));
+      else
+        asm volatile("s_nop 15\n\ts_nop 7" : "+v"(h[0][2]), "+v"(h[1][2]), "+v"(h[2][2]), "+v"(h[3][2]), "+v"(h[0][3]), "+v"(h[1][3]), "+v"(h[2][3]), "+v"(h[3][3]));
+      static_for<NT * kLag>([&](auto tc) {
+        constexpr int i = decltype(tc)::value;
+        finish(std::integral_constant<int, i % NT>{}, std::integral_constant<int, 4 - kLag + i / NT>{});
+      });
       bp += 4 * 1024;
 #pragma unroll
       for (int mt = 0; mt < 4; ++mt) b1[mt] = load16(br, l16b, bp + mt * 1024);
@@ -289,13 +300,13 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
       auto put_h = [&](int q) __attribute__((always_inline)) {
         u32x2* dst = reinterpret_cast<u32x2*>(lds + kXtU4 + (q & 1) * kHidU4 + (wave >> 1) * 64 + fresh()) + (wave & 1);
 #pragma unroll
-        for (int tt = 0; tt < 8; ++tt) dst[tt * 2 * 64 * 2] = ph[tt][q];
+        for (int tt = 0; tt < NT; ++tt) dst[tt * 2 * 64 * 2] = ph[tt][q];
       };
       put_h(0);
       put_h(1);
       __syncthreads();
 #pragma unroll
-      for (int tt = 0; tt < 8; ++tt) f[0][tt] = lds[kXtU4 + tt * 2 * 64 + ul];
+      for (int tt = 0; tt < NT; ++tt) f[0][tt] = lds[kXtU4 + tt * 2 * 64 + ul];
       static_for<4>([&](auto qc) {
         constexpr int q = decltype(qc)::value;
         const u32x4* hp = lds + kXtU4 + (q & 1) * kHidU4 + ul;
@@ -307,25 +318,25 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
             __syncthreads();
             if constexpr (q < 2) put_h(q + 2);
           }
-          static_for<64>([&](auto jc) {
-            constexpr int j = decltype(jc)::value, mt = j >> 3, tt = (mt & 1) ? 7 - (j & 7) : (j & 7);
-            acc[tt][mt] = mfma_f16_16x16x32(as_f16x8(rg[mt]), as_f16x8(f[kk][tt]), acc[tt][mt]);
-            if constexpr (j % 4 == 0 && j < 32) {
+          static_for<8 * NT>([&](auto jc) {
+            constexpr int j = decltype(jc)::value, mt = j / NT, tt = (mt & 1) ? NT - 1 - j % NT : j % NT, slot = (kk * 8 + mt) % R;
+            acc[tt][mt] = mfma_f16_16x16x32(as_f16x8(rg[slot]), as_f16x8(f[kk][tt]), acc[tt][mt]);
+            if constexpr (j % 4 == 0 && j < 4 * NT) {
               if constexpr (kk == 0) f[1][j / 4] = hp[(j / 4 * 2 + 1) * 64];
               else if constexpr (q < 3) f[0][j / 4] = hn[j / 4 * 2 * 64];
               else f[0][j / 4] = lds[j / 4 * 16 * 64 + ul];
             }
-            if constexpr ((j & 7) == 7) rg[mt] = load16(wr, l16b, wp + (mt + (int)kBlkRing) * 1024);
+            if constexpr (j % NT == NT - 1) rg[slot] = load16(wr, l16b, wp + (kk * 8 + mt + R) * 1024);
             __builtin_amdgcn_sched_barrier(0);
           });
-          wp += (int)kBlkRing * 1024;
         });
+        wp += 16 * 1024;
       });
     }
     layer_norm(a.ln2_g, a.ln2_b);
     if constexpr (!LAST) load_bf();  // in front of the stores: loads are counted in order with them
 #pragma unroll
-    for (int tt = 0; tt < 8; ++tt)
+    for (int tt = 0; tt < NT; ++tt)
 #pragma unroll
       for (int mt = 0; mt < 8; ++mt) store16(xr, l16b, (tt * 8 + mt) * 1024, __builtin_bit_cast(u32x4, acc[tt][mt]));
     if constexpr (!LAST) {
@@ -342,18 +353,18 @@ __global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1))) 
 #pragma unroll
       for (int mt = 0; mt < 8; ++mt)
 #pragma unroll
-        for (int tt = 0; tt < 8; ++tt) {
+        for (int tt = 0; tt < NT; ++tt) {
           if constexpr (r < 2) bias_a(acc[tt][mt], bf[mt], ones);
           else bias_a(acc[tt][mt], ones, bf[mt]);
         }
       if constexpr (r > 0) read_x();
       gemm_x(std::integral_constant<bool, r == 2>{});
       if constexpr (r < 2) load_bf();
-      static_for<16>([&](auto uc) {
+      static_for<2 * NT>([&](auto uc) {
         constexpr int u = decltype(uc)::value;
         static_for<2>([&](auto hc) {
           constexpr int head = decltype(hc)::value;
-          const int at = ((head * 3 + r) * 16 + u) * 1024;
+          const int at = ((head * 3 + r) * 16 + t0 * 2 + u) * 1024;
           if constexpr (r < 2) store16(qr, l16b, at, pack8(acc[u >> 1][head * 4 + 2 * (u & 1)], acc[u >> 1][head * 4 + 2 * (u & 1) + 1]));
           else store16(qr, l16b, at, pack8(acc[2 * (u >> 2)][head * 4 + (u & 3)], acc[2 * (u >> 2) + 1][head * 4 + (u & 3)]));
         });
@@ -419,18 +430,30 @@ __global__ __launch_bounds__(256) void pack_bias_kernel(PackArgs a) {
   a.bias[((size_t)wave * gridDim.x + blockIdx.x) * 64 + lane] = v;
 }
 
-template <bool FIRST, bool LAST>
-hipError_t launch(const BlockArgs& a, int blocks, hipStream_t stream) {
+template <int NT, bool FIRST, bool LAST>
+hipError_t launch(const BlockArgs& a, int n_layers, hipStream_t stream) {
   static bool attr_set = false;  // per instantiation; setting it again is harmless
   if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&encoder_block_kernel<FIRST, LAST>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kBlkLds);
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&encoder_block_kernel<NT, FIRST, LAST>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, BlockLds<NT>::kBytes);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  encoder_block_kernel<FIRST, LAST><<<blocks, 256, kBlkLds, stream>>>(a);
+  encoder_block_kernel<NT, FIRST, LAST><<<n_layers * a.parts, 256, BlockLds<NT>::kBytes, stream>>>(a);
   return hipGetLastError();
 }
+template <int NT>
+hipError_t launch_parts(BlockArgs a, int n_layers, int li, int n_enc, hipStream_t stream) {
+  a.parts = (a.T + NT * 16 - 1) / (NT * 16);
+  if (li == 0) return launch<NT, true, false>(a, n_layers, stream);
+  if (li == n_enc) return launch<NT, false, true>(a, n_layers, stream);
+  return launch<NT, false, false>(a, n_layers, stream);
+}
+// Up to this many blocks in flight (half the CUs) each is given to two workgroups.  A whole block's time is its matrix work, a half's
+// its weights' way from L2 (6.3 MB for each workgroup and layer, 64 bytes a clock and CU), and both take about the same: a quarter would win nothing.
+// us, halves / wholes: one layer of 5548 rows 821 / 1139, of 16 k 1132 / 1323, 16 of 500 665 / 978; with 129 .. 256 blocks some
+// CUs do two halves in turn, one layer of 26 k 1945 / 1738.
+constexpr int64_t kHalfBlocks = 128;
 }  // namespace
 
 hipError_t pack_encoder_blocks(const proxykv_config& c, const MapperWeights& w, void* blk_w, void* blk_b, hipStream_t stream) {
@@ -488,12 +511,9 @@ hipError_t launch_encoder_block(const proxykv_ctx* ctx, const MapPlan& p, int n_
   a.qkv = (u32x4*)qkv;
   a.T = (int)p.T;
   a.Tp = (int)p.Tp;
-  a.blocks = (int)((p.T + kBlk - 1) / kBlk);
   a.chunks = c.d_ffn / 256;
-  const int blocks = n_layers * a.blocks;
-  if (li == 0) return launch<true, false>(a, blocks, stream);
-  if (li == c.n_enc_layers) return launch<false, true>(a, blocks, stream);
-  return launch<false, false>(a, blocks, stream);
+  const int64_t blocks = (p.T + kBlk - 1) / kBlk * n_layers * p.lanes;  // of all lanes together
+  return blocks <= kHalfBlocks ? launch_parts<4>(a, n_layers, li, c.n_enc_layers, stream) : launch_parts<8>(a, n_layers, li, c.n_enc_layers, stream);
 }
 
 }  // namespace pkv

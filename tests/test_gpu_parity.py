@@ -491,9 +491,8 @@ def test_mapper_batches_of_layers(L_s, L_l, N):
 
 @pytest.mark.parametrize("L,N", [(1, 2049), (1, 2500), (1, 3072), (1, 3073), (2, 2048), (2, 2049), (3, 1365), (3, 1366)])
 def test_mapper_on_both_sides_of_the_small_tiles(L, N):
-    """Batches of up to 4096 window rows run in the small-tile kernels.  One layer of 2049 .. 3072 tokens has two windows there
-    (overlap averaging, a token's row stored into both windows, v split at the window), 3073 tokens are the first of the
-    large tiles; two and three layers of one window on either side of the line."""
+    """Around the sizes where the small-tile kernels end: one layer of one, two and three windows (overlap averaging, a token's row stored
+    into both windows, v split at the window), two and three layers of one window."""
     case = synth.scaled_case(synth.CASES["llama_8k"], name="small", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=N, N_q=1, chunk=1,
                              n_planted=0)
     w = synth.make_mapper_weights(case.H_kv, case.H_l)
@@ -520,6 +519,27 @@ def test_mapper_at_the_edges_of_a_block(L, N):
     torch.cuda.synchronize()
     assert_close(y, oracle.mapper(X.float(), w, L), f"map {L} layers, N={N}")
     pk.proxykv_destroy(ctx)
+
+
+@pytest.mark.parametrize("L,N", [(1, 2048), (2, 1280), (2, 1281), (5, 512), (5, 513), (20, 65), (21, 65)])
+def test_mapper_where_the_small_tiles_end(L, N):
+    """40 tiles of 64 rows are the last that the small tiles take: on the line and one row or layer beyond it, where half blocks begin."""
+    test_mapper_at_the_edges_of_a_block(L, N)
+
+
+def test_mapper_half_blocks_are_whole_blocks_bit_for_bit():
+    """26 layers of 600 tokens are two times 65 blocks, more than half of the CUs, and run as whole blocks; the first 8 of them alone
+    run as halves, of which each layer's last holds 24 rows."""
+    y = []
+    for L in (26, 8):
+        case = synth.scaled_case(synth.CASES["llama_8k"], name="halves", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=600, N_q=1, chunk=1, n_planted=0)
+        w = synth.make_mapper_weights(case.H_kv, case.H_l)
+        X = (torch.rand(26, case.H_kv, 600, generator=torch.Generator().manual_seed(77)) ** 8)[:L].contiguous()
+        ctx = _ctx(case, w)
+        y.append(pk.proxykv_map(ctx, X.float().cuda())[:8].clone())
+        torch.cuda.synchronize()
+        pk.proxykv_destroy(ctx)
+    assert torch.equal(y[0], y[1])
 
 
 def test_mapper_with_scores_beyond_the_half_range():
