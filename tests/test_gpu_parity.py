@@ -378,6 +378,23 @@ def test_score_few_and_many_query_blocks_agree(d, N, N_q, chunk):
         pk.proxykv_destroy(cf)
 
 
+@pytest.mark.parametrize("N_q", [512, 513])
+@pytest.mark.parametrize("scale", [1.0, 30.0])
+def test_score_of_1024_query_blocks_and_of_more(N_q, scale):
+    """64 layers of 8 heads of 128: 512 queries make the last 1024 blocks of pass 1 with 32-column matrix tiles, 513 use 16-column ones;
+    also with nearly one-hot rows, where its reference is replaced many times."""
+    L, H_q, H_kv, d, N, chunk = 64, 8, 2, 128, 300, 200
+    g = torch.Generator().manual_seed(N_q)
+    q = (scale * torch.randn(L, H_q, N_q, d, generator=g)).bfloat16()
+    kc, kr = (torch.randn(L, H_kv, n, d, generator=g).bfloat16() for n in (N, N_q))
+    ctx = pk.proxykv_create(pk.make_config(L, H_q, H_kv, d, 1, 4, 128))
+    x = pk.proxykv_score(ctx, q.cuda(), kc.cuda(), kr.cuda(), chunk)
+    torch.cuda.synchronize()
+    for l in (0, L - 1):
+        assert_close(x[l:l + 1], oracle.score(q[l:l + 1], kc[l:l + 1], kr[l:l + 1], chunk), f"score layer {l}")
+    pk.proxykv_destroy(ctx)
+
+
 @pytest.mark.parametrize("scale", [8.0, 30.0])
 def test_score_large_logits(scale):
     """Inputs scaled up until the softmax rows are nearly one-hot (logits of several hundred): the running reference of
