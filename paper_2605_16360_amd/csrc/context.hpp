@@ -121,15 +121,13 @@ inline void window_plan(int64_t N, int win, int stride, int64_t* n_win, int64_t*
 }
 
 // How the mapper runs a context of N tokens: the distinct proxy layers in `n_batches` batches, dealt to `lanes` streams.
-// Small layers leave the chip idle one by one (512 window rows are 12 output tiles of the QKV product), so a batch takes
-// several, up to kMapBatchRows rows.  Two batches side by side, on streams and in workspaces of their own, let one's stores and
-// residual reads run under the other's matrix work, so layers of more than kMapSplitRows rows together make an even number
-// of batches (3 layers of 3000 tokens in one 1592 us, in two 1462); and because two lanes of one long layer each are slower than
-// four layers in flight (N = 32 768: 83.3 and 82.7 ms), a batch takes two layers if they are no more than kMapPairRows rows.
+// Small layers leave the chip idle one by one (1500 rows are 12 blocks on 256 CUs), so a batch takes
+// several, up to kMapBatchRows rows.  Two batches side by side, on streams and in workspaces of their own, let one's loads, stores
+// and attention run beside the other's products, so layers of more than kMapSplitRows rows together make an even number
+// of batches (3 layers of 3000 tokens in one 990 us, in two 953); a batch takes two layers if they are no more than kMapPairRows rows.
 // Every row holds about 7 KB of workspace for as long as the context lives, so the limits are where more costs more than it gives.
-// 16 distinct layers, ms and MB: one layer per batch on four streams / batches of up to 131 072 rows, 12 KB per row / as here:
-//   N = 1500   4.56, 94  / 2.24, 334  / 2.12, 186      N = 8192    19.5, 690  / 18.7, 3410 / 18.9, 812
-//   N = 4096   9.06, 306 / 8.41, 1228 / 8.18, 700      N = 32 768  82.9, 2998 / 82.9, 3442 / 82.7, 1810
+// 16 distinct layers, us, one layer per batch / as here:
+//   N = 1500   1753 / 1491     N = 4096   7575 / 5973     N = 8192   13 756 / 13 939     N = 32 768   60 440 / 60 527
 constexpr int64_t kMapBatchRows = 65536, kMapPairRows = 131072, kMapSplitRows = 8192;
 constexpr int kMaxBatch = 32;
 static_assert(kMapBatchRows >= 256 * kMaxBatch && kMapSplitRows >= 256 * kMaxBatch, "a small-tile batch is neither cut nor split");

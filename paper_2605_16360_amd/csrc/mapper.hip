@@ -1,15 +1,14 @@
 // HybridAxialMapper forward (paper Sec. 4.1) for a batch of proxy layers at a time:
 //   stage 1  conv stem            stem_conv1_kernel (fp32 ALU) + conv 2 as an fp16 MFMA GEMM whose A rows
 //                                 are overlapping 3-token spans of the padded conv-1 output
-//   stage 2  time-axis encoder    per encoder layer: QKV GEMM (writes q, k row-major and v transposed
-//                                 for the attention's second product) -> window attention -> out-proj GEMM whose
-//                                 epilogue adds the residual and normalises the row -> FFN-1 GEMM -> FFN-2 GEMM
-//                                 with the same epilogue; all sliding windows of all proxy layers of the batch lie
-//                                 on the GEMM M axis
+//   stage 2  time-axis encoder    per encoder layer: encoder_block_kernel (mapper_block.hip; everything beside the attention, up to the
+//                                 next layer's q, k and v) -> window attention; the sliding windows of all proxy layers of
+//                                 the batch lie on one axis of rows
 //            overlap averaging    overlap_avg_kernel
 //   stage 3  head-axis attention  K/V projection GEMM (inner products with queries / output weights in its epilogue)
 //                                  + stage3_kernel (softmax over the slots per token and head, fp32 ALU)
-// Matrix products take IEEE half (fp16) operands and accumulate in fp32 on v_mfma_f32_32x32x16_f16; the
+// Matrix products take IEEE half (fp16) operands and accumulate in fp32, the two here on v_mfma_f32_32x32x16_f16, the encoder
+// and its attention on v_mfma_f32_16x16x32_f16, which draws less power per flop where the chip's power sets its clock; the
 // residual stream, normalisation, softmax and GELU are fp32.
 #include "common.hpp"
 #include "context.hpp"
@@ -48,7 +47,7 @@ __global__ __launch_bounds__(1024) void absmax_kernel(const float* __restrict__ 
 // rows 0 and N+1 of h1 are zero (the padding of the second convolution).
 // grid (ceil(N / tok), layers), 256 threads; thread owns channels tid, tid+256, ...  tok <= 64 tokens per workgroup: a
 // workgroup's tokens are a serial chain, so short inputs take fewer of them (512 tokens of one layer: 23.6 us with 64
-// tokens per workgroup, eight workgroups on 256 CUs).
+// tokens per workgroup, eight workgroups on 256 CUs, 8.3 with 16 and 5.0 with 4; from 8192 tokens on 16 give every CU two).
 // ------------------------------------------------------------------------------------------
 constexpr int kStemTok = 64;
 constexpr int kMaxHs = 16;
@@ -95,21 +94,20 @@ __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict
 // fp16 GEMM  C[M, Nn] = A[M, K] * W[Nn, K]^T  (+ epilogue), fp32 accumulation.
 // A rows start lda elements apart (lda < K gives the overlapping rows of the second convolution).
 //
-// Persistent kernel, one 512-thread workgroup per CU.  Block tile BM (rows of A) x BN (rows of W), 256 x 256 or
-// 128 x 512, K step 64 (full 128-byte lines per row), 8 waves, each 64 x 128 = 2 x 4 MFMA tiles.  A tile
-// of this size needs 1 byte from L2 per 100 to 128 flop; smaller tiles are bound by the L2 -> CU path, not by
-// the matrix pipe.  The 128 x 512 shape spans a whole row of the encoder's width, so its epilogue can normalise
-// the row (residual add + LayerNorm) before anything goes to memory.
+// The stem's second convolution and the stage-3 projection.  Persistent kernel, one 512-thread workgroup per CU.  Block tile
+// BM (rows of A) x BN (rows of W) = 256 x 256, K step 64 (full 128-byte lines per row), 8 waves, each 64 x 128 = 2 x 4 MFMA
+// tiles.  A tile of this size needs 1 byte from L2 per 128 flop; smaller tiles are bound by the L2 -> CU path, not by
+// the matrix pipe.
 //
 // The A rows go on the MFMA M axis and the W rows on the N axis, so a lane owns output COLUMNS.  The
 // W rows of a wave's 128-column block are staged in the order n = 4*l + jn (l = lane & 31, jn = MFMA
 // tile), so a lane holds four adjacent columns in its four tiles and every store instruction writes
-// whole 256-byte (fp16) or 512-byte (fp32) row segments, 8 or 16 bytes per lane.  Output (and residual)
+// whole 512-byte row segments, 16 bytes per lane.  Output
 // buffers have their row count padded to a multiple of 256, so the epilogue has no row predicate; rows
 // at and past M are written with values that nobody reads (the stem's epilogue, which writes a token's row into
 // the windows that hold it, skips them instead).
 //
-// The K steps of all tiles of a workgroup form one stream: two LDS stages (64 or 80 KB each) and ONE barrier
+// The K steps of all tiles of a workgroup form one stream: two LDS stages (64 KB each) and ONE barrier
 // per step.  A step is four phases of 8 MFMAs; the fragments of phase kk+1 are read from LDS between
 // the MFMAs of phase kk (phase 3 reads phase 0 of the next step, behind the barrier), step s+1 goes
 // from registers to LDS during phase 2 and each register is refilled with its part of step s+2 right
