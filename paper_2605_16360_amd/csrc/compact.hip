@@ -217,9 +217,11 @@ hipError_t launch_compact_inplace(void* k, void* v, const int32_t* idx, int64_t 
                                   const int32_t* counts, int heads, hipStream_t stream) {
   if (rows <= 0 || K <= 0) return hipSuccess;
   const int cpr = (int)(row_bytes / 16);
-  // 128-byte parts of a token where it divides into them, and 256-byte ones where the rows alone give most CUs a workgroup (D = 128, in
-  // place: 512 rows of 12 345 tokens, half kept, 697 and 680 us; 112 rows of 5000, 86 and 85; 4 rows of 20 000, 67 and 89)
-  const int part = rows >= 112 && cpr % 16 == 0 ? 16 : 8;
+  // 128-byte parts of a token where it divides into them, and 256-byte ones where K and V of the rows alone give every CU two workgroups
+  // (D = 128, 128-byte and 256-byte parts, us: 512 rows of 12 345 tokens, half kept, 697 and 680; 256 of 2000, 0.8 kept, 78 and 76, of
+  // 5000 with shared budgets, 0.3 kept, 139 and 128; but 112 of 2000 49 and 51, of 21 718 with shared budgets, 0.145 kept, 144 and 150: a long
+  // row is then all that is left at the end; 4 rows of 20 000, 67 and 89)
+  const int part = rows >= 256 && cpr % 16 == 0 ? 16 : 8;
   const int slices = cpr % part == 0 ? cpr / part : 1, cps = cpr / slices;
   const int per = (kInplaceTokens * cps + 255) / 256;                 // 16-byte pieces per thread and chunk
   u32x4 *kp = (u32x4*)k, *vp = (u32x4*)v;
