@@ -325,11 +325,9 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
 
 // Columns of an MFMA tile.  16 x 16 x 32 instructions draw less than 32 x 32 x 16, but there are twice as many to issue: at d = 128, where
 // the products take as long as the exponentials, they gain once there is enough work for the chip's power to set its clock (28 x 12 heads,
-// 10 007 keys, both passes 18 170 -> 17 000 us), but not in launches of at most two turns of the 512 places (32 and 16 columns, 28 x 12
-// heads, 214 keys 37.4 / 39.8 us, 300 55.6 / 57.5, 600 129.5 / 130.8, 300 queries of 12 000 keys 842 / 847; 900 keys, three
-// turns, 244.7 / 243.9).  At d = 64, where the vector ALU sets the time, they do not (16 x 32 heads, 8192 keys 9030 and 9050;
-// causal, 4097 tokens, pass 1 alone 885 and 920).
-constexpr int64_t kLseWideBlocks = 1024;
+// 10 007 keys, both passes 18 170 -> 17 000 us; 32 and 16 columns at 900 keys 244.7 / 243.9, at 600 129.5 / 130.8, at 300 55.6 / 57.5),
+// but not in the short launches whose workgroups share a block's keys (214 keys 37.4 / 39.8 us).  At d = 64, where the vector ALU
+// sets the time, they do not (16 x 32 heads, 8192 keys 9030 and 9050; causal, 4097 tokens, pass 1 alone 885 and 920).
 constexpr int kLseCols = 2;  // column sub-tiles per wave; 128 * kLseCols queries per workgroup
 
 // Workgroups per query block: as many as fill the chip (three per CU at d = 64), if the query blocks alone give it less than half
@@ -371,8 +369,7 @@ hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint
     if (splits > 1) PKV_LSE(64, 32, 3, true);
     else PKV_LSE(64, 32, 3, false);
   } else {
-    if (splits > 1) PKV_LSE(128, 32, 2, true);  // (384 blocks or fewer)
-    else if ((int64_t)grid.x * H_q * L_s <= kLseWideBlocks) PKV_LSE(128, 32, 2, false);
+    if (splits > 1) PKV_LSE(128, 32, 2, true);
     else PKV_LSE(128, 16, 2, false);
   }
 #undef PKV_LSE
