@@ -589,10 +589,9 @@ def test_mapper_with_scores_beyond_the_half_range():
 
 @pytest.mark.parametrize("sink", [30.0, 300.0, 3.0e3])
 def test_mapper_with_logits_far_above_those_of_the_first_keys(sink):
-    """The window attention of the large tiles takes a query's reference from its first 64 keys and looks at no later logit; where one is
-    more than 2^16 times as likely, half overflows, and the workgroup starts over with the reference raised on the way.  Sinks behind
-    the first keys of both windows give logits in the thousands; a cut last tile, two layers of which one is ordinary.  Three seeds and
-    two ways of summing stay within 0.29 of the bound up to 3e3; at 3e4 logits reach the millions, where one rounding of an operand
+    """The window attention of the large tiles takes a query's reference from its first 64 keys and raises it where a later logit is
+    more than 2^8 times as likely.  Sinks behind the first keys of both windows give logits in the thousands; a cut last tile, two
+    layers of which one is ordinary.  Three seeds and two ways of summing stay within 0.29 of the bound up to 3e3; at 3e4 logits reach the millions, where one rounding of an operand
     to half decides between two keys, and both ways are the same 4.9e-3 off."""
     case = synth.scaled_case(synth.CASES["llama_8k"], name="late", L_s=2, H_kv=2, H_q=2, L_l=2, H_l=4, N=2200, N_q=1, chunk=1, n_planted=0)
     w = synth.make_mapper_weights(case.H_kv, case.H_l)
@@ -606,6 +605,35 @@ def test_mapper_with_logits_far_above_those_of_the_first_keys(sink):
     torch.cuda.synchronize()
     assert_close(y, oracle.mapper(X, w, case.L_l), f"map with late sinks of {sink:g}")
     pk.proxykv_destroy(ctx)
+
+
+def test_mapper_takes_no_longer_where_the_attention_is_sharp():
+    """Attention weights that go beyond what half holds relative to the first keys' (here in every workgroup: q and k five times as
+    wide) cost a rescaling each and not another pass over the keys, which made this 1.42 times as long."""
+    case = synth.scaled_case(synth.CASES["llama_8k"], name="sharp", L_s=8, H_kv=2, H_q=2, L_l=8, H_l=4, N=8192, N_q=1, chunk=1, n_planted=0)
+    X = (torch.rand(case.L_s, case.H_kv, case.N, generator=torch.Generator().manual_seed(9)) ** 8).cuda()
+    ctxs = []
+    for width in (1.0, 5.0):
+        w = synth.make_mapper_weights(case.H_kv, case.H_l)
+        for name in w:
+            if name.endswith("in_proj.weight"):
+                w[name] = torch.cat([w[name][:1024] * width, w[name][1024:]])
+        ctxs.append(_ctx(case, w))
+    best = [float("inf")] * 2
+    y = torch.empty(case.L_l, case.H_l, case.N, device="cuda")
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    for rep in range(6):
+        for i, ctx in enumerate(ctxs):
+            a.record()
+            for _ in range(4):
+                pk.proxykv_map(ctx, X, yhat=y)
+            b.record()
+            torch.cuda.synchronize()
+            if rep:
+                best[i] = min(best[i], a.elapsed_time(b))
+    for ctx in ctxs:
+        pk.proxykv_destroy(ctx)
+    assert best[1] < 1.2 * best[0], best
 
 
 def test_mapper_context_reuse_across_lengths():
