@@ -40,7 +40,7 @@ constexpr float kRebase = 1.8446744e19f;  // 2^64
 // undoes the tile and sums it again chain by chain with the check.
 constexpr float kTileRedo = 1.2676506e30f;  // 2^100
 
-// SPLIT: `splits` workgroups per query block, neg_lse holds (reference, sum) pairs [splits][L_s * H_q * N_q].
+// SPLIT: `splits` workgroups per query block; with more than one neg_lse holds (reference, sum) pairs [splits][L_s * H_q * N_q].
 // x [n_x] (n_x may be 0) is cleared for a pass 2 whose workgroups raise it.
 template <int D, int NCOL, int W, int MINB, bool SPLIT>
 __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __restrict__ q,
@@ -311,12 +311,18 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
       tot = tot * __builtin_amdgcn_exp2f(m - mm) + l2 * __builtin_amdgcn_exp2f(m2 - mm);
       m = mm;
     }
-    if constexpr (SPLIT) {
-      if (lane < W && qi[ct] < N_q)
-        reinterpret_cast<LsePart*>(neg_lse)[((size_t)split * gridDim.z * H_q + l * H_q + h) * N_q + qi[ct]] = LsePart{m, tot};
-    } else {
-      const float L2 = m + __builtin_amdgcn_logf(tot);
-      if (lane < W && qi[ct] < N_q) neg_lse[(size_t)(l * H_q + h) * N_q + qi[ct]] = -L2 * inv_c;
+    const size_t at = ((size_t)split * gridDim.z * H_q + l * H_q + h) * N_q + qi[ct];
+    const float whole = -(m + __builtin_amdgcn_logf(tot)) * inv_c;
+    if (lane < W && qi[ct] < N_q) {
+      if constexpr (SPLIT && D == 64) {
+        reinterpret_cast<LsePart*>(neg_lse)[at] = LsePart{m, tot};
+      } else if constexpr (SPLIT) {  // also launched with one split (as a branch: 214 keys of 28 x 12 heads 38.0 us, so 37.8)
+        const int words = splits > 1 ? 2 : 1;
+        neg_lse[at * words + words - 1] = tot;
+        neg_lse[at * words] = splits > 1 ? m : whole;
+      } else {
+        neg_lse[at] = whole;
+      }
     }
   }
 }
@@ -325,9 +331,13 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
 
 // Columns of an MFMA tile.  16 x 16 x 32 instructions draw less than 32 x 32 x 16, but there are twice as many to issue: at d = 128, where
 // the products take as long as the exponentials, they gain once there is enough work for the chip's power to set its clock (28 x 12 heads,
-// 10 007 keys, both passes 18 170 -> 17 000 us; 32 and 16 columns at 900 keys 244.7 / 243.9, at 600 129.5 / 130.8, at 300 55.6 / 57.5),
-// but not in the short launches whose workgroups share a block's keys (214 keys 37.4 / 39.8 us).  At d = 64, where the vector ALU
-// sets the time, they do not (16 x 32 heads, 8192 keys 9030 and 9050; causal, 4097 tokens, pass 1 alone 885 and 920).
+// 10 007 keys, both passes 18 170 -> 17 000 us), but not in short launches, up to query blocks times keys of 2^20 or with shared
+// blocks.  Both passes, 32 / 16 columns, us: 214 keys 37.4 / 39.8, 257 53.2 / 55.7, 300 54.8 / 57.1, 420 74.0 / 75.8, 600 128.3 / 130.3,
+// 300 queries of 1500 keys 129.2 / 131.0; beyond the line 900 240.7 / 242.5, 1024 268.8 / 263.7, 300 queries of 4000 296.2 / 296.6, 500
+// 368.7 / 361.8.  Causal, with the longest blocks first, they gain from 400 tokens on (56.3 / 55.5, 700 97.2 / 91.6; 300 44.1 / 46.7, in
+// the order of the blocks 51.2).  At d = 64, where the vector ALU sets the time, they do not (16 x 32 heads, 8192 keys 9030 and
+// 9050; causal, 4097 tokens, pass 1 alone 885 and 920).
+constexpr int64_t kLseWideWork = 1 << 20;
 constexpr int kLseCols = 2;  // column sub-tiles per wave; 128 * kLseCols queries per workgroup
 
 // Workgroups per query block: as many as fill the chip (three per CU at d = 64), if the query blocks alone give it less than half
@@ -369,7 +379,8 @@ hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint
     if (splits > 1) PKV_LSE(64, 32, 3, true);
     else PKV_LSE(64, 32, 3, false);
   } else {
-    if (splits > 1) PKV_LSE(128, 32, 2, true);
+    const bool wide = N > 0 && (int64_t)grid.x * H_q * L_s * N <= kLseWideWork;
+    if (splits > 1 || wide) PKV_LSE(128, 32, 2, true);
     else PKV_LSE(128, 16, 2, false);
   }
 #undef PKV_LSE

@@ -381,9 +381,20 @@ def test_score_few_and_many_query_blocks_agree(d, N, N_q, chunk):
 @pytest.mark.parametrize("N_q", [256, 257])
 @pytest.mark.parametrize("scale", [1.0, 30.0])
 def test_score_of_few_query_blocks_and_of_more(N_q, scale):
-    """47 layers of 8 heads of 128: 256 queries make 376 blocks of pass 1, whose keys workgroups share, with 32-column matrix tiles; 257 make
-    752, one workgroup each, with 16-column ones.  Also with nearly one-hot rows, where its reference is replaced many times."""
-    L, H_q, H_kv, d, N, chunk = 47, 8, 2, 128, 300, 200
+    """47 layers of 8 heads of 128: 256 queries make 376 blocks of pass 1, whose keys workgroups share; 257 make 752, one workgroup each.  Also
+    with nearly one-hot rows, where its reference is replaced many times."""
+    _score_47_layers(N_q, 300, scale)
+
+
+@pytest.mark.parametrize("N", [1394, 1395])
+@pytest.mark.parametrize("scale", [1.0, 30.0])
+def test_score_where_the_wide_tiles_end(N, scale):
+    """752 blocks, one workgroup each: up to 2^20 blocks times keys with 32-column matrix tiles, beyond it with 16-column ones."""
+    _score_47_layers(257, N, scale)
+
+
+def _score_47_layers(N_q, N, scale):
+    L, H_q, H_kv, d, chunk = 47, 8, 2, 128, 200
     g = torch.Generator().manual_seed(N_q)
     q = (scale * torch.randn(L, H_q, N_q, d, generator=g)).bfloat16()
     kc, kr = (torch.randn(L, H_kv, n, d, generator=g).bfloat16() for n in (N, N_q))

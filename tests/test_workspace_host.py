@@ -233,3 +233,17 @@ def test_launches_of_many_rows_stay_within_the_runtime():
     assert out["mask"][0] == 0 and out["mask"][1][0][1:] == [5000000, 1, 1, 256]
     assert out["pooled"][0] == 0 and out["pooled"][1][0][1] * 64 <= 0xffffffff
     assert out["few"] == [0, 15]
+
+
+def test_short_launches_of_pass_1_take_the_wide_tiles():
+    """28 x 12 heads of 128: pass 1's 16-column tiles gain in long launches only (300 keys 54.8 us with 32 columns, 57.1 with 16)."""
+    out = run("""
+        ctx = context(QWEN32B)
+        out = {}
+        for n, n_q in ((300, 300), (768, 768), (1500, 300), (900, 900), (4000, 500), (10007, 10007)):
+            launches()
+            assert lib.proxykv_score(ctx, P, P, P, 0, n, n_q, 4096, P, None) == 0
+            out[f"{n} {n_q}"] = [l[0] for l in launches("score_lse_kernel")]
+    """)
+    for case, wide in (("300 300", True), ("768 768", True), ("1500 300", True), ("900 900", False), ("4000 500", False), ("10007 10007", False)):
+        assert len(out[case]) == 1 and ("ILi128ELi2ELi32E" in out[case][0]) == wide, (case, out[case])
