@@ -139,7 +139,6 @@ constexpr int64_t kMapSmallRows = 2560;
 struct MapPlan {
   int64_t N, n_win, T;  // tokens, windows and window rows of a layer
   int64_t Tp, Np;       // window rows and tokens of a layer, padded to the GEMM's 256-row tile
-  int64_t vt_ld;        // row length of the transposed v
   int n_batches, batch, lanes;  // batch: layers of the largest batch
   bool small;           // few rows: the small-tile kernels
 };
@@ -151,7 +150,6 @@ inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers,
   window_plan(N, c.win, c.stride, &p.n_win, &p.T);
   p.Tp = (p.T + 255) / 256 * 256;
   p.Np = (N + 255) / 256 * 256;
-  p.vt_ld = p.n_win > 1 ? c.win : p.Tp;
   const int64_t few = (distinct_layers + kMaxBatch - 1) / kMaxBatch;  // batches, if only their number of layers were limited
   p.small = (distinct_layers + few - 1) / few * ((p.T + 63) / 64 * 64) <= kMapSmallRows && c.n_enc_layers > 0;
   int64_t cap = kMapBatchRows / p.Tp;
@@ -171,7 +169,7 @@ inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers,
 // serves the small tiles of a shorter one, so their hidden rows count in every plan.  (12 KB of buffers per row, 7 KB with this one in their place.)
 inline size_t map_work_bytes(const proxykv_config& c, const MapPlan& p) {
   const size_t row = (size_t)c.d_time * 2, Tp = (size_t)p.Tp;
-  const size_t attn = 3 * Tp * row + (size_t)p.n_win * (size_t)p.vt_ld * row, hid = Tp * (size_t)c.d_ffn * 2;
+  const size_t attn = 4 * Tp * row, hid = Tp * (size_t)c.d_ffn * 2;
   const size_t h1 = ((size_t)(p.N + 2) * c.c_mid * 2 + 255) / 256 * 256, zg = (size_t)p.Np * row;
   const size_t a = attn > hid ? attn : hid, b = h1 > zg ? h1 : zg;
   return a > b ? a : b;

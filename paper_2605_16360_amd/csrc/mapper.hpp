@@ -86,7 +86,7 @@ struct LanePointers {
   uint16_t* h1;     // fp16 [(N+2), c_mid]  stem conv1 output with one zero row at each end
   float* x;
   uint16_t *xb, *qk;  // qk: fp16 [Tp, 2*d_time]  q and k of the current layer
-  uint16_t* vt;     // fp16 [n_win, heads, 64, vt_ld]  v transposed per window and head
+  uint16_t* vt;     // fp16 [heads, 64, Tp]  v transposed per head (small tiles)
   uint16_t* ao;     // fp16 [Tp, d_time]    attention output of the small tiles; of the large ones, whose q, k and v lie in blocks at qk, in xb
   uint16_t* hid;    // fp16 [Tp, d_ffn]
   uint16_t* zg;     // fp16 [Np, d_time]    overlap-averaged encoder output
@@ -97,7 +97,7 @@ inline LanePointers lane_pointers(const proxykv_config& c, const MapPlan& p, con
   uint16_t* work = (uint16_t*)m.work.ptr;
   const size_t n = (size_t)p.batch, d = (size_t)c.d_time;
   uint16_t* vt = work + n * p.Tp * 2 * d;
-  uint16_t* ao = vt + n * p.n_win * p.vt_ld * d;
+  uint16_t* ao = vt + n * p.Tp * d;
   return {work, (float*)m.x.ptr, (uint16_t*)m.xb.ptr, work, vt, ao, work, work, (float*)m.s3.ptr, (float*)m.pre.ptr, (uint32_t*)m.range.ptr};
 }
 

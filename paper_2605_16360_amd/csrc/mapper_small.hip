@@ -2,11 +2,12 @@
 // 512 rows is 4 to 16 workgroups on 256 CUs, each a chain of up to 32 K steps: latency, not throughput, is what such an
 // input costs.  These kernels cut the same products into small tiles, so that every CU has one, and shorten each chain:
 //   small_wide_kernel  K = d_time (512): 64 x 64 tiles whose A and W rows are loaded into LDS whole, one round trip to memory.
-//                      Its prologue can normalise the rows (LayerNorm) as it reads them, and average overlapping windows,
-//                      so that neither needs a launch of its own: QKV projection, FFN-1, stage-3 K/V projection.
+//                      Its prologue can normalise the rows (LayerNorm) as it reads them, so that this needs no launch of
+//                      its own: QKV projection, FFN-1, stage-3 K/V projection.
 //   small_deep_kernel  32 x 32 tiles, the four waves of a workgroup share the K axis and meet in LDS: second stem
 //                      convolution, out-projection, FFN-2.  It leaves the pre-norm sum to the next kernel's prologue.
-//   small_attention_kernel  32 queries of one (window, head) per workgroup, its four waves share the keys.
+//   small_attention_kernel  32 queries of one (layer, head) per workgroup, its four waves share the keys.
+// A layer of more than one window has more rows than they take, so a layer's tokens, window rows and window are the same here.
 // Results are rounded where the kernels of mapper.hip round; sums are fp32 in another order.
 // Measured, one layer of 512 rows: 867 -> 231 us, and 226 with row statistics in place of the normalised rows and four tokens per workgroup
 // of the first convolution; 2560 rows (kMapSmallRows) are their end.
@@ -22,6 +23,8 @@ typedef const __attribute__((address_space(1))) void* gptr_t;
 typedef __attribute__((address_space(3))) void* lptr_t;
 
 constexpr int kVmcnt0 = 0x0F70;  // s_waitcnt vmcnt(0)
+
+static_assert(kMapSmallRows < kWin + kStride + 1, "a layer of two windows is not for these kernels");
 
 // Tile of a block.  Blocks are dealt round-robin to the 8 XCDs; each XCD takes its own column tiles for all row tiles, so a
 // weight row is fetched into one L2 only (the weights outweigh the activations at these sizes).
@@ -40,8 +43,7 @@ __device__ __forceinline__ void small_tile(int n_tiles, int& nt, int& mt) {
 // Where the A rows of small_wide_kernel come from.
 enum Prologue {
   kProHalf,    // fp16 rows as they are
-  kProLn,      // LayerNorm of fp32 rows; their means and scales also go to `stats`, for the residual of the next sum
-  kProLnAvg    // token t: the mean, over the one or two windows that hold it, of the LayerNorm of its rows
+  kProLn       // LayerNorm of fp32 rows; their means and scales also go to `stats`, for the residual of the next sum
 };
 enum WideEpilogue { kWideQkv, kWideRelu, kWideStage3 };
 
@@ -53,17 +55,16 @@ struct RowStats {
 
 struct WideArgs {
   const uint16_t* a_half;
-  const float* pre;           // kProLn, kProLnAvg: rows to normalise
+  const float* pre;           // kProLn: rows to normalise
   const float *g, *b;         // LayerNorm scale and shift
   RowStats* stats;
   const uint16_t* w;          // [n_tiles * 64, 512]
   const float* bias;
   int n_tiles, tiles_per_layer;  // column tiles; row tiles of a layer
   int rows, stride;           // valid rows of a layer and rows between layers (A and outputs)
-  int pre_stride, n_win;      // kProLnAvg: rows between layers of `pre`, windows of a layer;  kWideQkv: n_win
   uint16_t *out_h, *out_v;
   float* out_f32;
-  int ldc, vt_ld;
+  int ldc;
   const float *queries, *out_w;  // kWideStage3
   int n_slot, n_head;
 };
@@ -140,51 +141,28 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void small_wide_kernel(WideArgs
     // The fp32 rows are asked for first and the W rows behind them (through registers: loads return in order), so that the
     // rows are normalised while the weights are on their way.
     const int j = lane & 15;
-    constexpr int kIts = kWideRows / 4, kBatch = PRO == kProLn ? kIts : 1;  // rows per lane group, and in flight
+    constexpr int kIts = kWideRows / 4;  // rows per lane group
     u32x4 wr[kWideRows];
-    f32x8 g[4], b[4];
+    f32x8 g[4], b[4], v[kIts][4];
 #pragma unroll
-    for (int it0 = 0; it0 < kIts; it0 += kBatch) {
-      f32x8 v[kBatch][4], v2[PRO == kProLnAvg ? kBatch : 1][4];
-      int two[kBatch];
+    for (int it = 0; it < kIts; ++it) {
+      const int row = wave * kWideRows + it * 4 + (lane >> 4);
+      const int m = r0 + row < a.rows ? r0 + row : a.rows - 1;
+      load_row16(a.pre + ((size_t)layer * a.stride + m) * kDT, j, v[it]);
+    }
+    load_row16(a.g, j, g);
+    load_row16(a.b, j, b);
 #pragma unroll
-      for (int it = 0; it < kBatch; ++it) {
-        const int row = wave * kWideRows + (it0 + it) * 4 + (lane >> 4);
-        const int m = r0 + row < a.rows ? r0 + row : a.rows - 1;
-        if constexpr (PRO == kProLn) {
-          load_row16(a.pre + ((size_t)layer * a.stride + m) * kDT, j, v[it]);
-        } else {
-          // token m sits at place m - 1024 k of window k = min(m / 1024, n_win - 1) and, if that window is not the first
-          // and the token lies in its first half, at place + 1024 of the window before
-          const int kq = m / kStride, k1 = kq < a.n_win ? kq : a.n_win - 1;
-          const float* src = a.pre + ((size_t)layer * a.pre_stride + (size_t)k1 * kWin + (m - k1 * kStride)) * kDT;
-          two[it] = k1 >= 1 && kq == k1;
-          load_row16(src, j, v[it]);
-          load_row16(two[it] ? src - (size_t)(kWin - kStride) * kDT : src, j, v2[it]);
-        }
-      }
-      if (it0 == 0) {
-        load_row16(a.g, j, g);
-        load_row16(a.b, j, b);
+    for (int i = 0; i < kWideRows; ++i) wr[i] = *reinterpret_cast<const u32x4*>(wsrc + i * kDT + (lane ^ ((wave * kWideRows + i) & 15)) * 8);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int i = 0; i < kWideRows; ++i) wr[i] = *reinterpret_cast<const u32x4*>(wsrc + i * kDT + (lane ^ ((wave * kWideRows + i) & 15)) * 8);
-        __builtin_amdgcn_sched_barrier(0);
-      }
+    for (int it = 0; it < kIts; ++it) {
+      const int row = wave * kWideRows + it * 4 + (lane >> 4);
+      const RowStats st = layernorm_row16(v[it], g, b);
+      if (EPI != kWideStage3 && nt == 0 && j == 0 && r0 + row < a.rows) a.stats[(size_t)layer * a.stride + r0 + row] = st;
 #pragma unroll
-      for (int it = 0; it < kBatch; ++it) {
-        const int row = wave * kWideRows + (it0 + it) * 4 + (lane >> 4);
-        const RowStats st = layernorm_row16(v[it], g, b);
-        if constexpr (PRO == kProLnAvg) {
-          layernorm_row16(v2[it], g, b);
-#pragma unroll
-          for (int c = 0; c < 4; ++c) v[it][c] = two[it] ? (v2[it][c] + v[it][c]) * 0.5f : v[it][c];
-        } else {
-          if (nt == 0 && j == 0 && r0 + row < a.rows) a.stats[(size_t)layer * a.stride + r0 + row] = st;
-        }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-          lds[row * 64 + ((c * 16 + j) ^ (row & 15))] = __builtin_bit_cast(u32x4, __builtin_convertvector(v[it][c], f16x8));
-      }
+      for (int c = 0; c < 4; ++c)
+        lds[row * 64 + ((c * 16 + j) ^ (row & 15))] = __builtin_bit_cast(u32x4, __builtin_convertvector(v[it][c], f16x8));
     }
 #pragma unroll
     for (int i = 0; i < kWideRows; ++i) lw[(wave * kWideRows + i) * 64 + lane] = wr[i];
@@ -230,8 +208,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void small_wide_kernel(WideArgs
       if (ks > 0) return;
       // v transposed and key-permuted as the attention reads it: registers 8u .. 8u+7 are eight consecutive positions
       const int rg = r0 + wm * 32, vc = n - 2 * kDT;
-      uint16_t* vb = a.out_v + ((size_t)((layer * a.n_win + rg / kWin) * kHeads + (vc >> 6)) * 64 + (vc & 63)) * a.vt_ld +
-                     (rg % kWin) + half * 8;
+      uint16_t* vb = a.out_v + ((size_t)(layer * kHeads + (vc >> 6)) * 64 + (vc & 63)) * a.stride + rg + half * 8;
 #pragma unroll
       for (int u = 0; u < 2; ++u) {
         f32x8 t;
@@ -297,7 +274,7 @@ __global__ __launch_bounds__(64 * kWideWaves, 1) void small_wide_kernel(WideArgs
 // ------------------------------------------------------------------------------------------
 enum DeepEpilogue {
   kDeepRes,       // out_f32 = res + (sum + bias): the pre-norm row
-  kDeepGeluPeWin  // the second stem convolution: GELU(sum * scale * 2^s + shift) + position, into every window that holds the token
+  kDeepGeluPe     // the second stem convolution: GELU(sum * scale * 2^s + shift) + position
 };
 struct DeepArgs {
   const uint16_t* a;
@@ -313,7 +290,6 @@ struct DeepArgs {
   float* out_f32;
   uint16_t* out_h;
   const float* pe;
-  int n_win;
   const uint32_t* range;
   float cw, cs;
 };
@@ -381,8 +357,8 @@ __global__ __launch_bounds__(256, 2) void small_deep_kernel(DeepArgs a) {
   for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(lds + w * 512) + row * 36 + c4);
   if (t >= a.rows) return;
   const f32x4 p0 = *reinterpret_cast<const f32x4*>(a.p0 + n);
+  const size_t o = ((size_t)layer * a.out_stride + t) * kDT + n;
   if constexpr (EPI == kDeepRes) {
-    const size_t o = ((size_t)layer * a.out_stride + t) * kDT + n;
     f32x4 r = *reinterpret_cast<const f32x4*>(a.res + o);
     if (a.stats != nullptr) {
       const RowStats st = a.stats[(size_t)layer * a.out_stride + t];
@@ -394,38 +370,26 @@ __global__ __launch_bounds__(256, 2) void small_deep_kernel(DeepArgs a) {
     const float up = exp2_int(stem_exponent(a.range + layer * kRangeWords, a.cw, a.cs));
 #pragma unroll
     for (int e = 0; e < 4; ++e) v[e] = gelu_erf(__builtin_fmaf(v[e], p0[e] * up, p1[e]));
-    const int kq = t / kStride, k1 = kq < a.n_win ? kq : a.n_win - 1, p1w = t - k1 * kStride;
-    const size_t o1 = ((size_t)layer * a.out_stride + (size_t)k1 * kWin + p1w) * kDT + n;
-    const f32x4 y1 = v + *reinterpret_cast<const f32x4*>(a.pe + (size_t)p1w * kDT + n);
-    *reinterpret_cast<f32x4*>(a.out_f32 + o1) = y1;
-    *reinterpret_cast<f16x4*>(a.out_h + o1) = __builtin_convertvector(y1, f16x4);
-    if (k1 >= 1 && kq == k1) {
-      const size_t o0 = o1 - (size_t)(kWin - kStride) * kDT;
-      const f32x4 y0 = v + *reinterpret_cast<const f32x4*>(a.pe + (size_t)(p1w + kStride) * kDT + n);
-      *reinterpret_cast<f32x4*>(a.out_f32 + o0) = y0;
-      *reinterpret_cast<f16x4*>(a.out_h + o0) = __builtin_convertvector(y0, f16x4);
-    }
+    const f32x4 y = v + *reinterpret_cast<const f32x4*>(a.pe + (size_t)t * kDT + n);
+    *reinterpret_cast<f32x4*>(a.out_f32 + o) = y;
+    *reinterpret_cast<f16x4*>(a.out_h + o) = __builtin_convertvector(y, f16x4);
   }
 }
 
 // ------------------------------------------------------------------------------------------
-// Window attention for few rows: a workgroup takes 32 queries of one (window, head); wave w takes the 64-key tiles w, w + 4,
+// Window attention for few rows: a workgroup takes 32 queries of one (layer, head); wave w takes the 64-key tiles w, w + 4,
 // ... through LDS of its own, each with an online softmax of its own, and the four meet in LDS at the end.  The products,
 // the lazily raised reference and the layouts are those of window_attention_kernel (mapper.hip).
-// grid layers * n_win * 8 heads * n_qb, n_qb = blocks of 32 queries per window; block b: head b % 8 (one XCD per head).
+// grid layers * 8 heads * n_qb, n_qb = blocks of 32 queries per layer; block b: head b % 8 (one XCD per head).
 // ------------------------------------------------------------------------------------------
 __global__ __launch_bounds__(256, 2) void small_attention_kernel(const uint16_t* __restrict__ qk, const uint16_t* __restrict__ vt,
-                                                                  uint16_t* __restrict__ ao, int T, int Tp, int n_win, int n_qb,
-                                                                  int vt_ld) {
+                                                                  uint16_t* __restrict__ ao, int len, int Tp, int n_qb) {
   __shared__ u32x4 lds[4 * 1024];  // per wave: K tile (64 keys x 8 chunks), V^T tile (64 d rows x 8 chunks)
   __shared__ float ml[2][4][32];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
   const int hd = blockIdx.x % kHeads, j8 = blockIdx.x / kHeads;
-  const int wg = j8 / n_qb, i0 = (j8 % n_qb) * 32;
-  const int layer = wg / n_win, wk = wg % n_win;
-  const int64_t base = (int64_t)layer * Tp + (int64_t)wk * kWin;
-  const int len = (wk < n_win - 1) ? kWin : T - wk * kWin;
-  if (i0 >= len) return;
+  const int layer = j8 / n_qb, i0 = (j8 % n_qb) * 32;
+  const int64_t base = (int64_t)layer * Tp;
   constexpr float c = 1.4426950408889634f * 0.125f;  // log2(e) / sqrt(64)
 
   f16x8 bq[4];
@@ -436,7 +400,7 @@ __global__ __launch_bounds__(256, 2) void small_attention_kernel(const uint16_t*
       bq[kk] = as_f16x8(*reinterpret_cast<const u32x4*>(qk + (size_t)(base + row) * (2 * kDT) + hd * 64 + kk * 16 + half * 8));
   }
   const uint16_t* kbase = qk + (size_t)base * (2 * kDT) + kDT + hd * 64;
-  const uint16_t* vbase = vt + (size_t)(wg * kHeads + hd) * 64 * vt_ld;
+  const uint16_t* vbase = vt + (size_t)(layer * kHeads + hd) * 64 * Tp;
   const int n_tiles = (len + 63) / 64;
   u32x4* lk = lds + wave * 1024;
   u32x4* lv = lk + 512;
@@ -449,7 +413,7 @@ __global__ __launch_bounds__(256, 2) void small_attention_kernel(const uint16_t*
       int j = t * 64 + row;
       j = j < len ? j : len - 1;
       rk[i] = *reinterpret_cast<const u32x4*>(kbase + (size_t)j * (2 * kDT) + sch * 8);
-      rv[i] = *reinterpret_cast<const u32x4*>(vbase + (size_t)row * vt_ld + t * 64 + sch * 8);
+      rv[i] = *reinterpret_cast<const u32x4*>(vbase + (size_t)row * Tp + t * 64 + sch * 8);
     }
   };
   f32x16 o[2];
@@ -561,7 +525,7 @@ hipError_t launch_deep(const DeepArgs& a, int layers, hipStream_t stream) {
 hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const MapPlan& p, int n_layers, int64_t N64, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const MapperWeights& w = ctx->w;
-  const int N = (int)N64, T = (int)p.T, Tp = (int)p.Tp, Np = (int)p.Np, n_win = (int)p.n_win, vt_ld = (int)p.vt_ld;
+  const int N = (int)N64, Np = (int)p.Np;  // a layer's rows, and padded
   const LanePointers m = lane_pointers(c, p, ws);
   float *x = m.x, *pre = m.pre;
   RowStats* stats = reinterpret_cast<RowStats*>(x);  // x is read for the last time before the first of them is written
@@ -575,32 +539,30 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   d.K = 3 * c.c_mid;
   d.rows = N;
   d.tiles_per_layer = (N + 31) / 32;
-  d.out_stride = Tp;
+  d.out_stride = Np;
   d.p0 = w.bn2_scale;
   d.p1 = w.bn2_shift;
   d.out_f32 = x;
   d.out_h = xb;
   d.pe = w.pe;
-  d.n_win = n_win;
   d.range = m.range;
   d.cw = w.stem_cw;
   d.cs = w.stem_cs;
-  PKV_TRY(launch_deep<kDeepGeluPeWin>(d, n_layers, stream));
+  PKV_TRY(launch_deep<kDeepGeluPe>(d, n_layers, stream));
 
   // x: the encoder's first rows, the residual of the first sum; pre: the sum that the next kernel normalises, and the one behind it once
   // more for its residual
-  const int n_qb = ((T < kWin ? T : kWin) + 31) / 32;
+  const int n_qb = (N + 31) / 32;
   WideArgs a = {};
-  a.tiles_per_layer = (T + 63) / 64;
-  a.rows = T;
-  a.stride = Tp;
-  a.n_win = n_win;
+  a.tiles_per_layer = (N + 63) / 64;
+  a.rows = N;
+  a.stride = Np;
   a.pre = pre;
   a.stats = stats;
   d = DeepArgs{};
-  d.rows = T;
-  d.tiles_per_layer = (T + 31) / 32;
-  d.out_stride = Tp;
+  d.rows = N;
+  d.tiles_per_layer = (N + 31) / 32;
+  d.out_stride = Np;
   d.res = x;
   d.out_f32 = pre;
   for (int li = 0; li < c.n_enc_layers; ++li) {
@@ -612,7 +574,6 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
     q.out_h = qk;
     q.out_v = vt;
     q.ldc = 2 * kDT;
-    q.vt_ld = vt_ld;
     if (li == 0) {
       q.a_half = xb;
       PKV_TRY((launch_wide<kProHalf, kWideQkv>(q, n_layers, stream)));
@@ -621,7 +582,7 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
       q.b = w.enc[li - 1].ln2_b;
       PKV_TRY((launch_wide<kProLn, kWideQkv>(q, n_layers, stream)));
     }
-    small_attention_kernel<<<(unsigned)(n_layers * n_win * kHeads * n_qb), 256, 0, stream>>>(qk, vt, ao, T, Tp, n_win, n_qb, vt_ld);
+    small_attention_kernel<<<(unsigned)(n_layers * kHeads * n_qb), 256, 0, stream>>>(qk, vt, ao, N, Np, n_qb);
     PKV_TRY(hipGetLastError());
     if (li > 0) {
       d.stats = stats;
@@ -630,7 +591,7 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
     }
     d.a = ao;
     d.lda = kDT;
-    d.a_layer = (int64_t)Tp * kDT;
+    d.a_layer = (int64_t)Np * kDT;
     d.w = e.out_w;
     d.K = kDT;
     d.p0 = e.out_b;
@@ -650,7 +611,7 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
     d.b = e.ln1_b;
     d.a = hid;
     d.lda = c.d_ffn;
-    d.a_layer = (int64_t)Tp * c.d_ffn;
+    d.a_layer = (int64_t)Np * c.d_ffn;
     d.w = e.ffn2_w;
     d.K = c.d_ffn;
     d.p0 = e.ffn2_b;
@@ -660,10 +621,6 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   h.w = w.kv_w;
   h.bias = w.kv_b;
   h.n_tiles = 2 * c.H_kv;
-  h.tiles_per_layer = (N + 63) / 64;
-  h.rows = N;
-  h.stride = Np;
-  h.pre_stride = Tp;
   h.g = w.enc[c.n_enc_layers - 1].ln2_g;
   h.b = w.enc[c.n_enc_layers - 1].ln2_b;
   h.out_f32 = m.s3;
@@ -672,7 +629,7 @@ hipError_t mapper_small_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   h.out_w = w.out_w;
   h.n_slot = c.H_kv;
   h.n_head = c.H_l;
-  return launch_wide<kProLnAvg, kWideStage3>(h, n_layers, stream);
+  return launch_wide<kProLn, kWideStage3>(h, n_layers, stream);
 }
 
 }  // namespace pkv

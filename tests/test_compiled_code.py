@@ -141,3 +141,11 @@ def test_encoder_block_keeps_its_registers():
     for name, body in blocks:
         for loop in re.findall(r"^(\.LBB\w+):(.*?)s_cbranch_scc\d \1$", body, re.M | re.S):
             assert "v_mfma" not in loop[1] or "scratch_" not in loop[1], name
+
+
+def test_small_mapper_loads_a_row_once():
+    """The products that normalise their 64 rows first load each once, whatever follows them: with a scale, a shift and the weights a lane
+    asks for 40 times 16 bytes.  (A layer with a second window, whose rows would be averaged, has too many rows for these kernels.)"""
+    wide = [(name, body) for name, body in kernels("mapper_small.hip") if "small_wide_kernel" in name]
+    loads = {name: len(re.findall(r"^\s+global_load_dwordx4", body[:body.index("v_mfma")], re.M)) for name, body in wide}
+    assert sorted(loads.values()) == [0, 40, 40, 40], loads  # (the first product's operands go to LDS directly)

@@ -518,9 +518,9 @@ def test_mapper_batches_of_layers(L_s, L_l, N):
 
 
 @pytest.mark.parametrize("L,N", [(1, 2049), (1, 2500), (1, 3072), (1, 3073), (2, 2048), (2, 2049), (3, 1365), (3, 1366)])
-def test_mapper_on_both_sides_of_the_small_tiles(L, N):
-    """Around the sizes where the small-tile kernels end: one layer of one, two and three windows (overlap averaging, a token's row stored
-    into both windows, v split at the window), two and three layers of one window."""
+def test_mapper_of_few_rows_in_large_tiles(L, N):
+    """Just more rows than the small-tile kernels take: one layer of two and three windows (overlap averaging, a token's row stored
+    into both windows), two and three layers of one window and of two."""
     case = synth.scaled_case(synth.CASES["llama_8k"], name="small", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=N, N_q=1, chunk=1,
                              n_planted=0)
     w = synth.make_mapper_weights(case.H_kv, case.H_l)
