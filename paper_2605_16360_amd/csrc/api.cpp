@@ -70,7 +70,8 @@ void free_lanes(proxykv_ctx* ctx) {
   ctx->map_len = 0;
 }
 
-int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) {
+// `need`: the mapper's workspace is given up where that makes room
+int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream, bool need = true) {
   if (bytes <= b.bytes) return PROXYKV_OK;
   if (b.ptr) {
     // earlier work on the stream may still read the old buffer
@@ -81,7 +82,7 @@ int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream) 
   }
   void* p = nullptr;
   hipError_t e = hipMalloc(&p, bytes);
-  if (e == hipErrorOutOfMemory && ctx->map_len > 0) {
+  if (need && e == hipErrorOutOfMemory && ctx->map_len > 0) {
     // the mapper makes do with less: it takes what is left when it runs next
     (void)hipGetLastError();
     PKV_HIP(ctx, hipStreamSynchronize(stream));
@@ -221,13 +222,15 @@ int query_splits(const proxykv_ctx* ctx, bool sum, bool causal, int64_t N, int64
   const int s = pkv::score_query_splits(sum, causal, c.L_s, c.H_q, c.H_kv, c.d, N, N_q);
   return sum && ctx->x_parts.bytes < (size_t)s * c.L_s * c.H_kv * (size_t)N * 4 ? 1 : s;
 }
-// where the wide histograms do not fit, the narrow ones
+// The masks are done without where they do not fit beside what is there (112 rows of 170 000 scores 67 -> 78 us), and where the wide
+// histograms do not fit, the narrow ones take their place.
 int reserve_topk(proxykv_ctx* ctx, int64_t rows, int64_t N, hipStream_t stream) {
   const size_t least = pkv::topk_scratch_bytes_least(rows, N);
   if (ctx->topk_short && ctx->topk_ws.bytes >= least) return PROXYKV_OK;
-  int rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes(rows, N), stream);
+  int rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes(rows, N), stream, false);
   ctx->topk_short = rc == PROXYKV_ENOMEM;
-  if (ctx->topk_short) rc = ensure(ctx, ctx->topk_ws, least, stream);
+  if (rc == PROXYKV_ENOMEM) rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes_no_masks(rows, N), stream);
+  if (rc == PROXYKV_ENOMEM) rc = ensure(ctx, ctx->topk_ws, least, stream);
   return rc;
 }
 int reserve_prune(proxykv_ctx* ctx, int64_t N, hipStream_t stream) {

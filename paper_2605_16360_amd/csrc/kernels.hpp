@@ -35,9 +35,10 @@ hipError_t launch_score_colsum(const uint16_t* q, const uint16_t* k_ctx, const f
                                hipStream_t stream);
 // Per-row Top-K.  Rows longer than 36 864 scores are split over several workgroups and need `scratch` (device memory, any
 // contents, 256-byte aligned; rows <= 65535 then) of topk_scratch_bytes(rows, N) bytes, which serve all calls of no more and no
-// longer rows, or, for one more pass over the scores, of topk_scratch_bytes_least(rows, N).
+// longer rows, or, where the scores are read once more each, of topk_scratch_bytes_no_masks(rows, N) or topk_scratch_bytes_least(rows, N).
 constexpr int64_t kTopkSingleMax = 36864;  // longest row one workgroup selects from
 size_t topk_scratch_bytes(int64_t rows, int64_t N);
+size_t topk_scratch_bytes_no_masks(int64_t rows, int64_t N);
 size_t topk_scratch_bytes_least(int64_t rows, int64_t N);
 hipError_t launch_topk(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
                        size_t scratch_bytes, hipStream_t stream);

@@ -632,10 +632,17 @@ static size_t topk_scratch(int64_t rows, int64_t N) {
 }
 constexpr size_t kMaskBytes = kTopkThreads * 16;  // of a part: four words per thread
 // (the parts of up to `rows` rows of up to N scores: 512, or as few as each row can have; the masks start on a 16-byte boundary)
+static size_t topk_most_parts(int64_t rows, int64_t N) {
+  const size_t least = (size_t)rows * (size_t)((N + kMwPartMax - 1) / kMwPartMax);
+  return least > 512 ? least : 512;
+}
+size_t topk_scratch_bytes_no_masks(int64_t rows, int64_t N) {
+  if (N <= kTopkRegMax || rows <= 0) return 0;
+  return ((size_t)rows * Mw<11>::kFixedWords + topk_most_parts(rows, N) * Mw<11>::kPartWords) * 4;
+}
 size_t topk_scratch_bytes(int64_t rows, int64_t N) {
   if (N <= kTopkRegMax || rows <= 0) return 0;
-  const size_t least = (size_t)rows * (size_t)((N + kMwPartMax - 1) / kMwPartMax), parts = least > 512 ? least : 512;
-  return ((size_t)rows * Mw<11>::kFixedWords + parts * Mw<11>::kPartWords) * 4 + 16 + parts * kMaskBytes;
+  return topk_scratch_bytes_no_masks(rows, N) + 16 + topk_most_parts(rows, N) * kMaskBytes;
 }
 size_t topk_scratch_bytes_least(int64_t rows, int64_t N) { return topk_scratch<8>(rows, N); }
 

@@ -235,6 +235,32 @@ def test_launches_of_many_rows_stay_within_the_runtime():
     assert out["few"] == [0, 15]
 
 
+def test_topk_masks_give_way_before_the_histograms_do():
+    """1000 rows of 170 000 scores: 106 MB of scratch memory with two bits per score, 41 MB without them, 8 MB with the narrow histograms.
+    Where the bits do not fit the wide histograms stay, and the mapper keeps its workspace, as long as they fit beside it."""
+    out = run("""
+        out = {}
+        rows, n = 1000, 170000
+        for room in (9, 50, 120):
+            h = context(LLAMA)
+            fake.fake_budget(fake.fake_used() + room * 1000 * 1000)
+            before = fake.fake_used()
+            out[str(room)] = [[lib.proxykv_topk(h, P, rows, n, 1000, P, None), len(launches("mw_pass_kernelILi11E"))] for _ in range(2)]
+            out[f"{room} MB"] = (fake.fake_used() - before) // 1000000
+            fake.fake_budget((1 << 63) - 1)
+        h = context(LLAMA, weights=True)
+        assert lib.proxykv_map(h, P, 4096, P, None) == 0
+        fake.fake_budget(fake.fake_used() + 50 * 1000 * 1000)
+        before = fake.fake_used()
+        out["beside"] = [lib.proxykv_topk(h, P, rows, n, 1000, P, None), len(launches("mw_pass_kernelILi11E")), (fake.fake_used() - before) // 1000000]
+        mallocs = fake.fake_mallocs()
+        assert lib.proxykv_map(h, P, 4096, P, None) == 0
+        out["map again"] = fake.fake_mallocs() - mallocs
+    """)
+    assert out == {"9": [[0, 0]] * 2, "9 MB": 8, "50": [[0, 3]] * 2, "50 MB": 41, "120": [[0, 3]] * 2, "120 MB": 106,
+                   "beside": [0, 3, 41], "map again": 0}
+
+
 def test_short_launches_of_pass_1_take_the_wide_tiles():
     """28 x 12 heads of 128: pass 1's 16-column tiles gain in long launches only (300 keys 54.8 us with 32 columns, 57.1 with 16)."""
     out = run("""
