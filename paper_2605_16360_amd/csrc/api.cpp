@@ -131,6 +131,7 @@ LaneBytes lane_bytes(const proxykv_config& c, const pkv::MapPlan& p) {
 // bytes of buffer i of a lane: the plan's largest batch.  Shorter calls are served from the same workspace, so `pre` covers the
 // small-tile batches of all shorter lengths (they have one lane, unless there are more layers than a batch takes).
 size_t lane_need(const proxykv_config& c, const pkv::MapPlan& p, const LaneBytes& lb, int lane, int distinct, int i) {
+  if (i == 4) return pkv::kMaxBatch * lb.per_layer[i];  // `range`, a line per layer: a long plan's few would limit a short call's batch
   if (i < kLaneBuffers - 1) return (size_t)p.batch * lb.per_layer[i];
   if (c.n_enc_layers == 0 || (lane > 0 && distinct <= pkv::kMaxBatch)) return 0;
   return (size_t)pkv::small_rows(p, distinct) * (size_t)c.d_time * 4;

@@ -169,6 +169,27 @@ def test_no_call_allocates_after_a_longer_one():
         assert rc == [0, 0, 0] and covered and mallocs == 0, (shape, longest, n, mallocs)
 
 
+def test_short_maps_after_a_long_one_keep_their_batches():
+    """A longer call holds few layers of many rows at a time, which is room for many layers of few rows: a shorter call makes the batches
+    that it would make in a context of its own."""
+    out = run("""
+        out = []
+        for shape in (LLAMA, QWEN, QWEN32B):
+            def batches(h, n):
+                launches()
+                assert lib.proxykv_map(h, P, n, P, None) == 0
+                return [l[2] for l in launches("stage3_kernel")]
+            fresh = {n: batches(context(shape, weights=True), n) for n in (80, 160, 1000, 1500, 2000)}
+            for longest in (8192, 32768, 170000):
+                h = context(shape, weights=True)
+                batches(h, longest)
+                out += [(shape[0], longest, n, batches(h, n), fresh[n]) for n in fresh]
+    """)
+    assert len(out) == 45
+    for layers, longest, n, got, own in out:
+        assert got == own, (layers, longest, n, got, own)
+
+
 def test_mapper_deals_few_layers_to_both_lanes():
     """More rows than fill the chip in one turn go to two streams also where one batch could hold all layers: three layers of 3000
     tokens one behind the other took longer than side by side.  Short ones stay in one batch."""
