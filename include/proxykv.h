@@ -23,8 +23,8 @@
  *     device copy of the mapper weights.  Workspace grows on demand inside a call; call
  *     proxykv_reserve beforehand to keep allocation out of a timed or captured region.  A call
  *     no longer than one that the context has served, or has reserved for, allocates nothing.
- *     The mapper takes about 7 KB per window row of as many proxy layers as run at a time (up to
- *     0.9 GB below 16 384 tokens, 1.9 GB at 32 768); where the device has less free, it runs
+ *     The mapper takes about 6 KB per window row of as many proxy layers as run at a time (up to
+ *     0.8 GB below 16 384 tokens, 1.6 GB at 32 768); where the device has less free, it runs
  *     fewer at a time, and only if one layer does not fit is PROXYKV_ENOMEM returned.
  *     One context serves one stream at a time; concurrent calls on one context race.
  *   - Return value: PROXYKV_OK (0) or a negative proxykv_status.  All argument checks run before

@@ -126,15 +126,19 @@ struct LaneBytes {
 };
 LaneBytes lane_bytes(const proxykv_config& c, const pkv::MapPlan& p) {
   const size_t row = (size_t)p.Tp * c.d_time;
-  return {{row * 4, row * 2, pkv::map_work_bytes(c, p), (size_t)p.Np * (size_t)(c.H_l + 1) * (size_t)c.H_kv * 4, 64, row * 4}};
+  return {{row * 4, row * 2, pkv::map_work_bytes(c, p, p.small), (size_t)p.Np * (size_t)(c.H_l + 1) * (size_t)c.H_kv * 4, 64, row * 4}};
 }
-// bytes of buffer i of a lane: the plan's largest batch.  Shorter calls are served from the same workspace, so `pre` covers the
-// small-tile batches of all shorter lengths (they have one lane, unless there are more layers than a batch takes).
+// bytes of buffer i of a lane: the plan's largest batch.  Shorter calls are served from the same workspace, so `pre` and, as long as
+// that takes no more than these layers would with the small tiles, `work` cover the small-tile batches of all shorter lengths (they
+// have one lane, unless there are more layers than a batch takes).
 size_t lane_need(const proxykv_config& c, const pkv::MapPlan& p, const LaneBytes& lb, int lane, int distinct, int i) {
-  if (i == 4) return pkv::kMaxBatch * lb.per_layer[i];  // `range`, a line per layer: a long plan's few would limit a short call's batch
-  if (i < kLaneBuffers - 1) return (size_t)p.batch * lb.per_layer[i];
-  if (c.n_enc_layers == 0 || (lane > 0 && distinct <= pkv::kMaxBatch)) return 0;
-  return (size_t)pkv::small_rows(p, distinct) * (size_t)c.d_time * 4;
+  constexpr int kWork = 2, kRange = 4, kPre = kLaneBuffers - 1;
+  if (i == kRange) return pkv::kMaxBatch * lb.per_layer[i];  // a line per layer: a long plan's few would limit a short call's batch
+  const size_t own = i == kPre ? 0 : (size_t)p.batch * lb.per_layer[i];
+  if ((i != kWork && i != kPre) || c.n_enc_layers == 0 || (lane > 0 && distinct <= pkv::kMaxBatch)) return own;
+  const pkv::SmallBatch s = pkv::small_batch(c, p, distinct);
+  if (i == kPre) return (size_t)(s.layers * s.plan.Tp) * (size_t)c.d_time * 4;
+  return std::max(own, std::min((size_t)s.layers * pkv::map_work_bytes(c, s.plan, true), (size_t)p.batch * pkv::map_work_bytes(c, p, true)));
 }
 // layers of the plan's length that lane m has room for
 int lane_room(pkv::MapperWorkspace& m, const pkv::MapPlan& p, const LaneBytes& lb) {

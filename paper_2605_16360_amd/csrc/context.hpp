@@ -125,7 +125,7 @@ inline void window_plan(int64_t N, int win, int stride, int64_t* n_win, int64_t*
 // several, up to kMapBatchRows rows.  Two batches side by side, on streams and in workspaces of their own, let one's loads, stores
 // and attention run beside the other's products, so layers of more than kMapSplitRows rows together make an even number
 // of batches (3 layers of 3000 tokens in one 990 us, in two 953); a batch takes two layers if they are no more than kMapPairRows rows.
-// Every row holds about 7 KB of workspace for as long as the context lives, so the limits are where more costs more than it gives.
+// Every row holds about 6 KB of workspace for as long as the context lives, so the limits are where more costs more than it gives.
 // 16 distinct layers, us, one layer per batch / as here:
 //   N = 1500   1753 / 1491     N = 4096   7575 / 5973     N = 8192   13 756 / 13 939     N = 32 768   60 440 / 60 527
 constexpr int64_t kMapBatchRows = 65536, kMapPairRows = 131072, kMapSplitRows = 8192;
@@ -165,20 +165,25 @@ inline MapPlan map_plan(const proxykv_config& c, int64_t N, int distinct_layers,
 }
 // Bytes of `work` per layer, the largest of what is there at a time: the stem's first output, read before the encoder starts;
 // q, k and v and, with the small tiles, the attention's output, all read before the FFN's hidden rows are written; those, which the
-// small tiles alone write, read before the next layer's q, k and v are; the overlap-averaged encoder output.  A longer call's buffer
-// serves the small tiles of a shorter one, so their hidden rows count in every plan.  (12 KB of buffers per row, 7 KB with this one in their place.)
-inline size_t map_work_bytes(const proxykv_config& c, const MapPlan& p) {
+// small tiles alone write, read before the next layer's q, k and v are; the overlap-averaged encoder output.  (With a buffer for each of
+// these a row took 12 KB.)
+inline size_t map_work_bytes(const proxykv_config& c, const MapPlan& p, bool small) {
   const size_t row = (size_t)c.d_time * 2, Tp = (size_t)p.Tp;
-  const size_t attn = 4 * Tp * row, hid = Tp * (size_t)c.d_ffn * 2;
+  const size_t attn = (small ? 4 : 3) * Tp * row, hid = small ? Tp * (size_t)c.d_ffn * 2 : 0;
   const size_t h1 = ((size_t)(p.N + 2) * c.c_mid * 2 + 255) / 256 * 256, zg = (size_t)p.Np * row;
   const size_t a = attn > hid ? attn : hid, b = h1 > zg ? h1 : zg;
   return a > b ? a : b;
 }
-// Layers of a small-tile batch times their padded rows, over all lengths of up to p.N tokens.
-inline int64_t small_rows(const MapPlan& p, int distinct_layers) {
+// The largest small-tile batch of all lengths of up to p.N tokens: that of the longest.
+struct SmallBatch {
+  int64_t layers;
+  MapPlan plan;
+};
+inline SmallBatch small_batch(const proxykv_config& c, const MapPlan& p, int distinct_layers) {
   const int64_t few = (distinct_layers + kMaxBatch - 1) / kMaxBatch, b = (distinct_layers + few - 1) / few;
-  const int64_t tp = (kMapSmallRows / b + 255) / 256 * 256;
-  return b * (p.Tp < tp ? p.Tp : tp);
+  int64_t n = kMapSmallRows / b / 64 * 64;
+  if (n > c.win) n = c.win;
+  return {b, map_plan(c, n < p.N ? n : p.N, distinct_layers)};
 }
 
 // Runs the mapper for every distinct proxy layer; implemented in mapper.hip.
