@@ -173,10 +173,21 @@ def test_topk_of_long_rows_by_bits_and_by_keys(rows):
 def test_compact_inplace_at_the_edges_of_chunks(D):
     """Kept counts around whole chunks of 128 tokens, every number of 16-byte pieces per thread, tokens with and without 128-byte
     parts, and kept tokens that each move by a few places only, so that a token's new place is another's old one."""
+    _check_compact_inplace(D, 3, (1, 127, 128, 129, 255, 256, 257, 1000))
+
+
+@pytest.mark.parametrize("D", [128, 256])
+@pytest.mark.parametrize("rows", [255, 256])
+def test_compact_inplace_at_the_edges_of_chunks_of_many_rows(D, rows):
+    """The same where a workgroup's part of a token becomes 256 bytes instead of 128: from 256 rows on."""
+    _check_compact_inplace(D, rows, (1, 127, 128, 129, 257))
+
+
+def _check_compact_inplace(D, rows, counts):
     ctx = _ctx(synth.CASES["tiny"])
     g = torch.Generator().manual_seed(D)
-    for K in (1, 127, 128, 129, 255, 256, 257, 1000):
-        N, rows = K + 5, 3
+    for K in counts:
+        N = K + 5
         idx = torch.stack([torch.randperm(N, generator=g)[:K].sort().values for _ in range(rows)]).to(torch.int32)
         kv = torch.randn(2, rows, N, D, generator=g).to(torch.bfloat16)
         k, v = kv[0].cuda(), kv[1].cuda()
@@ -185,7 +196,7 @@ def test_compact_inplace_at_the_edges_of_chunks(D):
         for got, src in ((k, kv[0]), (v, kv[1])):
             want = src.clone()
             want[:, :K] = torch.gather(src, 1, idx.long().unsqueeze(2).expand(-1, -1, D))
-            assert torch.equal(got.cpu().view(torch.int16), want.view(torch.int16)), K
+            assert torch.equal(got.cpu().view(torch.int16), want.view(torch.int16)), (rows, K)
     pk.proxykv_destroy(ctx)
 
 
@@ -204,14 +215,24 @@ def test_pooled_budget_bit_exact():
     """One budget per layer shared by its heads: kept flat indices, per-head counts, and the ragged in-place
     compaction, against the oracle.  Covers short rows (register-resident selection) and long ones, heads that
     get nothing, a head that gets everything it has, ties across heads."""
+    _check_pooled([(2, 4, 700, 128, 211), (1, 3, 130, 64, 130), (1, 1, 9, 128, 1), (3, 8, 6000, 128, 1800),
+                   (1, 2, 1537, 256, 300), (2, 5, 333, 64, 7)])
+
+
+@pytest.mark.parametrize("D", [128, 256])
+def test_pooled_budget_of_many_rows_bit_exact(D):
+    """The same with 256 (layer, head) pairs and more, whose tokens move in parts of 256 bytes; in every layer a head gets nothing."""
+    _check_pooled([(64, 4, 300, D, 129), (90, 3, 133, D, 40)], nothing=slice(None))
+
+
+def _check_pooled(cases, nothing=0):
     ctx = _ctx(synth.CASES["tiny"])
     g = torch.Generator().manual_seed(5)
-    for (L, H, N, D, K) in [(2, 4, 700, 128, 211), (1, 3, 130, 64, 130), (1, 1, 9, 128, 1), (3, 8, 6000, 128, 1800),
-                            (1, 2, 1537, 256, 300), (2, 5, 333, 64, 7)]:
+    for (L, H, N, D, K) in cases:
         s = torch.randn(L, H, N, generator=g)
         s[0, 0] += 4.0                                  # head 0 of layer 0 takes as much as it can
         if H > 2:
-            s[0, 2] -= 8.0                              # and head 2 gets nothing
+            s[nothing, 2] -= 8.0                        # and head 2 gets nothing
         if L > 1:
             s[1] = torch.round(s[1] * 2) / 2            # ties across heads
         flat_ref, counts_ref = oracle.topk_pooled(s, K)
@@ -219,6 +240,7 @@ def test_pooled_budget_bit_exact():
         torch.cuda.synchronize()
         assert torch.equal(flat.cpu(), flat_ref), (N, K)
         assert torch.equal(counts.cpu(), counts_ref), (N, K)
+        assert H < 3 or H * K > (H - 1) * N or bool((counts_ref[nothing, 2] == 0).all())
         kv = torch.randn(2, L, H, N, D, generator=g).to(torch.bfloat16)
         k, v = kv[0].cuda(), kv[1].cuda()
         pk.proxykv_compact_pooled(ctx, k, v, flat, counts)
