@@ -220,8 +220,10 @@ hipError_t launch_compact_inplace(void* k, void* v, const int32_t* idx, int64_t 
   // 128-byte parts of a token where it divides into them, and 256-byte ones where K and V of the rows alone give every CU two workgroups
   // (D = 128, 128-byte and 256-byte parts, us: 512 rows of 12 345 tokens, half kept, 697 and 680; 256 of 2000, 0.8 kept, 78 and 76, of
   // 5000 with shared budgets, 0.3 kept, 139 and 128; but 112 of 2000 49 and 51, of 21 718 with shared budgets, 0.145 kept, 144 and 150: a long
-  // row is then all that is left at the end; 4 rows of 20 000, 67 and 89)
-  const int part = rows >= 256 && cpr % 16 == 0 ? 16 : 8;
+  // row is then all that is left at the end; 4 rows of 20 000, 67 and 89).  Rows of equal budgets of up to four chunks are better off with
+  // twice as many workgroups (256 rows, kept 150 of 1500 18.3 and 19.3, 280 of 700 23.9 and 24.2, 500 of 5000 36.8 and 37.4; 600 of 1500 level,
+  // 512 rows 69.7 and 67.8), those of shared budgets are not (256 rows, 280 a head of 700 35.9 and 35.2, 400 of 1000 44.5 and 43.0).
+  const int part = rows >= 256 && (counts != nullptr || K > 4 * kInplaceTokens) && cpr % 16 == 0 ? 16 : 8;
   const int slices = cpr % part == 0 ? cpr / part : 1, cps = cpr / slices;
   const int per = (kInplaceTokens * cps + 255) / 256;                 // 16-byte pieces per thread and chunk
   u32x4 *kp = (u32x4*)k, *vp = (u32x4*)v;

@@ -179,8 +179,8 @@ def test_compact_inplace_at_the_edges_of_chunks(D):
 @pytest.mark.parametrize("D", [128, 256])
 @pytest.mark.parametrize("rows", [255, 256])
 def test_compact_inplace_at_the_edges_of_chunks_of_many_rows(D, rows):
-    """The same where a workgroup's part of a token becomes 256 bytes instead of 128: from 256 rows on."""
-    _check_compact_inplace(D, rows, (1, 127, 128, 129, 257))
+    """The same where a workgroup's part of a token becomes 256 bytes instead of 128: from 256 rows and 513 kept tokens on."""
+    _check_compact_inplace(D, rows, (1, 128, 257, 512, 513, 639, 640, 641))
 
 
 def _check_compact_inplace(D, rows, counts):
