@@ -380,8 +380,9 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
 // each) with one barrier per tile: while tile t is computed, tile t+1 lies there and t+2 and t+3 are on their way.
 // A column's reference is the largest logit of its first 64 keys, raised in any later tile whose largest exceeds it by more than 2^8, so a
 // tile costs the same wherever the sharp keys lie.  (Left out of the later tiles, with a second pass over the keys where a row sum
-// overflows half, the maxima save 0.3 to 0.9 %, 16 layers of 8192 and 20 000 tokens 13 667 -> 13 622 and 36 626 -> 36 280 us; but logits
-// five times as wide, beyond that in every workgroup, then take 19 506 and 52 549 us in place of 14 204 and 38 044.)
+// overflows half, the maxima save up to 1.4 %: 16 layers of 8192 and 20 000 tokens 13 994 and 14 039, 37 435 and 37 342 us, 28 of 1500
+// 2462 and 2429; but logits five times as wide, beyond that in every workgroup, then take 19 943, 53 491 and 3217 us, here
+// 14 373, 38 656 and 2503.)
 // Layer b of the batch owns rows [b * Tp, b * Tp + T); its windows start every 2048 rows.  What the 64 rows of a layer's last row hold beyond
 // it is finite, and keys there are masked; rows behind are not read as keys, and queries there are computed and dropped.
 // Block -> work mapping: blocks are dealt round-robin to the 8 XCDs, so with n_qb blocks of 256 queries per window block
@@ -415,7 +416,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
   // instructions as the exponentials.)  It takes the probabilities as the second product sees them, rounded to half.
   f32x4 ls[4];
   const f16x8 ones = {(_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f};
-  float m_run[4];
+  float m_run[4], beyond[4];  // reference, times c; the logit that raises it
 
   const int n_tiles = (len + 63) / 64;
   typedef const __attribute__((address_space(1))) void* gptr_t;
@@ -438,7 +439,8 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
 #pragma unroll
     for (int i = 0; i < 4; ++i) fk[i >> 1][i & 1] = as_f16x8(st[(kt * 2 + i) * 64]);
   };
-  auto tile = [&](int t) __attribute__((always_inline)) {
+  // one tile; `cut`: the keys end in it
+  auto tile = [&](int t, auto cut) __attribute__((always_inline)) {
     // this wave's part of tile t+1 has landed (the four loads of tile t+2 may be outstanding); behind the barrier everyone's has, and
     // every wave has finished tile t-1, whose stage takes tile t+3
     __builtin_amdgcn_s_waitcnt(0x0F74);  // vmcnt(4)
@@ -463,7 +465,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
     __builtin_amdgcn_sched_barrier(0);
     logits(2, fb[0]);
     logits(3, fb[1]);
-    if (j0 + 64 > len) {
+    if constexpr (decltype(cut)::value) {
       const int lim = len - j0 - quad * 4;  // element i of tile kt is key j0 + kt*16 + quad*4 + i
 #pragma unroll
       for (int kt = 0; kt < 4; ++kt)
@@ -472,26 +474,41 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
 #pragma unroll
           for (int i = 0; i < 4; ++i) s[kt][qt][i] = kt * 16 + i < lim ? s[kt][qt][i] : kNegInf;
     }
+    // the largest logits: of the first 32 keys while the products of the others are on their way
     float tmax[4];
     bool raise = false;
 #pragma unroll
     for (int qt = 0; qt < 4; ++qt) {
-      float m = max3f(s[0][qt][0], s[0][qt][1], s[0][qt][2]);
-      m = max3f(m, s[0][qt][3], s[1][qt][0]);
-      m = max3f(m, s[1][qt][1], s[1][qt][2]);
-      m = max3f(m, s[1][qt][3], s[2][qt][0]);
+      tmax[qt] = max3f(s[0][qt][0], s[0][qt][1], s[0][qt][2]);
+      tmax[qt] = max3f(tmax[qt], s[0][qt][3], s[1][qt][0]);
+      tmax[qt] = max3f(tmax[qt], s[1][qt][1], s[1][qt][2]);
+    }
+    if constexpr (!decltype(cut)::value) {
+#pragma unroll
+      for (int i = 0; i < 12; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
+        __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);  // one vector instruction
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int qt = 0; qt < 4; ++qt) {
+      float m = max3f(tmax[qt], s[1][qt][3], s[2][qt][0]);
       m = max3f(m, s[2][qt][1], s[2][qt][2]);
       m = max3f(m, s[2][qt][3], s[3][qt][0]);
       m = max3f(m, s[3][qt][1], s[3][qt][2]);
-      tmax[qt] = __builtin_fmaxf(m, s[3][qt][3]) * c;
-      raise |= tmax[qt] > m_run[qt] + kAttnLazy;
+      tmax[qt] = __builtin_fmaxf(m, s[3][qt][3]);
+      raise |= tmax[qt] > beyond[qt];
     }
     // a column's logits lie in four lanes; only where one of them is beyond the reference do they have to agree on a new one
     if (__builtin_amdgcn_ballot_w64(raise)) {
 #pragma unroll
       for (int qt = 0; qt < 4; ++qt) {
         const float tm = quads_max(tmax[qt]);
-        const float nm = tm > m_run[qt] + kAttnLazy ? tm : m_run[qt];
+        const bool up = tm > beyond[qt];
+        const float nm = up ? tm * c : m_run[qt];
+        beyond[qt] = up ? tm + kAttnLazy / c : beyond[qt];
         const float alpha = __builtin_amdgcn_exp2f(m_run[qt] - nm);
         ls[qt] *= alpha;
 #pragma unroll
@@ -546,7 +563,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
   for (int qt = 0; qt < 4; ++qt) {
 #pragma unroll
     for (int d = 0; d < 4; ++d) o[d][qt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    m_run[qt] = -1.0e30f;
+    m_run[qt] = beyond[qt] = -1.0e30f;
     ls[qt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
   fetch(0, 0);
@@ -555,7 +572,9 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
   __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8): tile 0
   __syncthreads();
   read_k(lds + lane, 0, fa);
-  for (int t = 0; t < n_tiles; ++t) tile(t);
+  const int whole = len / 64;
+  for (int t = 0; t < whole; ++t) tile(t, std::false_type{});
+  if (whole < n_tiles) tile(whole, std::true_type{});
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing of this workgroup writes LDS that anyone may have by then
 
   // output: O^T / row sum; a lane's eight accumulators are the unit that the next product's operand wants from it
