@@ -93,8 +93,7 @@ int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream, 
     hip_ok(ctx, e);
     return e == hipErrorOutOfMemory ? PROXYKV_ENOMEM : PROXYKV_EHIP;
   }
-  // start from zeros: padded regions that no kernel writes (the tail of a short last window in the
-  // transposed-V buffer) must hold finite values
+  // start from zeros: padding that no kernel writes is read, and dropped, as finite values
   e = hipMemset(p, 0, bytes);
   if (e != hipSuccess) {
     hip_ok(ctx, e);
