@@ -380,9 +380,9 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
 // each) with one barrier per tile: while tile t is computed, tile t+1 lies there and t+2 and t+3 are on their way.
 // A column's reference is the largest logit of its first 64 keys, raised in any later tile whose largest exceeds it by more than 2^8, so a
 // tile costs the same wherever the sharp keys lie.  (Left out of the later tiles, with a second pass over the keys where a row sum
-// overflows half, the maxima save up to 1.4 %: 16 layers of 8192 and 20 000 tokens 13 994 and 14 039, 37 435 and 37 342 us, 28 of 1500
-// 2462 and 2429; but logits five times as wide, beyond that in every workgroup, then take 19 943, 53 491 and 3217 us, here
-// 14 373, 38 656 and 2503.)
+// overflows half, the maxima save up to 1 %: 16 layers of 20 000 tokens 35 766 us and 36 114 here, of 8192 13 768 and 13 551, 28 of 1500
+// 2401 and 2404; but logits five times as wide, beyond that in every workgroup, then take 51 179, 19 260 and 3149 us, here
+// 36 843, 14 122 and 2476.)
 // Layer b of the batch owns rows [b * Tp, b * Tp + T); its windows start every 2048 rows.  What the 64 rows of a layer's last row hold beyond
 // it is finite, and keys there are masked; rows behind are not read as keys, and queries there are computed and dropped.
 // Block -> work mapping: blocks are dealt round-robin to the 8 XCDs, so with n_qb blocks of 256 queries per window block
@@ -474,14 +474,14 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
 #pragma unroll
           for (int i = 0; i < 4; ++i) s[kt][qt][i] = kt * 16 + i < lim ? s[kt][qt][i] : kNegInf;
     }
-    // the largest logits: of the first 32 keys while the products of the others are on their way
+    // the largest logits, or what they have to exceed: of the first 32 keys while the products of the others are on their way
     float tmax[4];
     bool raise = false;
 #pragma unroll
     for (int qt = 0; qt < 4; ++qt) {
-      tmax[qt] = max3f(s[0][qt][0], s[0][qt][1], s[0][qt][2]);
-      tmax[qt] = max3f(tmax[qt], s[0][qt][3], s[1][qt][0]);
-      tmax[qt] = max3f(tmax[qt], s[1][qt][1], s[1][qt][2]);
+      tmax[qt] = max3f(beyond[qt], s[0][qt][0], s[0][qt][1]);
+      tmax[qt] = max3f(tmax[qt], s[0][qt][2], s[0][qt][3]);
+      tmax[qt] = max3f(tmax[qt], s[1][qt][0], s[1][qt][1]);
     }
     if constexpr (!decltype(cut)::value) {
 #pragma unroll
@@ -494,11 +494,11 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
     }
 #pragma unroll
     for (int qt = 0; qt < 4; ++qt) {
-      float m = max3f(tmax[qt], s[1][qt][3], s[2][qt][0]);
-      m = max3f(m, s[2][qt][1], s[2][qt][2]);
-      m = max3f(m, s[2][qt][3], s[3][qt][0]);
-      m = max3f(m, s[3][qt][1], s[3][qt][2]);
-      tmax[qt] = __builtin_fmaxf(m, s[3][qt][3]);
+      tmax[qt] = max3f(tmax[qt], s[1][qt][2], s[1][qt][3]);
+      tmax[qt] = max3f(tmax[qt], s[2][qt][0], s[2][qt][1]);
+      tmax[qt] = max3f(tmax[qt], s[2][qt][2], s[2][qt][3]);
+      tmax[qt] = max3f(tmax[qt], s[3][qt][0], s[3][qt][1]);
+      tmax[qt] = max3f(tmax[qt], s[3][qt][2], s[3][qt][3]);
       raise |= tmax[qt] > beyond[qt];
     }
     // a column's logits lie in four lanes; only where one of them is beyond the reference do they have to agree on a new one
