@@ -577,6 +577,23 @@ def test_mapper_where_the_small_tiles_end(L, N):
     test_mapper_at_the_edges_of_a_block(L, N)
 
 
+@pytest.mark.parametrize("d_ffn,c_mid,n_enc", [(256, 256, 1), (512, 512, 2), (4096, 768, 1), (2048, 256, 0)])
+@pytest.mark.parametrize("L,N", [(2, 300), (2, 2600), (33, 1030)])
+def test_mapper_of_other_sizes(d_ffn, c_mid, n_enc, L, N):
+    """One chunk of hidden features and sixteen, a wider stem, encoders of no, one and two layers (whose first launch is followed by the
+    last); small tiles, half blocks of three windows and whole blocks, in more layers than one batch takes."""
+    dims = synth.MapperDims(d_ffn=d_ffn, c_mid=c_mid, n_enc_layers=n_enc)
+    w = synth.make_mapper_weights(2, 3, dims)
+    ctx = pk.proxykv_create(pk.make_config(L, 2, 2, 64, L, 3, 128, d_ffn=d_ffn, c_mid=c_mid, n_enc_layers=n_enc))
+    pk.proxykv_set_mapper_weights(ctx, w)
+    X = torch.rand(L, 2, N, generator=torch.Generator().manual_seed(N)) ** 8
+    y = pk.proxykv_map(ctx, X.cuda()).cpu()
+    torch.cuda.synchronize()
+    for l in {0, L - 1}:
+        assert_close(y[l:l + 1], oracle.mapper(X, w, L, layers=[l])[l:l + 1], f"map d_ffn={d_ffn} c_mid={c_mid} {n_enc} layers, N={N}, layer {l}")
+    pk.proxykv_destroy(ctx)
+
+
 def test_mapper_half_blocks_are_whole_blocks_bit_for_bit():
     """26 layers of 600 tokens are two times 65 blocks, more than half of the CUs, and run as whole blocks; the first 8 of them alone
     run as halves, of which each layer's last holds 24 rows."""
