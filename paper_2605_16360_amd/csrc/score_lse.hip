@@ -67,6 +67,8 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     l = it.set / H_q;
   }
   const int H_kv = H_q / G, hs = h / G, i0 = qb * QB;
+  // where the part's results start: at the end the grid's size would be waited for (causal, 256 tokens of 28 x 12 heads of 128 34.3 -> 33.6 us)
+  const size_t split0 = SPLIT ? (size_t)split * gridDim.z * H_q * N_q : 0;
   if (n_x > 0) {
     const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
     const int64_t stride = (int64_t)gridDim.x * gridDim.y * gridDim.z * 256;
@@ -311,15 +313,14 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
       tot = tot * __builtin_amdgcn_exp2f(m - mm) + l2 * __builtin_amdgcn_exp2f(m2 - mm);
       m = mm;
     }
-    const size_t at = ((size_t)split * gridDim.z * H_q + l * H_q + h) * N_q + qi[ct];
+    const size_t at = split0 + (size_t)(l * H_q + h) * N_q + qi[ct];
     const float whole = -(m + __builtin_amdgcn_logf(tot)) * inv_c;
     if (lane < W && qi[ct] < N_q) {
       if constexpr (SPLIT && D == 64) {
         reinterpret_cast<LsePart*>(neg_lse)[at] = LsePart{m, tot};
-      } else if constexpr (SPLIT) {  // also launched with one split (as a branch: 214 keys of 28 x 12 heads 38.0 us, so 37.8)
-        const int words = splits > 1 ? 2 : 1;
-        neg_lse[at * words + words - 1] = tot;
-        neg_lse[at * words] = splits > 1 ? m : whole;
+      } else if constexpr (SPLIT) {  // also launched with one split
+        if (splits > 1) reinterpret_cast<LsePart*>(neg_lse)[at] = LsePart{m, tot};
+        else neg_lse[at] = whole;
       } else {
         neg_lse[at] = whole;
       }
@@ -332,7 +333,7 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
 // Columns of an MFMA tile.  16 x 16 x 32 instructions draw less than 32 x 32 x 16, but there are twice as many to issue: at d = 128, where
 // the products take as long as the exponentials, they gain once there is enough work for the chip's power to set its clock (28 x 12 heads,
 // 10 007 keys, both passes 18 170 -> 17 000 us), but not in short launches, up to query blocks times keys of 2^20 or with shared
-// blocks.  Both passes, 32 / 16 columns, us: 214 keys 37.4 / 39.8, 257 53.2 / 55.7, 300 54.8 / 57.1, 420 74.0 / 75.8, 600 128.3 / 130.3,
+// blocks.  Both passes, 32 / 16 columns, us: 214 keys 37.6 / 39.8, 257 53.4 / 55.7, 300 55.1 / 57.0, 420 74.0 / 75.8, 600 128.3 / 130.3,
 // 300 queries of 1500 keys 129.2 / 131.0; beyond the line 900 240.7 / 242.5, 1024 268.8 / 263.7, 300 queries of 4000 296.2 / 296.6, 500
 // 368.7 / 361.8.  Causal, with the longest blocks first, they gain from 400 tokens on (56.3 / 55.5, 700 97.2 / 91.6; 300 44.1 / 46.7, in
 // the order of the blocks 51.2).  At d = 64, where the vector ALU sets the time, they do not (16 x 32 heads, 8192 keys 9030 and
