@@ -40,6 +40,15 @@ constexpr float kRebase = 1.8446744e19f;  // 2^64
 // undoes the tile and sums it again chain by chain with the check.
 constexpr float kTileRedo = 1.2676506e30f;  // 2^100
 
+// Query block of place x of nb in head g.  Workgroups go round the eight XCDs in launch order, and a block is the longer the further back
+// in its chunk it lies: where nb is a multiple of eight, an XCD would meet the same places of a chunk in every head (8192 tokens in chunks
+// of 2048: XCD 7 only blocks of 80 tiles, XCD 0 of 66), and all wait for the one with the longest.  So the blocks of a head are
+// turned, by as much as moves a block's XCD on by one from head to head.  Both passes: 16 x 32 heads, 2000 queries and keys 783 -> 725 us,
+// 8192 9067 -> 8463; 24 x 14 heads, 6001, sum form 4295 -> 4065; 28 x 12 heads of 128, 10 007 17 065 -> 16 270; with four blocks, where a place
+// has two XCDs, 16 x 32 heads of 900 196 -> 193.  Other numbers of blocks spread by themselves (six, turned: 24 x 14 heads of 1400 271 ->
+// 277), and workgroups that share a block are few and short (one layer of 512 keys 15.9 -> 16.2).
+__device__ __forceinline__ int turned_block(int x, int nb, int g) { return (x + (nb + 7) % 8 * (g % 8)) % nb; }
+
 // SPLIT: `splits` workgroups per query block; with more than one neg_lse holds (reference, sum) pairs [splits][L_s * H_q * N_q].
 // x [n_x] (n_x may be 0) is cleared for a pass 2 whose workgroups raise it.
 template <int D, int NCOL, int W, int MINB, bool SPLIT>
@@ -65,6 +74,9 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const uint16_t* __
     qb = nb - 1 - it.item;
     h = it.set % H_q;
     l = it.set / H_q;
+  }
+  if constexpr (!SPLIT || D == 128) {
+    if (N > 0 && gridDim.x % 4 == 0 && (!SPLIT || splits == 1)) qb = turned_block(qb, gridDim.x, l * H_q + h);
   }
   const int H_kv = H_q / G, hs = h / G, i0 = qb * QB;
   // where the part's results start: at the end the grid's size would be waited for (causal, 256 tokens of 28 x 12 heads of 128 34.3 -> 33.6 us)

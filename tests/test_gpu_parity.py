@@ -415,8 +415,15 @@ def test_score_where_the_wide_tiles_end(N, scale):
     _score_47_layers(257, N, scale)
 
 
-def _score_47_layers(N_q, N, scale):
-    L, H_q, H_kv, d, chunk = 47, 8, 2, 128, 200
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N_q", [769, 1024, 1025, 2048])
+def test_score_of_heads_of_four_and_eight_query_blocks(N_q, d):
+    """Four and eight query blocks per head, whose order is turned from head to head, and five, whose order is not."""
+    _score_47_layers(N_q, 300, 1.0, d)
+
+
+def _score_47_layers(N_q, N, scale, d=128):
+    L, H_q, H_kv, chunk = 47, 8, 2, 200
     g = torch.Generator().manual_seed(N_q)
     q = (scale * torch.randn(L, H_q, N_q, d, generator=g)).bfloat16()
     kc, kr = (torch.randn(L, H_kv, n, d, generator=g).bfloat16() for n in (N, N_q))
