@@ -18,20 +18,25 @@ constexpr int kNBuf = 3;
 constexpr int kVmcnt0 = 0x0F70;  // s_waitcnt vmcnt(0)
 
 // Block -> (group, item) on a one-dimensional grid.  The hardware deals blocks round-robin to the 8 XCDs, so XCD x
-// = block % 8 takes the (layer, KV head) groups x, x + 8, ... one after the other: the `per_group` blocks of a group run
+// = block % 8 takes the x-th eighth of the groups' items, (layer, KV head) groups one after the other: the `per_group` blocks of a group run
 // on one XCD at about the same time and share its L2 copy of the queries they all stream in pass 2 (measured: 4.9 GB
-// leave the L2s per launch at N = 32k instead of 18.5 GB with the key blocks of a group dealt over all XCDs).
+// leave the L2s per launch at N = 32k instead of 18.5 GB with the key blocks of a group dealt over all XCDs).  Eighths of the items, not of
+// the groups: two groups kept two XCDs busy and six idle (one layer of 4 heads, 14 000 queries and keys, both passes 426 -> 229 us,
+// the sum form with 6000 142 -> 74).
 constexpr int kScoreXcds = 8;
 struct GroupBlock {
-  int group, item;
+  int group, item;  // group == n_groups: nothing to do
 };
-__device__ __forceinline__ GroupBlock group_block(int per_group) {
+__device__ __forceinline__ GroupBlock group_block(int n_groups, int per_group) {
   const int xcd = blockIdx.x % kScoreXcds, j = blockIdx.x / kScoreXcds;
-  return {(j / per_group) * kScoreXcds + xcd, j % per_group};
+  const int total = n_groups * per_group, each = total / kScoreXcds, more = total % kScoreXcds;  // XCDs below `more` take one more
+  if (j >= each + (xcd < more)) return {n_groups, 0};
+  const int i = xcd * each + (xcd < more ? xcd : more) + j;
+  return {i / per_group, i % per_group};
 }
 // number of blocks of such a grid; 0 if it does not fit a one-dimensional launch
 inline unsigned group_grid(int64_t n_groups, int64_t per_group) {
-  const int64_t blocks = kScoreXcds * ((n_groups + kScoreXcds - 1) / kScoreXcds) * per_group;
+  const int64_t blocks = kScoreXcds * ((n_groups * per_group + kScoreXcds - 1) / kScoreXcds);
   return blocks < (1ll << 31) ? (unsigned)blocks : 0u;
 }
 

@@ -370,6 +370,26 @@ def test_score_degenerate_shapes(N, N_q, chunk):
         pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("L,H_q,H_kv", [(1, 1, 1), (3, 2, 1), (9, 1, 1), (13, 2, 1), (4, 4, 4)])
+@pytest.mark.parametrize("N", [257, 1100])
+def test_score_of_groups_that_do_not_fill_the_xcds_evenly(L, H_q, H_kv, N):
+    """Pass 2 deals the groups' key blocks to eight XCDs: one group, three, nine, thirteen (and sixteen, two each); max, sum and causal forms."""
+    g = torch.Generator().manual_seed(L + N)
+    q = torch.randn(L, H_q, 300, 64, generator=g).bfloat16()
+    kc, kr = (torch.randn(L, H_kv, n, 64, generator=g).bfloat16() for n in (N, 300))
+    own = torch.randn(L, H_q, N, 64, generator=g).bfloat16()
+    for reduce, code in (("max", pk.PROXYKV_REDUCE_MAX), ("sum", pk.PROXYKV_REDUCE_SUM)):
+        cfg = pk.make_config(L, H_q, H_kv, 64, 1, 4, 128)
+        cfg.reduce = code
+        ctx = pk.proxykv_create(cfg)
+        x = pk.proxykv_score(ctx, q.cuda(), kc.cuda(), kr.cuda(), 128)
+        xs = pk.proxykv_score_self(ctx, own.cuda(), kc.cuda())
+        torch.cuda.synchronize()
+        assert_close(x, oracle.score(q, kc, kr, 128, reduce=reduce), f"score {reduce}")
+        assert_close(xs, oracle.score_self(own, kc), "score_self")
+        pk.proxykv_destroy(ctx)
+
+
 @pytest.mark.parametrize("d,N,N_q,chunk", [(64, 1, 3, 2), (64, 700, 257, 100), (64, 1030, 130, 64), (128, 65, 300, 1000), (128, 900, 64, 33),
                                           (128, 1100, 200, 256), (64, 2600, 1700, 512)])
 def test_score_few_and_many_query_blocks_agree(d, N, N_q, chunk):
