@@ -40,8 +40,10 @@ constexpr int64_t kTopkSingleMax = 36864;  // longest row one workgroup selects 
 size_t topk_scratch_bytes(int64_t rows, int64_t N);
 size_t topk_scratch_bytes_no_masks(int64_t rows, int64_t N);
 size_t topk_scratch_bytes_least(int64_t rows, int64_t N);
+// `patience`: how long, in ticks of 10 ns, a workgroup waits for the others of its row before it selects by itself (topk.hip).
+constexpr unsigned long long kTopkPatience = 20000;
 hipError_t launch_topk(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
-                       size_t scratch_bytes, hipStream_t stream);
+                       size_t scratch_bytes, hipStream_t stream, unsigned long long patience = kTopkPatience);
 // The same selection with every workgroup gathering the token rows it kept: k_out[r, j, :] = k_in[r, idx[r, j], :] and
 // likewise v (row_bytes per token, 1024 / (row_bytes / 16) a whole number).
 hipError_t launch_topk_gather(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,

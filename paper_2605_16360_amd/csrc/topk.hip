@@ -9,7 +9,8 @@
 // by counting per (chunk, wave) and ranking inside a wave with ballots, so that stores too lie side by side.
 //
 // A row of up to 36 864 scores is one workgroup's, its keys stay in registers for all passes.  A longer row is split into
-// parts, one workgroup each, so that few long rows still fill the chip: three launches of an 11-bit radix pass on the raw
+// parts, one workgroup each.  Where there are rows enough, and all parts fit the chip at once, those stay in registers too and the workgroups
+// of a row meet after every digit (one launch).  Few rows, and more than fit, take three launches of an 11-bit radix pass on the raw
 // keys whose per-part histograms meet in a per-row histogram in device scratch memory (the last workgroup of a row to
 // arrive picks the digit), then one launch that writes every part's kept indices behind those of the parts before it.
 // Where the scratch memory is too small for 2048-bin histograms the same kernels run four passes of 8 bits.
@@ -38,6 +39,8 @@ __device__ __forceinline__ float key_score(uint32_t k) {
 // hi).  There is no branch: with one per quad the compiler waits for a quad before it asks for the next (nine trips to
 // memory, one after the other, in a row of 36 864 scores).
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ int quad_shift(int i, int hi) { return i > hi - 4 ? i - (hi - 4) : 0; }
 __device__ __forceinline__ f32x4 load_quad(const float* row, int i, int hi) {
   const f32x4_any v = *reinterpret_cast<const f32x4_any*>(row + (i - quad_shift(i, hi)));
@@ -71,41 +74,97 @@ __device__ __forceinline__ uint32_t wave_total(uint32_t v) {
   return (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_scan(v), 63);
 }
 // Ordered output of a wave's scores: quad q of lane l holds the scores 256 q + 4 l .. +3 of the wave's stretch, whose first has
-// index i0.  Kept: scores above the threshold (bit 4 q + j of m_gt), and those equal to it (m_eq) of which fewer than
+// index i0.  Kept: scores above the threshold (bit 4 (q % 8) + j of m_gt[q / 8]), and those equal to it (m_eq) of which fewer than
 // eq_take equal ones lie in front; gt and eq count the scores above and equal in front of the stretch.  A kept one goes to
 // out[kept ones in front of it].  Loops are left rolled: this code runs once per wave, and straight-line code of 25 KB
 // spends its time on instruction fetch (112 rows of 170 000 scores: 31 us without any load or store).
-__device__ __forceinline__ void wave_write(uint64_t m_gt, uint64_t m_eq, int quads, uint32_t gt, uint32_t eq, uint32_t eq_take,
-                                           int i0, int lane, int32_t* out) {
-  const bool any_eq = __builtin_amdgcn_ballot_w64(m_eq != 0) != 0;
+// Four quads share a prefix sum, a byte each: a lane has at most 252 scores of a quad in front of it, and what a full quad carries into the
+// next byte of lane 63's inclusive sum goes away with the lane's own counts.
+// Kept indices go to the wave's place in LDS first and from there to memory side by side: stored from where they are found,
+// a wave's stores of four quads are sixteen instructions of a fifth of its lanes each (256 rows of 32 767 scores, nine in ten kept: the whole
+// kernel 28.5 -> 23.3 us; 512 of 12 000, half kept, 14.3 -> 12.9 with the shared prefix sum).
+constexpr int kStageWords = 1024;  // of a wave: four quads
+template <int WORDS>
+__device__ __forceinline__ void wave_write(const uint32_t (&m_gt)[WORDS], const uint32_t (&m_eq)[WORDS], int quads, uint32_t gt, uint32_t eq,
+                                           uint32_t eq_take, int i0, int lane, int32_t* stage, int32_t* out) {
   int i = i0 + 4 * lane;
+  out += (size_t)gt + (eq < eq_take ? eq : eq_take);
+#pragma unroll
+  for (int w = 0; w < WORDS; ++w) {
+    uint32_t wg = m_gt[w], we = m_eq[w];
 #pragma unroll 1
-  for (int q = 0; q < quads; ++q, i += 256) {
-    const uint32_t bg = (uint32_t)m_gt & 15u;
-    m_gt >>= 4;
-    const uint32_t n = (uint32_t)__popc(bg), inc = wave_inclusive_scan(n);
-    uint32_t pos = gt + inc - n + (eq < eq_take ? eq : eq_take);
-    gt += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
-    if (!any_eq) {
+    for (int left = quads - 8 * w < 8 ? quads - 8 * w : 8; left > 0; left -= 4, wg >>= 16, we >>= 16, i += 1024) {
+      uint32_t n = wg & 0xffffu;  // per nibble its number of bits, to a byte
+      const uint64_t any_eq = __builtin_amdgcn_ballot_w64((we & 0xffffu) != 0);
+      uint32_t kept = wg;
+      if (any_eq != 0) {
+        // equal ones join the others here; lanes, and in a lane quads, hold them in another order than the indices': quad by quad
+        uint32_t first = eq;
+#pragma unroll 1
+        for (int q = 0; q < 4; ++q) {
+          const uint32_t be = (we >> (4 * q)) & 15u, ne = (uint32_t)__popc(be), inc = wave_inclusive_scan(ne);
+          uint32_t e = first + inc - ne, take = 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t b = (bg >> j) & 1u;
-        if (b) out[pos] = i + j;
-        pos += b;
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t is = (be >> j) & 1u;
+            take |= (e < eq_take ? is : 0u) << j;
+            e += is;
+          }
+          kept |= take << (4 * q);
+          first += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        }
+        eq = first;
+        n = kept & 0xffffu;
       }
-    } else {
-      const uint32_t be = (uint32_t)m_eq & 15u;
-      m_eq >>= 4;
-      const uint32_t ne = (uint32_t)__popc(be), ince = wave_inclusive_scan(ne);
-      uint32_t g = pos - (eq < eq_take ? eq : eq_take), e = eq + ince - ne;  // scores above, and equal ones, in front
-      eq += (uint32_t)__builtin_amdgcn_readlane((int)ince, 63);
+      if (left <= 2) {  // short rows and parts, and the end of others: stored from where they are found, the way through LDS is longer
+#pragma unroll 1
+        for (int q = 0; q < left; ++q, kept >>= 4) {
+          const uint32_t bits = kept & 15u, own = (uint32_t)__popc(bits), inc = wave_inclusive_scan(own);
+          int32_t* at = out + (inc - own);
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const bool is_g = (bg >> j) & 1u, is_e = (be >> j) & 1u;
-        if (is_g || (is_e && e < eq_take)) out[g + (e < eq_take ? e : eq_take)] = i + j;
-        g += is_g;
-        e += is_e;
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t bit = (bits >> j) & 1u;
+            if (bit) *at = i + q * 256 + j;
+            at += bit;
+          }
+          out += (uint32_t)__builtin_amdgcn_readlane((int)inc, 63);
+        }
+        continue;
       }
+      n = (n | n << 8) & 0x00ff00ffu;
+      n = (n | n << 4) & 0x0f0f0f0fu;
+      n -= (n >> 1) & 0x05050505u;
+      n = (n & 0x03030303u) + ((n >> 2) & 0x03030303u);
+      const uint32_t front = wave_inclusive_scan(n) - n;
+      const uint32_t last = (uint32_t)__builtin_amdgcn_readlane((int)front, 63), own = (uint32_t)__builtin_amdgcn_readlane((int)n, 63);
+      uint32_t total = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (q < left) {
+          int32_t* at = stage + total + ((front >> (8 * q)) & 255u);
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            const uint32_t bit = (kept >> (4 * q + j)) & 1u;
+            if (bit) *at = i + q * 256 + j;
+            at += bit;
+          }
+          total += ((last >> (8 * q)) & 255u) + ((own >> (8 * q)) & 255u);
+        }
+      }
+      // (a wave's LDS operations are carried out in order: the compiler is all that has to keep it)
+      asm volatile("" ::: "memory");
+      for (uint32_t k = 4 * lane; k < total; k += 256) {
+        const i32x4 v = *reinterpret_cast<const i32x4*>(stage + k);
+        if (k + 4 <= total) {
+          *reinterpret_cast<i32x4_any*>(out + k) = i32x4_any{v[0], v[1], v[2], v[3]};
+        } else {
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            if (k + j < total) out[k + j] = v[j];
+        }
+      }
+      asm volatile("" ::: "memory");
+      out += total;
     }
   }
 }
@@ -165,18 +224,75 @@ __device__ __forceinline__ void pick_digit(const uint32_t (&cnt)[kPer], uint32_t
 }
 
 // ---------------------------------------------------------------------------------------------
-// Rows of up to kTopkRegMax scores: the workgroup keeps the row's keys in registers, so the row is read from memory once
-// and every radix pass runs on registers: 11, 11 and 10 bits of the raw key.  The first digit holds the sign, the exponent
-// and two bits of mantissa, so scores of a row hit a few dozen of its 2048 bins; eight copies of every bin side by side,
-// one per lane modulo eight, keep the lanes of a wave off each other's words.  (8-bit digits of the key's distance from
-// the row's smallest, a histogram per wave: 28 us of the kernel's 44 in the passes where scores change sign, since the
-// positive ones then share two or three bins.)  Wave w owns the scores [w * seg, (w + 1) * seg), seg = 256 * ceil(N / 4096):
-// a short row is one quad per thread in all waves, not 36 scores per thread in a few.
+// Rows whose keys stay in registers, so that the row is read from memory once and every radix digit runs on registers: 11, 11 and 10 bits
+// of the raw key.  The first digit holds the sign, the exponent and two bits of mantissa, so scores of a row hit a few dozen of its 2048
+// bins; eight copies of every bin side by side, one per lane modulo eight, keep the lanes of a wave off each other's words.  (8-bit
+// digits of the key's distance from the row's smallest, a histogram per wave: 28 us of the kernel's 44 in the passes where scores change
+// sign, since the positive ones then share two or three bins.)  Wave w owns the scores [w * seg, (w + 1) * seg),
+// seg = 256 * ceil(length / 4096): a short row is one quad per thread in all waves, not 36 scores per thread in a few.
+// What bounds it is the vector ALU (1 us per instruction and 150 000 keys of a CU) and the first digit's adds, which run while the loads
+// arrive; later digits look at a quad's four keys with one comparison.
+//
+// TEAM = false: a workgroup per row of up to kTopkRegMax scores (QUADS = 9 per thread).
+//
+// TEAM: longer rows, QUADS = 21, in parts, where all parts fit the chip at once, one workgroup per CU.  After counting a digit the workgroups
+// of a row meet: each leaves its histogram in scratch memory, waits until all have, and adds them up by itself.  112 rows of
+// 170 000 scores: 66.7 us as five launches that read the scores three times, 50.7 so (20 until the first digit is counted, 19 for the
+// digits and their meetings, 10 for the write); 64 of 300 000 68.8 -> 51.7, 256 of 85 001 73.8 -> 51.5.
+// The wait ends whatever else the device runs: a workgroup whose others have not come within `patience` ticks of the constant clock
+// (another stream may hold their places) selects from the whole row by itself, every digit counted over the row as it
+// lies in memory, and goes on leaving what the others wait for.  The workgroups of a row follow each other eight apart in the launch, which
+// puts them on one XCD where workgroups go round the XCDs; nothing but the time depends on it.
+// Scratch memory: 16 words per row (arrivals per digit at [0], [1], [2]), cleared by a launch in front, then three histograms of 2048
+// words per part: one each, since a workgroup that goes on alone waits for nobody to have read the one before.
 // ---------------------------------------------------------------------------------------------
 constexpr int kTopkChunks = 9;                     // quads per thread
 constexpr int kTopkRegMax = kTopkChunks * kChunk;
 static_assert(kTopkRegMax == kTopkSingleMax, "kernels.hpp states the longest single-workgroup row");
+// Rows of up to two and five quads per thread have kernels of their own: 47 and 62 registers instead of 75 let two workgroups share a CU,
+// and a short row's has less code to fetch.  512 rows of 5000 / 20 000 scores 20.3 -> 17.4 and 31.6 -> 25.1 us, 256 of 2000 10.1 -> 9.6.
+constexpr int kShortChunks = 2, kMidChunks = 5;
 constexpr int kRegCopies = 8;
+
+constexpr int kTeamQuads = 21, kTeamPartMax = kTeamQuads * kChunk;
+// Workgroups in all, one per CU (what is left over would start when the first are done), and of a row; scores of a part and rows for which
+// it pays: every workgroup reads the others' histograms, so fewer and longer parts meet faster, and with few rows most of the chip
+// would wait either way.  Teams / five launches, us: 28 rows of 40 000 24.3 / 24.9, of 56 000 25.4 (28.1 in parts of 8192) / 25.7, 32 of 160 000
+// 31.3 / 35.1, 64 of 100 000 31.1 / 35.7; 16 of 60 000 25.1 / 24.2, 24 of 60 000 25.5 / 24.8, 4 of 120 000 27.7 / 23.9.
+constexpr int kTeamPlaces = 256, kTeamMost = 8, kTeamPartLeast = 16384, kTeamLeastRows = 28;
+constexpr int kTeamGroup = 8;                        // rows whose workgroups alternate
+constexpr int kTeamStateWords = 16, kTeamPartWords = 3 * 2048;
+
+struct TeamArgs {
+  int rows, parts, part_len;
+  uint32_t* scratch;
+  unsigned long long patience;
+};
+
+__global__ __launch_bounds__(256) void team_init_kernel(uint32_t* __restrict__ scratch, int words) {
+  const int i = (int)blockIdx.x * 256 + threadIdx.x;
+  if (i < words) scratch[i] = 0u;
+}
+
+// bits = 2 bits + (a > b), and with a == b
+__device__ __forceinline__ void shift_in_above(uint32_t& bits, uint32_t a, uint32_t b) {
+  asm("v_cmp_gt_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(a), "v"(b) : "vcc");
+}
+__device__ __forceinline__ void shift_in_equal(uint32_t& bits, uint32_t a, uint32_t b) {
+  asm("v_cmp_eq_u32 vcc, %1, %2\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(bits) : "v"(a), "v"(b) : "vcc");
+}
+
+// the thread's two bins, 2047 - 2 t and 2046 - 2 t, over the copies; clears them for the next digit, whose adds lie a barrier ahead
+__device__ __forceinline__ void take_bins(uint32_t* hist, int tid, uint32_t (&cnt)[2]) {
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    u32x4* h = reinterpret_cast<u32x4*>(hist + (2047 - (tid * 2 + i)) * kRegCopies);
+    const u32x4 a = h[0], b = h[1];
+    h[0] = u32x4{0, 0, 0, 0};
+    h[1] = u32x4{0, 0, 0, 0};
+    cnt[i] = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
+  }
+}
 
 // Ordered gather of the token rows a workgroup has just selected (the mask applied to the target's cache, Sec. 4.3):
 // dst[j, :] = src[list[j], :] for j in [j_lo, j_hi), K and V together.  `list` was written by this workgroup before
@@ -217,110 +333,241 @@ __device__ __forceinline__ void gather_rows(const GatherArgs& ga, size_t in_base
   }
 }
 
-template <bool GATHER>
-__global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __restrict__ scores, int N, int K,
-                                                                int32_t* __restrict__ idx_out, GatherArgs ga) {
-  const float* row = scores + (size_t)blockIdx.x * N;
-  int32_t* out = idx_out + (size_t)blockIdx.x * K;
+template <int QUADS, bool TEAM, bool GATHER>
+__global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __restrict__ scores, int N, int K, int32_t* __restrict__ idx_out,
+                                                                GatherArgs ga, TeamArgs ta) {
+  const int b = blockIdx.x, parts = TEAM ? ta.parts : 1;
+  const int r = TEAM ? b / (kTeamGroup * parts) * kTeamGroup + b % kTeamGroup : b, part = TEAM ? b / kTeamGroup % parts : 0;
+  if (TEAM && r >= ta.rows) return;
+  const float* row = scores + (size_t)r * N;
+  int32_t* out = idx_out + (size_t)r * K;
+  uint32_t* state = TEAM ? ta.scratch + (size_t)r * kTeamStateWords : nullptr;
+  uint32_t* team = TEAM ? ta.scratch + (size_t)ta.rows * kTeamStateWords + (size_t)r * parts * kTeamPartWords : nullptr;
   __shared__ __attribute__((aligned(16))) uint32_t hist[2048 * kRegCopies];
   __shared__ uint32_t wave_part[kTopkWaves], wave_eq[kTopkWaves];
-  __shared__ uint32_t s_prefix, s_krem;
+  __shared__ uint32_t s_prefix, s_krem, s_came;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const int seg = (N + kChunk - 1) / kChunk * 256, s0 = wave * seg;
-  const int left = N - s0 < seg ? N - s0 : seg, quads = left > 0 ? (left + 255) / 256 : 0;  // the wave's scores, and quads per lane
-  const int i0 = s0 + 4 * lane;  // index of the thread's first quad; the next ones follow 256 apart
+  const int lo = TEAM ? part * ta.part_len : 0, len = TEAM && N - lo > ta.part_len ? ta.part_len : N - lo;
+  const int seg = (len + kChunk - 1) / kChunk * 256, s0 = wave * seg;
+  const int left = len - s0 < seg ? len - s0 : seg, quads = left > 0 ? (left + 255) / 256 : 0;  // the wave's scores, and quads per lane
+  const int i0 = s0 + 4 * lane;  // index in the part of the thread's first quad; the next ones follow 256 apart
 
-#pragma unroll
-  for (int i = 0; i < 2048 * kRegCopies / 4 / kTopkThreads; ++i) reinterpret_cast<u32x4*>(hist)[tid + i * kTopkThreads] = u32x4{0, 0, 0, 0};
-
-  // keys of this thread's scores; those at and past N hold a key that no score has (the largest, +inf's, is 0xff800000)
+  // keys of this thread's scores; those at and past the end hold a key that no score has (the largest, +inf's, is 0xff800000)
   constexpr uint32_t kNoKey = 0xffffffffu;
-  uint32_t key[kTopkChunks][4];
-  f32x4 v[kTopkChunks];
-  if (N < 4) {
+  // (of 21 quads per thread 16 stay in registers and five go to LDS: all in registers, 48 of the 128 were spilled)
+  constexpr int kRegQuads = QUADS < 16 ? QUADS : 16;
+  __shared__ u32x4 stash[QUADS > kRegQuads ? (QUADS - kRegQuads) * kTopkThreads : 1];
+  uint32_t reg_key[kRegQuads][4];
+  auto set_quad = [&](int c, const u32x4& k) __attribute__((always_inline)) {
+    if (c < kRegQuads) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) reg_key[c][j] = k[j];
+    } else {
+      stash[(c - kRegQuads) * kTopkThreads + tid] = k;
+    }
+  };
+  auto quad = [&](int c) __attribute__((always_inline)) {
+    return c < kRegQuads ? u32x4{reg_key[c][0], reg_key[c][1], reg_key[c][2], reg_key[c][3]} : stash[(c - kRegQuads) * kTopkThreads + tid];
+  };
+  f32x4 v[QUADS];
+  if (!TEAM && N < 4) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) v[0][j] = row[j < N ? j : 0];
   } else {
 #pragma unroll
-    for (int c = 0; c < kTopkChunks; ++c)
-      if (c < quads) v[c] = load_quad(row, i0 + c * 256, N);
+    for (int c = 0; c < QUADS; ++c)
+      if (c < quads) v[c] = load_quad(row + lo, i0 + c * 256, len);
   }
 #pragma unroll
-  for (int c = 0; c < kTopkChunks; ++c)
-    if (c < quads) {
-      if (left < (c + 1) * 256 && N >= 4) v[c] = shift_quad(v[c], quad_shift(i0 + c * 256, N));
-#pragma unroll
-      for (int j = 0; j < 4; ++j) key[c][j] = i0 + c * 256 + j < N ? order_key(v[c][j]) : kNoKey;
-    }
-  __syncthreads();
+  for (int i = 0; i < 2048 * kRegCopies / 4 / kTopkThreads; ++i) reinterpret_cast<u32x4*>(hist)[tid + i * kTopkThreads] = u32x4{0, 0, 0, 0};
+  // (a barrier that does not wait for the scores)
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
   uint32_t* mine = hist + (lane & (kRegCopies - 1));
-  uint32_t prefix = 0, krem = (uint32_t)K;
-#pragma unroll 1
-  for (int hi_bit = 32; hi_bit > 0; hi_bit -= 11) {  // 11, 11 and 10 bits; rolled, like everything that runs once per wave
-    const int shift = hi_bit > 11 ? hi_bit - 11 : 0;
-    const uint32_t dmask = (1u << (hi_bit - shift)) - 1u;
-    const uint32_t high = hi_bit == 32 ? 0u : ~0u << hi_bit, want = hi_bit == 32 ? 0u : prefix << hi_bit;
+  // the first digit's adds go with the keys, as the loads arrive
 #pragma unroll
-    for (int c = 0; c < kTopkChunks; ++c)
-      if (c < quads) {
+  for (int c = 0; c < QUADS; ++c)
+    if (c < quads) {
+      u32x4 k;
+      if (left >= (c + 1) * 256) {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const uint32_t k = key[c][j];
-          if ((k & high) == want) atomicAdd(&mine[((k >> shift) & dmask) * kRegCopies], 1u);
+          k[j] = order_key(v[c][j]);
+          atomicAdd(&mine[(k[j] >> 21) * kRegCopies], 1u);
+        }
+      } else {
+        if (TEAM || N >= 4) v[c] = shift_quad(v[c], quad_shift(i0 + c * 256, len));
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const bool is = i0 + c * 256 + j < len;
+          k[j] = is ? order_key(v[c][j]) : kNoKey;
+          if (is) atomicAdd(&mine[(k[j] >> 21) * kRegCopies], 1u);
         }
       }
-    __syncthreads();
-    uint32_t cnt[2];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {  // the thread's bins, which it clears for the next pass (whose adds lie two barriers ahead)
-      u32x4* h = reinterpret_cast<u32x4*>(hist + (2047 - (tid * 2 + i)) * kRegCopies);
-      const u32x4 a = h[0], b = h[1];
-      h[0] = u32x4{0, 0, 0, 0};
-      h[1] = u32x4{0, 0, 0, 0};
-      cnt[i] = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
+      set_quad(c, k);
     }
-    if (hi_bit == 32 && tid == 0) cnt[0] = 0;  // kNoKey's bin
-    pick_digit<2048, 2>(cnt, krem, wave_part, tid, [&](uint32_t d, uint32_t left, uint32_t) {
-      s_prefix = prefix << (hi_bit - shift) | d;
-      s_krem = left;
+
+  uint32_t prefix = 0, krem = (uint32_t)K;
+  uint32_t g = 0, e = 0;  // of the parts in front: keys above T, and equal to it (summed over threads)
+  bool alone = false;
+  uint32_t alone_T = 0, alone_take = 0;
+#pragma unroll 1
+  for (int digit = 0; digit < 3; ++digit) {  // rolled, like everything that runs once per wave
+    const int shift = digit == 0 ? 21 : (digit == 1 ? 10 : 0), bits = digit == 2 ? 10 : 11;
+    if (digit > 0) {
+      const uint32_t from = prefix << (shift + bits), span = 1u << (shift + bits);
+#pragma unroll
+      for (int c = 0; c < QUADS; ++c)
+        if (c < quads) {
+          const u32x4 t = quad(c) - from;
+          const uint32_t a = t[0] < t[1] ? t[0] : t[1], z = t[2] < t[3] ? t[2] : t[3];
+          if ((a < z ? a : z) < span) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+              if (t[j] < span) atomicAdd(&mine[(t[j] >> shift) * kRegCopies], 1u);
+          }
+        }
+    }
+    __syncthreads();
+    uint32_t cnt[2], front[2] = {0, 0};
+    take_bins(hist, tid, cnt);
+    if constexpr (TEAM) {
+      uint64_t* own = reinterpret_cast<uint64_t*>(team + (size_t)part * kTeamPartWords + digit * 2048);
+      __hip_atomic_store(own + tid, (uint64_t)cnt[1] << 32 | cnt[0], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // every wave's words are where all meet before the arrival counts (see mw_pass_kernel)
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (tid == 0) {
+        atomicAdd(&state[digit], 1u);
+        uint32_t came = 1;
+        if (!alone) {
+          const unsigned long long start = __builtin_amdgcn_s_memrealtime();
+          while (__hip_atomic_load(&state[digit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)parts) {
+            if (__builtin_amdgcn_s_memrealtime() - start >= ta.patience) {
+              came = 0;
+              break;
+            }
+            __builtin_amdgcn_s_sleep(1);
+          }
+        }
+        s_came = came;
+      }
+      __syncthreads();
+      if (!alone && !s_came) {
+        alone = true;
+        alone_take = (uint32_t)K;
+        g = e = 0;  // what the digits before gave is counted again below
+#pragma unroll 1
+        for (int d = 0; d < 3; ++d) {
+          const int sh = d == 0 ? 21 : (d == 1 ? 10 : 0), n = d == 2 ? 10 : 11;
+          for (int i = tid; i < N; i += kTopkThreads) {
+            const uint32_t k = order_key(row[i]);
+            if (d == 0 || k >> ((sh + n) & 31) == alone_T) atomicAdd(&mine[((k >> sh) & ((1u << n) - 1u)) * kRegCopies], 1u);
+          }
+          __syncthreads();
+          uint32_t all[2];
+          take_bins(hist, tid, all);
+          pick_digit<2048, 2>(all, alone_take, wave_part, tid, [&](uint32_t found, uint32_t rest, uint32_t) {
+            s_prefix = alone_T << n | found;
+            s_krem = rest;
+          });
+          __syncthreads();
+          alone_T = s_prefix;
+          alone_take = s_krem;
+          __syncthreads();
+        }
+      }
+      if (alone) {
+        prefix = alone_T >> shift;
+        krem = alone_take;
+        continue;
+      }
+      for (int q = 0; q < parts; ++q) {
+        if (q == part) continue;
+        const uint64_t* theirs = reinterpret_cast<const uint64_t*>(team + (size_t)q * kTeamPartWords + digit * 2048);
+        const uint64_t two = __hip_atomic_load(theirs + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        cnt[0] += (uint32_t)two;
+        cnt[1] += (uint32_t)(two >> 32);
+        front[0] += q < part ? (uint32_t)two : 0u;
+        front[1] += q < part ? (uint32_t)(two >> 32) : 0u;
+      }
+    }
+    pick_digit<2048, 2>(cnt, krem, wave_part, tid, [&](uint32_t d, uint32_t rest, uint32_t) {
+      s_prefix = prefix << bits | d;
+      s_krem = rest;
     });
     __syncthreads();
     prefix = s_prefix;
     krem = s_krem;
+    if constexpr (TEAM) {
+      const int d = (int)(prefix & ((1u << bits) - 1u));
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int bin = 2047 - (tid * 2 + i);
+        g += bin > d ? front[i] : 0u;
+        if (digit == 2) e += bin == d ? front[i] : 0u;
+      }
+    }
   }
   const uint32_t T = prefix, eq_take = krem;
 
-  // kept: keys above T, and the eq_take lowest-index keys equal to T
-  uint64_t m_gt = 0, m_eq = 0;
+  // kept: keys above T, and the eq_take lowest-index keys equal to T; eight quads' bits to a word, the first key's lowest
+  constexpr int kWords = (QUADS + 7) / 8;
+  uint32_t m_gt[kWords], m_eq[kWords], n_gt = 0, n_eq = 0;
 #pragma unroll
-  for (int c = 0; c < kTopkChunks; ++c)
-    if (c < quads) {
-      uint32_t bg = 0, be = 0;
+  for (int w = 0; w < kWords; ++w) {
+    m_gt[w] = m_eq[w] = 0;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        bg |= (uint32_t)(key[c][j] > T && key[c][j] != kNoKey) << j;
-        be |= (uint32_t)(key[c][j] == T) << j;
+    for (int c = 8 * w; c < 8 * w + 8; ++c) {
+      uint32_t above = 0, equal = 0;
+      if (c < QUADS && c < quads) {
+        const u32x4 k = quad(c);
+#pragma unroll
+        for (int j = 3; j >= 0; --j) {
+          shift_in_above(above, k[j], T);
+          shift_in_equal(equal, k[j], T);
+        }
+        if (left < (c + 1) * 256) {
+          const int n = len - (i0 + c * 256);
+          above &= n >= 4 ? 15u : (n > 0 ? (1u << n) - 1u : 0u);
+        }
       }
-      m_gt |= (uint64_t)bg << (4 * c);
-      m_eq |= (uint64_t)be << (4 * c);
+      m_gt[w] |= above << (4 * (c % 8));
+      m_eq[w] |= equal << (4 * (c % 8));
     }
-  const uint32_t n_gt = wave_total((uint32_t)__popcll(m_gt)), n_eq = wave_total((uint32_t)__popcll(m_eq));
+    n_gt += (uint32_t)__popc(m_gt[w]);
+    n_eq += (uint32_t)__popc(m_eq[w]);
+  }
+  n_gt = wave_total(n_gt);
+  n_eq = wave_total(n_eq);
+  uint32_t gt = 0, eq = 0;  // in front of the wave's scores
+  if constexpr (TEAM) {
+    if (alone) {
+      for (int i = tid; i < lo; i += kTopkThreads) {
+        const uint32_t k = order_key(row[i]);
+        g += k > T;
+        e += k == T;
+      }
+    }
+    __syncthreads();
+    gt = block_sum(g, wave_part, tid);
+    eq = block_sum(e, wave_part, tid);
+  }
   if (lane == 0) {
     wave_part[wave] = n_gt;
     wave_eq[wave] = n_eq;
   }
   __syncthreads();
-  uint32_t gt = 0, eq = 0;  // in front of the wave's scores
 #pragma unroll
   for (int w = 0; w < kTopkWaves; ++w) {
     gt += w < wave ? wave_part[w] : 0u;
     eq += w < wave ? wave_eq[w] : 0u;
   }
-  wave_write(m_gt, m_eq, quads, gt, eq, eq_take, s0, lane, out);
+  static_assert(2048 * kRegCopies >= kTopkWaves * kStageWords, "the histogram's place");
+  wave_write(m_gt, m_eq, quads, gt, eq, eq_take, lo + s0, lane, reinterpret_cast<int32_t*>(hist) + wave * kStageWords, out);
   if constexpr (GATHER) {
     __syncthreads();  // the row's list is complete and visible to the whole workgroup
-    gather_rows(ga, (size_t)blockIdx.x * N * ga.cpr, (size_t)blockIdx.x * K * ga.cpr, out, 0, K, tid);
+    gather_rows(ga, (size_t)r * N * ga.cpr, (size_t)r * K * ga.cpr, out, 0, K, tid);
   }
 }
 
@@ -545,6 +792,7 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
   const uint32_t* rs = scratch + (size_t)blockIdx.y * row_words;
   int32_t* out = idx_out + (size_t)blockIdx.y * K;
   __shared__ uint32_t wave_part[kTopkWaves], wave_eq[kTopkWaves];
+  __shared__ __attribute__((aligned(16))) int32_t stage[kTopkWaves * kStageWords];
   const int lo = part * part_len, len = N - lo < part_len ? N - lo : part_len;
   row += lo;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -605,7 +853,8 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
     gt_end += a;
     eq_end += b;
   }
-  wave_write(m_gt, m_eq, quads, gt, eq, eq_take, lo + s0, lane, out);
+  const uint32_t w_gt[2] = {(uint32_t)m_gt, (uint32_t)(m_gt >> 32)}, w_eq[2] = {(uint32_t)m_eq, (uint32_t)(m_eq >> 32)};
+  wave_write(w_gt, w_eq, quads, gt, eq, eq_take, lo + s0, lane, stage + wave * kStageWords, out);
   if constexpr (GATHER) {
     __syncthreads();  // this part's stretch of the list is complete and visible to the whole workgroup
     gather_rows(ga, (size_t)blockIdx.y * N * ga.cpr, (size_t)blockIdx.y * K * ga.cpr, out,
@@ -613,6 +862,19 @@ __global__ __launch_bounds__(kTopkThreads, 8) void mw_write_kernel(const float* 
                 (int)(gt_end + (eq_end < eq_take ? eq_end : eq_take)), tid);
   }
 }
+
+// Parts of a row for the register kernel's teams: as many as the chip has places for, none longer than its registers take; 0 where there are not
+// places enough.
+static int team_parts(int64_t rows, int64_t N) {
+  const int64_t least = (N + kTeamPartMax - 1) / kTeamPartMax;
+  if (rows < kTeamLeastRows || rows * least > kTeamPlaces || least > kTeamMost) return 0;
+  int64_t parts = kTeamPlaces / rows;
+  const int64_t most = (N + kTeamPartLeast - 1) / kTeamPartLeast;
+  if (parts > most) parts = most;
+  if (parts > kTeamMost) parts = kTeamMost;
+  return (int)(parts > least ? parts : least);
+}
+static size_t team_scratch(int64_t rows, int parts) { return (size_t)rows * (kTeamStateWords + (size_t)parts * kTeamPartWords) * 4; }
 
 }  // namespace
 
@@ -677,25 +939,47 @@ static hipError_t launch_topk_split(const float* scores, int64_t rows, int64_t N
   return hipGetLastError();
 }
 
+static hipError_t launch_topk_team(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch, int most_parts,
+                                   unsigned long long patience, hipStream_t stream) {
+  const int part_len = (int)((((N + most_parts - 1) / most_parts) + 3) & ~(int64_t)3);
+  const int parts = (int)((N + part_len - 1) / part_len);
+  const int words = (int)rows * kTeamStateWords;
+  team_init_kernel<<<(unsigned)((words + 255) / 256), 256, 0, stream>>>((uint32_t*)scratch, words);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const GatherArgs none = {nullptr, nullptr, nullptr, nullptr, 0};
+  const TeamArgs ta = {(int)rows, parts, part_len, (uint32_t*)scratch, patience};
+  topk_reg_kernel<kTeamQuads, true, false><<<(unsigned)((rows + kTeamGroup - 1) / kTeamGroup * kTeamGroup * parts), kTopkThreads, 0, stream>>>(
+      scores, (int)N, (int)K, idx_out, none, ta);
+  return hipGetLastError();
+}
+
 // gather != nullptr: every workgroup also gathers the token rows it selected (k/v in [rows, N, row_bytes], out [rows, K, row_bytes])
 static hipError_t launch_topk_impl(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
-                                   size_t scratch_bytes, const GatherArgs* gather, hipStream_t stream) {
+                                   size_t scratch_bytes, const GatherArgs* gather, unsigned long long patience, hipStream_t stream) {
   if (rows <= 0) return hipSuccess;
   if (N <= kTopkRegMax) {
     const GatherArgs none = {nullptr, nullptr, nullptr, nullptr, 0};
-    if (gather) topk_reg_kernel<true><<<dim3((unsigned)rows), kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, idx_out, *gather);
-    else topk_reg_kernel<false><<<dim3((unsigned)rows), kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, idx_out, none);
+    const TeamArgs no_team = {0, 1, 0, nullptr, 0};
+    if (gather) topk_reg_kernel<kTopkChunks, false, true><<<dim3((unsigned)rows), kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, idx_out, *gather, no_team);
+    else if (N <= kShortChunks * kChunk) topk_reg_kernel<kShortChunks, false, false><<<dim3((unsigned)rows), kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, idx_out, none, no_team);
+    else if (N <= kMidChunks * kChunk) topk_reg_kernel<kMidChunks, false, false><<<dim3((unsigned)rows), kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, idx_out, none, no_team);
+    else topk_reg_kernel<kTopkChunks, false, false><<<dim3((unsigned)rows), kTopkThreads, 0, stream>>>(scores, (int)N, (int)K, idx_out, none, no_team);
     return hipGetLastError();
   }
   if (scratch == nullptr || rows > 65535) return hipErrorInvalidValue;
+  if (!gather) {
+    const int want = team_parts(rows, N);
+    if (want > 0 && scratch_bytes >= team_scratch(rows, want)) return launch_topk_team(scores, rows, N, K, idx_out, scratch, want, patience, stream);
+  }
   if (scratch_bytes >= topk_scratch<11>(rows, N)) return launch_topk_split<11>(scores, rows, N, K, idx_out, scratch, scratch_bytes, gather, stream);
   if (scratch_bytes >= topk_scratch<8>(rows, N)) return launch_topk_split<8>(scores, rows, N, K, idx_out, scratch, scratch_bytes, gather, stream);
   return hipErrorInvalidValue;
 }
 
 hipError_t launch_topk(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
-                       size_t scratch_bytes, hipStream_t stream) {
-  return launch_topk_impl(scores, rows, N, K, idx_out, scratch, scratch_bytes, nullptr, stream);
+                       size_t scratch_bytes, hipStream_t stream, unsigned long long patience) {
+  return launch_topk_impl(scores, rows, N, K, idx_out, scratch, scratch_bytes, nullptr, patience, stream);
 }
 
 hipError_t launch_topk_gather(const float* scores, int64_t rows, int64_t N, int64_t K, int32_t* idx_out, void* scratch,
@@ -703,7 +987,7 @@ hipError_t launch_topk_gather(const float* scores, int64_t rows, int64_t N, int6
                               hipStream_t stream) {
   const GatherArgs ga = {(const u32x4*)k_in, (const u32x4*)v_in, (u32x4*)k_out, (u32x4*)v_out, (int)(row_bytes / 16)};
   if (ga.cpr < 1 || ga.cpr > kTopkThreads || kTopkThreads % ga.cpr != 0) return hipErrorInvalidValue;
-  return launch_topk_impl(scores, rows, N, K, idx_out, scratch, scratch_bytes, &ga, stream);
+  return launch_topk_impl(scores, rows, N, K, idx_out, scratch, scratch_bytes, &ga, kTopkPatience, stream);
 }
 
 }  // namespace pkv

@@ -104,6 +104,39 @@ def test_topk_ties_nan_thresholds_and_odd_lengths(rows, N):
     pk.proxykv_destroy(ctx)
 
 
+def _topk_with_patience(scores, K, patience):
+    """The library's own launch of a Top-K, whose workgroups wait `patience` ticks of 10 ns for the others of their row."""
+    import ctypes
+    import re
+    import subprocess
+    names = subprocess.run(["nm", "-D", "--defined-only", pk.LIB_PATH], capture_output=True, text=True, check=True).stdout
+    launch = getattr(pk.load(), re.search(r"\S*11launch_topkE\S*", names)[0])
+    launch.argtypes = [ctypes.c_void_p] + [ctypes.c_int64] * 3 + [ctypes.c_void_p] * 2 + [ctypes.c_size_t, ctypes.c_void_p, ctypes.c_ulonglong]
+    rows, N = scores.shape
+    idx = torch.full((rows, K), -1, dtype=torch.int32, device="cuda")
+    scratch = torch.full((1 << 22,), 7, dtype=torch.int32, device="cuda")
+    assert launch(scores.data_ptr(), rows, N, K, idx.data_ptr(), scratch.data_ptr(), scratch.numel() * 4,
+                  torch.cuda.current_stream().cuda_stream, patience) == 0
+    torch.cuda.synchronize()
+    return idx.cpu()
+
+
+@pytest.mark.parametrize("patience", [0, 100, 20000])
+@pytest.mark.parametrize("rows,N", [(28, 36865), (29, 131073), (64, 98760), (85, 172033), (256, 86016), (32, 8 * 86016)])
+def test_topk_of_rows_that_workgroups_share(rows, N, patience):
+    """Rows cut into one part to eight whose workgroups meet after every digit (28 rows and more, parts that fit the chip at once); with no
+    patience, or 1 us of it, workgroups select from the whole row by themselves at one digit or another.  Ties across parts, NaN, infinities."""
+    g = torch.Generator().manual_seed(N)
+    base = 0.1 * torch.randn(3, N, generator=g)
+    base[1] = torch.round(base[1] * 30) / 30
+    base[2, torch.rand(N, generator=g) < 0.7] = float("nan")
+    base[2, ::11], base[2, 1::13], base[2, 2::17] = float("inf"), float("-inf"), -0.0
+    scores = base.repeat((rows + 2) // 3, 1)[:rows].contiguous().cuda()
+    for K in (1, N // 3, N - 1):
+        ref = oracle.topk(base, K).repeat((rows + 2) // 3, 1)[:rows]
+        assert torch.equal(_topk_with_patience(scores, K, patience).long(), ref.long()), (rows, N, K)
+
+
 def test_compact_bit_exact():
     ctx = _ctx(synth.CASES["tiny"])
     g = torch.Generator().manual_seed(3)
