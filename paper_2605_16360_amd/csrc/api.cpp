@@ -10,6 +10,9 @@
 #include "context.hpp"
 #include "kernels.hpp"
 
+// (a runtime that records no graphs need not have it)
+extern "C" hipError_t hipStreamIsCapturing(hipStream_t stream, hipStreamCaptureStatus* status) __attribute__((weak));
+
 using pkv::DeviceBuffer;
 
 namespace {
@@ -71,6 +74,14 @@ void free_lanes(proxykv_ctx* ctx) {
 }
 
 // `need`: the mapper's workspace is given up where that makes room
+// whether `stream` records a graph (or it cannot be told)
+bool capturing(hipStream_t stream) {
+  if (hipStreamIsCapturing == nullptr) return false;
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
 int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream, bool need = true) {
   if (bytes <= b.bytes) return PROXYKV_OK;
   if (b.ptr) {
@@ -236,6 +247,19 @@ int reserve_topk(proxykv_ctx* ctx, int64_t rows, int64_t N, hipStream_t stream) 
   if (rc == PROXYKV_ENOMEM) rc = ensure(ctx, ctx->topk_ws, pkv::topk_scratch_bytes_no_masks(rows, N), stream);
   if (rc == PROXYKV_ENOMEM) rc = ensure(ctx, ctx->topk_ws, least, stream);
   return rc;
+}
+// The in-place compaction's counters lie where the Top-K's do.  Where there is no memory for them, or a capture is under way, in which nothing can
+// be allocated, it does without.
+void reserve_inplace(proxykv_ctx* ctx, int64_t rows, int64_t K, int64_t row_bytes, int heads, hipStream_t stream) {
+  const size_t need = pkv::compact_inplace_scratch_bytes(rows, K, row_bytes, heads);
+  if (need > ctx->topk_ws.bytes && !capturing(stream)) (void)ensure(ctx, ctx->topk_ws, need, stream, false);
+}
+// ... for any number of kept tokens of this context's rows, with a budget per head or per layer
+size_t inplace_bytes(const proxykv_config& c, int64_t N) {
+  if (c.D * 2 > 512) return 0;  // not for proxykv_compact_inplace
+  const int64_t rows = (int64_t)c.L_l * c.H_l;
+  const size_t own = pkv::compact_inplace_scratch_bytes(rows, N, c.D * 2, 1), shared = pkv::compact_inplace_scratch_bytes(rows, N, c.D * 2, c.H_l);
+  return own > shared ? own : shared;
 }
 int reserve_prune(proxykv_ctx* ctx, int64_t N, hipStream_t stream) {
   const Sizes s = workspace_sizes(ctx->cfg, N, 1);
@@ -590,7 +614,8 @@ int proxykv_workspace_bytes(const proxykv_config* cfg, int64_t N, int64_t N_q, s
   const Sizes s = workspace_sizes(*cfg, N, N_q);
   const pkv::MapPlan p = pkv::map_plan(*cfg, N, distinct);
   const LaneBytes lb = lane_bytes(*cfg, p);
-  size_t total = s.neg_lse + s.x_parts + s.x_ws + s.yhat_ws + pkv::topk_scratch_bytes((int64_t)cfg->L_l * cfg->H_l, N);
+  const size_t topk = pkv::topk_scratch_bytes((int64_t)cfg->L_l * cfg->H_l, N), inplace = inplace_bytes(*cfg, N);
+  size_t total = s.neg_lse + s.x_parts + s.x_ws + s.yhat_ws + (topk > inplace ? topk : inplace);
   for (int lane = 0; lane < p.lanes; ++lane)
     for (int i = 0; i < kLaneBuffers; ++i) total += lane_need(*cfg, p, lb, lane, distinct, i);
   *out_bytes = total;
@@ -604,6 +629,7 @@ int proxykv_reserve(proxykv_ctx* ctx, int64_t N, int64_t N_q) {
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
   if ((rc = reserve_score(ctx, N, N_q, true, nullptr))) return rc;  // (proxykv_score_self has parts in any context)
   if ((rc = reserve_prune(ctx, N, nullptr))) return rc;
+  (void)ensure(ctx, ctx->topk_ws, inplace_bytes(ctx->cfg, N), nullptr, false);
   pkv::MapPlan p;
   return reserve_map(ctx, N, nullptr, &p);  // last: it makes do with what is left
 }
@@ -685,7 +711,8 @@ int proxykv_compact_inplace(proxykv_ctx* ctx, void* k, void* v, const int32_t* i
   if (rows <= 0 || N <= 0 || N >= (1ll << 31) || K < 1 || K > N || D <= 0) return PROXYKV_EINVAL;
   if ((D * 2) % 16 != 0 || D * 2 > 512) return PROXYKV_EUNSUPPORTED;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, idx, rows, N, K, D * 2, nullptr, 1, (hipStream_t)stream));
+  reserve_inplace(ctx, rows, K, D * 2, 1, (hipStream_t)stream);
+  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, idx, rows, N, K, D * 2, nullptr, 1, ctx->topk_ws.ptr, ctx->topk_ws.bytes, (hipStream_t)stream));
   return PROXYKV_OK;
 }
 
@@ -710,7 +737,8 @@ int proxykv_compact_pooled(proxykv_ctx* ctx, void* k, void* v, const int32_t* fl
   if (layers * heads >= (1ll << 31) || heads * N >= (1ll << 31) - 4096) return PROXYKV_EINVAL;
   if ((D * 2) % 16 != 0 || D * 2 > 512) return PROXYKV_EUNSUPPORTED;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, flat, layers * heads, N, K, D * 2, counts, (int)heads, (hipStream_t)stream));
+  reserve_inplace(ctx, layers * heads, K, D * 2, (int)heads, (hipStream_t)stream);
+  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, flat, layers * heads, N, K, D * 2, counts, (int)heads, ctx->topk_ws.ptr, ctx->topk_ws.bytes, (hipStream_t)stream));
   return PROXYKV_OK;
 }
 

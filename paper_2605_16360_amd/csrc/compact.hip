@@ -145,6 +145,124 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(u32x4* __restrict_
   }
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same in parts of a row that any number of workgroups move at once.  A workgroup takes kPartPieces pieces of 16 bytes (640 tokens of 256),
+// all of them into registers, and stores them when the parts in front of it in the row have been loaded: a token's new place never
+// lies behind its old one, so what a part's places still hold belongs to itself or to a part in front.  Parts are dealt by a
+// counter per layer and tensor, in order: whoever a workgroup waits for has started before it and waits for earlier ones only, so every wait
+// ends, whatever order the workgroups are launched in.  (The wait has a bound all the same, for a context that two
+// streams use at once, which races in any case.)
+// What bounds it is memory.  With workgroups of a whole row, two chunks of it in flight, a long row was what the launch waited for.  Half kept,
+// D = 128, us: 512 rows of 12 345 tokens 652 -> 548 (3.2 GB: 5.9 TB/s), with budgets that eight heads share 727 -> 567; 256 of 32 000, 0.3
+// kept, shared 756 -> 455; 112 of 8000 96 -> 87; 4 of 30 000 97 -> 16.
+// Parts of 160 KB, one workgroup on a CU; the first three also in us with 128 KB, two on a CU: 566, 574, 465; 256 KB: 548, 553, 442, but 256 rows
+// of 2200 64 instead of 57; 64 KB in eight pieces a thread 579, 641, 569.
+// state: per (layer, tensor) the counter, then a word per part, all zero at the start.  grid 2 * layers * (stride - 1).
+// ---------------------------------------------------------------------------------------------
+constexpr int kPartThreads = 512, kPartPer = 20, kPartPieces = kPartThreads * kPartPer;
+constexpr unsigned long long kPartPatience = 100000000;  // 1 s
+
+__global__ __launch_bounds__(256) void clear_words_kernel(uint32_t* __restrict__ words, int64_t n) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i < n) words[i] = 0u;
+}
+
+__device__ __forceinline__ int wave_scan(int v) {  // inclusive
+#pragma unroll
+  for (int off = 1; off < 64; off *= 2) {
+    const int o = __shfl_up(v, off, 64);
+    v += ((int)threadIdx.x & 63) >= off ? o : 0;
+  }
+  return v;
+}
+
+__global__ __launch_bounds__(kPartThreads, 3) void compact_parts_kernel(u32x4* __restrict__ k, u32x4* __restrict__ v, const int32_t* __restrict__ idx,
+                                                                     int64_t N, int K, int cpr, int part_tokens, const int32_t* __restrict__ counts,
+                                                                     int heads, uint32_t* __restrict__ state, int stride) {
+  __shared__ int32_t at[kPartPieces];
+  __shared__ int s_head, s_part, s_kept, s_start;
+  const int tid = threadIdx.x, lane = tid & 63, group = blockIdx.x / (stride - 1), layer = group >> 1;
+  uint32_t* mine = state + (size_t)group * stride;
+  uint32_t ticket = 0;
+  if (tid < 64) {
+    if (lane == 0) ticket = atomicAdd(mine, 1u);
+    ticket = (uint32_t)__builtin_amdgcn_readfirstlane((int)ticket);
+    // the head and part that this is, parts counted over the layer's heads
+    int part = (int)ticket, start = 0;
+    if (lane == 0) s_part = -1;
+    if (counts == nullptr) {
+      if (lane == 0 && part * (int64_t)part_tokens < K) {
+        s_head = 0;
+        s_part = part;
+        s_kept = K;
+        s_start = 0;
+      }
+    } else {
+      for (int h0 = 0; h0 < heads && part >= 0; h0 += 64) {
+        const int c = h0 + lane < heads ? counts[(size_t)layer * heads + h0 + lane] : 0;
+        const int parts = (c + part_tokens - 1) / part_tokens, upto = wave_scan(parts), kept = wave_scan(c);
+        if (part >= upto - parts && part < upto) {
+          s_head = h0 + lane;
+          s_part = part - (upto - parts);
+          s_kept = c;
+          s_start = start + kept - c;
+        }
+        part -= __shfl(upto, 63, 64);
+        start += __shfl(kept, 63, 64);
+      }
+    }
+  }
+  __syncthreads();
+  const int part = s_part, j0 = part * part_tokens;
+  if (part < 0) return;
+  const int n = s_kept - j0 < part_tokens ? s_kept - j0 : part_tokens;
+  const int32_t* list = idx + (size_t)layer * heads * K + s_start + j0;
+  const int32_t sub = (int32_t)(s_head * N);  // what a stored index is ahead of the row's token number
+  for (int i = tid; i < n; i += kPartThreads) at[i] = list[i] - sub;
+  __syncthreads();
+  u32x4* base = ((group & 1) ? v : k) + ((size_t)layer * heads + s_head) * N * cpr;
+  u32x4 x[kPartPer];
+  const int tok_step = kPartThreads / cpr, ch_step = kPartThreads % cpr;
+  {
+    int tok = tid / cpr, ch = tid % cpr;
+#pragma unroll
+    for (int u = 0; u < kPartPer; ++u) {  // (a piece without a token loads the last one's)
+      x[u] = __builtin_nontemporal_load(base + (size_t)at[tok < n ? tok : n - 1] * cpr + ch);
+      tok += tok_step;
+      ch += ch_step;
+      if (ch >= cpr) {
+        ch -= cpr;
+        ++tok;
+      }
+    }
+  }
+  // every thread's pieces have arrived: the part is loaded
+#pragma unroll
+  for (int u = 0; u < kPartPer; ++u) asm volatile("" : "+v"(x[u]));
+  __syncthreads();
+  if (tid < 64) {
+    uint32_t* loaded = mine + 1 + ticket;
+    if (lane == 0) __hip_atomic_store(loaded, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long begin = __builtin_amdgcn_s_memrealtime();
+    for (int p = lane; p < part; p += 64)
+      while (__hip_atomic_load(loaded - 1 - p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 &&
+             __builtin_amdgcn_s_memrealtime() - begin < kPartPatience)
+        __builtin_amdgcn_s_sleep(1);
+  }
+  __syncthreads();
+  int tok = tid / cpr, ch = tid % cpr;
+#pragma unroll
+  for (int u = 0; u < kPartPer; ++u) {
+    if (tok < n) __builtin_nontemporal_store(x[u], base + (size_t)(j0 + tok) * cpr + ch);
+    tok += tok_step;
+    ch += ch_step;
+    if (ch >= cpr) {
+      ch -= cpr;
+      ++tok;
+    }
+  }
+}
+
 // mask[r, n] = 1 for the kept tokens of row r, 0 elsewhere (uint8).  One workgroup per row clears the row,
 // then sets the kept positions: 1024 threads for rows that keep them busy (256 rows of 32 768: 9.2 us with 256, 5.4 us with
 // 1024; 512 rows of 3000: 1.9 and 3.1 us).
@@ -213,10 +331,37 @@ hipError_t launch_compact(const void* k_in, const void* v_in, const int32_t* idx
   return hipGetLastError();
 }
 
+// Parts that a layer's kept tokens (heads * K) can make, however its heads share them; 0 where a launch has no room for them.
+// Kept tokens per row, in parts, from which it pays: the launch that clears the state is in front, and what is left of a row fills its last
+// part badly.  Parts / whole rows, us: 256 rows that keep 1100 57 / 60, with shared budgets 60 / 70; 112 rows 27.5 / 26.8 and 32 / 36; 4 rows that
+// keep 1500 12.3 / 11.1; 256 rows of D = 64 that keep 1500 (1.2 parts) 44.6 / 42.0.
+static bool parts_pay(int64_t rows, int64_t K, int64_t row_bytes, int heads) {
+  return 2 * K >= (heads > 1 || rows >= 256 ? 3 : 6) * (kPartPieces / (row_bytes / 16));
+}
+static int64_t layer_parts(int64_t layers, int64_t K, int64_t row_bytes, int heads) {
+  const int64_t tokens = kPartPieces / (row_bytes / 16), parts = (heads * K + tokens - 1) / tokens + (heads > 1 ? heads - 1 : 0);
+  return 2 * layers * parts * kPartThreads <= kMaxThreads ? parts : 0;
+}
+size_t compact_inplace_scratch_bytes(int64_t rows, int64_t K, int64_t row_bytes, int heads) {
+  if (rows <= 0 || !parts_pay(rows, K, row_bytes, heads)) return 0;
+  const int64_t layers = rows / heads, parts = layer_parts(layers, K, row_bytes, heads);
+  return parts == 0 ? 0 : (size_t)(2 * layers * (parts + 1)) * 4;
+}
+
 hipError_t launch_compact_inplace(void* k, void* v, const int32_t* idx, int64_t rows, int64_t N, int64_t K, int64_t row_bytes,
-                                  const int32_t* counts, int heads, hipStream_t stream) {
+                                  const int32_t* counts, int heads, void* scratch, size_t scratch_bytes, hipStream_t stream) {
   if (rows <= 0 || K <= 0) return hipSuccess;
   const int cpr = (int)(row_bytes / 16);
+  const size_t need = compact_inplace_scratch_bytes(rows, K, row_bytes, heads);
+  if (need > 0 && scratch_bytes >= need) {
+    const int64_t layers = rows / heads, parts = layer_parts(layers, K, row_bytes, heads), words = (int64_t)(need / 4);
+    clear_words_kernel<<<(unsigned)((words + 255) / 256), 256, 0, stream>>>((uint32_t*)scratch, words);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    compact_parts_kernel<<<(unsigned)(2 * layers * parts), kPartThreads, 0, stream>>>((u32x4*)k, (u32x4*)v, idx, N, (int)K, cpr, kPartPieces / cpr,
+                                                                                     counts, heads, (uint32_t*)scratch, (int)parts + 1);
+    return hipGetLastError();
+  }
   // 128-byte parts of a token where it divides into them, and 256-byte ones where K and V of the rows alone give every CU two workgroups
   // (D = 128, 128-byte and 256-byte parts, us: 512 rows of 12 345 tokens, half kept, 697 and 680; 256 of 2000, 0.8 kept, 78 and 76, of
   // 5000 with shared budgets, 0.3 kept, 139 and 128; but 112 of 2000 49 and 51, of 21 718 with shared budgets, 0.145 kept, 144 and 150: a long

@@ -216,6 +216,45 @@ def test_compact_inplace_at_the_edges_of_chunks_of_many_rows(D, rows):
     _check_compact_inplace(D, rows, (1, 128, 257, 512, 513, 639, 640, 641))
 
 
+@pytest.mark.parametrize("D,rows,counts", [(128, 3, (1919, 1920, 1921, 2560, 3201)), (128, 256, (960, 1281)), (256, 2, (959, 960, 961, 2000)),
+                                           (72, 2, (3411, 3412, 4549)), (8, 1, (30720, 30721)), (64, 256, (1919, 1920, 1921))])
+def test_compact_inplace_in_parts_of_a_row(D, rows, counts):
+    """Rows long enough for several workgroups: a part takes 10 240 pieces of 16 bytes (640 tokens at D = 128, 1137 and seven pieces over at D = 72);
+    kept counts at the line and around whole parts."""
+    _check_compact_inplace(D, rows, counts)
+
+
+def test_compact_inplace_in_a_graph_and_in_a_context_without_memory():
+    """Under capture nothing can be allocated: a context that has its counters replays parts, one that does not whole rows; both as eagerly."""
+    g = torch.Generator().manual_seed(5)
+    rows, N, K, D = 4, 5000, 3000, 128
+    idx = torch.stack([torch.randperm(N, generator=g)[:K].sort().values for _ in range(rows)]).to(torch.int32).view(1, rows, K).cuda()
+    src = torch.randn(2, 1, rows, N, D, generator=g).to(torch.bfloat16).cuda()
+    want = torch.gather(src, 3, idx.long().unsqueeze(0).unsqueeze(4).expand(2, -1, -1, -1, D))
+    for warm in (False, True):
+        ctx = _ctx(synth.CASES["tiny"])
+        if warm:
+            pk.proxykv_compact_inplace(ctx, src[0].clone(), src[1].clone(), idx)
+        kv = src.clone()
+        torch.cuda.synchronize()
+        stream = torch.cuda.Stream()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            pk.proxykv_compact_inplace(ctx, kv[0], kv[1], idx)
+        for _ in range(3):
+            kv.copy_(src)
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(kv[:, :, :, :K], want) and torch.equal(kv[:, :, :, K:], src[:, :, :, K:]), warm
+        del graph
+        pk.proxykv_destroy(ctx)
+
+
+def test_pooled_compaction_of_many_heads_in_parts():
+    """More heads than a wave's lanes deal parts to, with heads that keep nothing and heads that keep all; budgets of several parts each."""
+    _check_pooled([(2, 70, 2000, 64, 1900), (1, 130, 1500, 128, 1000), (3, 2, 4000, 128, 1500)], nothing=slice(None))
+
+
 def _check_compact_inplace(D, rows, counts):
     ctx = _ctx(synth.CASES["tiny"])
     g = torch.Generator().manual_seed(D)
