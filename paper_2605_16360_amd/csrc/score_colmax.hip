@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
   static_assert(NCOL % 2 == 0, "column sub-tiles are processed in pairs");
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
   __shared__ __attribute__((aligned(16))) float lds_nl[kNBuf * C::ROWS];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, quad = lane >> 4;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, quad = lane >> 4;
   constexpr int KB = 128 * NCOL;
   const int H_kv = H_q / G;
   // a group's blocks: its key blocks (they stream the same queries), each in q_splits parts
@@ -132,6 +132,14 @@ __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(con
     runmax[pp * 4 + ct] = max3f(runmax[pp * 4 + ct], pend[rt][ct][e], pend[rt][ct][e + 1]);
   };
   constexpr int NP = NCOL / 2;  // pairs per sub-tile
+  if (n0 + wave * NT * 16 >= N) {  // a wave without a key helps with the tiles only
+    for (int t = 0; t < total; ++t) {
+      __syncthreads();
+      if (t + 2 < total) store(t + 2);
+      if (t + 3 < total) fetch_next();
+    }
+    return;
+  }
   for (int t = 0; t < total; ++t) {
     static_for<C::SUB * NP>([&](auto ic) {
       constexpr int i = decltype(ic)::value, s = i / NP, pr = i % NP;
@@ -203,7 +211,7 @@ __global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void sc
   using Acc = typename R::Acc;
   __shared__ u32x4 lds[kNBuf * C::TILE_U4];
   __shared__ __attribute__((aligned(16))) float lds_nl[kNBuf * C::ROWS];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, rows4 = lane / W * 4;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, rows4 = lane / W * 4;
   constexpr int KB = 128 * NCOL;
   const int H_kv = H_q / G;
   // a group's blocks: its key blocks (they stream the same queries), each in q_splits parts
@@ -275,12 +283,14 @@ __global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void sc
   __builtin_amdgcn_s_waitcnt(kVmcnt0);  // the resident keys have landed: no tile waits for them (see score_lse.hip)
   if (total > 2) fetch_next();
 
+  const bool idle = n0 + wave * NCOL * 32 >= N;  // a wave without a key helps with the tiles only
   int cqt = qt_first + first % nqg;  // query tile of step t
   for (int t = 0; t < total; ++t) {
     // every wave has finished tile t-1: its buffer takes tile t+2, the registers take tile t+3
     __syncthreads();
     if (t + 2 < total) store(t + 2);
     if (t + 3 < total) fetch_next();
+    if (idle) continue;
     const u32x4* buf = lds + (t % kNBuf) * C::TILE_U4;
     const float* nl = lds_nl + (t % kNBuf) * C::ROWS;
     const int row0 = cqt * C::ROWS;
