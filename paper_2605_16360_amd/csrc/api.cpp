@@ -319,6 +319,7 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
                int64_t N_q, int32_t chunk, float* x_out, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const uint16_t *q = (const uint16_t*)q_rec, *kc = (const uint16_t*)k_ctx, *kr = (const uint16_t*)k_rec;
+  const bool rounds = dtype == PROXYKV_FP32 && pkv::score_rounds_itself(c.L_s, c.H_q, c.d, N, N_q);
   int rc;
   if (dtype == PROXYKV_FP32) {
     const size_t nq = (size_t)c.L_s * c.H_q * (size_t)N_q * c.d, nkc = (size_t)c.L_s * c.H_kv * (size_t)N * c.d,
@@ -329,7 +330,7 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
     const float* const in[3] = {(const float*)q_rec, (const float*)k_ctx, (const float*)k_rec};
     uint16_t* const out[3] = {(uint16_t*)ctx->q_bf16.ptr, (uint16_t*)ctx->kctx_bf16.ptr, (uint16_t*)ctx->krec_bf16.ptr};
     const int64_t n[3] = {(int64_t)nq, (int64_t)nkc, (int64_t)nkr};
-    PKV_HIP(ctx, pkv::launch_f32_to_bf16(in, out, n, stream));
+    if (!rounds) PKV_HIP(ctx, pkv::launch_f32_to_bf16(in, out, n, stream));
     q = (const uint16_t*)ctx->q_bf16.ptr;
     kc = (const uint16_t*)ctx->kctx_bf16.ptr;
     kr = (const uint16_t*)ctx->krec_bf16.ptr;
@@ -342,7 +343,11 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N_q);
   const int q_splits = query_splits(ctx, sum, false, N, N_q);
   const int64_t n_clear = !sum && (splits > 1 || q_splits > 1) ? (int64_t)c.L_s * c.H_kv * N : 0;
-  PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, splits, x_out, n_clear, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
+  if (rounds)
+    PKV_HIP(ctx, pkv::launch_score_lse_fp32((const float*)q_rec, (const float*)k_ctx, (const float*)k_rec, nl, splits, x_out, n_clear,
+                                            (uint16_t*)ctx->q_bf16.ptr, (uint16_t*)ctx->kctx_bf16.ptr, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
+  else
+    PKV_HIP(ctx, pkv::launch_score_lse(q, kc, kr, nl, splits, x_out, n_clear, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, chunk, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
   if (sum)
     PKV_HIP(ctx, pkv::launch_score_colsum(q, kc, nl, splits, x_out, (float*)ctx->x_parts.ptr, q_splits, c.L_s, c.H_q, c.H_kv, c.d, N, N_q, false, stream));
@@ -358,6 +363,7 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
                     hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const uint16_t *q = (const uint16_t*)q_in, *k = (const uint16_t*)k_in;
+  const bool rounds = dtype == PROXYKV_FP32 && pkv::score_rounds_itself(c.L_s, c.H_q, c.d, N, N);
   int rc;
   if (dtype == PROXYKV_FP32) {
     const size_t nq = (size_t)c.L_s * c.H_q * (size_t)N * c.d, nk = (size_t)c.L_s * c.H_kv * (size_t)N * c.d;
@@ -366,7 +372,7 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
     const float* const in[3] = {(const float*)q_in, (const float*)k_in, nullptr};
     uint16_t* const out[3] = {(uint16_t*)ctx->q_bf16.ptr, (uint16_t*)ctx->krec_bf16.ptr, nullptr};
     const int64_t n[3] = {(int64_t)nq, (int64_t)nk, 0};
-    PKV_HIP(ctx, pkv::launch_f32_to_bf16(in, out, n, stream));
+    if (!rounds) PKV_HIP(ctx, pkv::launch_f32_to_bf16(in, out, n, stream));
     q = (const uint16_t*)ctx->q_bf16.ptr;
     k = (const uint16_t*)ctx->krec_bf16.ptr;
   }
@@ -376,7 +382,11 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
   if ((rcm = mark(ctx, 0, stream))) return rcm;
   const int splits = pkv::score_splits(c.L_s, c.H_q, c.d, N, N);
   const int q_splits = query_splits(ctx, true, true, N, N);
-  PKV_HIP(ctx, pkv::launch_score_lse(q, k, k, nl, splits, x_out, 0, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
+  if (rounds)
+    PKV_HIP(ctx, pkv::launch_score_lse_fp32((const float*)q_in, (const float*)k_in, (const float*)k_in, nl, splits, x_out, 0,
+                                            (uint16_t*)ctx->q_bf16.ptr, (uint16_t*)ctx->krec_bf16.ptr, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
+  else
+    PKV_HIP(ctx, pkv::launch_score_lse(q, k, k, nl, splits, x_out, 0, c.L_s, c.H_q, c.H_kv, c.d, 0, N, (int)N, stream));
   if ((rcm = mark(ctx, 1, stream))) return rcm;
   PKV_HIP(ctx, pkv::launch_score_colsum(q, k, nl, splits, x_out, (float*)ctx->x_parts.ptr, q_splits, c.L_s, c.H_q, c.H_kv, c.d, N, N, true, stream));
   if ((rcm = mark(ctx, 2, stream))) return rcm;

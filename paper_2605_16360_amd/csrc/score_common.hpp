@@ -98,6 +98,40 @@ __device__ __forceinline__ void tile_store(const TileRegs<D>& r, u32x4* lds, int
   }
 }
 
+// The same from fp32, rounded to bf16 (to nearest even) when the tile is stored.
+template <int D>
+struct TileRegsF32 {
+  u32x4 v[2 * ScoreCfg<D>::LOADS];
+};
+__device__ __forceinline__ u32x4 round_bf16(u32x4 lo, u32x4 hi) {
+  typedef float f32x8 __attribute__((ext_vector_type(8)));
+  const f32x4 a = __builtin_bit_cast(f32x4, lo), b = __builtin_bit_cast(f32x4, hi);
+  return __builtin_bit_cast(u32x4, __builtin_convertvector(f32x8{a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]}, bf16x8));
+}
+template <int D>
+__device__ __forceinline__ void tile_fetch(TileRegsF32<D>& r, const float* base, int row0, int row_limit, int tid) {
+  using C = ScoreCfg<D>;
+#pragma unroll
+  for (int i = 0; i < C::LOADS; ++i) {
+    const int id = tid + 256 * i, ch = id % C::CPR, row = row0 + id / C::CPR;
+    const float* at = base + (size_t)(row < row_limit ? row : row_limit - 1) * D + ch * 8;
+    r.v[2 * i] = *reinterpret_cast<const u32x4*>(at);
+    r.v[2 * i + 1] = *reinterpret_cast<const u32x4*>(at + 4);
+  }
+}
+// `copy`, if not null: the rounded tile goes there as well, rows below `copy_rows` (the tile's first row is row 0 of it).
+template <int D>
+__device__ __forceinline__ void tile_store(const TileRegsF32<D>& r, u32x4* lds, int tid, uint16_t* copy, int copy_rows) {
+  using C = ScoreCfg<D>;
+#pragma unroll
+  for (int i = 0; i < C::LOADS; ++i) {
+    const int id = tid + 256 * i, ch = id % C::CPR, row = id / C::CPR;
+    const u32x4 v = round_bf16(r.v[2 * i], r.v[2 * i + 1]);
+    lds[row * C::CPR + (ch ^ swz<D>(row))] = v;
+    if (copy != nullptr && row < copy_rows) *reinterpret_cast<u32x4*>(copy + (size_t)row * D + ch * 8) = v;
+  }
+}
+
 template <int D>
 __device__ __forceinline__ bf16x8 frag_read(const u32x4* lds, int row, int ch) {
   return as_bf16x8(lds[row * ScoreCfg<D>::CPR + (ch ^ swz<D>(row))]);
@@ -129,6 +163,17 @@ struct Rows32 {
   static __device__ __forceinline__ void columns(bf16x8 (&b)[KK], const uint16_t* base, int row, int lane) {
 #pragma unroll
     for (int kk = 0; kk < KK; ++kk) b[kk] = as_bf16x8(*reinterpret_cast<const u32x4*>(base + (size_t)row * D + kk * KS + lane / W * 8));
+  }
+  static __device__ __forceinline__ void columns(bf16x8 (&b)[KK], const float* base, int row, int lane) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const u32x4* at = reinterpret_cast<const u32x4*>(base + (size_t)row * D + kk * KS + lane / W * 8);
+      b[kk] = as_bf16x8(round_bf16(at[0], at[1]));
+    }
+  }
+  static __device__ __forceinline__ void keep_columns(const bf16x8 (&b)[KK], uint16_t* base, int row, int lane) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) *reinterpret_cast<u32x4*>(base + (size_t)row * D + kk * KS + lane / W * 8) = __builtin_bit_cast(u32x4, b[kk]);
   }
   static __device__ __forceinline__ Acc zero() {
     Acc c;

@@ -462,6 +462,24 @@ def test_score_of_groups_that_do_not_fill_the_xcds_evenly(L, H_q, H_kv, N):
         pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("N,N_q,chunk", [(1, 1, 1), (130, 257, 100), (700, 300, 128), (1000, 1000, 2048), (4096, 70, 64), (4097, 70, 64)])
+def test_score_of_fp32_inputs_is_that_of_their_bf16_roundings(N, N_q, chunk):
+    """Up to 4096 keys, where workgroups share a block's, pass 1 rounds fp32 inputs itself and leaves the copies that pass 2 reads; max, sum and
+    causal forms, groups of two heads, ties of the rounding and large values among the inputs."""
+    g = torch.Generator().manual_seed(N)
+    q, kc, kr, own = (torch.randn(2, h, n, 64, generator=g) for h, n in ((4, N_q), (2, N), (2, N_q), (4, N)))
+    q[0, 0, 0, :8] = torch.tensor([1.00390625, 1.01171875, -1.00390625, 3e-39, 1e-45, -0.0, 2.5e4, -2.5e4])
+    for reduce in (pk.PROXYKV_REDUCE_MAX, pk.PROXYKV_REDUCE_SUM):
+        cfg = pk.make_config(2, 4, 2, 64, 1, 4, 128)
+        cfg.reduce = reduce
+        ctx = pk.proxykv_create(cfg)
+        wide, half = ([t.to(dtype).cuda() for t in (q, kc, kr, own)] for dtype in (torch.float32, torch.bfloat16))
+        got = [pk.proxykv_score(ctx, t[0], t[1], t[2], chunk) for t in (wide, half)] + [pk.proxykv_score_self(ctx, t[3], t[1]) for t in (wide, half)]
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], got[1]) and torch.equal(got[2], got[3])
+        pk.proxykv_destroy(ctx)
+
+
 @pytest.mark.parametrize("d,N,N_q,chunk", [(64, 1, 3, 2), (64, 700, 257, 100), (64, 1030, 130, 64), (128, 65, 300, 1000), (128, 900, 64, 33),
                                           (128, 1100, 200, 256), (64, 2600, 1700, 512)])
 def test_score_few_and_many_query_blocks_agree(d, N, N_q, chunk):
