@@ -43,6 +43,13 @@ size_t score_lse_bytes(int L_s, int H_q, int64_t N_q) {
   return rows * 4 > pairs * sizeof(LsePart) ? rows * 4 : pairs * sizeof(LsePart);
 }
 
+// At d = 64 a workgroup of its own per block runs piped, except in the causal form up to 2048 tokens, where blocks have few whole tiles.  Both
+// passes, the other way / piped, us: 16 x 32 heads of 300 queries and keys 46.4 / 45.2, 2000 757 / 739, 8192 8728 / 8606, 16 000 32 680 / 31 810;
+// 24 x 14 heads of 10 000 8950 / 8590; causal, 1000 tokens 140 / 145, 2000 432 / 431, 4097 1547 / 1525.  (What is left is power: on zeros,
+// which draw little, 8192 7072 / 6503.  Three and four column tiles per wave with two workgroups per CU 8886 and 8529 at 8192, but 2454 and 2385
+// at 4000, where two take 2330.)
+constexpr int64_t kPipeCausal = 2048;
+
 hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint16_t* k_rec, float* neg_lse, int splits,
                             float* x, int64_t n_x, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
                             hipStream_t stream) {
@@ -50,6 +57,8 @@ hipError_t launch_score_lse(const uint16_t* q, const uint16_t* k_ctx, const uint
   const float c = 1.4426950408889634f / sqrtf((float)d), inv_c = 1.0f / c;
   // two column sub-tiles per wave; three workgroups per CU at d = 64 (at most 168 registers), two at d = 128
   constexpr int NCOL = kLseCols;
+  if (d == 64 && splits == 1 && (N > 0 || N_q > kPipeCausal))
+    return launch_score_lse_piped(q, k_ctx, k_rec, neg_lse, x, n_x, L_s, H_q, H_kv, N, N_q, chunk, stream);
   const dim3 grid = lse_grid(L_s, H_q, N_q, splits);
 #define PKV_LSE(D, W, MINB, SPLIT)                                                                                         \
   score_lse_kernel<D, NCOL, W, MINB, SPLIT><<<grid, 256, 0, stream>>>(q, k_ctx, k_rec, neg_lse, H_q, G, (int)N, (int)N_q, chunk, \

@@ -54,7 +54,7 @@ __device__ __forceinline__ int turned_block(int x, int nb, int g) { return (x + 
 // x [n_x] (n_x may be 0) is cleared for a pass 2 whose workgroups raise it.
 // In: what q, k_ctx and k_rec hold.  With fp32 the kernel rounds them itself and leaves bf16 copies of the queries and of the keys that
 // pass 2 reads (the context's, or the sequence's own) in q16 and k16.
-template <int D, int NCOL, int W, int MINB, bool SPLIT, class In = uint16_t>
+template <int D, int NCOL, int W, int MINB, bool SPLIT, class In = uint16_t, bool PIPE = false>
 __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const In* __restrict__ q,
                                                                const In* __restrict__ k_ctx,
                                                                const In* __restrict__ k_rec,
@@ -215,6 +215,54 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const In* __restri
     }
   };
 
+  // PIPE (32-column tiles): the same, a unit of one column tile and 32 keys at a time: its 16 fma, its 16 exponentials with the next unit's
+  // products between them, its 16 adds.  Two waves of a SIMD issue full-rate vector instructions (fma, add) in the same cycles, exponentials and
+  // products hold it alone, so the waves are kept in step: exponentials go first, and a wave that has done its own finds the other one
+  // at its fma and adds too.  (Out of registers, cycles per logit and SIMD: 15.9 in the compiler's order, 12.5 so; with the products 19.3
+  // and 15.5.)  `ready`: units[0] holds the first unit's products; afterwards it holds those of `next`, the tile behind it.
+  constexpr int UNITS = C::SUB * NT;
+  Acc units[2];
+  R keys;
+  auto unit_step = [&](Acc& unit, auto uc, auto kc) __attribute__((always_inline)) {  // k-step kc of unit u
+    constexpr int u = decltype(uc)::value % UNITS, kk = decltype(kc)::value;
+    if constexpr (kk == 0) unit = R::zero();
+    keys.step(unit, b[u % NT], 0, kk);
+  };
+  auto first_unit = [&](const u32x4* buf) __attribute__((always_inline)) {
+    keys.read(buf, 0, lane);
+    static_for<R::KK>([&](auto kc) { unit_step(units[0], std::integral_constant<int, 0>{}, kc); });
+  };
+  auto piped_tile = [&](const u32x4* buf, const u32x4* next) __attribute__((always_inline)) {
+    static_for<UNITS>([&](auto uc) {
+      constexpr int u = decltype(uc)::value, cur = u & 1, ct = u % NT, per = R::E / R::KK;
+      float e[R::E], sum[4];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < R::E; ++r) e[r] = __builtin_fmaf(units[cur].get(r), c, nref[ct]);
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(2);
+      static_for<R::KK>([&](auto kc) {
+        unit_step(units[cur ^ 1], std::integral_constant<int, u + 1>{}, kc);
+#pragma unroll
+        for (int r = decltype(kc)::value * per; r < (decltype(kc)::value + 1) * per; ++r) e[r] = __builtin_amdgcn_exp2f(e[r]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      __builtin_amdgcn_s_setprio(0);
+      // the products of the sub-tile's last unit are issued: its fragments make way for the next one's
+      if constexpr (ct == NT - 2) {
+        constexpr int s = u / NT + 1;
+        if constexpr (s < C::SUB) keys.read(buf, s * 32, lane);
+        else keys.read(next, 0, lane);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[r] = e[r];
+#pragma unroll
+      for (int r = 4; r < R::E; ++r) sum[r & 3] += e[r];
+      lsum[ct] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
   // Where a chain of the tile at row0 (32 keys from jbase on, the wave's 32 columns cs) stands: nothing of it is visible,
   // some of it, or all.  All of it is where every key lies at or before the first query, and inside its last one's chunk.
   auto hidden = [&](bool is_rec, int jbase, int limit, int cs) {
@@ -302,6 +350,7 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const In* __restri
   __builtin_amdgcn_s_waitcnt(kVmcnt0);
   if (total > 2) fetch(2);
 
+  bool ready = false;
   for (int t = 0; t < total; ++t) {
     // every wave has finished tile t-1: its buffer takes tile t+2, the registers take tile t+3
     __syncthreads();
@@ -312,6 +361,25 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const In* __restri
     if (wave_i_lo >= N_q) continue;
     const u32x4* buf = lds + (t % kNBuf) * C::TILE_U4;
     const int tg = t0 + t;
+    if constexpr (PIPE) {
+      static_assert(W == 32 && NT >= 2 && NT % 2 == 0, "units of a column tile, two at a time");
+      const bool is_rec = tg >= n_ctx;
+      const int row0 = is_rec ? rec_lo + (tg - n_ctx) * C::ROWS : tg * C::ROWS, limit = is_rec ? i_end : N;
+      const bool interior = is_rec ? row0 + C::ROWS - 1 <= i0 && row0 >= ((i_end - 1) / chunk) * chunk : row0 + C::ROWS <= N;
+      if (t == 0) first_reference(buf, interior, is_rec, row0);
+      if (interior) {
+        if (!ready) first_unit(buf);
+        ready = sum_unchecked([&]() __attribute__((always_inline)) { piped_tile(buf, lds + ((t + 1) % kNBuf) * C::TILE_U4); });
+        if (ready) continue;
+      } else {
+        ready = false;
+        if (sum_unchecked([&]() __attribute__((always_inline)) { cut_tile(buf, is_rec, row0, limit); })) continue;
+      }
+#pragma unroll 1
+      for (int s = 0; s < C::SUB; ++s)
+        if (!cut_rows(buf, is_rec, s, row0, limit, accumulate)) break;
+      continue;
+    }
     // Whole context tiles, nearly all there are, go round a loop of their own: with the choices below in it a tile of heads of
     // 128 took 1 to 3 % longer (28 layers of 12 heads, 300 queries of 16 000 keys, both passes: 1123 -> 1108 us).
     const bool whole = t > 0 && tg < n_whole;

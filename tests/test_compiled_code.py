@@ -51,6 +51,16 @@ def test_no_scoring_tile_waits_for_its_own_prefetch(source):
     assert seen >= 4
 
 
+@pytest.mark.parametrize("source", ["score_lse_fp32.hip", "score_lse_piped.hip"])
+def test_no_other_pass_1_tile_waits_for_its_own_prefetch(source):
+    """The same for pass 1's kernel on fp32 inputs and for the piped one, which spills nothing either."""
+    (name, body), = [(name, body) for name, body in kernels(source) if "score_lse_kernel" in name]
+    ops = re.findall(r"^\s+(s_waitcnt\b.*|v_mfma\w*|s_barrier|v_\w+|ds_\w+|global_\w+)", body, re.M)
+    first = next(i for i, op in enumerate(ops) if op.startswith("s_barrier"))
+    assert not [i for i in range(first, len(ops)) if ops[i].startswith("v_mfma") and "vmcnt" in ops[i - 1]], name
+    assert "scratch_" not in body
+
+
 def test_scoring_masks_do_not_branch_per_element():
     """A column sees one range of keys, so the mask of a cut tile is a comparison per element.  Written as a choice per element
     it compiles to hundreds of branches, fetched for the few cut tiles of a short input."""
