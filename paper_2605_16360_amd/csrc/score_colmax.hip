@@ -284,6 +284,62 @@ __global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void sc
   if (total > 2) fetch_next();
 
   const bool idle = n0 + wave * NCOL * 32 >= N;  // a wave without a key helps with the tiles only
+  // As pass 1's piped tiles (score_lse.hpp): a unit of one column tile and 32 queries at a time, its exponentials between the next one's products
+  // (24 x 14 heads of 64, 6001 keys, both passes 3862 -> 3793 us; 16 x 32, 2000 851 -> 835; not where there are few queries: one layer of 4 heads,
+  // 300 queries of 500 keys 18.1 -> 18.4).
+  constexpr bool kPiped = !CAUSAL && !SPLIT && W == 32;
+  constexpr int UNITS = C::SUB * NT;
+  Acc units[2], init;
+  R rows;
+  auto read_rows = [&](const u32x4* buf, const float* nl, int s) __attribute__((always_inline)) {
+    rows.read(buf, s * 32, lane);
+#pragma unroll
+    for (int r = 0; r < R::E; r += 4) {
+      const f32x4 v = *reinterpret_cast<const f32x4*>(&nl[s * 32 + R::acc_row(r) + rows4]);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) init.set(r + e, v[e]);
+    }
+  };
+  auto unit_step = [&](Acc& unit, auto uc, auto kc) __attribute__((always_inline)) {
+    constexpr int u = decltype(uc)::value % UNITS, kk = decltype(kc)::value;
+    if constexpr (kk == 0) unit = init;
+    rows.step(unit, b[u % NT], 0, kk);
+  };
+  auto first_unit = [&](const u32x4* buf, const float* nl) __attribute__((always_inline)) {
+    read_rows(buf, nl, 0);
+    static_for<R::KK>([&](auto kc) { unit_step(units[0], std::integral_constant<int, 0>{}, kc); });
+  };
+  auto piped_tile = [&](const u32x4* buf, const float* nl, const u32x4* next, const float* next_nl) __attribute__((always_inline)) {
+    static_for<UNITS>([&](auto uc) {
+      constexpr int u = decltype(uc)::value, cur = u & 1, ct = u % NT, per = R::E / R::KK;
+      float e[R::E], sum[4];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < R::E; ++r) e[r] = units[cur].get(r) * c;
+      __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(2);
+      static_for<R::KK>([&](auto kc) {
+        unit_step(units[cur ^ 1], std::integral_constant<int, u + 1>{}, kc);
+#pragma unroll
+        for (int r = decltype(kc)::value * per; r < (decltype(kc)::value + 1) * per; ++r) e[r] = __builtin_amdgcn_exp2f(e[r]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      __builtin_amdgcn_s_setprio(0);
+      if constexpr (ct == NT - 2) {
+        constexpr int s = u / NT + 1;
+        if constexpr (s < C::SUB) read_rows(buf, nl, s);
+        else read_rows(next, next_nl, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sum[r] = e[r];
+#pragma unroll
+      for (int r = 4; r < R::E; ++r) sum[r & 3] += e[r];
+      colsum[ct] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  bool ready = false;
   int cqt = qt_first + first % nqg;  // query tile of step t
   for (int t = 0; t < total; ++t) {
     // every wave has finished tile t-1: its buffer takes tile t+2, the registers take tile t+3
@@ -296,6 +352,12 @@ __global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void sc
     const int row0 = cqt * C::ROWS;
     const bool diag = CAUSAL && row0 < n0 + KB - 1;  // some query of the tile lies before some key of the block
     if (++cqt == nqt) cqt = qt_first;
+    if constexpr (kPiped) {
+      if (!ready) first_unit(buf, nl);
+      ready = t + 1 < total;
+      piped_tile(buf, nl, lds + ((t + 1) % kNBuf) * C::TILE_U4, lds_nl + ((t + 1) % kNBuf) * C::ROWS);
+      continue;
+    }
     // (unrolled, the four sub-tiles of the causal form take 256 registers and with them the third workgroup per CU)
     constexpr int kUnroll = CAUSAL ? 2 : C::SUB;
 #pragma unroll kUnroll
