@@ -453,7 +453,11 @@ hipError_t launch_parts(BlockArgs a, int n_layers, int li, int n_enc, hipStream_
 // its weights' way from L2 (6.3 MB for each workgroup and layer, 64 bytes a clock and CU), and both take about the same: a quarter would win nothing.
 // us, halves / wholes: one layer of 5548 rows 821 / 1139, of 16 k 1132 / 1323, 16 of 500 665 / 978; with 129 .. 256 blocks some
 // CUs do two halves in turn, one layer of 26 k 1945 / 1738.
-constexpr int64_t kHalfBlocks = 128;
+// Two lanes' blocks are not in step: while one lane's launch ends or its attention runs, the other's halves have the chip, so up to three quarters
+// of the CUs' number pay there (half of them in either launch).  16 layers of 1100 rows (144 blocks of both lanes) 1193 / 1306, of 1500 (192)
+// 1514 / 1644, 24 of 900 (192) 1305 / 1369, 28 of 700 (168) 1101 / 1190; beyond that the shapes differ: 16 of 1700 (224) 1786 / 1811, 28 of 1000
+// (224) 1547 / 1476, 16 of 2000 (256) 2331 / 2202.
+constexpr int64_t kHalfBlocks = 128, kHalfBlocksLanes = 192;
 }  // namespace
 
 hipError_t pack_encoder_blocks(const proxykv_config& c, const MapperWeights& w, void* blk_w, void* blk_b, hipStream_t stream) {
@@ -513,7 +517,7 @@ hipError_t launch_encoder_block(const proxykv_ctx* ctx, const MapPlan& p, int n_
   a.Tp = (int)p.Tp;
   a.chunks = c.d_ffn / 256;
   const int64_t blocks = (p.T + kBlk - 1) / kBlk * n_layers * p.lanes;  // of all lanes together
-  return blocks <= kHalfBlocks ? launch_parts<4>(a, n_layers, li, c.n_enc_layers, stream) : launch_parts<8>(a, n_layers, li, c.n_enc_layers, stream);
+  return blocks <= (p.lanes > 1 ? kHalfBlocksLanes : kHalfBlocks) ? launch_parts<4>(a, n_layers, li, c.n_enc_layers, stream) : launch_parts<8>(a, n_layers, li, c.n_enc_layers, stream);
 }
 
 }  // namespace pkv

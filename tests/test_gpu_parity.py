@@ -712,8 +712,8 @@ def test_mapper_of_other_sizes(d_ffn, c_mid, n_enc, L, N):
 
 
 def test_mapper_half_blocks_are_whole_blocks_bit_for_bit():
-    """26 layers of 600 tokens are two times 65 blocks, more than half of the CUs, and run as whole blocks; the first 8 of them alone
-    run as halves, of which each layer's last holds 24 rows."""
+    """26 layers of 600 tokens are two times 65 blocks in two lanes, the first 8 of them alone are 40 in one: either way halves, of which
+    each layer's last holds 24 rows.  (Whole blocks against halves: the next test.)"""
     y = []
     for L in (26, 8):
         case = synth.scaled_case(synth.CASES["llama_8k"], name="halves", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=600, N_q=1, chunk=1, n_planted=0)
@@ -724,6 +724,23 @@ def test_mapper_half_blocks_are_whole_blocks_bit_for_bit():
         torch.cuda.synchronize()
         pk.proxykv_destroy(ctx)
     assert torch.equal(y[0], y[1])
+
+
+@pytest.mark.parametrize("N,halves,wholes", [(1024, 24, 26), (1025, 20, 22), (600, 38, 40)])
+def test_mapper_half_blocks_of_two_lanes_are_whole_blocks_bit_for_bit(N, halves, wholes):
+    """Two lanes' blocks run as halves up to three quarters of the CUs, 192 of both lanes: layers that make so many, or the next fewer, against
+    the same layers among more.  The halves are compared with the oracle as well."""
+    X, y = torch.rand(wholes, 2, N, generator=torch.Generator().manual_seed(N)) ** 8, []
+    w = synth.make_mapper_weights(2, 4)
+    for L in (halves, wholes):
+        case = synth.scaled_case(synth.CASES["llama_8k"], name="halves", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=N, N_q=1, chunk=1, n_planted=0)
+        ctx = _ctx(case, w)
+        y.append(pk.proxykv_map(ctx, X[:L].float().contiguous().cuda())[:halves].cpu())
+        torch.cuda.synchronize()
+        pk.proxykv_destroy(ctx)
+    assert torch.equal(y[0], y[1])
+    for l in (0, halves - 1):
+        assert_close(y[0][l:l + 1], oracle.mapper(X[:halves].float(), w, halves, layers=[l])[l:l + 1], f"map {halves} layers, N={N}, layer {l}")
 
 
 def test_mapper_with_scores_beyond_the_half_range():
