@@ -94,18 +94,14 @@ __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict
 // fp16 GEMM  C[M, Nn] = A[M, K] * W[Nn, K]^T  (+ epilogue), fp32 accumulation.
 // A rows start lda elements apart (lda < K gives the overlapping rows of the second convolution).
 //
-// The stem's second convolution and the stage-3 projection.  Persistent kernel, one 512-thread workgroup per CU.  Block tile
-// BM (rows of A) x BN (rows of W) = 256 x 256, K step 64 (full 128-byte lines per row), 8 waves, each 64 x 128 = 2 x 4 MFMA
-// tiles.  A tile of this size needs 1 byte from L2 per 128 flop; smaller tiles are bound by the L2 -> CU path, not by
-// the matrix pipe.
+// The stage-3 projection where it has many tiles (where it has few, and for the second convolution: gemm_f16_tile_kernel).
+// Persistent kernel, one 512-thread workgroup per CU.  Block tile BM (rows of A) x BN (rows of W) = 256 x 256, K step 64 (full
+// 128-byte lines per row), 8 waves, each 64 x 128 = 2 x 4 MFMA tiles.  A tile of this size needs 1 byte from L2 per 128 flop.
 //
 // The A rows go on the MFMA M axis and the W rows on the N axis, so a lane owns output COLUMNS.  The
 // W rows of a wave's 128-column block are staged in the order n = 4*l + jn (l = lane & 31, jn = MFMA
 // tile), so a lane holds four adjacent columns in its four tiles and every store instruction writes
-// whole 512-byte row segments, 16 bytes per lane.  Output
-// buffers have their row count padded to a multiple of 256, so the epilogue has no row predicate; rows
-// at and past M are written with values that nobody reads (the stem's epilogue, which writes a token's row into
-// the windows that hold it, skips them instead).
+// whole 512-byte row segments, 16 bytes per lane.  Rows past a layer's last are not written.
 //
 // The K steps of all tiles of a workgroup form one stream: two LDS stages (64 KB each) and ONE barrier
 // per step.  A step is four phases of 8 MFMAs; the fragments of phase kk+1 are read from LDS between
@@ -164,10 +160,85 @@ __device__ __forceinline__ float reduce16_over_16_lanes(float (&v)[16], int lane
   return v[0];
 }
 
-template <int EPI>
+// What follows a wave's 32 MI x 128 accumulators: rows m0 .. of the batch, r0 .. of their layer, columns c0 ..
+template <int EPI, int MI>
+__device__ __forceinline__ void gemm_epilogue(const f32x16 (&acc)[MI][4], const f32x4 p0, const f32x4 p1, const EpiArgs& ep, int m0, int r0,
+                                              int layer, int rows, int c0, int lane) {
+  // a lane holds columns n .. n+3; register r of tile (i, jn) holds row i*32 + half*4 + (r/4)*8 + r%4
+  const int half = lane >> 5, l32 = lane & 31, n = c0 + 4 * l32;
+  if constexpr (EPI == kEpiStage3) {
+    // The 64 columns of a slot sit in 16 lanes (four columns each).  Per 32-row block: the lane's share of every row's
+    // inner product with one coefficient vector, sixteen rows reduced over the 16 lanes at once, lane j keeps row j of
+    // the sixteen that its half-wave holds.  Key slots take the n_head queries in turn, value slots the output weights.
+    const int col = c0 + (l32 >> 4) * 64;  // first column of the lane group's slot
+    const int slot = col >> 6, e0 = (l32 & 15) * 4;
+    const bool is_k = slot < ep.n_slot, is_v = !is_k && slot < 2 * ep.n_slot;
+    const int sv = is_k ? slot : slot - ep.n_slot;
+    const int j16 = l32 & 15;
+    const int n_pass = ep.n_head;  // uniform; value slots use pass 0 only
+    const float* cf = is_k ? ep.p1 + e0 : ep.g + e0;
+    f32x4 next = *reinterpret_cast<const f32x4*>(cf);  // coefficients of pass h, loaded a pass ahead
+    for (int h = 0; h < n_pass; ++h) {
+      const f32x4 c4 = next;
+      next = *reinterpret_cast<const f32x4*>(cf + (is_k && h + 1 < n_pass ? (size_t)(h + 1) * 64 : 0));
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        const int row = m0 + i * 32 + (j16 >> 2) * 8 + half * 4 + (j16 & 3);  // the row this lane ends up with
+        float* orow = ep.out_f32 + (size_t)row * ep.ldc;
+        float part[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          part[r] = (acc[i][0][r] + p0[0]) * c4[0] + (acc[i][1][r] + p0[1]) * c4[1] + (acc[i][2][r] + p0[2]) * c4[2] +
+                    (acc[i][3][r] + p0[3]) * c4[3];
+        const float tot = reduce16_over_16_lanes(part, l32);
+        if (row - m0 + r0 < rows) {
+          if (is_k) orow[h * ep.n_slot + sv] = tot * 0.125f;
+          else if (is_v && h == 0) orow[ep.n_head * ep.n_slot + sv] = tot;
+        }
+      }
+    }
+  } else {
+    f32x4* xo = reinterpret_cast<f32x4*>(ep.out_f32);
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+      // Token t sits at place t - 1024 k of window k = min(t / 1024, n_win - 1) and, if that window is not the first and the token lies in
+      // its first half, at place + 1024 of the window before: the same window for all 32 tokens, which lie in one 32nd of 1024.
+      // The 32 places lie in the table whether the tokens are there or not.
+      const int ti = r0 + i * 32, tl = half * 4;
+      if (ti >= rows) break;
+      const int kq = ti / kStride, k1 = kq < ep.n_win ? kq : ep.n_win - 1, place = ti - k1 * kStride + tl;
+      const float* pe = ep.pe + (size_t)place * kDT + n;
+      const int64_t row = (int64_t)layer * ep.out_stride + (int64_t)k1 * kWin + place;
+      const bool second = k1 >= 1 && kq == k1;
+      // Eight rows at a time, their positional rows loaded before the first GELU: a load behind each GELU would be waited for by itself.
+#pragma unroll
+      for (int g = 0; g < 16; g += 8) {
+        f32x4 e0[8], e1[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) e0[r] = *reinterpret_cast<const f32x4*>(pe + (((g + r) >> 2) * 8 + (r & 3)) * kDT);
+        if (second) {
+#pragma unroll
+          for (int r = 0; r < 8; ++r) e1[r] = *reinterpret_cast<const f32x4*>(pe + (kStride + ((g + r) >> 2) * 8 + (r & 3)) * kDT);
+        }
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const int t = ((g + r) >> 2) * 8 + (r & 3);
+          f32x4 v = {acc[i][0][g + r], acc[i][1][g + r], acc[i][2][g + r], acc[i][3][g + r]};
+#pragma unroll
+          for (int c = 0; c < 4; ++c) v[c] = gelu_erf(__builtin_fmaf(v[c], p0[c], p1[c]));
+          if (ti + tl + t < rows) {
+            xo[block_x4(row + t, n)] = v + e0[r];
+            if (second) xo[block_x4(row + t - (kWin - kStride), n)] = v + e1[r];
+          }
+        }
+      }
+    }
+  }
+}
+
 __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __restrict__ A, int lda, int64_t a_layer,
-                                                            const uint16_t* __restrict__ W, int M, int rows, int row_stride,
-                                                            int Nn, int K, EpiArgs ep) {
+                                                          const uint16_t* __restrict__ W, int M, int rows, int row_stride,
+                                                          int Nn, int K, EpiArgs ep) {
   constexpr int BM = kGemmTile, BN = kGemmTile, WM = BM / 64, WN = 8 / WM;  // waves along M and N
   constexpr int NA = BM / 64, NS = (BM + BN) / 64;  // 64-row parts of a stage: A parts, then W parts
   constexpr int kStageU4 = (BM + BN) * (kGemmBK / 8);  // 16-byte units per stage
@@ -240,18 +311,14 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
       for (int jn = 0; jn < 4; ++jn) acc[i][jn] = f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
   };
   zero_acc();
-  // bias (and scale) of the current tile's columns n .. n+3, loaded when the tile starts: a load inside
+  // bias of the current tile's columns n .. n+3, loaded when the tile starts: a load inside
   // the epilogue would have to wait for the prefetch of the next step as well
-  f32x4 p0, p1 = {0.0f, 0.0f, 0.0f, 0.0f};
+  f32x4 p0;
   auto load_bias = [&](int it) {
     int m0, n0;
     tile_of(it < my_tiles ? it : my_tiles - 1, m0, n0);
     const int n = n0 + wn * 128 + 4 * l32;
     p0 = *reinterpret_cast<const f32x4*>(ep.p0 + n);
-    if constexpr (EPI == kEpiGeluPeWin) {
-      p0 *= exp2_int(stem_exponent(ep.range + (m0 / row_stride) * kRangeWords, ep.cw, ep.cs));
-      p1 = *reinterpret_cast<const f32x4*>(ep.p1 + n);
-    }
   };
   load_bias(0);
 
@@ -307,66 +374,100 @@ __global__ __launch_bounds__(512, 1) void gemm_f16_kernel(const uint16_t* __rest
     fetch_advance();
     if (s % nk != nk - 1) continue;
 
-    // epilogue: lane holds columns n .. n+3; register r of tile (i, jn) holds row mb + (r/4)*8 + r%4
     int m0, n0;
     tile_of(s / nk, m0, n0);
-    const int n = n0 + wn * 128 + 4 * l32;
-    const int layer = m0 / row_stride, r0 = m0 - layer * row_stride;  // r0: the tile's first row within its layer
-    if constexpr (EPI == kEpiStage3) {
-      // The 64 columns of a slot sit in 16 lanes (four columns each).  Per 32-row block: the lane's share of every row's
-      // inner product with one coefficient vector, sixteen rows reduced over the 16 lanes at once, lane j keeps row j of
-      // the sixteen that its half-wave holds.  Key slots take the n_head queries in turn, value slots the output weights.
-      const int col = n0 + wn * 128 + (l32 >> 4) * 64;  // first column of the lane group's slot
-      const int slot = col >> 6, e0 = (l32 & 15) * 4;
-      const bool is_k = slot < ep.n_slot, is_v = !is_k && slot < 2 * ep.n_slot;
-      const int sv = is_k ? slot : slot - ep.n_slot;
-      const int j16 = l32 & 15;
-      const int n_pass = ep.n_head;  // uniform; value slots use pass 0 only
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const int row = m0 + wm * 64 + i * 32 + (j16 >> 2) * 8 + half * 4 + (j16 & 3);  // the row this lane ends up with
-        float* orow = ep.out_f32 + (size_t)row * ep.ldc;
-        for (int h = 0; h < n_pass; ++h) {
-          const float* cf = is_k ? ep.p1 + (size_t)h * 64 + e0 : ep.g + e0;
-          const f32x4 c4 = *reinterpret_cast<const f32x4*>(cf);
-          float part[16];
-#pragma unroll
-          for (int r = 0; r < 16; ++r)
-            part[r] = (acc[i][0][r] + p0[0]) * c4[0] + (acc[i][1][r] + p0[1]) * c4[1] + (acc[i][2][r] + p0[2]) * c4[2] +
-                      (acc[i][3][r] + p0[3]) * c4[3];
-          const float tot = reduce16_over_16_lanes(part, l32);
-          if (row - m0 + r0 < rows) {
-            if (is_k) orow[h * ep.n_slot + sv] = tot * 0.125f;
-            else if (is_v && h == 0) orow[ep.n_head * ep.n_slot + sv] = tot;
-          }
-        }
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          f32x4 v = {acc[i][0][r], acc[i][1][r], acc[i][2][r], acc[i][3][r]};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = gelu_erf(__builtin_fmaf(v[e], p0[e], p1[e]));
-          // token t sits at place t - 1024 k of window k = min(t / 1024, n_win - 1) and, if that window is not the
-          // first and the token lies in its first half, at place + 1024 of the window before
-          const int t = r0 + wm * 64 + i * 32 + half * 4 + (r >> 2) * 8 + (r & 3);
-          if (t < rows) {
-            const int kq = t / kStride, k1 = kq < ep.n_win ? kq : ep.n_win - 1, p1w = t - k1 * kStride;
-            const int64_t row = (int64_t)layer * ep.out_stride + (int64_t)k1 * kWin + p1w;
-            f32x4* xo = reinterpret_cast<f32x4*>(ep.out_f32);
-            xo[block_x4(row, n)] = v + *reinterpret_cast<const f32x4*>(ep.pe + (size_t)p1w * kDT + n);
-            // window k1 - 1, place p1w + 1024
-            if (k1 >= 1 && kq == k1)
-              xo[block_x4(row - (kWin - kStride), n)] = v + *reinterpret_cast<const f32x4*>(ep.pe + (size_t)(p1w + kStride) * kDT + n);
-          }
-        }
-      }
-    }
+    const int layer = m0 / row_stride;
+    gemm_epilogue<kEpiStage3, 2>(acc, p0, p0, ep, m0 + wm * 64, m0 - layer * row_stride + wm * 64, layer, rows, n0 + wn * 128, lane);
     zero_acc();
     load_bias(s / nk + 1);
   }
+}
+
+// ------------------------------------------------------------------------------------------
+// The same product, sum for sum, in tiles of 128 x 128: the second convolution, and the projection where it has few tiles (kTileProducts).
+// 256 threads, a wave computes 32 x 128; two stages of 32 KB, so two workgroups share a CU and one's products run beside the other's epilogue,
+// which in the convolution (a GELU per element, two stores) takes longer than its 12 K steps: with one 256 x 256 tile per CU
+// nothing stood beside it.  One layer of 3500 tokens, 28 large tiles or 112 of these: 52.5 us and 21.3 (25.6 with a
+// positional row loaded behind each GELU); eight layers of 600 tokens 40.8 / 19.9, one of 8192 beside another lane 134 / 123.  Loads write LDS
+// directly, a stage as the fragments are read (row r's unit u at place u ^ swz8(r)).  Four stages and one workgroup per CU are up to
+// 4 % of the mapper slower.
+// XCD x = block % 8 takes the row tiles x, x + 8, ..., a row's column tiles one after another.  layer_tiles row tiles per layer, row_tiles
+// in all; a layer's last tile re-reads its last row.
+// ------------------------------------------------------------------------------------------
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_f16_tile_kernel(const uint16_t* __restrict__ A, int lda, int64_t a_layer,
+                                                                const uint16_t* __restrict__ W, int row_tiles, int layer_tiles,
+                                                                int rows, int row_stride, int n_tiles, int K, EpiArgs ep) {
+  constexpr int kStageU4 = 256 * (kGemmBK / 8);
+  __shared__ u32x4 lds[2 * kStageU4];  // a stage: 128 rows of A, then 128 of W, in the order n = 4 * l + jn
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+  const int bj = blockIdx.x / kXcds, rt = (bj / n_tiles) * kXcds + blockIdx.x % kXcds, n0 = (bj % n_tiles) * 128;
+  if (rt >= row_tiles) return;
+  const int layer = rt / layer_tiles, r0 = (rt % layer_tiles) * 128;
+  const int nk = K / kGemmBK;
+  typedef const __attribute__((address_space(1))) void* gptr_t;
+  typedef __attribute__((address_space(3))) void* lptr_t;
+  const int srow = tid >> 3, sch = ((tid & 7) ^ swz8(srow)) * 8;
+  const uint16_t *pa[4], *pw = W + (size_t)(n0 + 4 * srow) * K + sch;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    int m = r0 + srow + 32 * i;
+    m = m < rows ? m : rows - 1;
+    pa[i] = A + (size_t)layer * a_layer + (size_t)m * lda + sch;
+  }
+  // past the last step that one is copied again, so that every step has the same loads behind it
+  auto fetch = [&](int s, int stage) __attribute__((always_inline)) {
+    const int k0 = (s < nk ? s : nk - 1) * kGemmBK;
+    u32x4* st = lds + stage * kStageU4 + wave * 64;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      __builtin_amdgcn_global_load_lds((gptr_t)(pa[i] + k0), (lptr_t)(st + i * 256), 16, 0, 0);
+      __builtin_amdgcn_global_load_lds((gptr_t)(pw + (size_t)i * K + k0), (lptr_t)(st + (4 + i) * 256), 16, 0, 0);
+    }
+  };
+  const int n = n0 + 4 * l32;
+  f32x4 p0 = *reinterpret_cast<const f32x4*>(ep.p0 + n), p1 = {0.0f, 0.0f, 0.0f, 0.0f};
+  if constexpr (EPI == kEpiGeluPeWin) {
+    p0 *= exp2_int(stem_exponent(ep.range + layer * kRangeWords, ep.cw, ep.cs));
+    p1 = *reinterpret_cast<const f32x4*>(ep.p1 + n);
+  }
+  f32x16 acc[1][4];
+#pragma unroll
+  for (int jn = 0; jn < 4; ++jn) acc[0][jn] = f32x16{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
+  fetch(0, 0);
+  fetch(1, 1);
+  __builtin_amdgcn_s_waitcnt(0x0F78);  // vmcnt(8): step 0
+  __syncthreads();
+  const int fsw = swz8(l32), xrow = (wave * 32 + l32) * 8, wrow = (128 + l32) * 8;
+  f16x8 fx[2], fw[2][4];
+  auto read_frags = [&](const u32x4* st, int kk, int set) __attribute__((always_inline)) {
+    const int slot = (kk * 2 + half) ^ fsw;
+    fx[set] = as_f16x8(st[xrow + slot]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) fw[set][j] = as_f16x8(st[wrow + j * 32 * 8 + slot]);
+  };
+  read_frags(lds, 0, 0);
+  for (int s = 0; s < nk; ++s) {
+    const u32x4 *st = lds + (s & 1) * kStageU4, *st_next = lds + ((s + 1) & 1) * kStageU4;
+    static_for<4>([&](auto kc) {
+      constexpr int kk = decltype(kc)::value, cur = kk & 1, nxt = cur ^ 1;
+      if constexpr (kk == 3) {
+        // this wave's part of step s + 1 has landed; behind the barrier everyone's has, and every wave has read the last of step s
+        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+        __syncthreads();
+        fetch(s + 2, s & 1);
+        read_frags(st_next, 0, nxt);
+      } else {
+        read_frags(st, kk + 1, nxt);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[0][j] = mfma_f16_32x32x16(fx[cur], fw[cur][j], acc[0][j]);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing of this workgroup writes LDS that anyone may have by then
+  gemm_epilogue<EPI, 1>(acc, p0, p1, ep, layer * row_stride + r0 + wave * 32, r0 + wave * 32, layer, rows, n0, lane);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -655,28 +756,38 @@ __global__ __launch_bounds__(256) void stage3_kernel(const float* __restrict__ s
   for (int ll = ll_lo; ll < ll_hi; ++ll) yhat[((size_t)ll * H_l + h) * N + t] = y;
 }
 
+// Up to so many large tiles (half the CUs) the projection takes the 128 x 128 tiles as well: 14 of them (one layer of 3500 tokens) 18.2 us, in
+// small ones 9.9, 96 (8 layers of 600) 25.6 / 17.9; 192 (8 of 1500) 33.5 / 37.9, 128 in either lane (one of 8192) 100 / 125.  The large ones
+// read half as much and sum a coefficient vector's 64 rows per load.  The convolution is faster in small ones at every size.
+constexpr int kTileProducts = 128;
 template <int EPI>
 hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowSpace& rs, int Nn, int K, const EpiArgs& ep,
                        int n_cu, hipStream_t stream) {
   constexpr int BM = kGemmTile, BN = kGemmTile, kLdsBytes = 2 * (BM + BN) * (kGemmBK / 8) * 16;
-  static bool attr_set = false;  // per instantiation; setting it again is harmless
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f16_kernel<EPI>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
   const int64_t M = (int64_t)rs.layers * rs.stride;
   if (Nn % BN != 0 || K % kGemmBK != 0 || rs.valid <= 0 || rs.valid > rs.stride || rs.stride % 256 != 0 || M > INT32_MAX)
     return hipErrorInvalidValue;
   const int m_tiles = (int)(M / BM), n_tiles = Nn / BN;
-  // one workgroup per CU, a multiple of the XCD count, no more than there are tiles per XCD list
-  const int per_xcd_tiles = ((m_tiles + kXcds - 1) / kXcds) * n_tiles;
-  int wg_per_xcd = n_cu / kXcds;
-  if (wg_per_xcd < 1) wg_per_xcd = 1;
-  if (wg_per_xcd > per_xcd_tiles) wg_per_xcd = per_xcd_tiles;
-  gemm_f16_kernel<EPI><<<kXcds * wg_per_xcd, 512, kLdsBytes, stream>>>(A, lda, rs.a_layer, W, (int)M, rs.valid,
-                                                                             rs.stride, Nn, K, ep);
+  if (EPI != kEpiStage3 || (int64_t)m_tiles * n_tiles <= kTileProducts) {
+    const int layer_tiles = (rs.valid + 127) / 128, row_tiles = layer_tiles * rs.layers;
+    const unsigned blocks = (unsigned)((row_tiles + kXcds - 1) / kXcds * kXcds) * (unsigned)(Nn / 128);
+    gemm_f16_tile_kernel<EPI><<<blocks, 256, 0, stream>>>(A, lda, rs.a_layer, W, row_tiles, layer_tiles, rs.valid, rs.stride, Nn / 128, K, ep);
+    return hipGetLastError();
+  }
+  if constexpr (EPI == kEpiStage3) {
+    static bool attr_set = false;  // setting it again is harmless
+    if (!attr_set) {
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_f16_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+      if (e != hipSuccess) return e;
+      attr_set = true;
+    }
+    // one workgroup per CU, a multiple of the XCD count, no more than there are tiles per XCD list
+    const int per_xcd_tiles = ((m_tiles + kXcds - 1) / kXcds) * n_tiles;
+    int wg_per_xcd = n_cu / kXcds;
+    if (wg_per_xcd < 1) wg_per_xcd = 1;
+    if (wg_per_xcd > per_xcd_tiles) wg_per_xcd = per_xcd_tiles;
+    gemm_f16_kernel<<<kXcds * wg_per_xcd, 512, kLdsBytes, stream>>>(A, lda, rs.a_layer, W, (int)M, rs.valid, rs.stride, Nn, K, ep);
+  }
   return hipGetLastError();
 }
 

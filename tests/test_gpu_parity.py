@@ -688,6 +688,23 @@ def test_mapper_at_the_edges_of_a_block(L, N):
     pk.proxykv_destroy(ctx)
 
 
+@pytest.mark.parametrize("N", [2561, 2688, 2689, 2816])
+def test_mapper_products_in_tiles_of_128_and_of_256_rows_agree(N):
+    """One layer's projection has at most 44 large tiles and takes tiles of 128 rows, as the convolution always does; that of eight layers has
+    352 and takes the large ones.  Layers whose last tile holds one row, or all, of 128, alone and among 16: the same bits.  Tokens of
+    a third window, whose rows go to two windows."""
+    case = lambda L: synth.scaled_case(synth.CASES["llama_8k"], name="tiles", L_s=L, H_kv=8, H_q=8, L_l=L, H_l=3, N=N, N_q=1, chunk=1, n_planted=0)
+    w = synth.make_mapper_weights(8, 3)
+    X, y = torch.rand(16, 8, N, generator=torch.Generator().manual_seed(N)) ** 8, []
+    for L in (1, 16):
+        ctx = _ctx(case(L), w)
+        y.append(pk.proxykv_map(ctx, X[:L].float().contiguous().cuda())[0].cpu())
+        torch.cuda.synchronize()
+        pk.proxykv_destroy(ctx)
+    assert torch.equal(y[0], y[1])
+    assert_close(y[0][None], oracle.mapper(X[:1].float(), w, 1), f"map 1 layer, N={N}")
+
+
 @pytest.mark.parametrize("L,N", [(1, 2048), (2, 1280), (2, 1281), (5, 512), (5, 513), (20, 65), (21, 65)])
 def test_mapper_where_the_small_tiles_end(L, N):
     """40 tiles of 64 rows are the last that the small tiles take: on the line and one row or layer beyond it, where half blocks begin."""
