@@ -476,8 +476,8 @@ __global__ __launch_bounds__(256, 2) void gemm_f16_tile_kernel(const uint16_t* _
 // [16 rows][32 of d]; v: [32 keys][16 of d].  ao: [block][16 rows][32 columns], the next product's fragments.
 // Computes S^T = K Q^T so that a lane owns one query column; P^T then feeds the second MFMA as its
 // B operand straight from the accumulator registers, with V^T fragments as the A operand.
-// 256 threads; a workgroup owns 256 queries of one (window, head), a wave 64 of them (four 16-column
-// sub-tiles); keys stream in tiles of 64, copied as they lie, by loads that write LDS, into four LDS stages (K, then V, 8 KB
+// 256 threads; a workgroup owns 64 QT queries of one (window, head), a wave 16 QT of them (QT 16-column
+// sub-tiles: four, or two, narrow_attention_pays); keys stream in tiles of 64, copied as they lie, by loads that write LDS, into four LDS stages (K, then V, 8 KB
 // each) with one barrier per tile: while tile t is computed, tile t+1 lies there and t+2 and t+3 are on their way.
 // A column's reference is the largest logit of its first 64 keys, raised in any later tile whose largest exceeds it by more than 2^8, so a
 // tile costs the same wherever the sharp keys lie.  (Left out of the later tiles, with a second pass over the keys where a row sum
@@ -486,10 +486,11 @@ __global__ __launch_bounds__(256, 2) void gemm_f16_tile_kernel(const uint16_t* _
 // 36 843, 14 122 and 2476.)
 // Layer b of the batch owns rows [b * Tp, b * Tp + T); its windows start every 2048 rows.  What the 64 rows of a layer's last row hold beyond
 // it is finite, and keys there are masked; rows behind are not read as keys, and queries there are computed and dropped.
-// Block -> work mapping: blocks are dealt round-robin to the 8 XCDs, so with n_qb blocks of 256 queries per window block
+// Block -> work mapping: blocks are dealt round-robin to the 8 XCDs, so with n_qb workgroups per window block
 // b takes q-block (b / 8) % n_qb of item (b / 8 / n_qb) * 8 + b % 8: the q-blocks of one (window, head) run on one XCD
 // and share its L2 copy of that head's K and V.
 // ------------------------------------------------------------------------------------------
+template <int QT>
 __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* __restrict__ qkv,
                                                                    u32x4* __restrict__ ao, int T, int Tp, int n_win, int n_qb) {
   __shared__ u32x4 lds[4 * 1024];
@@ -499,25 +500,25 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
   const int layer = wg / n_win, wk = wg % n_win;
   const size_t blk0 = ((size_t)layer * Tp + (size_t)wk * kWin) / kBlk;  // the window's first block of rows
   const int len = (wk < n_win - 1) ? kWin : T - wk * kWin;
-  const int i0 = (bj % n_qb) * 256;
+  const int i0 = (bj % n_qb) * (64 * QT);
   if (i0 >= len) return;
   constexpr float c = 1.4426950408889634f * 0.125f;  // log2(e) / sqrt(64)
 
   const u32x4* hbase = qkv + (blk0 * kHeads + hd) * 3 * 1024;
   constexpr size_t kBlkStride = kHeads * 3 * 1024;
-  const int q0 = (i0 >> 4) + wave * 4;  // the wave's first tile of 16 queries; its four lie in one block
+  const int q0 = (i0 >> 4) + wave * QT;  // the wave's first tile of 16 queries; all of them lie in one block
   const u32x4* qb = hbase + (size_t)(q0 >> 3) * kBlkStride + (q0 & 7) * 2 * 64 + lane;
-  f16x8 bq[4][2];
+  f16x8 bq[QT][2];
 #pragma unroll
-  for (int qt = 0; qt < 4; ++qt)
+  for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
     for (int kk = 0; kk < 2; ++kk) bq[qt][kk] = as_f16x8(qb[(qt * 2 + kk) * 64]);
-  f32x4 o[4][4];  // [16 of d][query sub-tile]
+  f32x4 o[4][QT];  // [16 of d][query sub-tile]
   // Row sums: one more product, ones times P^T, whose sixteen rows are all the sum.  (Two probabilities per v_dot2 took half as many vector
   // instructions as the exponentials.)  It takes the probabilities as the second product sees them, rounded to half.
-  f32x4 ls[4];
+  f32x4 ls[QT];
   const f16x8 ones = {(_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f, (_Float16)1.0f};
-  float m_run[4], beyond[4];  // reference, times c; the logit that raises it
+  float m_run[QT], beyond[QT];  // reference, times c; the logit that raises it
 
   const int n_tiles = (len + 63) / 64;
   typedef const __attribute__((address_space(1))) void* gptr_t;
@@ -551,15 +552,15 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
     const int j0 = t * 64;
 
     // S^T tiles: s[kt][qt] = K[kt] Q[qt]^T, 16 keys each
-    f32x4 s[4][4];
+    f32x4 s[4][QT];
     read_k(st, 2, fb);
 #pragma unroll
     for (int d = 0; d < 4; ++d) fv[d] = as_f16x8(st[512 + d * 64]);
     auto logits = [&](int kt, const f16x8 (&fk)[2]) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) s[kt][q] = mfma_f16_16x16x32(fk[0], bq[q][0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+      for (int q = 0; q < QT; ++q) s[kt][q] = mfma_f16_16x16x32(fk[0], bq[q][0], f32x4{0.0f, 0.0f, 0.0f, 0.0f});
 #pragma unroll
-      for (int q = 3; q >= 0; --q) s[kt][q] = mfma_f16_16x16x32(fk[1], bq[q][1], s[kt][q]);
+      for (int q = QT - 1; q >= 0; --q) s[kt][q] = mfma_f16_16x16x32(fk[1], bq[q][1], s[kt][q]);
     };
     logits(0, fa[0]);
     logits(1, fa[1]);
@@ -571,30 +572,30 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
 #pragma unroll
       for (int kt = 0; kt < 4; ++kt)
 #pragma unroll
-        for (int qt = 0; qt < 4; ++qt)
+        for (int qt = 0; qt < QT; ++qt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) s[kt][qt][i] = kt * 16 + i < lim ? s[kt][qt][i] : kNegInf;
     }
     // the largest logits, or what they have to exceed: of the first 32 keys while the products of the others are on their way
-    float tmax[4];
+    float tmax[QT];
     bool raise = false;
 #pragma unroll
-    for (int qt = 0; qt < 4; ++qt) {
+    for (int qt = 0; qt < QT; ++qt) {
       tmax[qt] = max3f(beyond[qt], s[0][qt][0], s[0][qt][1]);
       tmax[qt] = max3f(tmax[qt], s[0][qt][2], s[0][qt][3]);
       tmax[qt] = max3f(tmax[qt], s[1][qt][0], s[1][qt][1]);
     }
     if constexpr (!decltype(cut)::value) {
 #pragma unroll
-      for (int i = 0; i < 12; ++i) {
+      for (int i = 0; i < 3 * QT; ++i) {
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
         __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);  // one vector instruction
       }
-      __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);
+      __builtin_amdgcn_sched_group_barrier(0x008, QT, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
-    for (int qt = 0; qt < 4; ++qt) {
+    for (int qt = 0; qt < QT; ++qt) {
       tmax[qt] = max3f(tmax[qt], s[1][qt][2], s[1][qt][3]);
       tmax[qt] = max3f(tmax[qt], s[2][qt][0], s[2][qt][1]);
       tmax[qt] = max3f(tmax[qt], s[2][qt][2], s[2][qt][3]);
@@ -605,7 +606,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
     // a column's logits lie in four lanes; only where one of them is beyond the reference do they have to agree on a new one
     if (__builtin_amdgcn_ballot_w64(raise)) {
 #pragma unroll
-      for (int qt = 0; qt < 4; ++qt) {
+      for (int qt = 0; qt < QT; ++qt) {
         const float tm = quads_max(tmax[qt]);
         const bool up = tm > beyond[qt];
         const float nm = up ? tm * c : m_run[qt];
@@ -619,25 +620,26 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
         m_run[qt] = nm;
       }
     }
-    // Four steps of 32 keys and 32 queries.  A wave issues in order, so an MFMA that finds the matrix pipe busy holds back the vector
+    // Four (two) steps of 32 keys and 32 queries.  A wave issues in order, so an MFMA that finds the matrix pipe busy holds back the vector
     // instructions behind it: the ten MFMAs of step u-1 are therefore spread between the vector instructions of
     // step u (one MFMA, then a tenth of the step's exponentials and conversions), each finding the pipe free.
+    constexpr int QH = QT / 2;
     f16x8 pb[2][2];  // [step parity][query sub-tile of the step]
-    static_for<5>([&](auto uc) {
+    static_for<2 * QH + 1>([&](auto uc) {
       constexpr int u = decltype(uc)::value;
       if constexpr (u > 0) {
-        constexpr int qh = (u - 1) & 1;
+        constexpr int qh = (u - 1) % QH;
 #pragma unroll
         for (int d = 0; d < 4; ++d) {
 #pragma unroll
           for (int i = 0; i < 2; ++i) o[d][qh * 2 + i] = mfma_f16_16x16x32(fv[d], pb[(u - 1) & 1][i], o[d][qh * 2 + i]);
-          if constexpr (u == 2) fv[d] = as_f16x8(st[512 + (4 + d) * 64]);
+          if constexpr (u == QH) fv[d] = as_f16x8(st[512 + (4 + d) * 64]);
         }
 #pragma unroll
         for (int i = 0; i < 2; ++i) ls[qh * 2 + i] = mfma_f16_16x16x32(ones, pb[(u - 1) & 1][i], ls[qh * 2 + i]);
       }
-      if constexpr (u < 4) {
-        constexpr int p = u >> 1, qh = u & 1;
+      if constexpr (u < 2 * QH) {
+        constexpr int p = u / QH, qh = u % QH;
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
           constexpr int q2 = qh * 2;
@@ -661,7 +663,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
     });
   };
 #pragma unroll
-  for (int qt = 0; qt < 4; ++qt) {
+  for (int qt = 0; qt < QT; ++qt) {
 #pragma unroll
     for (int d = 0; d < 4; ++d) o[d][qt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
     m_run[qt] = beyond[qt] = -1.0e30f;
@@ -680,7 +682,7 @@ __global__ __launch_bounds__(256, 2) void window_attention_kernel(const u32x4* _
 
   // output: O^T / row sum; a lane's eight accumulators are the unit that the next product's operand wants from it
 #pragma unroll
-  for (int qt = 0; qt < 4; ++qt) {
+  for (int qt = 0; qt < QT; ++qt) {
     const float inv = 1.0f / ls[qt][0];
     const int tile = q0 + qt;
     if (tile * 16 >= n_tiles * 64) continue;
@@ -791,6 +793,16 @@ hipError_t launch_gemm(const uint16_t* A, int lda, const uint16_t* W, const RowS
   return hipGetLastError();
 }
 
+// 128 queries per workgroup instead of 256?  `wide` workgroups of 256 and `narrow` ones of 128 in all lanes.  Two narrow ones read twice the
+// keys that one wide does and take up to a tenth longer, but a CU runs two side by side: where wide ones would have it to
+// themselves, a wave per SIMD and nothing beside its chain of products and exponentials, or where one lane's leave half of the CUs one and
+// half two, the narrow ones are faster; and where a window's last wide one is mostly beyond it, a tenth fewer are computed.  Mapper, us, wide /
+// narrow: one layer of 2600 tokens (wide 120) 744 / 671, of 3500 (176) 753 / 715, of 7000 (376) 946 / 918, of 8000 (448) 987 / 1021; 16 of
+// 600 (384, narrow 640) 714 / 696, of 800 (512, 896) 819 / 796, of 1100 (640, 1152) 1139 / 1112, of 1000 (512, 1024) 946 / 960.
+inline bool narrow_attention_pays(int64_t wide, int64_t narrow, int lanes) {
+  return wide <= (lanes == 1 ? 384 : 256) || 5 * narrow <= 9 * wide;
+}
+
 // Second stem convolution, encoder and stage-3 inner products of one batch with the large tiles: from h1 to s3.
 hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const MapPlan& p, int n_layers, int64_t N, int n_cu, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
@@ -814,11 +826,17 @@ hipError_t mapper_large_body(proxykv_ctx* ctx, const MapperWorkspace& ws, const 
   PKV_TRY(launch_gemm<kEpiGeluPeWin>(m.h1, c.c_mid, w.conv2_w, rows_conv, kDT, 3 * c.c_mid, e2, n_cu, stream));
 
   // stage 2 (the stem's epilogue has written its input rows)
-  const int n_qb = ((T < kWin ? T : kWin) + 255) / 256;
+  const int tail = T - (n_win - 1) * kWin;
+  auto in_window = [](int len, int q) { return (len + q - 1) / q; };
+  auto workgroups = [&](int q) { return (int64_t)nl * p.lanes * kHeads * ((n_win - 1) * in_window(kWin, q) + in_window(tail, q)); };
+  const bool narrow = narrow_attention_pays(workgroups(256), workgroups(128), p.lanes);
+  const int n_qb = in_window(T < kWin ? T : kWin, narrow ? 128 : 256);
   for (int li = 0; li < c.n_enc_layers; ++li) {
     PKV_TRY(launch_encoder_block(ctx, p, n_layers, li, m.x, m.xb, m.qk, stream));
-    window_attention_kernel<<<nl * (unsigned)(n_win * kHeads * n_qb), 256, 0, stream>>>(
-        reinterpret_cast<const u32x4*>(m.qk), reinterpret_cast<u32x4*>(m.xb), T, Tp, n_win, n_qb);
+    const u32x4* qkv = reinterpret_cast<const u32x4*>(m.qk);
+    u32x4* ao = reinterpret_cast<u32x4*>(m.xb);
+    auto* attention = narrow ? window_attention_kernel<2> : window_attention_kernel<4>;
+    attention<<<nl * (unsigned)(n_win * kHeads * n_qb), 256, 0, stream>>>(qkv, ao, T, Tp, n_win, n_qb);
     PKV_TRY(hipGetLastError());
   }
   if (c.n_enc_layers > 0) PKV_TRY(launch_encoder_block(ctx, p, n_layers, c.n_enc_layers, m.x, m.xb, m.qk, stream));

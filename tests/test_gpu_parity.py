@@ -705,6 +705,22 @@ def test_mapper_products_in_tiles_of_128_and_of_256_rows_agree(N):
     assert_close(y[0][None], oracle.mapper(X[:1].float(), w, 1), f"map 1 layer, N={N}")
 
 
+@pytest.mark.parametrize("few,many,N", [(4, 24, 1000), (4, 24, 961), (2, 16, 2303), (2, 16, 3072)])
+def test_mapper_attention_of_128_and_of_256_queries_agree(few, many, N):
+    """The attention of few layers, at most 256 workgroups of 256 queries, is given to twice as many; that of many layers is not.  A
+    window's queries end in a workgroup's first wave, or its last; the same bits either way."""
+    case = lambda L: synth.scaled_case(synth.CASES["llama_8k"], name="queries", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=N, N_q=1, chunk=1, n_planted=0)
+    w = synth.make_mapper_weights(2, 4)
+    X, y = torch.rand(many, 2, N, generator=torch.Generator().manual_seed(N)) ** 8, []
+    for L in (few, many):
+        ctx = _ctx(case(L), w)
+        y.append(pk.proxykv_map(ctx, X[:L].float().contiguous().cuda())[:few].cpu())
+        torch.cuda.synchronize()
+        pk.proxykv_destroy(ctx)
+    assert torch.equal(y[0], y[1])
+    assert_close(y[0][:1], oracle.mapper(X[:few].float(), w, few, layers=[0])[:1], f"map {few} layers, N={N}")
+
+
 @pytest.mark.parametrize("L,N", [(1, 2048), (2, 1280), (2, 1281), (5, 512), (5, 513), (20, 65), (21, 65)])
 def test_mapper_where_the_small_tiles_end(L, N):
     """40 tiles of 64 rows are the last that the small tiles take: on the line and one row or layer beyond it, where half blocks begin."""
