@@ -159,7 +159,7 @@ int proxykv_map(proxykv_ctx* ctx, const float* x, int64_t N, float* yhat, void* 
  * Keeps the K entries that come first under the total order (higher score first, equal scores by
  * lower index; -0.0 == +0.0; NaN below every number) and writes their indices in ascending order.
  * A row of up to 36 864 scores is selected by one workgroup; a longer row is split over several, which meet in
- * per-row histograms in the context's workspace (then rows <= 65535, PROXYKV_EUNSUPPORTED otherwise). */
+ * histograms in the context's workspace (then rows <= 65535, PROXYKV_EUNSUPPORTED otherwise). */
 int proxykv_topk(proxykv_ctx* ctx, const float* scores, int64_t rows, int64_t N, int64_t K,
                  int32_t* idx_out, void* stream);
 
@@ -194,6 +194,8 @@ int proxykv_compact(proxykv_ctx* ctx, const void* k_in, const void* v_in, const 
  * source and destination.  Afterwards tokens 0 .. K-1 of every row are the kept tokens in order
  * (k[r, j, :] = old k[r, idx[r, j], :]); tokens K .. N-1 are left as they were.  idx [rows, K] must be
  * strictly ascending within a row (as proxykv_topk writes it): the kernel relies on idx[r, j] >= j.
+ * Rows that keep much are moved by several workgroups each, which use a few words of the context's workspace; without
+ * room for them (or, while `stream` captures, without a reserve) a row is moved by fewer, slower, with the same result.
  * D*2 bytes a multiple of 16 and at most 512. */
 int proxykv_compact_inplace(proxykv_ctx* ctx, void* k, void* v, const int32_t* idx, int64_t rows,
                             int64_t N, int64_t K, int64_t D, void* stream);
