@@ -499,7 +499,10 @@ int proxykv_set_mapper_weights(proxykv_ctx* ctx, const float* blob, size_t n_flo
   const float* c1w = take(C1 * Hs * 3);
   const float* c1b = take(C1);
   const float *g1 = take(C1), *b1 = take(C1), *m1 = take(C1), *v1 = take(C1);
-  const size_t o_c1w = st.put_f32(c1w, C1 * Hs * 3);
+  std::vector<float> c1t(C1 * Hs * 3);  // a channel's weights lie C1 apart: the kernel's lanes are channels
+  for (size_t ch = 0; ch < C1; ++ch)
+    for (size_t i = 0; i < Hs * 3; ++i) c1t[i * C1 + ch] = c1w[ch * Hs * 3 + i];
+  const size_t o_c1w = st.put_f32(c1t.data(), c1t.size());
   size_t o_s1, o_h1;
   fold(c1b, g1, b1, m1, v1, C1, &o_s1, &o_h1);
   // bound of the first block's output, |GELU(y)| <= |y| <= |scale_c| * sum |w_c| * max|x| + |shift_c|

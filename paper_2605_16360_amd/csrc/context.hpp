@@ -31,7 +31,7 @@ struct EncoderLayerWeights {
 };
 
 struct MapperWeights {
-  const float* conv1_w;                  // fp32 [c_mid, H_kv*3]
+  const float* conv1_w;                  // fp32 [H_kv*3, c_mid]
   const float *bn1_scale, *bn1_shift;    // batch norm and conv bias folded: y = conv * scale + shift
   float stem_cw = 0.0f, stem_cs = 0.0f;  // |first conv block's output| <= stem_cw * max|x| + stem_cs (host values)
   const uint16_t* conv2_w;               // fp16 [d_time, 3*c_mid], k index = tap * c_mid + channel

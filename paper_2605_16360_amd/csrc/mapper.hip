@@ -48,6 +48,8 @@ __global__ __launch_bounds__(1024) void absmax_kernel(const float* __restrict__ 
 // grid (ceil(N / tok), layers), 256 threads; thread owns channels tid, tid+256, ...  tok <= 64 tokens per workgroup: a
 // workgroup's tokens are a serial chain, so short inputs take fewer of them (512 tokens of one layer: 23.6 us with 64
 // tokens per workgroup, eight workgroups on 256 CUs, 8.3 with 16 and 5.0 with 4; from 8192 tokens on 16 give every CU two).
+// The weights lie [H_s * 3][c_mid], so a wave's load is 256 bytes in one piece; with a channel's side by side each touched 48 lines, and
+// eight layers of 600 tokens, 1200 workgroups of four tokens, took 22.1 us instead of 11.0, of 1500 21.0 / 14.4.
 // ------------------------------------------------------------------------------------------
 constexpr int kStemTok = 64;
 constexpr int kMaxHs = 16;
@@ -71,7 +73,7 @@ __global__ __launch_bounds__(256) void stem_conv1_kernel(const float* __restrict
   for (int c = threadIdx.x; c < c_mid; c += 256) {
     float wr[kMaxHs * 3];
 #pragma unroll
-    for (int i = 0; i < kMaxHs * 3; ++i) wr[i] = (i < H_s * 3) ? w[(size_t)c * H_s * 3 + i] : 0.0f;
+    for (int i = 0; i < kMaxHs * 3; ++i) wr[i] = (i < H_s * 3) ? w[i * c_mid + c] : 0.0f;
     const float sc = scale[c], sh = shift[c];
     for (int tt = 0; tt < tok && t0 + tt < N; ++tt) {
       float acc = 0.0f;
