@@ -10,9 +10,6 @@
 #include "context.hpp"
 #include "kernels.hpp"
 
-// (a runtime that records no graphs need not have it)
-extern "C" hipError_t hipStreamIsCapturing(hipStream_t stream, hipStreamCaptureStatus* status) __attribute__((weak));
-
 using pkv::DeviceBuffer;
 
 namespace {
@@ -73,15 +70,15 @@ void free_lanes(proxykv_ctx* ctx) {
   ctx->map_len = 0;
 }
 
-// `need`: the mapper's workspace is given up where that makes room
 // whether `stream` records a graph (or it cannot be told)
 bool capturing(hipStream_t stream) {
-  if (hipStreamIsCapturing == nullptr) return false;
   hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
   (void)hipGetLastError();
   return true;
 }
+
+// `need`: the mapper's workspace is given up where that makes room
 int ensure(proxykv_ctx* ctx, DeviceBuffer& b, size_t bytes, hipStream_t stream, bool need = true) {
   if (bytes <= b.bytes) return PROXYKV_OK;
   if (b.ptr) {
@@ -248,11 +245,14 @@ int reserve_topk(proxykv_ctx* ctx, int64_t rows, int64_t N, hipStream_t stream) 
   if (rc == PROXYKV_ENOMEM) rc = ensure(ctx, ctx->topk_ws, least, stream);
   return rc;
 }
-// The in-place compaction's counters lie where the Top-K's do.  Where there is no memory for them, or a capture is under way, in which nothing can
-// be allocated, it does without.
-void reserve_inplace(proxykv_ctx* ctx, int64_t rows, int64_t K, int64_t row_bytes, int heads, hipStream_t stream) {
+// The in-place compaction's counters lie where the Top-K's do; nothing where it moves whole rows without them: where rows are short, where there is no
+// memory, and while the stream captures.  A graph may be replayed after a later call has moved that workspace, and after the context is gone,
+// so a captured call holds the caller's pointers only.  (Half of 512 rows of 12 345 tokens, 652 us replayed instead of 548.)
+DeviceBuffer inplace_counters(proxykv_ctx* ctx, int64_t rows, int64_t K, int64_t row_bytes, int heads, hipStream_t stream) {
   const size_t need = pkv::compact_inplace_scratch_bytes(rows, K, row_bytes, heads);
-  if (need > ctx->topk_ws.bytes && !capturing(stream)) (void)ensure(ctx, ctx->topk_ws, need, stream, false);
+  if (need == 0 || capturing(stream)) return {};
+  if (need > ctx->topk_ws.bytes) (void)ensure(ctx, ctx->topk_ws, need, stream, false);
+  return ctx->topk_ws;
 }
 // ... for any number of kept tokens of this context's rows, with a budget per head or per layer
 size_t inplace_bytes(const proxykv_config& c, int64_t N) {
@@ -724,8 +724,8 @@ int proxykv_compact_inplace(proxykv_ctx* ctx, void* k, void* v, const int32_t* i
   if (rows <= 0 || N <= 0 || N >= (1ll << 31) || K < 1 || K > N || D <= 0) return PROXYKV_EINVAL;
   if ((D * 2) % 16 != 0 || D * 2 > 512) return PROXYKV_EUNSUPPORTED;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  reserve_inplace(ctx, rows, K, D * 2, 1, (hipStream_t)stream);
-  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, idx, rows, N, K, D * 2, nullptr, 1, ctx->topk_ws.ptr, ctx->topk_ws.bytes, (hipStream_t)stream));
+  const DeviceBuffer counters = inplace_counters(ctx, rows, K, D * 2, 1, (hipStream_t)stream);
+  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, idx, rows, N, K, D * 2, nullptr, 1, counters.ptr, counters.bytes, (hipStream_t)stream));
   return PROXYKV_OK;
 }
 
@@ -750,8 +750,8 @@ int proxykv_compact_pooled(proxykv_ctx* ctx, void* k, void* v, const int32_t* fl
   if (layers * heads >= (1ll << 31) || heads * N >= (1ll << 31) - 4096) return PROXYKV_EINVAL;
   if ((D * 2) % 16 != 0 || D * 2 > 512) return PROXYKV_EUNSUPPORTED;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  reserve_inplace(ctx, layers * heads, K, D * 2, (int)heads, (hipStream_t)stream);
-  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, flat, layers * heads, N, K, D * 2, counts, (int)heads, ctx->topk_ws.ptr, ctx->topk_ws.bytes, (hipStream_t)stream));
+  const DeviceBuffer counters = inplace_counters(ctx, layers * heads, K, D * 2, (int)heads, (hipStream_t)stream);
+  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, flat, layers * heads, N, K, D * 2, counts, (int)heads, counters.ptr, counters.bytes, (hipStream_t)stream));
   return PROXYKV_OK;
 }
 

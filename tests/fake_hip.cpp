@@ -13,7 +13,7 @@ struct dim3 {
 enum { kSuccess = 0, kOutOfMemory = 2, kInvalidConfiguration = 9 };
 
 static size_t g_budget = ~(size_t)0, g_used = 0, g_peak = 0;
-static int g_mallocs = 0;
+static int g_mallocs = 0, g_capturing = 0;
 static uintptr_t g_next = (uintptr_t)1 << 40;
 static std::map<uintptr_t, size_t> g_live;
 static std::map<const void*, std::string>& names() {
@@ -29,6 +29,7 @@ void fake_budget(size_t bytes) { g_budget = bytes; }
 size_t fake_used() { return g_used; }
 size_t fake_peak() { return g_peak; }
 int fake_mallocs() { return g_mallocs; }
+void fake_capturing(int on) { g_capturing = on; }  // every stream
 const char* fake_launches() {  // since the last call, "name gx gy gz bx\n" each
   static std::string out;
   out.swap(g_log);
@@ -80,6 +81,10 @@ int hipStreamCreateWithFlags(void** s, unsigned) {
   return kSuccess;
 }
 int hipStreamDestroy(void*) { return kSuccess; }
+int hipStreamIsCapturing(void*, int* status) {
+  *status = g_capturing;
+  return kSuccess;
+}
 int hipStreamWaitEvent(void*, void*, unsigned) { return kSuccess; }
 int hipEventCreate(void** e) { return hipStreamCreateWithFlags(e, 0); }
 int hipEventCreateWithFlags(void** e, unsigned) { return hipStreamCreateWithFlags(e, 0); }

@@ -225,7 +225,7 @@ def test_compact_inplace_in_parts_of_a_row(D, rows, counts):
 
 
 def test_compact_inplace_in_a_graph_and_in_a_context_without_memory():
-    """Under capture nothing can be allocated: a context that has its counters replays parts, one that does not whole rows; both as eagerly."""
+    """A graph moves whole rows, with the caller's pointers alone, whether the context that captures has room for an eager call's counters or not."""
     g = torch.Generator().manual_seed(5)
     rows, N, K, D = 4, 5000, 3000, 128
     idx = torch.stack([torch.randperm(N, generator=g)[:K].sort().values for _ in range(rows)]).to(torch.int32).view(1, rows, K).cuda()
@@ -248,6 +248,34 @@ def test_compact_inplace_in_a_graph_and_in_a_context_without_memory():
             assert torch.equal(kv[:, :, :, :K], want) and torch.equal(kv[:, :, :, K:], src[:, :, :, K:]), warm
         del graph
         pk.proxykv_destroy(ctx)
+
+
+def test_graph_of_an_in_place_compaction_outlives_its_context():
+    """Captured by a context that has counters, replayed after longer calls have made its workspace grow, and after it is destroyed, with other
+    memory taken in between: the same tokens."""
+    g = torch.Generator().manual_seed(6)
+    rows, N, K, D = 3, 6000, 4000, 128
+    idx = torch.stack([torch.randperm(N, generator=g)[:K].sort().values for _ in range(rows)]).to(torch.int32).view(1, rows, K).cuda()
+    src = torch.randn(2, 1, rows, N, D, generator=g).to(torch.bfloat16).cuda()
+    want = torch.gather(src, 3, idx.long().unsqueeze(0).unsqueeze(4).expand(2, -1, -1, -1, D))
+    ctx = _ctx(synth.CASES["tiny"])
+    pk.proxykv_compact_inplace(ctx, src[0].clone(), src[1].clone(), idx)
+    kv = src.clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pk.proxykv_compact_inplace(ctx, kv[0], kv[1], idx)
+    taken = []
+    for step in range(3):
+        if step == 1:
+            pk.proxykv_topk(ctx, torch.randn(1, 40, 300000, device="cuda"), 1000)
+        if step == 2:
+            pk.proxykv_destroy(ctx)
+        taken.append(torch.full((1 << 22,), 255, dtype=torch.uint8, device="cuda"))
+        kv.copy_(src)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(kv[:, :, :, :K], want) and torch.equal(kv[:, :, :, K:], src[:, :, :, K:]), step
 
 
 def test_pooled_compaction_of_many_heads_in_parts():

@@ -344,3 +344,27 @@ def test_in_place_compaction_of_short_rows_has_more_workgroups():
             out[f"{layers} {heads}"] = [l[1:3] for l in launches("compact_inplace_kernel")]
     """)
     assert out == {"256 512": [[256, 4]], "256 513": [[256, 2]], "255 600": [[255, 4]], "64 4": [[256, 2]], "51 5": [[255, 4]]}
+
+
+def test_a_captured_in_place_compaction_holds_nothing_of_the_context():
+    """A graph may outlive what the context's calls behind it grow, and the context itself: a captured call moves whole rows with the caller's
+    pointers alone, also where the context has room for the counters of an eager one, which uses them."""
+    out = run("""
+        out = []
+        h = context(LLAMA)
+        for reserved in (False, True):
+            if reserved:
+                assert lib.proxykv_reserve(h, 8192, 8192) == 0
+            for pooled in (False, True):
+                for capturing in (0, 1, 0):
+                    fake.fake_capturing(capturing)
+                    launches()
+                    before = fake.fake_mallocs()
+                    rc = (lib.proxykv_compact_pooled(h, P, P, P, P, 32, 8, 8192, 4096, 128, None) if pooled else
+                          lib.proxykv_compact_inplace(h, P, P, P, 256, 8192, 4096, 128, None))
+                    names = "".join(sorted(l[0] for l in launches()))
+                    out.append((rc, capturing, "compact_parts_kernel" in names, "compact_inplace_kernel" in names, capturing and fake.fake_mallocs() - before))
+    """)
+    assert len(out) == 12
+    for rc, capturing, parts, whole, mallocs in out:
+        assert (rc, parts, whole, mallocs) == (0, not capturing, bool(capturing), 0), out
