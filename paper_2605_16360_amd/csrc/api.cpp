@@ -245,14 +245,23 @@ int reserve_topk(proxykv_ctx* ctx, int64_t rows, int64_t N, hipStream_t stream) 
   if (rc == PROXYKV_ENOMEM) rc = ensure(ctx, ctx->topk_ws, least, stream);
   return rc;
 }
-// The in-place compaction's counters lie where the Top-K's do; nothing where it moves whole rows without them: where rows are short, where there is no
-// memory, and while the stream captures.  A graph may be replayed after a later call has moved that workspace, and after the context is gone,
-// so a captured call holds the caller's pointers only.  (Half of 512 rows of 12 345 tokens, 652 us replayed instead of 548.)
+// Room for the in-place compaction's counters.  Where there is none, what was there stays.
+bool reserve_inplace(proxykv_ctx* ctx, size_t bytes, hipStream_t stream) {
+  if (bytes <= ctx->inplace_ws.bytes) return true;
+  void* p = nullptr;
+  if (!hip_ok(ctx, hipMalloc(&p, bytes))) return false;
+  if (ctx->inplace_ws.ptr) (void)hipStreamSynchronize(stream);
+  free_buffer(ctx->inplace_ws);
+  ctx->inplace_ws = {p, bytes};
+  return true;
+}
+// The counters of a call; nothing where it moves whole rows without them: where rows are short, where there is no memory, and while the
+// stream captures.  A graph may be replayed after a later call has moved that workspace, and after the context is gone, so
+// a captured call holds the caller's pointers only.  (Half of 512 rows of 12 345 tokens, 652 us replayed instead of 548.)
 DeviceBuffer inplace_counters(proxykv_ctx* ctx, int64_t rows, int64_t K, int64_t row_bytes, int heads, hipStream_t stream) {
   const size_t need = pkv::compact_inplace_scratch_bytes(rows, K, row_bytes, heads);
-  if (need == 0 || capturing(stream)) return {};
-  if (need > ctx->topk_ws.bytes) (void)ensure(ctx, ctx->topk_ws, need, stream, false);
-  return ctx->topk_ws;
+  if (need == 0 || capturing(stream) || !reserve_inplace(ctx, need, stream)) return {};
+  return ctx->inplace_ws;
 }
 // ... for any number of kept tokens of this context's rows, with a budget per head or per layer
 size_t inplace_bytes(const proxykv_config& c, int64_t N) {
@@ -438,7 +447,7 @@ int proxykv_create(proxykv_ctx** out, const proxykv_config* cfg) {
 int proxykv_destroy(proxykv_ctx* ctx) {
   if (!ctx) return PROXYKV_OK;
   std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->block_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
-                                    &ctx->neg_lse, &ctx->x_parts, &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws};
+                                    &ctx->neg_lse, &ctx->x_parts, &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws, &ctx->inplace_ws};
   for (pkv::MapperWorkspace& m : ctx->m) {
     DeviceBuffer* b[kLaneBuffers];
     lane_buffers(m, b);
@@ -627,8 +636,7 @@ int proxykv_workspace_bytes(const proxykv_config* cfg, int64_t N, int64_t N_q, s
   const Sizes s = workspace_sizes(*cfg, N, N_q);
   const pkv::MapPlan p = pkv::map_plan(*cfg, N, distinct);
   const LaneBytes lb = lane_bytes(*cfg, p);
-  const size_t topk = pkv::topk_scratch_bytes((int64_t)cfg->L_l * cfg->H_l, N), inplace = inplace_bytes(*cfg, N);
-  size_t total = s.neg_lse + s.x_parts + s.x_ws + s.yhat_ws + (topk > inplace ? topk : inplace);
+  size_t total = s.neg_lse + s.x_parts + s.x_ws + s.yhat_ws + pkv::topk_scratch_bytes((int64_t)cfg->L_l * cfg->H_l, N) + inplace_bytes(*cfg, N);
   for (int lane = 0; lane < p.lanes; ++lane)
     for (int i = 0; i < kLaneBuffers; ++i) total += lane_need(*cfg, p, lb, lane, distinct, i);
   *out_bytes = total;
@@ -642,7 +650,7 @@ int proxykv_reserve(proxykv_ctx* ctx, int64_t N, int64_t N_q) {
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
   if ((rc = reserve_score(ctx, N, N_q, true, nullptr))) return rc;  // (proxykv_score_self has parts in any context)
   if ((rc = reserve_prune(ctx, N, nullptr))) return rc;
-  (void)ensure(ctx, ctx->topk_ws, inplace_bytes(ctx->cfg, N), nullptr, false);
+  (void)reserve_inplace(ctx, inplace_bytes(ctx->cfg, N), nullptr);  // (in-place calls do without)
   pkv::MapPlan p;
   return reserve_map(ctx, N, nullptr, &p);  // last: it makes do with what is left
 }

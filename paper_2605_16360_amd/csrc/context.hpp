@@ -93,7 +93,8 @@ struct proxykv_ctx {
   size_t parts_short = 0;                          // bytes of x_parts that the device did not have
   pkv::DeviceBuffer x_ws;                          // fp32 [L_s, H_kv, N]
   pkv::DeviceBuffer yhat_ws;                       // fp32 [L_l, H_l, N]
-  pkv::DeviceBuffer topk_ws;                       // state of Top-K and in-place compaction where workgroups share a row
+  pkv::DeviceBuffer topk_ws;                       // state of Top-K where workgroups share a row
+  pkv::DeviceBuffer inplace_ws;                    // ... of the in-place compaction
   bool topk_short = false;                         // memory was short: topk_ws has no masks, or only the narrower histograms
   bool fused_select = false;                       // proxykv_prune: selection and gather in one launch (measured slower)
   pkv::MapperWorkspace m[pkv::kMapLanes];          // one per lane; only the lanes a length needs are allocated

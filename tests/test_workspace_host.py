@@ -368,3 +368,26 @@ def test_a_captured_in_place_compaction_holds_nothing_of_the_context():
     assert len(out) == 12
     for rc, capturing, parts, whole, mallocs in out:
         assert (rc, parts, whole, mallocs) == (0, not capturing, bool(capturing), 0), out
+
+
+def test_in_place_counters_take_nothing_from_the_topk():
+    """Where there is no memory for the in-place compaction's counters (15 MB of them here) the call moves whole rows, and the Top-K's workspace stays: rows
+    that fitted before are selected without an allocation, on the narrow histograms too."""
+    out = run("""
+        out = []
+        for narrow in (False, True):
+            for pooled in (False, True):
+                h = context(LLAMA)
+                fake.fake_budget(fake.fake_used() + (1000 * 1000 if narrow else 1 << 40))
+                assert lib.proxykv_topk(h, P, 40, 60000, 9, P, None) == 0
+                fake.fake_budget(fake.fake_used() + 1000)
+                launches()
+                rc = (lib.proxykv_compact_pooled(h, P, P, P, P, 8000, 5, 40000, 30000, 128, None) if pooled else
+                      lib.proxykv_compact_inplace(h, P, P, P, 40000, 40000, 30000, 128, None))
+                whole = len(launches("compact_inplace_kernel"))
+                before = fake.fake_mallocs()
+                again = lib.proxykv_topk(h, P, 40, 60000, 9, P, None)
+                out.append((rc, whole, again, fake.fake_mallocs() - before))
+                fake.fake_budget((1 << 63) - 1)
+    """)
+    assert out == [[0, 1, 0, 0]] * 4
