@@ -29,7 +29,8 @@
  *     A graph that has captured calls holds the addresses of that workspace and of the weights: it is replayed before a
  *     longer call makes the workspace grow, new weights are set or the context is destroyed, not behind that.  Captured
  *     calls of proxykv_compact, proxykv_compact_inplace, proxykv_compact_pooled and proxykv_mask hold nothing of the context.
- *     One context serves one stream at a time; concurrent calls on one context race.
+ *     One context serves one stream at a time; concurrent calls on one context race.  (Not so those four: on tensors of
+ *     their own they may run from several threads and on several streams at once.)
  *   - Return value: PROXYKV_OK (0) or a negative proxykv_status.  All argument checks run before
  *     the first HIP call, so PROXYKV_EINVAL / PROXYKV_EUNSUPPORTED are returned on any machine.
  *     PROXYKV_EHIP means a HIP runtime call failed; proxykv_last_hip_error gives its code.
@@ -198,8 +199,9 @@ int proxykv_compact(proxykv_ctx* ctx, const void* k_in, const void* v_in, const 
  * (k[r, j, :] = old k[r, idx[r, j], :]); tokens K .. N-1 are left as they were.  idx [rows, K] must be
  * strictly ascending within a row (as proxykv_topk writes it): the kernel relies on idx[r, j] >= j.
  * Rows that keep much are moved by several workgroups each, which use a few words of the context's workspace; without
- * room for them a row is moved by fewer, slower, with the same result.  So it is while `stream` captures: the graph then holds
- * no memory but the caller's, and later calls on the context, or its end, do not concern it.
+ * room for them a row is moved by fewer, slower, with the same result.  So it is on streams beyond the 32 that a context
+ * has met in such calls first, on the per-thread default stream, and while `stream` captures: the graph then holds no memory but the
+ * caller's, and later calls on the context, or its end, do not concern it.
  * D*2 bytes a multiple of 16 and at most 512. */
 int proxykv_compact_inplace(proxykv_ctx* ctx, void* k, void* v, const int32_t* idx, int64_t rows,
                             int64_t N, int64_t K, int64_t D, void* stream);

@@ -245,25 +245,51 @@ int reserve_topk(proxykv_ctx* ctx, int64_t rows, int64_t N, hipStream_t stream) 
   if (rc == PROXYKV_ENOMEM) rc = ensure(ctx, ctx->topk_ws, least, stream);
   return rc;
 }
-// Room for the in-place compaction's counters.  Where there is none, what was there stays.
-bool reserve_inplace(proxykv_ctx* ctx, size_t bytes, hipStream_t stream) {
-  if (bytes <= ctx->inplace_ws.bytes) return true;
+// Room for the in-place compaction's counters, `piece` bytes for every stream.  Where there is none, what was there stays.  (The mutex is held.)
+size_t inplace_block_bytes(size_t piece) { return (piece + 255) / 256 * 256 * pkv::kInplaceStreams; }
+bool reserve_inplace(proxykv_ctx* ctx, size_t piece) {
+  pkv::InplaceCounters& c = ctx->inplace;
+  size_t bytes = inplace_block_bytes(piece);
+  if (bytes <= c.block.bytes) return true;
+  bytes = std::max(bytes, 2 * c.block.bytes);
+  if (c.block.ptr && c.n_older == (int)(sizeof(c.older) / sizeof(c.older[0]))) return false;
+  // (another stream's capture does not forbid it: nothing that is captured has to do with this memory)
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  if (!hip_ok(ctx, hipThreadExchangeStreamCaptureMode(&mode))) return false;
   void* p = nullptr;
-  if (!hip_ok(ctx, hipMalloc(&p, bytes))) return false;
-  if (ctx->inplace_ws.ptr) (void)hipStreamSynchronize(stream);
-  free_buffer(ctx->inplace_ws);
-  ctx->inplace_ws = {p, bytes};
+  const hipError_t e = hipMalloc(&p, bytes);
+  (void)hipThreadExchangeStreamCaptureMode(&mode);
+  if (!hip_ok(ctx, e)) return false;
+  if (c.block.ptr) c.older[c.n_older++] = c.block.ptr;
+  c.block = {p, bytes};
   return true;
 }
-// The counters of a call; nothing where it moves whole rows without them: where rows are short, where there is no memory, and while the
-// stream captures.  A graph may be replayed after a later call has moved that workspace, and after the context is gone, so
-// a captured call holds the caller's pointers only.  (Half of 512 rows of 12 345 tokens, 652 us replayed instead of 548.)
-DeviceBuffer inplace_counters(proxykv_ctx* ctx, int64_t rows, int64_t K, int64_t row_bytes, int heads, hipStream_t stream) {
-  const size_t need = pkv::compact_inplace_scratch_bytes(rows, K, row_bytes, heads);
-  if (need == 0 || capturing(stream) || !reserve_inplace(ctx, need, stream)) return {};
-  return ctx->inplace_ws;
+// The counters of a call on `stream`, whose calls follow each other; nullptr where there is no room for them or for another stream.  (The mutex is held.)
+void* inplace_counters(proxykv_ctx* ctx, size_t bytes, hipStream_t stream) {
+  pkv::InplaceCounters& c = ctx->inplace;
+  if (stream == hipStreamPerThread) return nullptr;  // the same handle in every thread, and not the same stream
+  int i = 0;
+  while (i < c.streams && c.stream[i] != stream) ++i;
+  if (i == pkv::kInplaceStreams || !reserve_inplace(ctx, bytes)) return nullptr;
+  if (i == c.streams) c.stream[c.streams++] = stream;
+  return (uint8_t*)c.block.ptr + c.block.bytes / pkv::kInplaceStreams * i;
 }
-// ... for any number of kept tokens of this context's rows, with a budget per head or per layer
+// Whole rows are moved without counters: where rows are short, where there are no counters to be had, and while the stream captures.  A graph may
+// be replayed on any stream, after a later call has taken other memory and after the context is gone, so a captured call holds the
+// caller's pointers only.  (Half of 512 rows of 12 345 tokens, 652 us replayed instead of 548.)
+int inplace_impl(proxykv_ctx* ctx, void* k, void* v, const int32_t* idx, int64_t rows, int64_t N, int64_t K, int64_t row_bytes, const int32_t* counts,
+                 int heads, hipStream_t stream) {
+  const size_t need = pkv::compact_inplace_scratch_bytes(rows, K, row_bytes, heads);
+  std::unique_lock<std::mutex> lock(ctx->inplace.mutex, std::defer_lock);
+  void* counters = nullptr;
+  if (need > 0 && !capturing(stream)) {
+    lock.lock();
+    counters = inplace_counters(ctx, need, stream);
+  }
+  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, idx, rows, N, K, row_bytes, counts, heads, counters, counters ? need : 0, stream));
+  return PROXYKV_OK;
+}
+// What the counters take for any number of kept tokens of this context's rows, with a budget per head or per layer
 size_t inplace_bytes(const proxykv_config& c, int64_t N) {
   if (c.D * 2 > 512) return 0;  // not for proxykv_compact_inplace
   const int64_t rows = (int64_t)c.L_l * c.H_l;
@@ -447,7 +473,7 @@ int proxykv_create(proxykv_ctx** out, const proxykv_config* cfg) {
 int proxykv_destroy(proxykv_ctx* ctx) {
   if (!ctx) return PROXYKV_OK;
   std::vector<DeviceBuffer*> all = {&ctx->weight_blob, &ctx->block_blob, &ctx->q_bf16, &ctx->kctx_bf16, &ctx->krec_bf16,
-                                    &ctx->neg_lse, &ctx->x_parts, &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws, &ctx->inplace_ws};
+                                    &ctx->neg_lse, &ctx->x_parts, &ctx->x_ws,   &ctx->yhat_ws, &ctx->topk_ws, &ctx->inplace.block};
   for (pkv::MapperWorkspace& m : ctx->m) {
     DeviceBuffer* b[kLaneBuffers];
     lane_buffers(m, b);
@@ -459,6 +485,7 @@ int proxykv_destroy(proxykv_ctx* ctx) {
     (void)hipSetDevice(ctx->cfg.device);
     (void)hipDeviceSynchronize();
     for (DeviceBuffer* b : all) free_buffer(*b);
+    for (int i = 0; i < ctx->inplace.n_older; ++i) (void)hipFree(ctx->inplace.older[i]);
     if (ctx->ev_created)
       for (int i = 0; i < PROXYKV_N_STAGES + 1; ++i) (void)hipEventDestroy(ctx->ev[i]);
     for (int i = 1; i < pkv::kMapLanes; ++i) {
@@ -636,7 +663,7 @@ int proxykv_workspace_bytes(const proxykv_config* cfg, int64_t N, int64_t N_q, s
   const Sizes s = workspace_sizes(*cfg, N, N_q);
   const pkv::MapPlan p = pkv::map_plan(*cfg, N, distinct);
   const LaneBytes lb = lane_bytes(*cfg, p);
-  size_t total = s.neg_lse + s.x_parts + s.x_ws + s.yhat_ws + pkv::topk_scratch_bytes((int64_t)cfg->L_l * cfg->H_l, N) + inplace_bytes(*cfg, N);
+  size_t total = s.neg_lse + s.x_parts + s.x_ws + s.yhat_ws + pkv::topk_scratch_bytes((int64_t)cfg->L_l * cfg->H_l, N) + inplace_block_bytes(inplace_bytes(*cfg, N));
   for (int lane = 0; lane < p.lanes; ++lane)
     for (int i = 0; i < kLaneBuffers; ++i) total += lane_need(*cfg, p, lb, lane, distinct, i);
   *out_bytes = total;
@@ -650,7 +677,10 @@ int proxykv_reserve(proxykv_ctx* ctx, int64_t N, int64_t N_q) {
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
   if ((rc = reserve_score(ctx, N, N_q, true, nullptr))) return rc;  // (proxykv_score_self has parts in any context)
   if ((rc = reserve_prune(ctx, N, nullptr))) return rc;
-  (void)reserve_inplace(ctx, inplace_bytes(ctx->cfg, N), nullptr);  // (in-place calls do without)
+  {
+    std::lock_guard<std::mutex> lock(ctx->inplace.mutex);
+    (void)reserve_inplace(ctx, inplace_bytes(ctx->cfg, N));  // (in-place calls do without)
+  }
   pkv::MapPlan p;
   return reserve_map(ctx, N, nullptr, &p);  // last: it makes do with what is left
 }
@@ -732,9 +762,7 @@ int proxykv_compact_inplace(proxykv_ctx* ctx, void* k, void* v, const int32_t* i
   if (rows <= 0 || N <= 0 || N >= (1ll << 31) || K < 1 || K > N || D <= 0) return PROXYKV_EINVAL;
   if ((D * 2) % 16 != 0 || D * 2 > 512) return PROXYKV_EUNSUPPORTED;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  const DeviceBuffer counters = inplace_counters(ctx, rows, K, D * 2, 1, (hipStream_t)stream);
-  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, idx, rows, N, K, D * 2, nullptr, 1, counters.ptr, counters.bytes, (hipStream_t)stream));
-  return PROXYKV_OK;
+  return inplace_impl(ctx, k, v, idx, rows, N, K, D * 2, nullptr, 1, (hipStream_t)stream);
 }
 
 int proxykv_topk_pooled(proxykv_ctx* ctx, const float* scores, int64_t layers, int64_t heads, int64_t N, int64_t K,
@@ -758,9 +786,7 @@ int proxykv_compact_pooled(proxykv_ctx* ctx, void* k, void* v, const int32_t* fl
   if (layers * heads >= (1ll << 31) || heads * N >= (1ll << 31) - 4096) return PROXYKV_EINVAL;
   if ((D * 2) % 16 != 0 || D * 2 > 512) return PROXYKV_EUNSUPPORTED;
   PKV_HIP(ctx, hipSetDevice(ctx->cfg.device));
-  const DeviceBuffer counters = inplace_counters(ctx, layers * heads, K, D * 2, (int)heads, (hipStream_t)stream);
-  PKV_HIP(ctx, pkv::launch_compact_inplace(k, v, flat, layers * heads, N, K, D * 2, counts, (int)heads, counters.ptr, counters.bytes, (hipStream_t)stream));
-  return PROXYKV_OK;
+  return inplace_impl(ctx, k, v, flat, layers * heads, N, K, D * 2, counts, (int)heads, (hipStream_t)stream);
 }
 
 int proxykv_mask(proxykv_ctx* ctx, const int32_t* idx, int64_t rows, int64_t N, int64_t K, uint8_t* mask_out, void* stream) {

@@ -5,6 +5,7 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <vector>
 
 #include "../../include/proxykv.h"
@@ -14,6 +15,20 @@ namespace pkv {
 struct DeviceBuffer {
   void* ptr = nullptr;
   size_t bytes = 0;
+};
+
+// Counters of the in-place compaction: an equal piece of `block` for each of the first streams that make such calls.  Nothing orders calls of
+// different streams, on caches of their own, so they must not meet in the counters.  A piece is 4 bytes per 160 KB that a call moves, so
+// that 32 of them are 0.08 % of that (512 rows of 12 345 tokens of D = 128, half kept: 45 KB each).
+constexpr int kInplaceStreams = 32;
+struct InplaceCounters {
+  std::mutex mutex;  // held from where a call finds its counters until its launches are made
+  DeviceBuffer block;
+  hipStream_t stream[kInplaceStreams];
+  int streams = 0;
+  // Blocks that became too small: calls that were made may still count there.  Each has at most half the bytes of the next.
+  void* older[48];
+  int n_older = 0;
 };
 
 // Device pointers into one allocation that holds the prepared mapper weights.
@@ -94,7 +109,7 @@ struct proxykv_ctx {
   pkv::DeviceBuffer x_ws;                          // fp32 [L_s, H_kv, N]
   pkv::DeviceBuffer yhat_ws;                       // fp32 [L_l, H_l, N]
   pkv::DeviceBuffer topk_ws;                       // state of Top-K where workgroups share a row
-  pkv::DeviceBuffer inplace_ws;                    // ... of the in-place compaction
+  pkv::InplaceCounters inplace;
   bool topk_short = false;                         // memory was short: topk_ws has no masks, or only the narrower histograms
   bool fused_select = false;                       // proxykv_prune: selection and gather in one launch (measured slower)
   pkv::MapperWorkspace m[pkv::kMapLanes];          // one per lane; only the lanes a length needs are allocated

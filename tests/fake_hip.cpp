@@ -5,6 +5,7 @@
 #include <stdio.h>
 
 #include <map>
+#include <mutex>
 #include <string>
 
 struct dim3 {
@@ -21,7 +22,12 @@ static std::map<const void*, std::string>& names() {
   return m;
 }
 static std::string g_log;
-static dim3 g_grid, g_block;
+static thread_local dim3 g_grid, g_block;
+static thread_local void* g_stream;
+static std::mutex g_mutex;
+static std::string g_watched;
+static int g_argument = 0;
+static uintptr_t g_value = 0;
 
 extern "C" {
 // ---- what a test sees and sets
@@ -37,8 +43,16 @@ const char* fake_launches() {  // since the last call, "name gx gy gz bx\n" each
   return out.c_str();
 }
 
+// from now on, pointer argument `i` of the last launch of a kernel whose name contains `part`
+void fake_watch(const char* part, int i) {
+  g_watched = part;
+  g_argument = i;
+}
+uintptr_t fake_argument() { return g_value; }
+
 // ---- memory
 int hipMalloc(void** p, size_t n) {
+  std::lock_guard<std::mutex> lock(g_mutex);
   ++g_mallocs;
   if (g_used + n > g_budget) return kOutOfMemory;
   *p = (void*)g_next;
@@ -49,6 +63,7 @@ int hipMalloc(void** p, size_t n) {
   return kSuccess;
 }
 int hipFree(void* p) {
+  std::lock_guard<std::mutex> lock(g_mutex);
   auto it = g_live.find((uintptr_t)p);
   if (it != g_live.end()) {
     g_used -= it->second;
@@ -64,6 +79,7 @@ int hipGetSymbolAddress(void** p, const void*) {
 }
 
 // ---- device, streams, events
+int hipThreadExchangeStreamCaptureMode(int*) { return kSuccess; }
 int hipSetDevice(int) { return kSuccess; }
 int hipGetDevice(int* d) {
   *d = 0;
@@ -107,16 +123,17 @@ void __hipRegisterFunction(void**, const void* host, char*, const char* name, un
   names()[host] = name;
 }
 int hipFuncSetAttribute(const void*, int, int) { return kSuccess; }
-int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, void*) {
+int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t, void* stream) {
   g_grid = grid;
   g_block = block;
+  g_stream = stream;
   return kSuccess;
 }
 int __hipPopCallConfiguration(dim3* grid, dim3* block, size_t* lds, void** stream) {
   *grid = g_grid;
   *block = g_block;
   *lds = 0;
-  *stream = nullptr;
+  *stream = g_stream;
   return kSuccess;
 }
 static int g_launch_error = 0;
@@ -125,8 +142,10 @@ int hipGetLastError() {
   g_launch_error = kSuccess;
   return e;
 }
-int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void**, size_t, void*) {
+int hipLaunchKernel(const void* f, dim3 grid, dim3 block, void** args, size_t, void*) {
   char line[512];
+  std::lock_guard<std::mutex> lock(g_mutex);
+  if (!g_watched.empty() && names()[f].find(g_watched) != std::string::npos) g_value = *(uintptr_t*)args[g_argument];
   const bool bad = grid.x == 0 || grid.y == 0 || grid.z == 0 || grid.y > 65535 || grid.z > 65535 || block.x > 1024 ||
                    (uint64_t)grid.x * block.x > 0xffffffffu;  // the runtime counts work-items per dimension in 32 bits
   snprintf(line, sizeof line, "%s%s %u %u %u %u\n", bad ? "REFUSED " : "", names()[f].c_str(), grid.x, grid.y, grid.z, block.x);

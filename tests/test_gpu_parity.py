@@ -278,6 +278,51 @@ def test_graph_of_an_in_place_compaction_outlives_its_context():
         assert torch.equal(kv[:, :, :, :K], want) and torch.equal(kv[:, :, :, K:], src[:, :, :, K:]), step
 
 
+def test_in_place_compactions_of_one_context_side_by_side():
+    """Calls on two streams, made by two threads, and on the capturing thread's other stream while one is captured: caches of their own, so nothing orders
+    the calls, and the kept tokens of each are its own."""
+    import threading
+    g = torch.Generator().manual_seed(8)
+    N, D = 5000, 128
+    ctx = _ctx(synth.CASES["tiny"])
+    jobs = []
+    for rows, K in ((40, 3000), (64, 2500)):
+        idx = torch.stack([torch.randperm(N, generator=g)[:K].sort().values for _ in range(rows)]).to(torch.int32).view(1, rows, K).cuda()
+        src = torch.randn(2, 1, rows, N, D, generator=g).to(torch.bfloat16).cuda()
+        want = torch.gather(src, 3, idx.long().unsqueeze(0).unsqueeze(4).expand(2, -1, -1, -1, D))
+        jobs.append((torch.cuda.Stream(), idx, src, want, [src.clone() for _ in range(6)]))
+    torch.cuda.synchronize()
+
+    def work(stream, idx, src, want, caches):
+        with torch.cuda.stream(stream):
+            for kv in caches:
+                pk.proxykv_compact_inplace(ctx, kv[0], kv[1], idx)
+    threads = [threading.Thread(target=work, args=job) for job in jobs]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    for _, idx, src, want, caches in jobs:
+        for kv in caches:
+            assert torch.equal(kv[:, :, :, :idx.shape[2]], want) and torch.equal(kv[:, :, :, idx.shape[2]:], src[:, :, :, idx.shape[2]:])
+
+    fresh = _ctx(synth.CASES["tiny"])  # has no counters yet
+    (side, idx, src, want, _), captured, eager = jobs[0], jobs[0][2].clone(), jobs[0][2].clone()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pk.proxykv_compact_inplace(fresh, captured[0], captured[1], idx)
+        with torch.cuda.stream(side):
+            pk.proxykv_compact_inplace(fresh, eager[0], eager[1], idx)
+    graph.replay()
+    torch.cuda.synchronize()
+    for kv in (captured, eager):
+        assert torch.equal(kv[:, :, :, :idx.shape[2]], want)
+    pk.proxykv_destroy(fresh)
+    pk.proxykv_destroy(ctx)
+
+
 def test_pooled_compaction_of_many_heads_in_parts():
     """More heads than a wave's lanes deal parts to, with heads that keep nothing and heads that keep all; budgets of several parts each."""
     _check_pooled([(2, 70, 2000, 64, 1900), (1, 130, 1500, 128, 1000), (3, 2, 4000, 128, 1500)], nothing=slice(None))

@@ -391,3 +391,59 @@ def test_in_place_counters_take_nothing_from_the_topk():
                 fake.fake_budget((1 << 63) - 1)
     """)
     assert out == [[0, 1, 0, 0]] * 4
+
+
+def test_in_place_calls_of_several_streams_count_apart():
+    """In-place calls of one context on several streams, on caches of their own, need not follow each other, so each stream has counters of its own, the same
+    again on its next call and apart from the others' also after one of them had to have more.  The streams beyond
+    those that have some, and the per-thread default stream, whose handle is the same in every thread, move whole rows."""
+    out = run("""
+        out = {}
+        fake.fake_argument.restype = ctypes.c_uint64
+        fake.fake_watch(b"compact_parts_kernel", 9)
+        h = context(LLAMA)
+        def counters(stream, rows=256, K=4096):
+            launches()
+            assert lib.proxykv_compact_inplace(h, P, P, P, rows, 8192, K, 128, ctypes.c_void_p(stream)) == 0
+            parts = launches("compact_parts_kernel")
+            return fake.fake_argument() if parts else 0
+        out["first"] = [counters(1000 + i) for i in range(40)]
+        out["again"] = [counters(1000 + i) for i in range(40)]
+        size = 4 * 2 * 256 * 8  # seven parts and the counter for every row, K and V
+        out["apart"] = all(abs(a - b) >= size for a in out["first"] for b in out["first"] if a and b and a != b)
+        mallocs = fake.fake_mallocs()
+        out["more"] = [counters(1000 + i, rows=600) for i in (0, 1, 0)]
+        out["grown"] = fake.fake_mallocs() - mallocs
+        out["older"] = [counters(1000 + i) for i in range(3)]
+        out["per thread"] = counters(2)
+        h = context(LLAMA)
+        out["default"] = [counters(0), counters(2), counters(0)]
+    """)
+    with_some = [c for c in out["first"] if c]
+    assert len(with_some) == len(set(with_some)) == 32 and out["first"] == with_some + [0] * 8
+    assert out["again"] == out["first"] and out["apart"] and out["grown"] == 1
+    a, b, c = out["more"]
+    assert a == c and abs(a - b) >= 4 * 2 * 600 * 8 and len(set(out["older"])) == 3
+    assert out["per thread"] == 0
+    assert out["default"][0] == out["default"][2] != 0 and out["default"][1] == 0
+
+
+def test_in_place_calls_of_several_threads():
+    """Four threads and a context: none loses its counters while another makes room for its own.  (A block has less than twice what is asked for, the
+    ones before it together less than it.)"""
+    out = run("""
+        import threading
+        out = []
+        h = context(LLAMA)
+        def work(stream):
+            for k in range(1000, 8000, 50):
+                out.append(lib.proxykv_compact_inplace(h, P, P, P, 256, 8192, k, 128, ctypes.c_void_p(stream)))
+        before = fake.fake_used()
+        threads = [threading.Thread(target=work, args=(1000 + i,)) for i in range(4)]
+        for t in threads: t.start()
+        for t in threads: t.join()
+        grew = fake.fake_used() - before
+        kept.clear()
+        out = [sorted(set(out)), len(out), grew < 4 * 32 * 4 * 2 * 256 * 14, fake.fake_used() <= before]
+    """)
+    assert out == [[0], 560, True, True]
