@@ -150,8 +150,8 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(u32x4* __restrict_
 // all of them into registers, and stores them when the parts in front of it in the row have been loaded: a token's new place never
 // lies behind its old one, so what a part's places still hold belongs to itself or to a part in front.  Parts are dealt by a
 // counter per layer and tensor, in order: whoever a workgroup waits for has started before it and waits for earlier ones only, so every wait
-// ends, whatever order the workgroups are launched in.  (The wait has a bound all the same, for a context that two
-// streams use at once, which races in any case.)
+// ends, whatever order the workgroups are launched in, as long as no other launch uses the same counters at the same time.  It has no
+// bound: a part that stored before the ones in front are loaded would destroy tokens, and a clock goes on while the queue is off the chip.
 // What bounds it is memory.  With workgroups of a whole row, two chunks of it in flight, a long row was what the launch waited for.  Half kept,
 // D = 128, us: 512 rows of 12 345 tokens 652 -> 548 (3.2 GB: 5.9 TB/s), with budgets that eight heads share 727 -> 567; 256 of 32 000, 0.3
 // kept, shared 756 -> 455; 112 of 8000 96 -> 87; 4 of 30 000 97 -> 16.
@@ -160,7 +160,6 @@ __global__ __launch_bounds__(256) void compact_inplace_kernel(u32x4* __restrict_
 // state: per (layer, tensor) the counter, then a word per part, all zero at the start.  grid 2 * layers * (stride - 1).
 // ---------------------------------------------------------------------------------------------
 constexpr int kPartThreads = 512, kPartPer = 20, kPartPieces = kPartThreads * kPartPer;
-constexpr unsigned long long kPartPatience = 100000000;  // 1 s
 
 __global__ __launch_bounds__(256) void clear_words_kernel(uint32_t* __restrict__ words, int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -243,11 +242,8 @@ __global__ __launch_bounds__(kPartThreads, 3) void compact_parts_kernel(u32x4* _
   if (tid < 64) {
     uint32_t* loaded = mine + 1 + ticket;
     if (lane == 0) __hip_atomic_store(loaded, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long begin = __builtin_amdgcn_s_memrealtime();
     for (int p = lane; p < part; p += 64)
-      while (__hip_atomic_load(loaded - 1 - p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0 &&
-             __builtin_amdgcn_s_memrealtime() - begin < kPartPatience)
-        __builtin_amdgcn_s_sleep(1);
+      while (__hip_atomic_load(loaded - 1 - p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) __builtin_amdgcn_s_sleep(1);
   }
   __syncthreads();
   int tok = tid / cpr, ch = tid % cpr;

@@ -103,6 +103,35 @@ def test_in_place_compaction_holds_a_chunk_before_it_stores_one():
             assert not stores or not any("vmcnt" in op for op in behind[:stores[0]]), (name, behind)
 
 
+def _compaction_in_parts():
+    (body,) = [body for name, body in kernels("compact.hip") if "compact_parts_kernel" in name]
+    return body
+
+
+def test_compaction_in_parts_never_gives_up_its_wait():
+    """A part that stores before the parts in front of it in its row have been loaded destroys what they still have to move.  Those have started and wait for
+    earlier ones only, so the wait ends; one bounded by a clock, which goes on while the queue is off the chip, might end too early."""
+    body = _compaction_in_parts()
+    assert "s_memrealtime" not in body and "s_memtime" not in body and "s_getreg" not in body
+    waits = [loop for loop in loops(body) if "s_sleep" in loop and "global_load_dword " in loop]
+    assert waits and all(len(re.findall(r"^\s+s_sleep", loop, re.M)) == 1 for loop in waits)
+
+
+def test_compaction_in_parts_holds_its_part_before_it_says_so():
+    """A part's flag lets the parts behind it store where it loads from, so all loads of its pieces, of every wave, have to be over before the flag is
+    stored: a wait for all of them, then a barrier, which by itself waits for no load, then the flag; and no piece is stored in front of the barrier
+    behind the wait for the parts in front."""
+    ops = re.findall(r"^\s+(s_barrier|s_waitcnt\b.*|s_sleep|global_\w+)", _compaction_in_parts(), re.M)
+    loads = [i for i, op in enumerate(ops) if op == "global_load_dwordx4"]
+    stores = [i for i, op in enumerate(ops) if op == "global_store_dwordx4"]
+    (flag,) = [i for i, op in enumerate(ops) if op == "global_store_dword"]
+    wait = [i for i, op in enumerate(ops) if op == "s_sleep"][-1]
+    assert len(loads) == len(stores) == 20
+    barrier = next(i for i in range(loads[-1], len(ops)) if ops[i] == "s_barrier")
+    assert any("vmcnt(0)" in op for op in ops[loads[-1]:barrier]) and barrier < flag
+    assert flag < wait and "s_barrier" in ops[wait:stores[0]] and stores[0] > wait
+
+
 def _registers(text):
     """{("v", 3), ("v", 4), ...} named in an operand list"""
     out = set()
