@@ -293,7 +293,7 @@ int inplace_impl(proxykv_ctx* ctx, void* k, void* v, const int32_t* idx, int64_t
 size_t inplace_bytes(const proxykv_config& c, int64_t N) {
   if (c.D * 2 > 512) return 0;  // not for proxykv_compact_inplace
   const int64_t rows = (int64_t)c.L_l * c.H_l;
-  const size_t own = pkv::compact_inplace_scratch_bytes(rows, N, c.D * 2, 1), shared = pkv::compact_inplace_scratch_bytes(rows, N, c.D * 2, c.H_l);
+  const size_t own = pkv::compact_inplace_scratch_most(rows, N, c.D * 2, 1), shared = pkv::compact_inplace_scratch_most(rows, N, c.D * 2, c.H_l);
   return own > shared ? own : shared;
 }
 int reserve_prune(proxykv_ctx* ctx, int64_t N, hipStream_t stream) {

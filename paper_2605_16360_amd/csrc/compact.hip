@@ -3,6 +3,8 @@
 // and V in one launch so the index read is shared.  Pure data movement in 16-byte pieces, two token rows in flight per thread (measured at
 // N = 32 768, keep ratio 0.3: 0.436 ms with one or two, 0.45 ms with four, 0.96 ms with eight; plain instead of
 // non-temporal loads 0.48 ms).
+#include <math.h>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -328,20 +330,35 @@ hipError_t launch_compact(const void* k_in, const void* v_in, const int32_t* idx
 }
 
 // Parts that a layer's kept tokens (heads * K) can make, however its heads share them; 0 where a launch has no room for them.
-// Kept tokens per row, in parts, from which it pays: the launch that clears the state is in front, and what is left of a row fills its last
-// part badly.  Parts / whole rows, us: 256 rows that keep 1100 57 / 60, with shared budgets 60 / 70; 112 rows 27.5 / 26.8 and 32 / 36; 4 rows that
-// keep 1500 12.3 / 11.1; 256 rows of D = 64 that keep 1500 (1.2 parts) 44.6 / 42.0.
-static bool parts_pay(int64_t rows, int64_t K, int64_t row_bytes, int heads) {
-  return 2 * K >= (heads > 1 || rows >= 256 ? 3 : 6) * (kPartPieces / (row_bytes / 16));
-}
 static int64_t layer_parts(int64_t layers, int64_t K, int64_t row_bytes, int heads) {
   const int64_t tokens = kPartPieces / (row_bytes / 16), parts = (heads * K + tokens - 1) / tokens + (heads > 1 ? heads - 1 : 0);
   return 2 * layers * parts * kPartThreads <= kMaxThreads ? parts : 0;
 }
+// Whether parts are faster than whole rows.  What a row keeps has to fill one and a half of them (three with budgets of their own in fewer
+// than 256 rows), and they have to be worth their turns: whole rows take as long as a workgroup's chain, 8 ns a token, and as their bytes
+// beside it; parts a launch that clears the state and 10 us for every 256 of them, the last few like a full turn.  In us, fitted over
+// 1832 shapes with cold caches: 1 to 512 rows, D = 8 to 256, 1.5 to 50 parts a row, 0.3 and 0.7 kept.  With parts taken by their number
+// alone 128 of the shapes were more than 2 % slower than whole rows, up to 1.29 times; so 52, up to 1.19 (80 rows of D = 256, 3.9 parts,
+// parts / whole rows 43.6 / 36.6; 112 of D = 128, shared budgets, 1.6 parts 31.1 / 28.3 and 31.8 / 31.6).  Parts / whole rows on either side: D = 256,
+// one row that keeps 1440 tokens 12.8 / 10.5, 1984 12.8 / 14.5; 28 rows, 1440 23.7 / 19.0, 2880 35.2 / 37.3; D = 128, four rows with shared
+// budgets, 1024 12.3 / 9.9, 1408 12.3 / 12.0 to 13.2; 256 rows, 1024 54 / 57.
+static bool parts_pay(int64_t rows, int64_t K, int64_t row_bytes, int heads) {
+  const int64_t cpr = row_bytes / 16, tokens = kPartPieces / cpr, least = heads > 1 || rows >= 256 ? 3 : 6;
+  if (2 * K < least * tokens) return false;
+  const double mb = 2e-6 * (double)rows * (double)K * (double)row_bytes, wide = cpr % 8 == 0 ? 1.0 : (double)cpr / 8.0;
+  const double chain = 0.008 * wide * (double)K + 0.25 * mb, bytes = 0.38 * mb;
+  const double whole = (chain > bytes ? chain : bytes) * (heads > 1 ? 1.2 : 1.0);  // (of shared budgets the longest row is what is left)
+  const double parts = 2.0 * (double)rows * (heads > 1 ? (double)K / (double)tokens + 0.5 : (double)((K + tokens - 1) / tokens));
+  const double turns = 4.0 + 10.0 * ceil(parts / 256.0);
+  return (turns > 0.36 * mb ? turns : 0.36 * mb) <= whole;
+}
+size_t compact_inplace_scratch_most(int64_t rows, int64_t K, int64_t row_bytes, int heads) {
+  const int64_t layers = rows / heads, parts = rows > 0 ? layer_parts(layers, K, row_bytes, heads) : 0;
+  return (size_t)(2 * layers * (parts + 1)) * 4;
+}
 size_t compact_inplace_scratch_bytes(int64_t rows, int64_t K, int64_t row_bytes, int heads) {
-  if (rows <= 0 || !parts_pay(rows, K, row_bytes, heads)) return 0;
-  const int64_t layers = rows / heads, parts = layer_parts(layers, K, row_bytes, heads);
-  return parts == 0 ? 0 : (size_t)(2 * layers * (parts + 1)) * 4;
+  if (rows <= 0 || layer_parts(rows / heads, K, row_bytes, heads) == 0 || !parts_pay(rows, K, row_bytes, heads)) return 0;
+  return compact_inplace_scratch_most(rows, K, row_bytes, heads);
 }
 
 hipError_t launch_compact_inplace(void* k, void* v, const int32_t* idx, int64_t rows, int64_t N, int64_t K, int64_t row_bytes,

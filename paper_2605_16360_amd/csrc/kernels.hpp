@@ -66,6 +66,8 @@ hipError_t launch_compact(const void* k_in, const void* v_in, const int32_t* idx
 // contents) of compact_inplace_scratch_bytes several workgroups share a row; that is 0 where one per row is better or has to do.  A launch on
 // another stream must not use the same scratch memory before this one is over: parts of a row wait for each other in it without a bound.
 size_t compact_inplace_scratch_bytes(int64_t rows, int64_t K, int64_t row_bytes, int heads);
+// no less than that for any number of kept tokens up to K
+size_t compact_inplace_scratch_most(int64_t rows, int64_t K, int64_t row_bytes, int heads);
 hipError_t launch_compact_inplace(void* k, void* v, const int32_t* idx, int64_t rows, int64_t N, int64_t K, int64_t row_bytes,
                                   const int32_t* counts, int heads, void* scratch, size_t scratch_bytes, hipStream_t stream);
 // counts [layers, heads] from a layer's ascending flat indices h * N + n (heads * K per layer)

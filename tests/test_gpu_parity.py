@@ -224,6 +224,17 @@ def test_compact_inplace_in_parts_of_a_row(D, rows, counts):
     _check_compact_inplace(D, rows, counts)
 
 
+def test_compact_inplace_in_parts_that_pay():
+    """D = 256, 320 tokens to a part: six parts, one token less and one more, and eight; many rows whose third part is a third full."""
+    _check_compact_inplace(256, 2, (1919, 1920, 1921, 2241))
+    _check_compact_inplace(128, 256, (1500,))
+
+
+def test_pooled_compaction_in_parts_of_more_heads_than_a_wave_has_lanes():
+    """A layer's parts are dealt to its heads 64 at a time: 70 and 130 heads, some of which keep nothing and some everything."""
+    _check_pooled([(2, 70, 5000, 64, 4000), (1, 130, 4000, 128, 3000)], nothing=slice(None))
+
+
 def test_compact_inplace_in_a_graph_and_in_a_context_without_memory():
     """A graph moves whole rows, with the caller's pointers alone, whether the context that captures has room for an eager call's counters or not."""
     g = torch.Generator().manual_seed(5)

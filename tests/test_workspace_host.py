@@ -447,3 +447,35 @@ def test_in_place_calls_of_several_threads():
         out = [sorted(set(out)), len(out), grew < 4 * 32 * 4 * 2 * 256 * 14, fake.fake_used() <= before]
     """)
     assert out == [[0], 560, True, True]
+
+
+def test_in_place_compaction_in_parts_only_where_whole_rows_are_slower():
+    """Few short rows are moved before a second launch has begun (D = 256, one row that keeps 1440 tokens: 10.5 us whole, 12.8 in parts), and 280 parts are two
+    turns on 256 places; the tests of parts on a GPU keep enough for them."""
+    out = run("""
+        out = []
+        h = context(LLAMA)
+        def parts(layers, heads, D, K, pooled, N=None):
+            launches()
+            N = N or K + 5
+            rc = (lib.proxykv_compact_pooled(h, P, P, P, P, layers, heads, N, K, D, None) if pooled else
+                  lib.proxykv_compact_inplace(h, P, P, P, layers * heads, N, K, D, None))
+            assert rc == 0
+            return len(launches("compact_parts_kernel"))
+        out.append([parts(*c) for c in ((1, 1, 256, 1440, 0), (1, 4, 256, 1440, 0), (4, 7, 256, 1440, 0), (1, 4, 128, 1024, 1), (4, 7, 256, 512, 1),
+                                        (1, 4, 256, 1024, 1))])
+        out.append([parts(*c) for c in ((1, 1, 256, 1984, 0), (1, 4, 256, 1984, 0), (1, 1, 128, 2048, 0), (1, 4, 128, 1500, 1), (4, 7, 64, 2048, 1), (28, 4, 128, 1920, 0),
+                                        (28, 4, 128, 1500, 1), (32, 8, 128, 1024, 0), (64, 8, 128, 6172, 0), (64, 8, 128, 6172, 1), (32, 8, 8, 20000, 0))])
+        # as in test_gpu_parity.py
+        out.append([parts(*c) for c in ((1, 3, 128, 1921, 0), (1, 256, 128, 960, 0), (1, 256, 128, 1500, 0), (1, 2, 256, 2000, 0), (1, 2, 72, 3411, 0), (1, 1, 8, 30720, 0), (1, 256, 64, 1920, 0),
+                                        (1, 2, 256, 1919, 0), (1, 2, 256, 1920, 0), (1, 2, 256, 1921, 0), (1, 2, 256, 2241, 0), (1, 130, 128, 3000, 1, 4000),
+                                        (2, 70, 64, 4000, 1, 5000), (3, 2, 128, 1500, 1, 4000), (1, 4, 128, 3000, 0), (1, 3, 128, 4000, 0), (1, 40, 128, 3000, 0), (1, 64, 128, 2500, 0))])
+        # what is reserved is enough for every number of kept tokens
+        h = context(LLAMA)
+        assert lib.proxykv_reserve(h, 9000, 64) == 0
+        before = fake.fake_mallocs()
+        for K in range(1, 9001, 7):
+            parts(32, 8, 128, K, K % 2, 9000)
+        out.append(fake.fake_mallocs() - before)
+    """)
+    assert out[0] == [0] * 6 and out[1] == [1] * 11 and out[2] == [1] * 18 and out[3] == 0
