@@ -354,7 +354,7 @@ int score_impl(proxykv_ctx* ctx, const void* q_rec, const void* k_ctx, const voi
                int64_t N_q, int32_t chunk, float* x_out, hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const uint16_t *q = (const uint16_t*)q_rec, *kc = (const uint16_t*)k_ctx, *kr = (const uint16_t*)k_rec;
-  const bool rounds = dtype == PROXYKV_FP32 && pkv::score_rounds_itself(c.L_s, c.H_q, c.d, N, N_q);
+  const bool rounds = dtype == PROXYKV_FP32 && pkv::score_rounds_itself(c.L_s, c.H_q, c.H_kv, c.d, N, N_q);
   int rc;
   if (dtype == PROXYKV_FP32) {
     const size_t nq = (size_t)c.L_s * c.H_q * (size_t)N_q * c.d, nkc = (size_t)c.L_s * c.H_kv * (size_t)N * c.d,
@@ -398,7 +398,7 @@ int score_self_impl(proxykv_ctx* ctx, const void* q_in, const void* k_in, int32_
                     hipStream_t stream) {
   const proxykv_config& c = ctx->cfg;
   const uint16_t *q = (const uint16_t*)q_in, *k = (const uint16_t*)k_in;
-  const bool rounds = dtype == PROXYKV_FP32 && pkv::score_rounds_itself(c.L_s, c.H_q, c.d, N, N);
+  const bool rounds = dtype == PROXYKV_FP32 && pkv::score_rounds_itself(c.L_s, c.H_q, c.H_kv, c.d, N, N);
   int rc;
   if (dtype == PROXYKV_FP32) {
     const size_t nq = (size_t)c.L_s * c.H_q * (size_t)N * c.d, nk = (size_t)c.L_s * c.H_kv * (size_t)N * c.d;

@@ -23,7 +23,7 @@ hipError_t launch_score_lse_piped(const uint16_t* q, const uint16_t* k_ctx, cons
                                   int H_q, int H_kv, int64_t N, int64_t N_q, int chunk, hipStream_t stream);
 // The same with fp32 inputs, which the kernel rounds by itself; q16 [L_s, H_q, N_q, d] and k16 (k_ctx, or with N = 0 k_rec) take the
 // rounded copies for pass 2.  Only where score_rounds_itself.
-bool score_rounds_itself(int L_s, int H_q, int d, int64_t N, int64_t N_q);
+bool score_rounds_itself(int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q);
 hipError_t launch_score_lse_fp32(const float* q, const float* k_ctx, const float* k_rec, float* neg_lse, int splits, float* x, int64_t n_x,
                                  uint16_t* q16, uint16_t* k16, int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q, int chunk,
                                  hipStream_t stream);

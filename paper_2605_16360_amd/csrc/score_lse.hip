@@ -28,12 +28,27 @@ int score_splits(int L_s, int H_q, int d, int64_t N, int64_t N_q) {
   return (int)(s < kMaxLseSplits ? s : kMaxLseSplits);
 }
 
-// fp32 inputs that pass 1 rounds by itself instead of a launch in front: where workgroups share a block's keys, up to as many as one wants to read
-// in twice the bytes.  Both passes, with a launch / so, us: one layer of 4 heads, 128 queries of 512 keys 16.1 / 14.7, 1000 20.5 / 19.0, 4000
-// 38.2 / 36.6; 8000 85.5 / 88.8.
-constexpr int64_t kRoundKeys = 4096;
-bool score_rounds_itself(int L_s, int H_q, int d, int64_t N, int64_t N_q) {
-  return d == 64 && N <= kRoundKeys && score_splits(L_s, H_q, d, N, N_q) > 1;
+// fp32 inputs that pass 1 rounds by itself instead of a launch in front, which costs 3 us and reads and writes them once.  The keys, up to
+// kRoundKeys of them, are then staged in twice the bytes, and what that costs is decided by how many XCDs read them: the workgroups of a
+// KV head that read one share of its keys (its heads' query blocks) lie on one XCD where there are eight shares, and past their L2 every
+// further XCD reads the share again.  Both passes, with a launch / so, us, or so's part of the time.  One XCD: one layer of 4 heads, 4000
+// tokens 38.2 / 36.6 (8000 85.5 / 88.8); 2 x 32/8 heads, 256 queries of 4096 keys 0.93, 16 x 16/16, 64 of 4096 0.89.  Two for eight
+// workgroups: 12 x 16/2, 64 of 4096 0.91.  Four for seven: 24 x 14/2, 256 of 1600 0.95, 64 of 4096 0.94; eight for 21: 6 x 14/2, 700 of 4096
+// 1.04.  Four for six: 28 x 12/2, 64 of 1600 1.04, of 4096 1.17.  One for each, 64 of 4096: 20 x 8/4 1.14, 14 x 14/2 1.19, 9 x 32/8 1.31.
+// Few keys are rounded either way, as long as queries times keys are few too: one layer of 4 heads, 128 of 512 16.1 / 14.7; 4 x 32/8, 256 of
+// 512 0.91; 8 x 32/8, 256 of 256 0.99, of 512 1.01, 64 of 1000 0.97, of 2000 1.10; of more blocks than CUs fewer: 9 x 32/8, 64 of 400 0.93, of 800
+// 1.11, 24 of 513 1.04; 256 of 100 0.91, of 200 1.04.
+constexpr int64_t kRoundKeys = 4096, kRoundKeysLeast = 128, kRoundWork = 1 << 24;
+bool score_rounds_itself(int L_s, int H_q, int H_kv, int d, int64_t N, int64_t N_q) {
+  const int splits = score_splits(L_s, H_q, d, N, N_q);
+  if (d != 64 || N > kRoundKeys || splits < 2) return false;
+  const int blocks = (int)((N_q + 128 * kLseCols - 1) / (128 * kLseCols)), readers = H_q / H_kv * blocks;
+  unsigned xcds = 0;
+  for (int r = 0; r < readers; ++r) xcds |= 1u << (unsigned)(r * splits % kScoreXcds);
+  const int copies = __builtin_popcount(xcds);
+  if (copies == 1 || 4 * readers >= 7 * copies) return true;
+  const int64_t few = (int64_t)L_s * H_q * blocks <= 256 ? 1024 : 512;
+  return N <= kRoundKeysLeast || (N <= few && (int64_t)L_s * H_q * N_q * N <= kRoundWork);
 }
 
 // The most that any input of up to N_q queries takes: one float per query, or pairs of up to 768 workgroups (score_splits).

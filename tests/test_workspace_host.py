@@ -479,3 +479,23 @@ def test_in_place_compaction_in_parts_only_where_whole_rows_are_slower():
         out.append(fake.fake_mallocs() - before)
     """)
     assert out[0] == [0] * 6 and out[1] == [1] * 11 and out[2] == [1] * 18 and out[3] == 0
+
+
+def test_fp32_scores_are_rounded_in_front_where_several_xcds_read_a_share_of_the_keys():
+    """Pass 1 rounds fp32 keys itself only where that does not read much of them in twice the bytes: a share of a KV head's keys goes to one XCD (shares make
+    eight workgroups per query block), or each XCD that reads it does so for several workgroups, or the keys are few."""
+    out = run("""
+        out = []
+        for L, H_q, H_kv, N, N_q, self in ((11, 32, 8, 2000, 256, 0), (11, 32, 8, 4096, 128, 0), (9, 32, 8, 4096, 64, 0), (9, 32, 8, 400, 256, 0), (8, 32, 8, 2000, 64, 0),
+                                           (20, 8, 4, 4096, 64, 0), (28, 12, 2, 4096, 64, 0), (4, 32, 8, 4096, 512, 0), (14, 14, 2, 4096, 64, 0), (11, 32, 8, 256, 256, 0),
+                                           (11, 32, 8, 300, 300, 1), (1, 4, 2, 8000, 128, 0), (16, 32, 8, 512, 512, 0),
+                                           (1, 4, 2, 512, 128, 0), (1, 4, 2, 4096, 4096, 0), (2, 32, 8, 4096, 256, 0), (3, 32, 8, 1600, 64, 0), (12, 16, 2, 4096, 64, 0),
+                                           (16, 16, 16, 4096, 64, 0), (24, 14, 2, 1600, 256, 0), (9, 32, 8, 100, 256, 0), (9, 32, 8, 200, 64, 0), (8, 32, 8, 256, 64, 0),
+                                           (1, 4, 2, 4000, 4000, 1), (4, 32, 8, 512, 256, 0), (8, 32, 8, 1000, 64, 0)):
+            h = context((L, H_q, H_kv, 64, 1, 4, 128))
+            launches()
+            rc = lib.proxykv_score_self(h, P, P, 1, N, P, None) if self else lib.proxykv_score(h, P, P, P, 1, N, N_q, 2048, P, None)
+            assert rc == 0
+            out.append(len(launches("f32_to_bf16_kernel")))
+    """)
+    assert out == [1] * 13 + [0] * 13
