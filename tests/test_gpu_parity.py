@@ -616,6 +616,59 @@ def test_score_of_heads_of_four_and_eight_query_blocks(N_q, d):
     _score_47_layers(N_q, 300, 1.0, d)
 
 
+@pytest.mark.parametrize("N", [1395, 1536])
+def test_score_of_whole_tiles_out_of_range(N):
+    """Heads of 64 in blocks of their own, logits of a standard deviation of 30: a column's sum leaves its range in many whole tiles, which are undone and
+    summed again with new references."""
+    _score_47_layers(257, N, 30.0, 64)
+
+
+@pytest.mark.parametrize("far", [11.0, 40.0])
+def test_score_of_keys_far_above_the_reference_in_a_middle_tile(far):
+    """Context keys that are `far` times a query, from the fourth tile on, in two tiles in a row and in the last whole one, and reconstruction keys like that in a
+    tile that every query of a block sees: the sum of a tile, begun while the one before was summed, exceeds 2^100 (11: about 2^127) or is infinite.
+    Max and sum forms; heads of 64, blocks of their own."""
+    L, H_q, H_kv, N_q, N, chunk = 48, 8, 2, 400, 1340, 300
+    g = torch.Generator().manual_seed(int(far))
+    q = torch.randn(L, H_q, N_q, 64, generator=g).bfloat16()
+    kc, kr = (torch.randn(L, H_kv, n, 64, generator=g).bfloat16() for n in (N, N_q))
+    for l in range(L):
+        for h in range(H_kv):
+            for at in (400, 530, 650, 1279) if l % 3 else (900, 901, 1024, 1339):
+                i = int(torch.randint(N_q, (1,), generator=g))
+                kc[l, h, at] = (far * q[l, 4 * h + (at + l) % 4, i].float()).bfloat16()
+            if l % 2:  # seen by the queries behind it in its chunk
+                kr[l, h, 130] = (far * q[l, 4 * h, 299].float()).bfloat16()
+    for reduce, code in (("max", pk.PROXYKV_REDUCE_MAX), ("sum", pk.PROXYKV_REDUCE_SUM)):
+        cfg = pk.make_config(L, H_q, H_kv, 64, 1, 4, 128)
+        cfg.reduce = code
+        ctx = pk.proxykv_create(cfg)
+        x = pk.proxykv_score(ctx, q.cuda(), kc.cuda(), kr.cuda(), chunk)
+        torch.cuda.synchronize()
+        assert_close(x, oracle.score(q, kc, kr, chunk, reduce=reduce), f"score {reduce}")
+        pk.proxykv_destroy(ctx)
+
+
+@pytest.mark.parametrize("far", [0.0, 11.0, 40.0])
+def test_causal_score_of_keys_far_above_the_reference(far):
+    """The causal form beyond 2048 tokens, whose whole tiles are the reconstruction's: the same for keys in the middle of the sequence, at its end and in its
+    first tile."""
+    L, H_q, H_kv, N = 6, 8, 2, 2222
+    g = torch.Generator().manual_seed(3)
+    q = torch.randn(L, H_q, N, 64, generator=g).bfloat16()
+    k = torch.randn(L, H_kv, N, 64, generator=g).bfloat16()
+    if far:
+        for l in range(L):
+            for h in range(H_kv):
+                for at in (700, 831, 1500, 2100) if l % 2 else (40, 1000, 1001, 2047):
+                    k[l, h, at] = (far * q[l, 4 * h + at % 4, int(torch.randint(at, N, (1,), generator=g))].float()).bfloat16()
+    ctx = pk.proxykv_create(pk.make_config(L, H_q, H_kv, 64, 1, 4, 128))
+    x = pk.proxykv_score_self(ctx, q.cuda(), k.cuda())
+    torch.cuda.synchronize()
+    assert_close(x, oracle.score_self(q, k), "score_self")
+    pk.proxykv_destroy(ctx)
+
+
 def _score_47_layers(N_q, N, scale, d=128):
     L, H_q, H_kv, chunk = 47, 8, 2, 200
     g = torch.Generator().manual_seed(N_q)
