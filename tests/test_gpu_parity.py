@@ -882,13 +882,13 @@ def test_mapper_of_other_sizes(d_ffn, c_mid, n_enc, L, N):
 
 
 def test_mapper_half_blocks_are_whole_blocks_bit_for_bit():
-    """26 layers of 600 tokens are two times 65 blocks in two lanes, the first 8 of them alone are 40 in one: either way halves, of which
-    each layer's last holds 24 rows.  (Whole blocks against halves: the next test.)"""
+    """40 layers of 600 tokens are two times 100 blocks in two lanes, more than these run as halves; the first 8 of them alone are 40 blocks in one
+    lane, which run as halves, of which each layer's last holds 24 rows."""
     y = []
-    for L in (26, 8):
+    for L in (40, 8):
         case = synth.scaled_case(synth.CASES["llama_8k"], name="halves", L_s=L, H_kv=2, H_q=2, L_l=L, H_l=4, N=600, N_q=1, chunk=1, n_planted=0)
         w = synth.make_mapper_weights(case.H_kv, case.H_l)
-        X = (torch.rand(26, case.H_kv, 600, generator=torch.Generator().manual_seed(77)) ** 8)[:L].contiguous()
+        X = (torch.rand(40, case.H_kv, 600, generator=torch.Generator().manual_seed(77)) ** 8)[:L].contiguous()
         ctx = _ctx(case, w)
         y.append(pk.proxykv_map(ctx, X.float().cuda())[:8].clone())
         torch.cuda.synchronize()
