@@ -218,8 +218,8 @@ __global__ __launch_bounds__(256, MINB) void score_lse_kernel(const In* __restri
   // PIPE (32-column tiles): the same, a unit of one column tile and 32 keys at a time: its 16 fma, its 16 exponentials with the next unit's
   // products between them, its 16 adds.  Two waves of a SIMD issue full-rate vector instructions (fma, add) in the same cycles, exponentials and
   // products hold it alone, so the waves are kept in step: exponentials go first, and a wave that has done its own finds the other one
-  // at its fma and adds too.  (Out of registers, cycles per logit and SIMD: 15.9 in the compiler's order, 12.5 so; with the products 19.3
-  // and 15.5.)  `ready`: units[0] holds the first unit's products; afterwards it holds those of `next`, the tile behind it.
+  // at its fma and adds too.  (Out of registers with the products, three waves per SIMD, ns per logit of a lane: 8.35 in the compiler's order and
+  // 6.91 so on zeros, 9.01 and 8.19 on random numbers, where power sets the clock: microbench/score_mix.hip.)  `ready`: units[0] holds the first unit's products; afterwards it holds those of `next`, the tile behind it.
   constexpr int UNITS = C::SUB * NT;
   Acc units[2];
   R keys;
