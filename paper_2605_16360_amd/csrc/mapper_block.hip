@@ -449,8 +449,9 @@ hipError_t launch_parts(BlockArgs a, int n_layers, int li, int n_enc, hipStream_
   if (li == n_enc) return launch<NT, false, true>(a, n_layers, stream);
   return launch<NT, false, false>(a, n_layers, stream);
 }
-// Up to this many blocks in flight (half the CUs) each is given to two workgroups.  A whole block's time is its matrix work, a half's
-// its weights' way from L2 (6.3 MB for each workgroup and layer, 64 bytes a clock and CU), and both take about the same: a quarter would win nothing.
+// Up to this many blocks in flight (half the CUs) each is given to two workgroups.  A whole block's time is its matrix work (131 us a middle launch
+// alone on the chip), a half's its weights' way from L2 (6.3 MB for each workgroup and layer, 42 us at 64 bytes a clock and CU) and its products (42 us)
+// in turn, with one wave per SIMD to do both: 88 us.  A quarter would read as many weights for half of the products.
 // us, halves / wholes: one layer of 5548 rows 821 / 1139, of 16 k 1132 / 1323, 16 of 500 665 / 978; with 129 .. 256 blocks some
 // CUs do two halves in turn, one layer of 26 k 1945 / 1738.
 // Two lanes' blocks are not in step: while one lane's launch ends or its attention runs, the other's halves have the chip, so up to three quarters

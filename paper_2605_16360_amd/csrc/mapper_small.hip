@@ -27,7 +27,8 @@ constexpr int kVmcnt0 = 0x0F70;  // s_waitcnt vmcnt(0)
 static_assert(kMapSmallRows < kWin + kStride + 1, "a layer of two windows is not for these kernels");
 
 // Tile of a block.  Blocks are dealt round-robin to the 8 XCDs; each XCD takes its own column tiles for all row tiles, so a
-// weight row is fetched into one L2 only (the weights outweigh the activations at these sizes).
+// weight row is fetched into one L2 only, and every activation into all of them.  (The weights outweigh the activations up to about 512 rows: the second FFN
+// product's are 2 MB either way there.)
 __device__ __forceinline__ void small_tile(int n_tiles, int& nt, int& mt) {
   const int b = (int)blockIdx.x;
   if (n_tiles % kXcds == 0) {

@@ -37,7 +37,7 @@ namespace {
 // Chains are handled in pairs (two column sub-tiles): the MFMAs of pair i are issued while the
 // VALU reduces the accumulators of pair i-1 (also across tile boundaries).
 // ---------------------------------------------------------------------------------------------
-// SPLIT (see score_lse.hip): neg_lse holds shares.  QSPLIT: the query tiles of a key block are dealt to q_splits workgroups, and
+// SPLIT (see score_lse.hpp): neg_lse holds shares.  QSPLIT: the query tiles of a key block are dealt to q_splits workgroups, and
 // each raises x (cleared by pass 1; probabilities are not negative, so their bits compare like integers).
 template <int D, int NCOL, bool SPLIT, bool QSPLIT>
 __global__ __launch_bounds__(256, D == 128 ? 1 : 2) void score_colmax_kernel(const uint16_t* __restrict__ q,
@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256, D == 64 && !(CAUSAL && SPLIT) ? 3 : 2) void sc
     fetch_next();
     store(1);
   }
-  __builtin_amdgcn_s_waitcnt(kVmcnt0);  // the resident keys have landed: no tile waits for them (see score_lse.hip)
+  __builtin_amdgcn_s_waitcnt(kVmcnt0);  // the resident keys have landed: no tile waits for them (see score_lse.hpp)
   if (total > 2) fetch_next();
 
   const bool idle = n0 + wave * NCOL * 32 >= N;  // a wave without a key helps with the tiles only

@@ -230,10 +230,12 @@ __device__ __forceinline__ void pick_digit(const uint32_t (&cnt)[kPer], uint32_t
 // digits of the key's distance from the row's smallest, a histogram per wave: 28 us of the kernel's 44 in the passes where scores change
 // sign, since the positive ones then share two or three bins.)  Wave w owns the scores [w * seg, (w + 1) * seg),
 // seg = 256 * ceil(length / 4096): a short row is one quad per thread in all waves, not 36 scores per thread in a few.
-// What bounds it is the vector ALU (1 us per instruction and 150 000 keys of a CU) and the first digit's adds, which run while the loads
-// arrive; later digits look at a quad's four keys with one comparison.
+// What bounds it is the vector ALU (1 us per instruction and 150 000 keys of a CU), the loads, and the first digit's adds, which go with the making of
+// the keys.  A wave waits for all of its loads before the first of them: there is a branch around each, so that the compiler cannot count
+// them.  Later digits look at a quad's four keys with one comparison.
 //
 // TEAM = false: a workgroup per row of up to kTopkRegMax scores (QUADS = 9 per thread).
+// (Its wait for the loads stands in front of the first barrier.)
 //
 // TEAM: longer rows, QUADS = 21, in parts, where all parts fit the chip at once, one workgroup per CU.  After counting a digit the workgroups
 // of a row meet: each leaves its histogram in scratch memory, waits until all have, and adds them up by itself.  112 rows of
@@ -354,7 +356,9 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
 
   // keys of this thread's scores; those at and past the end hold a key that no score has (the largest, +inf's, is 0xff800000)
   constexpr uint32_t kNoKey = 0xffffffffu;
-  // (of 21 quads per thread 16 stay in registers and five go to LDS: all in registers, 48 of the 128 were spilled)
+  // (Of 21 quads per thread 16 are meant for registers and five go to LDS; all 21 in registers, 48 of the 128 were spilled.  So it is 40 still: one quad, and
+  // what only the wait needs, lie in 20 bytes of scratch memory per lane, written once and read again for each later digit and the write.  112 rows of
+  // 170 000 scores write 32.2 MB, of which indices and histograms are 28.4.)
   constexpr int kRegQuads = QUADS < 16 ? QUADS : 16;
   __shared__ u32x4 stash[QUADS > kRegQuads ? (QUADS - kRegQuads) * kTopkThreads : 1];
   uint32_t reg_key[kRegQuads][4];
@@ -380,11 +384,11 @@ __global__ __launch_bounds__(kTopkThreads) void topk_reg_kernel(const float* __r
   }
 #pragma unroll
   for (int i = 0; i < 2048 * kRegCopies / 4 / kTopkThreads; ++i) reinterpret_cast<u32x4*>(hist)[tid + i * kTopkThreads] = u32x4{0, 0, 0, 0};
-  // (a barrier that does not wait for the scores)
+  // (a barrier that need not wait for the scores; in the team's kernel alone it does not)
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 
   uint32_t* mine = hist + (lane & (kRegCopies - 1));
-  // the first digit's adds go with the keys, as the loads arrive
+  // the first digit's adds go with the keys
 #pragma unroll
   for (int c = 0; c < QUADS; ++c)
     if (c < quads) {
